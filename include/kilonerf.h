@@ -226,12 +226,15 @@ int kn_composite_deltas(void *stream, const float *sigma /*dev*/, const float *r
                         const float bg[3] /*host*/, float *rgb_out /*dev R*3*/, float *T_out /*dev R, nullable*/,
                         int32_t *n_used /*dev R, nullable*/);
 
-/* The whole path (Sec. 3.1 Eq. 1-4, Sec. 3.2, Sec. 3.4): render R rays.  Samples are taken in
+/* The whole path (Sec. 3.1 Eq. 1-4, Sec. 3.2, Sec. 3.4): render R rays.
+ * 16-bit scenes (of up to 65536 networks) are rendered by one kernel behind a short set-up, and the call reads
+ * nothing back, unless `stats` is given or the context has a wave schedule or option of its own: then, and for
+ * fp32 scenes, samples are taken in
  * waves from near to far; rays whose transmittance fell below term_eps, or that ran out of
  * lattice points, drop out between waves.  The result per ray equals the sequential definition
  * (march, evaluate, blend, stop at T < term_eps) regardless of how waves are cut.
  * R*2^ceil(log2 K) must be <= 2^32, R times the slot budget per ray (kn_set_render_params; 128 unless set)
- * below 2^31, and R <= 2^26: KN_E_UNSUPPORTED beyond.  The call enqueues the first two waves without looking at their outcome
+ * below 2^31, and R <= 2^26: KN_E_UNSUPPORTED beyond.  With waves, the call enqueues the first two of them without looking at their outcome
  * (their shape is computed on the device) and reads the count of surviving rays on the host only to decide
  * about further waves; when it returns, the last wave has been enqueued but `stream` may still be running
  * (it does not wait at all when the slot budget guarantees that the second wave ends every ray and `stats`
@@ -307,7 +310,7 @@ typedef struct {
     double ms_cell;        /* point -> cell id (kn_eval_grouped only; fused into marching in kn_render) */
     double ms_march;       /* marching + empty-space skipping (kn_render: the per-wave marching kernel)  */
     double ms_bucket;      /* ordering by network: radix passes / grouping passes, offsets, tile list   */
-    double ms_mlp;         /* the fused grouped-MLP kernel                                             */
+    double ms_mlp;         /* the fused grouped-MLP kernel / kn_render's fused kernel                  */
     double ms_blend;       /* blending + early termination + live-ray compaction                       */
     int64_t mlp_launches;  /* launches of the grouped-MLP kernel                                       */
     int64_t mlp_samples;   /* samples those launches evaluated                                         */

@@ -14,7 +14,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkilonerf_hip.so")
 PEAKS_LIB = os.path.join(HERE, "libkn_peaks.so")
 PEAKS_SOURCE = "kn_peaks.hip"
-SOURCES = ["kn_api.hip", "kn_bucket.hip", "kn_group.hip", "kn_mlp_f32.hip", "kn_mlp_mfma.hip", "kn_render.hip", "kn_reorder.hip"]
+SOURCES = ["kn_api.hip", "kn_bucket.hip", "kn_fused.hip", "kn_group.hip", "kn_mlp_f32.hip", "kn_mlp_mfma.hip", "kn_render.hip", "kn_reorder.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-ffp-contract=off", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-mfma-vgpr-form=1",
          "-I", INCLUDE, "-I", CSRC]
@@ -23,8 +23,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-ffp-contract=o
 # The matrix-core MLP kernel uses the VALU "times two" output modifier in its double-angle recurrence; the
 # compiler only emits it with flushed fp32 denormals, without IEEE mode, and when signed zeros / NaNs need
 # no special care.  Only that file gets these flags; the index arithmetic elsewhere stays strict.
-PER_FILE_FLAGS = {"kn_mlp_mfma.hip": ["-fgpu-flush-denormals-to-zero", "-fno-signed-zeros", "-fno-honor-nans",
-                                      "-mno-amdgpu-ieee"]}
+_MLP16_FLAGS = ["-fgpu-flush-denormals-to-zero", "-fno-signed-zeros", "-fno-honor-nans", "-mno-amdgpu-ieee"]
+PER_FILE_FLAGS = {"kn_mlp_mfma.hip": _MLP16_FLAGS, "kn_fused.hip": _MLP16_FLAGS}
 
 
 def _compile(src: str) -> str:

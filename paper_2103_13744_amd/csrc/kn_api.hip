@@ -273,22 +273,34 @@ __global__ void k_pack_occupancy(const uint8_t *__restrict__ occ, int64_t n_vox,
     bits[w] = v;
 }
 
-// skip field, step 1: 0 for blocks of 4^3 voxels that contain an occupied voxel, 255 otherwise
-__global__ void k_skip_seed(const uint8_t *__restrict__ occ, int ox, int oy, int oz, int sx, int sy, int sz,
-                            uint8_t *__restrict__ dist)
+// One thread per block of 4^3 voxels: its 64 occupancy bits (bit 16 x + 4 y + z of the voxel (x, y, z) inside the block;
+// zero beyond the grid's end), and the seed of the skip field: 0 where a voxel is occupied, 255 otherwise.
+__global__ void k_pack_bricks(const uint8_t *__restrict__ occ, int ox, int oy, int oz, int sx, int sy, int sz,
+                              uint4 *__restrict__ bricks, uint8_t *__restrict__ dist)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= (int64_t)sx * sy * sz) return;
     const int cz = (int)(c % sz), cy = (int)((c / sz) % sy), cx = (int)(c / ((int64_t)sz * sy));
-    bool any = false;
-    for (int x = cx * KN_SKIP_BLOCK; x < min((cx + 1) * KN_SKIP_BLOCK, ox) && !any; ++x)
-        for (int y = cy * KN_SKIP_BLOCK; y < min((cy + 1) * KN_SKIP_BLOCK, oy) && !any; ++y)
-            for (int z = cz * KN_SKIP_BLOCK; z < min((cz + 1) * KN_SKIP_BLOCK, oz); ++z)
-                if (occ[((int64_t)x * oy + y) * oz + z] != 0) { any = true; break; }
-    dist[c] = any ? 0 : 255;
+    const bool words = (oz & 3) == 0 && ((uintptr_t)occ & 3) == 0; // (uniform) a row of four voxels is one aligned word
+    uint64_t bits = 0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int x = 4 * cx + r / 4, y = 4 * cy + r % 4;
+        if (x >= ox || y >= oy) continue;
+        const uint8_t *row = occ + ((int64_t)x * oy + y) * oz + 4 * cz;
+        if (words) {
+            const uint32_t w = *(const uint32_t *)row;
+#pragma unroll
+            for (int z = 0; z < 4; ++z) bits |= (uint64_t)(((w >> (8 * z)) & 0xffu) != 0u) << (4 * r + z);
+        } else {
+            for (int z = 0; z < 4 && 4 * cz + z < oz; ++z) bits |= (uint64_t)(row[z] != 0) << (4 * r + z);
+        }
+    }
+    bricks[c] = make_uint4((uint32_t)bits, (uint32_t)(bits >> 32), 0u, 0u);
+    dist[c] = bits ? 0 : 255;
 }
 
-// skip field, step 2 (repeated): one Jacobi sweep of d = min(d, 1 + min over the 26 neighbours);
+// skip field (repeated): one Jacobi sweep of d = min(d, 1 + min over the 26 neighbours);
 // after n sweeps every value <= n is the exact Chebyshev distance
 __global__ void k_skip_sweep(const uint8_t *__restrict__ in, int sx, int sy, int sz, uint8_t *__restrict__ out)
 {
@@ -303,10 +315,28 @@ __global__ void k_skip_sweep(const uint8_t *__restrict__ in, int sx, int sy, int
     out[c] = (uint8_t)min(best, 255);
 }
 
-__global__ void k_skip_cap(uint8_t *__restrict__ d, int64_t n)
+// skip field, last step: values capped; they and the block's network join the occupancy bits.  shift >= 0: a network cell
+// is 2^shift[a] >= 4 voxels wide along axis a, so a block lies inside one cell (else its points look their networks up).
+struct BrickNets {
+    const int32_t *cell_net;
+    int32_t shift[3], res1, res2;
+};
+__global__ void k_finish_bricks(uint8_t *__restrict__ d, int sx, int sy, int sz, BrickNets nets, uint4 *__restrict__ bricks)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < n && d[c] > KN_SKIP_MAX) d[c] = KN_SKIP_MAX;
+    if (c >= (int64_t)sx * sy * sz) return;
+    const uint8_t v = d[c] > KN_SKIP_MAX ? KN_SKIP_MAX : d[c];
+    d[c] = v;
+    uint4 b = bricks[c];
+    b.w = v;
+    if (nets.shift[0] >= 0) {
+        const int cz = (int)(c % sz), cy = (int)((c / sz) % sy), cx = (int)(c / ((int64_t)sz * sy));
+        const int32_t cell = ((4 * cx >> nets.shift[0]) * nets.res1 + (4 * cy >> nets.shift[1])) * nets.res2 + (4 * cz >> nets.shift[2]);
+        const int32_t net = kn_net_of_cell(nets.cell_net, cell);
+        b.z = (uint32_t)net;
+        if (net < 0) b.x = b.y = 0u; // a cell without a network is empty space
+    }
+    bricks[c] = b;
 }
 
 // zero the outputs of the points that fell outside the AABB (bucket N of the sorted list)
@@ -450,6 +480,7 @@ static SceneLayout scene_layout(const kn_scene_desc *d)
 }
 struct SceneBufs {
     int32_t *cell_net;
+    uint4 *bricks;
     uint32_t *occ_bits;
     uint8_t *skip_dist, *skip_tmp;
     char *packed_w;
@@ -459,6 +490,7 @@ static void carve_scene(KnCarver &c, const SceneLayout &l, SceneBufs &b)
     b = SceneBufs{};
     if (l.sparse) b.cell_net = c.carve<int32_t>(l.cells);
     if (l.has_occ) {
+        b.bricks = c.carve<uint4>(l.skip_cells);
         b.occ_bits = c.carve<uint32_t>(l.words);
         b.skip_dist = c.carve<uint8_t>(l.skip_cells);
         b.skip_tmp = c.carve<uint8_t>(l.skip_cells); // second buffer of the sweeps (unused afterwards)
@@ -507,6 +539,8 @@ extern "C" int kn_scene_create(kn_ctx *ctx, const kn_scene_desc *desc, void *str
     make_grid(desc->aabb_min, desc->aabb_max, desc->res, sc->net_grid);
     sc->has_occ = lay.has_occ;
     sc->packed_halfs_per_net = 0;
+    sc->brick_nets = false;
+    sc->net_shift[0] = sc->net_shift[1] = sc->net_shift[2] = -1;
     sc->skip_res[0] = sc->skip_res[1] = sc->skip_res[2] = 0;
     sc->own_buffer = nullptr;
     if (!buffer) {
@@ -521,6 +555,7 @@ extern "C" int kn_scene_create(kn_ctx *ctx, const kn_scene_desc *desc, void *str
     SceneBufs bufs;
     carve_scene(carver, lay, bufs);
     sc->cell_net = bufs.cell_net;
+    sc->bricks = bufs.bricks;
     sc->occ_bits = bufs.occ_bits;
     sc->skip_dist = bufs.skip_dist;
     sc->packed_w = bufs.packed_w;
@@ -536,20 +571,27 @@ extern "C" int kn_scene_create(kn_ctx *ctx, const kn_scene_desc *desc, void *str
         const int64_t vox = (int64_t)desc->occ_res[0] * desc->occ_res[1] * desc->occ_res[2];
         hipLaunchKernelGGL(k_pack_occupancy, dim3((unsigned)kn_div_up(lay.words, 256)), dim3(256), 0, st, desc->occupancy, vox,
                            sc->occ_bits);
-        if (hipGetLastError() != hipSuccess) rc = KN_E_HIP;
-        if (rc == KN_OK) { // skip field: seed, KN_SKIP_MAX sweeps (ping-pong), cap
+        { // blocks and skip field: seed, KN_SKIP_MAX sweeps (ping-pong), cap
             int sr[3];
             for (int a = 0; a < 3; ++a) sr[a] = sc->skip_res[a] = (int)kn_div_up(desc->occ_res[a], KN_SKIP_BLOCK);
             const int64_t cells = lay.skip_cells;
             const dim3 grid((unsigned)kn_div_up(cells, 256)), block(256);
-            hipLaunchKernelGGL(k_skip_seed, grid, block, 0, st, desc->occupancy, desc->occ_res[0], desc->occ_res[1],
-                               desc->occ_res[2], sr[0], sr[1], sr[2], sc->skip_dist);
+            hipLaunchKernelGGL(k_pack_bricks, grid, block, 0, st, desc->occupancy, desc->occ_res[0], desc->occ_res[1],
+                               desc->occ_res[2], sr[0], sr[1], sr[2], sc->bricks, sc->skip_dist);
             uint8_t *a = sc->skip_dist, *b = bufs.skip_tmp;
             for (int it = 0; it < KN_SKIP_MAX; ++it) { // even count: the result ends in skip_dist
                 hipLaunchKernelGGL(k_skip_sweep, grid, block, 0, st, a, sr[0], sr[1], sr[2], b);
                 uint8_t *t = a; a = b; b = t;
             }
-            hipLaunchKernelGGL(k_skip_cap, grid, block, 0, st, sc->skip_dist, cells);
+            BrickNets nets{sc->cell_net, {0, 0, 0}, sc->net_grid.res[1], sc->net_grid.res[2]};
+            sc->brick_nets = true;
+            for (int a_ = 0; a_ < 3; ++a_) {
+                sc->net_shift[a_] = kn_refinement(sc->net_grid.res[a_], desc->occ_res[a_]);
+                if (sc->net_shift[a_] < 2) sc->brick_nets = false;
+                nets.shift[a_] = sc->net_shift[a_];
+            }
+            if (!sc->brick_nets) nets.shift[0] = -1;
+            hipLaunchKernelGGL(k_finish_bricks, grid, block, 0, st, sc->skip_dist, sr[0], sr[1], sr[2], nets, sc->bricks);
             if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) rc = KN_E_HIP;
             if (rc == KN_OK) rc = content_box_from_skip_field(sc, cells);
         }

@@ -77,6 +77,11 @@ struct kn_ctx {
 // snapshot of the schedule and limits, taken under the mutex at the start of a call
 struct KnKnobs {
     int32_t first_wave_samples, slots_per_ray, wave_growth, group_fused_max, group_hash_slots;
+    bool is_default() const
+    {
+        return first_wave_samples == 0 && slots_per_ray == KN_DEFAULT_SLOTS && wave_growth == KN_DEFAULT_GROWTH &&
+               group_fused_max == KN_GROUP_FUSED_MAX_BINS && group_hash_slots == KN_GROUP_HASH_SLOTS_MAX;
+    }
 };
 KnKnobs kn_knobs(const kn_ctx *ctx);
 
@@ -90,7 +95,12 @@ struct kn_scene {
     KnGrid net_grid;
     KnGrid occ_grid;
     bool has_occ;
-    uint32_t *occ_bits;    // device, one bit per voxel, linear voxel index = bit index
+    // device, one entry per block of 4^3 voxels, in skip-field order: .x, .y = the block's occupancy bits (bit 16 x + 4 y + z
+    // of the 64; with brick_nets, none in a cell without a network), .z = its network (brick_nets), .w = its skip-field value
+    uint4 *bricks;
+    uint32_t *occ_bits; // device, a bit per voxel
+    bool brick_nets;       // every block lies inside one network cell
+    int32_t net_shift[3];  // per axis: the occupancy grid refines the network grid by 2^net_shift (-1: it does not)
     void *packed_w;        // device, matrix-core operand order (16-bit types only)
     int64_t packed_halfs_per_net;
     // Coarse skip field over the occupancy grid: one byte per block of KN_SKIP_BLOCK^3 voxels holding
@@ -103,6 +113,13 @@ struct kn_scene {
     KnGrid content_box;
     void *own_buffer;      // device memory the library allocated for the scene's data (nullptr: the caller lent it)
 };
+// q where fine = coarse * 2^q, else -1
+static inline int32_t kn_refinement(int32_t coarse, int32_t fine)
+{
+    for (int32_t q = 0; q < 16; ++q)
+        if ((int64_t)coarse << q == (int64_t)fine) return q;
+    return -1;
+}
 #define KN_SKIP_BLOCK 4
 #define KN_SKIP_MAX 32
 

@@ -1,0 +1,19 @@
+// Interface between kn_render (kn_render.hip), which prepares a frame, and the kernel that renders it (kn_fused.hip).
+#pragma once
+
+#include "kn_common.h"
+
+struct KnFusedJob {
+    const void *march; // MarchParams of the call (kn_march.h)
+    const float *rays_o, *rays_d;
+    int64_t R;
+    const int4 *list;  // live rays (ray, first lattice index, end of the clipped range, -), ctl[0] of them
+    int32_t *ctl;      // ctl[1] must be zero
+    float eps;
+    const float *bg;
+    float *rgb_out;
+    unsigned long long *counters; // nullable
+    bool strat;
+};
+bool kn_fused_supports(const kn_scene *sc);
+int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, hipEvent_t ev_start, hipEvent_t ev_stop);

@@ -1,0 +1,658 @@
+// The whole path behind one kernel (Sec. 3.4, Eq. 1-4, Eq. 7): marching with empty-space skipping, grouping by network,
+// the fused tiny MLP and blending with early ray termination, for scenes with 16-bit weights.
+//
+// A wavefront owns a pool of P rays (P a power of two, G = 64 / P lanes per ray) and works through them alone, without
+// workgroup barriers.  One round: every ray of the pool collects up to S kept samples (P * S slots of LDS per
+// wavefront); the samples are evaluated network by network; every ray blends its samples in order and ends, or stays
+// for the next round; free places are filled with the next rays of the live list.  Samples, results and encoded
+// directions never leave the LDS, a frame needs no slot buffers, no histogram and no host decision in the middle, and a
+// ray stops within S samples of its termination point.  Against the wave loop (march, group, evaluate and blend kernels
+// per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 66 us; 800x800 230 -> 204; 1080p,
+// width 64, 1430 -> 1078.
+//
+// What bounds it: vector-ALU issue (65 to 80 % of the slots while wavefronts are there: a march step of 256 points takes
+// about 350 instructions, a tile of 16 samples about 75), and the spread of the wavefronts' work: at 800x800 they are
+// busy for 103 us on average, the last one for 200.  Tried against that spread and slower: larger or smaller shares per
+// hand-out (32 rays 230 us, 64 rays 266; few rays each towards the end 213), the rays that are left re-dealt to all
+// wavefronts by a second launch (240), pools per workgroup instead of per wavefront (227), hand-out counters per part of
+// the list (217: neighbours in the list run at the same time, so that weights are found in the caches).
+//
+// The wavefronts of a SIMD are in different phases at different times, so the latency of the march runs under the
+// evaluation of the others.  Results are the bits of the wave loop (kn_render.hip): same lattice points, same operand
+// order in the networks (a sample's outputs do not depend on which samples share its tile), same recurrence per ray.
+#include "kn_common.h"
+#include "kn_fused.h"
+#include "kn_march.h"
+#include "kn_mlp_core.h"
+#include <hip/hip_ext.h>
+
+namespace {
+
+constexpr int FUSED_WAVES = 4;
+enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last rays of a workgroup are shared out
+
+// Slots per wavefront: what the LDS of a compute unit gives each of its 16 (width 32) / 8 (width 64) wavefronts after
+// the encoded directions (64 bytes per ray) and the index list (2 bytes per slot): 10,112 / 20,224 bytes.
+template <int H> struct Pool {
+    static constexpr int SLOTS = H == 32 ? 384 : 768, MAX_LG = H == 32 ? 5 : 6, RAYS = 1 << MAX_LG, NQ = SLOTS / KN_WAVE;
+    static constexpr int WAVES_PER_SIMD = H == 32 ? 3 : 2;
+    static constexpr int MIN_LG = 2, MAX_S = 32;
+};
+
+// lattice points a lane tests per step of the march: enough look-ups in flight, and the work per step that does not
+// depend on the number of points (ranks, frontier, skip field) is shared by four
+constexpr int STEPS = 4;
+
+// the grid that is marched through, for voxel_coords
+struct VoxelFast {
+    float inv[3], shift[3], guard, one_minus_guard, bmin[3], cell[3];
+    int32_t res[3];
+};
+
+struct FusedArgs {
+    MarchParams p;
+    VoxelFast vox, net; // the grid that is marched through, the network grid
+    const uint16_t *packed;
+    const float *rays_o, *rays_d;
+    const int4 *list;  // live rays: (ray, first lattice index, end of the clipped range, -)
+    int32_t *ctl;      // [0] = live rays, [1] = rays handed out beyond the wavefronts' first pools
+    float eps, bg[3];
+    float *rgb_out;
+    unsigned long long *counters; // nullable: [0] += samples evaluated, [1] += samples blended
+};
+
+// The arguments are read from the kernel's own argument segment where they are used: `opaque` hides where the pointer and
+// the lane number come from, so that neither arguments nor values derived from the lane number stay in registers across
+// the phases of a round (the evaluation has none to spare).
+typedef const __attribute__((address_space(4))) FusedArgs *ArgsPtr;
+__device__ __forceinline__ ArgsPtr opaque(ArgsPtr p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ int opaque(int lane)
+{
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// float -> floor as an integer, as the instruction defines it for every input: saturated, NaN -> 0
+__device__ __forceinline__ int32_t floor_int(float f)
+{
+    int32_t i;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(f));
+    return i;
+}
+__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c) { return (int32_t)(__umul24((uint32_t)a, (uint32_t)b) + (uint32_t)c); }
+
+// Eq. 6 per axis on the grid that is marched through: integer cell coordinates (any value outside [0, res) for points
+// outside).  u = x / cell - bmin / cell in one multiply-add differs from the quotient of Eq. 6 by less than `guard` (host:
+// voxel_fast); true where some u is that close to an integer: the caller then evaluates the divisions themselves.
+__device__ __forceinline__ bool voxel_coords(const VoxelFast &g, float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz)
+{
+    const float ux = fmaf(x, g.inv[0], g.shift[0]), uy = fmaf(y, g.inv[1], g.shift[1]), uz = fmaf(z, g.inv[2], g.shift[2]);
+    const float fx = __builtin_amdgcn_fractf(ux), fy = __builtin_amdgcn_fractf(uy), fz = __builtin_amdgcn_fractf(uz);
+    ix = floor_int(ux);
+    iy = floor_int(uy);
+    iz = floor_int(uz);
+    return (fminf(fminf(fx, fy), fz) <= g.guard) | (fmaxf(fmaxf(fx, fy), fz) >= g.one_minus_guard);
+}
+
+__device__ __forceinline__ void voxel_coords_exact(const VoxelFast &g, float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz)
+{
+    ix = floor_int((x - g.bmin[0]) / g.cell[0]);
+    iy = floor_int((y - g.bmin[1]) / g.cell[1]);
+    iz = floor_int((z - g.bmin[2]) / g.cell[2]);
+    __builtin_amdgcn_sched_barrier(0); // (the divisions of several points side by side would cost more registers than there are)
+}
+__device__ __forceinline__ bool inside(const VoxelFast &g, int32_t ix, int32_t iy, int32_t iz)
+{
+    return ((uint32_t)ix < (uint32_t)g.res[0]) & ((uint32_t)iy < (uint32_t)g.res[1]) & ((uint32_t)iz < (uint32_t)g.res[2]);
+}
+
+// LDS writes of the wavefront's lanes before, reads after
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int H, bool BF, bool WRAP, bool STRAT>
+__global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
+    __attribute__((amdgpu_waves_per_eu(Pool<H>::WAVES_PER_SIMD, Pool<H>::WAVES_PER_SIMD))) k_render_fused(FusedArgs args_by_value)
+{
+    using L = Lay<H>;
+    using Pl = Pool<H>;
+    constexpr int HT = L::HT, HK = L::HK, NBLK = L::NBLK, NQ = Pl::NQ;
+    __shared__ f4 s_slot[FUSED_WAVES][Pl::SLOTS];      // sample j of pool ray s at j * P + s: (x, y, z, density scale), then (r, g, b, alpha)
+    __shared__ u4 s_dir[FUSED_WAVES][Pl::RAYS * 4];    // gamma(d) of pool ray s in operand order
+    __shared__ f4 s_ray[FUSED_WAVES][Pl::RAYS * 2];    // (origin, jump scale), (direction, jump offset) of pool ray s
+    __shared__ uint16_t s_idx[FUSED_WAVES][Pl::SLOTS]; // the samples' networks, then the slots of the network at hand
+    // sharing of the last rays inside the workgroup (see share_rays): what each wavefront is doing, the number of rays it
+    // was given, and how many wavefronts are out of work
+    __shared__ int32_t s_state[FUSED_WAVES], s_given[FUSED_WAVES], s_idle;
+
+    const ArgsPtr args = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); // = &args_by_value
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
+    f4 *slots = s_slot[wave];
+    u4 *dirs = s_dir[wave];
+    f4 *rays = s_ray[wave];
+    uint16_t *idx = s_idx[wave];
+
+    const int n_live = args->ctl[0];
+    const int total_waves = gridDim.x * FUSED_WAVES;
+    // rays per pool: as many as give every wavefront one, up to the pool's size
+    int lgP = Pl::MIN_LG;
+    while (lgP < Pl::MAX_LG && ((int64_t)total_waves << lgP) < n_live) ++lgP;
+
+    // First pools: equal contiguous shares of the list's head; what lies beyond is handed out as places become free.
+    // Neighbouring rays cost alike, so the four wavefronts of a SIMD (wavefront v of the workgroups b, b + 256, ...) take
+    // shares from the four quarters of the list, and the four shares that lie side by side go to one compute unit.
+    const int b = blockIdx.x, quarter_blocks = gridDim.x >> 2;
+    int wid;
+    if ((gridDim.x & 3) == 0) {
+        const int j = b / quarter_blocks;
+        wid = ((wave + j) & 3) * gridDim.x + (b - j * quarter_blocks) * 4 + j;
+    } else {
+        wid = b * FUSED_WAVES + wave;
+    }
+    const int n_first = (int)min((int64_t)n_live, (int64_t)total_waves << lgP);
+    int at = __builtin_amdgcn_readfirstlane((int)((int64_t)wid * n_first / total_waves));
+    int end = __builtin_amdgcn_readfirstlane((int)((int64_t)(wid + 1) * n_first / total_waves));
+    bool more = n_live > n_first;
+    if (threadIdx.x < FUSED_WAVES) s_state[threadIdx.x] = BUSY;
+    if (threadIdx.x == 0) s_idle = 0;
+    __syncthreads();
+
+    int ray = -1, k = 0, k_hi = 0; // (the same in all lanes of a ray's group, like everything per ray below)
+    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+    long long evaluated = 0, blended = 0; // (uniform)
+
+    for (;;) {
+        bool moved = false;
+        if (at >= end && !more) {
+            // ---- The list is exhausted.  The rays that are left differ in cost (most end within two rounds, some take ten),
+            // and a wavefront with many long ones would run on alone: one that has run out of rays waits for a part of
+            // another wavefront's of its workgroup.  (LDS only; a waiting wavefront ends when all four are out of work.)
+            unsigned long long live = __ballot(ray >= 0) & (lgP == 6 ? ~0ull : (1ull << (1 << lgP)) - 1ull);
+            int n = __popcll(live);
+            const int ln = opaque(lane);
+            if (n == 0) {
+                if (ln == 0) {
+                    __hip_atomic_store(&s_state[wave], IDLE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __hip_atomic_fetch_add(&s_idle, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                int st;
+                for (;;) {
+                    st = __hip_atomic_load(&s_state[wave], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (__builtin_amdgcn_readfirstlane(st) == GIVEN) break;
+                    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_idle, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == FUSED_WAVES) break;
+                    __builtin_amdgcn_s_sleep(4);
+                }
+                if (__builtin_amdgcn_readfirstlane(st) != GIVEN) break; // everybody is out of work
+                n = __builtin_amdgcn_readfirstlane(s_given[wave]);
+                if (ln == 0) __hip_atomic_store(&s_state[wave], BUSY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                lgP = Pl::MAX_LG;
+                const int place = ln & ((1 << lgP) - 1);
+                if (place < n) {
+                    const f4 q0 = slots[2 * place], q1 = slots[2 * place + 1];
+                    ray = __float_as_int(q0[0]);
+                    k = __float_as_int(q0[1]);
+                    k_hi = __float_as_int(q0[2]);
+                    T = q0[3];
+                    c0 = q1[0];
+                    c1 = q1[1];
+                    c2 = q1[2];
+                }
+                live = (1ull << n) - 1ull; // (at most half a pool was given)
+                wave_sync();
+            } else if (n >= 2 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > 0) {
+                int to = -1;
+                if (ln == 0)
+                    for (int w = 1; w < FUSED_WAVES && to < 0; ++w) {
+                        int expect = IDLE;
+                        const int other = (wave + w) & (FUSED_WAVES - 1);
+                        if (__hip_atomic_compare_exchange_strong(&s_state[other], &expect, CLAIMED, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
+                                                                 __HIP_MEMORY_SCOPE_WORKGROUP)) {
+                            to = other;
+                            __hip_atomic_fetch_sub(&s_idle, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        }
+                    }
+                to = __builtin_amdgcn_readfirstlane(to);
+                if (to >= 0) { // the upper half of the live rays moves to wavefront `to`'s part of the LDS
+                    const int P = 1 << lgP, place = ln & (P - 1), keep = n - n / 2;
+                    const int rank = __popcll(live & ((1ull << place) - 1ull)) - keep;
+                    const bool gives = ray >= 0 && rank >= 0;
+                    if (gives && ln < P) {
+                        s_slot[to][2 * rank] = (f4){__int_as_float(ray), __int_as_float(k), __int_as_float(k_hi), T};
+                        s_slot[to][2 * rank + 1] = (f4){c0, c1, c2, 0.0f};
+                    }
+                    if (gives) ray = -1;
+                    if (ln == 0) {
+                        s_given[to] = n / 2;
+                        // (the LDS is written in order: the rays are there before the state says so)
+                        __hip_atomic_store(&s_state[to], GIVEN, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    n = keep;
+                    live = __ballot(ray >= 0) & (lgP == 6 ? ~0ull : (1ull << P) - 1ull);
+                }
+            }
+            // ---- the rays that are left move together, so that each gets more lanes and more slots
+            int lg = lgP;
+            while (lg > Pl::MIN_LG && n <= (1 << (lg - 1))) --lg;
+            if (lg < lgP) {
+                if ((live >> ln) & 1ull) idx[__popcll(live & ((1ull << ln) - 1ull))] = (uint16_t)ln; // (a leading lane is its place's number)
+                wave_sync();
+                const int place = ln & ((1 << lg) - 1);
+                const int from = place < n ? (int)idx[place] : 0;
+                ray = __shfl(ray, from, KN_WAVE);
+                k = __shfl(k, from, KN_WAVE);
+                k_hi = __shfl(k_hi, from, KN_WAVE);
+                T = __shfl(T, from, KN_WAVE);
+                c0 = __shfl(c0, from, KN_WAVE);
+                c1 = __shfl(c1, from, KN_WAVE);
+                c2 = __shfl(c2, from, KN_WAVE);
+                if (place >= n) ray = -1;
+                moved = true;
+                lgP = lg;
+                wave_sync();
+            }
+        }
+        const int P = 1 << lgP, G = KN_WAVE >> lgP;
+        const int S_max = min(Pl::SLOTS >> lgP, Pl::MAX_S);
+        const unsigned long long firsts = lgP == 6 ? ~0ull : (1ull << P) - 1ull; // lanes that lead a ray's group
+        int cnt = 0;
+        {
+            const ArgsPtr a = opaque(args);
+            const int ln = opaque(lane), slot = ln & (P - 1), gl = ln >> lgP;
+            // ---- fill the free places of the pool
+            const unsigned long long free_places = __ballot(ray < 0) & firsts;
+            const int n_free = __popcll(free_places);
+            bool fresh = moved;
+            if (n_free > 0) {
+                if (at >= end && more) {
+                    int base = 0;
+                    if (ln == 0) base = atomicAdd(&a->ctl[1], n_free);
+                    at = n_first + __builtin_amdgcn_readfirstlane(base);
+                    end = min(at + n_free, n_live);
+                    more = at + n_free < n_live;
+                }
+                const int avail = end - at;
+                if (avail > 0) {
+                    const int rank = __popcll(free_places & ((1ull << slot) - 1ull));
+                    if (ray < 0 && rank < avail) {
+                        const int4 e = a->list[at + rank];
+                        ray = e.x;
+                        k = e.y;
+                        k_hi = e.z;
+                        T = 1.0f;
+                        c0 = c1 = c2 = 0.0f;
+                        fresh = true;
+                    }
+                    at += min(n_free, avail);
+                }
+            }
+            if (__ballot(ray >= 0) == 0ull) continue; // (only where the hand-out counter gave nothing any more)
+            if (ray >= 0 && fresh && gl == 0) { // a ray takes its place: what the rounds need of it goes to the LDS
+                float o[3], d[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    o[c] = a->rays_o[3 * (int64_t)ray + c];
+                    d[c] = a->rays_d[3 * (int64_t)ray + c];
+                }
+                const SkipJump sj(*(const MarchParams *)&a->p, o, d, STRAT);
+                rays[2 * slot] = (f4){o[0], o[1], o[2], sj.use ? sj.a : 0.0f};
+                rays[2 * slot + 1] = (f4){d[0], d[1], d[2], sj.use ? sj.b : 1e30f}; // (no jumps)
+                kn_enc::u4 q[4];
+                kn_enc::dir_slots<BF>(d[0], d[1], d[2], q);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dirs[4 * slot + i] = q[i];
+            }
+            wave_sync();
+
+            // ---- march: up to S kept samples per ray.  A step tests G * STEPS consecutive lattice points, STEPS per lane,
+            // with all look-ups of the step in flight together; the skip field is asked at each lane's last point only.
+            // What the loop reads of the arguments is copied out in front of it (scalar registers): a scalar load inside costs
+            // its latency per step, and there were twenty of them (7,200 cycles per step, 1,300 without).
+            if (ray >= 0) {
+                const VoxelFast vf = *(const VoxelFast *)&a->vox;
+                const float t_near = a->p.t_near, step = a->p.step;
+                const uint4 *__restrict__ const bricks = a->p.bricks;
+                const int32_t *__restrict__ const cell_net = a->p.cell_net;
+                const uint32_t last_block = (uint32_t)(a->p.skip_res[0] * a->p.skip_res[1] * a->p.skip_res[2] - 1); // (points outside look up any block)
+                const int32_t skip1 = a->p.skip_res[1], skip2 = a->p.skip_res[2];
+                const int32_t has_occ = a->p.has_occ, brick_nets = a->p.brick_nets;
+                const int n_lanes = __popcll(__ballot(true));
+                const f4 ro = rays[2 * slot], rd = rays[2 * slot + 1];
+                const int S = S_max;
+                const uint32_t ray_key = kn_mix32(a->p.seed_key + (uint32_t)ray);
+                // The march of a round ends when fewer than half of the pool's rays still collect: the others would only wait.
+                while (2 * __popcll(__ballot(k < k_hi && cnt < S)) >= n_lanes) {
+                  if (k < k_hi && cnt < S) {
+                    const int k0 = k + gl * STEPS;
+                    float x[STEPS], y[STEPS], z[STEPS];
+                    int32_t ix[STEPS], iy[STEPS], iz[STEPS], net[STEPS];
+                    bool in[STEPS], close = false;
+#pragma unroll
+                    for (int c = 0; c < STEPS; ++c) {
+                        kn_lattice_point<STRAT>(ro[0], ro[1], ro[2], rd[0], rd[1], rd[2], t_near, step, k0 + c, x[c], y[c], z[c], ray_key);
+                        close |= voxel_coords(vf, x[c], y[c], z[c], ix[c], iy[c], iz[c]);
+                    }
+                    if (close) { // some point within rounding of a voxel's face: the divisions themselves
+#pragma unroll
+                        for (int c = 0; c < STEPS; ++c) voxel_coords_exact(vf, x[c], y[c], z[c], ix[c], iy[c], iz[c]);
+                    }
+#pragma unroll
+                    for (int c = 0; c < STEPS; ++c) // (saturated integers: whatever the coordinates are, the look-ups stay inside)
+                        in[c] = inside(vf, ix[c], iy[c], iz[c]) & (k0 + c < k_hi);
+                    int32_t dist = 0;
+                    if (has_occ) { // (uniform)
+                        // occupancy bits, network and skip-field value of each point's block: one load per point, all in flight together
+                        uint4 brick[STEPS];
+#pragma unroll
+                        for (int c = 0; c < STEPS; ++c)
+                            brick[c] = bricks[min((uint32_t)mad24(mad24(ix[c] >> 2, skip1, iy[c] >> 2), skip2, iz[c] >> 2), last_block)];
+                        dist = in[STEPS - 1] ? (int32_t)brick[STEPS - 1].w : 0;
+#pragma unroll
+                        for (int c = 0; c < STEPS; ++c) {
+                            const uint64_t bits = (uint64_t)brick[c].y << 32 | brick[c].x;
+                            in[c] = in[c] & (((bits >> (((ix[c] & 3) << 4) | ((iy[c] & 3) << 2) | (iz[c] & 3))) & 1ull) != 0ull);
+                            net[c] = (int32_t)brick[c].z;
+                        }
+                    }
+                    if (!brick_nets) { // (uniform) a block may lie in several cells, or there is no occupancy grid
+                        const VoxelFast vn = *(const VoxelFast *)&a->net;
+                        bool close_net = false;
+#pragma unroll
+                        for (int c = 0; c < STEPS; ++c) {
+                            int32_t nx, ny, nz;
+                            close_net |= voxel_coords(vn, x[c], y[c], z[c], nx, ny, nz);
+                            in[c] = in[c] & inside(vn, nx, ny, nz);
+                            net[c] = mad24(mad24(nx, vn.res[1], ny), vn.res[2], nz);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (close_net) {
+#pragma unroll
+                            for (int c = 0; c < STEPS; ++c) {
+                                int32_t nx, ny, nz;
+                                voxel_coords_exact(vn, x[c], y[c], z[c], nx, ny, nz);
+                                in[c] = in[c] & inside(vn, nx, ny, nz);
+                                net[c] = mad24(mad24(nx, vn.res[1], ny), vn.res[2], nz);
+                            }
+                        }
+                        if (cell_net) { // (uniform) a sparse grid: the cell's network, or none
+                            const uint32_t last_cell = (uint32_t)(vn.res[0] * vn.res[1] * vn.res[2] - 1);
+#pragma unroll
+                            for (int c = 0; c < STEPS; ++c) net[c] = cell_net[min((uint32_t)net[c], last_cell)];
+#pragma unroll
+                            for (int c = 0; c < STEPS; ++c) in[c] = in[c] & (net[c] >= 0);
+                        }
+                    }
+                    // ranks in order along the ray: kept points of the lanes in front of this one in the group, then this lane's
+                    int own = 0;
+#pragma unroll
+                    for (int c = 0; c < STEPS; ++c) own += in[c] ? 1 : 0;
+                    int incl = own;
+                    for (int w = P; w < KN_WAVE; w <<= 1) {
+                        const int v = __shfl_up(incl, w, KN_WAVE);
+                        if (ln >= w + slot) incl += v; // (lane ln - w belongs to the group as well)
+                    }
+                    const int total = __shfl(incl, slot + KN_WAVE - P, KN_WAVE);
+                    int rank = cnt + incl - own;
+                    int stop = 0x7fffffff; // first kept point that does not fit: where the next round resumes
+#pragma unroll
+                    for (int c = 0; c < STEPS; ++c) {
+                        if (in[c] & (rank < S)) {
+                            const int at_slot = (rank << lgP) + slot;
+                            float dscale = 1.0f;
+                            if constexpr (STRAT)
+                                dscale = (kn_lattice_t<true>(t_near, step, k0 + c + 1, ray_key) - kn_lattice_t<true>(t_near, step, k0 + c, ray_key)) / step;
+                            slots[at_slot] = (f4){x[c], y[c], z[c], dscale};
+                            idx[at_slot] = (uint16_t)net[c];
+                        }
+                        stop = (in[c] & (rank == S)) ? k0 + c : stop;
+                        rank += in[c] ? 1 : 0;
+                    }
+                    // the frontier: every index of this step was tested; the farthest jump extends the known-empty range
+                    const bool over = cnt + total > S; // (uniform in the group)
+                    int32_t v = over ? -stop : (dist >= 2 ? k0 + STEPS + (int32_t)fmaxf(floorf((float)(dist - 1) * ro[3] - rd[3]), 0.0f) : 0); // (SkipJump::jump)
+                    for (int w = P; w < KN_WAVE; w <<= 1) v = max(v, __shfl_xor(v, w, KN_WAVE));
+                    k = over ? -v : max(k + G * STEPS, v);
+                    cnt = min(cnt + total, S);
+                  }
+                }
+            }
+        }
+        wave_sync();
+
+        // ---- evaluate: one network after the other
+        {
+            const ArgsPtr a = opaque(args);
+            const int ln = opaque(lane), n = ln & 15, g = ln >> 4;
+            const unsigned m3 = (g == 3) ? 0xffffffffu : 0u;
+            const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+            // which word of a sample's slot each of a lane's three restart angles comes from, and its scale (see k_mlp_mfma)
+            const int wo0 = g < 3 ? g : 0, wo1 = g < 3 ? g : 1, wo2 = g < 3 ? g : 2;
+            const float f0 = g < 3 ? INV_2PI : 256.0f * INV_2PI, f1 = g < 3 ? 4.0f * INV_2PI : 256.0f * INV_2PI,
+                        f2_ = g < 3 ? 16.0f * INV_2PI : 256.0f * INV_2PI;
+            const float step = a->p.step;
+            // the networks of the slots a lane looks after, ln + 64 q (they are its own ray's)
+            uint32_t nq[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) nq[q] = (ln >> lgP) + q * G < cnt ? (uint32_t)idx[ln + KN_WAVE * q] : 0xffffffffu;
+            __builtin_amdgcn_wave_barrier();
+            for (;;) {
+                uint32_t mine = 0xffffffffu;
+#pragma unroll
+                for (int q = NQ - 1; q >= 0; --q) mine = nq[q] != 0xffffffffu ? nq[q] : mine;
+                const unsigned long long pending = __ballot(mine != 0xffffffffu);
+                if (pending == 0ull) break;
+                const int32_t sel = __builtin_amdgcn_readlane((int)mine, (int)__builtin_ctzll(pending));
+                // (weights are not kept across rounds: the march needs the registers)
+                u4 areg[NBLK], a_out[HK];
+                f4 bias2[HT], bias_out;
+                const u4 *__restrict__ wp = (const u4 *)(a->packed + (int64_t)sel * L::HALFS);
+#pragma unroll
+                for (int b = 0; b < NBLK; ++b) areg[b] = wp[b * KN_WAVE + ln];
+                const float *__restrict__ tail = (const float *)(wp + NBLK * KN_WAVE);
+#pragma unroll
+                for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
+                bias_out = *(const f4 *)(tail + H);
+                int c = 0;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const bool hit = nq[q] == (uint32_t)sel;
+                    const unsigned long long b = __ballot(hit);
+                    if (hit) {
+                        idx[c + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u))] = (uint16_t)(ln + KN_WAVE * q);
+                        nq[q] = 0xffffffffu;
+                    }
+                    c += __popcll(b);
+                }
+                wave_sync();
+                // density row and colour rows side by side (they are disjoint rows, repeated with period four: every lane group
+                // computes the four values of a sample, and group u keeps those of sample tile u)
+#pragma unroll
+                for (int kb = 0; kb < HK; ++kb) a_out[kb] = areg[L::LS + kb] | areg[L::L5 + kb];
+                for (int t0 = 0; t0 < c; t0 += KN_WAVE) {
+                    const int len = min(KN_WAVE, c - t0);
+                    f4 out = zero4; // pre-activations (r, g, b, sigma) of sample ln of the tile
+                    auto sample_tile = [&](int u) {
+                        f4 o_sig = bias_out, o_col = bias_out;
+                        const int i = idx[min(t0 + 16 * u + n, c - 1)];
+                        const float *sp = (const float *)(slots + i);
+                        const float v0 = sp[wo0], v1 = sp[wo1], v2 = sp[wo2];
+                        const f4 ang = {v0 * f0, v1 * f1, v2 * f2_, 0.0f};
+                        const u4 ident = {pk<BF>(v0, v1), pk<BF>(v2, 1.0f), 0u, 0u}; // (group 3: v0..v2 are x, y, z)
+                        u4 Bx[2];
+                        encode_position<BF, WRAP>(ang, ident, m3, Bx);
+                        const u4 Bd = dirs[4 * (i & (P - 1)) + g];
+                        f4 acc[HT];
+                        u4 Bh[HK];
+#pragma unroll
+                        for (int t = 0; t < HT; ++t) {
+                            acc[t] = mfma<BF>(areg[L::L1 + 2 * t], Bx[0], zero4);
+                            acc[t] = mfma<BF>(areg[L::L1 + 2 * t + 1], Bx[1], acc[t]);
+                        }
+                        pack_acts<H, BF, true>(acc, Bh);
+#pragma unroll
+                        for (int t = 0; t < HT; ++t) {
+                            acc[t] = bias2[t];
+#pragma unroll
+                            for (int kb = 0; kb < HK; ++kb) acc[t] = mfma<BF>(areg[L::L2 + t * HK + kb], Bh[kb], acc[t]);
+                        }
+                        pack_acts<H, BF, true>(acc, Bh);
+#pragma unroll
+                        for (int kb = 0; kb < HK; ++kb) o_sig = mfma<BF>(a_out[kb], Bh[kb], o_sig);
+#pragma unroll
+                        for (int t = 0; t < HT; ++t) {
+                            acc[t] = mfma<BF>(areg[L::L4 + t * (HK + 1) + HK], Bd, zero4);
+#pragma unroll
+                            for (int kb = 0; kb < HK; ++kb) acc[t] = mfma<BF>(areg[L::L4 + t * (HK + 1) + kb], Bh[kb], acc[t]);
+                        }
+                        pack_acts<H, BF, true>(acc, Bh);
+#pragma unroll
+                        for (int kb = 0; kb < HK; ++kb) o_col = mfma<BF>(a_out[kb], Bh[kb], o_col);
+                        out = g == u ? (f4){o_col[0], o_col[1], o_col[2], o_sig[3]} : out;
+                    };
+                    // (two sample tiles side by side wherever two are there; uniform branches)
+                    if (len > 16) { sample_tile(0); sample_tile(1); }
+                    else sample_tile(0);
+                    if (len > 48) { sample_tile(2); sample_tile(3); }
+                    else if (len > 32) sample_tile(2);
+                    if (ln < len) { // lane l holds sample l of the tile; its result takes the place of its position
+                        const int i = idx[t0 + ln];
+                        float sg = fmaxf(out[3], 0.0f);
+                        if constexpr (STRAT) sg *= slots[i][3];
+                        f4 res;
+#pragma unroll
+                        for (int q = 0; q < 3; ++q)
+                            res[q] = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * out[q]));
+                        res[3] = 1.0f - expf(-sg * step); // alpha (Eq. 4)
+                        slots[i] = res;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        wave_sync();
+
+        // ---- blend (Eq. 2-4): the sequential recurrence, the same in all lanes of a ray's group
+        {
+            const ArgsPtr a = opaque(args);
+            const int ln = opaque(lane), slot = ln & (P - 1), gl = ln >> lgP;
+            const float eps = a->eps;
+            int used = 0;
+            if (ray >= 0) {
+                bool dead = false;
+                for (int j = 0; j < cnt && !dead; ++j) {
+                    const f4 q = slots[(j << lgP) + slot];
+                    const float wgt = T * q[3];
+                    c0 = fmaf(wgt, q[0], c0);
+                    c1 = fmaf(wgt, q[1], c1);
+                    c2 = fmaf(wgt, q[2], c2);
+                    T *= (1.0f - q[3]);
+                    ++used;
+                    dead = eps > 0.0f && T < eps;
+                }
+                if (dead || k >= k_hi) {
+                    if (gl == 0) {
+                        float *px = a->rgb_out + 3 * (int64_t)ray;
+                        px[0] = fmaf(T, a->bg[0], c0);
+                        px[1] = fmaf(T, a->bg[1], c1);
+                        px[2] = fmaf(T, a->bg[2], c2);
+                    }
+                    ray = -1;
+                }
+            }
+            if (a->counters) { // (uniform)
+                evaluated += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(gl == 0 ? cnt : 0), KN_WAVE - 1);
+                blended += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(gl == 0 ? used : 0), KN_WAVE - 1);
+            }
+        }
+        __builtin_amdgcn_wave_barrier(); // the slots are rewritten by the next round
+    }
+    if (args->counters && lane == 0) {
+        atomicAdd(&args->counters[0], (unsigned long long)evaluated);
+        atomicAdd(&args->counters[1], (unsigned long long)blended);
+    }
+}
+
+} // namespace
+
+// u = fma(x, fl(1/cell), fl(-bmin * fl(1/cell))) against fl(fl(x - bmin) / cell): with A = max(|bmin|, |bmax|) / cell, the
+// roundings of 1/cell, of the product and of u amount to 2^-24 (3 A + res), those of Eq. 6 to 2^-23 res, for every x
+// inside the box; 2e-7 (A + res + 1) is above their sum.
+static VoxelFast voxel_fast(const KnGrid &g)
+{
+    VoxelFast v;
+    v.guard = 0.0f;
+    for (int a = 0; a < 3; ++a) {
+        v.bmin[a] = g.bmin[a];
+        v.cell[a] = g.cell[a];
+        v.res[a] = g.res[a];
+        v.inv[a] = 1.0f / g.cell[a];
+        v.shift[a] = -g.bmin[a] * v.inv[a];
+        const float reach = fmaxf(fabsf(g.bmin[a]), fabsf(g.bmin[a] + g.cell[a] * (float)g.res[a]));
+        v.guard = fmaxf(v.guard, 2e-7f * (reach * v.inv[a] + (float)g.res[a] + 1.0f) + 1e-30f);
+    }
+    v.one_minus_guard = 1.0f - v.guard;
+    return v;
+}
+
+// The kernel's voxel, block and cell numbers are formed with 24-bit multiplications, and it keeps a sample's network in
+// 16 bits.
+bool kn_fused_supports(const kn_scene *sc)
+{
+    if (sc->desc.wdtype == KN_F32 || sc->N > 65536) return false;
+    auto fits = [](const int32_t r[3]) {
+        constexpr int64_t lim = 1ll << 24;
+        return (int64_t)r[0] * r[1] <= lim && r[0] < lim && r[1] < lim && r[2] < lim;
+    };
+    return fits(sc->net_grid.res) && (!sc->has_occ || fits(sc->skip_res));
+}
+
+int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    const int H = sc->desc.hidden;
+    const bool bf = sc->desc.wdtype == KN_BF16;
+    FusedArgs a;
+    a.p = *(const MarchParams *)job.march;
+    a.net = voxel_fast(a.p.net);
+    a.vox = voxel_fast(a.p.occ);
+    a.packed = (const uint16_t *)sc->packed_w;
+    a.rays_o = job.rays_o;
+    a.rays_d = job.rays_d;
+    a.list = job.list;
+    a.ctl = job.ctl;
+    a.eps = job.eps;
+    for (int c = 0; c < 3; ++c) a.bg[c] = job.bg[c];
+    a.rgb_out = job.rgb_out;
+    a.counters = job.counters;
+    float reach = 0.0f; // (see the launch of k_mlp_mfma)
+    for (int c = 0; c < 3; ++c) reach = fmaxf(reach, fmaxf(fabsf(sc->desc.aabb_min[c]), fabsf(sc->desc.aabb_max[c])));
+    const bool wrap = !(reach * (256.0f * INV_2PI) < 250.0f);
+    // one workgroup per compute unit and resident wavefront of a SIMD; fewer where there are fewer than four rays for each
+    // of their wavefronts
+    int64_t blocks = kn_div_up(job.R, FUSED_WAVES << Pool<32>::MIN_LG);
+    const int64_t fill = 256 * (H == 32 ? Pool<32>::WAVES_PER_SIMD : Pool<64>::WAVES_PER_SIMD);
+    if (blocks > fill) blocks = fill;
+    using Fn = decltype(&k_render_fused<32, false, false, false>);
+    static const Fn table[2][2][2][2] = {
+        {{{k_render_fused<32, false, false, false>, k_render_fused<32, false, false, true>},
+          {k_render_fused<32, false, true, false>, k_render_fused<32, false, true, true>}},
+         {{k_render_fused<32, true, false, false>, k_render_fused<32, true, false, true>},
+          {k_render_fused<32, true, true, false>, k_render_fused<32, true, true, true>}}},
+        {{{k_render_fused<64, false, false, false>, k_render_fused<64, false, false, true>},
+          {k_render_fused<64, false, true, false>, k_render_fused<64, false, true, true>}},
+         {{k_render_fused<64, true, false, false>, k_render_fused<64, true, false, true>},
+          {k_render_fused<64, true, true, false>, k_render_fused<64, true, true, true>}}}};
+    if (H != 32 && H != 64) return KN_E_UNSUPPORTED;
+    const Fn kernel = table[H == 64][bf][wrap][job.strat ? 1 : 0];
+    const dim3 grid((unsigned)blocks), block(FUSED_WAVES * KN_WAVE);
+    if (ev_start && ev_stop) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev_start, ev_stop, 0, a);
+    else hipLaunchKernelGGL(kernel, grid, block, 0, st, a);
+    KN_CHECK_LAUNCH();
+    return KN_OK;
+}

@@ -45,46 +45,15 @@
 // to revolutions per restart frequency, so that each lane group reads exactly the operands of its
 // role.
 #include "kn_common.h"
-#include "kn_dir_encode.h"
+#include "kn_mlp_core.h"
 #include <hip/hip_ext.h>
 #include "kn_mlp_shared.h"
 #include "kn_probe.h"
 
 namespace {
 
-using kn_enc::double_angle;
-using kn_enc::INV_2PI;
-using kn_enc::pk;
-using kn_enc::sincos_rev;
-
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-typedef short s2 __attribute__((ext_vector_type(2)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef unsigned u4 __attribute__((ext_vector_type(4)));
-
 constexpr int MLP_WAVES = 4;     // wavefronts per workgroup (one per SIMD of a compute unit)
 constexpr int MLP_TILE_LEN = 64; // one chunk: the unit in which work is dealt out to the wavefronts
-
-template <int H> struct Lay {
-    static constexpr int HT = H / 16, HK = H / 32;
-    static constexpr int L1 = 0;                          // (t, kb) -> L1 + 2t + kb
-    static constexpr int L2 = L1 + 2 * HT;                // (t, kb) -> L2 + t*HK + kb
-    static constexpr int LS = L2 + HT * HK;               // density row of layer 3, (kb)
-    static constexpr int L4 = LS + HK;                    // (t, kb) -> L4 + t*(HK+1) + kb; kb < HK: h2 through the folded
-                                                          // feature layer, kb = HK: gamma(d)
-    static constexpr int L5 = L4 + HT * (HK + 1);         // colour rows, (kb)
-    static constexpr int NBLK = L5 + HK;
-    static constexpr int TAIL_FLOATS = H + 4;             // b2[H], b5[3], b3 density
-    static constexpr int HALFS = NBLK * 512 + TAIL_FLOATS * 2;
-    // canonical offsets
-    static constexpr int oW1 = 0, ob1 = 63 * H, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H,
-                         ob3 = oW3 + H * (H + 1), oW4 = ob3 + H + 1, ob4 = oW4 + (H + 27) * H, oW5 = ob4 + H,
-                         ob5 = oW5 + 3 * H;
-};
 
 __host__ __device__ inline int hid_feat(int kb, int g, int j) { return 16 * (2 * kb + j / 4) + 4 * g + j % 4; }
 
@@ -198,69 +167,6 @@ __global__ void k_pack_weights(const uint16_t *__restrict__ w, int64_t P, int32_
 __global__ void k_clear_flag(int32_t *flag) { *flag = 0; }
 
 // ---------------------------------------------------------------------------------------------
-template <bool BF> __device__ __forceinline__ f4 mfma(u4 a, u4 b, f4 c)
-{
-    if constexpr (BF)
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
-}
-
-// ReLU on two packed 16-bit floats: as signed 16-bit integers every negative float is negative
-__device__ __forceinline__ unsigned relu2(unsigned v)
-{
-    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(s2, v), (s2){0, 0}));
-}
-
-// accumulators of one layer (HT tiles) -> B operands of the next (HK blocks)
-template <int H, bool BF, bool RELU> __device__ __forceinline__ void pack_acts(const f4 *acc, u4 *B)
-{
-#pragma unroll
-    for (int kb = 0; kb < H / 32; ++kb) {
-        unsigned r0 = pk<BF>(acc[2 * kb][0], acc[2 * kb][1]);
-        unsigned r1 = pk<BF>(acc[2 * kb][2], acc[2 * kb][3]);
-        unsigned r2 = pk<BF>(acc[2 * kb + 1][0], acc[2 * kb + 1][1]);
-        unsigned r3 = pk<BF>(acc[2 * kb + 1][2], acc[2 * kb + 1][3]);
-        if (RELU) { r0 = relu2(r0); r1 = relu2(r1); r2 = relu2(r2); r3 = relu2(r3); }
-        B[kb] = (u4){r0, r1, r2, r3};
-    }
-}
-
-// B operands of layer 1 for one lane: gamma(x) slots of lane group g (see "Slot order").  ang[0..2]: the lane's three
-// restart angles in revolutions; ident[0..1]: the packed pairs (x, y), (z, 1) that sit in group 3's last slots.
-template <bool BF, bool WRAP> __device__ __forceinline__ void encode_position(f4 ang, u4 ident, unsigned m3, u4 (&Bx)[2])
-{
-    // s[q] = sin, m[q] = cos of the q-th angle of this lane
-    float s[8], m[8];
-    sincos_rev<WRAP>(ang[0], s[0], m[0]);
-    double_angle(s[0], m[0], s[1], m[1]);
-    sincos_rev<WRAP>(ang[1], s[2], m[2]);
-    double_angle(s[2], m[2], s[3], m[3]);
-    sincos_rev<WRAP>(ang[2], s[4], m[4]);
-    double_angle(s[4], m[4], s[5], m[5]);
-    double_angle(s[5], m[5], s[6], m[6]);
-    double_angle(s[6], m[6], s[7], m[7]);
-    unsigned p[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) p[q] = pk<BF>(s[q], m[q]);
-    p[6] = (ident[0] & m3) | (p[6] & ~m3);
-    p[7] = (ident[1] & m3) | (p[7] & ~m3);
-    Bx[0] = (u4){p[0], p[1], p[2], p[3]};
-    Bx[1] = (u4){p[4], p[5], p[6], p[7]};
-}
-// The gamma(d) block of layer 4.  rev: the lane's direction component in revolutions; ident[2..3]: (dx, dy), (dz, 1).
-template <bool BF> __device__ __forceinline__ u4 encode_direction(float rev, u4 ident, unsigned m3)
-{
-    float s[4], m[4];
-    sincos_rev<false>(rev, s[0], m[0]); // directions: |d| far below 256 revolutions
-    double_angle(s[0], m[0], s[1], m[1]);
-    double_angle(s[1], m[1], s[2], m[2]);
-    double_angle(s[2], m[2], s[3], m[3]);
-    // group 3: slots 0..3 hold dx, dy, dz, 1; its slots 4..7 meet zero weights, any finite value does
-    return (u4){(ident[2] & m3) | (pk<BF>(s[0], m[0]) & ~m3), (ident[3] & m3) | (pk<BF>(s[1], m[1]) & ~m3),
-                pk<BF>(s[2], m[2]), pk<BF>(s[3], m[3])};
-}
-
 // Weights stay in registers: 12 blocks (48 VGPRs) for H = 32, four wavefronts per SIMD; 32 blocks (128 VGPRs) for
 // H = 64, two wavefronts per SIMD (the matrix-core operands are read straight from the register file either way).
 // STRAT (render with stratified sampling): the lattice points sit at their drawn offsets and the density is

@@ -12,196 +12,18 @@
 // compacted into a list.
 #include "kn_common.h"
 #include "kn_dir_encode.h"
+#include "kn_fused.h"
+#include "kn_march.h"
 
 #include <math.h>
 
+#include <algorithm>
 #include <chrono>
 
 namespace {
 
 constexpr int MARCH_G = 16;    // lanes per ray of the stage kernel and of the blend of long rows
 constexpr int LIST_GROUP = 16; // rows per group in which the blend counts survivors and the next march compacts the list
-
-struct MarchParams {
-    KnGrid net, occ;
-    KnGrid content; // box around everything occupied (res 0: nothing is); rays are clipped against it
-    const uint32_t *occ_bits;
-    const uint8_t *skip_dist;
-    int32_t skip_res[3];
-    float skip_inv[3];   // 1 / (edge of a skip block) per axis
-    float skip_edge_min; // shortest edge of a skip block
-    float skip_margin;   // safety margin on the jump radius (position rounding)
-    int32_t has_occ;
-    // >= 0 on every axis: the occupancy grid refines the network grid by 2^net_shift[a] (same box), so that the
-    // network cell of a point is its voxel coordinate shifted right, exactly (scaling the cell edge by a power of two
-    // scales the fp32 quotient of Eq. 6 by the same power of two without a rounding difference)
-    int32_t net_shift[3];
-    float t_near, step;
-    int32_t K;
-    const int32_t *cell_net; // sparse network grid: cell -> network or -1 (kernels built with OPT_SPARSE read it)
-    uint32_t seed_key;       // stratified sampling: kn_mix32(seed) (kernels built with OPT_STRAT use it)
-};
-
-// Variants of the marching kernels, chosen at compile time so that the plain path carries none of their cost:
-// a sparse network grid (a table look-up per kept point; points in cells without a network are dropped) and
-// stratified sampling (lattice points at their drawn offsets instead of the middle of their intervals).
-constexpr int OPT_SPARSE = 1, OPT_STRAT = 2;
-
-// One axis of Eq. 6 without the division when the result cannot depend on it: u' = rel * (1/cell)
-// differs from the correctly rounded quotient by a few ulp (less than 4.8e-7 |u'|); only when u' sits that close
-// to an integer is the division itself evaluated.  `guard` is that bound for the largest |u'| that matters,
-// res + 1: beyond it both u' and the quotient are outside [0, res) whatever their last bits are, and callers only
-// ask whether the result is inside that range, and which integer it is if so.  Returns floor(quotient) as a float
-// (for values inside the range; some value outside the range otherwise; NaN and inf stay what they are).
-__device__ __forceinline__ float axis_floor(float rel, float cell, float inv_cell, float guard, float one_minus_guard)
-{
-    const float u = rel * inv_cell;
-    const float f = floorf(u);
-    const float frac = u - f;
-    if (frac <= guard || frac >= one_minus_guard) return floorf(rel / cell); // (both false for NaN / inf)
-    return f;
-}
-
-struct GridFast {
-    float bmin[3], cell[3], inv[3], resf[3], guard[3], one_minus_guard[3];
-    int32_t res1, res2;
-};
-
-__device__ __forceinline__ GridFast make_fast(const KnGrid &g)
-{
-    GridFast f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        f.bmin[a] = g.bmin[a];
-        f.cell[a] = g.cell[a];
-        f.inv[a] = 1.0f / g.cell[a];
-        f.resf[a] = (float)g.res[a];
-        f.guard[a] = ((float)g.res[a] + 1.0f) * 4.8e-7f + 1e-30f;
-        f.one_minus_guard[a] = 1.0f - f.guard[a];
-    }
-    f.res1 = g.res[1];
-    f.res2 = g.res[2];
-    return f;
-}
-
-// Eq. 6 per axis: integer cell coordinates of a point, false when it is outside the grid
-__device__ __forceinline__ bool grid_coords_fast(const GridFast &g, float x, float y, float z, int32_t &ix, int32_t &iy,
-                                                 int32_t &iz)
-{
-    const float fx = axis_floor(x - g.bmin[0], g.cell[0], g.inv[0], g.guard[0], g.one_minus_guard[0]);
-    const float fy = axis_floor(y - g.bmin[1], g.cell[1], g.inv[1], g.guard[1], g.one_minus_guard[1]);
-    const float fz = axis_floor(z - g.bmin[2], g.cell[2], g.inv[2], g.guard[2], g.one_minus_guard[2]);
-    const bool in = (fx >= 0.0f) && (fx < g.resf[0]) && (fy >= 0.0f) && (fy < g.resf[1]) && (fz >= 0.0f) &&
-                    (fz < g.resf[2]);
-    ix = (int32_t)fx;
-    iy = (int32_t)fy;
-    iz = (int32_t)fz;
-    return in;
-}
-
-__device__ __forceinline__ int32_t grid_index_fast(const GridFast &g, float x, float y, float z)
-{
-    const float fx = axis_floor(x - g.bmin[0], g.cell[0], g.inv[0], g.guard[0], g.one_minus_guard[0]);
-    const float fy = axis_floor(y - g.bmin[1], g.cell[1], g.inv[1], g.guard[1], g.one_minus_guard[1]);
-    const float fz = axis_floor(z - g.bmin[2], g.cell[2], g.inv[2], g.guard[2], g.one_minus_guard[2]);
-    const bool in = (fx >= 0.0f) && (fx < g.resf[0]) && (fy >= 0.0f) && (fy < g.resf[1]) && (fz >= 0.0f) &&
-                    (fz < g.resf[2]);
-    if (!in) return -1;
-    return ((int32_t)fx * g.res1 + (int32_t)fy) * g.res2 + (int32_t)fz;
-}
-
-// Conservative range [k_lo, k_hi) of lattice indices whose point can lie inside the AABB (slab
-// test widened by the rounding error of x_k = fma(t_k, d, o) and two steps).  Every index
-// outside the range is provably outside the box; indices inside it are still tested exactly.
-__device__ __forceinline__ void clip_ray(const KnGrid &g, const float o[3], const float d[3], float t_near, float step,
-                                         int32_t K, int32_t &k_lo, int32_t &k_hi)
-{
-    if (g.res[0] == 0) { // empty box
-        k_lo = k_hi = 0;
-        return;
-    }
-    float tmin = -INFINITY, tmax = INFINITY;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (d[a] != 0.0f) {
-            const float lo = g.bmin[a], hi = g.bmin[a] + g.cell[a] * (float)g.res[a];
-            const float inv = 1.0f / d[a];
-            float t0 = (lo - o[a]) * inv, t1 = (hi - o[a]) * inv;
-            if (t0 > t1) { float s = t0; t0 = t1; t1 = s; }
-            const float mag = fabsf(lo) + fabsf(hi) + fabsf(o[a]) + g.cell[a];
-            const float margin = mag * 2.4e-7f * fabsf(inv) + 1e-6f * (fabsf(t0) + fabsf(t1));
-            tmin = fmaxf(tmin, t0 - margin);
-            tmax = fminf(tmax, t1 + margin);
-        }
-    }
-    // k such that t_near + (k + 1/2) step lies in [tmin, tmax], widened by two steps
-    float a = floorf((tmin - t_near) / step - 0.5f) - 2.0f;
-    float b = ceilf((tmax - t_near) / step - 0.5f) + 3.0f;
-    a = fminf(fmaxf(a, 0.0f), (float)K); // NaN -> 0
-    b = fminf(fmaxf(b, 0.0f), (float)K);
-    if (!(tmin <= tmax)) { // empty -> nothing; NaN -> stay conservative (full range)
-        if (tmin > tmax) { a = 0.0f; b = 0.0f; } else { a = 0.0f; b = (float)K; }
-    }
-    k_lo = (int32_t)a;
-    k_hi = (int32_t)b;
-}
-
-// Jump length bookkeeping shared by the two users of the skip field.  A point whose block has
-// Chebyshev distance dist >= 2 to the nearest occupied block lies in an empty block, and so does
-// every point within Euclidean distance (dist-1) * (shortest block edge) of it, minus a rounding
-// margin: jump(dist) is how many further lattice indices that covers.
-struct SkipJump {
-    float a, b;
-    bool use;
-    // strat: with stratified sampling point k + j lies up to j + 1 steps from point k, one more than on the
-    // midpoint lattice
-    __device__ __forceinline__ SkipJump(const MarchParams &p, const float o[3], const float d[3], bool strat)
-    {
-        const float dlen = sqrtf(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-        const float inv_step_len = 1.0f / (p.step * dlen); // 1 / distance covered by one lattice step
-        a = p.skip_edge_min * inv_step_len;
-        b = (p.skip_margin + 1e-6f * (fabsf(o[0]) + fabsf(o[1]) + fabsf(o[2]))) * inv_step_len + (strat ? 2.0f : 1.0f);
-        use = p.skip_dist != nullptr && isfinite(inv_step_len);
-    }
-    __device__ __forceinline__ int32_t jump(int32_t dist) const { return (int32_t)fmaxf(floorf((float)(dist - 1) * a - b), 0.0f); }
-};
-
-// skip-field value at a point; -1 = the point is (up to rounding) outside the field
-__device__ __forceinline__ int32_t skip_lookup(const MarchParams &p, float x, float y, float z)
-{
-    const float cx = floorf((x - p.occ.bmin[0]) * p.skip_inv[0]);
-    const float cy = floorf((y - p.occ.bmin[1]) * p.skip_inv[1]);
-    const float cz = floorf((z - p.occ.bmin[2]) * p.skip_inv[2]);
-    if (cx >= 0.0f && cx < (float)p.skip_res[0] && cy >= 0.0f && cy < (float)p.skip_res[1] && cz >= 0.0f &&
-        cz < (float)p.skip_res[2])
-        return p.skip_dist[((int32_t)cx * p.skip_res[1] + (int32_t)cy) * p.skip_res[2] + (int32_t)cz];
-    return -1;
-}
-
-// One thread walks a ray through provably empty space: returns the first index in [k, k_hi) whose
-// point is not known to be empty (or k_hi).  No index it passes over can be a kept sample.
-template <int OPT>
-__device__ __forceinline__ int32_t skip_to_content(const MarchParams &p, const GridFast &go, const float o[3],
-                                                   const float d[3], int32_t k, int32_t k_hi, uint32_t ray_key)
-{
-    constexpr bool STRAT = (OPT & OPT_STRAT) != 0;
-    if (k >= k_hi) return k_hi; // the ray misses the content box: nothing to walk through
-    const SkipJump sj(p, o, d, STRAT);
-    if (!sj.use) return k;
-    while (k < k_hi) {
-        float x, y, z;
-        kn_lattice_point<STRAT>(o[0], o[1], o[2], d[0], d[1], d[2], p.t_near, p.step, k, x, y, z, ray_key);
-        const int32_t dist = skip_lookup(p, x, y, z);
-        if (dist >= 2) {
-            k += 1 + sj.jump(dist);
-        } else if (dist < 0 && grid_index_fast(go, x, y, z) < 0) {
-            k += 1; // exactly outside the AABB (the clip range starts a little before the box)
-        } else {
-            break;
-        }
-    }
-    return min(k, k_hi);
-}
 
 // Largest value among the G lanes of a marching group, in every lane of the group.  A group is one row (16 lanes) or
 // half a row (8) of the data-parallel-primitive network, so a few permutations inside the row do it, without the LDS
@@ -469,6 +291,165 @@ __global__ void __launch_bounds__(RAY_BLOCK)
         *n_live = before + total;
         set_wave(ctl, before + total, sched.first, sched);
         post_mailbox(mailbox, seq, (unsigned long long)(before + total));
+    }
+}
+
+// Set-up of the fused render: clips every ray and walks it to the first lattice point near content; rays without any
+// sample get the background right away.  recs[r] = (first lattice index, end of the clipped range, bucket, rank in the
+// bucket) of a live ray (a dead one: bucket -1), blk_sum[block] = its live rays + 2^16 * its runs of equal buckets.
+//
+// A bucket is a box of the scene, 32 per axis, that the ray's first point lies in.  Rays that follow each other in the
+// caller's arrays share a bucket for a while when they come from an image; rays in random order do not, and a wavefront
+// of the fused kernel would then load a network's weights for a sample or two.  SORT (frames of SORT_RAYS and more):
+// counts the buckets, so that k_fused_list can order the rays.  Ordering an image anyway gained nothing (1080p, width 64:
+// 1.17 ms against 1.08), ordering two million shuffled rays of it took 12.3 ms to 2.5.
+constexpr int FUSED_BUCKETS_LG = 5, FUSED_BUCKETS = 1 << (3 * FUSED_BUCKETS_LG);
+constexpr int64_t SORT_RAYS = 32768; // below, a frame has fewer rays than the first pools of the wavefronts hold
+struct BucketMap {
+    float scale[3], shift[3];
+};
+__device__ __forceinline__ int32_t spread3(int32_t v) // bit i of a 5-bit number -> bit 3 i
+{
+    v = (v | v << 8) & 0x100f;
+    v = (v | v << 4) & 0x10c3;
+    return (v | v << 2) & 0x1249;
+}
+template <bool STRAT, bool SORT>
+__global__ void __launch_bounds__(RAY_BLOCK)
+    k_fused_init(MarchParams p, BucketMap map, const float *__restrict__ rays_o, const float *__restrict__ rays_d, int64_t R,
+                 int4 *__restrict__ recs, int32_t *__restrict__ blk_sum, int32_t *__restrict__ counts, float bg0, float bg1, float bg2,
+                 float *__restrict__ rgb_out)
+{
+    __shared__ int32_t lds[RAY_BLOCK / KN_WAVE];
+    const int64_t r = (int64_t)blockIdx.x * RAY_BLOCK + threadIdx.x;
+    const int lane = threadIdx.x & (KN_WAVE - 1);
+    int32_t k_lo = 0, k_hi = 0, key = -1;
+    if (r < R) {
+        const float o[3] = {rays_o[3 * r], rays_o[3 * r + 1], rays_o[3 * r + 2]};
+        const float d[3] = {rays_d[3 * r], rays_d[3 * r + 1], rays_d[3 * r + 2]};
+        const uint32_t ray_key = kn_mix32(p.seed_key + (uint32_t)r);
+        clip_ray(p.content, o, d, p.t_near, p.step, p.K, k_lo, k_hi);
+        // (a ray with a component that is no finite number has no lattice point inside the box)
+        if (!(isfinite(o[0]) && isfinite(o[1]) && isfinite(o[2]) && isfinite(d[0]) && isfinite(d[1]) && isfinite(d[2]))) k_hi = k_lo;
+        k_lo = skip_to_content<STRAT ? OPT_STRAT : 0>(p, make_fast(p.occ), o, d, k_lo, k_hi, ray_key);
+        if (k_lo < k_hi) {
+            key = 0;
+            if constexpr (SORT) {
+                float x[3];
+                kn_lattice_point<STRAT>(o[0], o[1], o[2], d[0], d[1], d[2], p.t_near, p.step, k_lo, x[0], x[1], x[2], ray_key);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) // (Morton order)
+                    key |= spread3((int32_t)fminf(fmaxf(fmaf(x[a], map.scale[a], map.shift[a]), 0.0f), (float)((1 << FUSED_BUCKETS_LG) - 1))) << a;
+            }
+        } else {
+            rgb_out[3 * r] = bg0;
+            rgb_out[3 * r + 1] = bg1;
+            rgb_out[3 * r + 2] = bg2;
+        }
+    }
+    int32_t rank = 0, mine = key >= 0 ? 1 : 0;
+    if constexpr (SORT) { // one atomic per run of lanes with the same bucket
+        const int32_t prev = __shfl_up(key, 1, KN_WAVE);
+        const unsigned long long heads = __ballot(lane == 0 || prev != key); // bit l: lane l starts a run
+        const int head = KN_WAVE - 1 - __builtin_clzll(heads & (~0ull >> (KN_WAVE - 1 - lane)));
+        const unsigned long long behind = lane == KN_WAVE - 1 ? 0ull : heads >> (lane + 1); // the runs behind this lane
+        const int len = behind ? __builtin_ctzll(behind) + 1 : KN_WAVE - lane;             // (used at the head)
+        int32_t base = 0;
+        if (head == lane && key >= 0) {
+            base = atomicAdd(&counts[key], len);
+            mine += 1 << 16;
+        }
+        rank = __shfl(base, head, KN_WAVE) + lane - head;
+    }
+    if (r < R) recs[r] = make_int4(k_lo, k_hi, key, rank);
+    const int32_t total = kn_block_sum(mine, lds);
+    if (threadIdx.x == 0) blk_sum[blockIdx.x] = total;
+}
+
+// The list of live rays, (ray, first lattice index, end of the clipped range, -): in the caller's order, or with SORT, where
+// that order's runs of equal buckets are shorter than SORT_RUN rays on average, in the order of the buckets.
+// ctl[0] = number of live rays, everything behind it is cleared for the fused kernel.
+constexpr int LIST_BLOCK = 1024, LIST_RAYS = 8, LIST_WAVES = LIST_BLOCK / KN_WAVE; // threads, rays per thread
+constexpr int SORT_RUN = 4;
+constexpr int FUSED_CTL = 8; // ctl words: live rays, hand-out counter, -, -, two 64-bit counters
+template <bool SORT>
+__global__ void __launch_bounds__(LIST_BLOCK)
+    k_fused_list(const int4 *__restrict__ recs, int64_t R, const int32_t *__restrict__ blk_sum, const int32_t *__restrict__ counts,
+                 int4 *__restrict__ list, int32_t *__restrict__ ctl)
+{
+    __shared__ int32_t s_start[SORT ? FUSED_BUCKETS : 1], s_live[LIST_WAVES], s_sum[3][LIST_WAVES];
+    const int lane = threadIdx.x & (KN_WAVE - 1), wv = threadIdx.x / KN_WAVE;
+    // wavefront w of the workgroup looks after LIST_RAYS * 64 rays in a row
+    const int64_t r0 = (int64_t)blockIdx.x * (LIST_BLOCK * LIST_RAYS) + wv * (KN_WAVE * LIST_RAYS) + lane;
+    int4 rec[LIST_RAYS];
+#pragma unroll
+    for (int i = 0; i < LIST_RAYS; ++i) rec[i] = recs[min(r0 + i * KN_WAVE, R - 1)];
+    // live rays in front of the workgroup; live rays and runs of the whole frame
+    const int n_blk = (int)((R + RAY_BLOCK - 1) / RAY_BLOCK), b_first = blockIdx.x * (LIST_BLOCK * LIST_RAYS / RAY_BLOCK);
+    int32_t front = 0, all = 0, runs = 0;
+    for (int b = threadIdx.x; b < n_blk; b += LIST_BLOCK) {
+        const int32_t v = blk_sum[b];
+        front += b < b_first ? v & 0xffff : 0;
+        all += v & 0xffff;
+        runs += v >> 16;
+    }
+    unsigned long long live[LIST_RAYS];
+    int32_t n_live = 0;
+#pragma unroll
+    for (int i = 0; i < LIST_RAYS; ++i) {
+        live[i] = __ballot(r0 + i * KN_WAVE < R && rec[i].z >= 0);
+        n_live += __popcll(live[i]);
+    }
+    front = kn_wave_inclusive_scan(front);
+    all = kn_wave_inclusive_scan(all);
+    runs = kn_wave_inclusive_scan(runs);
+    if (lane == KN_WAVE - 1) {
+        s_live[wv] = n_live;
+        s_sum[0][wv] = front;
+        s_sum[1][wv] = all;
+        s_sum[2][wv] = runs;
+    }
+    __syncthreads();
+    front = all = runs = 0;
+    for (int w = 0; w < LIST_WAVES; ++w) {
+        front += s_sum[0][w] + (w < wv ? s_live[w] : 0);
+        all += s_sum[1][w];
+        runs += s_sum[2][w];
+    }
+    if (blockIdx.x == 0 && threadIdx.x < FUSED_CTL) ctl[threadIdx.x] = threadIdx.x == 0 ? all : 0;
+    if constexpr (SORT) {
+        if (all < (int64_t)SORT_RUN * runs) { // (uniform: the same in every workgroup)
+            constexpr int PER = FUSED_BUCKETS / LIST_BLOCK;
+            const int b0 = wv * KN_WAVE * PER + lane;
+            int32_t c[PER], sum = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) c[i] = counts[b0 + i * KN_WAVE];
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int32_t inc = kn_wave_inclusive_scan(c[i]);
+                c[i] = sum + inc - c[i];
+                sum += __builtin_amdgcn_readlane(inc, KN_WAVE - 1);
+            }
+            __syncthreads(); // (s_live has been read)
+            if (lane == 0) s_live[wv] = sum;
+            __syncthreads();
+            int32_t before = 0;
+            for (int w = 0; w < wv; ++w) before += s_live[w];
+#pragma unroll
+            for (int i = 0; i < PER; ++i) s_start[b0 + i * KN_WAVE] = before + c[i];
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < LIST_RAYS; ++i)
+                if ((live[i] >> lane) & 1ull)
+                    list[s_start[rec[i].z] + rec[i].w] = make_int4((int32_t)(r0 + i * KN_WAVE), rec[i].x, rec[i].y, 0);
+            return;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < LIST_RAYS; ++i) {
+        if ((live[i] >> lane) & 1ull)
+            list[front + __popcll(live[i] & ((1ull << lane) - 1ull))] = make_int4((int32_t)(r0 + i * KN_WAVE), rec[i].x, rec[i].y, 0);
+        front += __popcll(live[i]);
     }
 }
 
@@ -999,7 +980,9 @@ MarchParams make_params(const kn_scene *sc, float t_near, float step, int32_t K,
     p.net = sc->net_grid;
     p.occ = sc->has_occ ? sc->occ_grid : sc->net_grid;
     p.content = sc->content_box;
+    p.bricks = sc->bricks;
     p.occ_bits = sc->occ_bits;
+    p.brick_nets = sc->brick_nets ? 1 : 0;
     p.has_occ = sc->has_occ ? 1 : 0;
     p.skip_dist = sc->has_occ ? sc->skip_dist : nullptr;
     p.skip_edge_min = INFINITY;
@@ -1012,13 +995,7 @@ MarchParams make_params(const kn_scene *sc, float t_near, float step, int32_t K,
         mag = fmaxf(mag, fabsf(p.occ.bmin[a]) + p.occ.cell[a] * (float)p.occ.res[a]);
     }
     p.skip_margin = 1e-3f * p.skip_edge_min + 4e-6f * mag;
-    for (int a = 0; a < 3; ++a) {
-        int sft = -1;
-        if (sc->has_occ)
-            for (int q = 0; q < 16; ++q)
-                if ((int64_t)p.net.res[a] << q == (int64_t)p.occ.res[a]) sft = q;
-        p.net_shift[a] = sft;
-    }
+    for (int a = 0; a < 3; ++a) p.net_shift[a] = sc->net_shift[a];
     if (p.net_shift[0] < 0 || p.net_shift[1] < 0 || p.net_shift[2] < 0) p.net_shift[0] = p.net_shift[1] = p.net_shift[2] = -1;
     p.t_near = t_near;
     p.step = step;
@@ -1168,13 +1145,30 @@ static void carve_render(KnCarver &ws, int64_t R, int64_t slots, RenderWs &w)
     w.dir_table = ws.carve<uint16_t>(32 * R);
 }
 
+// The fused render (kn_fused.hip): set-up, ordered list of live rays, one kernel for the rest; nothing is read back.
+struct FusedWs {
+    int4 *recs, *list;
+    int32_t *blk_sum, *counts, *ctl;
+};
+static void carve_fused(KnCarver &ws, int64_t R, FusedWs &w)
+{
+    w.recs = ws.carve<int4>(R);
+    w.list = ws.carve<int4>(R);
+    w.blk_sum = ws.carve<int32_t>(kn_div_up(R, RAY_BLOCK));
+    w.counts = ws.carve<int32_t>(R < SORT_RAYS ? 0 : FUSED_BUCKETS);
+    w.ctl = ws.carve<int32_t>(FUSED_CTL);
+}
+
 int64_t kn_render_ws_bytes(const kn_scene *sc, int64_t R, int32_t slots_per_ray)
 {
     KnCarver c((void *)256, INT64_MAX / 2);
     RenderWs w;
     const int64_t slots = R * slots_per_ray;
     carve_render(c, R, slots, w);
-    return c.used + kn_group_ws_bytes(slots, sc->N);
+    KnCarver cf((void *)256, INT64_MAX / 2);
+    FusedWs wf;
+    carve_fused(cf, R, wf);
+    return std::max(c.used + kn_group_ws_bytes(slots, sc->N), cf.used);
 }
 
 static int march_impl(const kn_scene *sc, void *stream, const float *rays_o, const float *rays_d, int64_t R, float t_near,
@@ -1235,6 +1229,72 @@ extern "C" int kn_composite_deltas(void *stream, const float *sigma, const float
     return composite_impl(stream, sigma, rgb, delta, offsets, R, 1.0f, term_eps, bg, rgb_out, T_out, n_used);
 }
 
+// Where the fused kernel is the faster one, from 120 frames of 2,000 to 2.6 million rays, 2^3 to 48^3 networks, dense,
+// sparse, stratified and open.  It evaluates a wavefront's samples network by network and loads the network's weights for
+// each, so it needs several samples of a ray per network: the lattice points in a cell's edge say how many there are
+// (5 at width 32, 8 on a sparse grid, 16 at width 64, whose weights are three times as many bytes; below, frames took up to 1.5 times the
+// wave loop's time, above 0.6 to 0.9 of it).  Frames too small to fill the wave loop's launches gain in any case (0.4 to
+// 0.8), large ones at width 32 mostly.  Without early termination every sample is evaluated anyway and the wave loop's
+// full tiles win (0.8 to 0.97) unless the frame is tiny.
+static bool fused_pays(const kn_scene *sc, int64_t R, float step, float term_eps)
+{
+    if (term_eps == 0.0f) return R <= 8192;
+    if (R <= 32768 || sc->N <= 64) return true;
+    const KnGrid &g = sc->net_grid;
+    const float points = fminf(g.cell[0], fminf(g.cell[1], g.cell[2])) / step;
+    if (sc->desc.hidden == 64) return points >= 16.0f;
+    return sc->cell_net ? points >= 8.0f : points >= 5.0f || R >= (1ll << 19);
+}
+
+static int render_fused(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, const MarchParams &p, const float *rays_o, const float *rays_d,
+                        int64_t R, float term_eps, const float bg[3], const uint32_t *seed, float *rgb_out, KnCarver &ws)
+{
+    FusedWs w;
+    carve_fused(ws, R, w);
+    if (!ws.ok()) return KN_E_WORKSPACE;
+    BucketMap map;
+    for (int a = 0; a < 3; ++a) {
+        map.scale[a] = (float)(1 << FUSED_BUCKETS_LG) / (p.net.cell[a] * (float)p.net.res[a]);
+        map.shift[a] = -p.net.bmin[a] * map.scale[a];
+    }
+    KnStageTimer tm(ctx, st);
+    tm.begin();
+    const bool sort = R >= SORT_RAYS;
+    if (sort) KN_TRY(kn_fill_i32(st, w.counts, FUSED_BUCKETS, 0));
+    const auto init = sort ? (seed ? k_fused_init<true, true> : k_fused_init<false, true>)
+                           : (seed ? k_fused_init<true, false> : k_fused_init<false, false>);
+    hipLaunchKernelGGL(init, dim3((unsigned)kn_div_up(R, RAY_BLOCK)), dim3(RAY_BLOCK), 0, st, p, map, rays_o, rays_d, R, w.recs, w.blk_sum,
+                       w.counts, bg[0], bg[1], bg[2], rgb_out);
+    KN_CHECK_LAUNCH();
+    hipLaunchKernelGGL(sort ? k_fused_list<true> : k_fused_list<false>, dim3((unsigned)kn_div_up(R, LIST_BLOCK * LIST_RAYS)), dim3(LIST_BLOCK), 0,
+                       st, w.recs, R, w.blk_sum, w.counts, w.list, w.ctl);
+    KN_CHECK_LAUNCH();
+    tm.mark(KN_ST_SETUP);
+    KnFusedJob job{};
+    job.march = &p;
+    job.rays_o = rays_o;
+    job.rays_d = rays_d;
+    job.R = R;
+    job.list = w.list;
+    job.ctl = w.ctl;
+    job.eps = term_eps;
+    job.bg = bg;
+    job.rgb_out = rgb_out;
+    job.counters = tm.counts ? (unsigned long long *)(w.ctl + 4) : nullptr;
+    job.strat = seed != nullptr;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    (void)tm.kernel_events(KN_ST_MLP, &e0, &e1);
+    KN_TRY(kn_fused_launch(sc, st, job, e0, e1));
+    tm.mark(KN_ST_MLP);
+    if (tm.counts) {
+        unsigned long long c[2] = {0ull, 0ull};
+        KN_HIP(hipMemcpyAsync(c, w.ctl + 4, sizeof(c), hipMemcpyDeviceToHost, st));
+        KN_HIP(hipStreamSynchronize(st));
+        tm.add(1, (int64_t)c[0], 0, 1);
+    }
+    return KN_OK;
+}
+
 static int render_impl(kn_ctx *ctx, const kn_scene *sc, void *stream, const float *rays_o, const float *rays_d, int64_t R, float t_near,
                        float step, int32_t K, float term_eps, const float bg[3], const uint32_t *seed, float *rgb_out,
                        kn_render_stats *stats, void *workspace, int64_t workspace_bytes)
@@ -1256,6 +1316,11 @@ static int render_impl(kn_ctx *ctx, const kn_scene *sc, void *stream, const floa
 
     hipStream_t st = (hipStream_t)stream;
     KnCarver ws(workspace, workspace_bytes);
+    const MarchParams p = make_params(sc, t_near, step, K, seed);
+    const int opt = march_options(sc, seed);
+    // Counts per wave and a schedule or limits set by the caller are the wave loop's.
+    if (!stats && knobs.is_default() && kn_fused_supports(sc) && fused_pays(sc, R, step, term_eps))
+        return render_fused(ctx, sc, st, p, rays_o, rays_d, R, term_eps, bg, seed, rgb_out, ws);
     RenderWs w;
     const int64_t budget = R * knobs.slots_per_ray;
     carve_render(ws, R, budget, w);
@@ -1264,8 +1329,6 @@ static int render_impl(kn_ctx *ctx, const kn_scene *sc, void *stream, const floa
     kn_group_carve(ws, budget, sc->N, &gw);
     if (!ws.ok()) return KN_E_WORKSPACE;
 
-    const MarchParams p = make_params(sc, t_near, step, K, seed);
-    const int opt = march_options(sc, seed);
     RayState rs{w.T, w.C, w.k_next, w.k_end};
     const unsigned rblocks = (unsigned)kn_div_up(R, RAY_BLOCK);
     const int64_t n_hist = 2 * (int64_t)sc->N; // histogram and fill cursors of the sample grouping

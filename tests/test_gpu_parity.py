@@ -1396,6 +1396,35 @@ def test_stratified_render_on_a_sparse_grid_and_on_grids_that_do_not_nest():
     render_check(cfg)
 
 
+@pytest.mark.parametrize("wdtype,H,rays,res,occ,order", [
+    ("f16", 32, 1, (16, 16, 16), "nested", "image"), ("bf16", 64, 17, (4, 4, 4), "nested", "image"),
+    ("f16", 64, 1025, (5, 8, 5), "odd", "image"), ("bf16", 32, 12288, (16, 16, 16), "none", "image"),
+    ("f16", 32, 32767, (16, 16, 16), "nested", "shuffled"), ("f16", 32, 32768, (16, 16, 16), "nested", "shuffled"),
+    ("bf16", 64, 40001, (16, 16, 16), "nested", "shuffled"), ("f16", 64, 131073, (7, 6, 5), "odd", "image"),
+    ("bf16", 32, 200000, (32, 32, 32), "nested", "image")])
+@pytest.mark.parametrize("seed", [None, 7])
+def test_render_in_one_kernel_equals_the_wave_loop(wdtype, H, rays, res, occ, order, seed):
+    """Bit for bit: ray counts around the pool and set-up limits, grids that nest, do not nest or are absent."""
+    import torch
+    log("fused render", wdtype, H, rays, res, occ, order, seed)
+    cfg = configs.config3(64, 64)
+    grid = {"nested": cfg["scene"]["occupancy"], "odd": ks.blob_occupancy((50, 45, 61), 12, 0.15, 5), "none": None}[occ]
+    lo, hi = (cfg["scene"][k] if occ != "odd" else v for k, v in (("aabb_min", (-1, -1, -1)), ("aabb_max", (1, 1, 1))))
+    dev, _ = make_pair(scene_dict(res, lo, hi, H, wdtype, 13, occ=grid, sigma_scale=60.0))
+    g = torch.Generator().manual_seed(rays)
+    o, d = torch.from_numpy(cfg["rays_o"]), torch.from_numpy(cfg["rays_d"])
+    pick = torch.randint(0, len(o), (rays,), generator=g) if order == "shuffled" else torch.arange(rays) % len(o)
+    o, d = o[pick].clone(), d[pick].clone()
+    if rays > 1:
+        o[rays // 2] = float("nan")     # no sample
+        d[rays // 3] = -d[rays // 3]    # away from the scene
+    o, d = o.cuda(), d.cuda()
+    args = (cfg["t_near"], cfg["step"], cfg["K"], cfg["term_eps"], cfg["bg"])
+    waves, st = dev.render(o, d, *args, want_stats=True, seed=seed)
+    fused = dev.render(o, d, *args, seed=seed)
+    assert torch.equal(fused, waves) and (rays < 1000 or st["samples_blended"] > rays)
+
+
 def test_sparse_and_stratified_edge_cases():
     import torch
     import paper_2103_13744_amd as kn
