@@ -1,5 +1,6 @@
 // Host side of the C ABI: scene objects, validation, workspace sizing, kn_eval_grouped.
 #include "kn_common.h"
+#include "kn_direct.h"
 #include "kn_probe.h"
 
 #include <math.h>
@@ -663,6 +664,17 @@ static int eval_grouped_impl(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, co
 {
     KnCarver ws(workspace, workspace_bytes);
     KnStageTimer tm(ctx, st, timed);
+    const int lg_points = reorder && M > 0 && !counts && !perm ? kn_direct_lg_points(sc, M) : -1;
+    if (lg_points >= 0) { // a small batch whose order nobody asks for
+        tm.begin();
+        KnDirectJob job{sc->net_grid, sc->cell_net, points, dirs, M, lg_points, cell_id, sigma, rgb};
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        (void)tm.kernel_events(KN_ST_MLP, &e0, &e1);
+        KN_TRY(kn_direct_launch(sc, st, job, e0, e1));
+        tm.mark(KN_ST_MLP);
+        tm.add(1, M, M, 1);
+        return KN_OK;
+    }
     if (reorder && M > 0) {
         // the samples themselves are brought into grouped order (Sec. 3.5); the kernel reads them contiguously
         tm.begin();

@@ -25,6 +25,7 @@
 // Encoding: accurate sincosf at frequencies 0, 4 (positions), 0 (directions) and 8 (group 3), up to three steps
 // of the double-angle recurrence in between; all in fp32.
 #include "kn_common.h"
+#include "kn_direct.h"
 #include "kn_mlp_shared.h"
 #include <hip/hip_ext.h>
 #include "kn_probe.h"
@@ -112,34 +113,14 @@ __global__ void k_pack_weights_f32(const float *__restrict__ w, int64_t P, int32
     packed[i] = s < 0 ? 0.0f : w[net * P + s];
 }
 
-template <int H>
-__global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 2 : 1, H == 32 ? 2 : 1)))
-    k_mlp_f32(const float *__restrict__ packed, KnSampleSrc src, const int32_t *__restrict__ perm,
-              const KnTile *__restrict__ tiles, const int32_t *__restrict__ n_tiles, float *__restrict__ sigma,
-              float *__restrict__ rgb)
-{
-    constexpr int HT = H / 16, HQ = H / 4; // output tiles per layer, MFMAs per hidden input vector
-    __shared__ float stage[F32_WAVES][KN_WAVE][8]; // x, y, z, dx, dy, dz of the chunk's samples
-
-    const int wave = threadIdx.x / KN_WAVE, lane = threadIdx.x & (KN_WAVE - 1);
-    const int n = lane & 15, g = lane >> 4;
-    const bool g3 = g == 3;
-    const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-
-    const int total_tiles = *n_tiles;
-    const int total_waves = gridDim.x * F32_WAVES;
-    // workgroup b runs on XCD b % 8: renumbered so that an XCD (one L2) works on a contiguous eighth of the tile list
-    const int xcd_share = gridDim.x >> 3;
-    const int block_no = (gridDim.x & 7) == 0 ? (int)(blockIdx.x & 7) * xcd_share + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-    const int wid = __builtin_amdgcn_readfirstlane(block_no * F32_WAVES + wave);
-    const int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)wid * total_tiles / total_waves));
-    const int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(wid + 1) * total_tiles / total_waves));
-    if (t_lo >= t_hi) return;
-
+// one network's weights in registers
+template <int H> struct NetF32 {
     using R = Regs<H>;
+    static constexpr int HT = H / 16, HQ = H / 4; // output tiles per layer, MFMAs per hidden input vector
     float w1[HT][16], w2[HT][HQ], w3[HT][HQ], w4[HT][HQ + 8], wo[HQ];
     f4 bias2[HT], bias3[HT], bias_out;
-    auto load_network = [&](int32_t net) {
+    __device__ __forceinline__ void load(const float *__restrict__ packed, int32_t net, int lane)
+    {
         const float *__restrict__ wp = packed + (int64_t)net * (R::N * KN_WAVE) + lane;
         auto reg = [&](int r) { return wp[r * KN_WAVE]; };
 #pragma unroll
@@ -163,8 +144,128 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         for (int k = 0; k < HQ; ++k) wo[k] = reg(R::WO + k);
 #pragma unroll
         for (int j = 0; j < 4; ++j) bias_out[j] = reg(R::BO + j);
-    };
+    }
+};
 
+// n_tiles sample tiles (16 u .. 16 u + 15, u < n_tiles <= 4) of a staged chunk; lane l returns the pre-activations
+// (r, g, b, sigma) of sample l
+template <int H> __device__ __forceinline__ f4 eval_chunk(const NetF32<H> &w, const float (*stage)[8], int lane, int n_tiles)
+{
+    constexpr int HT = H / 16, HQ = H / 4;
+    const int n = lane & 15, g = lane >> 4;
+    const bool g3 = g == 3;
+    const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    f4 out = w.bias_out;
+#pragma unroll 1
+    for (int u = 0; u < n_tiles; ++u) {
+        const f4 s0 = *(const f4 *)&stage[16 * u + n][0];
+        const f4 s1 = *(const f4 *)&stage[16 * u + n][4];
+        const float p[3] = {s0[0], s0[1], s0[2]}, d[3] = {s0[3], s1[0], s1[1]};
+        const float pg = g == 0 ? p[0] : (g == 1 ? p[1] : p[2]);
+        const float dg = g == 0 ? d[0] : (g == 1 ? d[1] : d[2]);
+        // three accurate evaluations per lane; groups 0..2: axis g at frequencies 0 and 4 and the direction at 0,
+        // group 3: the three axes at frequency 8
+        const float ang[3] = {g3 ? 256.0f * p[0] : pg, g3 ? 256.0f * p[1] : 16.0f * pg, g3 ? 256.0f * p[2] : dg};
+        float cs[3][4], cc[3][4];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            sincosf(ang[c], &cs[c][0], &cc[c][0]);
+#pragma unroll
+            for (int k = 1; k < 4; ++k) double_angle(cs[c][k - 1], cc[c][k - 1], cs[c][k], cc[c][k]);
+        }
+        float enc[16], dirv[8];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int f = q >> 1;
+            const float axis_v = (q & 1) ? cc[f >> 2][f & 3] : cs[f >> 2][f & 3];
+            const float g3_v = q < 12 ? ((q & 1) ? cc[q >> 2][(q >> 1) & 1] : cs[q >> 2][(q >> 1) & 1])
+                                      : (q < 15 ? p[q >= 12 && q < 15 ? q - 12 : 0] : 1.0f);
+            enc[q] = g3 ? g3_v : axis_v;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float axis_v = (q & 1) ? cc[2][q >> 1] : cs[2][q >> 1];
+            const float g3_v = q < 3 ? d[q < 3 ? q : 0] : (q == 3 ? 1.0f : 0.0f);
+            dirv[q] = g3 ? g3_v : axis_v;
+        }
+        const bool my_tile = (n >> 2) == u;
+        const bool sig_row = my_tile && (n & 3) == 3, col_row = my_tile && (n & 3) < 3;
+
+        f4 acc[HT], h[HT];
+        // layer 1: gamma(x) -> H, ReLU
+#pragma unroll
+        for (int t2 = 0; t2 < HT; ++t2) {
+            acc[t2] = zero4;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[t2] = mfma4(w.w1[t2][q], enc[q], acc[t2]);
+        }
+#pragma unroll
+        for (int t2 = 0; t2 < HT; ++t2)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
+        // layer 2: H -> H, ReLU
+#pragma unroll
+        for (int t2 = 0; t2 < HT; ++t2) {
+            acc[t2] = w.bias2[t2];
+#pragma unroll
+            for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w.w2[t2][k], h[k >> 2][k & 3], acc[t2]);
+        }
+#pragma unroll
+        for (int t2 = 0; t2 < HT; ++t2)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
+        // layer 3: H -> feature (no activation) and density (row 4u + 3 of the shared tile)
+#pragma unroll
+        for (int t2 = 0; t2 < HT; ++t2) {
+            acc[t2] = w.bias3[t2];
+#pragma unroll
+            for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w.w3[t2][k], h[k >> 2][k & 3], acc[t2]);
+        }
+#pragma unroll
+        for (int k = 0; k < HQ; ++k) out = mfma4(sig_row ? w.wo[k] : 0.0f, h[k >> 2][k & 3], out);
+#pragma unroll
+        for (int t2 = 0; t2 < HT; ++t2) h[t2] = acc[t2];
+        // layer 4: [feature, gamma(d)] -> H, ReLU
+#pragma unroll
+        for (int t2 = 0; t2 < HT; ++t2) {
+            acc[t2] = zero4;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[t2] = mfma4(w.w4[t2][HQ + q], dirv[q], acc[t2]);
+#pragma unroll
+            for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w.w4[t2][k], h[k >> 2][k & 3], acc[t2]);
+        }
+#pragma unroll
+        for (int t2 = 0; t2 < HT; ++t2)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
+        // layer 5: H -> colour rows 4u + 0..2 of the shared tile
+#pragma unroll
+        for (int k = 0; k < HQ; ++k) out = mfma4(col_row ? w.wo[k] : 0.0f, h[k >> 2][k & 3], out);
+    }
+    return out;
+}
+
+template <int H>
+__global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 2 : 1, H == 32 ? 2 : 1)))
+    k_mlp_f32(const float *__restrict__ packed, KnSampleSrc src, const int32_t *__restrict__ perm,
+              const KnTile *__restrict__ tiles, const int32_t *__restrict__ n_tiles, float *__restrict__ sigma,
+              float *__restrict__ rgb)
+{
+    __shared__ float stage[F32_WAVES][KN_WAVE][8]; // x, y, z, dx, dy, dz of the chunk's samples
+
+    const int wave = threadIdx.x / KN_WAVE, lane = threadIdx.x & (KN_WAVE - 1);
+
+    const int total_tiles = *n_tiles;
+    const int total_waves = gridDim.x * F32_WAVES;
+    // workgroup b runs on XCD b % 8: renumbered so that an XCD (one L2) works on a contiguous eighth of the tile list
+    const int xcd_share = gridDim.x >> 3;
+    const int block_no = (gridDim.x & 7) == 0 ? (int)(blockIdx.x & 7) * xcd_share + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    const int wid = __builtin_amdgcn_readfirstlane(block_no * F32_WAVES + wave);
+    const int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)wid * total_tiles / total_waves));
+    const int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(wid + 1) * total_tiles / total_waves));
+    if (t_lo >= t_hi) return;
+
+    NetF32<H> w;
     auto descriptor = [&](int t) -> KnTile { return tiles[min(t, t_hi - 1)]; };
     auto sample_index = [&](const KnTile &d) {
         const int32_t pos = d.start + min(lane, d.len - 1);
@@ -183,7 +284,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         dsc_next = descriptor(t + 1);
         idx_next = sample_index(dsc_next);
         if (tl.net != net_cur) { // uniform
-            load_network(tl.net);
+            w.load(packed, tl.net, lane);
             net_cur = tl.net;
         }
         *(f4 *)&stage[wave][lane][0] = (f4){x, y, z, dx};
@@ -192,93 +293,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-        f4 out = bias_out;
-#pragma unroll 1
-        for (int u = 0; u < 4; ++u) {
-            const f4 s0 = *(const f4 *)&stage[wave][16 * u + n][0];
-            const f4 s1 = *(const f4 *)&stage[wave][16 * u + n][4];
-            const float p[3] = {s0[0], s0[1], s0[2]}, d[3] = {s0[3], s1[0], s1[1]};
-            const float pg = g == 0 ? p[0] : (g == 1 ? p[1] : p[2]);
-            const float dg = g == 0 ? d[0] : (g == 1 ? d[1] : d[2]);
-            // three accurate evaluations per lane; groups 0..2: axis g at frequencies 0 and 4 and the direction at 0,
-            // group 3: the three axes at frequency 8
-            const float ang[3] = {g3 ? 256.0f * p[0] : pg, g3 ? 256.0f * p[1] : 16.0f * pg, g3 ? 256.0f * p[2] : dg};
-            float cs[3][4], cc[3][4];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                sincosf(ang[c], &cs[c][0], &cc[c][0]);
-#pragma unroll
-                for (int k = 1; k < 4; ++k) double_angle(cs[c][k - 1], cc[c][k - 1], cs[c][k], cc[c][k]);
-            }
-            float enc[16], dirv[8];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int f = q >> 1;
-                const float axis_v = (q & 1) ? cc[f >> 2][f & 3] : cs[f >> 2][f & 3];
-                const float g3_v = q < 12 ? ((q & 1) ? cc[q >> 2][(q >> 1) & 1] : cs[q >> 2][(q >> 1) & 1])
-                                          : (q < 15 ? p[q >= 12 && q < 15 ? q - 12 : 0] : 1.0f);
-                enc[q] = g3 ? g3_v : axis_v;
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const float axis_v = (q & 1) ? cc[2][q >> 1] : cs[2][q >> 1];
-                const float g3_v = q < 3 ? d[q < 3 ? q : 0] : (q == 3 ? 1.0f : 0.0f);
-                dirv[q] = g3 ? g3_v : axis_v;
-            }
-            const bool my_tile = (n >> 2) == u;
-            const bool sig_row = my_tile && (n & 3) == 3, col_row = my_tile && (n & 3) < 3;
-
-            f4 acc[HT], h[HT];
-            // layer 1: gamma(x) -> H, ReLU
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2) {
-                acc[t2] = zero4;
-#pragma unroll
-                for (int q = 0; q < 16; ++q) acc[t2] = mfma4(w1[t2][q], enc[q], acc[t2]);
-            }
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-            // layer 2: H -> H, ReLU
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2) {
-                acc[t2] = bias2[t2];
-#pragma unroll
-                for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w2[t2][k], h[k >> 2][k & 3], acc[t2]);
-            }
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-            // layer 3: H -> feature (no activation) and density (row 4u + 3 of the shared tile)
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2) {
-                acc[t2] = bias3[t2];
-#pragma unroll
-                for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w3[t2][k], h[k >> 2][k & 3], acc[t2]);
-            }
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) out = mfma4(sig_row ? wo[k] : 0.0f, h[k >> 2][k & 3], out);
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2) h[t2] = acc[t2];
-            // layer 4: [feature, gamma(d)] -> H, ReLU
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2) {
-                acc[t2] = zero4;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) acc[t2] = mfma4(w4[t2][HQ + q], dirv[q], acc[t2]);
-#pragma unroll
-                for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w4[t2][k], h[k >> 2][k & 3], acc[t2]);
-            }
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-            // layer 5: H -> colour rows 4u + 0..2 of the shared tile
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) out = mfma4(col_row ? wo[k] : 0.0f, h[k >> 2][k & 3], out);
-        }
+        const f4 out = eval_chunk<H>(w, stage[wave], lane, 4);
         __builtin_amdgcn_wave_barrier(); // the staging buffer is rewritten by the next iteration
 
         if (lane < tl.len) {
@@ -294,6 +309,51 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
                 for (int c = 0; c < 3; ++c) rgb[3 * (int64_t)out_idx + c] = col[c];
             }
         }
+    }
+}
+
+// A small batch in the caller's order: a wavefront takes a few consecutive points and evaluates them network by network
+// (kn_direct.hip says when and why).
+template <int H>
+__global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 2 : 1, H == 32 ? 2 : 1)))
+    k_eval_direct_f32(const float *__restrict__ packed, KnDirectJob job)
+{
+    __shared__ float stage[F32_WAVES][KN_WAVE][8]; // x, y, z, dx, dy, dz, lane of the sample: the samples of one network
+    const int wave = threadIdx.x / KN_WAVE, lane = threadIdx.x & (KN_WAVE - 1);
+    const int64_t first = (int64_t)(blockIdx.x * F32_WAVES + wave) << job.lg_points;
+    KnDirectPoint pt;
+    unsigned long long pending = kn_direct_point(job, first, lane, pt);
+    while (pending != 0ull) {
+        const int32_t sel = __builtin_amdgcn_readlane(pt.net, (int)__builtin_ctzll(pending));
+        NetF32<H> w;
+        w.load(packed, sel, lane);
+        const bool hit = pt.net == sel;
+        const unsigned long long hits = __ballot(hit);
+        const int c = __popcll(hits), from = (int)__builtin_ctzll(hits);
+        // the samples move to the front; the places behind them repeat the first one (the sample tiles share an accumulator, so
+        // what is in them has to be a sample of the network)
+        const int hits_below = __popcll(hits & ((1ull << lane) - 1ull)), place = hit ? hits_below : c + lane - hits_below;
+        float v[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            const float own = q < 3 ? pt.p[q < 3 ? q : 0] : pt.d[q < 3 ? 0 : q - 3];
+            const float first_one = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own), from));
+            v[q] = hit ? own : first_one;
+        }
+        *(f4 *)&stage[wave][place][0] = (f4){v[0], v[1], v[2], v[3]};
+        *(f4 *)&stage[wave][place][4] = (f4){v[4], v[5], __int_as_float(lane), 0.0f};
+        pending &= ~hits;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const f4 out = eval_chunk<H>(w, stage[wave], lane, (c + 15) / 16);
+        if (lane < c) {
+            const int64_t to = first + __float_as_int(stage[wave][lane][6]);
+            job.sigma[to] = fmaxf(out[3], 0.0f);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) job.rgb[3 * to + q] = 1.0f / (1.0f + expf(-out[q]));
+        }
+        __builtin_amdgcn_wave_barrier(); // the staging buffer is rewritten by the next pass
     }
 }
 
@@ -473,6 +533,19 @@ int kn_mlp_f32_launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &src
         hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev_start, ev_stop, 0, w, src, b.perm, b.tiles, b.n_tiles, sigma, rgb);
     else
         hipLaunchKernelGGL(kernel, grid, block, 0, st, w, src, b.perm, b.tiles, b.n_tiles, sigma, rgb);
+    KN_CHECK_LAUNCH();
+    return KN_OK;
+}
+
+int kn_direct_f32_launch(const kn_scene *sc, hipStream_t st, const KnDirectJob &job, unsigned blocks, hipEvent_t ev_start,
+                         hipEvent_t ev_stop)
+{
+    const int H = sc->desc.hidden;
+    if (H != 32 && H != 64) return KN_E_UNSUPPORTED;
+    auto kernel = H == 32 ? k_eval_direct_f32<32> : k_eval_direct_f32<64>;
+    const dim3 grid(blocks), block(F32_WAVES * KN_WAVE);
+    if (ev_start && ev_stop) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev_start, ev_stop, 0, (const float *)sc->packed_w, job);
+    else hipLaunchKernelGGL(kernel, grid, block, 0, st, (const float *)sc->packed_w, job);
     KN_CHECK_LAUNCH();
     return KN_OK;
 }

@@ -271,6 +271,29 @@ def test_eval_grouped_density_scaled_and_tiny_groups():
     check_eval(sc, pts, ks.sphere_dirs(M, 8), sigma_unit=100.0)
 
 
+@pytest.mark.parametrize("wdtype,H", [("f16", 32), ("bf16", 64), ("f32", 32), ("f32", 64)])
+@pytest.mark.parametrize("res,M", [((16, 16, 16), 1), ((16, 16, 16), 63), ((5, 8, 5), 4097), ((16, 16, 16), 3001), ((2, 2, 2), 8190),
+                                   ((2, 2, 2), 16385), ((24, 20, 28), 4095)])
+def test_eval_grouped_without_aux_equals_the_ordered_batch(wdtype, H, res, M):
+    """A batch whose order nobody asks for may be evaluated without ordering it (small ones) or in another order: the
+    results per point are those of the call that reports counts and permutation."""
+    import torch
+    log("eval without aux", wdtype, H, res, M)
+    dev, _ = make_pair(scene_dict(res, (-1, -1, -1), (1, 1, 1), H, wdtype, 23))
+    pts, dirs = cuda(ks.uniform_points(M, 31, lo=(-1.02,) * 3, hi=(1.02,) * 3)), cuda(ks.sphere_dirs(M, 32))
+    pts[M // 2:] = pts[M // 2:] * 0.2       # half of them share few networks
+    if M > 5:
+        pts[M // 3, 1] = float("nan")
+        pts[M // 4, 2] = float("inf")
+    want = dev.eval_grouped(pts, dirs, want_aux=True)
+    out = (torch.full((M,), -7.0, device="cuda"), torch.full((M, 3), -7.0, device="cuda"))
+    got = dev.eval_grouped(pts, dirs, out=out)
+    if wdtype == "f32":     # (which samples share a tile moves the last bits of an fp32 sum by a zero more or less at most)
+        assert torch.allclose(got[0], want[0], rtol=1e-5, atol=1e-6) and torch.allclose(got[1], want[1], rtol=1e-5, atol=1e-6)
+    else:
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 def test_eval_grouped_empty_and_permutation_invariance():
     import torch
     sc = scene_dict((4, 4, 4), (0, 0, 0), (1, 1, 1), 32, "f16", 9)
