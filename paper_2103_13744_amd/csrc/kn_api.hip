@@ -642,8 +642,8 @@ static int64_t index_ws_bytes(const kn_scene *sc, int64_t M)
 // ... and of kn_eval_grouped, which moves the samples themselves
 static int64_t eval_ws_bytes(const kn_scene *sc, int64_t M)
 {
-    const int64_t a = index_ws_bytes(sc, M), b = kn_reorder_ws_bytes(M, sc->N);
-    return a > b ? a : b;
+    const int64_t a = index_ws_bytes(sc, M), b = kn_reorder_ws_bytes(M, sc->N), c = kn_order_ws_bytes(M, sc->N);
+    return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 
 extern "C" int kn_workspace_bytes(const kn_ctx *ctx, const kn_scene *sc, int64_t max_points, int64_t max_rays,
@@ -671,6 +671,21 @@ static int eval_grouped_impl(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, co
         hipEvent_t e0 = nullptr, e1 = nullptr;
         (void)tm.kernel_events(KN_ST_MLP, &e0, &e1);
         KN_TRY(kn_direct_launch(sc, st, job, e0, e1));
+        tm.mark(KN_ST_MLP);
+        tm.add(1, M, M, 1);
+        return KN_OK;
+    }
+    if (reorder && M > 0 && !perm && kn_order_pays(sc, M)) {
+        tm.begin();
+        KnBucketOut bo;
+        KN_TRY(kn_order_run(sc, st, points, M, kn_mlp_tile_len(sc), cell_id, counts, sigma, rgb, ws, &bo, &tm));
+        tm.mark(KN_ST_BUCKET);
+        KnSampleSrc src{};
+        src.points = points;
+        src.dirs = dirs;
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        (void)tm.kernel_events(KN_ST_MLP, &e0, &e1);
+        KN_TRY(kn_mlp_launch(sc, st, src, bo, M, sigma, rgb, e0, e1));
         tm.mark(KN_ST_MLP);
         tm.add(1, M, M, 1);
         return KN_OK;

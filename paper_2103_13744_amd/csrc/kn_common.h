@@ -287,6 +287,12 @@ int kn_reorder_run(const kn_scene *sc, hipStream_t st, const float *points, cons
                    const uint32_t *records[2], float **out4, KnStageTimer *tm /* nullable: marks the end of the cell-id stage */);
 int kn_reorder_configure(); // once per device: lifts the dynamic-LDS limit of the scatter kernels
 int kn_reorder_split_results(hipStream_t st, const float *out4, int64_t M, float *sigma, float *rgb);
+// Order of a batch by network alone (no order inside a network): out->perm, out->counts and the tiles; zero results of the
+// points without a network go straight to sigma / rgb.
+int64_t kn_order_ws_bytes(int64_t M, int32_t N);
+bool kn_order_pays(const kn_scene *sc, int64_t M);
+int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_t M, int32_t tile_len, int32_t *user_ids,
+                 int32_t *user_counts, float *sigma, float *rgb, KnCarver &ws, KnBucketOut *out, KnStageTimer *tm);
 // Unstable grouping of a render wave's samples (row layout: row i holds cnt[i] samples in slots i*S ..).
 // out->perm lists slot numbers group by group, in no particular order inside a group or between groups;
 // out->counts / out->offsets are not produced.

@@ -112,9 +112,9 @@ __global__ void __launch_bounds__(DIRECT_WAVES *KN_WAVE) __attribute__((amdgpu_w
 
 // A batch goes unordered when its weight traffic takes less time than ordering does.  The traffic is at most one fetch per
 // point, or per wavefront and network where there are few networks; it was seen at 7 to 8 TB/s, and at 18 where the weights
-// of all networks fit the 4 MB of an XCD's L2.  Ordering costs 28 us with up to 255 networks (one radix pass) and 45 and
-// more with more.  At the border, random points, width 32, fp16: 16,384 points on 16^3 networks 29 us against 62, 32,768
-// (not taken) 55 against 64; 32,768 on 5x8x5 networks 20 against 37.
+// of all networks fit the 4 MB of an XCD's L2.  Ordering costs
+// some 20 us with up to 255 networks, and 35 and more beyond.  At the border, random points, width 32, fp16: 16,384 points on 16^3 networks 29 us against 36, 32,768
+// (not taken) 55 against 36; 16,384 on 5x8x5 networks 15 against 23.
 int kn_direct_lg_points(const kn_scene *sc, int64_t M)
 {
     const int H = sc->desc.hidden;
@@ -126,7 +126,7 @@ int kn_direct_lg_points(const kn_scene *sc, int64_t M)
     const double shares = (double)kn_div_up(M, 1ll << lg), networks = (double)(sc->N < (1 << lg) ? sc->N : 1 << lg);
     const double fetches = fmin((double)M, shares * networks);
     const double us = fetches * (all / sc->N) / (all <= 3e6 ? 18e6 : 8e6);
-    return us <= (sc->N <= 255 ? 28.0 : 45.0) ? lg : -1;
+    return us <= (sc->N <= 255 ? 24.0 : 40.0) ? lg : -1;
 }
 
 int kn_direct_launch(const kn_scene *sc, hipStream_t st, const KnDirectJob &job, hipEvent_t ev_start, hipEvent_t ev_stop)

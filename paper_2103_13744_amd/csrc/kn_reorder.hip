@@ -9,6 +9,8 @@
 // kn_bucket_run (the stage call kn_bucket, the layer-at-a-time and the static-scratch evaluation) sorts (key, index)
 // pairs and leaves the permutation.
 //
+// kn_order_run (kn_eval_grouped, small batches whose order nobody asks for) orders indices by counting, without passes.
+//
 // One pass = (digit, block) count table -> per-digit exclusive scan over the blocks -> stable scatter.  Inside a
 // block, stability comes from ranking each 64-element row of a wavefront with ballot-built peer masks and
 // wave-private counters: no atomics in the ordering path, so the order is the unique stable one.
@@ -425,6 +427,140 @@ __global__ void __launch_bounds__(OT_THREADS)
     }
 }
 
+// Ordering of a batch whose order inside a network nobody asks for: the rank of a point in its network comes from an
+// atomic, so there are no passes.  Latency bound (kn_order_pays says where it is used).  k_rank counts (counts: zeroed N + 1), k_place turns the counts into starts, every
+// workgroup for itself, and writes the list of points and the tiles.
+//   LDS_HIST (few networks, many points in each): a workgroup counts in LDS and takes its share of each network with one
+//   atomic; else one atomic per run of lanes with the same network (11 ns each on one address).
+constexpr int RANK_POINTS = 4; // per thread
+template <bool LDS_HIST>
+__global__ void __launch_bounds__(RO_THREADS)
+    k_rank(const float *__restrict__ pts, int64_t M, KnGrid g, const int32_t *__restrict__ cell_net, int32_t *__restrict__ ids, int32_t N,
+           int32_t *__restrict__ counts, uint2 *__restrict__ ranks, float *__restrict__ sigma, float *__restrict__ rgb)
+{
+    extern __shared__ int32_t hist[]; // N + 1
+    const int lane = threadIdx.x & (KN_WAVE - 1);
+    if constexpr (LDS_HIST) {
+        for (int i = threadIdx.x; i <= N; i += RO_THREADS) hist[i] = 0;
+        __syncthreads();
+    }
+    const int64_t i0 = (int64_t)blockIdx.x * (RO_THREADS * RANK_POINTS) + threadIdx.x;
+    float p[RANK_POINTS][3];
+#pragma unroll
+    for (int r = 0; r < RANK_POINTS; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) p[r][c] = pts[3 * min(i0 + r * RO_THREADS, M - 1) + c];
+    int32_t key[RANK_POINTS], rank[RANK_POINTS];
+#pragma unroll
+    for (int r = 0; r < RANK_POINTS; ++r) {
+        const int64_t i = i0 + r * RO_THREADS;
+        const int32_t id = kn_net_of_cell(cell_net, kn_grid_index(g, p[r][0], p[r][1], p[r][2]));
+        key[r] = i < M ? (id < 0 ? N : id) : -1;
+        if (i < M) {
+            if (ids) ids[i] = id;
+            if (id < 0) { // no network: the result is zero
+                sigma[i] = 0.0f;
+                rgb[3 * i] = rgb[3 * i + 1] = rgb[3 * i + 2] = 0.0f;
+            }
+        }
+        if constexpr (LDS_HIST) {
+            rank[r] = key[r] >= 0 ? atomicAdd(&hist[key[r]], 1) : 0;
+        } else {
+            const int32_t prev = __shfl_up(key[r], 1, KN_WAVE);
+            const unsigned long long heads = __ballot(lane == 0 || prev != key[r]); // bit l: lane l starts a run
+            const int head = KN_WAVE - 1 - __builtin_clzll(heads & (~0ull >> (KN_WAVE - 1 - lane)));
+            const unsigned long long behind = lane == KN_WAVE - 1 ? 0ull : heads >> (lane + 1); // the runs behind this lane
+            const int len = behind ? __builtin_ctzll(behind) + 1 : KN_WAVE - lane;             // (used at the head)
+            int32_t base = 0;
+            if (head == lane && key[r] >= 0) base = atomicAdd(&counts[key[r]], len);
+            rank[r] = __shfl(base, head, KN_WAVE) + lane - head;
+        }
+    }
+    if constexpr (LDS_HIST) {
+        __syncthreads();
+        for (int i = threadIdx.x; i <= N; i += RO_THREADS) {
+            const int32_t c = hist[i];
+            if (c > 0) hist[i] = atomicAdd(&counts[i], c);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < RANK_POINTS; ++r)
+            if (key[r] >= 0) rank[r] += hist[key[r]];
+    }
+#pragma unroll
+    for (int r = 0; r < RANK_POINTS; ++r)
+        if (key[r] >= 0) ranks[i0 + r * RO_THREADS] = make_uint2((uint32_t)key[r], (uint32_t)rank[r]);
+}
+
+// Dynamic LDS: PLACE_WAVES * 64 * per ints, the networks' starts; per: steps of 64 networks per wavefront.
+constexpr int PLACE_THREADS = 1024, PLACE_WAVES = PLACE_THREADS / KN_WAVE, PLACE_POINTS = 2; // points per thread
+__global__ void __launch_bounds__(PLACE_THREADS)
+    k_place(const uint2 *__restrict__ ranks, int64_t M, int32_t N, int32_t per, int32_t tile_len, const int32_t *__restrict__ counts,
+            int32_t *__restrict__ perm, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles, int32_t *__restrict__ n_tiles)
+{
+    extern __shared__ int32_t start[];
+    __shared__ int32_t s_sum[2][PLACE_WAVES];
+    const int lane = threadIdx.x & (KN_WAVE - 1), wv = threadIdx.x / KN_WAVE, b0 = wv * KN_WAVE * per + lane;
+    const int64_t i0 = (int64_t)blockIdx.x * (PLACE_THREADS * PLACE_POINTS) + threadIdx.x;
+    uint2 kr[PLACE_POINTS];
+#pragma unroll
+    for (int r = 0; r < PLACE_POINTS; ++r) kr[r] = ranks[min(i0 + r * PLACE_THREADS, M - 1)];
+    // exclusive starts of the networks inside the wavefront's share, then across wavefronts (tiles: the same sums, kept for
+    // the networks this workgroup writes the tiles of)
+    int32_t sum = 0, tile_sum = 0;
+    for (int s = 0; s < per; ++s) {
+        const int32_t n = b0 + s * KN_WAVE, c = n <= N ? counts[n] : 0;
+        const int32_t inc = kn_wave_inclusive_scan(c);
+        start[n] = sum + inc - c;
+        sum += __builtin_amdgcn_readlane(inc, KN_WAVE - 1);
+        const int32_t t = n < N ? (c + tile_len - 1) / tile_len : 0;
+        tile_sum += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(t), KN_WAVE - 1);
+        if (user_counts && n <= N && blockIdx.x == 0) user_counts[n] = c;
+    }
+    if (lane == 0) {
+        s_sum[0][wv] = sum;
+        s_sum[1][wv] = tile_sum;
+    }
+    __syncthreads();
+    int32_t before = 0, tiles_before = 0, tiles_all = 0;
+    for (int w = 0; w < PLACE_WAVES; ++w) {
+        before += w < wv ? s_sum[0][w] : 0;
+        tiles_before += w < wv ? s_sum[1][w] : 0;
+        tiles_all += s_sum[1][w];
+    }
+    if (before)
+        for (int s = 0; s < per; ++s) start[b0 + s * KN_WAVE] += before;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_tiles = tiles_all;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PLACE_POINTS; ++r) {
+        const int64_t i = i0 + r * PLACE_THREADS;
+        if (i < M) perm[start[kr[r].x] + (int32_t)kr[r].y] = (int32_t)i;
+    }
+    // tiles: those of step s of wavefront w are written by workgroup (w * per + s) % gridDim.x
+    for (int s = 0; s < per; ++s) {
+        const int32_t n = b0 + s * KN_WAVE, c = n <= N ? counts[n] : 0, t = n < N ? (c + tile_len - 1) / tile_len : 0;
+        const int32_t inc = kn_wave_inclusive_scan(t);
+        if ((wv * per + s) % (int)gridDim.x == (int)blockIdx.x) { // (uniform)
+            for (int q = 0; q < KN_WAVE; ++q) {
+                const int32_t tq = __builtin_amdgcn_readlane(t, q), base = tiles_before + __builtin_amdgcn_readlane(inc, q) - tq;
+                const int32_t nq = n - lane + q, cq = __builtin_amdgcn_readlane(c, q);
+                if (tq == 0) continue; // (uniform)
+                const int32_t first = start[nq];
+                for (int32_t k = lane; k < tq; k += KN_WAVE) {
+                    KnTile tl;
+                    tl.net = nq;
+                    tl.start = first + k * tile_len;
+                    tl.len = min(tile_len, cq - k * tile_len);
+                    tl.pad = 0;
+                    tiles[base + k] = tl;
+                }
+            }
+        }
+        tiles_before += __builtin_amdgcn_readlane(inc, KN_WAVE - 1);
+    }
+}
+
 // staging array (r, g, b, sigma per point, caller order) -> the caller's sigma and rgb arrays; 4 points per thread
 __global__ void __launch_bounds__(256) k_split_results(const float *__restrict__ out4, int64_t M, float *__restrict__ sigma, float *__restrict__ rgb)
 {
@@ -549,6 +685,75 @@ int kn_reorder_run(const kn_scene *sc, hipStream_t st, const float *points, cons
     records[0] = (const uint32_t *)sorted_pos;
     records[1] = (const uint32_t *)sorted_dir;
     *out4 = w.out4;
+    return KN_OK;
+}
+
+// ---------------------------------------------------------------------------------------------
+// order without passes
+namespace {
+struct OrderWs {
+    int32_t *counts, *n_tiles, *perm;
+    uint2 *ranks;
+    KnTile *tiles;
+};
+void carve_order(KnCarver &c, int64_t M, int32_t N, OrderWs &w)
+{
+    w.n_tiles = c.carve<int32_t>(1);
+    w.counts = c.carve<int32_t>(N + 1);
+    w.ranks = c.carve<uint2>(M);
+    w.perm = c.carve<int32_t>(M);
+    w.tiles = c.carve<KnTile>(kn_max_tiles(M, N, 64));
+}
+// Every workgroup of k_place scans the counts of all networks, in steps of 1,024: up to eight of them.
+constexpr int32_t ORDER_MAX_N = 8191;
+constexpr int32_t ORDER_LDS_N = 2048; // below: k_rank counts in LDS
+} // namespace
+
+int64_t kn_order_ws_bytes(int64_t M, int32_t N)
+{
+    KnCarver c((void *)256, INT64_MAX / 2);
+    OrderWs w;
+    carve_order(c, M, N, w);
+    return c.used;
+}
+
+// For batches that do not fill the chip with the radix passes' workgroups: four launches instead of nine (six with up to 255
+// networks), and kernels of many small workgroups.  The evaluation then gathers its points and scatters its results, which
+// costs more than moving the samples does once a batch is far larger than the caches.  65,537 points, fp16, width 32:
+// 16^3 networks 65 us -> 38, 10x16x10 61 -> 31, 5x8x5 39 -> 25; fp32 (10x16x10) 77 -> 50.  At the border: 262,144 points on
+// 5x8x5 48 -> 41; 131,072 on 16^3 67 -> 46, 262,144 skewed (not taken: atomics on few addresses) 72 -> 90.
+bool kn_order_pays(const kn_scene *sc, int64_t M)
+{
+    return sc->N <= ORDER_MAX_N && M <= (sc->N < ORDER_LDS_N ? 1ll << 18 : 1ll << 17);
+}
+
+int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_t M, int32_t tile_len, int32_t *user_ids,
+                 int32_t *user_counts, float *sigma, float *rgb, KnCarver &ws, KnBucketOut *out, KnStageTimer *tm)
+{
+    const int32_t N = sc->N;
+    if (M < 1 || M > (1ll << 30) || N < 1 || N > ORDER_MAX_N || tile_len < 64) return KN_E_INVALID_ARG;
+    OrderWs w;
+    carve_order(ws, M, N, w);
+    if (!ws.ok()) return KN_E_WORKSPACE;
+    KN_TRY(kn_fill_i32(st, w.counts, N + 1, 0));
+    const dim3 grid((unsigned)kn_div_up(M, RO_THREADS * RANK_POINTS)), block(RO_THREADS);
+    if (N < ORDER_LDS_N)
+        hipLaunchKernelGGL(k_rank<true>, grid, block, (size_t)(N + 1) * 4, st, points, M, sc->net_grid, sc->cell_net, user_ids, N, w.counts,
+                           w.ranks, sigma, rgb);
+    else
+        hipLaunchKernelGGL(k_rank<false>, grid, block, 0, st, points, M, sc->net_grid, sc->cell_net, user_ids, N, w.counts, w.ranks, sigma,
+                           rgb);
+    KN_CHECK_LAUNCH();
+    if (tm) tm->mark(KN_ST_CELL);
+    const int32_t per = (int32_t)kn_div_up(N + 1, PLACE_THREADS);
+    hipLaunchKernelGGL(k_place, dim3((unsigned)kn_div_up(M, PLACE_THREADS * PLACE_POINTS)), dim3(PLACE_THREADS), (size_t)per * PLACE_THREADS * 4, st,
+                       w.ranks, M, N, per, tile_len, w.counts, w.perm, user_counts, w.tiles, w.n_tiles);
+    KN_CHECK_LAUNCH();
+    out->perm = w.perm;
+    out->counts = w.counts;
+    out->offsets = nullptr;
+    out->tiles = w.tiles;
+    out->n_tiles = w.n_tiles;
     return KN_OK;
 }
 
