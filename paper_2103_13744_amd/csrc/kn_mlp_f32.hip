@@ -293,7 +293,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-        const f4 out = eval_chunk<H>(w, stage[wave], lane, 4);
+        const f4 out = eval_chunk<H>(w, stage[wave], lane, (tl.len + 15) >> 4); // (a small group needs no empty sample tiles)
         __builtin_amdgcn_wave_barrier(); // the staging buffer is rewritten by the next iteration
 
         if (lane < tl.len) {
