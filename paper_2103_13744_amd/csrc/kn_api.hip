@@ -19,7 +19,7 @@ int kn_mlp_mfma_launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &sr
 int kn_mlp_mfma_tile_len(const kn_scene *sc);
 int kn_mlp_f32_tile_len(const kn_scene *sc);
 int kn_mlp_f32_pack_weights(kn_scene *sc, hipStream_t st);
-int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, const KnProbeJob &job);
+int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, const KnProbeRowsJob &job);
 int kn_probe_f32_launch(const kn_scene *sc, hipStream_t st, const KnProbeJob &job);
 int64_t kn_layered_act_bytes(const kn_scene *sc, int64_t M);
 int kn_mlp_layered_launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &src, const KnBucketOut &b, int64_t M,
@@ -839,10 +839,40 @@ __global__ void k_probe_ranges(KnGrid occ, KnGrid net, int32_t *first0, int32_t 
     }
 }
 
+// Set-up of the 16-bit kernels in one launch: workgroups 0..2 find the first probe of every network cell along their axis
+// (KnProbeRowsJob; a search: positions and Eq. 6 are non-decreasing in the probe's number), the others clear the grid.
+__global__ void __launch_bounds__(256) k_probe_rows_setup(KnGrid occ, KnGrid net, int64_t *first0, int64_t *first1, int64_t *first2,
+                                                          uint8_t *bytes, int64_t n)
+{
+    if (blockIdx.x >= 3) {
+        const int64_t i = ((int64_t)(blockIdx.x - 3) * 256 + threadIdx.x) * 16;
+        if (i + 16 <= n && ((uintptr_t)(bytes + i) & 15) == 0) {
+            *(uint4 *)(bytes + i) = make_uint4(0u, 0u, 0u, 0u);
+        } else {
+            for (int64_t j = i; j < n && j < i + 16; ++j) bytes[j] = 0;
+        }
+        return;
+    }
+    const int a = blockIdx.x;
+    int64_t *first = a == 0 ? first0 : (a == 1 ? first1 : first2);
+    for (int c = threadIdx.x; c <= net.res[a]; c += 256) {
+        int64_t lo = 0, hi = 3 * (int64_t)occ.res[a]; // the first probe in cell c or beyond lies in [lo, hi]
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            const int32_t v = (int32_t)(mid / 3);
+            const float cell = floorf((kn_probe_coord(occ, a, v, (int32_t)(mid - 3 * (int64_t)v)) - net.bmin[a]) / net.cell[a]); // Eq. 6
+            if (cell >= (float)c) hi = mid;
+            else lo = mid + 1;
+        }
+        first[c] = lo;
+    }
+}
+
 int64_t extract_ws_bytes(const kn_scene *sc)
 {
+    const int64_t entry = sc->desc.wdtype == KN_F32 ? 4 : 8;
     int64_t b = 0;
-    for (int a = 0; a < 3; ++a) b += kn_align_up(((int64_t)sc->desc.res[a] + 1) * 4, 256);
+    for (int a = 0; a < 3; ++a) b += kn_align_up(((int64_t)sc->desc.res[a] + 1) * entry, 256);
     return b;
 }
 
@@ -870,6 +900,36 @@ extern "C" int kn_extract_occupancy(kn_ctx *ctx, const kn_scene *sc, void *strea
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < extract_ws_bytes(sc)) return KN_E_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     KnCarver ws(workspace, workspace_bytes);
+    KnStageTimer tm(ctx, st);
+    if (sc->desc.wdtype != KN_F32) {
+        KnProbeRowsJob rows{};
+        int64_t *first_probe[3], units = 1;
+        for (int a = 0; a < 3; ++a) {
+            rows.first[a] = first_probe[a] = ws.carve<int64_t>(sc->desc.res[a] + 1);
+            rows.net_res[a] = sc->desc.res[a];
+            const int64_t per_cell = kn_div_up(occ_res[a], sc->desc.res[a]); // voxels
+            units *= a == 0 ? per_cell : (a == 1 ? kn_div_up(per_cell, 5) : kn_div_up(per_cell, 16));
+        }
+        if (!ws.ok()) return KN_E_WORKSPACE;
+        rows.occ = job.occ;
+        rows.cell_net = sc->cell_net;
+        rows.tau = tau;
+        rows.occupancy = occupancy;
+        // several times the workgroups that are resident (1,024 at width 32), each wavefront with two units of work or more
+        int64_t parts = kn_div_up(4096, sc->cells);
+        if (parts > units / 8) parts = units / 8;
+        if (parts < 1) parts = 1;
+        rows.parts = (int32_t)parts;
+        tm.begin();
+        hipLaunchKernelGGL(k_probe_rows_setup, dim3((unsigned)(3 + kn_div_up(kn_div_up(voxels, 16), 256))), dim3(256), 0, st, rows.occ,
+                           sc->net_grid, first_probe[0], first_probe[1], first_probe[2], occupancy, voxels);
+        KN_CHECK_LAUNCH();
+        tm.mark(KN_ST_SETUP);
+        KN_TRY(kn_probe_mfma_launch(sc, st, rows));
+        tm.mark(KN_ST_MLP);
+        tm.add(1, KN_PROBES * voxels, 0, 1);
+        return KN_OK;
+    }
     int32_t *first[3];
     for (int a = 0; a < 3; ++a) first[a] = ws.carve<int32_t>(sc->desc.res[a] + 1);
     if (!ws.ok()) return KN_E_WORKSPACE;
@@ -893,17 +953,13 @@ extern "C" int kn_extract_occupancy(kn_ctx *ctx, const kn_scene *sc, void *strea
     if (parts < 1) parts = 1;
     job.parts = (int32_t)parts;
 
-    KnStageTimer tm(ctx, st);
     tm.begin();
     hipLaunchKernelGGL(k_zero_bytes, dim3((unsigned)kn_div_up(kn_div_up(voxels, 16), 256)), dim3(256), 0, st, occupancy, voxels);
     KN_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_probe_ranges, dim3(3), dim3(256), 0, st, job.occ, job.net, first[0], first[1], first[2]);
     KN_CHECK_LAUNCH();
     tm.mark(KN_ST_SETUP);
-    if (sc->desc.wdtype == KN_F32)
-        KN_TRY(kn_probe_f32_launch(sc, st, job));
-    else
-        KN_TRY(kn_probe_mfma_launch(sc, st, job));
+    KN_TRY(kn_probe_f32_launch(sc, st, job));
     tm.mark(KN_ST_MLP);
     tm.add(1, KN_PROBES * voxels, 0, 1);
     return KN_OK;

@@ -47,6 +47,7 @@
 #include "kn_common.h"
 #include "kn_mlp_core.h"
 #include <hip/hip_ext.h>
+#include <type_traits>
 #include "kn_mlp_shared.h"
 #include "kn_probe.h"
 
@@ -467,130 +468,189 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
 }
 
 
-// Density only, for occupancy extraction (Sec. 3.4): layers 1 and 2 and the density row of layer 3 at the probe
-// points of one network cell's voxels, which are generated in the kernel.  Same formulation as k_mlp_mfma.
+// Density only, for occupancy extraction (Sec. 3.4): layers 1 and 2 and the density row of layer 3 at the probes of one
+// network cell (KnProbeRowsJob).
+//
+// The probes of a cell are a lattice, and gamma(x) is a concatenation of what belongs to x, to y and to z, so layer 1 is a
+// sum of three vectors that depend on one coordinate each.  A wavefront takes the probes of one voxel in x, up to five in
+// y and three tiles of 16 in z: it forms the x and y parts of layer 1 (with the bias) for its 3 x 15 rows first, 16 rows
+// per matrix product, and keeps them in LDS; its z operands stay in registers.  A tile of 16 probes then takes one matrix
+// product per 16 outputs for layer 1, whose accumulator starts at the row's part, and no encoding.  (K = 32 holds what
+// belongs to z: frequencies 0..3 in lane group 0, 4..7 in group 1, 8, 9 and z itself in group 2, nothing in group 3.)
+// The largest density of a voxel's nine rows is kept per lane; a lane marks the voxel of its z.
+//
+// Bound: vector-ALU issue at width 32 (19 instructions per tile, 16 of them the packing of two layers; with the issue of
+// the 5 products 116 cycles, 124 measured), the matrix cores at width 64 (14 products, 224 cycles of 265).  Against
+// encoding every probe and two products more per 16 outputs: 256^3 voxels on 16^3 networks, width 32, fp16 4.18 -> 1.81 ms,
+// width 64, bf16 6.91 -> 3.87; 200x150x100, grids that do not nest (two passes per tile before), 1.96 -> 0.64;
+// 64^3 on 8^3 0.083 -> 0.052.  Five wavefronts per SIMD at width 32 are no faster; width 64 with two 3.96.
+constexpr int PROBE_Y = 5, PROBE_ZT = 3; // voxels in y, tiles of 16 probes in z
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 template <int H, bool BF, int WAVES, bool WRAP>
 __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 4 : 3, H == 32 ? 4 : 3)))
-    k_probe_mfma(const uint16_t *__restrict__ packed, KnProbeJob job)
+    k_probe_mfma(const uint16_t *__restrict__ packed, KnProbeRowsJob job)
 {
     using L = Lay<H>;
-    constexpr int HT = L::HT, HK = L::HK;
-    __shared__ f4 stage[WAVES][4][2][KN_WAVE]; // as in k_mlp_mfma, without the direction
-    const int wave = threadIdx.x / KN_WAVE, lane = threadIdx.x & (KN_WAVE - 1);
+    constexpr int HT = L::HT, HK = L::HK, ROW = 4 * HT + 1; // (padded: 16 rows are written side by side)
+    __shared__ f4 s_row[WAVES][3 * 16][ROW]; // [sub-cell in x, row in y][output / 4]: the row's part of layer 1
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
     const int n = lane & 15, g = lane >> 4;
     const unsigned m3 = (g == 3) ? 0xffffffffu : 0u;
-    const int mrow = n >> 2;
     const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const u4 zero_u4 = {0u, 0u, 0u, 0u};
+    f4(*rows)[ROW] = s_row[wave];
 
     const int32_t cell = blockIdx.x / job.parts, part = blockIdx.x - cell * job.parts;
-    const KnProbeBox box = kn_probe_box(job, cell);
-    if (box.points == 0) return;
-    const int shares = job.parts * WAVES, share = part * WAVES + wave;
-    const int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)share * box.tiles / shares));
-    const int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(share + 1) * box.tiles / shares));
-    if (t_lo >= t_hi) return;
-
-    u4 a1[2 * HT], a2[HT * HK], a_sig[HK];
-    // (width 32: the density block restricted to the rows of sample tile u, made once per network; at width 64 the copies
-    // would cost the third wavefront per SIMD, and the block is masked where it is used)
-    constexpr bool MASKED_COPIES = H == 32;
-    u4 a_sig_of[MASKED_COPIES ? 4 : 1][HK];
-    f4 bias2[HT];
-    float bias_sig = 0.0f;
-    auto load_network = [&](int32_t net) {
-        const u4 *__restrict__ wp = (const u4 *)(packed + (int64_t)net * L::HALFS);
+    const int32_t net = __builtin_amdgcn_readfirstlane(kn_net_of_cell(job.cell_net, cell));
+    if (net < 0) return; // no network: nothing to mark
+    // the cell's probes per axis, counted from the first one of voxel v0: p0 .. p1-1 (uniform, like all numbers of units)
+    int32_t v0[3], p0[3], p1[3];
+    {
+        const int32_t q = cell / job.net_res[2], c[3] = {q / job.net_res[1], q % job.net_res[1], cell % job.net_res[2]};
 #pragma unroll
-        for (int b = 0; b < 2 * HT; ++b) a1[b] = wp[(L::L1 + b) * KN_WAVE + lane];
-#pragma unroll
-        for (int b = 0; b < HT * HK; ++b) a2[b] = wp[(L::L2 + b) * KN_WAVE + lane];
-#pragma unroll
-        for (int kb = 0; kb < HK; ++kb) a_sig[kb] = wp[(L::LS + kb) * KN_WAVE + lane];
-        if constexpr (MASKED_COPIES) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int kb = 0; kb < HK; ++kb) a_sig_of[u][kb] = mrow == u ? a_sig[kb] : zero_u4;
+        for (int a = 0; a < 3; ++a) {
+            const int64_t lo = job.first[a][c[a]], hi = job.first[a][c[a] + 1];
+            if (lo >= hi) return;
+            v0[a] = uniform((int32_t)((uint64_t)lo / 3u));
+            p0[a] = uniform((int32_t)(lo - 3 * (int64_t)v0[a]));
+            p1[a] = uniform((int32_t)(hi - 3 * (int64_t)v0[a]));
         }
-        const float *__restrict__ tail = (const float *)(wp + L::NBLK * KN_WAVE);
-#pragma unroll
-        for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
-        bias_sig = tail[H + 3];
-    };
-    int32_t net_loaded = -1;
+    }
+    const int32_t nvx = (p1[0] + 2) / 3, nvy = (p1[1] + 2) / 3, z_tiles = (p1[2] - p0[2] + 15) / 16;
+    const int32_t y_parts = (nvy + PROBE_Y - 1) / PROBE_Y, z_parts = (z_tiles + PROBE_ZT - 1) / PROBE_ZT;
+    const int64_t units = (int64_t)nvx * y_parts * z_parts;
+    const int shares = job.parts * WAVES, share = part * WAVES + wave;
+    const int32_t u_lo = uniform((int32_t)(share * units / shares)), u_hi = uniform((int32_t)((share + 1) * units / shares));
+    if (u_lo >= u_hi) return;
 
-    // every probe of a voxel in its home cell: one network for the whole box (none: nothing to mark)
-    const int32_t home_net = kn_net_of_cell(job.cell_net, cell);
-    if (job.nested && home_net < 0) return;
-    KnProbeCursor cur = kn_probe_cursor(box, t_lo * KN_WAVE + lane);
-    for (int t = t_lo; t < t_hi; ++t, kn_probe_cursor_step(box, cur)) {
-        const int32_t p = t * KN_WAVE + lane;
-        const bool active = p < box.points; // (beyond the box's last probe the cursor points past the box: unused)
-        float x, y, z;
-        int64_t voxel;
-        const int32_t probe = cur.probe;
-        kn_probe_point(job, box, cur, x, y, z, voxel);
-        const int32_t net = job.nested ? home_net : kn_net_of_cell(job.cell_net, kn_grid_index(job.net, x, y, z));
-        bool todo = active && net >= 0;
-        float sg = 0.0f;
-        {
-            const float p3[3] = {x, y, z};
+    const u4 *__restrict__ wp = (const u4 *)(packed + (int64_t)net * L::HALFS);
+    u4 a_z[HT], a2[HT * HK], a_sig[HK];
+    f4 bias2[HT];
 #pragma unroll
-            for (int a = 0; a < 3; ++a)
-                stage[wave][a][0][lane] = (f4){p3[a] * INV_2PI, p3[a] * (4.0f * INV_2PI), p3[a] * (16.0f * INV_2PI), 0.0f};
-            stage[wave][3][0][lane] = (f4){x * (256.0f * INV_2PI), y * (256.0f * INV_2PI), z * (256.0f * INV_2PI), 0.0f};
-            const u4 ident = {pk<BF>(x, y), pk<BF>(z, 1.0f), 0u, 0u};
-            stage[wave][3][1][lane] = __builtin_bit_cast(f4, ident);
+    for (int t = 0; t < HT; ++t) {
+        // what belongs to z of the slot-order blocks: group 2 of both, and of group 3's part of the second all but x, y, 1
+        const int blk = L::L1 + 2 * t + (g == 0 ? 0 : 1), from = g < 2 ? 32 + n : 48 + n;
+        const u4 w = wp[blk * KN_WAVE + from];
+        a_z[t] = g < 2 ? w : (g == 2 ? (u4){w[0], w[1], 0u, w[3] & 0xffffu} : zero_u4);
+    }
+#pragma unroll
+    for (int b = 0; b < HT * HK; ++b) a2[b] = wp[(L::L2 + b) * KN_WAVE + lane];
+#pragma unroll
+    for (int kb = 0; kb < HK; ++kb) a_sig[kb] = wp[(L::LS + kb) * KN_WAVE + lane]; // (row 3 of every four: all lane groups get the density)
+    const float *__restrict__ tail = (const float *)(wp + L::NBLK * KN_WAVE);
+#pragma unroll
+    for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
+    const f4 bias_sig = {0.0f, 0.0f, 0.0f, tail[H + 3]};
+
+    // unit = (voxel in x, part in y, part in z), z fastest; parts of equal size or one more
+    const int32_t y_each = nvy / y_parts, y_more = nvy % y_parts, z_each = z_tiles / z_parts, z_more = z_tiles % z_parts;
+    int32_t vx = u_lo / (y_parts * z_parts), yp = u_lo / z_parts - vx * y_parts, zp = u_lo % z_parts;
+    for (int32_t unit = u_lo; unit < u_hi; ++unit) {
+        const int32_t ya = yp * y_each + min(yp, y_more), yb = ya + y_each + (yp < y_more ? 1 : 0);
+        const int32_t ta = zp * z_each + min(zp, z_more), tb = ta + z_each + (zp < z_more ? 1 : 0);
+        // (voxels in x and y and probes are counted from v0)
+        const int32_t y_lo = max(3 * ya, p0[1]), y_hi = min(3 * yb, p1[1]);
+        const int32_t x_lo = max(3 * vx, p0[0]), nx = min(3 * vx + 3, p1[0]) - x_lo; // at most 3, and at most 15 rows in y
+        const int32_t z_lo = p0[2] + 16 * ta, z_hi = min(p0[2] + 16 * tb, p1[2]);
+
+        // ---- the rows' parts of layer 1: row n of the unit in lane n
+        {
+            const u4 *wu = wp;
+            asm volatile("" : "+s"(wu)); // (the blocks of x and y are fetched per unit: they would take registers from the tiles)
+            const float y = kn_probe_coord(job.occ, 1, v0[1], min(y_lo + n, y_hi - 1));
+            const float yg = y * (g == 3 ? 256.0f * INV_2PI : INV_2PI);
+            for (int sx = 0; sx < nx; ++sx) {
+                const float x = kn_probe_coord(job.occ, 0, v0[0], x_lo + sx);
+                const float p = g == 0 ? x : (g == 1 ? y : 0.0f);
+                const f4 ang = {g == 3 ? x * (256.0f * INV_2PI) : p * INV_2PI, g == 3 ? yg : p * (4.0f * INV_2PI),
+                                g == 3 ? 0.0f : p * (16.0f * INV_2PI), 0.0f};
+                u4 B[2];
+                encode_position<BF, WRAP>(ang, (u4){pk<BF>(x, y), pk<BF>(0.0f, 1.0f), 0u, 0u}, m3, B);
+                if (g == 2) B[0] = B[1] = zero_u4; // what belongs to z
+                if (g == 3) B[1][0] = B[1][1] = 0u;
+#pragma unroll
+                for (int t = 0; t < HT; ++t) {
+                    f4 acc = mfma<BF>(wu[(L::L1 + 2 * t) * KN_WAVE + lane], B[0], zero4);
+                    acc = mfma<BF>(wu[(L::L1 + 2 * t + 1) * KN_WAVE + lane], B[1], acc);
+                    rows[16 * sx + n][4 * t + g] = acc;
+                }
+            }
+        }
+        // ---- z operands
+        u4 Bz[PROBE_ZT];
+#pragma unroll
+        for (int q = 0; q < PROBE_ZT; ++q) {
+            const float z = kn_probe_coord(job.occ, 2, v0[2], min(z_lo + 16 * q + n, z_hi - 1));
+            // groups 0, 1: frequencies 0..3 / 4..7, with the restarts at 0, 2 and 4 of encode_position; group 2: 8, 9
+            const float r0 = z * (g == 0 ? INV_2PI : (g == 1 ? 16.0f * INV_2PI : 256.0f * INV_2PI));
+            float s[4], m[4];
+            sincos_rev<WRAP>(r0, s[0], m[0]);
+            double_angle(s[0], m[0], s[1], m[1]);
+            float s2, m2;
+            double_angle(s[1], m[1], s[2], m[2]);
+            sincos_rev<WRAP>(z * (4.0f * INV_2PI), s2, m2);
+            if (g == 0) {
+                s[2] = s2;
+                m[2] = m2;
+            }
+            double_angle(s[2], m[2], s[3], m[3]);
+            Bz[q] = (u4){pk<BF>(s[0], m[0]), pk<BF>(s[1], m[1]), pk<BF>(s[2], m[2]), pk<BF>(s[3], m[3])};
+            if (g >= 2) Bz[q] = (u4){Bz[q][0], Bz[q][1], 0u, pk<BF>(z, 0.0f)}; // (group 3 meets zero weights)
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-        // One pass per network met in the tile: a single pass when the grids nest, a second one for the probes
-        // of voxels that reach into a neighbouring cell otherwise.
-        for (;;) {
-            const unsigned long long pending = __ballot(todo);
-            if (pending == 0ull) break;
-            const int32_t nsel = __builtin_amdgcn_readlane(net, (int)__builtin_ctzll(pending));
-            if (nsel != net_loaded) {
-                load_network(nsel);
-                net_loaded = nsel;
+        // ---- tiles: voxel by voxel in y
+        const int tiles = tb - ta;
+        auto unit_tiles = [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;
+            for (int32_t vy = ya; vy < yb; ++vy) {
+                const int r0 = max(3 * vy, y_lo) - y_lo, r1 = min(3 * vy + 3, y_hi) - y_lo;
+                float top[PROBE_ZT] = {0.0f, 0.0f, 0.0f};
+                for (int sx = 0; sx < nx; ++sx)
+                    for (int r = r0; r < r1; ++r) {
+                        f4 part1[HT];
+#pragma unroll
+                        for (int t = 0; t < HT; ++t) part1[t] = rows[16 * sx + r][4 * t + g];
+#pragma unroll
+                        for (int q = 0; q < NT; ++q) {
+                            f4 acc[HT];
+                            u4 Bh[HK];
+#pragma unroll
+                            for (int t = 0; t < HT; ++t) acc[t] = mfma<BF>(a_z[t], Bz[q], part1[t]);
+                            pack_acts<H, BF, true>(acc, Bh);
+#pragma unroll
+                            for (int t = 0; t < HT; ++t) {
+                                acc[t] = bias2[t];
+#pragma unroll
+                                for (int kb = 0; kb < HK; ++kb) acc[t] = mfma<BF>(a2[t * HK + kb], Bh[kb], acc[t]);
+                            }
+                            pack_acts<H, BF, true>(acc, Bh);
+                            f4 out = bias_sig;
+#pragma unroll
+                            for (int kb = 0; kb < HK; ++kb) out = mfma<BF>(a_sig[kb], Bh[kb], out);
+                            top[q] = fmaxf(top[q], out[3]);
+                        }
+                    }
+                // lane group q holds the same values as the others and marks for tile q
+                const float mine = g == 0 ? top[0] : (g == 1 ? top[1] : top[2]);
+                const int32_t iz = z_lo + lane;
+                if (mine > job.tau && iz < z_hi)
+                    job.occupancy[((int64_t)(v0[0] + vx) * job.occ.res[1] + (v0[1] + vy)) * job.occ.res[2] + v0[2] + (int32_t)((uint32_t)iz / 3u)] = 1;
             }
-            f4 out = {0.0f, 0.0f, 0.0f, bias_sig};
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const f4 ang = stage[wave][g][0][16 * u + n];
-                const u4 ident = __builtin_bit_cast(u4, stage[wave][g][1][16 * u + n]);
-                u4 Bx[2];
-                encode_position<BF, WRAP>(ang, ident, m3, Bx);
-                f4 acc[HT];
-                u4 Bh[HK];
-#pragma unroll
-                for (int t2 = 0; t2 < HT; ++t2) {
-                    acc[t2] = mfma<BF>(a1[2 * t2], Bx[0], zero4);
-                    acc[t2] = mfma<BF>(a1[2 * t2 + 1], Bx[1], acc[t2]);
-                }
-                pack_acts<H, BF, true>(acc, Bh);
-#pragma unroll
-                for (int t2 = 0; t2 < HT; ++t2) {
-                    acc[t2] = bias2[t2];
-#pragma unroll
-                    for (int kb = 0; kb < HK; ++kb) acc[t2] = mfma<BF>(a2[t2 * HK + kb], Bh[kb], acc[t2]);
-                }
-                pack_acts<H, BF, true>(acc, Bh);
-#pragma unroll
-                for (int kb = 0; kb < HK; ++kb) {
-                    if constexpr (MASKED_COPIES) out = mfma<BF>(a_sig_of[u][kb], Bh[kb], out);
-                    else out = mfma<BF>(mrow == u ? a_sig[kb] : zero_u4, Bh[kb], out);
-                }
-            }
-            if (todo && net == nsel) {
-                sg = fmaxf(out[3], 0.0f);
-                todo = false;
+        };
+        if (tiles == 3) unit_tiles(std::integral_constant<int, 3>{});
+        else if (tiles == 2) unit_tiles(std::integral_constant<int, 2>{});
+        else unit_tiles(std::integral_constant<int, 1>{});
+        __builtin_amdgcn_wave_barrier(); // the rows are rewritten by the next unit
+        if (++zp == z_parts) {
+            zp = 0;
+            if (++yp == y_parts) {
+                yp = 0;
+                ++vx;
             }
         }
-        __builtin_amdgcn_wave_barrier(); // the staging buffer is rewritten by the next iteration
-        kn_probe_mark(job, active, sg > job.tau, voxel, probe, lane);
     }
 }
 
@@ -841,7 +901,7 @@ int kn_mlp_pack_weights(kn_scene *sc, hipStream_t st)
     return overflow ? KN_E_UNSUPPORTED : KN_OK;
 }
 
-int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, const KnProbeJob &job)
+int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, const KnProbeRowsJob &job)
 {
     const bool bf = sc->desc.wdtype == KN_BF16;
     const int H = sc->desc.hidden;

@@ -1,5 +1,5 @@
-// Occupancy grid extraction (Sec. 3.4, "Empty Space Skipping"): work decomposition shared by the 16-bit and the
-// fp32 density kernels.
+// Occupancy grid extraction (Sec. 3.4, "Empty Space Skipping"): work decomposition of the fp32 kernel (KnProbeJob) and of
+// the 16-bit kernels (KnProbeRowsJob, at the end).
 //
 // Every voxel of the grid being filled is probed at the 27 sub-cell centres of a 3x3x3 subgrid,
 // x = bmin + (v + c) * cell per axis with c in {1/6, 1/2, 5/6}, evaluated as fmaf((float)v + c, cell, bmin); the voxel
@@ -123,4 +123,24 @@ __device__ __forceinline__ void kn_probe_mark(const KnProbeJob &j, bool active, 
         const unsigned long long bits = (mask >> lane) & ((1ull << len) - 1ull);
         if (bits) j.occupancy[voxel] = 1;
     }
+}
+
+// 16-bit kernels.  Probe i = 3 v + s of an axis (s-th sub-cell centre of voxel v) sits at kn_probe_coord, whatever the other
+// axes' probes are, and Eq. 6 is per axis as well: the probes of axis a that lie in network cell c are first[a][c] ..
+// first[a][c+1]-1 (positions and Eq. 6 are non-decreasing in i), and the probes of a cell are the box of its three ranges,
+// all of one network, whether or not the grids nest.
+struct KnProbeRowsJob {
+    KnGrid occ;              // the grid being filled
+    int32_t net_res[3];      // the network grid
+    const int32_t *cell_net; // as in KnProbeJob
+    const int64_t *first[3]; // device, net_res[a] + 1 entries per axis
+    int32_t parts;           // workgroups per network cell
+    float tau;
+    uint8_t *occupancy;      // device, occ.res[0]*[1]*[2] bytes, zero before the launch
+};
+// probe i of the axis, counted from the first one of voxel v0 (i >= 0)
+__device__ __forceinline__ float kn_probe_coord(const KnGrid &occ, int axis, int32_t v0, int32_t i)
+{
+    const int32_t v = (int32_t)((uint32_t)i / 3u), s = i - 3 * v;
+    return fmaf((float)(v0 + v) + (s == 0 ? 1.0f / 6.0f : (s == 1 ? 0.5f : 5.0f / 6.0f)), occ.cell[axis], occ.bmin[axis]);
 }
