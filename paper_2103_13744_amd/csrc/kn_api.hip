@@ -642,8 +642,10 @@ static int64_t index_ws_bytes(const kn_scene *sc, int64_t M)
 // ... and of kn_eval_grouped, which moves the samples themselves
 static int64_t eval_ws_bytes(const kn_scene *sc, int64_t M)
 {
-    const int64_t a = index_ws_bytes(sc, M), b = kn_reorder_ws_bytes(M, sc->N), c = kn_order_ws_bytes(M, sc->N);
-    return a > b ? (a > c ? a : c) : (b > c ? b : c);
+    const int64_t a = index_ws_bytes(sc, M), b = kn_reorder_ws_bytes(M, sc->N), c = kn_order_ws_bytes(M, sc->N),
+                  d = kn_count_ws_bytes(M, sc->N);
+    const int64_t ab = a > b ? a : b, cd = c > d ? c : d;
+    return ab > cd ? ab : cd;
 }
 
 extern "C" int kn_workspace_bytes(const kn_ctx *ctx, const kn_scene *sc, int64_t max_points, int64_t max_rays,
@@ -696,7 +698,10 @@ static int eval_grouped_impl(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, co
         KnBucketOut bo;
         const uint32_t *records[2] = {nullptr, nullptr};
         float *out4 = nullptr;
-        KN_TRY(kn_reorder_run(sc, st, points, dirs, M, kn_mlp_tile_len(sc), cell_id, counts, perm, ws, &bo, records, &out4, &tm));
+        if (!perm && kn_count_pays(M, sc->N))
+            KN_TRY(kn_count_run(sc, st, points, dirs, M, kn_mlp_tile_len(sc), cell_id, counts, ws, &bo, records, &out4, &tm));
+        else
+            KN_TRY(kn_reorder_run(sc, st, points, dirs, M, kn_mlp_tile_len(sc), cell_id, counts, perm, ws, &bo, records, &out4, &tm));
         tm.mark(KN_ST_BUCKET);
         KnSampleSrc src{};
         src.records = records[0];

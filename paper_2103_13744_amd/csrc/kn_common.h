@@ -293,6 +293,12 @@ int64_t kn_order_ws_bytes(int64_t M, int32_t N);
 bool kn_order_pays(const kn_scene *sc, int64_t M);
 int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_t M, int32_t tile_len, int32_t *user_ids,
                  int32_t *user_counts, float *sigma, float *rgb, KnCarver &ws, KnBucketOut *out, KnStageTimer *tm);
+// kn_reorder_run without an order inside a network (no permutation is left), in fewer trips: where kn_count_pays.
+int64_t kn_count_ws_bytes(int64_t M, int32_t N); // 0 where it does not
+bool kn_count_pays(int64_t M, int32_t N);
+int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,
+                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, const uint32_t *records[2], float **out4,
+                 KnStageTimer *tm);
 // Unstable grouping of a render wave's samples (row layout: row i holds cnt[i] samples in slots i*S ..).
 // out->perm lists slot numbers group by group, in no particular order inside a group or between groups;
 // out->counts / out->offsets are not produced.

@@ -9,7 +9,8 @@
 // kn_bucket_run (the stage call kn_bucket, the layer-at-a-time and the static-scratch evaluation) sorts (key, index)
 // pairs and leaves the permutation.
 //
-// kn_order_run (kn_eval_grouped, small batches whose order nobody asks for) orders indices by counting, without passes.
+// kn_order_run and kn_count_run (kn_eval_grouped where nobody asks for the permutation) order by counting, without passes:
+// the first indices (batches of up to some 10^5 points), the second the samples.
 //
 // One pass = (digit, block) count table -> per-digit exclusive scan over the blocks -> stable scatter.  Inside a
 // block, stability comes from ranking each 64-element row of a wavefront with ballot-built peer masks and
@@ -561,6 +562,240 @@ __global__ void __launch_bounds__(PLACE_THREADS)
     }
 }
 
+// Order by counting with the samples themselves (kn_eval_grouped, large batches whose permutation nobody asks for): one
+// trip of the samples instead of one per digit.  A workgroup of T threads takes T * CO_ROWS consecutive points.
+//   k_keys_count    network of each point, the workgroup's count per network (LDS) -> row of the (workgroup, network) table
+//   k_table_scan    per network exclusive prefix over the workgroups, totals
+//   k_count_scatter the workgroup's samples into sorted order in LDS (a sample's rank comes from an LDS atomic), then to
+//                   memory; every workgroup forms the networks' starts from the totals for itself and writes its share of
+//                   the tiles
+// A workgroup has about two samples per network with 4,096 networks, 32 bytes of each half side by side: the runs of one
+// network follow each other by workgroup, so an XCD takes one contiguous part of the batch, and its workgroups, which go
+// through the networks at the same pace, fill the lines in its L2 together.
+// Bound by memory traffic: 4 M points, 16^3 networks: count 22 us, scan 8, scatter 70 (232 MB, 3.3 TB/s), against 158 for the
+// two radix passes and 10 for the search for the tiles.  Whole calls, width 32, fp16: 4 M points 322 -> 245 us, 10x16x10
+// networks 313 -> 215; 8 M 584 -> 470; 1 M 106 -> 76; 262,143 73 -> 57.
+constexpr int CO_ROWS = 8;
+// COUNT_MAX_N: the staging buffer of 1,024 threads (128 KB) and the networks' starts are the LDS of a compute unit.
+// COUNT_WIDE_M: 1,024 threads from where their workgroups nearly fill the chip (1.3 M points 99 us with 512, 1.4 M 89 with 1,024).
+// COUNT_MIN_N: with up to 255 networks the radix sort is one trip as well.  COUNT_MIN_M: kn_order_pays.
+constexpr int32_t COUNT_MIN_N = 256, COUNT_MAX_N = 6143;
+constexpr int64_t COUNT_MIN_M = 1 << 17, COUNT_WIDE_M = 5 << 18;
+typedef uint16_t h4_t __attribute__((ext_vector_type(4)));
+
+// (the same numbering in both kernels: row b of the table)
+__device__ __forceinline__ int32_t xcd_block(int32_t nblk)
+{
+    const int32_t x = blockIdx.x & 7, each = nblk >> 3, more = nblk & 7;
+    return x * each + min(x, more) + ((int32_t)blockIdx.x >> 3);
+}
+
+template <int T>
+__global__ void __launch_bounds__(T)
+    k_keys_count(const float *__restrict__ pts, int64_t M, KnGrid g, const int32_t *__restrict__ cell_net, int32_t *__restrict__ ids,
+                 uint16_t *__restrict__ keys, int32_t N, int32_t nblk, int32_t *__restrict__ table, float *__restrict__ out4)
+{
+    extern __shared__ int32_t hist[]; // N + 1
+    for (int i = threadIdx.x; i <= N; i += T) hist[i] = 0;
+    __syncthreads();
+    const int32_t b = xcd_block(nblk);
+    auto point = [&](int64_t i, float x, float y, float z) -> uint16_t {
+        const int32_t id = kn_net_of_cell(cell_net, kn_grid_index(g, x, y, z));
+        const int32_t key = id < 0 ? N : id;
+        if (ids) ids[i] = id;
+        if (id < 0) *(float4 *)(out4 + 4 * i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f); // no network: the result is zero
+        atomicAdd(&hist[key], 1);
+        return (uint16_t)key;
+    };
+    const int64_t base = (int64_t)b * (T * CO_ROWS);
+    if (base + T * CO_ROWS <= M && ((uintptr_t)pts & 15) == 0) { // (uniform) four points per thread and step, 16-byte loads
+        float4 v[CO_ROWS / 4][3];
+#pragma unroll
+        for (int r = 0; r < CO_ROWS / 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[r][c] = *(const float4 *)(pts + 3 * (base + 4 * (r * T + (int)threadIdx.x)) + 4 * c);
+#pragma unroll
+        for (int r = 0; r < CO_ROWS / 4; ++r) {
+            const int64_t i = base + 4 * (r * T + (int)threadIdx.x);
+            const float4 p = v[r][0], q = v[r][1], s = v[r][2];
+            h4_t k;
+            k[0] = point(i, p.x, p.y, p.z);
+            k[1] = point(i + 1, p.w, q.x, q.y);
+            k[2] = point(i + 2, q.z, q.w, s.x);
+            k[3] = point(i + 3, s.y, s.z, s.w);
+            *(h4_t *)(keys + i) = k;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < CO_ROWS; ++r) {
+            const int64_t i = base + r * T + threadIdx.x;
+            if (i < M) keys[i] = point(i, pts[3 * i], pts[3 * i + 1], pts[3 * i + 2]);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i <= N; i += T) table[(int64_t)b * (N + 1) + i] = hist[i];
+}
+
+// 32 networks per workgroup, 32 shares of the table's rows
+__global__ void __launch_bounds__(1024) k_table_scan(int32_t *__restrict__ table, int32_t bins, int32_t nblk, int32_t *__restrict__ totals)
+{
+    __shared__ int32_t part[32][33];
+    const int lane = threadIdx.x & 31, seg = threadIdx.x >> 5;
+    const int32_t d = blockIdx.x * 32 + lane;
+    const int32_t each = (nblk + 31) / 32, r0 = min(seg * each, nblk), r1 = min(r0 + each, nblk);
+    const bool has = d < bins;
+    int32_t *col = table + (has ? d : bins - 1);
+    constexpr int KEPT = 32; // rows of a share that stay in registers between the two sweeps (all loads in flight together)
+    int32_t v[KEPT], sum = 0, run = 0;
+#pragma unroll
+    for (int k = 0; k < KEPT; ++k) v[k] = r0 + k < r1 ? col[(int64_t)(r0 + k) * bins] : 0;
+#pragma unroll
+    for (int k = 0; k < KEPT; ++k) sum += v[k];
+    for (int32_t r = r0 + KEPT; r < r1; ++r) sum += col[(int64_t)r * bins];
+    part[seg][lane] = sum;
+    __syncthreads();
+    for (int q = 0; q < seg; ++q) run += part[q][lane];
+    if (!has) return;
+    if (seg == 31) totals[d] = run + sum;
+#pragma unroll
+    for (int k = 0; k < KEPT; ++k) {
+        if (r0 + k < r1) col[(int64_t)(r0 + k) * bins] = run;
+        run += v[k];
+    }
+    for (int32_t r = r0 + KEPT; r < r1; ++r) {
+        const int32_t c = col[(int64_t)r * bins];
+        col[(int64_t)r * bins] = run;
+        run += c;
+    }
+}
+
+// Dynamic LDS: T * CO_ROWS halves of 16 bytes (first the counts), then N + 1 ints.
+// networks whose tiles one workgroup writes, at most: network d is workgroup d % nblk's
+constexpr int co_list(int threads)
+{
+    const int64_t min_m = threads == 512 ? COUNT_MIN_M : COUNT_WIDE_M, min_blocks = min_m / (threads * CO_ROWS);
+    return (int)((COUNT_MAX_N + min_blocks) / min_blocks);
+}
+static_assert((COUNT_MAX_N + 1) * 4 <= 512 * CO_ROWS * 16, "the counts share the staging buffer's place");
+template <int T>
+__global__ void __launch_bounds__(T)
+    k_count_scatter(const uint16_t *__restrict__ keys, const float *__restrict__ pts, const float *__restrict__ dirs, u4 *__restrict__ pout,
+                    u4 *__restrict__ dout, int64_t M, int32_t N, int32_t nblk, const int32_t *__restrict__ table,
+                    const int32_t *__restrict__ totals, int32_t tile_len, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles,
+                    int32_t *__restrict__ n_tiles)
+{
+    extern __shared__ u4 stage[];
+    __shared__ int32_t s_sum[3][T / KN_WAVE];
+    __shared__ int4 s_list[co_list(T)]; // (network, samples, first sample, first tile)
+    __shared__ int32_t s_listed;
+    int32_t *cnt = (int32_t *)stage, *delta = (int32_t *)(stage + T * CO_ROWS);
+    const int lane = threadIdx.x & (KN_WAVE - 1), wv = threadIdx.x / KN_WAVE;
+    const int32_t b = xcd_block(nblk), bins = N + 1;
+    const int64_t base = (int64_t)b * (T * CO_ROWS);
+    const int32_t n_here = (int32_t)min((int64_t)(T * CO_ROWS), M - base);
+    if (threadIdx.x == 0) s_listed = 0;
+    for (int i = threadIdx.x; i < bins; i += T) cnt[i] = 0;
+    uint32_t key[CO_ROWS];
+    float p[CO_ROWS][3];
+#pragma unroll
+    for (int r = 0; r < CO_ROWS; ++r) {
+        const int64_t i = base + min(r * T + (int)threadIdx.x, n_here - 1);
+        key[r] = keys[i];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) p[r][c] = pts[3 * i + c];
+    }
+    __syncthreads();
+    int32_t lpos[CO_ROWS];
+#pragma unroll
+    for (int r = 0; r < CO_ROWS; ++r) lpos[r] = r * T + (int)threadIdx.x < n_here ? atomicAdd(&cnt[key[r]], 1) : 0;
+    __syncthreads();
+    // thread t: networks t * per ..; sums in front of them of the workgroup's samples, of all samples and of tiles
+    const int32_t per = (bins + T - 1) / T, d0 = min((int32_t)threadIdx.x * per, bins), d1 = min(d0 + per, bins);
+    int32_t own[3] = {0, 0, 0}, run[3];
+    for (int32_t d = d0; d < d1; ++d) {
+        const int32_t c = totals[d];
+        own[0] += cnt[d];
+        own[1] += c;
+        own[2] += d < N ? (c + tile_len - 1) / tile_len : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        run[q] = kn_wave_inclusive_scan(own[q]);
+        if (lane == KN_WAVE - 1) s_sum[q][wv] = run[q];
+        run[q] -= own[q];
+    }
+    __syncthreads();
+    int32_t tiles_all = 0;
+    for (int w = 0; w < T / KN_WAVE; ++w) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) run[q] += w < wv ? s_sum[q][w] : 0;
+        tiles_all += s_sum[2][w];
+    }
+    if (b == 0 && threadIdx.x == 0) *n_tiles = tiles_all;
+    for (int32_t d = d0; d < d1; ++d) {
+        const int32_t c = totals[d], n_t = d < N ? (c + tile_len - 1) / tile_len : 0, mine = cnt[d];
+        delta[d] = run[1] + table[(int64_t)b * bins + d] - run[0];
+        cnt[d] = run[0];
+        if (n_t > 0 && d % nblk == b) s_list[atomicAdd(&s_listed, 1)] = make_int4(d, c, run[1], run[2]);
+        if (user_counts && b == 0) user_counts[d] = c;
+        run[0] += mine;
+        run[1] += c;
+        run[2] += n_t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < CO_ROWS; ++r) lpos[r] += cnt[key[r]];
+    __syncthreads(); // the counts' place is the staging buffer's from here on
+#pragma unroll
+    for (int r = 0; r < CO_ROWS; ++r)
+        if (r * T + (int)threadIdx.x < n_here)
+            stage[lpos[r]] = (u4){__float_as_uint(p[r][0]), __float_as_uint(p[r][1]), __float_as_uint(p[r][2]), key[r]};
+#pragma unroll
+    for (int r = 0; r < CO_ROWS; ++r) { // (the second halves are under way while the first ones are written)
+        const int64_t i = base + min(r * T + (int)threadIdx.x, n_here - 1);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) p[r][c] = dirs[3 * i + c];
+    }
+    __syncthreads();
+    int32_t dst[CO_ROWS];
+#pragma unroll
+    for (int k = 0; k < CO_ROWS; ++k) {
+        const int32_t sp = k * T + threadIdx.x;
+        if (sp < n_here) {
+            const u4 v = stage[sp];
+            dst[k] = sp + delta[v[3]];
+            pout[dst[k]] = v;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < CO_ROWS; ++r)
+        if (r * T + (int)threadIdx.x < n_here)
+            stage[lpos[r]] = (u4){__float_as_uint(p[r][0]), __float_as_uint(p[r][1]), __float_as_uint(p[r][2]), (uint32_t)(base + r * T + threadIdx.x)};
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CO_ROWS; ++k) {
+        const int32_t sp = k * T + threadIdx.x;
+        if (sp < n_here) dout[dst[k]] = stage[sp];
+    }
+    // tiles: a wavefront per network, the whole workgroup for networks of more than one tile per lane
+    const int32_t listed = s_listed;
+    for (int pass = 0; pass < 2; ++pass)
+        for (int e = pass == 0 ? wv : 0; e < listed; e += pass == 0 ? T / KN_WAVE : 1) {
+            const int4 l = s_list[e];
+            const int32_t n_t = (l.y + tile_len - 1) / tile_len;
+            if ((n_t > KN_WAVE) != (pass == 1)) continue;
+            for (int32_t k = pass == 0 ? lane : (int)threadIdx.x; k < n_t; k += pass == 0 ? KN_WAVE : T) {
+                KnTile tl;
+                tl.net = l.x;
+                tl.start = l.z + k * tile_len;
+                tl.len = min(tile_len, l.y - k * tile_len);
+                tl.pad = 0;
+                tiles[l.w + k] = tl;
+            }
+        }
+}
+
 // staging array (r, g, b, sigma per point, caller order) -> the caller's sigma and rgb arrays; 4 points per thread
 __global__ void __launch_bounds__(256) k_split_results(const float *__restrict__ out4, int64_t M, float *__restrict__ sigma, float *__restrict__ rgb)
 {
@@ -721,10 +956,11 @@ int64_t kn_order_ws_bytes(int64_t M, int32_t N)
 // networks), and kernels of many small workgroups.  The evaluation then gathers its points and scatters its results, which
 // costs more than moving the samples does once a batch is far larger than the caches.  65,537 points, fp16, width 32:
 // 16^3 networks 65 us -> 38, 10x16x10 61 -> 31, 5x8x5 39 -> 25; fp32 (10x16x10) 77 -> 50.  At the border: 262,144 points on
-// 5x8x5 48 -> 41; 131,072 on 16^3 67 -> 46, 262,144 skewed (not taken: atomics on few addresses) 72 -> 90.
+// 5x8x5 48 -> 41; with more networks than 255 against kn_count_run: 131,000 on 16^3 55 against 61, 180,000 58 against 59;
+// 10x16x10 38 against 41 and 42 against 41, 262,143 51 against 43.
 bool kn_order_pays(const kn_scene *sc, int64_t M)
 {
-    return sc->N <= ORDER_MAX_N && M <= (sc->N < ORDER_LDS_N ? 1ll << 18 : 1ll << 17);
+    return sc->N <= ORDER_MAX_N && M <= (sc->N < COUNT_MIN_N ? 1ll << 18 : 1ll << 17);
 }
 
 int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_t M, int32_t tile_len, int32_t *user_ids,
@@ -754,6 +990,75 @@ int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_
     out->offsets = nullptr;
     out->tiles = w.tiles;
     out->n_tiles = w.n_tiles;
+    return KN_OK;
+}
+
+// ---------------------------------------------------------------------------------------------
+// order by counting, samples moved
+namespace {
+struct CountWs {
+    int32_t *n_tiles, *totals, *table;
+    uint16_t *keys;
+    KnTile *tiles;
+    u4 *pos, *dir;
+    float *out4;
+    int32_t threads, nblk;
+};
+void carve_count(KnCarver &c, int64_t M, int32_t N, CountWs &w)
+{
+    w.threads = M > COUNT_WIDE_M ? 1024 : 512;
+    w.nblk = (int32_t)kn_div_up(M, w.threads * CO_ROWS);
+    w.n_tiles = c.carve<int32_t>(1);
+    w.totals = c.carve<int32_t>(N + 1);
+    w.table = c.carve<int32_t>((int64_t)w.nblk * (N + 1));
+    w.keys = c.carve<uint16_t>(M);
+    w.tiles = c.carve<KnTile>(kn_max_tiles(M, N, 64));
+    w.pos = c.carve<u4>(M);
+    w.dir = c.carve<u4>(M);
+    w.out4 = c.carve<float>(4 * M);
+}
+} // namespace
+
+bool kn_count_pays(int64_t M, int32_t N) { return N >= COUNT_MIN_N && N <= COUNT_MAX_N && M >= COUNT_MIN_M; }
+
+int64_t kn_count_ws_bytes(int64_t M, int32_t N)
+{
+    if (!kn_count_pays(M, N)) return 0;
+    KnCarver c((void *)256, INT64_MAX / 2);
+    CountWs w;
+    carve_count(c, M, N, w);
+    return c.used;
+}
+
+int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,
+                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, const uint32_t *records[2], float **out4,
+                 KnStageTimer *tm)
+{
+    const int32_t N = sc->N;
+    if (!kn_count_pays(M, N) || M > (1ll << 30) || tile_len < 64) return KN_E_INVALID_ARG;
+    CountWs w;
+    carve_count(ws, M, N, w);
+    if (!ws.ok()) return KN_E_WORKSPACE;
+    const dim3 grid((unsigned)w.nblk), block((unsigned)w.threads);
+    const size_t bins = (size_t)(N + 1) * 4;
+    auto count = w.threads == 1024 ? k_keys_count<1024> : k_keys_count<512>;
+    auto scatter = w.threads == 1024 ? k_count_scatter<1024> : k_count_scatter<512>;
+    hipLaunchKernelGGL(count, grid, block, bins, st, points, M, sc->net_grid, sc->cell_net, user_ids, w.keys, N, w.nblk, w.table, w.out4);
+    KN_CHECK_LAUNCH();
+    if (tm) tm->mark(KN_ST_CELL);
+    hipLaunchKernelGGL(k_table_scan, dim3((unsigned)kn_div_up(N + 1, 32)), dim3(1024), 0, st, w.table, N + 1, w.nblk, w.totals);
+    KN_CHECK_LAUNCH();
+    hipLaunchKernelGGL(scatter, grid, block, (size_t)w.threads * CO_ROWS * sizeof(u4) + bins, st, w.keys, points, dirs, w.pos, w.dir, M, N,
+                       w.nblk, w.table, w.totals, tile_len, user_counts, w.tiles, w.n_tiles);
+    KN_CHECK_LAUNCH();
+    out->perm = nullptr; // the records are the sorted list
+    out->counts = w.totals;
+    out->offsets = nullptr;
+    out->tiles = w.tiles;
+    out->n_tiles = w.n_tiles;
+    records[0] = (const uint32_t *)w.pos;
+    records[1] = (const uint32_t *)w.dir;
+    *out4 = w.out4;
     return KN_OK;
 }
 
@@ -853,5 +1158,8 @@ int kn_reorder_configure()
     const int bytes = (int)(RO_TILE * sizeof(u4));
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<true>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    const int counts = (COUNT_MAX_N + 1) * 4;
+    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<512>, hipFuncAttributeMaxDynamicSharedMemorySize, 512 * CO_ROWS * 16 + counts));
+    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, 1024 * CO_ROWS * 16 + counts));
     return KN_OK;
 }

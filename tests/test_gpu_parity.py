@@ -294,6 +294,38 @@ def test_eval_grouped_without_aux_equals_the_ordered_batch(wdtype, H, res, M):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
+@pytest.mark.parametrize("wdtype,H,res,M", [
+    ("f16", 32, (10, 16, 10), 65537), ("f32", 32, (16, 16, 16), 131071),                    # indices ordered by counting
+    ("f16", 32, (16, 16, 16), 131073), ("f32", 32, (16, 16, 16), 140000), ("bf16", 64, (4, 8, 8), 300001),  # samples moved, 512 threads
+    ("f16", 32, (16, 16, 16), 5 << 18), ("bf16", 32, (17, 19, 19), (5 << 18) + 1), ("f16", 64, (16, 16, 16), 2100003)])  # 1,024
+@pytest.mark.parametrize("spread", ["all over", "one network", "none"])
+def test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread):
+    """Batches ordered by counting: results, ids and counts are those of the call that reports the permutation."""
+    import torch
+    log("eval by counting", wdtype, H, res, M, spread)
+    dev, _ = make_pair(scene_dict(res, (-1, -1, -1), (1, 1, 1), H, wdtype, 24))
+    pts, dirs = cuda(ks.uniform_points(M, 33, lo=(-1.02,) * 3, hi=(1.02,) * 3)), cuda(ks.sphere_dirs(M, 34))
+    if spread == "one network":
+        pts[5:] = 0.01 + 0.1 / max(res) * pts[5:].abs()
+    if spread == "none":
+        pts += 3.0
+    pts[M // 3, 1] = float("nan")
+    want = dev.eval_grouped(pts, dirs, want_aux=True)
+    out = (torch.full((M,), -7.0, device="cuda"), torch.full((M, 3), -7.0, device="cuda"))
+    got = dev.eval_grouped(pts, dirs, out=out)
+    if wdtype == "f32":     # (as above)
+        assert torch.allclose(got[0], want[0], rtol=1e-5, atol=1e-6) and torch.allclose(got[1], want[1], rtol=1e-5, atol=1e-6)
+    else:
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    ids, counts = torch.full_like(want[2], -9), torch.full_like(want[3], -9)
+    from paper_2103_13744_amd import _check, _ptr, _stream
+    ws = dev._workspace(max_points=M, ctx=None)
+    _check(dev.L.kn_eval_grouped(dev._ctx(None), dev.h, _stream(), _ptr(pts), _ptr(dirs), M, _ptr(out[0]), _ptr(out[1]), _ptr(ids),
+                                 _ptr(counts), None, _ptr(ws), ws.numel()), "kn_eval_grouped")
+    assert torch.equal(ids, want[2]) and torch.equal(counts, want[3])
+    assert torch.equal(got[0], out[0]) and torch.equal(got[1], out[1])
+
+
 def test_eval_grouped_empty_and_permutation_invariance():
     import torch
     sc = scene_dict((4, 4, 4), (0, 0, 0), (1, 1, 1), 32, "f16", 9)
