@@ -296,9 +296,18 @@ int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_
 // kn_reorder_run without an order inside a network (no permutation is left), in fewer trips: where kn_count_pays.
 int64_t kn_count_ws_bytes(int64_t M, int32_t N); // 0 where it does not
 bool kn_count_pays(int64_t M, int32_t N);
+// The MLP kernel leaves the results in `out4` (already zero for the points without a network), kn_count_results brings them to
+// sigma / rgb.
+struct KnCountBack {
+    float *out4;
+    const uint32_t *at;   // nullptr: out4 is in the caller's order; else in the samples'
+    const uint16_t *from;
+    int32_t nblk;
+};
 int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,
-                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, const uint32_t *records[2], float **out4,
-                 KnStageTimer *tm);
+                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, const uint32_t *records[2],
+                 KnCountBack *back, KnStageTimer *tm);
+int kn_count_results(hipStream_t st, const KnCountBack &back, int64_t M, float *sigma, float *rgb);
 // Unstable grouping of a render wave's samples (row layout: row i holds cnt[i] samples in slots i*S ..).
 // out->perm lists slot numbers group by group, in no particular order inside a group or between groups;
 // out->counts / out->offsets are not produced.

@@ -579,6 +579,10 @@ constexpr int CO_ROWS = 8;
 // COUNT_MAX_N: the staging buffer of 1,024 threads (128 KB) and the networks' starts are the LDS of a compute unit.
 // COUNT_WIDE_M: 1,024 threads from where their workgroups nearly fill the chip (1.3 M points 99 us with 512, 1.4 M 89 with 1,024).
 // COUNT_MIN_N: with up to 255 networks the radix sort is one trip as well.  COUNT_MIN_M: kn_order_pays.
+// COUNT_BACK_THREADS: results go through k_results_back.  Width 32, fp16 / width 64, bf16, 16^3 networks: 1.4 M points 88 -> 88 /
+// 123 -> 111 us, 4 M 245 -> 218 / 285 -> 276; with 512 threads (not taken) 1 M 76 -> 75 / 93 -> 91, 10x16x10 networks 60 -> 60 /
+// 73 -> 75, 262,143 43 -> 44 / 50 -> 53.
+constexpr int COUNT_BACK_THREADS = 1024;
 constexpr int32_t COUNT_MIN_N = 256, COUNT_MAX_N = 6143;
 constexpr int64_t COUNT_MIN_M = 1 << 17, COUNT_WIDE_M = 5 << 18;
 typedef uint16_t h4_t __attribute__((ext_vector_type(4)));
@@ -593,7 +597,7 @@ __device__ __forceinline__ int32_t xcd_block(int32_t nblk)
 template <int T>
 __global__ void __launch_bounds__(T)
     k_keys_count(const float *__restrict__ pts, int64_t M, KnGrid g, const int32_t *__restrict__ cell_net, int32_t *__restrict__ ids,
-                 uint16_t *__restrict__ keys, int32_t N, int32_t nblk, int32_t *__restrict__ table, float *__restrict__ out4)
+                 uint16_t *__restrict__ keys, int32_t N, int32_t nblk, int32_t *__restrict__ table)
 {
     extern __shared__ int32_t hist[]; // N + 1
     for (int i = threadIdx.x; i <= N; i += T) hist[i] = 0;
@@ -603,7 +607,6 @@ __global__ void __launch_bounds__(T)
         const int32_t id = kn_net_of_cell(cell_net, kn_grid_index(g, x, y, z));
         const int32_t key = id < 0 ? N : id;
         if (ids) ids[i] = id;
-        if (id < 0) *(float4 *)(out4 + 4 * i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f); // no network: the result is zero
         atomicAdd(&hist[key], 1);
         return (uint16_t)key;
     };
@@ -682,8 +685,9 @@ __global__ void __launch_bounds__(T)
     k_count_scatter(const uint16_t *__restrict__ keys, const float *__restrict__ pts, const float *__restrict__ dirs, u4 *__restrict__ pout,
                     u4 *__restrict__ dout, int64_t M, int32_t N, int32_t nblk, const int32_t *__restrict__ table,
                     const int32_t *__restrict__ totals, int32_t tile_len, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles,
-                    int32_t *__restrict__ n_tiles)
+                    int32_t *__restrict__ n_tiles, uint32_t *__restrict__ at, uint16_t *__restrict__ from, float *__restrict__ out4)
 {
+    constexpr bool BACK = T == COUNT_BACK_THREADS;
     extern __shared__ u4 stage[];
     __shared__ int32_t s_sum[3][T / KN_WAVE];
     __shared__ int4 s_list[co_list(T)]; // (network, samples, first sample, first tile)
@@ -753,6 +757,7 @@ __global__ void __launch_bounds__(T)
 #pragma unroll
     for (int r = 0; r < CO_ROWS; ++r) { // (the second halves are under way while the first ones are written)
         const int64_t i = base + min(r * T + (int)threadIdx.x, n_here - 1);
+        if (!BACK && key[r] == (uint32_t)N) *(float4 *)(out4 + 4 * i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int c = 0; c < 3; ++c) p[r][c] = dirs[3 * i + c];
     }
@@ -765,18 +770,30 @@ __global__ void __launch_bounds__(T)
             const u4 v = stage[sp];
             dst[k] = sp + delta[v[3]];
             pout[dst[k]] = v;
+            if constexpr (BACK) at[base + sp] = (uint32_t)dst[k];
+            // no network: the result is zero
+            if (BACK && v[3] == (uint32_t)N) *(float4 *)(out4 + 4 * (int64_t)dst[k]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < CO_ROWS; ++r)
         if (r * T + (int)threadIdx.x < n_here)
-            stage[lpos[r]] = (u4){__float_as_uint(p[r][0]), __float_as_uint(p[r][1]), __float_as_uint(p[r][2]), (uint32_t)(base + r * T + threadIdx.x)};
+            stage[lpos[r]] = (u4){__float_as_uint(p[r][0]), __float_as_uint(p[r][1]), __float_as_uint(p[r][2]), (uint32_t)(r * T + threadIdx.x)};
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < CO_ROWS; ++k) {
         const int32_t sp = k * T + threadIdx.x;
-        if (sp < n_here) dout[dst[k]] = stage[sp];
+        if (sp < n_here) {
+            u4 v = stage[sp];
+            if constexpr (BACK) {
+                from[base + sp] = (uint16_t)v[3];
+                v[3] = (uint32_t)dst[k]; // the result goes to the sample's own place
+            } else {
+                v[3] += (uint32_t)base; // to the place in the caller's order
+            }
+            dout[dst[k]] = v;
+        }
     }
     // tiles: a wavefront per network, the whole workgroup for networks of more than one tile per lane
     const int32_t listed = s_listed;
@@ -794,6 +811,58 @@ __global__ void __launch_bounds__(T)
                 tiles[l.w + k] = tl;
             }
         }
+}
+
+// Results in the order of the samples -> the caller's sigma and rgb arrays, by the workgroups of k_count_scatter: sample `sp` of
+// a workgroup's sorted order is its point `from` and lies at `at`.  Through LDS, so that a workgroup reads runs of a few
+// results, which its neighbours on the XCD read the rest of the lines of, and writes its points one after the other.
+// Instead of one random 16-byte store per sample by the MLP kernel (one transaction each, 57 G/s): 4 M points, 16^3 networks,
+// MLP kernel 120 -> 82 us, this kernel 41 (152 MB, 3.7 TB/s) against 25 for k_split_results.
+template <int T>
+__global__ void __launch_bounds__(T)
+    k_results_back(const float *__restrict__ out4, const uint32_t *__restrict__ at, const uint16_t *__restrict__ from, int64_t M, int32_t nblk,
+                   float *__restrict__ sigma, float *__restrict__ rgb)
+{
+    extern __shared__ u4 stage[]; // T * CO_ROWS results
+    const int64_t base = (int64_t)xcd_block(nblk) * (T * CO_ROWS);
+    const int32_t n_here = (int32_t)min((int64_t)(T * CO_ROWS), M - base);
+    uint32_t a[CO_ROWS], f[CO_ROWS];
+    u4 v[CO_ROWS];
+#pragma unroll
+    for (int k = 0; k < CO_ROWS; ++k) {
+        const int64_t i = base + min(k * T + (int)threadIdx.x, n_here - 1);
+        a[k] = at[i];
+        f[k] = from[i];
+    }
+#pragma unroll
+    for (int k = 0; k < CO_ROWS; ++k) v[k] = *(const u4 *)(out4 + 4 * (int64_t)a[k]);
+#pragma unroll
+    for (int k = 0; k < CO_ROWS; ++k) stage[f[k]] = v[k]; // (beyond the end: the last sample once more)
+    __syncthreads();
+    const float *res = (const float *)stage;
+    const bool aligned = (((uintptr_t)sigma | (uintptr_t)rgb) & 15) == 0; // (base is a multiple of 4,096)
+#pragma unroll
+    for (int r = 0; r < CO_ROWS / 4; ++r) {
+        const int32_t q = 4 * (r * T + (int)threadIdx.x);
+        if (q + 3 < n_here && aligned) {
+            float4 o[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = *(const float4 *)(res + 4 * (q + k));
+            *(float4 *)(sigma + base + q) = make_float4(o[0].w, o[1].w, o[2].w, o[3].w);
+            float4 *c = (float4 *)(rgb + 3 * (base + q));
+            c[0] = make_float4(o[0].x, o[0].y, o[0].z, o[1].x);
+            c[1] = make_float4(o[1].y, o[1].z, o[2].x, o[2].y);
+            c[2] = make_float4(o[2].z, o[3].x, o[3].y, o[3].z);
+        } else {
+            for (int32_t j = q; j < n_here && j < q + 4; ++j) {
+                const float4 o = *(const float4 *)(res + 4 * j);
+                sigma[base + j] = o.w;
+                rgb[3 * (base + j)] = o.x;
+                rgb[3 * (base + j) + 1] = o.y;
+                rgb[3 * (base + j) + 2] = o.z;
+            }
+        }
+    }
 }
 
 // staging array (r, g, b, sigma per point, caller order) -> the caller's sigma and rgb arrays; 4 points per thread
@@ -1001,6 +1070,8 @@ struct CountWs {
     uint16_t *keys;
     KnTile *tiles;
     u4 *pos, *dir;
+    uint32_t *at;
+    uint16_t *from;
     float *out4;
     int32_t threads, nblk;
 };
@@ -1015,6 +1086,8 @@ void carve_count(KnCarver &c, int64_t M, int32_t N, CountWs &w)
     w.tiles = c.carve<KnTile>(kn_max_tiles(M, N, 64));
     w.pos = c.carve<u4>(M);
     w.dir = c.carve<u4>(M);
+    w.at = w.threads == COUNT_BACK_THREADS ? c.carve<uint32_t>(M) : nullptr;
+    w.from = w.threads == COUNT_BACK_THREADS ? c.carve<uint16_t>(M) : nullptr;
     w.out4 = c.carve<float>(4 * M);
 }
 } // namespace
@@ -1031,7 +1104,7 @@ int64_t kn_count_ws_bytes(int64_t M, int32_t N)
 }
 
 int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,
-                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, const uint32_t *records[2], float **out4,
+                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, const uint32_t *records[2], KnCountBack *back,
                  KnStageTimer *tm)
 {
     const int32_t N = sc->N;
@@ -1043,13 +1116,13 @@ int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const 
     const size_t bins = (size_t)(N + 1) * 4;
     auto count = w.threads == 1024 ? k_keys_count<1024> : k_keys_count<512>;
     auto scatter = w.threads == 1024 ? k_count_scatter<1024> : k_count_scatter<512>;
-    hipLaunchKernelGGL(count, grid, block, bins, st, points, M, sc->net_grid, sc->cell_net, user_ids, w.keys, N, w.nblk, w.table, w.out4);
+    hipLaunchKernelGGL(count, grid, block, bins, st, points, M, sc->net_grid, sc->cell_net, user_ids, w.keys, N, w.nblk, w.table);
     KN_CHECK_LAUNCH();
     if (tm) tm->mark(KN_ST_CELL);
     hipLaunchKernelGGL(k_table_scan, dim3((unsigned)kn_div_up(N + 1, 32)), dim3(1024), 0, st, w.table, N + 1, w.nblk, w.totals);
     KN_CHECK_LAUNCH();
     hipLaunchKernelGGL(scatter, grid, block, (size_t)w.threads * CO_ROWS * sizeof(u4) + bins, st, w.keys, points, dirs, w.pos, w.dir, M, N,
-                       w.nblk, w.table, w.totals, tile_len, user_counts, w.tiles, w.n_tiles);
+                       w.nblk, w.table, w.totals, tile_len, user_counts, w.tiles, w.n_tiles, w.at, w.from, w.out4);
     KN_CHECK_LAUNCH();
     out->perm = nullptr; // the records are the sorted list
     out->counts = w.totals;
@@ -1058,7 +1131,17 @@ int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const 
     out->n_tiles = w.n_tiles;
     records[0] = (const uint32_t *)w.pos;
     records[1] = (const uint32_t *)w.dir;
-    *out4 = w.out4;
+    *back = KnCountBack{w.out4, w.at, w.from, w.nblk};
+    return KN_OK;
+}
+
+int kn_count_results(hipStream_t st, const KnCountBack &back, int64_t M, float *sigma, float *rgb)
+{
+    if (!back.at) return kn_reorder_split_results(st, back.out4, M, sigma, rgb);
+    constexpr int T = COUNT_BACK_THREADS;
+    hipLaunchKernelGGL(k_results_back<T>, dim3((unsigned)back.nblk), dim3(T), T * CO_ROWS * sizeof(u4), st, back.out4, back.at, back.from, M,
+                       back.nblk, sigma, rgb);
+    KN_CHECK_LAUNCH();
     return KN_OK;
 }
 
@@ -1159,6 +1242,8 @@ int kn_reorder_configure()
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<true>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     const int counts = (COUNT_MAX_N + 1) * 4;
+    KN_HIP(hipFuncSetAttribute((const void *)k_results_back<COUNT_BACK_THREADS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               COUNT_BACK_THREADS * CO_ROWS * 16));
     KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<512>, hipFuncAttributeMaxDynamicSharedMemorySize, 512 * CO_ROWS * 16 + counts));
     KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, 1024 * CO_ROWS * 16 + counts));
     return KN_OK;
