@@ -16,11 +16,22 @@
 //                         group 3:    q < 12: axis q/4, frequency 8 + (q/2)%2, sin / cos; q = 12..14: x, y, z;
 //                                     q = 15: the constant 1 that multiplies b1.
 //   gamma(d), 8 MFMAs q:  group g < 3: axis g, frequency q/2, sin / cos; group 3: dx, dy, dz, 1 (b4), 0 x 4.
-// b2, b3 and b5 initialise accumulators.
+// b2 initialises accumulators.
 //
-// Density and colour (1 + 3 output rows) share one accumulator among the four 16-sample tiles of a chunk:
-// for tile u the A operand is masked to rows 4u..4u+3 (colour 4u+0..2, density 4u+3), after which lane l holds
-// (r, g, b, sigma) of sample l of the 64.
+// Feature layer: layer 3's feature vector has no activation (Sec. 3.2), so feature layer and layer 4 are one affine map of
+// the second hidden vector.  The weights' image holds the product of the two (64-bit sums, rounded once), and layer 4 is
+// evaluated on the second hidden vector: H/16 * H/4 MFMAs of a sample tile fewer, and a rounding fewer in the results.
+//
+// Density and colour (1 + 3 outputs) would be 4 of 16 rows of their MFMAs.  They are dot products on the vector ALU
+// instead, over the hidden units a lane holds, summed over the four lane groups with lane swaps; lane group u keeps the
+// (r, g, b, sigma) of sample tile u, so that lane l holds those of sample l of the 64.
+//
+// What bounds it: the matrix cores (fp32 MFMAs take 32 cycles each; 80 per sample tile at width 32, 224 at width 64), with
+// the vector ALU's some 300 instructions per tile beside them, which two wavefronts per SIMD hide in part (cores busy 70 % of
+// the kernel at 4 M points; three wavefronts spill and are slower).  Against five separate layers with the heads on the
+// matrix cores (112 and 320 MFMAs): 4 M points, 16^3 networks, width 32, 751 -> 633 us, 2 M at width 64 841 -> 675; 800x800
+// frame, width 32, 759 -> 619.  Relative error against 64 bits (65,537 points): density 2.4e-7 -> 2.3e-7, colour 1.16e-7 ->
+// 1.08e-7; width 64 2.4e-7 -> 2.3e-7, 1.42e-7 -> 1.23e-7.
 //
 // Encoding: accurate sincosf at frequencies 0, 4 (positions), 0 (directions) and 8 (group 3), up to three steps
 // of the double-angle recurrence in between; all in fp32.
@@ -50,19 +61,19 @@ template <int H> struct Regs {
     static constexpr int HT = H / 16, HQ = H / 4;
     static constexpr int W1 = 0;                     // (t, q)  -> W1 + 16 t + q
     static constexpr int W2 = W1 + 16 * HT;          // (t, k)  -> W2 + HQ t + k
-    static constexpr int W3 = W2 + HQ * HT;          // feature rows
-    static constexpr int W4 = W3 + HQ * HT;          // (t, k)  -> W4 + (HQ + 8) t + k; k >= HQ: gamma(d)
-    static constexpr int WO = W4 + (HQ + 8) * HT;    // colour rows (A rows with m%4 < 3) and the density row (m%4 = 3)
-    static constexpr int B2 = WO + HQ;               // (t, j): accumulator initial values of this lane
-    static constexpr int B3 = B2 + 4 * HT;
-    static constexpr int BO = B3 + 4 * HT;
+    static constexpr int W4 = W2 + HQ * HT;          // (t, k)  -> W4 + (HQ + 8) t + k; k < HQ: folded with the feature layer; k >= HQ: gamma(d)
+    static constexpr int WO = W4 + (HQ + 8) * HT;    // (c, k)  -> WO + HQ c + k: colour c (c < 3) / density, hidden unit k of the lane group
+    static constexpr int B2 = WO + 4 * HQ;           // (t, j): accumulator initial values of this lane
+    static constexpr int BO = B2 + 4 * HT;
     static constexpr int N = BO + 4;
     // canonical offsets (Sec. 3.2: five layers, weights before biases)
     static constexpr int oW1 = 0, ob1 = 63 * H, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H, ob3 = oW3 + H * (H + 1),
                          oW4 = ob3 + H + 1, ob4 = oW4 + (H + 27) * H, oW5 = ob4 + H, ob5 = oW5 + 3 * H;
 };
 
-// canonical index of the value in register r of lane `lane`; -1 = zero
+// canonical index of the value in register r of lane `lane`; -1 = zero; FOLD_ROW - (unit * H + col): that element of the
+// product of feature layer and layer 4; FOLD_BIAS - col: element of the folded bias, b4 + W4f^T b3f
+constexpr int FOLD_ROW = -2, FOLD_BIAS = -2 - 64 * 64;
 template <int H> __device__ int reg_source(int r, int lane)
 {
     using R = Regs<H>;
@@ -75,28 +86,23 @@ template <int H> __device__ int reg_source(int r, int lane)
         if (q < 12) return R::oW1 + (3 + 6 * (8 + ((q >> 1) & 1)) + 3 * (q & 1) + (q >> 2)) * H + col;
         return q < 15 ? R::oW1 + (q - 12) * H + col : R::ob1 + col;
     }
-    if (r < R::W3) {
+    if (r < R::W4) {
         const int t = (r - R::W2) / HQ, k = (r - R::W2) % HQ;
         return R::oW2 + unit(k) * H + 16 * t + m;
     }
-    if (r < R::W4) {
-        const int t = (r - R::W3) / HQ, k = (r - R::W3) % HQ;
-        return R::oW3 + unit(k) * (H + 1) + 1 + 16 * t + m;
-    }
     if (r < R::WO) {
         const int t = (r - R::W4) / (HQ + 8), k = (r - R::W4) % (HQ + 8), col = 16 * t + m;
-        if (k < HQ) return R::oW4 + unit(k) * H + col;
+        if (k < HQ) return FOLD_ROW - (unit(k) * H + col);
         const int q = k - HQ;
         if (g < 3) return R::oW4 + (H + 3 + 6 * (q >> 1) + 3 * (q & 1) + g) * H + col;
         if (q < 3) return R::oW4 + (H + q) * H + col;
-        return q == 3 ? R::ob4 + col : -1;
+        return q == 3 ? FOLD_BIAS - col : -1;
     }
     if (r < R::B2) {
-        const int k = r - R::WO;
-        return (m & 3) < 3 ? R::oW5 + unit(k) * 3 + (m & 3) : R::oW3 + unit(k) * (H + 1);
+        const int c = (r - R::WO) / HQ, k = (r - R::WO) % HQ;
+        return c < 3 ? R::oW5 + unit(k) * 3 + c : R::oW3 + unit(k) * (H + 1);
     }
-    if (r < R::B3) return R::ob2 + 16 * ((r - R::B2) >> 2) + 4 * g + ((r - R::B2) & 3);
-    if (r < R::BO) return R::ob3 + 1 + 16 * ((r - R::B3) >> 2) + 4 * g + ((r - R::B3) & 3);
+    if (r < R::BO) return R::ob2 + 16 * ((r - R::B2) >> 2) + 4 * g + ((r - R::B2) & 3);
     const int j = r - R::BO;
     return j < 3 ? R::ob5 + j : R::ob3;
 }
@@ -110,15 +116,27 @@ __global__ void k_pack_weights_f32(const float *__restrict__ w, int64_t P, int32
     const int64_t net = i / per;
     const int e = (int)(i - net * per);
     const int s = reg_source<H>(e >> 6, e & 63);
-    packed[i] = s < 0 ? 0.0f : w[net * P + s];
+    const float *src = w + net * P;
+    if (s >= -1) {
+        packed[i] = s < 0 ? 0.0f : src[s];
+    } else {
+        using R = Regs<H>;
+        const bool bias = s <= FOLD_BIAS;
+        const int k = bias ? 0 : (FOLD_ROW - s) / H, col = bias ? FOLD_BIAS - s : (FOLD_ROW - s) % H;
+        double acc = bias ? (double)src[R::ob4 + col] : 0.0;
+        for (int f = 0; f < H; ++f)
+            acc = fma((double)(bias ? src[R::ob3 + 1 + f] : src[R::oW3 + k * (H + 1) + 1 + f]), (double)src[R::oW4 + f * H + col], acc);
+        // (finite factors stay finite: a product with an activation of zero is zero)
+        packed[i] = fabs(acc) <= 1.7976931348623157e308 ? (float)fmin(fmax(acc, -3.4028234663852886e38), 3.4028234663852886e38) : (float)acc;
+    }
 }
 
 // one network's weights in registers
 template <int H> struct NetF32 {
     using R = Regs<H>;
     static constexpr int HT = H / 16, HQ = H / 4; // output tiles per layer, MFMAs per hidden input vector
-    float w1[HT][16], w2[HT][HQ], w3[HT][HQ], w4[HT][HQ + 8], wo[HQ];
-    f4 bias2[HT], bias3[HT], bias_out;
+    float w1[HT][16], w2[HT][HQ], w4[HT][HQ + 8], wo[4][HQ];
+    f4 bias2[HT], bias_out;
     __device__ __forceinline__ void load(const float *__restrict__ packed, int32_t net, int lane)
     {
         const float *__restrict__ wp = packed + (int64_t)net * (R::N * KN_WAVE) + lane;
@@ -128,24 +146,29 @@ template <int H> struct NetF32 {
 #pragma unroll
             for (int q = 0; q < 16; ++q) w1[t][q] = reg(R::W1 + 16 * t + q);
 #pragma unroll
-            for (int k = 0; k < HQ; ++k) {
-                w2[t][k] = reg(R::W2 + HQ * t + k);
-                w3[t][k] = reg(R::W3 + HQ * t + k);
-            }
+            for (int k = 0; k < HQ; ++k) w2[t][k] = reg(R::W2 + HQ * t + k);
 #pragma unroll
             for (int k = 0; k < HQ + 8; ++k) w4[t][k] = reg(R::W4 + (HQ + 8) * t + k);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bias2[t][j] = reg(R::B2 + 4 * t + j);
-                bias3[t][j] = reg(R::B3 + 4 * t + j);
-            }
+            for (int j = 0; j < 4; ++j) bias2[t][j] = reg(R::B2 + 4 * t + j);
         }
 #pragma unroll
-        for (int k = 0; k < HQ; ++k) wo[k] = reg(R::WO + k);
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int k = 0; k < HQ; ++k) wo[c][k] = reg(R::WO + HQ * c + k);
 #pragma unroll
         for (int j = 0; j < 4; ++j) bias_out[j] = reg(R::BO + j);
     }
 };
+
+// sum over the four lane groups, in all of them
+__device__ __forceinline__ float sum_groups(float v)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const float h = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(h), __float_as_uint(h), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 
 // n_tiles sample tiles (16 u .. 16 u + 15, u < n_tiles <= 4) of a staged chunk; lane l returns the pre-activations
 // (r, g, b, sigma) of sample l
@@ -155,9 +178,10 @@ template <int H> __device__ __forceinline__ f4 eval_chunk(const NetF32<H> &w, co
     const int n = lane & 15, g = lane >> 4;
     const bool g3 = g == 3;
     const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    f4 out = w.bias_out;
+    f4 out = zero4;
 #pragma unroll 1
     for (int u = 0; u < n_tiles; ++u) {
+        __builtin_amdgcn_s_setprio(0);
         const f4 s0 = *(const f4 *)&stage[16 * u + n][0];
         const f4 s1 = *(const f4 *)&stage[16 * u + n][4];
         const float p[3] = {s0[0], s0[1], s0[2]}, d[3] = {s0[3], s1[0], s1[1]};
@@ -188,9 +212,7 @@ template <int H> __device__ __forceinline__ f4 eval_chunk(const NetF32<H> &w, co
             const float g3_v = q < 3 ? d[q < 3 ? q : 0] : (q == 3 ? 1.0f : 0.0f);
             dirv[q] = g3 ? g3_v : axis_v;
         }
-        const bool my_tile = (n >> 2) == u;
-        const bool sig_row = my_tile && (n & 3) == 3, col_row = my_tile && (n & 3) < 3;
-
+        __builtin_amdgcn_s_setprio(1); // the other wavefront of the SIMD encodes under these: 650 -> 630 us for 4 M points
         f4 acc[HT], h[HT];
         // layer 1: gamma(x) -> H, ReLU
 #pragma unroll
@@ -214,18 +236,11 @@ template <int H> __device__ __forceinline__ f4 eval_chunk(const NetF32<H> &w, co
         for (int t2 = 0; t2 < HT; ++t2)
 #pragma unroll
             for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-        // layer 3: H -> feature (no activation) and density (row 4u + 3 of the shared tile)
+        // layer 3: the density; its feature vector is folded into layer 4
+        f4 o = zero4;
 #pragma unroll
-        for (int t2 = 0; t2 < HT; ++t2) {
-            acc[t2] = w.bias3[t2];
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w.w3[t2][k], h[k >> 2][k & 3], acc[t2]);
-        }
-#pragma unroll
-        for (int k = 0; k < HQ; ++k) out = mfma4(sig_row ? w.wo[k] : 0.0f, h[k >> 2][k & 3], out);
-#pragma unroll
-        for (int t2 = 0; t2 < HT; ++t2) h[t2] = acc[t2];
-        // layer 4: [feature, gamma(d)] -> H, ReLU
+        for (int k = 0; k < HQ; ++k) o[3] = fmaf(w.wo[3][k], h[k >> 2][k & 3], o[3]);
+        // layer 4: [second hidden vector through the folded feature layer, gamma(d)] -> H, ReLU
 #pragma unroll
         for (int t2 = 0; t2 < HT; ++t2) {
             acc[t2] = zero4;
@@ -238,9 +253,16 @@ template <int H> __device__ __forceinline__ f4 eval_chunk(const NetF32<H> &w, co
         for (int t2 = 0; t2 < HT; ++t2)
 #pragma unroll
             for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-        // layer 5: H -> colour rows 4u + 0..2 of the shared tile
+        // layer 5: H -> colour
 #pragma unroll
-        for (int k = 0; k < HQ; ++k) out = mfma4(col_row ? w.wo[k] : 0.0f, h[k >> 2][k & 3], out);
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int k = 0; k < HQ; ++k) o[c] = fmaf(w.wo[c][k], h[k >> 2][k & 3], o[c]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float v = sum_groups(o[c]) + w.bias_out[c];
+            out[c] = g == u ? v : out[c];
+        }
     }
     return out;
 }
@@ -330,8 +352,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         const bool hit = pt.net == sel;
         const unsigned long long hits = __ballot(hit);
         const int c = __popcll(hits), from = (int)__builtin_ctzll(hits);
-        // the samples move to the front; the places behind them repeat the first one (the sample tiles share an accumulator, so
-        // what is in them has to be a sample of the network)
+        // the samples move to the front; the places behind them repeat the first one
         const int hits_below = __popcll(hits & ((1ull << lane) - 1ull)), place = hit ? hits_below : c + lane - hits_below;
         float v[6];
 #pragma unroll
@@ -395,7 +416,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
             for (int j = 0; j < 4; ++j) bias2[t][j] = reg(R::B2 + 4 * t + j);
         }
 #pragma unroll
-        for (int k = 0; k < HQ; ++k) wo[k] = reg(R::WO + k);
+        for (int k = 0; k < HQ; ++k) wo[k] = reg(R::WO + 3 * HQ + k);
         bias_sig = reg(R::BO + 3);
     };
     int32_t net_loaded = -1;

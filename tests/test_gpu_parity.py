@@ -271,6 +271,24 @@ def test_eval_grouped_density_scaled_and_tiny_groups():
     check_eval(sc, pts, ks.sphere_dirs(M, 8), sigma_unit=100.0)
 
 
+@pytest.mark.parametrize("H", [32, 64])
+def test_eval_grouped_fp32_weights_whose_product_leaves_the_range(H):
+    """Feature layer and layer 4 are one affine map in the kernel: a product of their weights beyond fp32 that only meets a
+    hidden unit which is never active, and a feature that is always zero, changes nothing."""
+    sc = scene_dict((2, 2, 2), (-1, -1, -1), (1, 1, 1), H, "f32", 27)
+    w, at = sc["weights"].copy(), []
+    for fi, fo in ks.layer_shapes(H):
+        at.append((at[-1][1] if at else 0, (at[-1][1] if at else 0) + fi * fo + fo))
+    W = lambda l: w[:, at[l][0]:at[l][1] - ks.layer_shapes(H)[l][1]].reshape(len(w), *ks.layer_shapes(H)[l])  # noqa: E731
+    b = lambda l: w[:, at[l][1] - ks.layer_shapes(H)[l][1]:at[l][1]]  # noqa: E731
+    W(1)[:, :, 0], b(1)[:, 0] = 0.0, -1.0                              # hidden unit 0 of layer 2 is never active,
+    W(2)[:, :, 1], b(2)[:, 1] = 0.0, 0.0                               # and feature 0 reads nothing but that unit
+    W(2)[:, 0, 1], W(3)[:, 0, :] = 1e30, 1e30
+    assert W(3).base is not None and float(w.max()) > 9e29
+    sc["weights"] = w
+    check_eval(sc, ks.uniform_points(5000, 41, lo=(-1,) * 3, hi=(1,) * 3), ks.sphere_dirs(5000, 42))
+
+
 @pytest.mark.parametrize("wdtype,H", [("f16", 32), ("bf16", 64), ("f32", 32), ("f32", 64)])
 @pytest.mark.parametrize("res,M", [((16, 16, 16), 1), ((16, 16, 16), 63), ((5, 8, 5), 4097), ((16, 16, 16), 3001), ((2, 2, 2), 8190),
                                    ((2, 2, 2), 16385), ((24, 20, 28), 4095)])
