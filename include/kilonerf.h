@@ -237,8 +237,8 @@ int kn_composite_deltas(void *stream, const float *sigma /*dev*/, const float *r
  * below 2^31, and R <= 2^26: KN_E_UNSUPPORTED beyond.  With waves, the call enqueues the first two of them without looking at their outcome
  * (their shape is computed on the device) and reads the count of surviving rays on the host only to decide
  * about further waves; when it returns, the last wave has been enqueued but `stream` may still be running
- * (it does not wait at all when the slot budget guarantees that the second wave ends every ray and `stats`
- * is NULL).  Work of successive calls on one stream is ordered as usual.  Calls on different streams (and from
+ * (it does not wait for survivors when the slot budget guarantees that the first or second wave ends every ray and
+ * `stats` is NULL, and frames of that kind of up to 32,768 rays are enqueued without any wait).  Work of successive calls on one stream is ordered as usual.  Calls on different streams (and from
  * different threads) may be in flight at the same time on one scene, through one context or several, each with a
  * workspace and an output buffer of its own; one stream must not be used by two calls at once.  A context keeps 8
  * host mailboxes, one per stream with a call in flight (a mailbox whose last call has reported is handed to the

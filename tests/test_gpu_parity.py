@@ -1481,6 +1481,24 @@ def test_stratified_render_on_a_sparse_grid_and_on_grids_that_do_not_nest():
     render_check(cfg)
 
 
+@pytest.mark.parametrize("rays", [1, 4095, 32768, 32769])
+@pytest.mark.parametrize("K,eps", [(1, 0.01), (48, 0.0), (49, 0.01), (128, 0.01), (129, 0.01)])
+def test_render_whose_waves_need_no_count_equals_the_counted_one(rays, K, eps):
+    """Waves that are known to end every ray (up to 48 samples: the first, up to 128: the second) are not counted, and small
+    frames of that kind read no count at all: same pixels as with counts, also where no ray meets the scene."""
+    import torch
+    dev, _ = make_pair(scene_dict((4, 5, 3), (0, 0, 0), (1, 1, 1), 32, "f32", 19, sigma_scale=20.0))
+    g = torch.Generator().manual_seed(rays + K)
+    o = torch.tensor([0.5, 0.5, 3.0]) + 0.1 * torch.randn((rays, 3), generator=g)
+    d = torch.tensor([0.0, 0.0, -1.0]) + 0.25 * torch.randn((rays, 3), generator=g)
+    for away in (False, True):
+        args = (o.cuda(), (-d if away else d).cuda(), 1.5, 2.5 / K, K, eps, (0.2, 0.4, 0.9))
+        want, st = dev.render(*args, want_stats=True)
+        assert (st["samples_evaluated"] == 0) == away or rays == 1
+        for _ in range(2):
+            assert torch.equal(dev.render(*args), want)
+
+
 @pytest.mark.parametrize("wdtype,H,rays,res,occ,order", [
     ("f16", 32, 1, (16, 16, 16), "nested", "image"), ("bf16", 64, 17, (4, 4, 4), "nested", "image"),
     ("f16", 64, 1025, (5, 8, 5), "odd", "image"), ("bf16", 32, 12288, (16, 16, 16), "none", "image"),
