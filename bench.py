@@ -398,11 +398,16 @@ def measure_render(kn, torch, np, configs, cfg, wdtype, steps, warmup, poses, tr
     blended = sum(stats[i % n_p]["samples_blended"] for i in range(steps))
     evaluated = sum(stats[i % n_p]["samples_evaluated"] for i in range(steps))
     waves = sum(stats[i % n_p]["waves"] for i in range(steps))
-    launches = waves  # one launch of each per-wave kernel per wave
     timed = range(0, steps, EVENTS_EVERY)  # the frames of the timed region that carried events
-    timed_counts = {"evaluated": sum(stats[i % n_p]["samples_evaluated"] for i in timed),
+    # A frame is one kernel behind its set-up (its samples are counted in the pass above), or waves of one launch per kernel
+    # (counted by the calls that return statistics, which always run in waves).
+    one_kernel = prof_all["ms_march"] == 0.0 and prof_all["ms_blend"] == 0.0
+    if one_kernel:
+        evaluated, waves = prof_all["mlp_samples"], steps
+    launches = waves  # one launch of each per-wave kernel per wave
+    timed_counts = {"evaluated": evaluated * len(timed) / steps if one_kernel else sum(stats[i % n_p]["samples_evaluated"] for i in timed),
                     "blended": sum(stats[i % n_p]["samples_blended"] for i in timed),
-                    "launches": sum(stats[i % n_p]["waves"] for i in timed), "frames": len(timed)}
+                    "launches": len(timed) if one_kernel else sum(stats[i % n_p]["waves"] for i in timed), "frames": len(timed)}
     all_counts = {"evaluated": evaluated, "blended": blended, "launches": launches, "frames": steps}
     H = sc["hidden"]
     f32 = wdtype == "f32"
@@ -413,15 +418,16 @@ def measure_render(kn, torch, np, configs, cfg, wdtype, steps, warmup, poses, tr
         n = n or all_counts
         s_ = p["ms_mlp"] * 1e-3
         tf = FLOP_PER_SAMPLE[H] * n["evaluated"] / s_ / 1e12 if s_ > 0 else 0.0
-        r = {"kernel": "k_mlp_f32 (fused grouped MLP, fp32 MFMA)" if f32 else "k_mlp_mfma (fused grouped MLP)", "bound": "mfma",
+        kernel = "k_render_fused (march, grouping, MLP and blend of a frame)" if one_kernel else "k_mlp_mfma (fused grouped MLP)"
+        r = {"kernel": "k_mlp_f32 (fused grouped MLP, fp32 MFMA)" if f32 else kernel, "bound": "mfma",
              "achieved": tf, "peak": mfma_peak / 1e12, "unit": "TFLOP/s", "frac": tf * 1e12 / mfma_peak,
-             "traffic": traffic.get("k_mlp_mfma"), "avg_launch_ms": p["ms_mlp"] / max(n["launches"], 1), "launches": n["launches"],
+             "traffic": traffic.get("k_render_fused" if one_kernel else "k_mlp_mfma"), "avg_launch_ms": p["ms_mlp"] / max(n["launches"], 1), "launches": n["launches"],
              "frames_with_events": n["frames"], "samples_per_launch": n["evaluated"] / max(n["launches"], 1),
              # the same kernel on the samples the method itself evaluates (those in front of the termination point)
              "achieved_on_blended_samples": tf * n["blended"] / max(n["evaluated"], 1)}
         r["flop_per_sample"] = FLOP_PER_SAMPLE[H]
         r["flop_per_sample_executed"] = FLOP_PER_SAMPLE[H] if f32 else FLOP_PER_SAMPLE_EXECUTED_16BIT[H]
-        if not f32:
+        if not f32 and not one_kernel:
             # second view: its vector-ALU issue slots (counted in the generated code, transcendental instructions
             # twice) against what 1024 SIMDs can issue at 2.4 GHz, one slot per 4 cycles
             slots = VALU_SLOTS_PER_16_SAMPLES[H] / 16.0 * n["evaluated"]
@@ -466,9 +472,11 @@ def measure_render(kn, torch, np, configs, cfg, wdtype, steps, warmup, poses, tr
         "stage_ms_per_frame": {k: v / steps for k, v in stage_ms.items()},
         "dominant_kernel_stage": dominant,
         "roofline": roofline,
-        "roofline_mlp_all_events": roof_mlp(prof_all), "roofline_march_all_events": roof_march(prof_all),
-        "roofline_group_all_events": roof_group(prof_all), "roofline_blend_all_events": roof_blend(prof_all),
+        "roofline_mlp_all_events": roof_mlp(prof_all),
     }
+    if not one_kernel:
+        res.update({"roofline_march_all_events": roof_march(prof_all), "roofline_group_all_events": roof_group(prof_all),
+                    "roofline_blend_all_events": roof_blend(prof_all)})
     return res, dict(scene=scene, rays=rays, args=args, out=out, R=R, rays_fn=rays_fn, blended_per_frame=blended / steps)
 
 
