@@ -577,7 +577,7 @@ __global__ void __launch_bounds__(PLACE_THREADS)
 constexpr int CO_ROWS = 8;
 // COUNT_MAX_N: the staging buffer of 1,024 threads (128 KB) and the networks' starts are the LDS of a compute unit.
 // COUNT_WIDE_M: 1,024 threads from where their workgroups nearly fill the chip (1.3 M points 99 us with 512, 1.4 M 89 with 1,024).
-// COUNT_MIN_M: kn_order_pays.  (Few networks, where the radix sort is one trip as well: 5x8x5, 270,000 points 50 -> 38 us, 1 M
+// COUNT_MIN_M: see kn_order_pays, which is asked first.  (Few networks, where the radix sort is one trip as well: 5x8x5, 270,000 points 50 -> 38 us, 1 M
 // 67 -> 51, 4 M 219 -> 169; 2^3 with nine in ten points in one network, the most LDS atomics on one address, 4 M 279 -> 180.)
 // COUNT_BACK_THREADS: results go through k_results_back.  Width 32, fp16 / width 64, bf16, 16^3 networks: 1.4 M points 88 -> 88 /
 // 123 -> 111 us, 4 M 245 -> 218 / 285 -> 276; with 512 threads (not taken) 1 M 76 -> 75 / 93 -> 91, 10x16x10 networks 60 -> 60 /
@@ -1010,6 +1010,7 @@ void carve_order(KnCarver &c, int64_t M, int32_t N, OrderWs &w)
 }
 // Every workgroup of k_place scans the counts of all networks, in steps of 1,024: up to eight of them.
 constexpr int32_t ORDER_MAX_N = 8191;
+constexpr int64_t ORDER_MAX_M = 9 << 14;
 constexpr int32_t ORDER_LDS_N = 2048; // below: k_rank counts in LDS
 } // namespace
 
@@ -1024,12 +1025,12 @@ int64_t kn_order_ws_bytes(int64_t M, int32_t N)
 // For batches that do not fill the chip with the radix passes' workgroups: four launches instead of nine (six with up to 255
 // networks), and kernels of many small workgroups.  The evaluation then gathers its points and scatters its results, which
 // costs more than moving the samples does once a batch is far larger than the caches.  65,537 points, fp16, width 32:
-// 16^3 networks 65 us -> 38, 10x16x10 61 -> 31, 5x8x5 39 -> 25; fp32 (10x16x10) 77 -> 50.  At the border, against kn_count_run: 131,000
-// points on 16^3 networks 55 against 61, 180,000 58 against 59; 10x16x10 38 against 41 and 42 against 41, 262,143 51 against 43;
-// 5x8x8 32 against 31, 262,143 43 against 37.
+// 16^3 networks 65 us -> 33, 10x16x10 61 -> 28, 5x8x5 39 -> 25; fp32 (10x16x10) 77 -> 41.  At the border, against kn_count_run: 150,000
+// points on 16^3 networks 42 us against 57, skewed (atomics on few addresses) 58 against 56, 196,608 50 against 55 and 68 against 54;
+// on 10x16x10 33 against 40 and 36 against 39; on 5x8x8 30 against 31 and 38 against 32.
 bool kn_order_pays(const kn_scene *sc, int64_t M)
 {
-    return sc->N <= ORDER_MAX_N && M <= 1ll << 17;
+    return sc->N <= ORDER_MAX_N && M <= ORDER_MAX_M;
 }
 
 int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_t M, int32_t tile_len, int32_t *user_ids,

@@ -314,8 +314,8 @@ def test_eval_grouped_without_aux_equals_the_ordered_batch(wdtype, H, res, M):
 
 @pytest.mark.parametrize("wdtype,H,res,M", [
     ("f16", 32, (10, 16, 10), 65537), ("f32", 32, (16, 16, 16), 131071),                    # indices ordered by counting
-    ("f16", 32, (16, 16, 16), 131073), ("f32", 32, (16, 16, 16), 140000), ("bf16", 64, (4, 8, 8), 300001),
-    ("f16", 32, (1, 1, 1), 140001), ("f32", 64, (5, 8, 5), 131073), ("bf16", 32, (2, 2, 2), 1400001),  # samples moved, 512 threads
+    ("f16", 32, (16, 16, 16), 131073), ("f32", 32, (16, 16, 16), 160000), ("bf16", 64, (4, 8, 8), 300001),
+    ("f16", 32, (1, 1, 1), 147457), ("f16", 32, (16, 16, 16), 147456), ("f16", 32, (16, 16, 16), 147457), ("f32", 64, (5, 8, 5), 131073), ("bf16", 32, (2, 2, 2), 1400001),  # samples moved, 512 threads
     ("f16", 32, (16, 16, 16), 5 << 18), ("bf16", 32, (17, 19, 19), (5 << 18) + 1), ("f16", 64, (16, 16, 16), 2100003)])  # 1,024
 @pytest.mark.parametrize("spread", ["all over", "one network", "none"])
 def test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread):
