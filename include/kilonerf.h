@@ -124,6 +124,9 @@ int kn_destroy(kn_ctx *ctx);
  * the two as one affine map, W3f W4f and b4 + W4f^T b3f, formed here in fp32 and rounded to the scene's type (the
  * result is Eq. 7 up to the rounding that 16-bit operands have anyway).  KN_E_UNSUPPORTED if an element of that
  * product is finite but beyond the type's range (fp16: 65504): such networks belong in bf16 or fp32 scenes.
+ * fp32 scenes: the same product, summed in 64 bits and rounded once.  Where the product, or a sum over it, could leave fp32
+ * although the two layers do not (bounded over the scene's box from the weights' magnitudes), they are evaluated one after the
+ * other in every network of the scene, which is slower and accepts any weights.
  */
 int kn_scene_bytes(const kn_scene_desc *desc, int64_t *out_bytes);
 int kn_scene_create(kn_ctx *ctx, const kn_scene_desc *desc, void *stream, void *buffer /*dev, nullable*/,

@@ -540,6 +540,7 @@ extern "C" int kn_scene_create(kn_ctx *ctx, const kn_scene_desc *desc, void *str
     make_grid(desc->aabb_min, desc->aabb_max, desc->res, sc->net_grid);
     sc->has_occ = lay.has_occ;
     sc->packed_halfs_per_net = 0;
+    sc->f32_apart = false;
     sc->brick_nets = false;
     sc->net_shift[0] = sc->net_shift[1] = sc->net_shift[2] = -1;
     sc->skip_res[0] = sc->skip_res[1] = sc->skip_res[2] = 0;

@@ -101,8 +101,9 @@ struct kn_scene {
     uint32_t *occ_bits; // device, a bit per voxel
     bool brick_nets;       // every block lies inside one network cell
     int32_t net_shift[3];  // per axis: the occupancy grid refines the network grid by 2^net_shift (-1: it does not)
-    void *packed_w;        // device, matrix-core operand order (16-bit types only)
+    void *packed_w;        // device, matrix-core operand order
     int64_t packed_halfs_per_net;
+    bool f32_apart;        // fp32 weights: feature layer and layer 4 are kept apart (some network's product could leave fp32)
     // Coarse skip field over the occupancy grid: one byte per block of KN_SKIP_BLOCK^3 voxels holding
     // the Chebyshev distance, in blocks, to the nearest block with an occupied voxel (0 = occupied
     // block, capped at KN_SKIP_MAX).  Lets marching jump over provably empty lattice points.

@@ -21,6 +21,8 @@
 // Feature layer: layer 3's feature vector has no activation (Sec. 3.2), so feature layer and layer 4 are one affine map of
 // the second hidden vector.  The weights' image holds the product of the two (64-bit sums, rounded once), and layer 4 is
 // evaluated on the second hidden vector: H/16 * H/4 MFMAs of a sample tile fewer, and a rounding fewer in the results.
+// Weights so large or so small that the product, or a sum over it, could leave fp32 where the two layers by themselves
+// do not (k_fold_bound) are kept apart: a scene with such a network is evaluated by the FOLD = false variants.
 //
 // Density and colour (1 + 3 outputs) would be 4 of 16 rows of their MFMAs.  They are dot products on the vector ALU
 // instead, over the hidden units a lane holds, summed over the four lane groups with lane swaps; lane group u keeps the
@@ -65,16 +67,18 @@ template <int H> struct Regs {
     static constexpr int WO = W4 + (HQ + 8) * HT;    // (c, k)  -> WO + HQ c + k: colour c (c < 3) / density, hidden unit k of the lane group
     static constexpr int B2 = WO + 4 * HQ;           // (t, j): accumulator initial values of this lane
     static constexpr int BO = B2 + 4 * HT;
-    static constexpr int N = BO + 4;
+    static constexpr int W3 = BO + 4;                // (t, k)  -> W3 + HQ t + k: feature rows, (t, j) -> B3 + 4 t + j: their biases;
+    static constexpr int B3 = W3 + HQ * HT;          // both only where the feature layer is kept apart
+    static constexpr int N = B3 + 4 * HT;
     // canonical offsets (Sec. 3.2: five layers, weights before biases)
     static constexpr int oW1 = 0, ob1 = 63 * H, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H, ob3 = oW3 + H * (H + 1),
                          oW4 = ob3 + H + 1, ob4 = oW4 + (H + 27) * H, oW5 = ob4 + H, ob5 = oW5 + 3 * H;
 };
 
-// canonical index of the value in register r of lane `lane`; -1 = zero; FOLD_ROW - (unit * H + col): that element of the
-// product of feature layer and layer 4; FOLD_BIAS - col: element of the folded bias, b4 + W4f^T b3f
+// canonical index of the value in register r of lane `lane`; -1 = zero; with FOLD, FOLD_ROW - (unit * H + col): that element
+// of the product of feature layer and layer 4; FOLD_BIAS - col: element of the folded bias, b4 + W4f^T b3f
 constexpr int FOLD_ROW = -2, FOLD_BIAS = -2 - 64 * 64;
-template <int H> __device__ int reg_source(int r, int lane)
+template <int H, bool FOLD> __device__ int reg_source(int r, int lane)
 {
     using R = Regs<H>;
     constexpr int HQ = R::HQ;
@@ -92,22 +96,72 @@ template <int H> __device__ int reg_source(int r, int lane)
     }
     if (r < R::WO) {
         const int t = (r - R::W4) / (HQ + 8), k = (r - R::W4) % (HQ + 8), col = 16 * t + m;
-        if (k < HQ) return FOLD_ROW - (unit(k) * H + col);
+        if (k < HQ) return FOLD ? FOLD_ROW - (unit(k) * H + col) : R::oW4 + unit(k) * H + col;
         const int q = k - HQ;
         if (g < 3) return R::oW4 + (H + 3 + 6 * (q >> 1) + 3 * (q & 1) + g) * H + col;
         if (q < 3) return R::oW4 + (H + q) * H + col;
-        return q == 3 ? FOLD_BIAS - col : -1;
+        return q == 3 ? (FOLD ? FOLD_BIAS - col : R::ob4 + col) : -1;
     }
     if (r < R::B2) {
         const int c = (r - R::WO) / HQ, k = (r - R::WO) % HQ;
         return c < 3 ? R::oW5 + unit(k) * 3 + c : R::oW3 + unit(k) * (H + 1);
     }
     if (r < R::BO) return R::ob2 + 16 * ((r - R::B2) >> 2) + 4 * g + ((r - R::B2) & 3);
-    const int j = r - R::BO;
-    return j < 3 ? R::ob5 + j : R::ob3;
+    if (r < R::W3) return r - R::BO < 3 ? R::ob5 + (r - R::BO) : R::ob3;
+    if (FOLD) return -1; // (not read)
+    if (r < R::B3) {
+        const int t = (r - R::W3) / HQ, k = (r - R::W3) % HQ;
+        return R::oW3 + unit(k) * (H + 1) + 1 + 16 * t + m;
+    }
+    return R::ob3 + 1 + 16 * ((r - R::B3) >> 2) + 4 * g + ((r - R::B3) & 3);
 }
 
+// Sets `apart` unless the product of feature layer and layer 4 may stand for the two.  One workgroup of H threads per network;
+// thread j bounds output j of each layer for every point of the scene's box (|coordinate| <= reach; sines and cosines are at
+// most 1): if the sum of all magnitudes in layer 4, with each feature bounded the same way, is far inside fp32, then so are the
+// features, the elements of the product and every partial sum over either.  And an element that underflows is off by 2^-150 at
+// most: what that can move a colour's pre-activation by has to be below 2^-30.  (NaN and infinity fail the comparisons.)
 template <int H>
+__global__ void __launch_bounds__(H) k_fold_bound(const float *__restrict__ w, int64_t P, float reach, int32_t *__restrict__ apart)
+{
+    using R = Regs<H>;
+    constexpr float LIMIT = 1e38f;
+    __shared__ float s_h[H], s_moved[H];
+    const float *src = w + blockIdx.x * P;
+    const int j = threadIdx.x;
+    float b = fabsf(src[R::ob1 + j]);
+    for (int i = 0; i < 63; ++i) b += fabsf(src[R::oW1 + i * H + j]) * (i < 3 ? reach : 1.0f);
+    s_h[j] = b;
+    __syncthreads();
+    b = fabsf(src[R::ob2 + j]);
+    for (int i = 0; i < H; ++i) b += fabsf(src[R::oW2 + i * H + j]) * s_h[i];
+    __syncthreads();
+    s_h[j] = b < 1.0f ? 1.0f : b; // (at least 1: the elements of the product are bounded as well)
+    __syncthreads();
+    b = fabsf(src[R::ob3 + 1 + j]);
+    float sum = 1.0f;
+    for (int i = 0; i < H; ++i) {
+        b += fabsf(src[R::oW3 + i * (H + 1) + 1 + j]) * s_h[i];
+        sum += s_h[i];
+    }
+    float out = 0.0f;
+    for (int c = 0; c < 3; ++c) out += fabsf(src[R::oW5 + 3 * j + c]);
+    s_moved[j] = out * sum * 7.0064923216240854e-46f; // 2^-150
+    __syncthreads();
+    s_h[j] = b;
+    __syncthreads();
+    b = fabsf(src[R::ob4 + j]);
+    float moved = 0.0f;
+    for (int i = 0; i < H; ++i) {
+        b += fabsf(src[R::oW4 + i * H + j]) * s_h[i];
+        moved += s_moved[i];
+    }
+    for (int i = H; i < H + 27; ++i) b += fabsf(src[R::oW4 + i * H + j]); // (unit directions)
+    if (!(b <= LIMIT) || !(moved <= 9.3132257e-10f)) atomicOr(apart, 1);
+}
+__global__ void k_clear_apart(int32_t *apart) { *apart = 0; }
+
+template <int H, bool FOLD>
 __global__ void k_pack_weights_f32(const float *__restrict__ w, int64_t P, int32_t N, float *__restrict__ packed)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -115,7 +169,7 @@ __global__ void k_pack_weights_f32(const float *__restrict__ w, int64_t P, int32
     if (i >= per * N) return;
     const int64_t net = i / per;
     const int e = (int)(i - net * per);
-    const int s = reg_source<H>(e >> 6, e & 63);
+    const int s = reg_source<H, FOLD>(e >> 6, e & 63);
     const float *src = w + net * P;
     if (s >= -1) {
         packed[i] = s < 0 ? 0.0f : src[s];
@@ -126,17 +180,17 @@ __global__ void k_pack_weights_f32(const float *__restrict__ w, int64_t P, int32
         double acc = bias ? (double)src[R::ob4 + col] : 0.0;
         for (int f = 0; f < H; ++f)
             acc = fma((double)(bias ? src[R::ob3 + 1 + f] : src[R::oW3 + k * (H + 1) + 1 + f]), (double)src[R::oW4 + f * H + col], acc);
-        // (finite factors stay finite: a product with an activation of zero is zero)
-        packed[i] = fabs(acc) <= 1.7976931348623157e308 ? (float)fmin(fmax(acc, -3.4028234663852886e38), 3.4028234663852886e38) : (float)acc;
+        packed[i] = (float)acc;
     }
 }
 
 // one network's weights in registers
-template <int H> struct NetF32 {
+template <int H, bool FOLD> struct NetF32 {
     using R = Regs<H>;
     static constexpr int HT = H / 16, HQ = H / 4; // output tiles per layer, MFMAs per hidden input vector
     float w1[HT][16], w2[HT][HQ], w4[HT][HQ + 8], wo[4][HQ];
-    f4 bias2[HT], bias_out;
+    float w3[FOLD ? 1 : HT][HQ]; // (FOLD: not there)
+    f4 bias2[HT], bias3[FOLD ? 1 : HT], bias_out;
     __device__ __forceinline__ void load(const float *__restrict__ packed, int32_t net, int lane)
     {
         const float *__restrict__ wp = packed + (int64_t)net * (R::N * KN_WAVE) + lane;
@@ -151,6 +205,12 @@ template <int H> struct NetF32 {
             for (int k = 0; k < HQ + 8; ++k) w4[t][k] = reg(R::W4 + (HQ + 8) * t + k);
 #pragma unroll
             for (int j = 0; j < 4; ++j) bias2[t][j] = reg(R::B2 + 4 * t + j);
+            if constexpr (!FOLD) {
+#pragma unroll
+                for (int k = 0; k < HQ; ++k) w3[t][k] = reg(R::W3 + HQ * t + k);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bias3[t][j] = reg(R::B3 + 4 * t + j);
+            }
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
@@ -172,7 +232,7 @@ __device__ __forceinline__ float sum_groups(float v)
 
 // n_tiles sample tiles (16 u .. 16 u + 15, u < n_tiles <= 4) of a staged chunk; lane l returns the pre-activations
 // (r, g, b, sigma) of sample l
-template <int H> __device__ __forceinline__ f4 eval_chunk(const NetF32<H> &w, const float (*stage)[8], int lane, int n_tiles)
+template <int H, bool FOLD> __device__ __forceinline__ f4 eval_chunk(const NetF32<H, FOLD> &w, const float (*stage)[8], int lane, int n_tiles)
 {
     constexpr int HT = H / 16, HQ = H / 4;
     const int n = lane & 15, g = lane >> 4;
@@ -236,11 +296,21 @@ template <int H> __device__ __forceinline__ f4 eval_chunk(const NetF32<H> &w, co
         for (int t2 = 0; t2 < HT; ++t2)
 #pragma unroll
             for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-        // layer 3: the density; its feature vector is folded into layer 4
+        // layer 3: the density; its feature vector is folded into layer 4, or takes the second hidden vector's place
         f4 o = zero4;
 #pragma unroll
         for (int k = 0; k < HQ; ++k) o[3] = fmaf(w.wo[3][k], h[k >> 2][k & 3], o[3]);
-        // layer 4: [second hidden vector through the folded feature layer, gamma(d)] -> H, ReLU
+        if constexpr (!FOLD) {
+#pragma unroll
+            for (int t2 = 0; t2 < HT; ++t2) {
+                acc[t2] = w.bias3[t2];
+#pragma unroll
+                for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w.w3[t2][k], h[k >> 2][k & 3], acc[t2]);
+            }
+#pragma unroll
+            for (int t2 = 0; t2 < HT; ++t2) h[t2] = acc[t2];
+        }
+        // layer 4: [second hidden vector through the folded feature layer (or the features), gamma(d)] -> H, ReLU
 #pragma unroll
         for (int t2 = 0; t2 < HT; ++t2) {
             acc[t2] = zero4;
@@ -267,7 +337,7 @@ template <int H> __device__ __forceinline__ f4 eval_chunk(const NetF32<H> &w, co
     return out;
 }
 
-template <int H>
+template <int H, bool FOLD>
 __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 2 : 1, H == 32 ? 2 : 1)))
     k_mlp_f32(const float *__restrict__ packed, KnSampleSrc src, const int32_t *__restrict__ perm,
               const KnTile *__restrict__ tiles, const int32_t *__restrict__ n_tiles, float *__restrict__ sigma,
@@ -287,7 +357,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
     const int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(wid + 1) * total_tiles / total_waves));
     if (t_lo >= t_hi) return;
 
-    NetF32<H> w;
+    NetF32<H, FOLD> w;
     auto descriptor = [&](int t) -> KnTile { return tiles[min(t, t_hi - 1)]; };
     auto sample_index = [&](const KnTile &d) {
         const int32_t pos = d.start + min(lane, d.len - 1);
@@ -315,7 +385,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-        const f4 out = eval_chunk<H>(w, stage[wave], lane, (tl.len + 15) >> 4); // (a small group needs no empty sample tiles)
+        const f4 out = eval_chunk<H, FOLD>(w, stage[wave], lane, (tl.len + 15) >> 4); // (a small group needs no empty sample tiles)
         __builtin_amdgcn_wave_barrier(); // the staging buffer is rewritten by the next iteration
 
         if (lane < tl.len) {
@@ -336,7 +406,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
 
 // A small batch in the caller's order: a wavefront takes a few consecutive points and evaluates them network by network
 // (kn_direct.hip says when and why).
-template <int H>
+template <int H, bool FOLD>
 __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 2 : 1, H == 32 ? 2 : 1)))
     k_eval_direct_f32(const float *__restrict__ packed, KnDirectJob job)
 {
@@ -347,7 +417,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
     unsigned long long pending = kn_direct_point(job, first, lane, pt);
     while (pending != 0ull) {
         const int32_t sel = __builtin_amdgcn_readlane(pt.net, (int)__builtin_ctzll(pending));
-        NetF32<H> w;
+        NetF32<H, FOLD> w;
         w.load(packed, sel, lane);
         const bool hit = pt.net == sel;
         const unsigned long long hits = __ballot(hit);
@@ -367,7 +437,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const f4 out = eval_chunk<H>(w, stage[wave], lane, (c + 15) / 16);
+        const f4 out = eval_chunk<H, FOLD>(w, stage[wave], lane, (c + 15) / 16);
         if (lane < c) {
             const int64_t to = first + __float_as_int(stage[wave][lane][6]);
             job.sigma[to] = fmaxf(out[3], 0.0f);
@@ -512,14 +582,17 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
 
 int kn_mlp_f32_tile_len(const kn_scene *) { return F32_TILE_LEN; }
 
+static int64_t image_bytes(int32_t H, int64_t N) { return (int64_t)(H == 32 ? Regs<32>::N : Regs<64>::N) * KN_WAVE * 4 * N; }
+
 // bytes of the packed weights of N networks of width H (0: no kernel for that width)
+// (+ one status word behind the last network, for kn_mlp_f32_pack_weights)
 int64_t kn_mlp_f32_packed_bytes(int32_t H, int64_t N)
 {
     if (H != 32 && H != 64) return 0;
-    return (int64_t)(H == 32 ? Regs<32>::N : Regs<64>::N) * KN_WAVE * 4 * N;
+    return image_bytes(H, N) + 256;
 }
 
-// fills sc->packed_w (kn_mlp_f32_packed_bytes bytes, assigned by the caller)
+// fills sc->packed_w (kn_mlp_f32_packed_bytes bytes, assigned by the caller) and sets sc->f32_apart; waits for the stream
 int kn_mlp_f32_pack_weights(kn_scene *sc, hipStream_t st)
 {
     const int H = sc->desc.hidden;
@@ -529,10 +602,20 @@ int kn_mlp_f32_pack_weights(kn_scene *sc, hipStream_t st)
     const int64_t blocks = kn_div_up(per * sc->N, 256);
     if (blocks > 0x7fffffffLL) return KN_E_UNSUPPORTED;
     const float *w = (const float *)sc->desc.weights;
-    if (H == 32)
-        hipLaunchKernelGGL(k_pack_weights_f32<32>, dim3((unsigned)blocks), dim3(256), 0, st, w, sc->P, sc->N, (float *)sc->packed_w);
-    else
-        hipLaunchKernelGGL(k_pack_weights_f32<64>, dim3((unsigned)blocks), dim3(256), 0, st, w, sc->P, sc->N, (float *)sc->packed_w);
+    int32_t *flag = (int32_t *)((char *)sc->packed_w + image_bytes(H, sc->N));
+    float reach = 1.0f;
+    for (int a = 0; a < 3; ++a) reach = fmaxf(reach, fmaxf(fabsf(sc->desc.aabb_min[a]), fabsf(sc->desc.aabb_max[a])));
+    hipLaunchKernelGGL(k_clear_apart, dim3(1), dim3(1), 0, st, flag);
+    KN_CHECK_LAUNCH();
+    hipLaunchKernelGGL(H == 32 ? k_fold_bound<32> : k_fold_bound<64>, dim3((unsigned)sc->N), dim3(H), 0, st, w, sc->P, reach, flag);
+    KN_CHECK_LAUNCH();
+    int32_t apart = 0;
+    KN_HIP(hipMemcpyAsync(&apart, flag, sizeof(apart), hipMemcpyDeviceToHost, st));
+    KN_HIP(hipStreamSynchronize(st));
+    sc->f32_apart = apart != 0;
+    auto pack = H == 32 ? (apart ? k_pack_weights_f32<32, false> : k_pack_weights_f32<32, true>)
+                        : (apart ? k_pack_weights_f32<64, false> : k_pack_weights_f32<64, true>);
+    hipLaunchKernelGGL(pack, dim3((unsigned)blocks), dim3(256), 0, st, w, sc->P, sc->N, (float *)sc->packed_w);
     KN_CHECK_LAUNCH();
     return KN_OK;
 }
@@ -549,7 +632,8 @@ int kn_mlp_f32_launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &src
     const int64_t fill = H == 32 ? 512 : 256;
     if (blocks > fill) blocks = fill;
     dim3 grid((unsigned)blocks), block(F32_WAVES * KN_WAVE);
-    auto kernel = H == 32 ? k_mlp_f32<32> : k_mlp_f32<64>;
+    auto kernel = H == 32 ? (sc->f32_apart ? k_mlp_f32<32, false> : k_mlp_f32<32, true>)
+                          : (sc->f32_apart ? k_mlp_f32<64, false> : k_mlp_f32<64, true>);
     if (ev_start && ev_stop)
         hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev_start, ev_stop, 0, w, src, b.perm, b.tiles, b.n_tiles, sigma, rgb);
     else
@@ -563,7 +647,8 @@ int kn_direct_f32_launch(const kn_scene *sc, hipStream_t st, const KnDirectJob &
 {
     const int H = sc->desc.hidden;
     if (H != 32 && H != 64) return KN_E_UNSUPPORTED;
-    auto kernel = H == 32 ? k_eval_direct_f32<32> : k_eval_direct_f32<64>;
+    auto kernel = H == 32 ? (sc->f32_apart ? k_eval_direct_f32<32, false> : k_eval_direct_f32<32, true>)
+                          : (sc->f32_apart ? k_eval_direct_f32<64, false> : k_eval_direct_f32<64, true>);
     const dim3 grid(blocks), block(F32_WAVES * KN_WAVE);
     if (ev_start && ev_stop) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev_start, ev_stop, 0, (const float *)sc->packed_w, job);
     else hipLaunchKernelGGL(kernel, grid, block, 0, st, (const float *)sc->packed_w, job);

@@ -289,6 +289,37 @@ def test_eval_grouped_fp32_weights_whose_product_leaves_the_range(H):
     check_eval(sc, ks.uniform_points(5000, 41, lo=(-1,) * 3, hi=(1,) * 3), ks.sphere_dirs(5000, 42))
 
 
+@pytest.mark.parametrize("H", [32, 64])
+@pytest.mark.parametrize("case", ["element", "sum", "underflow"])
+def test_eval_grouped_fp32_weights_that_only_separate_layers_can_carry(H, case):
+    """One network of eight whose feature layer and layer 4 are finite, with active units, while an element of their product
+    leaves fp32 (1e39), a sum over the product does (two terms of 1e39 whose features cancel), or an element vanishes (1e-49)."""
+    import torch
+    sc = scene_dict((2, 2, 2), (-1, -1, -1), (1, 1, 1), H, "f32", 28)
+    w, at = sc["weights"].copy(), 0
+    W, b = [], []
+    for fi, fo in ks.layer_shapes(H):
+        W.append(w[3, at:at + fi * fo].reshape(fi, fo))
+        b.append(w[3, at + fi * fo:at + fi * fo + fo])
+        at += fi * fo + fo
+    hidden, feature, last, out = {"element": ([0.01], [1e20], 1e19, 1e-37), "underflow": ([1e25], [1e-25], 1e-24, 1e24),
+                                  "sum": ([2.0 ** 30, 2.0 ** 30], [2.0 ** 50, -(2.0 ** 50) * (1 - 2.0 ** -6)], 2.0 ** 50, 2.0 ** -124)}[case]
+    W[2][:, 1], b[2][1] = 0.0, 0.0                  # feature 0 reads only the units below, and only column 0 of layer 4 reads
+    W[3][0, :], W[3][:, 0], b[3][0] = 0.0, 0.0, 0.0  # feature 0 and nothing else: its value is 1 / out
+    for i, (h, f) in enumerate(zip(hidden, feature)):
+        W[1][:, i], b[1][i], W[2][i, :] = 0.0, h, 0.0
+        W[2][i, 1] = f
+    W[3][0, 0], W[4][0, :] = last, out
+    assert np.isclose(sum(np.float64(h) * f for h, f in zip(hidden, feature)) * last * out, 1.0)
+    sc["weights"] = w
+    pts, dirs = ks.uniform_points(5000, 41, lo=(-1,) * 3, hi=(1,) * 3), ks.sphere_dirs(5000, 42)
+    dev = check_eval(sc, pts, dirs)
+    for n in (5000, 5):         # (ordered by counting; a handful, not ordered)
+        a, o = dev.eval_grouped(cuda(pts[:n]), cuda(dirs[:n])), make_pair(sc)[1].eval_points(pts[:n], dirs[:n])
+        torch.cuda.synchronize()
+        assert np.abs(a[0].cpu().numpy() - o[0]).max() <= 1e-4 and np.abs(a[1].cpu().numpy() - o[1]).max() <= 1e-4
+
+
 @pytest.mark.parametrize("wdtype,H", [("f16", 32), ("bf16", 64), ("f32", 32), ("f32", 64)])
 @pytest.mark.parametrize("res,M", [((16, 16, 16), 1), ((16, 16, 16), 63), ((5, 8, 5), 4097), ((16, 16, 16), 3001), ((2, 2, 2), 8190),
                                    ((2, 2, 2), 16385), ((24, 20, 28), 4095)])
