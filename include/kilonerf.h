@@ -275,6 +275,7 @@ int kn_eval_grouped_layered(kn_ctx *ctx, const kn_scene *scene, void *stream, co
  * axis x = b_min + (v + c) * cell, c in {1/6, 1/2, 5/6}, cell = (b_max - b_min) / occ_res, taken
  * in fp32 as fma((float)v + c, cell, b_min).  Only layers 1-3 of the networks run (the density
  * does not depend on the direction), with the scene's arithmetic (fp32, or 16-bit operands).
+ * Densities are never negative: a negative tau marks every voxel.
  * occupancy: dev, occ_res[0]*occ_res[1]*occ_res[2] bytes, x slowest -- the format kn_scene_desc
  * takes; any occupancy grid the scene itself was created with plays no role.  The workspace
  * (kn_extract_workspace_bytes, dev, 256-byte aligned) holds small index tables.  Asynchronous on

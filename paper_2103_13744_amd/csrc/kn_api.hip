@@ -820,13 +820,14 @@ extern "C" int kn_eval_grouped_layered(kn_ctx *ctx, const kn_scene *sc, void *st
 // Occupancy grid extraction (Sec. 3.4)
 namespace {
 
-__global__ void k_zero_bytes(uint8_t *p, int64_t n)
+__global__ void k_fill_bytes(uint8_t *p, int64_t n, uint8_t v)
 {
     const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 16;
     if (i + 16 <= n && ((uintptr_t)(p + i) & 15) == 0) {
-        *(uint4 *)(p + i) = make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t w = v * 0x01010101u;
+        *(uint4 *)(p + i) = make_uint4(w, w, w, w);
     } else {
-        for (int64_t j = i; j < n && j < i + 16; ++j) p[j] = 0;
+        for (int64_t j = i; j < n && j < i + 16; ++j) p[j] = v;
     }
 }
 
@@ -912,6 +913,15 @@ extern "C" int kn_extract_occupancy(kn_ctx *ctx, const kn_scene *sc, void *strea
     hipStream_t st = (hipStream_t)stream;
     KnCarver ws(workspace, workspace_bytes);
     KnStageTimer tm(ctx, st);
+    const dim3 fill_grid((unsigned)kn_div_up(kn_div_up(voxels, 16), 256));
+    if (tau < 0.0f) { // a density is 0 (no network, or ReLU) or more, and so above tau: the kernels below mark only what a network says
+        tm.begin();
+        hipLaunchKernelGGL(k_fill_bytes, fill_grid, dim3(256), 0, st, occupancy, voxels, (uint8_t)1);
+        KN_CHECK_LAUNCH();
+        tm.mark(KN_ST_SETUP);
+        tm.add(0, 0, 0, 1);
+        return KN_OK;
+    }
     if (sc->desc.wdtype != KN_F32) {
         KnProbeRowsJob rows{};
         int64_t *first_probe[3], units = 1;
@@ -965,7 +975,7 @@ extern "C" int kn_extract_occupancy(kn_ctx *ctx, const kn_scene *sc, void *strea
     job.parts = (int32_t)parts;
 
     tm.begin();
-    hipLaunchKernelGGL(k_zero_bytes, dim3((unsigned)kn_div_up(kn_div_up(voxels, 16), 256)), dim3(256), 0, st, occupancy, voxels);
+    hipLaunchKernelGGL(k_fill_bytes, fill_grid, dim3(256), 0, st, occupancy, voxels, (uint8_t)0);
     KN_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_probe_ranges, dim3(3), dim3(256), 0, st, job.occ, job.net, first[0], first[1], first[2]);
     KN_CHECK_LAUNCH();

@@ -1392,6 +1392,22 @@ def test_sparse_grid_extraction(wdtype):
         assert (ids < 0).sum() > 1000 and not got[ids < 0].any()
 
 
+@pytest.mark.parametrize("wdtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("occ_res", [(24, 20, 28), (25, 23, 30), (2, 3, 1)])
+def test_sparse_grid_extraction_below_any_density(wdtype, occ_res):
+    """Density 0, of a cell without a network too, is above a negative tau; none is above 0 there."""
+    sc = scene_dict((6, 5, 7), (-1, -1, -1), (1, 1, 1), 32, wdtype, 41, sigma_scale=5.0)
+    sc = configs.sparsify(sc, np.random.default_rng(8).random(6 * 5 * 7) < 0.5, 9)
+    dev, orc = make_pair(sc, threads=True)
+    want = orc.extract_occupancy(occ_res, -0.5)[0].reshape(occ_res)
+    assert want.all()
+    np.testing.assert_array_equal(dev.extract_occupancy(occ_res, -0.5).cpu().numpy(), want)
+    assert not dev.extract_occupancy(occ_res, 1e30).cpu().numpy().any()
+    none = dict(sc, weights=sc["weights"][:1].copy(), cell_net=np.full(6 * 5 * 7, -1, np.int32))
+    dev = make_pair(none)[0]
+    assert dev.extract_occupancy(occ_res, -1e-30).cpu().numpy().all() and not dev.extract_occupancy(occ_res, -0.0).cpu().numpy().any()
+
+
 def test_sparse_grid_with_more_cells_than_a_dense_grid_may_have():
     cfg = configs.config_sparse(96, 96)
     sc = cfg["scene"]
