@@ -431,66 +431,48 @@ __global__ void __launch_bounds__(OT_THREADS)
 // Ordering of a batch whose order inside a network nobody asks for: the rank of a point in its network comes from an
 // atomic, so there are no passes.  Latency bound (kn_order_pays says where it is used).  k_rank counts (counts: zeroed N + 1), k_place turns the counts into starts, every
 // workgroup for itself, and writes the list of points and the tiles.
-//   LDS_HIST (few networks, many points in each): a workgroup counts in LDS and takes its share of each network with one
-//   atomic; else one atomic per run of lanes with the same network (11 ns each on one address).
-constexpr int RANK_POINTS = 4; // per thread
-template <bool LDS_HIST>
-__global__ void __launch_bounds__(RO_THREADS)
+//   A workgroup counts its points per network in LDS and takes its share of each network with one atomic: atomics on one
+//   address execute one after the other, 11 ns each, and one per run of lanes with the same network took 398 us of a call for
+//   131,072 points in random order over two cells of 16^3 (26 like this, 26 over eight, 39 -> 34 all over the grid).  The lanes
+//   go through the networks side by side, so that an atomic instruction meets few lines (one atomic per network by the first
+//   point that counted it: 65,537 points, 10x16x10, this kernel 12 us; 5 like this), which 1,024 threads with a point each do
+//   faster than 256 with four (131,072 points fp32, 16^3 networks 53 -> 51 us a call, 24x20x16 72 -> 70).
+constexpr int RANK_THREADS = 1024, RANK_BINS = 4; // networks per thread whose atomics are in flight together
+__global__ void __launch_bounds__(RANK_THREADS)
     k_rank(const float *__restrict__ pts, int64_t M, KnGrid g, const int32_t *__restrict__ cell_net, int32_t *__restrict__ ids, int32_t N,
            int32_t *__restrict__ counts, uint2 *__restrict__ ranks, float *__restrict__ sigma, float *__restrict__ rgb)
 {
     extern __shared__ int32_t hist[]; // N + 1
-    const int lane = threadIdx.x & (KN_WAVE - 1);
-    if constexpr (LDS_HIST) {
-        for (int i = threadIdx.x; i <= N; i += RO_THREADS) hist[i] = 0;
-        __syncthreads();
-    }
-    const int64_t i0 = (int64_t)blockIdx.x * (RO_THREADS * RANK_POINTS) + threadIdx.x;
-    float p[RANK_POINTS][3];
+    const int64_t i = (int64_t)blockIdx.x * RANK_THREADS + threadIdx.x;
+    float p[3];
 #pragma unroll
-    for (int r = 0; r < RANK_POINTS; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) p[r][c] = pts[3 * min(i0 + r * RO_THREADS, M - 1) + c];
-    int32_t key[RANK_POINTS], rank[RANK_POINTS];
-#pragma unroll
-    for (int r = 0; r < RANK_POINTS; ++r) {
-        const int64_t i = i0 + r * RO_THREADS;
-        const int32_t id = kn_net_of_cell(cell_net, kn_grid_index(g, p[r][0], p[r][1], p[r][2]));
-        key[r] = i < M ? (id < 0 ? N : id) : -1;
-        if (i < M) {
-            if (ids) ids[i] = id;
-            if (id < 0) { // no network: the result is zero
-                sigma[i] = 0.0f;
-                rgb[3 * i] = rgb[3 * i + 1] = rgb[3 * i + 2] = 0.0f;
-            }
-        }
-        if constexpr (LDS_HIST) {
-            rank[r] = key[r] >= 0 ? atomicAdd(&hist[key[r]], 1) : 0;
-        } else {
-            const int32_t prev = __shfl_up(key[r], 1, KN_WAVE);
-            const unsigned long long heads = __ballot(lane == 0 || prev != key[r]); // bit l: lane l starts a run
-            const int head = KN_WAVE - 1 - __builtin_clzll(heads & (~0ull >> (KN_WAVE - 1 - lane)));
-            const unsigned long long behind = lane == KN_WAVE - 1 ? 0ull : heads >> (lane + 1); // the runs behind this lane
-            const int len = behind ? __builtin_ctzll(behind) + 1 : KN_WAVE - lane;             // (used at the head)
-            int32_t base = 0;
-            if (head == lane && key[r] >= 0) base = atomicAdd(&counts[key[r]], len);
-            rank[r] = __shfl(base, head, KN_WAVE) + lane - head;
+    for (int c = 0; c < 3; ++c) p[c] = pts[3 * min(i, M - 1) + c];
+    for (int n = threadIdx.x; n <= N; n += RANK_THREADS) hist[n] = 0;
+    const int32_t id = kn_net_of_cell(cell_net, kn_grid_index(g, p[0], p[1], p[2])), key = id < 0 ? N : id;
+    const bool active = i < M;
+    if (active) {
+        if (ids) ids[i] = id;
+        if (id < 0) { // no network: the result is zero
+            sigma[i] = 0.0f;
+            rgb[3 * i] = rgb[3 * i + 1] = rgb[3 * i + 2] = 0.0f;
         }
     }
-    if constexpr (LDS_HIST) {
-        __syncthreads();
-        for (int i = threadIdx.x; i <= N; i += RO_THREADS) {
-            const int32_t c = hist[i];
-            if (c > 0) hist[i] = atomicAdd(&counts[i], c);
-        }
-        __syncthreads();
+    __syncthreads();
+    const int32_t rank = active ? atomicAdd(&hist[key], 1) : 0;
+    __syncthreads();
+    for (int n = threadIdx.x; n <= N; n += RANK_THREADS * RANK_BINS) {
+        int32_t c[RANK_BINS];
 #pragma unroll
-        for (int r = 0; r < RANK_POINTS; ++r)
-            if (key[r] >= 0) rank[r] += hist[key[r]];
+        for (int q = 0; q < RANK_BINS; ++q) c[q] = n + q * RANK_THREADS <= N ? hist[n + q * RANK_THREADS] : 0;
+#pragma unroll
+        for (int q = 0; q < RANK_BINS; ++q)
+            if (c[q] > 0) c[q] = atomicAdd(&counts[n + q * RANK_THREADS], c[q]);
+#pragma unroll
+        for (int q = 0; q < RANK_BINS; ++q)
+            if (n + q * RANK_THREADS <= N) hist[n + q * RANK_THREADS] = c[q];
     }
-#pragma unroll
-    for (int r = 0; r < RANK_POINTS; ++r)
-        if (key[r] >= 0) ranks[i0 + r * RO_THREADS] = make_uint2((uint32_t)key[r], (uint32_t)rank[r]);
+    __syncthreads();
+    if (active) ranks[i] = make_uint2((uint32_t)key, (uint32_t)(rank + hist[key]));
 }
 
 // Dynamic LDS: PLACE_WAVES * 64 * per ints, the networks' starts; per: steps of 64 networks per wavefront.
@@ -1011,7 +993,6 @@ void carve_order(KnCarver &c, int64_t M, int32_t N, OrderWs &w)
 // Every workgroup of k_place scans the counts of all networks, in steps of 1,024: up to eight of them.
 constexpr int32_t ORDER_MAX_N = 8191;
 constexpr int64_t ORDER_MAX_M = 9 << 14;
-constexpr int32_t ORDER_LDS_N = 2048; // below: k_rank counts in LDS
 } // namespace
 
 int64_t kn_order_ws_bytes(int64_t M, int32_t N)
@@ -1024,10 +1005,12 @@ int64_t kn_order_ws_bytes(int64_t M, int32_t N)
 
 // For batches that do not fill the chip with the radix passes' workgroups: four launches instead of nine (six with up to 255
 // networks), and kernels of many small workgroups.  The evaluation then gathers its points and scatters its results, which
-// costs more than moving the samples does once a batch is far larger than the caches.  65,537 points, fp16, width 32:
-// 16^3 networks 65 us -> 33, 10x16x10 61 -> 28, 5x8x5 39 -> 25; fp32 (10x16x10) 77 -> 41.  At the border, against kn_count_run: 150,000
-// points on 16^3 networks 42 us against 57, skewed (atomics on few addresses) 58 against 56, 196,608 50 against 55 and 68 against 54;
-// on 10x16x10 33 against 40 and 36 against 39; on 5x8x8 30 against 31 and 38 against 32.
+// costs more than moving the samples does once a batch is far larger than the caches.  65,537 points, fp16, width 32, against the
+// radix passes: 16^3 networks 66 us -> 29, 10x16x10 61 -> 28, 5x8x5 39 -> 25; fp32 (10x16x10) 77 -> 35; in random order over two
+// cells of 16^3 60 -> 27.  The line was drawn at 147,456 points when atomics on few addresses slowed skewed batches beyond it
+// (150,000 points, 16^3 networks, nine in ten of them in a twentieth of the cells: 58 us against 56 for kn_count_run).  k_rank has lost that cost since, and the line stayed:
+// 150,000 points all over / skewed 36 / 38 us against 55 / 54, 196,608 41 / 42 against 54 / 52, on 10x16x10 networks 33 / 32
+// against 39 / 39, on 5x8x8 37 / 26 against 32 / 32.
 bool kn_order_pays(const kn_scene *sc, int64_t M)
 {
     return sc->N <= ORDER_MAX_N && M <= ORDER_MAX_M;
@@ -1042,13 +1025,9 @@ int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_
     carve_order(ws, M, N, w);
     if (!ws.ok()) return KN_E_WORKSPACE;
     KN_TRY(kn_fill_i32(st, w.counts, N + 1, 0));
-    const dim3 grid((unsigned)kn_div_up(M, RO_THREADS * RANK_POINTS)), block(RO_THREADS);
-    if (N < ORDER_LDS_N)
-        hipLaunchKernelGGL(k_rank<true>, grid, block, (size_t)(N + 1) * 4, st, points, M, sc->net_grid, sc->cell_net, user_ids, N, w.counts,
-                           w.ranks, sigma, rgb);
-    else
-        hipLaunchKernelGGL(k_rank<false>, grid, block, 0, st, points, M, sc->net_grid, sc->cell_net, user_ids, N, w.counts, w.ranks, sigma,
-                           rgb);
+    const dim3 grid((unsigned)kn_div_up(M, RANK_THREADS)), block(RANK_THREADS);
+    hipLaunchKernelGGL(k_rank, grid, block, (size_t)(N + 1) * 4, st, points, M, sc->net_grid, sc->cell_net, user_ids, N, w.counts, w.ranks,
+                       sigma, rgb);
     KN_CHECK_LAUNCH();
     if (tm) tm->mark(KN_ST_CELL);
     const int32_t per = (int32_t)kn_div_up(N + 1, PLACE_THREADS);
