@@ -108,7 +108,7 @@ int kn_last_hip_error(void);
 int64_t kn_params_per_net(int32_t hidden, int32_t L_pos, int32_t L_dir);
 
 /* A context on HIP device `device_index` (which must be a gfx950 device; the call makes it current in the calling
- * thread).  Allocates only host memory: the pinned, device-mapped mailboxes.  kn_destroy waits for the device. */
+ * thread).  Allocates only host memory: the pinned, device-mapped mailboxes and a status word.  kn_destroy waits for the device. */
 int kn_create(kn_ctx **out, int device_index);
 int kn_destroy(kn_ctx *ctx);
 

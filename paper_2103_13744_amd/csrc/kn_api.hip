@@ -18,7 +18,7 @@ int kn_mlp_mfma_launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &sr
                        float *sigma, float *rgb, hipEvent_t ev_start, hipEvent_t ev_stop);
 int kn_mlp_mfma_tile_len(const kn_scene *sc);
 int kn_mlp_f32_tile_len(const kn_scene *sc);
-int kn_mlp_f32_pack_weights(kn_scene *sc, hipStream_t st);
+int kn_mlp_f32_pack_weights(kn_scene *sc, hipStream_t st, const KnHostWord &word);
 int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, const KnProbeRowsJob &job);
 int kn_probe_f32_launch(const kn_scene *sc, hipStream_t st, const KnProbeJob &job);
 int64_t kn_layered_act_bytes(const kn_scene *sc, int64_t M);
@@ -233,15 +233,18 @@ extern "C" int kn_create(kn_ctx **out, int device_index)
     ctx->use_counter = 0;
     ctx->static_scratch = scratch_ptr;
     for (auto &m : ctx->mailbox) m = KnMailbox{nullptr, nullptr, 0ull, 0ull, 0ull, nullptr, false};
+    ctx->scene_word = KnHostWord{nullptr, nullptr};
     void *hp = nullptr, *dp = nullptr;
-    if (hipHostMalloc(&hp, 64 * KN_MAILBOXES, hipHostMallocMapped) == hipSuccess && hipHostGetDevicePointer(&dp, hp, 0) == hipSuccess) {
-        memset(hp, 0, 64 * KN_MAILBOXES);
+    constexpr size_t host_bytes = 64 * (KN_MAILBOXES + 1); // the mailboxes, then the scenes' word
+    if (hipHostMalloc(&hp, host_bytes, hipHostMallocMapped) == hipSuccess && hipHostGetDevicePointer(&dp, hp, 0) == hipSuccess) {
+        memset(hp, 0, host_bytes);
+        ctx->scene_word = KnHostWord{(volatile int32_t *)((char *)hp + 64 * KN_MAILBOXES), (int32_t *)((char *)dp + 64 * KN_MAILBOXES)};
         for (int i = 0; i < KN_MAILBOXES; ++i) {
             ctx->mailbox[i].host = (volatile unsigned long long *)((char *)hp + 64 * i);
             ctx->mailbox[i].dev = (unsigned long long *)((char *)dp + 64 * i);
         }
     } else if (hp) {
-        (void)hipHostFree(hp); // (kn_render then waits for its stream instead of polling)
+        (void)hipHostFree(hp); // (kn_render then waits for its stream instead of polling, and fp32 layers are kept apart)
     }
     *out = ctx;
     return KN_OK;
@@ -601,7 +604,12 @@ extern "C" int kn_scene_create(kn_ctx *ctx, const kn_scene_desc *desc, void *str
         sc->occ_grid = sc->net_grid;
         sc->content_box = sc->net_grid;
     }
-    if (rc == KN_OK) rc = desc->wdtype == KN_F32 ? kn_mlp_f32_pack_weights(sc, st) : kn_mlp_pack_weights(sc, st);
+    if (rc == KN_OK && desc->wdtype == KN_F32) {
+        std::lock_guard<std::mutex> lock(ctx->scene_mutex);
+        rc = kn_mlp_f32_pack_weights(sc, st, ctx->scene_word);
+    } else if (rc == KN_OK) {
+        rc = kn_mlp_pack_weights(sc, st);
+    }
     // the descriptor's buffers may go once the call returns
     if (rc == KN_OK && hipStreamSynchronize(st) != hipSuccess) rc = KN_E_HIP;
     if (rc != KN_OK) {

@@ -41,6 +41,12 @@ struct KnMailbox {
     bool taken;
 };
 
+// A word of pinned, device-mapped host memory that a kernel reports to its own call through.
+struct KnHostWord {
+    volatile int32_t *host; // nullptr: could not be allocated
+    int32_t *dev;
+};
+
 enum KnStage { KN_ST_CELL = 0, KN_ST_MARCH, KN_ST_BUCKET, KN_ST_MLP, KN_ST_BLEND, KN_ST_SETUP, KN_ST_NONE };
 constexpr int KN_N_EVENTS = 1024;
 constexpr int KN_DEFAULT_SLOTS = 128, KN_DEFAULT_GROWTH = 32;
@@ -72,6 +78,8 @@ struct kn_ctx {
     // streams would overwrite each other).
     KnMailbox mailbox[KN_MAILBOXES];
     unsigned long long use_counter;
+    std::mutex scene_mutex; // scene_word belongs to one scene creation at a time
+    KnHostWord scene_word;
     void *static_scratch; // device address of the library's static scratch array on this device
 };
 // snapshot of the schedule and limits, taken under the mutex at the start of a call

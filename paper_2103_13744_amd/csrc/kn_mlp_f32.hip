@@ -22,7 +22,7 @@
 // the second hidden vector.  The weights' image holds the product of the two (64-bit sums, rounded once), and layer 4 is
 // evaluated on the second hidden vector: H/16 * H/4 MFMAs of a sample tile fewer, and a rounding fewer in the results.
 // Weights so large or so small that the product, or a sum over it, could leave fp32 where the two layers by themselves
-// do not (k_fold_bound) are kept apart: a scene with such a network is evaluated by the FOLD = false variants.
+// do not (fold_leaves_range) are kept apart: a scene with such a network is evaluated by the FOLD = false variants.
 //
 // Density and colour (1 + 3 outputs) would be 4 of 16 rows of their MFMAs.  They are dot products on the vector ALU
 // instead, over the hidden units a lane holds, summed over the four lane groups with lane swaps; lane group u keeps the
@@ -75,9 +75,8 @@ template <int H> struct Regs {
                          oW4 = ob3 + H + 1, ob4 = oW4 + (H + 27) * H, oW5 = ob4 + H, ob5 = oW5 + 3 * H;
 };
 
-// canonical index of the value in register r of lane `lane`; -1 = zero; with FOLD, FOLD_ROW - (unit * H + col): that element
-// of the product of feature layer and layer 4; FOLD_BIAS - col: element of the folded bias, b4 + W4f^T b3f
-constexpr int FOLD_ROW = -2, FOLD_BIAS = -2 - 64 * 64;
+// canonical index of the value in register r of lane `lane`; -1 = zero (or, with FOLD, an element of the product of feature
+// layer and layer 4 or of its bias, which the packing kernel forms)
 template <int H, bool FOLD> __device__ int reg_source(int r, int lane)
 {
     using R = Regs<H>;
@@ -96,11 +95,11 @@ template <int H, bool FOLD> __device__ int reg_source(int r, int lane)
     }
     if (r < R::WO) {
         const int t = (r - R::W4) / (HQ + 8), k = (r - R::W4) % (HQ + 8), col = 16 * t + m;
-        if (k < HQ) return FOLD ? FOLD_ROW - (unit(k) * H + col) : R::oW4 + unit(k) * H + col;
+        if (k < HQ) return FOLD ? -1 : R::oW4 + unit(k) * H + col;
         const int q = k - HQ;
         if (g < 3) return R::oW4 + (H + 3 + 6 * (q >> 1) + 3 * (q & 1) + g) * H + col;
         if (q < 3) return R::oW4 + (H + q) * H + col;
-        return q == 3 ? (FOLD ? FOLD_BIAS - col : R::ob4 + col) : -1;
+        return q == 3 && !FOLD ? R::ob4 + col : -1;
     }
     if (r < R::B2) {
         const int c = (r - R::WO) / HQ, k = (r - R::WO) % HQ;
@@ -108,7 +107,6 @@ template <int H, bool FOLD> __device__ int reg_source(int r, int lane)
     }
     if (r < R::BO) return R::ob2 + 16 * ((r - R::B2) >> 2) + 4 * g + ((r - R::B2) & 3);
     if (r < R::W3) return r - R::BO < 3 ? R::ob5 + (r - R::BO) : R::ob3;
-    if (FOLD) return -1; // (not read)
     if (r < R::B3) {
         const int t = (r - R::W3) / HQ, k = (r - R::W3) % HQ;
         return R::oW3 + unit(k) * (H + 1) + 1 + 16 * t + m;
@@ -116,74 +114,148 @@ template <int H, bool FOLD> __device__ int reg_source(int r, int lane)
     return R::ob3 + 1 + 16 * ((r - R::B3) >> 2) + 4 * g + ((r - R::B3) & 3);
 }
 
-// Sets `apart` unless the product of feature layer and layer 4 may stand for the two.  One workgroup of H threads per network;
-// thread j bounds output j of each layer for every point of the scene's box (|coordinate| <= reach; sines and cosines are at
-// most 1): if the sum of all magnitudes in layer 4, with each feature bounded the same way, is far inside fp32, then so are the
-// features, the elements of the product and every partial sum over either.  And an element that underflows is off by 2^-150 at
-// most: what that can move a colour's pre-activation by has to be below 2^-30.  (NaN and infinity fail the comparisons.)
+// the wavefront's LDS writes before, its reads after
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Whether the product of feature layer and layer 4 may not stand for the two.  Lane j < H of a wavefront bounds output j of each
+// layer for every point of the scene's box (|coordinate| <= reach; sines and cosines are at most 1): if the sum of all
+// magnitudes in layer 4, with each feature bounded the same way, is far inside fp32, then so are the features, the elements of
+// the product and every partial sum over either.  And an element that underflows is off by 2^-150 at most: what that can move a
+// colour's pre-activation by has to be below 2^-30.  (NaN and infinity fail the comparisons.)
 template <int H>
-__global__ void __launch_bounds__(H) k_fold_bound(const float *__restrict__ w, int64_t P, float reach, int32_t *__restrict__ apart)
+__device__ bool fold_leaves_range(const float *__restrict__ src, const float *w3, const float *w4, float reach, int j, float *s_h, float *s_moved)
 {
     using R = Regs<H>;
     constexpr float LIMIT = 1e38f;
-    __shared__ float s_h[H], s_moved[H];
-    const float *src = w + blockIdx.x * P;
-    const int j = threadIdx.x;
+    j = min(j, H - 1); // (the lanes behind repeat the last output)
     float b = fabsf(src[R::ob1 + j]);
+#pragma unroll
     for (int i = 0; i < 63; ++i) b += fabsf(src[R::oW1 + i * H + j]) * (i < 3 ? reach : 1.0f);
     s_h[j] = b;
-    __syncthreads();
+    wave_sync();
     b = fabsf(src[R::ob2 + j]);
+#pragma unroll
     for (int i = 0; i < H; ++i) b += fabsf(src[R::oW2 + i * H + j]) * s_h[i];
-    __syncthreads();
+    wave_sync();
     s_h[j] = b < 1.0f ? 1.0f : b; // (at least 1: the elements of the product are bounded as well)
-    __syncthreads();
+    wave_sync();
     b = fabsf(src[R::ob3 + 1 + j]);
     float sum = 1.0f;
+#pragma unroll 8
     for (int i = 0; i < H; ++i) {
-        b += fabsf(src[R::oW3 + i * (H + 1) + 1 + j]) * s_h[i];
+        b += fabsf(w3[i * (H + 1) + 1 + j]) * s_h[i];
         sum += s_h[i];
     }
     float out = 0.0f;
     for (int c = 0; c < 3; ++c) out += fabsf(src[R::oW5 + 3 * j + c]);
     s_moved[j] = out * sum * 7.0064923216240854e-46f; // 2^-150
-    __syncthreads();
+    wave_sync();
     s_h[j] = b;
-    __syncthreads();
+    wave_sync();
     b = fabsf(src[R::ob4 + j]);
     float moved = 0.0f;
+#pragma unroll 8
     for (int i = 0; i < H; ++i) {
-        b += fabsf(src[R::oW4 + i * H + j]) * s_h[i];
+        b += fabsf(w4[i * H + j]) * s_h[i];
         moved += s_moved[i];
     }
+#pragma unroll
     for (int i = H; i < H + 27; ++i) b += fabsf(src[R::oW4 + i * H + j]); // (unit directions)
-    if (!(b <= LIMIT) || !(moved <= 9.3132257e-10f)) atomicOr(apart, 1);
+    return !(b <= LIMIT) || !(moved <= 9.3132257e-10f);
 }
-__global__ void k_clear_apart(int32_t *apart) { *apart = 0; }
 
+// One workgroup per network.  Four (H = 64: eight) wavefronts gather the image register by register (which value a register
+// holds is uniform but for the lane) and, with FOLD, form the product of the two layers from LDS; one more forms its bias and
+// sets `apart` where the product may not be used.
+// Bound by the latency of its few trips to memory on small scenes, by memory traffic on large ones.
+// Against a thread per element that sums its own product over global memory (which made no bound), creating a scene of 16^3
+// networks: width 32 105 -> 71 us (this kernel 50, 232 MB), width 64 469 -> 210 (189, 628 MB); 32^3 931 -> 444 and 3,572 ->
+// 1,447; 2^3 24 -> 29 and 25 -> 36 (the bound's chain of layers, and the wait for it).
+template <int H> constexpr int PACK_WAVES = H == 32 ? 4 : 8;
 template <int H, bool FOLD>
-__global__ void k_pack_weights_f32(const float *__restrict__ w, int64_t P, int32_t N, float *__restrict__ packed)
+__global__ void __launch_bounds__((PACK_WAVES<H> + FOLD) * KN_WAVE)
+    k_pack_weights_f32(const float *__restrict__ w, int64_t P, float reach, float *__restrict__ packed, int32_t *__restrict__ apart)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    constexpr int64_t per = Regs<H>::N * KN_WAVE;
-    if (i >= per * N) return;
-    const int64_t net = i / per;
-    const int e = (int)(i - net * per);
-    const int s = reg_source<H, FOLD>(e >> 6, e & 63);
-    const float *src = w + net * P;
-    if (s >= -1) {
-        packed[i] = s < 0 ? 0.0f : src[s];
-    } else {
-        using R = Regs<H>;
-        const bool bias = s <= FOLD_BIAS;
-        const int k = bias ? 0 : (FOLD_ROW - s) / H, col = bias ? FOLD_BIAS - s : (FOLD_ROW - s) % H;
-        double acc = bias ? (double)src[R::ob4 + col] : 0.0;
-        for (int f = 0; f < H; ++f)
-            acc = fma((double)(bias ? src[R::ob3 + 1 + f] : src[R::oW3 + k * (H + 1) + 1 + f]), (double)src[R::oW4 + f * H + col], acc);
-        packed[i] = (float)acc;
+    using R = Regs<H>;
+    constexpr int HQ = R::HQ, WAVES = PACK_WAVES<H>;
+    __shared__ float s_w3[FOLD ? H * (H + 1) : 1], s_w4[FOLD ? H * H : 1], s_h[H], s_moved[H];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
+    const float *__restrict__ src = w + blockIdx.x * P;
+    float *__restrict__ image = packed + (int64_t)blockIdx.x * (R::N * KN_WAVE);
+    if constexpr (FOLD) {
+        constexpr int T = (WAVES + 1) * KN_WAVE, STEPS = (H * (H + 1) + T - 1) / T;
+        float v[2][STEPS]; // (all loads in flight together)
+#pragma unroll
+        for (int q = 0; q < STEPS; ++q) {
+            const int i = threadIdx.x + q * T;
+            v[0][q] = src[R::oW3 + min(i, H * (H + 1) - 1)];
+            v[1][q] = src[R::oW4 + min(i, H * H - 1)];
+        }
+#pragma unroll
+        for (int q = 0; q < STEPS; ++q) {
+            const int i = threadIdx.x + q * T;
+            if (i < H * (H + 1)) s_w3[i] = v[0][q];
+            if (i < H * H) s_w4[i] = v[1][q];
+        }
+        __syncthreads();
+        if (wave == WAVES) {
+            if (lane < H) {
+                double acc = (double)src[R::ob4 + lane];
+#pragma unroll 16
+                for (int f = 0; f < H; ++f) acc = fma((double)src[R::ob3 + 1 + f], (double)s_w4[f * H + lane], acc);
+                image[(R::W4 + (HQ + 8) * (lane >> 4) + HQ + 3) * KN_WAVE + 48 + (lane & 15)] = (float)acc;
+            }
+            const bool out_of_range = fold_leaves_range<H>(src, s_w3, s_w4, reach, lane, s_h, s_moved);
+            if (__ballot(out_of_range) != 0ull && lane == 0) __hip_atomic_store(apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            return;
+        }
+    }
+    constexpr int LAST = FOLD ? R::W3 : R::N, BATCH = 16; // registers whose loads are in flight together
+    for (int r0 = wave; r0 < LAST; r0 += WAVES * BATCH) {
+        int at[BATCH];
+        float v[BATCH];
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) at[q] = reg_source<H, FOLD>(min(r0 + WAVES * q, LAST - 1), lane);
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) v[q] = src[max(at[q], 0)];
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) {
+            const int r = r0 + WAVES * q, k = r >= R::W4 && r < R::WO ? (r - R::W4) % (HQ + 8) : -1;
+            // (FOLD: elements of the product and its bias are written elsewhere)
+            if (r < LAST && !(FOLD && ((k >= 0 && k < HQ) || (k == HQ + 3 && lane >= 48)))) image[r * KN_WAVE + lane] = at[q] < 0 ? 0.0f : v[q];
+        }
+    }
+    if constexpr (FOLD) { // thread: rows 4 kt .. + 3 of the product, columns ct + COLS c
+        constexpr int CT = H * H / (4 * WAVES * KN_WAVE), COLS = H / CT;
+        static_assert(CT >= 1 && COLS % 16 == 0, "a thread's columns lie in different output tiles at the same lane");
+        const int kt = threadIdx.x / COLS, ct = threadIdx.x % COLS;
+        double acc[4][CT] = {};
+#pragma unroll 4
+        for (int f = 0; f < H; ++f) {
+            double b[CT];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) b[c] = (double)s_w4[f * H + ct + COLS * c];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double a = (double)s_w3[(4 * kt + q) * (H + 1) + 1 + f];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) acc[q][c] = fma(a, b[c], acc[q][c]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) { // hidden unit 4 kt + q is MFMA 4 (kt / 4) + q of lane group kt % 4
+                const int col = ct + COLS * c;
+                image[(R::W4 + (HQ + 8) * (col >> 4) + 4 * (kt >> 2) + q) * KN_WAVE + 16 * (kt & 3) + (col & 15)] = (float)acc[q][c];
+            }
     }
 }
-
 // one network's weights in registers
 template <int H, bool FOLD> struct NetF32 {
     using R = Regs<H>;
@@ -585,38 +657,37 @@ int kn_mlp_f32_tile_len(const kn_scene *) { return F32_TILE_LEN; }
 static int64_t image_bytes(int32_t H, int64_t N) { return (int64_t)(H == 32 ? Regs<32>::N : Regs<64>::N) * KN_WAVE * 4 * N; }
 
 // bytes of the packed weights of N networks of width H (0: no kernel for that width)
-// (+ one status word behind the last network, for kn_mlp_f32_pack_weights)
 int64_t kn_mlp_f32_packed_bytes(int32_t H, int64_t N)
 {
     if (H != 32 && H != 64) return 0;
-    return image_bytes(H, N) + 256;
+    return (int64_t)(H == 32 ? Regs<32>::N : Regs<64>::N) * KN_WAVE * 4 * N;
 }
 
 // fills sc->packed_w (kn_mlp_f32_packed_bytes bytes, assigned by the caller) and sets sc->f32_apart; waits for the stream
-int kn_mlp_f32_pack_weights(kn_scene *sc, hipStream_t st)
+int kn_mlp_f32_pack_weights(kn_scene *sc, hipStream_t st, const KnHostWord &word)
 {
     const int H = sc->desc.hidden;
     if (H != 32 && H != 64) return KN_E_UNSUPPORTED;
     if (!sc->packed_w) return KN_E_INVALID_ARG;
-    const int64_t per = (H == 32 ? Regs<32>::N : Regs<64>::N) * KN_WAVE;
-    const int64_t blocks = kn_div_up(per * sc->N, 256);
-    if (blocks > 0x7fffffffLL) return KN_E_UNSUPPORTED;
     const float *w = (const float *)sc->desc.weights;
-    int32_t *flag = (int32_t *)((char *)sc->packed_w + image_bytes(H, sc->N));
+    float *image = (float *)sc->packed_w;
     float reach = 1.0f;
     for (int a = 0; a < 3; ++a) reach = fmaxf(reach, fmaxf(fabsf(sc->desc.aabb_min[a]), fabsf(sc->desc.aabb_max[a])));
-    hipLaunchKernelGGL(k_clear_apart, dim3(1), dim3(1), 0, st, flag);
-    KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL(H == 32 ? k_fold_bound<32> : k_fold_bound<64>, dim3((unsigned)sc->N), dim3(H), 0, st, w, sc->P, reach, flag);
-    KN_CHECK_LAUNCH();
-    int32_t apart = 0;
-    KN_HIP(hipMemcpyAsync(&apart, flag, sizeof(apart), hipMemcpyDeviceToHost, st));
-    KN_HIP(hipStreamSynchronize(st));
-    sc->f32_apart = apart != 0;
-    auto pack = H == 32 ? (apart ? k_pack_weights_f32<32, false> : k_pack_weights_f32<32, true>)
-                        : (apart ? k_pack_weights_f32<64, false> : k_pack_weights_f32<64, true>);
-    hipLaunchKernelGGL(pack, dim3((unsigned)blocks), dim3(256), 0, st, w, sc->P, sc->N, (float *)sc->packed_w);
-    KN_CHECK_LAUNCH();
+    const dim3 grid((unsigned)sc->N), without((H == 32 ? PACK_WAVES<32> : PACK_WAVES<64>) * KN_WAVE), with_fold(without.x + KN_WAVE);
+    sc->f32_apart = true;
+    if (word.host) {
+        *word.host = 0;
+        auto pack = H == 32 ? k_pack_weights_f32<32, true> : k_pack_weights_f32<64, true>;
+        hipLaunchKernelGGL(pack, grid, with_fold, 0, st, w, sc->P, reach, image, word.dev);
+        KN_CHECK_LAUNCH();
+        KN_HIP(hipStreamSynchronize(st));
+        sc->f32_apart = *word.host != 0;
+    }
+    if (sc->f32_apart) {
+        auto pack = H == 32 ? k_pack_weights_f32<32, false> : k_pack_weights_f32<64, false>;
+        hipLaunchKernelGGL(pack, grid, without, 0, st, w, sc->P, reach, image, (int32_t *)nullptr);
+        KN_CHECK_LAUNCH();
+    }
     return KN_OK;
 }
 

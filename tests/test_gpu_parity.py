@@ -922,6 +922,59 @@ def test_scene_in_a_buffer_the_caller_lends():
     assert L.kn_scene_destroy(h) == 0
 
 
+def test_fp32_scenes_created_from_two_threads_with_and_without_folded_layers():
+    """Whether a scene's layers are kept apart is reported to the scene's own creation."""
+    import threading
+    import torch
+    import paper_2103_13744_amd as kn
+    sc = scene_dict((2, 2, 2), (0, 0, 0), (1, 1, 1), 32, "f32", 29)
+    plain, large = cuda(sc["weights"]), cuda(sc["weights"])
+    at = 63 * 32 + 32 + 32 * 32 + 32
+    large[:, at:at + 32 * 33] *= 1e25                 # feature weights whose product with layer 4's leaves the bound for the fold
+    large[:, at + 32 * 33 + 33:at + 32 * 33 + 33 + 32 * 32] *= 1e15     # (large but finite: 1e40 as a product)
+    pts, dirs = cuda(ks.uniform_points(500, 3)), cuda(ks.sphere_dirs(500, 4))
+
+    def results(w, out, n):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(n):
+                s = kn.Scene((2, 2, 2), (0, 0, 0), (1, 1, 1), 32, w)
+                out.append(torch.cat([v.reshape(-1) for v in s.eval_grouped(pts, dirs)]).cpu())
+                s.close()
+    torch.cuda.synchronize()
+    outs = ([], [], [], [])
+    results(plain, outs[0], 1)
+    results(large, outs[1], 1)
+    threads = [threading.Thread(target=results, args=(w, o, 20)) for w, o in ((plain, outs[2]), (large, outs[3]))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for got, want in ((outs[2], outs[0]), (outs[3], outs[1])):
+        assert len(got) == 20 and all(torch.equal(g.nan_to_num(-3.0), want[0].nan_to_num(-3.0)) for g in got)
+    assert not torch.equal(outs[0][0], outs[1][0])
+
+
+def test_fp32_scene_creation_takes_a_few_copies_of_its_weights():
+    """The folded layers are formed from LDS; summed over global memory by a thread per element, a scene of 16^3 networks of
+    width 64 took 3.8 times as long as a copy of its weights (1.7 like this)."""
+    import time
+    import torch
+    import paper_2103_13744_amd as kn
+    w = torch.rand((4096, ks.params_per_net(64)), device="cuda") * 0.2 - 0.1
+
+    def best_us(f):
+        times = []
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            f()
+            torch.cuda.synchronize()
+            times.append((time.perf_counter() - t) * 1e6)
+        return min(times)
+    spare = torch.empty_like(w)
+    assert best_us(lambda: kn.Scene((16, 16, 16), (0, 0, 0), (1, 1, 1), 64, w).close()) <= 2.5 * best_us(lambda: spare.copy_(w))
+
+
 def test_render_network_grid_above_the_fused_grouping_limit():
     """21^3 = 9,261 networks: more than the grouping keeps a counter each for in LDS (hash tables instead), and not a
     multiple of four (the offset arrays then start at odd alignments)."""
