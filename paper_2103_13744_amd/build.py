@@ -20,9 +20,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-ffp-contract=o
          "-I", INCLUDE, "-I", CSRC]
 
 
-# The matrix-core MLP kernel uses the VALU "times two" output modifier in its double-angle recurrence; the
+# The matrix-core MLP kernels use the VALU "times two" output modifier in their double-angle recurrence; the
 # compiler only emits it with flushed fp32 denormals, without IEEE mode, and when signed zeros / NaNs need
-# no special care.  Only that file gets these flags; the index arithmetic elsewhere stays strict.
+# no special care.  Two files get these flags.  In kn_mlp_mfma.hip no index depends on them (lattice points are rebuilt,
+# not tested); kn_fused.hip also marches and blends, with denormals switched on around those parts, and rays that are not
+# finite end in its set-up.  The index arithmetic elsewhere stays strict.
 _MLP16_FLAGS = ["-fgpu-flush-denormals-to-zero", "-fno-signed-zeros", "-fno-honor-nans", "-mno-amdgpu-ieee"]
 PER_FILE_FLAGS = {"kn_mlp_mfma.hip": _MLP16_FLAGS, "kn_fused.hip": _MLP16_FLAGS}
 

@@ -76,6 +76,28 @@ __device__ __forceinline__ int opaque(int lane)
     return lane;
 }
 
+// The file is compiled for flushed fp32 denormals (the evaluation's encoding needs that, see build.py).  Where lattice points
+// are placed and tested, and in the blend, denormals count: a point at -1e-40 lies outside a box that starts at 0.  There the mode
+// register says so; the compiler's own divisions would set it back, so none is left to it in those parts, and neither is a
+// multiplication by two (the output modifier does nothing there).
+__device__ __forceinline__ void keep_denormals(bool keep)
+{
+    constexpr int FP32_DENORM = 1 | (4 << 6) | (1 << 11); // MODE, bits 4 and 5
+    if (keep) __builtin_amdgcn_s_setreg(FP32_DENORM, 3);
+    else __builtin_amdgcn_s_setreg(FP32_DENORM, 0);
+}
+// a / b rounded to nearest, with denormals kept: the instruction set's scaled division
+__device__ __forceinline__ float divide(float a, float b)
+{
+    bool scaled, unused;
+    const float d = __builtin_amdgcn_div_scalef(a, b, false, &unused), n = __builtin_amdgcn_div_scalef(a, b, true, &scaled);
+    float r = __builtin_amdgcn_rcpf(d);
+    r = fmaf(fmaf(-d, r, 1.0f), r, r);
+    float q = n * r;
+    q = fmaf(fmaf(-d, q, n), r, q);
+    return __builtin_amdgcn_div_fixupf(__builtin_amdgcn_div_fmasf(fmaf(-d, q, n), r, q, scaled), b, a);
+}
+
 // float -> floor as an integer, as the instruction defines it for every input: saturated, NaN -> 0
 __device__ __forceinline__ int32_t floor_int(float f)
 {
@@ -100,9 +122,9 @@ __device__ __forceinline__ bool voxel_coords(const VoxelFast &g, float x, float 
 
 __device__ __forceinline__ void voxel_coords_exact(const VoxelFast &g, float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz)
 {
-    ix = floor_int((x - g.bmin[0]) / g.cell[0]);
-    iy = floor_int((y - g.bmin[1]) / g.cell[1]);
-    iz = floor_int((z - g.bmin[2]) / g.cell[2]);
+    ix = floor_int(divide(x - g.bmin[0], g.cell[0]));
+    iy = floor_int(divide(y - g.bmin[1], g.cell[1]));
+    iz = floor_int(divide(z - g.bmin[2], g.cell[2]));
     __builtin_amdgcn_sched_barrier(0); // (the divisions of several points side by side would cost more registers than there are)
 }
 __device__ __forceinline__ bool inside(const VoxelFast &g, int32_t ix, int32_t iy, int32_t iz)
@@ -311,6 +333,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
             }
             wave_sync();
 
+            keep_denormals(true);
             // ---- march: up to S kept samples per ray.  A step tests G * STEPS consecutive lattice points, STEPS per lane,
             // with all look-ups of the step in flight together; the skip field is asked at each lane's last point only.
             // What the loop reads of the arguments is copied out in front of it (scalar registers): a scalar load inside costs
@@ -407,7 +430,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
                             const int at_slot = (rank << lgP) + slot;
                             float dscale = 1.0f;
                             if constexpr (STRAT)
-                                dscale = (kn_lattice_t<true>(t_near, step, k0 + c + 1, ray_key) - kn_lattice_t<true>(t_near, step, k0 + c, ray_key)) / step;
+                                dscale = divide(kn_lattice_t<true>(t_near, step, k0 + c + 1, ray_key) - kn_lattice_t<true>(t_near, step, k0 + c, ray_key), step);
                             slots[at_slot] = (f4){x[c], y[c], z[c], dscale};
                             idx[at_slot] = (uint16_t)net[c];
                         }
@@ -427,6 +450,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
         wave_sync();
 
         // ---- evaluate: one network after the other
+        keep_denormals(false);
         {
             const ArgsPtr a = opaque(args);
             const int ln = opaque(lane), n = ln & 15, g = ln >> 4;
@@ -539,6 +563,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
         wave_sync();
 
         // ---- blend (Eq. 2-4): the sequential recurrence, the same in all lanes of a ray's group
+        keep_denormals(true);
         {
             const ArgsPtr a = opaque(args);
             const int ln = opaque(lane), slot = ln & (P - 1), gl = ln >> lgP;
@@ -571,6 +596,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
                 blended += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(gl == 0 ? used : 0), KN_WAVE - 1);
             }
         }
+        keep_denormals(false);
         __builtin_amdgcn_wave_barrier(); // the slots are rewritten by the next round
     }
     if (args->counters && lane == 0) {

@@ -1658,6 +1658,33 @@ def test_render_in_one_kernel_equals_the_wave_loop(wdtype, H, rays, res, occ, or
     assert torch.equal(fused, waves) and (rays < 1000 or st["samples_blended"] > rays)
 
 
+@pytest.mark.parametrize("wdtype,occ", [("f16", None), ("bf16", (8, 8, 8)), ("f16", (7, 6, 5))])
+@pytest.mark.parametrize("seed", [None, 5])
+def test_render_of_points_at_denormal_distances(wdtype, occ, seed):
+    """Rays that run along a face of the box at coordinates, or with components of their directions, below the smallest normal
+    number: a point at -1e-40 is outside a box that starts at 0, one at 1e-40 inside."""
+    import torch
+    sc = scene_dict((2, 2, 2), (0, 0, 0), (1, 1, 1), 32, wdtype, 14, occ=None if occ is None else np.ones(occ, np.uint8))
+    at = 63 * 32 + 32 + 32 * 32 + 32
+    sc["weights"][:, at + 32 * 33] = 8.0               # the density's bias: every point inside is seen
+    dev, orc = make_pair(sc)
+    o, d = [], []
+    for axis in range(3):
+        for x, dx in ((-1e-40, 0.0), (1e-40, 0.0), (0.0, -1e-39), (0.0, 1e-39), (-1e-44, 0.0), (-1e-40, 1e-40), (1e-38, -8e-39), (0.0, 0.0)):
+            a, b = np.full(3, 0.5), np.zeros(3)
+            a[axis], b[axis] = x, dx
+            a[(axis + 1) % 3], b[(axis + 1) % 3] = 2.0, -1.0
+            o.append(a), d.append(b)
+    o, d = np.float32(o), np.float32(d)
+    args = (0.5, 0.02, 100, 0.01, (1.0, 1.0, 1.0))
+    waves, st = dev.render(cuda(o), cuda(d), *args, want_stats=True, seed=seed)
+    ref, n, _, mg = orc.render(o, d, *args, seed=seed)
+    fused = dev.render(cuda(o), cuda(d), *args, seed=seed)
+    assert (n == 0).sum() >= 9 and (n > 0).sum() >= 9
+    np.testing.assert_array_equal((fused.cpu().numpy() != 1.0).any(axis=1), n > 0)
+    assert torch.equal(fused, waves) and np.abs(fused.cpu().numpy() - ref).max() <= 2e-2 + 0.01
+
+
 def test_sparse_and_stratified_edge_cases():
     import torch
     import paper_2103_13744_amd as kn
