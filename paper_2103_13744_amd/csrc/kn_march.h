@@ -152,6 +152,7 @@ struct SkipJump {
         b = (p.skip_margin + 1e-6f * (fabsf(o[0]) + fabsf(o[1]) + fabsf(o[2]))) * inv_step_len + (strat ? 2.0f : 1.0f);
         use = p.skip_dist != nullptr && isfinite(inv_step_len);
     }
+    // (up to the largest integer)
     __device__ __forceinline__ int32_t jump(int32_t dist) const { return (int32_t)fmaxf(floorf((float)(dist - 1) * a - b), 0.0f); }
 };
 
@@ -182,7 +183,8 @@ __device__ __forceinline__ int32_t skip_to_content(const MarchParams &p, const G
         kn_lattice_point<STRAT>(o[0], o[1], o[2], d[0], d[1], d[2], p.t_near, p.step, k, x, y, z, ray_key);
         const int32_t dist = skip_lookup(p, x, y, z);
         if (dist >= 2) {
-            k += 1 + sj.jump(dist);
+            const int32_t further = sj.jump(dist); // (saturated where a step is far shorter than a block: the sum would wrap)
+            k = further >= k_hi - k ? k_hi : k + 1 + further;
         } else if (dist < 0 && grid_index_fast(go, x, y, z) < 0) {
             k += 1; // exactly outside the AABB (the clip range starts a little before the box)
         } else {

@@ -1658,6 +1658,24 @@ def test_render_in_one_kernel_equals_the_wave_loop(wdtype, H, rays, res, occ, or
     assert torch.equal(fused, waves) and (rays < 1000 or st["samples_blended"] > rays)
 
 
+@pytest.mark.parametrize("wdtype", ["f32", "f16"])
+@pytest.mark.parametrize("step", [1e-7, 1e-12, 1e-30, 2e-38])
+def test_render_with_steps_far_shorter_than_a_block_of_voxels(wdtype, step):
+    """A jump over an empty block is more lattice points than an integer holds; rays start in the empty and in the full half."""
+    occ = np.zeros((64, 64, 64), np.uint8)
+    occ[40:, :, :] = 1
+    dev, orc = make_pair(scene_dict((4, 4, 4), (-1, -1, -1), (1, 1, 1), 32, wdtype, 14, occ=occ, sigma_scale=60.0))
+    o = np.float32([[-0.9, 0.1, 0.2], [-0.9, 0.1, 0.2], [0.9, 0.1, 0.2], [-3.0, 0.0, 0.0], [0.24999, 0.1, 0.2]])
+    d = np.float32([[1, 0, 0], [-1, 0, 0], [0, 0, 1], [1, 0, 0], [1, 0, 0]])
+    for seed in (None, 3):
+        args = (0.0, step, 300, 0.01, (0.2, 0.4, 0.6))
+        ref = orc.render(o, d, *args, seed=seed)[0]
+        img, st = dev.render(cuda(o), cuda(d), *args, want_stats=True, seed=seed)
+        for got in (img, dev.render(cuda(o), cuda(d), *args, seed=seed)):
+            assert np.abs(got.cpu().numpy() - ref).max() <= TOL[wdtype]
+        assert st["samples_blended"] >= 300
+
+
 @pytest.mark.parametrize("wdtype,occ", [("f16", None), ("bf16", (8, 8, 8)), ("f16", (7, 6, 5))])
 @pytest.mark.parametrize("seed", [None, 5])
 def test_render_of_points_at_denormal_distances(wdtype, occ, seed):
