@@ -190,7 +190,7 @@ int kn_eval_grouped_static(kn_ctx *ctx, const kn_scene *scene, void *stream, con
  * iff x_k is inside the AABB and its occupancy voxel is non-zero (and, on a sparse grid, its cell
  * has a network).  out_k[r*S + j] = j-th kept
  * index (unused slots -1), out_count[r] = kept, out_k_next[r] (nullable) = where to resume
- * (K when the ray is exhausted). */
+ * (K when the ray is exhausted).  K <= 2^31 - 1025 (KN_E_UNSUPPORTED beyond; kn_render too). */
 int kn_march(const kn_scene *scene, void *stream, const float *rays_o /*dev R*3*/,
              const float *rays_d /*dev R*3*/, int64_t R, float t_near, float step, int32_t K,
              const int32_t *k_begin /*dev R, nullable*/, int32_t S, int32_t *out_k /*dev R*S*/,

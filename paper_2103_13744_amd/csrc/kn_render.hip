@@ -1012,6 +1012,8 @@ MarchParams make_params(const kn_scene *sc, float t_near, float step, int32_t K,
 // covers K slots for every ray that reaches content, the second wave is known to finish the frame and the
 // call returns without waiting for it.
 constexpr int DEFAULT_FIRST_WAVE = 48;
+// A step of a march tests up to 64 lattice points side by side, some of them behind the last one: their indices are 32-bit.
+constexpr int32_t MAX_K = 0x7fffffff - 1024;
 constexpr int64_t BLIND_RAYS = 32768; // see render_impl
 
 bool finite_pos(float v) { return isfinite(v) && v > 0.0f; }
@@ -1107,7 +1109,7 @@ static int wait_count(const KnMailbox *mb, hipStream_t st, unsigned long long se
 static int kbits_for(int32_t K)
 {
     int b = 1;
-    while ((1 << b) < K) ++b;
+    while ((1ll << b) < K) ++b;
     return b;
 }
 
@@ -1180,7 +1182,7 @@ static int march_impl(const kn_scene *sc, void *stream, const float *rays_o, con
     if (R > 0 && (!rays_o || !rays_d || !out_k || !out_count)) return KN_E_INVALID_ARG;
     if (R == 0) return KN_OK;
     const int64_t blocks = kn_div_up(R * MARCH_G, 256);
-    if (blocks > 0x7fffffffLL) return KN_E_UNSUPPORTED;
+    if (blocks > 0x7fffffffLL || K > MAX_K) return KN_E_UNSUPPORTED;
     if (seed && R > 0xffffffffLL) return KN_E_UNSUPPORTED; // ray numbers are 32-bit
     hipLaunchKernelGGL(march_stage_kernel(march_options(sc, seed)), dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream,
                        make_params(sc, t_near, step, K, seed), rays_o, rays_d, R, k_begin, S, out_k, out_count, out_k_next);
@@ -1310,7 +1312,7 @@ static int render_impl(kn_ctx *ctx, const kn_scene *sc, void *stream, const floa
     if (R == 0) return KN_OK;
     const KnKnobs knobs = kn_knobs(ctx); // the schedule this call runs with, whatever is set meanwhile
     const int kbits = kbits_for(K > 1 ? K : 2);
-    if (R > (1ll << (32 - kbits)) || R > 0x7fffffffLL / knobs.slots_per_ray || R > (1ll << 26))
+    if (R > (1ll << (32 - kbits)) || R > 0x7fffffffLL / knobs.slots_per_ray || R > (1ll << 26) || K > MAX_K)
         return KN_E_UNSUPPORTED; // slot numbers, row * lanes and byte offsets into the table of encoded directions are 32-bit
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < kn_render_ws_bytes(sc, R, knobs.slots_per_ray))
         return KN_E_WORKSPACE;

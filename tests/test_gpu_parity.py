@@ -1676,6 +1676,20 @@ def test_render_with_steps_far_shorter_than_a_block_of_voxels(wdtype, step):
         assert st["samples_blended"] >= 300
 
 
+def test_numbers_of_lattice_points_that_integers_cannot_step_over():
+    """Refused before anything is launched, and before a loop over the bits of K that has no end there."""
+    import paper_2103_13744_amd as kn
+    dev, _ = make_pair(scene_dict((2, 2, 2), (0, 0, 0), (1, 1, 1), 32, "f16", 14))
+    o, d = cuda(np.float32([[0.5, 0.5, -1.0]] * 5)), cuda(np.float32([[0, 0, 1]] * 5))
+    for K in (2 ** 31 - 1, 2 ** 31 - 1024):
+        with pytest.raises(kn.KnError, match="unsupported"):
+            dev.render(o[:1], d[:1], 0.0, 1e-9, K)
+        with pytest.raises(kn.KnError, match="unsupported"):
+            dev.march(o[:1], d[:1], 0.0, 1e-9, K, S=4)
+    with pytest.raises(kn.KnError, match="unsupported"):
+        dev.render(o, d, 0.0, 1e-9, 2 ** 30 + 1)          # (two rays at most)
+
+
 @pytest.mark.parametrize("wdtype,occ", [("f16", None), ("bf16", (8, 8, 8)), ("f16", (7, 6, 5))])
 @pytest.mark.parametrize("seed", [None, 5])
 def test_render_of_points_at_denormal_distances(wdtype, occ, seed):
