@@ -686,7 +686,8 @@ def test_composite_stage_with_a_delta_per_sample():
 
 # ------------------------------------------------------------------ a1-a6: render
 def render_check(cfg, sel=None, margin=None):
-    """Render on the device, compare (a subset of) pixels with the oracle."""
+    """Render on the device, compare (a subset of) pixels with the oracle: of the call that reports counts (in waves) and of the
+    plain one (16-bit scenes: mostly in one kernel)."""
     import torch
     sc = cfg["scene"]
     tol = TOL[sc["wdtype"]]
@@ -707,9 +708,12 @@ def render_check(cfg, sel=None, margin=None):
         "(straddling rays: %d, max err there %.3g)" % (cfg["name"], len(o), stats["waves"], stats["samples_evaluated"],
                                                      stats["samples_blended"], n_eval.sum(), err[~straddle].max(),
                                                      straddle.sum(), err[straddle].max() if straddle.any() else 0))
-    assert err[~straddle].max() <= tol
-    if straddle.any():
-        assert err[straddle].max() <= tol + cfg["term_eps"]
+    plain = dev.render(cuda(o), cuda(d), cfg["t_near"], cfg["step"], cfg["K"], cfg["term_eps"], cfg["bg"], seed=seed)
+    plain_err = np.abs(plain.cpu().numpy().astype(np.float64)[sel] - ref).max(axis=1)
+    for e in (err, plain_err):
+        assert e[~straddle].max() <= tol
+        if straddle.any():
+            assert e[straddle].max() <= tol + cfg["term_eps"]
     assert straddle.mean() < {"f32": 0.002, "f16": 0.02, "bf16": 0.06}[sc["wdtype"]]     # observed: 0.001, 0.005, 0.04
     assert stats["rays"] == len(o) and stats["samples_evaluated"] >= stats["samples_blended"]
     if sel is None or len(sel) == len(o):
@@ -1656,6 +1660,50 @@ def test_render_in_one_kernel_equals_the_wave_loop(wdtype, H, rays, res, occ, or
     waves, st = dev.render(o, d, *args, want_stats=True, seed=seed)
     fused = dev.render(o, d, *args, seed=seed)
     assert torch.equal(fused, waves) and (rays < 1000 or st["samples_blended"] > rays)
+
+
+@pytest.mark.parametrize("wdtype,H,res,occ_res,keep,box,eps", [
+    ("f16", 32, (24, 24, 24), (96, 96, 96), 0.6, 1.0, 0.01),      # sparse, a block of voxels lies in one cell
+    ("bf16", 64, (12, 12, 24), (96, 48, 96), 0.5, 1.0, 0.01),
+    ("f16", 64, (16, 16, 16), (32, 32, 32), 0.6, 1.0, 0.01),      # sparse, a block lies in eight cells: looked up per point
+    ("bf16", 32, (7, 6, 5), (50, 45, 61), 0.7, 1.0, 0.01),        # sparse, grids that do not nest
+    ("f16", 32, (6, 5, 7), None, 0.6, 1.0, 0.0),                  # sparse, no occupancy grid, no termination
+    ("f16", 32, (16, 16, 16), (128, 128, 128), None, 9.0, 0.01),  # coordinates beyond what the sine hardware reduces
+    ("f16", 64, (5, 8, 5), None, None, 9.0, 0.01),
+    ("bf16", 32, (7, 6, 5), (50, 45, 61), 0.7, 9.0, 0.01)])       # (and sparse)
+@pytest.mark.parametrize("seed", [None, 7])
+def test_render_in_one_kernel_on_sparse_grids_and_in_large_boxes(wdtype, H, res, occ_res, keep, box, eps, seed):
+    """The plain call of a small frame, which is one kernel (the timers say so): the wave loop's bits, and the oracle's pixels."""
+    import torch
+    import paper_2103_13744_amd as kn
+    occ = None if occ_res is None else ks.blob_occupancy(occ_res, 12, 0.15, 5)
+    sc = scene_dict(res, (-box,) * 3, (box,) * 3, H, wdtype, 13, occ=occ, sigma_scale=60.0 / box)
+    if keep is not None:
+        sc = configs.sparsify(sc, np.random.default_rng(8).random(int(np.prod(res))) < keep, 9)
+    dev, orc = make_pair(sc, threads=True)
+    o, d = ks.camera_rays(72, 72, 40.0, 4.0 * box, 45.0, 30.0)
+    K = 384 if occ is not None else 64
+    args = ((4.0 - math.sqrt(3.0)) * box, 2 * math.sqrt(3.0) * box / K, K, eps, (1.0, 1.0, 1.0))
+    waves, st = dev.render(cuda(o), cuda(d), *args, want_stats=True, seed=seed)
+    kn.profile_enable(1)
+    try:
+        kn.profile_read()
+        plain = dev.render(cuda(o), cuda(d), *args, seed=seed)
+        p = kn.profile_read()
+    finally:
+        kn.profile_enable(0)
+    assert p["ms_march"] == 0.0 and p["mlp_launches"] == 1 and p["mlp_samples"] >= st["samples_blended"] > len(o)
+    assert torch.equal(plain, waves)
+    if box > 1.0 and wdtype == "bf16":
+        return          # (coordinates of 9 rounded to bf16 cost more than the bar alone: compared with the wave loop only)
+    sel = np.arange(0, len(o), 3)
+    ref, _, _, mg = orc.render(o[sel], d[sel], *args, seed=seed, ray_ids=None if seed is None else sel)
+    err, straddle = np.abs(plain.cpu().numpy()[sel] - ref).max(axis=1), mg < MARGIN[wdtype]
+    bar = pixel_bar(wdtype, 60.0 / box * args[1])
+    log("  one kernel", wdtype, H, res, occ_res, keep, box, seed, "max err %.3g, straddling %.3g, bar %.3g" %
+        (err[~straddle].max(), straddle.mean(), bar))
+    assert err[~straddle].max() <= bar and err.max() <= bar + eps
+    assert straddle.mean() < {"f16": 0.02, "bf16": 0.06}[wdtype]
 
 
 @pytest.mark.parametrize("wdtype", ["f32", "f16"])
