@@ -42,11 +42,12 @@ def cpu_model():
     except OSError:
         pass
     return "unknown"
-# Sec. 3.2's network: 2 * (63 H + H H + H (H + 1) + (H + 27) H + 3 H) FLOP per sample.  The 16-bit kernels take the
+# Sec. 3.2's network: 2 * (63 H + H H + H (H + 1) + (H + 27) H + 3 H) FLOP per sample.  The kernels take the
 # activation-free feature layer and layer 4 as one affine map and execute 2 * (63 H + H H + H + (H + 27) H + 3 H); the
 # roofline counts the network as defined (the work the method asks for) and the line states both.
 FLOP_PER_SAMPLE = {32: 12160, 64: 36608}
-FLOP_PER_SAMPLE_EXECUTED_16BIT = {32: 10112, 64: 28416}
+FLOP_PER_SAMPLE_EXECUTED = {32: 10112, 64: 28416}
+NETWORK_BYTES_16BIT = {32: 12432, 64: 33040}  # weights of one network in matrix-core operand order
 # vector-ALU issue slots of the render variant of k_mlp_mfma per 16 samples, counted in the generated code of its main
 # loop (269 / 363 vector instructions per 64 samples, 30 of them transcendental and counted twice)
 VALU_SLOTS_PER_16_SAMPLES = {32: 75, 64: 98}
@@ -223,13 +224,16 @@ def isolated_mlp(kn, torch, wdtype, iters=10, skewed=False, layered=True):
         kn.profile_enable(False)
         mlp_ms_l = prof_l["ms_mlp"] / iters
         del ws_l
-    # Re-ordering stage (everything between the cell ids and the MLP kernel: two radix passes that move the samples,
-    # their count tables and scans, offsets and tile list; and, after the MLP kernel, the copy of the staged results
-    # into the caller's arrays).  Algorithmic bytes per point = what a physical re-ordering of the batch has to move
-    # once: key 4 + position and direction 24 read, one 32-byte record written, results 16 read and 16 written = 92.
-    # What the kernels really move is 164 (first pass 28 in, 36 out; second 36 in, 32 out; results 16 in, 16 out); the
-    # figure a sort of indices alone would be charged with, 16 per key (the definition this line used while the stage
-    # sorted indices), is kept beside it.  The scattered 16-byte store of each result is inside the MLP kernel's time.
+    # Re-ordering stage (everything between the cell ids and the MLP kernel, scan of the count table and the samples' one trip,
+    # and after the MLP kernel the results' way back).  Algorithmic bytes per point = what a physical re-ordering of the batch has to
+    # move once: key 4 + position and direction 24 read, one 32-byte record written, results 16 read and 16 written = 92.
+    # What the kernels of batches of this size really move: k_count_scatter reads a 2-byte key and 24, writes 32 and the
+    # sample's two places (4 + 2); k_results_back reads those and 16, writes 16; the count table, a word per network and
+    # workgroup of 8,192 points, is read and written by the scan and read again.  (k_keys_count is in ms_cell_ids.)  The figure a
+    # sort of indices alone would be charged with, 16 per key (the definition this line used while the stage sorted
+    # indices), is kept beside it.
+    moved = 26.0 + 38.0 + 38.0 + 3 * 4.0 * (scene.N + 1) / 8192
+    mlp_bytes = 48.0 * M + scene.N * NETWORK_BYTES_16BIT[sc["hidden"]]  # record read, result written; every network's weights once
     t_bucket = prof["ms_bucket"] / iters * 1e-3
     return {"workload": ("cfg4: 2^23 points, 90 %% in 5 %% of the cells, 16^3 networks, %s" if skewed else
                          "cfg2: 2^22 points, 16^3 networks, %s") % wdtype, "points": M, "points_per_sec": M / (dt_s / iters),
@@ -244,13 +248,13 @@ def isolated_mlp(kn, torch, wdtype, iters=10, skewed=False, layered=True):
                                            "achieved": tflops, "peak": PEAK_MFMA_16BIT / 1e12, "unit": "TFLOP/s",
                                            "frac": tflops * 1e12 / PEAK_MFMA_16BIT, "traffic": None},
                                           "mfma_bf16_tflops" if wdtype == "bf16" else "mfma_f16_tflops"),
-            "roofline_bucket": with_measured({"kernel": "k_reorder_scatter x2 + k_key_hist + k_digit_scan x2 + k_offsets_tiles "
-                                                        "+ k_split_results (stable re-ordering of the samples by network, results back in caller order)",
+            "roofline_bucket": with_measured({"kernel": "k_table_scan + k_count_scatter + k_results_back (samples ordered by counting, "
+                                                        "results back in caller order)",
                                               "bound": "hbm", "achieved": 92.0 * M / t_bucket / 1e9,
                                               "peak": PEAK_HBM / 1e9, "unit": "GB/s",
                                               "frac": 92.0 * M / t_bucket / PEAK_HBM, "traffic": None,
-                                              "bytes_per_point_algorithmic": 92, "bytes_per_point_moved": 164,
-                                              "moved_gbps": 164.0 * M / t_bucket / 1e9},
+                                              "bytes_per_point_algorithmic": 92, "bytes_per_point_moved": moved,
+                                              "moved_gbps": moved * M / t_bucket / 1e9},
                                              "hbm_copy_gbps"),
             "bucket_gbps_algorithmic": 92.0 * M / t_bucket / 1e9,
             "bucket_gbps_at_16_bytes_per_key": 16.0 * M / t_bucket / 1e9,
@@ -260,7 +264,7 @@ def isolated_mlp(kn, torch, wdtype, iters=10, skewed=False, layered=True):
                                               "bound": "hbm", "ms": bucket_stage_ms, "achieved": 16.0 * M / (bucket_stage_ms * 1e-3) / 1e9,
                                               "peak": PEAK_HBM / 1e9, "unit": "GB/s", "frac": 16.0 * M / (bucket_stage_ms * 1e-3) / PEAK_HBM,
                                               "traffic": None}, "hbm_copy_gbps"),
-            "mlp_hbm_gbps_algorithmic": (32.0 + 16.0 + 16.0 + 16.0 + 3.5) * M / (mlp_ms * 1e-3) / 1e9}
+            "mlp_hbm_gbps_algorithmic": mlp_bytes / (mlp_ms * 1e-3) / 1e9}
 
 
 def occupancy_extraction(kn, torch, scene, sc, occ_res, iters=5):
@@ -426,7 +430,7 @@ def measure_render(kn, torch, np, configs, cfg, wdtype, steps, warmup, poses, tr
              # the same kernel on the samples the method itself evaluates (those in front of the termination point)
              "achieved_on_blended_samples": tf * n["blended"] / max(n["evaluated"], 1)}
         r["flop_per_sample"] = FLOP_PER_SAMPLE[H]
-        r["flop_per_sample_executed"] = FLOP_PER_SAMPLE[H] if f32 else FLOP_PER_SAMPLE_EXECUTED_16BIT[H]
+        r["flop_per_sample_executed"] = FLOP_PER_SAMPLE_EXECUTED[H]
         if not f32 and not one_kernel:
             # second view: its vector-ALU issue slots (counted in the generated code, transcendental instructions
             # twice) against what 1024 SIMDs can issue at 2.4 GHz, one slot per 4 cycles
