@@ -31,8 +31,11 @@ namespace {
 constexpr int FUSED_WAVES = 4;
 enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last rays of a workgroup are shared out
 
-// Slots per wavefront: what the LDS of a compute unit gives each of its 16 (width 32) / 8 (width 64) wavefronts after
-// the encoded directions (64 bytes per ray) and the index list (2 bytes per slot): 10,112 / 20,224 bytes.
+// Slots per wavefront.  With the index list (2 bytes per slot) and 96 bytes per ray a wavefront takes 9,984 (width 32) / 19,968 bytes
+// of LDS.  At width 64 that is what the eight wavefronts of a compute unit have.  At width 32 it was chosen for sixteen wavefronts,
+// but the kernel's registers allow twelve, which could take 512 slots (12,288 bytes): fewer weight loads in large frames, a little
+// more march than needed in small ones.  Measured with 256 / 384 / 512 slots, one frame each from four sides: 800x800 174 / 187 /
+// 183, 248 / 245 / 227, 233 / 222 / 212, 184 / 189 / 181 us; 200x151 64 / 66 / 67 us.
 template <int H> struct Pool {
     static constexpr int SLOTS = H == 32 ? 384 : 768, MAX_LG = H == 32 ? 5 : 6, RAYS = 1 << MAX_LG, NQ = SLOTS / KN_WAVE;
     static constexpr int WAVES_PER_SIMD = H == 32 ? 3 : 2;

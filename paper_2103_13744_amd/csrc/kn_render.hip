@@ -1232,13 +1232,17 @@ extern "C" int kn_composite_deltas(void *stream, const float *sigma, const float
     return composite_impl(stream, sigma, rgb, delta, offsets, R, 1.0f, term_eps, bg, rgb_out, T_out, n_used);
 }
 
-// Where the fused kernel is the faster one, from 120 frames of 2,000 to 2.6 million rays, 2^3 to 48^3 networks, dense,
-// sparse, stratified and open.  It evaluates a wavefront's samples network by network and loads the network's weights for
-// each, so it needs several samples of a ray per network: the lattice points in a cell's edge say how many there are
-// (5 at width 32, 8 on a sparse grid, 16 at width 64, whose weights are three times as many bytes; below, frames took up to 1.5 times the
-// wave loop's time, above 0.6 to 0.9 of it).  Frames too small to fill the wave loop's launches gain in any case (0.4 to
-// 0.8), large ones at width 32 mostly.  Without early termination every sample is evaluated anyway and the wave loop's
-// full tiles win (0.8 to 0.97) unless the frame is tiny.
+// Where the fused kernel is the faster one.  It evaluates a wavefront's samples network by network and loads the network's weights
+// for each, so it needs several samples of a ray per network: the lattice points in a cell's edge say how many there are.
+// Both ways on 120 frames of 2,000 to 3.2 million rays (its time over the wave loop's; profiles/frames_one_kernel_against_waves.csv):
+//   up to 32,768 rays, which do not fill the wave loop's launches: 0.42 to 0.89 in 39 frames, 1.82 in one (1.2 points, 32^3 networks
+//   without an occupancy grid); few networks, whose weights stay in the caches: 0.42 to 0.52;
+//   width 32, from 5 points on: 0.42 to 0.82 (1.02 in one of 29); 2.5 to 5: 0.70 to 0.87, so that the line at 5 gives
+//   some away; below: 0.70 and 1.37;
+//   sparse grids: 8 to 16 points 0.77 to 0.87, 2.5 to 8 0.70 to 0.89 (the same), below 1.01 to 1.53;
+//   width 64, whose weights are three times as many bytes: from 16 points on 0.64 to 0.91, 8 to 16 0.97 (sparse 1.58), below 0.78 to 3.89;
+//   without early termination, where every sample is evaluated anyway and the wave loop's tiles are full: up to 8,192 rays 0.47 to
+//   0.72; beyond 0.57 to 1.92, with no rule found yet that separates them.
 static bool fused_pays(const kn_scene *sc, int64_t R, float step, float term_eps)
 {
     if (term_eps == 0.0f) return R <= 8192;
