@@ -10,12 +10,13 @@
 // per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 66 us; 800x800 230 -> 204; 1080p,
 // width 64, 1430 -> 1078.
 //
-// What bounds it: vector-ALU issue (65 to 80 % of the slots while wavefronts are there: a march step of 256 points takes
-// about 350 instructions, a tile of 16 samples about 75), and the spread of the wavefronts' work: at 800x800 they are
-// busy for 103 us on average, the last one for 200.  Tried against that spread and slower: larger or smaller shares per
-// hand-out (32 rays 230 us, 64 rays 266; few rays each towards the end 213), the rays that are left re-dealt to all
-// wavefronts by a second launch (240), pools per workgroup instead of per wavefront (227), hand-out counters per part of
-// the list (217: neighbours in the list run at the same time, so that weights are found in the caches).
+// What bounds it: the spread of the wavefronts' work and vector-ALU issue.  At 800x800 a wavefront is alive for 61 % of the launch on
+// average and a compute unit busy for 69 % of it; in the cycles in which there are wavefronts the vector ALU is active in
+// 54 %, the matrix cores in 13 % (a march step of 256 points takes about 350 instructions, a tile of 16 samples about 75).  1080p,
+// width 64: 89 and 91 % of the launch, 55 and 33 % (profiles/issue_counters_render_kernels.txt).  Tried against the spread and slower than
+// 204 us at 800x800: larger or smaller shares per hand-out (32 rays 230 us, 64 rays 266; few rays each towards the end 213), the
+// rays that are left re-dealt to all wavefronts by a second launch (240), pools per workgroup instead of per wavefront (227), hand-out
+// counters per part of the list (217: neighbours in the list run at the same time, so that weights are found in the caches).
 //
 // The wavefronts of a SIMD are in different phases at different times, so the latency of the march runs under the
 // evaluation of the others.  Results are the bits of the wave loop (kn_render.hip): same lattice points, same operand

@@ -553,7 +553,8 @@ __global__ void __launch_bounds__(PLACE_THREADS)
 // A workgroup has about two samples per network with 4,096 networks, 32 bytes of each half side by side: the runs of one
 // network follow each other by workgroup, so an XCD takes one contiguous part of the batch, and its workgroups, which go
 // through the networks at the same pace, fill the lines in its L2 together.
-// Bound by memory traffic: 4 M points, 16^3 networks: count 22 us, scan 8, scatter 70 (232 MB, 3.3 TB/s), against 158 for the
+// Bound by memory traffic: 4 M points, 16^3 networks: count 20 us, scan 10, scatter 70 (118 MB read, 202 written where 159 are
+// needed: 4.6 TB/s, what a copy reaches), against 158 for the
 // two radix passes and 10 for the search for the tiles.  Whole calls, width 32, fp16: 4 M points 322 -> 245 us, 10x16x10
 // networks 313 -> 215; 8 M 584 -> 470; 1 M 106 -> 76; 262,143 73 -> 57.
 constexpr int CO_ROWS = 8;
@@ -799,7 +800,7 @@ __global__ void __launch_bounds__(T)
 // a workgroup's sorted order is its point `from` and lies at `at`.  Through LDS, so that a workgroup reads runs of a few
 // results, which its neighbours on the XCD read the rest of the lines of, and writes its points one after the other.
 // Instead of one random 16-byte store per sample by the MLP kernel (one transaction each, 57 G/s): 4 M points, 16^3 networks,
-// MLP kernel 120 -> 82 us, this kernel 41 (152 MB, 3.7 TB/s) against 25 for k_split_results.
+// MLP kernel 120 -> 83 us, this kernel 40 (169 MB, 4.2 TB/s) against 25 for k_split_results.
 template <int T>
 __global__ void __launch_bounds__(T)
     k_results_back(const float *__restrict__ out4, const uint32_t *__restrict__ at, const uint16_t *__restrict__ from, int64_t M, int32_t nblk,
