@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
 //
 // Bound: vector-ALU issue at width 32 (19 instructions per tile, 16 of them the packing of two layers, beside 5 products: 133
 // cycles a tile at 256^3 voxels, the vector ALU active in 81 % of them, the matrix cores in 62 %), the matrix cores at width 64
-// (14 products, 224 cycles of 265).  Against
+// (14 products, busy in 78 % of the 291 cycles a tile).  Against
 // encoding every probe and two products more per 16 outputs: 256^3 voxels on 16^3 networks, width 32, fp16 4.18 -> 1.81 ms,
 // width 64, bf16 6.91 -> 3.87; 200x150x100, grids that do not nest (two passes per tile before), 1.96 -> 0.64;
 // 64^3 on 8^3 0.083 -> 0.052.  Five wavefronts per SIMD at width 32 are no faster; width 64 with two 3.96.
