@@ -1,6 +1,7 @@
 // Host side of the C ABI: scene objects, validation, workspace sizing, kn_eval_grouped.
 #include "kn_common.h"
 #include "kn_direct.h"
+#include "kn_fused.h"
 #include "kn_probe.h"
 
 #include <math.h>
@@ -52,6 +53,7 @@ static int static_scratch_address(int dev, void **out)
     if (!g_device_configured[dev]) {
         KN_TRY(kn_group_configure());
         KN_TRY(kn_reorder_configure());
+        KN_TRY(kn_fused_configure());
         g_device_configured[dev] = true;
     }
     *out = g_scratch_ptr[dev];

@@ -3,17 +3,20 @@
 
 #include "kn_common.h"
 
+constexpr int KN_FUSED_CTL = 8; // control words of a frame: live rays, rays handed out beyond the first pools, -, -, two 64-bit counters
+
 struct KnFusedJob {
     const void *march; // MarchParams of the call (kn_march.h)
     const float *rays_o, *rays_d;
     int64_t R;
     const int4 *list;  // live rays (ray, first lattice index, end of the clipped range, -), ctl[0] of them
-    int32_t *ctl;      // ctl[1] must be zero
+    int32_t *ctl;      // KN_FUSED_CTL words, zero behind the first
     float eps;
     const float *bg;
     float *rgb_out;
     unsigned long long *counters; // nullable
     bool strat;
 };
+int kn_fused_configure(); // once per device
 bool kn_fused_supports(const kn_scene *sc);
 int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, hipEvent_t ev_start, hipEvent_t ev_stop);

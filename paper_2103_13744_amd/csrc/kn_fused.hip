@@ -10,13 +10,14 @@
 // per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 66 us; 800x800 230 -> 204; 1080p,
 // width 64, 1430 -> 1078.
 //
-// What bounds it: the spread of the wavefronts' work and vector-ALU issue.  At 800x800 a wavefront is alive for 61 % of the launch on
-// average and a compute unit busy for 69 % of it; in the cycles in which there are wavefronts the vector ALU is active in
-// 54 %, the matrix cores in 13 % (a march step of 256 points takes about 350 instructions, a tile of 16 samples about 75).  1080p,
-// width 64: 89 and 91 % of the launch, 55 and 33 % (profiles/issue_counters_render_kernels.txt).  Tried against the spread and slower than
-// 204 us at 800x800: larger or smaller shares per hand-out (32 rays 230 us, 64 rays 266; few rays each towards the end 213), the
-// rays that are left re-dealt to all wavefronts by a second launch (240), pools per workgroup instead of per wavefront (227), hand-out
-// counters per part of the list (217: neighbours in the list run at the same time, so that weights are found in the caches).
+// What bounds it: vector-ALU issue while there is work (a march step of 256 points takes about 300 instructions, a tile of 16
+// samples about 65, a round about 350 besides), and the end of a frame, when the rays that are left are few.  The rays' costs differ
+// (most end within two rounds, some take ten) and neighbours cost alike, so a workgroup is all of a compute unit's wavefronts, whose
+// first pools lie in as many parts of the list, and who share their last rays through the LDS: workgroups of four
+// wavefronts, all places in a list filled by an atomic per wavefront and round, 203 us at 800x800 (call, with the set-up's 31), 181
+// at 767x577 stratified, 1,093 at 1080p, width 64; like this 164, 148 and 1,038.  Tried and slower: contiguous pieces of the list
+// larger than what a wavefront has places for (800x800 +3, 1080p +60: the last pieces decide), hand-out counters per XCD (+3, +20),
+// half of the list handed out beforehand (+6, +190), 12 wavefronts per compute unit (+3).
 //
 // The wavefronts of a SIMD are in different phases at different times, so the latency of the march runs under the
 // evaluation of the others.  Results are the bits of the wave loop (kn_render.hip): same lattice points, same operand
@@ -27,20 +28,37 @@
 #include "kn_mlp_core.h"
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 namespace {
 
-constexpr int FUSED_WAVES = 4;
 enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last rays of a workgroup are shared out
 
-// Slots per wavefront.  With the index list (2 bytes per slot) and 96 bytes per ray a wavefront takes 9,984 (width 32) / 19,968 bytes
-// of LDS.  At width 64 that is what the eight wavefronts of a compute unit have.  At width 32 it was chosen for sixteen wavefronts,
-// but the kernel's registers allow twelve, which could take 512 slots (12,288 bytes): fewer weight loads in large frames, a little
-// more march than needed in small ones.  Measured with 256 / 384 / 512 slots, one frame each from four sides: 800x800 174 / 187 /
-// 183, 248 / 245 / 227, 233 / 222 / 212, 184 / 189 / 181 us; 200x151 64 / 66 / 67 us.
+// Rays and slots per wavefront.  Large pools keep few lanes per ray and cut a ray into many rounds, small ones evaluate more samples
+// behind the termination point; many slots mean many samples per visit of a network, few fit a step of the march (256 points).
+// Rays x slots, 800x800 and 767x577 / 1080p at width 64, us: 32 x 384 183, 167 / 64 x 768 1,211; 16 x 384 173, 163 / 32 x 768 1,100;
+// 16 x 256 169, 156 / 32 x 896 1,100; 32 x 256 182, 164 / 32 x 512 1,225; 16 x 768 at width 64 1,191.
 template <int H> struct Pool {
-    static constexpr int SLOTS = H == 32 ? 384 : 768, MAX_LG = H == 32 ? 5 : 6, RAYS = 1 << MAX_LG, NQ = SLOTS / KN_WAVE;
-    static constexpr int WAVES_PER_SIMD = H == 32 ? 3 : 2;
+    static constexpr int SLOTS = H == 32 ? 256 : 768, MAX_LG = H == 32 ? 4 : 5, RAYS = 1 << MAX_LG, NQ = SLOTS / KN_WAVE;
+    static constexpr int WAVES_PER_SIMD = H == 32 ? 4 : 2, MAX_WAVES = 4 * WAVES_PER_SIMD;
     static constexpr int MIN_LG = 2, MAX_S = 32;
+    // A round's march ends when fewer than half of the pool's rays have this little of their slots filled: at width 32 a second step
+    // for the rest of a ray's slots is mostly thrown away; at width 64, where a visit of a network costs more, it pays.
+    static constexpr int NEED_QUARTERS = H == 32 ? 2 : 4;
+};
+
+// Rays beyond the first pools are handed to a workgroup in chunks, its wavefronts take from those what they have places for: an
+// eighth of a workgroup's even share of what is left, so that the chunks become small towards the end.  (An atomic per wavefront
+// and round, all on one word, kept the wavefronts waiting: 11 ns each, 45 us for the 4,096 that ask after their first round.)
+constexpr int CHUNK_SHARE = 8, CHUNK_MIN = 16, CHUNK_MAX = 512;
+constexpr int FEW_RAYS = 1; // rays per wavefront below which a workgroup starts with fewer wavefronts
+
+// a wavefront's part of the LDS
+template <int H> struct WaveLds {
+    f4 slot[Pool<H>::SLOTS];      // sample j of pool ray s at j * P + s: (x, y, z, density scale), then (r, g, b, alpha)
+    u4 dir[Pool<H>::RAYS * 4];    // gamma(d) of pool ray s in operand order
+    f4 ray[Pool<H>::RAYS * 2];    // (origin, jump scale), (direction, jump offset) of pool ray s
+    uint16_t idx[Pool<H>::SLOTS]; // the samples' networks, then the slots of the network at hand
 };
 
 // lattice points a lane tests per step of the march: enough look-ups in flight, and the work per step that does not
@@ -145,50 +163,47 @@ __device__ __forceinline__ void wave_sync()
 }
 
 template <int H, bool BF, bool WRAP, bool STRAT>
-__global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
+__global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
     __attribute__((amdgpu_waves_per_eu(Pool<H>::WAVES_PER_SIMD, Pool<H>::WAVES_PER_SIMD))) k_render_fused(FusedArgs args_by_value)
 {
     using L = Lay<H>;
     using Pl = Pool<H>;
     constexpr int HT = L::HT, HK = L::HK, NBLK = L::NBLK, NQ = Pl::NQ;
-    __shared__ f4 s_slot[FUSED_WAVES][Pl::SLOTS];      // sample j of pool ray s at j * P + s: (x, y, z, density scale), then (r, g, b, alpha)
-    __shared__ u4 s_dir[FUSED_WAVES][Pl::RAYS * 4];    // gamma(d) of pool ray s in operand order
-    __shared__ f4 s_ray[FUSED_WAVES][Pl::RAYS * 2];    // (origin, jump scale), (direction, jump offset) of pool ray s
-    __shared__ uint16_t s_idx[FUSED_WAVES][Pl::SLOTS]; // the samples' networks, then the slots of the network at hand
-    // sharing of the last rays inside the workgroup (see share_rays): what each wavefront is doing, the number of rays it
+    extern __shared__ f4 s_dynamic[];
+    WaveLds<H> *const s_wave = (WaveLds<H> *)s_dynamic; // one per wavefront of the workgroup
+    // sharing of the last rays inside the workgroup: what each wavefront is doing, the number of rays it
     // was given, and how many wavefronts are out of work
-    __shared__ int32_t s_state[FUSED_WAVES], s_given[FUSED_WAVES], s_idle;
+    __shared__ int32_t s_state[Pl::MAX_WAVES], s_given[Pl::MAX_WAVES], s_idle;
+    __shared__ int32_t s_lock, s_at, s_end; // what is left of the workgroup's chunk of the list
 
     const ArgsPtr args = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); // = &args_by_value
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
-    f4 *slots = s_slot[wave];
-    u4 *dirs = s_dir[wave];
-    f4 *rays = s_ray[wave];
-    uint16_t *idx = s_idx[wave];
+    const int n_waves = blockDim.x / KN_WAVE;
+    f4 *slots = s_wave[wave].slot;
+    u4 *dirs = s_wave[wave].dir;
+    f4 *rays = s_wave[wave].ray;
+    uint16_t *idx = s_wave[wave].idx;
 
     const int n_live = args->ctl[0];
-    const int total_waves = gridDim.x * FUSED_WAVES;
+    // as many wavefronts as get FEW_RAYS rays each; the others take what is shared out
+    const int users = min(n_waves, max(1, (n_live + (int)gridDim.x * FEW_RAYS - 1) / ((int)gridDim.x * FEW_RAYS)));
+    const int total_waves = gridDim.x * users;
     // rays per pool: as many as give every wavefront one, up to the pool's size
     int lgP = Pl::MIN_LG;
     while (lgP < Pl::MAX_LG && ((int64_t)total_waves << lgP) < n_live) ++lgP;
 
-    // First pools: equal contiguous shares of the list's head; what lies beyond is handed out as places become free.
-    // Neighbouring rays cost alike, so the four wavefronts of a SIMD (wavefront v of the workgroups b, b + 256, ...) take
-    // shares from the four quarters of the list, and the four shares that lie side by side go to one compute unit.
-    const int b = blockIdx.x, quarter_blocks = gridDim.x >> 2;
-    int wid;
-    if ((gridDim.x & 3) == 0) {
-        const int j = b / quarter_blocks;
-        wid = ((wave + j) & 3) * gridDim.x + (b - j * quarter_blocks) * 4 + j;
-    } else {
-        wid = b * FUSED_WAVES + wave;
-    }
+    // First pools: equal contiguous shares of the list's head.  A workgroup takes four that lie side by side (rays that meet the
+    // same networks) from each of up to four parts of the list (rays that cost differently); inside a part, shares that lie side by
+    // side go to the workgroups of one XCD (b mod 8), which find each other's networks in its L2.  A workgroup's shares
+    // scattered one by one: the same for large frames, 164x94 rays with a network per sample 79 -> 96 us instead of 72.
+    const int part = wave >> 2, width = min(4, users - 4 * part);
+    const int wid = 4 * part * (int)gridDim.x + (((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3)) * width + (wave & 3);
     const int n_first = (int)min((int64_t)n_live, (int64_t)total_waves << lgP);
-    int at = __builtin_amdgcn_readfirstlane((int)((int64_t)wid * n_first / total_waves));
-    int end = __builtin_amdgcn_readfirstlane((int)((int64_t)(wid + 1) * n_first / total_waves));
+    int at = __builtin_amdgcn_readfirstlane(wave < users ? (int)((int64_t)wid * n_first / total_waves) : 0);
+    int end = __builtin_amdgcn_readfirstlane(wave < users ? (int)((int64_t)(wid + 1) * n_first / total_waves) : 0);
     bool more = n_live > n_first;
-    if (threadIdx.x < FUSED_WAVES) s_state[threadIdx.x] = BUSY;
-    if (threadIdx.x == 0) s_idle = 0;
+    if (threadIdx.x < n_waves) s_state[threadIdx.x] = BUSY;
+    if (threadIdx.x == 0) s_idle = s_lock = s_at = s_end = 0;
     __syncthreads();
 
     int ray = -1, k = 0, k_hi = 0; // (the same in all lanes of a ray's group, like everything per ray below)
@@ -200,8 +215,8 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
         if (at >= end && !more) {
             // ---- The list is exhausted.  The rays that are left differ in cost (most end within two rounds, some take ten),
             // and a wavefront with many long ones would run on alone: one that has run out of rays waits for a part of
-            // another wavefront's of its workgroup.  (LDS only; a waiting wavefront ends when all four are out of work.)
-            unsigned long long live = __ballot(ray >= 0) & (lgP == 6 ? ~0ull : (1ull << (1 << lgP)) - 1ull);
+            // another wavefront's of its workgroup.  (LDS only; a waiting wavefront ends when all are out of work.)
+            unsigned long long live = __ballot(ray >= 0) & ((1ull << (1 << lgP)) - 1ull);
             int n = __popcll(live);
             const int ln = opaque(lane);
             if (n == 0) {
@@ -213,7 +228,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
                 for (;;) {
                     st = __hip_atomic_load(&s_state[wave], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
                     if (__builtin_amdgcn_readfirstlane(st) == GIVEN) break;
-                    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_idle, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == FUSED_WAVES) break;
+                    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_idle, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == n_waves) break;
                     __builtin_amdgcn_s_sleep(4);
                 }
                 if (__builtin_amdgcn_readfirstlane(st) != GIVEN) break; // everybody is out of work
@@ -236,9 +251,9 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
             } else if (n >= 2 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > 0) {
                 int to = -1;
                 if (ln == 0)
-                    for (int w = 1; w < FUSED_WAVES && to < 0; ++w) {
+                    for (int w = 1; w < n_waves && to < 0; ++w) {
                         int expect = IDLE;
-                        const int other = (wave + w) & (FUSED_WAVES - 1);
+                        const int other = wave + w < n_waves ? wave + w : wave + w - n_waves;
                         if (__hip_atomic_compare_exchange_strong(&s_state[other], &expect, CLAIMED, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
                                                                  __HIP_MEMORY_SCOPE_WORKGROUP)) {
                             to = other;
@@ -251,8 +266,8 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
                     const int rank = __popcll(live & ((1ull << place) - 1ull)) - keep;
                     const bool gives = ray >= 0 && rank >= 0;
                     if (gives && ln < P) {
-                        s_slot[to][2 * rank] = (f4){__int_as_float(ray), __int_as_float(k), __int_as_float(k_hi), T};
-                        s_slot[to][2 * rank + 1] = (f4){c0, c1, c2, 0.0f};
+                        s_wave[to].slot[2 * rank] = (f4){__int_as_float(ray), __int_as_float(k), __int_as_float(k_hi), T};
+                        s_wave[to].slot[2 * rank + 1] = (f4){c0, c1, c2, 0.0f};
                     }
                     if (gives) ray = -1;
                     if (ln == 0) {
@@ -261,7 +276,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
                         __hip_atomic_store(&s_state[to], GIVEN, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                     n = keep;
-                    live = __ballot(ray >= 0) & (lgP == 6 ? ~0ull : (1ull << P) - 1ull);
+                    live = __ballot(ray >= 0) & ((1ull << P) - 1ull);
                 }
             }
             // ---- the rays that are left move together, so that each gets more lanes and more slots
@@ -287,7 +302,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
         }
         const int P = 1 << lgP, G = KN_WAVE >> lgP;
         const int S_max = min(Pl::SLOTS >> lgP, Pl::MAX_S);
-        const unsigned long long firsts = lgP == 6 ? ~0ull : (1ull << P) - 1ull; // lanes that lead a ray's group
+        const unsigned long long firsts = (1ull << P) - 1ull; // lanes that lead a ray's group
         int cnt = 0;
         {
             const ArgsPtr a = opaque(args);
@@ -298,11 +313,28 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
             bool fresh = moved;
             if (n_free > 0) {
                 if (at >= end && more) {
-                    int base = 0;
-                    if (ln == 0) base = atomicAdd(&a->ctl[1], n_free);
-                    at = n_first + __builtin_amdgcn_readfirstlane(base);
-                    end = min(at + n_free, n_live);
-                    more = at + n_free < n_live;
+                    int got = 0, last = 0;
+                    if (ln == 0) { // (the lock's holder is a resident wavefront and waits for nothing but memory)
+                        int expect = 0;
+                        while (!__hip_atomic_compare_exchange_strong(&s_lock, &expect, 1, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
+                            expect = 0;
+                            __builtin_amdgcn_s_sleep(1);
+                        }
+                        got = __hip_atomic_load(&s_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        last = __hip_atomic_load(&s_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        const int chunk = min(max((n_live - max(last, n_first)) / ((int)gridDim.x * CHUNK_SHARE), CHUNK_MIN), CHUNK_MAX);
+                        if (got >= last && last < n_live) {
+                            got = min(n_first + atomicAdd(&a->ctl[1], chunk), n_live);
+                            last = min(got + chunk, n_live);
+                            __hip_atomic_store(&s_end, last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        }
+                        __hip_atomic_store(&s_at, min(got + n_free, last), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_store(&s_lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    at = __builtin_amdgcn_readfirstlane(got);
+                    last = __builtin_amdgcn_readfirstlane(last);
+                    end = min(at + n_free, last);
+                    more = end < n_live;
                 }
                 const int avail = end - at;
                 if (avail > 0) {
@@ -355,7 +387,7 @@ __global__ void __launch_bounds__(FUSED_WAVES *KN_WAVE)
                 const int S = S_max;
                 const uint32_t ray_key = kn_mix32(a->p.seed_key + (uint32_t)ray);
                 // The march of a round ends when fewer than half of the pool's rays still collect: the others would only wait.
-                while (2 * __popcll(__ballot(k < k_hi && cnt < S)) >= n_lanes) {
+                while (2 * __popcll(__ballot(k < k_hi && 4 * cnt < Pl::NEED_QUARTERS * S)) >= n_lanes) {
                   if (k < k_hi && cnt < S) {
                     const int k0 = k + gl * STEPS;
                     float x[STEPS], y[STEPS], z[STEPS];
@@ -643,6 +675,27 @@ bool kn_fused_supports(const kn_scene *sc)
     return fits(sc->net_grid.res) && (!sc->has_occ || fits(sc->skip_res));
 }
 
+using FusedFn = decltype(&k_render_fused<32, false, false, false>);
+static const FusedFn fused_table[2][2][2][2] = {
+    {{{k_render_fused<32, false, false, false>, k_render_fused<32, false, false, true>},
+      {k_render_fused<32, false, true, false>, k_render_fused<32, false, true, true>}},
+     {{k_render_fused<32, true, false, false>, k_render_fused<32, true, false, true>},
+      {k_render_fused<32, true, true, false>, k_render_fused<32, true, true, true>}}},
+    {{{k_render_fused<64, false, false, false>, k_render_fused<64, false, false, true>},
+      {k_render_fused<64, false, true, false>, k_render_fused<64, false, true, true>}},
+     {{k_render_fused<64, true, false, false>, k_render_fused<64, true, false, true>},
+      {k_render_fused<64, true, true, false>, k_render_fused<64, true, true, true>}}}};
+
+// a workgroup's LDS is above the default limit of dynamic LDS (once per device, from kn_create)
+int kn_fused_configure()
+{
+    for (int i = 0; i < 16; ++i) {
+        const int bytes = (i & 8) ? Pool<64>::MAX_WAVES * (int)sizeof(WaveLds<64>) : Pool<32>::MAX_WAVES * (int)sizeof(WaveLds<32>);
+        KN_HIP(hipFuncSetAttribute((const void *)fused_table[i >> 3][(i >> 2) & 1][(i >> 1) & 1][i & 1], hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    }
+    return KN_OK;
+}
+
 int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     const int H = sc->desc.hidden;
@@ -663,26 +716,18 @@ int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, h
     float reach = 0.0f; // (see the launch of k_mlp_mfma)
     for (int c = 0; c < 3; ++c) reach = fmaxf(reach, fmaxf(fabsf(sc->desc.aabb_min[c]), fabsf(sc->desc.aabb_max[c])));
     const bool wrap = !(reach * (256.0f * INV_2PI) < 250.0f);
-    // one workgroup per compute unit and resident wavefront of a SIMD; fewer where there are fewer than four rays for each
-    // of their wavefronts
-    int64_t blocks = kn_div_up(job.R, FUSED_WAVES << Pool<32>::MIN_LG);
-    const int64_t fill = 256 * (H == 32 ? Pool<32>::WAVES_PER_SIMD : Pool<64>::WAVES_PER_SIMD);
-    if (blocks > fill) blocks = fill;
-    using Fn = decltype(&k_render_fused<32, false, false, false>);
-    static const Fn table[2][2][2][2] = {
-        {{{k_render_fused<32, false, false, false>, k_render_fused<32, false, false, true>},
-          {k_render_fused<32, false, true, false>, k_render_fused<32, false, true, true>}},
-         {{k_render_fused<32, true, false, false>, k_render_fused<32, true, false, true>},
-          {k_render_fused<32, true, true, false>, k_render_fused<32, true, true, true>}}},
-        {{{k_render_fused<64, false, false, false>, k_render_fused<64, false, false, true>},
-          {k_render_fused<64, false, true, false>, k_render_fused<64, false, true, true>}},
-         {{k_render_fused<64, true, false, false>, k_render_fused<64, true, false, true>},
-          {k_render_fused<64, true, true, false>, k_render_fused<64, true, true, true>}}}};
+    // one workgroup per compute unit, of as many wavefronts as get four rays each, up to what a compute unit holds; a multiple of
+    // eight workgroups, for the shares of the XCDs
+    const int max_waves = H == 32 ? Pool<32>::MAX_WAVES : Pool<64>::MAX_WAVES;
+    const int64_t want = kn_div_up(job.R, 1 << Pool<32>::MIN_LG);
+    const int waves = (int)std::min<int64_t>(std::max<int64_t>(kn_div_up(want, 256), 4), max_waves);
+    const int64_t blocks = std::min<int64_t>(8 * kn_div_up(want, 8 * waves), 256);
+    const size_t lds = waves * (H == 32 ? sizeof(WaveLds<32>) : sizeof(WaveLds<64>));
     if (H != 32 && H != 64) return KN_E_UNSUPPORTED;
-    const Fn kernel = table[H == 64][bf][wrap][job.strat ? 1 : 0];
-    const dim3 grid((unsigned)blocks), block(FUSED_WAVES * KN_WAVE);
-    if (ev_start && ev_stop) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev_start, ev_stop, 0, a);
-    else hipLaunchKernelGGL(kernel, grid, block, 0, st, a);
+    const FusedFn kernel = fused_table[H == 64][bf][wrap][job.strat ? 1 : 0];
+    const dim3 grid((unsigned)blocks), block(waves * KN_WAVE);
+    if (ev_start && ev_stop) hipExtLaunchKernelGGL(kernel, grid, block, lds, st, ev_start, ev_stop, 0, a);
+    else hipLaunchKernelGGL(kernel, grid, block, lds, st, a);
     KN_CHECK_LAUNCH();
     return KN_OK;
 }

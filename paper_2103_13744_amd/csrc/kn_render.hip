@@ -371,7 +371,6 @@ __global__ void __launch_bounds__(RAY_BLOCK)
 // ctl[0] = number of live rays, everything behind it is cleared for the fused kernel.
 constexpr int LIST_BLOCK = 1024, LIST_RAYS = 8, LIST_WAVES = LIST_BLOCK / KN_WAVE; // threads, rays per thread
 constexpr int SORT_RUN = 4;
-constexpr int FUSED_CTL = 8; // ctl words: live rays, hand-out counter, -, -, two 64-bit counters
 template <bool SORT>
 __global__ void __launch_bounds__(LIST_BLOCK)
     k_fused_list(const int4 *__restrict__ recs, int64_t R, const int32_t *__restrict__ blk_sum, const int32_t *__restrict__ counts,
@@ -416,7 +415,7 @@ __global__ void __launch_bounds__(LIST_BLOCK)
         all += s_sum[1][w];
         runs += s_sum[2][w];
     }
-    if (blockIdx.x == 0 && threadIdx.x < FUSED_CTL) ctl[threadIdx.x] = threadIdx.x == 0 ? all : 0;
+    if (blockIdx.x == 0 && threadIdx.x < KN_FUSED_CTL) ctl[threadIdx.x] = threadIdx.x == 0 ? all : 0;
     if constexpr (SORT) {
         if (all < (int64_t)SORT_RUN * runs) { // (uniform: the same in every workgroup)
             constexpr int PER = FUSED_BUCKETS / LIST_BLOCK;
@@ -1159,7 +1158,7 @@ static void carve_fused(KnCarver &ws, int64_t R, FusedWs &w)
     w.list = ws.carve<int4>(R);
     w.blk_sum = ws.carve<int32_t>(kn_div_up(R, RAY_BLOCK));
     w.counts = ws.carve<int32_t>(R < SORT_RAYS ? 0 : FUSED_BUCKETS);
-    w.ctl = ws.carve<int32_t>(FUSED_CTL);
+    w.ctl = ws.carve<int32_t>(KN_FUSED_CTL);
 }
 
 int64_t kn_render_ws_bytes(const kn_scene *sc, int64_t R, int32_t slots_per_ray)

@@ -1665,6 +1665,29 @@ def test_render_in_one_kernel_equals_the_wave_loop(wdtype, H, rays, res, occ, or
     assert torch.equal(fused, waves) and (rays < 1000 or st["samples_blended"] > rays)
 
 
+@pytest.mark.parametrize("wdtype,H,rays", [
+    ("f16", 32, 33), ("bf16", 32, 4097), ("f16", 64, 5121), ("f16", 32, 7200), ("bf16", 32, 13313),  # workgroups of 4, 5, 8, 14 wavefronts
+    ("f16", 32, 65536), ("bf16", 32, 65537), ("f16", 32, 65536 + 16), ("f16", 32, 180003),          # first pools just full; chunks of the list
+    ("bf16", 64, 65535), ("f16", 64, 65600), ("bf16", 64, 230001)])
+def test_render_in_one_kernel_hands_every_ray_out(wdtype, H, rays):
+    """Frames in which every ray meets content: the wave loop's bits around the numbers of rays that the first pools hold (16 rays
+    for each of 4,096 wavefronts at width 32, 32 for 2,048 at width 64)."""
+    import torch
+    log("fused render, all rays live", wdtype, H, rays)
+    cfg = configs.config3(96, 96)
+    dev, _ = make_pair(scene_dict((8, 8, 8), cfg["scene"]["aabb_min"], cfg["scene"]["aabb_max"], H, wdtype, 13,
+                                  occ=cfg["scene"]["occupancy"], sigma_scale=60.0))
+    args = (cfg["t_near"], cfg["step"], cfg["K"], cfg["term_eps"], (7.0, 7.0, 7.0))
+    o, d = cuda(cfg["rays_o"]), cuda(cfg["rays_d"])
+    live = (dev.render(o, d, *args, want_stats=True)[0] != 7.0).any(dim=1).nonzero().squeeze(1)
+    pick = live[torch.arange(rays, device="cuda") % len(live)]
+    o, d = o[pick].contiguous(), d[pick].contiguous()
+    waves, st = dev.render(o, d, *args, want_stats=True)
+    for _ in range(2):
+        assert torch.equal(dev.render(o, d, *args), waves)
+    assert st["samples_blended"] >= rays
+
+
 @pytest.mark.parametrize("wdtype,H,res,occ_res,keep,box,eps", [
     ("f16", 32, (24, 24, 24), (96, 96, 96), 0.6, 1.0, 0.01),      # sparse, a block of voxels lies in one cell
     ("bf16", 64, (12, 12, 24), (96, 48, 96), 0.5, 1.0, 0.01),
