@@ -5,11 +5,13 @@
 
 constexpr int KN_FUSED_CTL = 8; // control words of a frame: live rays, rays handed out beyond the first pools, -, -, two 64-bit counters
 
+constexpr int64_t KN_FUSED_OWN_RAYS = 32767; // frames of up to so many rays need no list
+
 struct KnFusedJob {
     const void *march; // MarchParams of the call (kn_march.h)
     const float *rays_o, *rays_d;
     int64_t R;
-    const int4 *list;  // live rays (ray, first lattice index, end of the clipped range, -), ctl[0] of them
+    const int4 *list;  // live rays (ray, first lattice index, end of the clipped range, -), ctl[0] of them; nullptr: the kernel sets the rays up itself
     int32_t *ctl;      // KN_FUSED_CTL words, zero behind the first
     float eps;
     const float *bg;

@@ -7,8 +7,9 @@
 // for the next round; free places are filled with the next rays of the live list.  Samples, results and encoded
 // directions never leave the LDS, a frame needs no slot buffers, no histogram and no host decision in the middle, and a
 // ray stops within S samples of its termination point.  Against the wave loop (march, group, evaluate and blend kernels
-// per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 66 us; 800x800 230 -> 204; 1080p,
-// width 64, 1430 -> 1078.
+// per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 57 us; 800x800 230 -> 164; 1080p,
+// width 64, 1430 -> 1025.  Frames of up to 32,767 rays are this kernel alone: a workgroup also clips its rays and walks them to their
+// first lattice point near content (200x151: 67 us with two launches in front of it).
 //
 // What bounds it: vector-ALU issue while there is work (a march step of 256 points takes about 300 instructions, a tile of 16
 // samples about 65, a round about 350 besides), and the end of a frame, when the rays that are left are few.  The rays' costs differ
@@ -37,21 +38,29 @@ enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last
 // Rays and slots per wavefront.  Large pools keep few lanes per ray and cut a ray into many rounds, small ones evaluate more samples
 // behind the termination point; many slots mean many samples per visit of a network, few fit a step of the march (256 points).
 // Rays x slots, 800x800 and 767x577 / 1080p at width 64, us: 32 x 384 183, 167 / 64 x 768 1,211; 16 x 384 173, 163 / 32 x 768 1,100;
-// 16 x 256 169, 156 / 32 x 896 1,100; 32 x 256 182, 164 / 32 x 512 1,225; 16 x 768 at width 64 1,191.
+// 16 x 256 169, 156 / 32 x 896 1,100; 32 x 256 182, 164 / 32 x 512 1,225; 16 x 768 at width 64 1,191.  (kn_fused_launch chooses between
+// full pools of 1 << MAX_LG rays and of half as many.)
 template <int H> struct Pool {
-    static constexpr int SLOTS = H == 32 ? 256 : 768, MAX_LG = H == 32 ? 4 : 5, RAYS = 1 << MAX_LG, NQ = SLOTS / KN_WAVE;
+    static constexpr int SLOTS = H == 32 ? 256 : 768, MAX_LG = H == 32 ? 5 : 6, RAYS = 1 << MAX_LG, NQ = SLOTS / KN_WAVE;
     static constexpr int WAVES_PER_SIMD = H == 32 ? 4 : 2, MAX_WAVES = 4 * WAVES_PER_SIMD;
     static constexpr int MIN_LG = 2, MAX_S = 32;
+    static constexpr bool CHUNKS = H == 32;
     // A round's march ends when fewer than half of the pool's rays have this little of their slots filled: at width 32 a second step
     // for the rest of a ray's slots is mostly thrown away; at width 64, where a visit of a network costs more, it pays.
     static constexpr int NEED_QUARTERS = H == 32 ? 2 : 4;
 };
 
-// Rays beyond the first pools are handed to a workgroup in chunks, its wavefronts take from those what they have places for: an
-// eighth of a workgroup's even share of what is left, so that the chunks become small towards the end.  (An atomic per wavefront
-// and round, all on one word, kept the wavefronts waiting: 11 ns each, 45 us for the 4,096 that ask after their first round.)
+// Rays beyond the first pools.  Width 32: they are handed to a workgroup in chunks, its wavefronts take from those what they have places
+// for: an eighth of a workgroup's even share of what is left, so that the chunks become small towards the end.  (An atomic per
+// wavefront and round, all on one word, kept the wavefronts waiting: 11 ns each, 45 us for the 4,096 that ask after their first round.)
+// Width 64: half as many wavefronts, whose rounds take three times as long, take them for themselves (1080p 1,051 us, 1,084 in chunks:
+// rays that are under way at the same time lie closer together).
 constexpr int CHUNK_SHARE = 8, CHUNK_MIN = 16, CHUNK_MAX = 512;
-constexpr int FEW_RAYS = 1; // rays per wavefront below which a workgroup starts with fewer wavefronts
+// Rays in a row that a workgroup which sets up its own rays takes together: some eight groups per workgroup, so that those rays that
+// meet content are spread evenly, of rays that meet the same networks.  Groups of 2 / 4 / 8 / 16 rays: 111x80 32 / 31 / 30 / 30 us, 87x90 25 /
+// 25 / 27 / -, 236x134 at width 64 169 / 149 / 136 / 131.
+constexpr int OWN_GROUP_MIN = 4, OWN_GROUP_MAX = 16;
+constexpr int OWN_RAYS_MAX = OWN_GROUP_MAX * (int)((KN_FUSED_OWN_RAYS + 256 * OWN_GROUP_MAX - 1) / (256 * OWN_GROUP_MAX));
 
 // a wavefront's part of the LDS
 template <int H> struct WaveLds {
@@ -65,17 +74,14 @@ template <int H> struct WaveLds {
 // depend on the number of points (ranks, frontier, skip field) is shared by four
 constexpr int STEPS = 4;
 
-// the grid that is marched through, for voxel_coords
-struct VoxelFast {
-    float inv[3], shift[3], guard, one_minus_guard, bmin[3], cell[3];
-    int32_t res[3];
-};
-
 struct FusedArgs {
     MarchParams p;
     VoxelFast vox, net; // the grid that is marched through, the network grid
     const uint16_t *packed;
     const float *rays_o, *rays_d;
+    int32_t max_lg;    // log2 of the rays of a full pool
+    int32_t few_rays;  // a workgroup starts with fewer wavefronts where its wavefronts would get fewer rays than this
+    int32_t R, own_rays, own_group; // own_rays > 0: a workgroup sets up that many rays by itself, groups of own_group, and there is no list
     const int4 *list;  // live rays: (ray, first lattice index, end of the clipped range, -)
     int32_t *ctl;      // [0] = live rays, [1] = rays handed out beyond the wavefronts' first pools
     float eps, bg[3];
@@ -120,28 +126,7 @@ __device__ __forceinline__ float divide(float a, float b)
     return __builtin_amdgcn_div_fixupf(__builtin_amdgcn_div_fmasf(fmaf(-d, q, n), r, q, scaled), b, a);
 }
 
-// float -> floor as an integer, as the instruction defines it for every input: saturated, NaN -> 0
-__device__ __forceinline__ int32_t floor_int(float f)
-{
-    int32_t i;
-    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(f));
-    return i;
-}
-__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c) { return (int32_t)(__umul24((uint32_t)a, (uint32_t)b) + (uint32_t)c); }
-
-// Eq. 6 per axis on the grid that is marched through: integer cell coordinates (any value outside [0, res) for points
-// outside).  u = x / cell - bmin / cell in one multiply-add differs from the quotient of Eq. 6 by less than `guard` (host:
-// voxel_fast); true where some u is that close to an integer: the caller then evaluates the divisions themselves.
-__device__ __forceinline__ bool voxel_coords(const VoxelFast &g, float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz)
-{
-    const float ux = fmaf(x, g.inv[0], g.shift[0]), uy = fmaf(y, g.inv[1], g.shift[1]), uz = fmaf(z, g.inv[2], g.shift[2]);
-    const float fx = __builtin_amdgcn_fractf(ux), fy = __builtin_amdgcn_fractf(uy), fz = __builtin_amdgcn_fractf(uz);
-    ix = floor_int(ux);
-    iy = floor_int(uy);
-    iz = floor_int(uz);
-    return (fminf(fminf(fx, fy), fz) <= g.guard) | (fmaxf(fmaxf(fx, fy), fz) >= g.one_minus_guard);
-}
-
+// Eq. 6 itself
 __device__ __forceinline__ void voxel_coords_exact(const VoxelFast &g, float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz)
 {
     ix = floor_int(divide(x - g.bmin[0], g.cell[0]));
@@ -149,10 +134,13 @@ __device__ __forceinline__ void voxel_coords_exact(const VoxelFast &g, float x, 
     iz = floor_int(divide(z - g.bmin[2], g.cell[2]));
     __builtin_amdgcn_sched_barrier(0); // (the divisions of several points side by side would cost more registers than there are)
 }
-__device__ __forceinline__ bool inside(const VoxelFast &g, int32_t ix, int32_t iy, int32_t iz)
-{
-    return ((uint32_t)ix < (uint32_t)g.res[0]) & ((uint32_t)iy < (uint32_t)g.res[1]) & ((uint32_t)iz < (uint32_t)g.res[2]);
-}
+struct ExactDivide {
+    __device__ __forceinline__ float operator()(float a, float b) const { return divide(a, b); }
+};
+__device__ __forceinline__ bool is_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; } // (the file is compiled without NaNs)
+
+// the first n lanes, 1 <= n <= 64
+__device__ __forceinline__ unsigned long long lanes_below(int n) { return ~0ull >> (KN_WAVE - n); }
 
 // LDS writes of the wavefront's lanes before, reads after
 __device__ __forceinline__ void wave_sync()
@@ -175,6 +163,7 @@ __global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
     // was given, and how many wavefronts are out of work
     __shared__ int32_t s_state[Pl::MAX_WAVES], s_given[Pl::MAX_WAVES], s_idle;
     __shared__ int32_t s_lock, s_at, s_end; // what is left of the workgroup's chunk of the list
+    __shared__ int32_t s_own;               // live rays of a workgroup that sets up its own
 
     const ArgsPtr args = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); // = &args_by_value
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
@@ -184,20 +173,75 @@ __global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
     f4 *rays = s_wave[wave].ray;
     uint16_t *idx = s_wave[wave].idx;
 
-    const int n_live = args->ctl[0];
-    // as many wavefronts as get FEW_RAYS rays each; the others take what is shared out
-    const int users = min(n_waves, max(1, (n_live + (int)gridDim.x * FEW_RAYS - 1) / ((int)gridDim.x * FEW_RAYS)));
-    const int total_waves = gridDim.x * users;
+    // this workgroup's place among all: those of one XCD (b mod 8) side by side
+    const int place_of_block = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+    int4 *const own_list = (int4 *)(s_wave + n_waves);
+    const int own_rays = args->own_rays;
+    if (own_rays > 0) {
+        // ---- Small frames: the set-up is part of the kernel.  A workgroup takes groups of rays that lie as far apart as there are
+        // workgroups, eight lanes walk a ray, each through an eighth of its range.
+        if (threadIdx.x == 0) s_own = 0;
+        __syncthreads();
+        keep_denormals(true);
+        const ArgsPtr a = opaque(args);
+        const MarchParams &p = *(const MarchParams *)&a->p;
+        const VoxelFast vf = *(const VoxelFast *)&a->vox;
+        constexpr int LANES = 8, RAYS = KN_WAVE / LANES;
+        const int sub = lane & (LANES - 1);
+        for (int j0 = wave * RAYS; j0 < own_rays; j0 += n_waves * RAYS) {
+            const int j = j0 + lane / LANES;
+            const int group = a->own_group; // (a power of two)
+            const int r = (place_of_block + (int)gridDim.x * (j / group)) * group + (j & (group - 1));
+            int32_t k_lo = 0, k_hi = 0, first = 0x7fffffff;
+            if (r < a->R) {
+                const float o[3] = {a->rays_o[3 * (int64_t)r], a->rays_o[3 * (int64_t)r + 1], a->rays_o[3 * (int64_t)r + 2]};
+                const float d[3] = {a->rays_d[3 * (int64_t)r], a->rays_d[3 * (int64_t)r + 1], a->rays_d[3 * (int64_t)r + 2]};
+                clip_ray(*(const KnGrid *)&a->p.content, o, d, a->p.t_near, a->p.step, a->p.K, k_lo, k_hi, ExactDivide{});
+                // (a ray with a component that is no finite number has no lattice point inside the box)
+                if (!(is_finite(o[0]) & is_finite(o[1]) & is_finite(o[2]) & is_finite(d[0]) & is_finite(d[1]) & is_finite(d[2]))) k_hi = k_lo;
+                const int32_t part = (int32_t)(((uint32_t)(k_hi - k_lo) + (LANES - 1)) / LANES);
+                const int32_t from = k_lo + sub * part, to = min(from + part, k_hi);
+                const int32_t at = walk_to_content<STRAT>(p, vf, o, d, from, to, kn_mix32(a->p.seed_key + (uint32_t)r),
+                                                          [&](float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz) { voxel_coords_exact(vf, x, y, z, ix, iy, iz); });
+                if (at < to) first = at;
+            }
+#pragma unroll
+            for (int w = 1; w < LANES; w <<= 1) first = min(first, __shfl_xor(first, w, KN_WAVE));
+            const bool lives = first < k_hi;
+            const unsigned long long m = __ballot(lives && sub == 0);
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&s_own, __popcll(m));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (sub == 0 && r < a->R) {
+                if (lives) {
+                    own_list[base + __popcll(m & ((1ull << lane) - 1ull))] = make_int4(r, first, k_hi, 0);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) a->rgb_out[3 * (int64_t)r + c] = a->bg[c];
+                }
+            }
+        }
+        keep_denormals(false);
+        __syncthreads();
+    }
+    const int n_live = own_rays > 0 ? s_own : args->ctl[0];
+    const int peers = own_rays > 0 ? 1 : (int)gridDim.x; // workgroups that share the list
+    const int few_rays = args->few_rays;
+    // as many wavefronts as get few_rays rays each; the others take what is shared out
+    const int users = min(n_waves, max(1, (n_live + peers * few_rays - 1) / (peers * few_rays)));
+    const int total_waves = peers * users;
     // rays per pool: as many as give every wavefront one, up to the pool's size
     int lgP = Pl::MIN_LG;
-    while (lgP < Pl::MAX_LG && ((int64_t)total_waves << lgP) < n_live) ++lgP;
+    // (width 32: large pools only where they are filled a second time)
+    const int max_lg = H == 32 && n_live < 3 * (total_waves << (Pl::MAX_LG - 1)) ? Pl::MAX_LG - 1 : args->max_lg;
+    while (lgP < max_lg && ((int64_t)total_waves << lgP) < n_live) ++lgP;
 
     // First pools: equal contiguous shares of the list's head.  A workgroup takes four that lie side by side (rays that meet the
     // same networks) from each of up to four parts of the list (rays that cost differently); inside a part, shares that lie side by
     // side go to the workgroups of one XCD (b mod 8), which find each other's networks in its L2.  A workgroup's shares
     // scattered one by one: the same for large frames, 164x94 rays with a network per sample 79 -> 96 us instead of 72.
     const int part = wave >> 2, width = min(4, users - 4 * part);
-    const int wid = 4 * part * (int)gridDim.x + (((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3)) * width + (wave & 3);
+    const int wid = own_rays > 0 ? wave : 4 * part * (int)gridDim.x + place_of_block * width + (wave & 3);
     const int n_first = (int)min((int64_t)n_live, (int64_t)total_waves << lgP);
     int at = __builtin_amdgcn_readfirstlane(wave < users ? (int)((int64_t)wid * n_first / total_waves) : 0);
     int end = __builtin_amdgcn_readfirstlane(wave < users ? (int)((int64_t)(wid + 1) * n_first / total_waves) : 0);
@@ -216,7 +260,7 @@ __global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
             // ---- The list is exhausted.  The rays that are left differ in cost (most end within two rounds, some take ten),
             // and a wavefront with many long ones would run on alone: one that has run out of rays waits for a part of
             // another wavefront's of its workgroup.  (LDS only; a waiting wavefront ends when all are out of work.)
-            unsigned long long live = __ballot(ray >= 0) & ((1ull << (1 << lgP)) - 1ull);
+            unsigned long long live = __ballot(ray >= 0) & lanes_below(1 << lgP);
             int n = __popcll(live);
             const int ln = opaque(lane);
             if (n == 0) {
@@ -276,7 +320,7 @@ __global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
                         __hip_atomic_store(&s_state[to], GIVEN, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                     n = keep;
-                    live = __ballot(ray >= 0) & ((1ull << P) - 1ull);
+                    live = __ballot(ray >= 0) & lanes_below(P);
                 }
             }
             // ---- the rays that are left move together, so that each gets more lanes and more slots
@@ -302,7 +346,7 @@ __global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
         }
         const int P = 1 << lgP, G = KN_WAVE >> lgP;
         const int S_max = min(Pl::SLOTS >> lgP, Pl::MAX_S);
-        const unsigned long long firsts = (1ull << P) - 1ull; // lanes that lead a ray's group
+        const unsigned long long firsts = lanes_below(P); // lanes that lead a ray's group
         int cnt = 0;
         {
             const ArgsPtr a = opaque(args);
@@ -314,22 +358,27 @@ __global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
             if (n_free > 0) {
                 if (at >= end && more) {
                     int got = 0, last = 0;
-                    if (ln == 0) { // (the lock's holder is a resident wavefront and waits for nothing but memory)
-                        int expect = 0;
-                        while (!__hip_atomic_compare_exchange_strong(&s_lock, &expect, 1, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                            expect = 0;
-                            __builtin_amdgcn_s_sleep(1);
+                    if (ln == 0) {
+                        if constexpr (Pl::CHUNKS) { // (the lock's holder is a resident wavefront and waits for nothing but memory)
+                            int expect = 0;
+                            while (!__hip_atomic_compare_exchange_strong(&s_lock, &expect, 1, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
+                                expect = 0;
+                                __builtin_amdgcn_s_sleep(1);
+                            }
+                            got = __hip_atomic_load(&s_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            last = __hip_atomic_load(&s_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            const int chunk = min(max((n_live - max(last, n_first)) / ((int)gridDim.x * CHUNK_SHARE), CHUNK_MIN), CHUNK_MAX);
+                            if (got >= last && last < n_live) {
+                                got = min(n_first + atomicAdd(&a->ctl[1], chunk), n_live);
+                                last = min(got + chunk, n_live);
+                                __hip_atomic_store(&s_end, last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            }
+                            __hip_atomic_store(&s_at, min(got + n_free, last), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            __hip_atomic_store(&s_lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        } else {
+                            got = min(n_first + atomicAdd(&a->ctl[1], n_free), n_live);
+                            last = min(got + n_free, n_live);
                         }
-                        got = __hip_atomic_load(&s_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        last = __hip_atomic_load(&s_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        const int chunk = min(max((n_live - max(last, n_first)) / ((int)gridDim.x * CHUNK_SHARE), CHUNK_MIN), CHUNK_MAX);
-                        if (got >= last && last < n_live) {
-                            got = min(n_first + atomicAdd(&a->ctl[1], chunk), n_live);
-                            last = min(got + chunk, n_live);
-                            __hip_atomic_store(&s_end, last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        }
-                        __hip_atomic_store(&s_at, min(got + n_free, last), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        __hip_atomic_store(&s_lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                     at = __builtin_amdgcn_readfirstlane(got);
                     last = __builtin_amdgcn_readfirstlane(last);
@@ -340,7 +389,7 @@ __global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
                 if (avail > 0) {
                     const int rank = __popcll(free_places & ((1ull << slot) - 1ull));
                     if (ray < 0 && rank < avail) {
-                        const int4 e = a->list[at + rank];
+                        const int4 e = a->own_rays > 0 ? own_list[at + rank] : a->list[at + rank];
                         ray = e.x;
                         k = e.y;
                         k_hi = e.z;
@@ -643,26 +692,6 @@ __global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
 
 } // namespace
 
-// u = fma(x, fl(1/cell), fl(-bmin * fl(1/cell))) against fl(fl(x - bmin) / cell): with A = max(|bmin|, |bmax|) / cell, the
-// roundings of 1/cell, of the product and of u amount to 2^-24 (3 A + res), those of Eq. 6 to 2^-23 res, for every x
-// inside the box; 2e-7 (A + res + 1) is above their sum.
-static VoxelFast voxel_fast(const KnGrid &g)
-{
-    VoxelFast v;
-    v.guard = 0.0f;
-    for (int a = 0; a < 3; ++a) {
-        v.bmin[a] = g.bmin[a];
-        v.cell[a] = g.cell[a];
-        v.res[a] = g.res[a];
-        v.inv[a] = 1.0f / g.cell[a];
-        v.shift[a] = -g.bmin[a] * v.inv[a];
-        const float reach = fmaxf(fabsf(g.bmin[a]), fabsf(g.bmin[a] + g.cell[a] * (float)g.res[a]));
-        v.guard = fmaxf(v.guard, 2e-7f * (reach * v.inv[a] + (float)g.res[a] + 1.0f) + 1e-30f);
-    }
-    v.one_minus_guard = 1.0f - v.guard;
-    return v;
-}
-
 // The kernel's voxel, block and cell numbers are formed with 24-bit multiplications, and it keeps a sample's network in
 // 16 bits.
 bool kn_fused_supports(const kn_scene *sc)
@@ -690,7 +719,8 @@ static const FusedFn fused_table[2][2][2][2] = {
 int kn_fused_configure()
 {
     for (int i = 0; i < 16; ++i) {
-        const int bytes = (i & 8) ? Pool<64>::MAX_WAVES * (int)sizeof(WaveLds<64>) : Pool<32>::MAX_WAVES * (int)sizeof(WaveLds<32>);
+        const int bytes = ((i & 8) ? Pool<64>::MAX_WAVES * (int)sizeof(WaveLds<64>) : Pool<32>::MAX_WAVES * (int)sizeof(WaveLds<32>)) +
+                          OWN_RAYS_MAX * (int)sizeof(int4);
         KN_HIP(hipFuncSetAttribute((const void *)fused_table[i >> 3][(i >> 2) & 1][(i >> 1) & 1][i & 1], hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     }
     return KN_OK;
@@ -708,6 +738,7 @@ int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, h
     a.rays_o = job.rays_o;
     a.rays_d = job.rays_d;
     a.list = job.list;
+    a.R = (int32_t)job.R;
     a.ctl = job.ctl;
     a.eps = job.eps;
     for (int c = 0; c < 3; ++c) a.bg[c] = job.bg[c];
@@ -722,7 +753,20 @@ int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, h
     const int64_t want = kn_div_up(job.R, 1 << Pool<32>::MIN_LG);
     const int waves = (int)std::min<int64_t>(std::max<int64_t>(kn_div_up(want, 256), 4), max_waves);
     const int64_t blocks = std::min<int64_t>(8 * kn_div_up(want, 8 * waves), 256);
-    const size_t lds = waves * (H == 32 ? sizeof(WaveLds<32>) : sizeof(WaveLds<64>));
+    // Full pools of many rays with few samples each where rays end after few samples, of half as many rays otherwise.  How many a ray
+    // takes depends on the scene; coarse lattices need fewer than fine ones.  Half / all, one frame each: 1424x1070, width 32, K = 32 (2^3
+    // networks) 294 / 268 us, K = 128 (16^3) 176 / 168, 800x800, K = 512, 169 / 182; width 64, 1424x1070, K = 64 (2^3) 580 / 390, K = 256 (8^3)
+    // 340 / 310, K = 512 (16^3) 460 / 457, 1080p, K = 1024, 1,051 / 1,110.
+    a.max_lg = H == 32 ? (a.p.K < 256 ? 5 : 4) : (a.p.K < 512 ? 6 : 5);
+    a.own_group = OWN_GROUP_MIN;
+    while (a.own_group < OWN_GROUP_MAX && job.R > 6 * 256 * (int64_t)a.own_group) a.own_group *= 2;
+    // With hardly two samples of a ray per network the weights' way to the wavefronts is what bounds a frame: there, and with enough
+    // rays for all compute units, four rays or more share what a wavefront loads (164x94, 1.2 samples per network, width 32 / 64: 93 -> 80 /
+    // 224 -> 172 us); elsewhere every wavefront gets a ray if there is one (100x100, 1.5 samples per network: 47 us, 62 with four).
+    const float points = fminf(a.p.net.cell[0], fminf(a.p.net.cell[1], a.p.net.cell[2])) / a.p.step;
+    a.few_rays = points < 2.0f && job.R > 12288 ? 4 : 1;
+    a.own_rays = job.list ? 0 : (int32_t)(a.own_group * kn_div_up(job.R, a.own_group * blocks));
+    const size_t lds = waves * (H == 32 ? sizeof(WaveLds<32>) : sizeof(WaveLds<64>)) + a.own_rays * sizeof(int4);
     if (H != 32 && H != 64) return KN_E_UNSUPPORTED;
     const FusedFn kernel = fused_table[H == 64][bf][wrap][job.strat ? 1 : 0];
     const dim3 grid((unsigned)blocks), block(waves * KN_WAVE);

@@ -102,8 +102,12 @@ __device__ __forceinline__ int32_t grid_index_fast(const GridFast &g, float x, f
 // Conservative range [k_lo, k_hi) of lattice indices whose point can lie inside the AABB (slab
 // test widened by the rounding error of x_k = fma(t_k, d, o) and two steps).  Every index
 // outside the range is provably outside the box; indices inside it are still tested exactly.
+struct PlainDivide {
+    __device__ __forceinline__ float operator()(float a, float b) const { return a / b; }
+};
+template <typename Divide = PlainDivide>
 __device__ __forceinline__ void clip_ray(const KnGrid &g, const float o[3], const float d[3], float t_near, float step,
-                                         int32_t K, int32_t &k_lo, int32_t &k_hi)
+                                         int32_t K, int32_t &k_lo, int32_t &k_hi, Divide divide = Divide{})
 {
     if (g.res[0] == 0) { // empty box
         k_lo = k_hi = 0;
@@ -114,7 +118,7 @@ __device__ __forceinline__ void clip_ray(const KnGrid &g, const float o[3], cons
     for (int a = 0; a < 3; ++a) {
         if (d[a] != 0.0f) {
             const float lo = g.bmin[a], hi = g.bmin[a] + g.cell[a] * (float)g.res[a];
-            const float inv = 1.0f / d[a];
+            const float inv = divide(1.0f, d[a]);
             float t0 = (lo - o[a]) * inv, t1 = (hi - o[a]) * inv;
             if (t0 > t1) { float s = t0; t0 = t1; t1 = s; }
             const float mag = fabsf(lo) + fabsf(hi) + fabsf(o[a]) + g.cell[a];
@@ -124,8 +128,8 @@ __device__ __forceinline__ void clip_ray(const KnGrid &g, const float o[3], cons
         }
     }
     // k such that t_near + (k + 1/2) step lies in [tmin, tmax], widened by two steps
-    float a = floorf((tmin - t_near) / step - 0.5f) - 2.0f;
-    float b = ceilf((tmax - t_near) / step - 0.5f) + 3.0f;
+    float a = floorf(divide(tmin - t_near, step) - 0.5f) - 2.0f;
+    float b = ceilf(divide(tmax - t_near, step) - 0.5f) + 3.0f;
     a = fminf(fmaxf(a, 0.0f), (float)K); // NaN -> 0
     b = fminf(fmaxf(b, 0.0f), (float)K);
     if (!(tmin <= tmax)) { // empty -> nothing; NaN -> stay conservative (full range)
@@ -190,6 +194,102 @@ __device__ __forceinline__ int32_t skip_to_content(const MarchParams &p, const G
         } else {
             break;
         }
+    }
+    return min(k, k_hi);
+}
+
+// a grid, for voxel_coords
+struct VoxelFast {
+    float inv[3], shift[3], guard, one_minus_guard, bmin[3], cell[3];
+    int32_t res[3];
+};
+
+// float -> floor as an integer, as the instruction defines it for every input: saturated, NaN -> 0
+__device__ __forceinline__ int32_t floor_int(float f)
+{
+    int32_t i;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(f));
+    return i;
+}
+__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c) { return (int32_t)(__umul24((uint32_t)a, (uint32_t)b) + (uint32_t)c); }
+
+// Eq. 6 per axis on the grid that is marched through: integer cell coordinates (any value outside [0, res) for points
+// outside).  u = x / cell - bmin / cell in one multiply-add differs from the quotient of Eq. 6 by less than `guard` (host:
+// voxel_fast); true where some u is that close to an integer: the caller then evaluates the divisions themselves.
+__device__ __forceinline__ bool voxel_coords(const VoxelFast &g, float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz, float *u = nullptr)
+{
+    const float ux = fmaf(x, g.inv[0], g.shift[0]), uy = fmaf(y, g.inv[1], g.shift[1]), uz = fmaf(z, g.inv[2], g.shift[2]);
+    const float fx = __builtin_amdgcn_fractf(ux), fy = __builtin_amdgcn_fractf(uy), fz = __builtin_amdgcn_fractf(uz);
+    ix = floor_int(ux);
+    iy = floor_int(uy);
+    iz = floor_int(uz);
+    if (u) { // (known at compile time)
+        u[0] = ux;
+        u[1] = uy;
+        u[2] = uz;
+    }
+    return (fminf(fminf(fx, fy), fz) <= g.guard) | (fmaxf(fmaxf(fx, fy), fz) >= g.one_minus_guard);
+}
+
+__device__ __forceinline__ bool inside(const VoxelFast &g, int32_t ix, int32_t iy, int32_t iz)
+{
+    return ((uint32_t)ix < (uint32_t)g.res[0]) & ((uint32_t)iy < (uint32_t)g.res[1]) & ((uint32_t)iz < (uint32_t)g.res[2]);
+}
+
+// u = fma(x, fl(1/cell), fl(-bmin * fl(1/cell))) against fl(fl(x - bmin) / cell): with A = max(|bmin|, |bmax|) / cell, the
+// roundings of 1/cell, of the product and of u amount to 2^-24 (3 A + res), those of Eq. 6 to 2^-23 res, for every x
+// inside the box; 2e-7 (A + res + 1) is above their sum.
+inline VoxelFast voxel_fast(const KnGrid &g)
+{
+    VoxelFast v;
+    v.guard = 0.0f;
+    for (int a = 0; a < 3; ++a) {
+        v.bmin[a] = g.bmin[a];
+        v.cell[a] = g.cell[a];
+        v.res[a] = g.res[a];
+        v.inv[a] = 1.0f / g.cell[a];
+        v.shift[a] = -g.bmin[a] * v.inv[a];
+        const float reach = fmaxf(fabsf(g.bmin[a]), fabsf(g.bmin[a] + g.cell[a] * (float)g.res[a]));
+        v.guard = fmaxf(v.guard, 2e-7f * (reach * v.inv[a] + (float)g.res[a] + 1.0f) + 1e-30f);
+    }
+    v.one_minus_guard = 1.0f - v.guard;
+    return v;
+}
+
+// The fused render's walk to content: the first index in [k, k_hi) whose point is in a block that is occupied or next to one (or
+// k_hi); no index in front of it can be a kept sample.  From a point whose block has distance D to the nearest occupied block the
+// ray jumps out of the empty cube of blocks around it ((2 D - 1)^3 of them, wherever in its block the point is), where skip_to_content
+// jumps by the radius of the ball that is empty around every point of the block: half as many dependent look-ups.
+// exact(x, y, z, ix, iy, iz): Eq. 6 with its divisions, for points within rounding of a voxel's face.
+template <bool STRAT, typename Exact>
+__device__ __forceinline__ int32_t walk_to_content(const MarchParams &p, const VoxelFast &g, const float o[3], const float d[3], int32_t k,
+                                                   int32_t k_hi, uint32_t ray_key, Exact exact)
+{
+    if (k >= k_hi || !p.skip_dist) return min(k, k_hi);
+    float per_block[3]; // lattice steps per block (infinite: the ray does not move along the axis)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) per_block[a] = __builtin_amdgcn_rcpf(fabsf(d[a] * (p.step * p.skip_inv[a])));
+    const float margin = (p.skip_margin + 1e-6f * (fabsf(o[0]) + fabsf(o[1]) + fabsf(o[2]))) * (1.000001f * __builtin_amdgcn_rcpf(p.skip_edge_min));
+    while (k < k_hi) {
+        float x, y, z, u[3];
+        int32_t ix, iy, iz;
+        kn_lattice_point<STRAT>(o[0], o[1], o[2], d[0], d[1], d[2], p.t_near, p.step, k, x, y, z, ray_key);
+        if (voxel_coords(g, x, y, z, ix, iy, iz, u)) exact(x, y, z, ix, iy, iz);
+        if (!inside(g, ix, iy, iz)) { // (the clipped range starts a little in front of the box)
+            ++k;
+            continue;
+        }
+        const int32_t dist = p.skip_dist[mad24(mad24(ix >> 2, p.skip_res[1], iy >> 2), p.skip_res[2], iz >> 2)];
+        if (dist < 2) break;
+        float steps = INFINITY;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float f = __builtin_amdgcn_fractf(u[a] * (1.0f / KN_SKIP_BLOCK));
+            steps = fminf(steps, ((float)dist - margin - (d[a] > 0.0f ? f : 1.0f - f)) * per_block[a]);
+        }
+        // (stratified: point k + j lies up to j + 1 steps from point k; saturated, the sum below would wrap)
+        const int32_t further = (int32_t)fminf(fmaxf(floorf(steps * 0.999996f) - (STRAT ? 2.0f : 1.0f), 0.0f), 2147483520.0f);
+        k = further >= k_hi - k ? k_hi : k + 1 + further;
     }
     return min(k, k_hi);
 }

@@ -316,7 +316,7 @@ __device__ __forceinline__ int32_t spread3(int32_t v) // bit i of a 5-bit number
 }
 template <bool STRAT, bool SORT>
 __global__ void __launch_bounds__(RAY_BLOCK)
-    k_fused_init(MarchParams p, BucketMap map, const float *__restrict__ rays_o, const float *__restrict__ rays_d, int64_t R,
+    k_fused_init(MarchParams p, VoxelFast vox, BucketMap map, const float *__restrict__ rays_o, const float *__restrict__ rays_d, int64_t R,
                  int4 *__restrict__ recs, int32_t *__restrict__ blk_sum, int32_t *__restrict__ counts, float bg0, float bg1, float bg2,
                  float *__restrict__ rgb_out)
 {
@@ -331,7 +331,11 @@ __global__ void __launch_bounds__(RAY_BLOCK)
         clip_ray(p.content, o, d, p.t_near, p.step, p.K, k_lo, k_hi);
         // (a ray with a component that is no finite number has no lattice point inside the box)
         if (!(isfinite(o[0]) && isfinite(o[1]) && isfinite(o[2]) && isfinite(d[0]) && isfinite(d[1]) && isfinite(d[2]))) k_hi = k_lo;
-        k_lo = skip_to_content<STRAT ? OPT_STRAT : 0>(p, make_fast(p.occ), o, d, k_lo, k_hi, ray_key);
+        k_lo = walk_to_content<STRAT>(p, vox, o, d, k_lo, k_hi, ray_key, [&](float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz) {
+            ix = floor_int((x - vox.bmin[0]) / vox.cell[0]);
+            iy = floor_int((y - vox.bmin[1]) / vox.cell[1]);
+            iz = floor_int((z - vox.bmin[2]) / vox.cell[2]);
+        });
         if (k_lo < k_hi) {
             key = 0;
             if constexpr (SORT) {
@@ -1265,23 +1269,27 @@ static int render_fused(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, const M
     }
     KnStageTimer tm(ctx, st);
     tm.begin();
-    const bool sort = R >= SORT_RAYS;
-    if (sort) KN_TRY(kn_fill_i32(st, w.counts, FUSED_BUCKETS, 0));
-    const auto init = sort ? (seed ? k_fused_init<true, true> : k_fused_init<false, true>)
-                           : (seed ? k_fused_init<true, false> : k_fused_init<false, false>);
-    hipLaunchKernelGGL(init, dim3((unsigned)kn_div_up(R, RAY_BLOCK)), dim3(RAY_BLOCK), 0, st, p, map, rays_o, rays_d, R, w.recs, w.blk_sum,
-                       w.counts, bg[0], bg[1], bg[2], rgb_out);
-    KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL(sort ? k_fused_list<true> : k_fused_list<false>, dim3((unsigned)kn_div_up(R, LIST_BLOCK * LIST_RAYS)), dim3(LIST_BLOCK), 0,
-                       st, w.recs, R, w.blk_sum, w.counts, w.list, w.ctl);
-    KN_CHECK_LAUNCH();
-    tm.mark(KN_ST_SETUP);
+    // (sample counts are gathered through the list's control words)
+    const bool own = R <= KN_FUSED_OWN_RAYS && !tm.counts;
+    if (!own) {
+        const bool sort = R >= SORT_RAYS;
+        if (sort) KN_TRY(kn_fill_i32(st, w.counts, FUSED_BUCKETS, 0));
+        const auto init = sort ? (seed ? k_fused_init<true, true> : k_fused_init<false, true>)
+                               : (seed ? k_fused_init<true, false> : k_fused_init<false, false>);
+        hipLaunchKernelGGL(init, dim3((unsigned)kn_div_up(R, RAY_BLOCK)), dim3(RAY_BLOCK), 0, st, p, voxel_fast(p.occ), map, rays_o, rays_d, R, w.recs, w.blk_sum,
+                           w.counts, bg[0], bg[1], bg[2], rgb_out);
+        KN_CHECK_LAUNCH();
+        hipLaunchKernelGGL(sort ? k_fused_list<true> : k_fused_list<false>, dim3((unsigned)kn_div_up(R, LIST_BLOCK * LIST_RAYS)), dim3(LIST_BLOCK), 0,
+                           st, w.recs, R, w.blk_sum, w.counts, w.list, w.ctl);
+        KN_CHECK_LAUNCH();
+        tm.mark(KN_ST_SETUP);
+    }
     KnFusedJob job{};
     job.march = &p;
     job.rays_o = rays_o;
     job.rays_d = rays_d;
     job.R = R;
-    job.list = w.list;
+    job.list = own ? nullptr : w.list;
     job.ctl = w.ctl;
     job.eps = term_eps;
     job.bg = bg;
