@@ -15,6 +15,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libkilonerf_hip.so")
 
 KN_F32, KN_F16, KN_BF16 = 0, 1, 2
+KN_E_WORKSPACE = -3
 DTYPES = {"f32": KN_F32, "f16": KN_F16, "bf16": KN_BF16}
 
 EXPORTS = ["kn_error_string", "kn_last_hip_error", "kn_params_per_net", "kn_create", "kn_destroy", "kn_set_option",
@@ -47,16 +48,17 @@ class Profile(C.Structure):
 
 
 _lib = None
+torch = None  # set by load_library, which whatever uses it calls first: importing this package alone does not import torch
 
 
 def load_library(build_if_missing: bool = True):
     """dlopen the in-tree library (building it first only if it does not exist)."""
-    global _lib
+    global _lib, torch
     if _lib is not None:
         return _lib
     # torch ships its own HIP runtime; it must be the one already loaded when the library is opened,
     # so that device pointers and streams created by torch are valid inside the library
-    import torch  # noqa: F401
+    import torch
     if not os.path.exists(LIB_PATH):
         if not build_if_missing:
             raise KnError("libkilonerf_hip.so has not been built (run paper_2103_13744_amd/build.py)")
@@ -114,6 +116,9 @@ def _ptr(t, dtype=None, allow_none=False, shape=None):
         if allow_none:
             return None
         raise KnError("missing tensor argument")
+    # (what a call nearly always is; anything else is looked at part by part below)
+    if t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype) and (shape is None or t.shape == shape):
+        return t.data_ptr()
     if not t.is_cuda or not t.is_contiguous():
         raise KnError("tensor arguments must be contiguous device tensors")
     if dtype is not None and t.dtype != dtype:
@@ -125,8 +130,8 @@ def _ptr(t, dtype=None, allow_none=False, shape=None):
 
 
 def _stream():
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    """The current device's current stream, as torch.cuda.current_stream().cuda_stream gives it (which takes 2.9 us for it)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def params_per_net(hidden: int, L_pos: int = 10, L_dir: int = 4) -> int:
@@ -178,7 +183,7 @@ _default_ctx = {}
 
 def default_context(device=None) -> Context:
     """One shared context per device, created on first use (scenes and the module-level helpers use it unless told otherwise)."""
-    import torch
+    load_library()
     dev = torch.cuda.current_device() if device is None else int(device)
     if dev not in _default_ctx:
         _default_ctx[dev] = Context(dev)
@@ -208,7 +213,6 @@ class Scene:
 
     def __init__(self, res, aabb_min, aabb_max, hidden, weights, occupancy=None, L_pos=10, L_dir=4, cell_net=None, ctx=None,
                  lend_buffer=True):
-        import torch
         self.L = load_library()
         self.ctx = default_context(weights.device.index) if ctx is None else ctx
         wd = {torch.float32: KN_F32, torch.float16: KN_F16, torch.bfloat16: KN_BF16}.get(weights.dtype)
@@ -269,7 +273,6 @@ class Scene:
         return out.value
 
     def _workspace(self, max_points=0, max_rays=0, ctx=None):
-        import torch
         need = self.workspace_bytes(max_points, max_rays, ctx)
         if self._ws is None or self._ws.numel() < need:
             self._ws = torch.empty(need, dtype=torch.uint8, device=self.device)
@@ -277,7 +280,6 @@ class Scene:
 
     # -- stages --------------------------------------------------------------------------
     def cell_ids(self, points):
-        import torch
         M = points.shape[0]
         ids = torch.empty(M, dtype=torch.int32, device=self.device)
         _check(self.L.kn_cell_ids(self.h, _stream(), _ptr(points, torch.float32, shape=(M, 3)) if M else None, M,
@@ -285,7 +287,6 @@ class Scene:
         return ids
 
     def bucket(self, ids, ctx=None):
-        import torch
         M = ids.shape[0]
         counts = torch.empty(self.N + 1, dtype=torch.int32, device=self.device)
         offsets = torch.empty(self.N + 2, dtype=torch.int32, device=self.device)
@@ -298,11 +299,13 @@ class Scene:
     def _eval_args(self, points, dirs, out, aux):
         """Checked pointers of an eval_grouped call: points, dirs (M, 3) float32; out = (sigma (M,), rgb (M, 3)) float32;
         aux = None or (ids (M,), counts (N + 1,), perm (M,)) int32."""
-        import torch
         M = points.shape[0]
         sigma, rgb = out
-        ids, counts, perm = aux if aux is not None else (None, None, None)
         f, i = torch.float32, torch.int32
+        if aux is None and M > 0:
+            return M, (_ptr(points, f, shape=(M, 3)), _ptr(dirs, f, shape=(M, 3))), \
+                (_ptr(sigma, f, shape=(M,)), _ptr(rgb, f, shape=(M, 3))), (None, None, None)
+        ids, counts, perm = aux if aux is not None else (None, None, None)
         if M == 0:
             return 0, (None, None), (None, None), (None, _ptr(counts, i, allow_none=True, shape=(self.N + 1,)), None)
         return M, (_ptr(points, f, shape=(M, 3)), _ptr(dirs, f, shape=(M, 3))), \
@@ -311,7 +314,6 @@ class Scene:
              _ptr(perm, i, allow_none=True, shape=(M,)))
 
     def eval_grouped(self, points, dirs, want_aux=False, out=None, ctx=None):
-        import torch
         M = points.shape[0]
         if out is None:
             out = (torch.empty(M, dtype=torch.float32, device=self.device),
@@ -321,10 +323,15 @@ class Scene:
             aux = (torch.empty(M, dtype=torch.int32, device=self.device),
                    torch.empty(self.N + 1, dtype=torch.int32, device=self.device),
                    torch.empty(M, dtype=torch.int32, device=self.device))
-        ws = self._workspace(max_points=max(M, 1), ctx=ctx)
         M, pin, pout, paux = self._eval_args(points, dirs, out, aux)
-        _check(self.L.kn_eval_grouped(self._ctx(ctx), self.h, _stream(), *pin, M, *pout, *paux, _ptr(ws), ws.numel()),
-               "kn_eval_grouped")
+        ws = self._ws
+        # (the call looks at the workspace's size before anything else: asking for it beforehand would cost every call 0.9 us)
+        rc = KN_E_WORKSPACE if ws is None else self.L.kn_eval_grouped(self._ctx(ctx), self.h, _stream(), *pin, M, *pout, *paux,
+                                                                      ws.data_ptr(), ws.numel())
+        if rc == KN_E_WORKSPACE:
+            ws = self._workspace(max_points=max(M, 1), ctx=ctx)
+            rc = self.L.kn_eval_grouped(self._ctx(ctx), self.h, _stream(), *pin, M, *pout, *paux, ws.data_ptr(), ws.numel())
+        _check(rc, "kn_eval_grouped")
         if want_aux:
             return (*out, *aux)
         return out
@@ -339,7 +346,6 @@ class Scene:
     def eval_grouped_layered(self, points, dirs, out=None, workspace=None, ctx=None):
         """eval_grouped one layer at a time (grouped matrix products with activations in device memory): the
         comparison point for the fused kernel.  16-bit scenes only."""
-        import torch
         M = points.shape[0]
         if out is None:
             out = (torch.empty(M, dtype=torch.float32, device=self.device),
@@ -356,7 +362,6 @@ class Scene:
     def extract_occupancy(self, occ_res, tau, out=None, ctx=None):
         """Occupancy grid of resolution ``occ_res`` from the scene's own density field (27 probes per voxel,
         marked where any density is above ``tau``): a uint8 device tensor of shape ``occ_res``."""
-        import torch
         res = tuple(int(r) for r in occ_res)
         occ = torch.empty(res, dtype=torch.uint8, device=self.device) if out is None else out
         need = C.c_int64()
@@ -368,7 +373,6 @@ class Scene:
 
     def march(self, rays_o, rays_d, t_near, step, K, S=None, k_begin=None, seed=None):
         """``seed`` None: midpoint lattice (kn_march); else stratified sampling (kn_march_stratified)."""
-        import torch
         R = rays_o.shape[0]
         S = int(K if S is None else S)
         out_k = torch.empty((R, S), dtype=torch.int32, device=self.device)
@@ -388,11 +392,10 @@ class Scene:
         """``seed`` None: midpoint lattice (kn_render); else stratified sampling (kn_render_stratified).  ``workspace``: a uint8 device tensor of at least ``workspace_bytes(max_rays=R)`` bytes; by default one
         cached workspace per scene is used.  Calls that are in flight at the same time (on different streams) need
         a workspace each."""
-        import torch
         R = rays_o.shape[0]
         rgb = torch.empty((R, 3), dtype=torch.float32, device=self.device) if out is None else out
         ws = self._workspace(max_rays=max(R, 1), ctx=ctx) if workspace is None else workspace
-        st = RenderStats()
+        st = RenderStats() if want_stats else None
         bgc = (C.c_float * 3)(*[float(v) for v in bg])
         f = torch.float32
         head = (self._ctx(ctx), self.h, _stream(), _ptr(rays_o, f, shape=(R, 3)) if R else None,
@@ -410,7 +413,6 @@ class Scene:
 def composite(sigma, rgb, offsets, step, term_eps=0.0, bg=(0.0, 0.0, 0.0)):
     """``step``: the constant sample spacing (kn_composite), or a float32 device tensor with a spacing per sample
     (kn_composite_deltas)."""
-    import torch
     L = load_library()
     R = offsets.shape[0] - 1
     out = torch.empty((R, 3), dtype=torch.float32, device=offsets.device)
