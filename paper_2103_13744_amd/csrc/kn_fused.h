@@ -20,5 +20,7 @@ struct KnFusedJob {
     bool strat;
 };
 int kn_fused_configure(); // once per device
+int kn_fused_f32_configure();
 bool kn_fused_supports(const kn_scene *sc);
 int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, hipEvent_t ev_start, hipEvent_t ev_stop);
+int kn_fused_f32_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, hipEvent_t ev_start, hipEvent_t ev_stop);

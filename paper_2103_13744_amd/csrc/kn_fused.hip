@@ -1,702 +1,139 @@
-// The whole path behind one kernel (Sec. 3.4, Eq. 1-4, Eq. 7): marching with empty-space skipping, grouping by network,
-// the fused tiny MLP and blending with early ray termination, for scenes with 16-bit weights.
-//
-// A wavefront owns a pool of P rays (P a power of two, G = 64 / P lanes per ray) and works through them alone, without
-// workgroup barriers.  One round: every ray of the pool collects up to S kept samples (P * S slots of LDS per
-// wavefront); the samples are evaluated network by network; every ray blends its samples in order and ends, or stays
-// for the next round; free places are filled with the next rays of the live list.  Samples, results and encoded
-// directions never leave the LDS, a frame needs no slot buffers, no histogram and no host decision in the middle, and a
-// ray stops within S samples of its termination point.  Against the wave loop (march, group, evaluate and blend kernels
-// per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 57 us; 800x800 230 -> 164; 1080p,
-// width 64, 1430 -> 1025.  Frames of up to 32,767 rays are this kernel alone: a workgroup also clips its rays and walks them to their
-// first lattice point near content (200x151: 67 us with two launches in front of it).
-//
-// What bounds it: vector-ALU issue while there is work (a march step of 256 points takes about 300 instructions, a tile of 16
-// samples about 65, a round about 350 besides), and the end of a frame, when the rays that are left are few.  The rays' costs differ
-// (most end within two rounds, some take ten) and neighbours cost alike, so a workgroup is all of a compute unit's wavefronts, whose
-// first pools lie in as many parts of the list, and who share their last rays through the LDS: workgroups of four
-// wavefronts, all places in a list filled by an atomic per wavefront and round, 203 us at 800x800 (call, with the set-up's 31), 181
-// at 767x577 stratified, 1,093 at 1080p, width 64; like this 164, 148 and 1,038.  Tried and slower: contiguous pieces of the list
-// larger than what a wavefront has places for (800x800 +3, 1080p +60: the last pieces decide), hand-out counters per XCD (+3, +20),
-// half of the list handed out beforehand (+6, +190), 12 wavefronts per compute unit (+3).
-//
-// The wavefronts of a SIMD are in different phases at different times, so the latency of the march runs under the
-// evaluation of the others.  Results are the bits of the wave loop (kn_render.hip): same lattice points, same operand
-// order in the networks (a sample's outputs do not depend on which samples share its tile), same recurrence per ray.
-#include "kn_common.h"
-#include "kn_fused.h"
-#include "kn_march.h"
+// The fused render (kn_fused_core.h) of scenes with 16-bit weights.
+#include "kn_fused_core.h"
 #include "kn_mlp_core.h"
-#include <hip/hip_ext.h>
-
-#include <algorithm>
 
 namespace {
 
-enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last rays of a workgroup are shared out
+template <int H, bool BF, bool WRAP> struct Net16 {
+    using L = Lay<H>;
+    static constexpr int HT = L::HT, HK = L::HK, NBLK = L::NBLK;
+    static constexpr bool FLUSHED = true;
+    static constexpr int DIR = 4;
 
-// Rays and slots per wavefront.  Large pools keep few lanes per ray and cut a ray into many rounds, small ones evaluate more samples
-// behind the termination point; many slots mean many samples per visit of a network, few fit a step of the march (256 points).
-// Rays x slots, 800x800 and 767x577 / 1080p at width 64, us: 32 x 384 183, 167 / 64 x 768 1,211; 16 x 384 173, 163 / 32 x 768 1,100;
-// 16 x 256 169, 156 / 32 x 896 1,100; 32 x 256 182, 164 / 32 x 512 1,225; 16 x 768 at width 64 1,191.  (kn_fused_launch chooses between
-// full pools of 1 << MAX_LG rays and of half as many.)
-template <int H> struct Pool {
-    static constexpr int SLOTS = H == 32 ? 256 : 768, MAX_LG = H == 32 ? 5 : 6, RAYS = 1 << MAX_LG, NQ = SLOTS / KN_WAVE;
+    // Rays and slots per wavefront.  Large pools keep few lanes per ray and cut a ray into many rounds, small ones evaluate more samples
+    // behind the termination point; many slots mean many samples per visit of a network, few fit a step of the march (256 points).
+    // Rays x slots, 800x800 and 767x577 / 1080p at width 64, us: 32 x 384 183, 167 / 64 x 768 1,211; 16 x 384 173, 163 / 32 x 768 1,100;
+    // 16 x 256 169, 156 / 32 x 896 1,100; 32 x 256 182, 164 / 32 x 512 1,225; 16 x 768 at width 64 1,191.
+    static constexpr int SLOTS = H == 32 ? 256 : 768, MIN_LG = 2, MAX_LG = H == 32 ? 5 : 6, MAX_S = 32;
     static constexpr int WAVES_PER_SIMD = H == 32 ? 4 : 2, MAX_WAVES = 4 * WAVES_PER_SIMD;
-    static constexpr int MIN_LG = 2, MAX_S = 32;
-    static constexpr bool CHUNKS = H == 32;
+    // Full pools of many rays with few samples each where rays end after few samples, of half as many rays otherwise.  How many a ray
+    // takes depends on the scene; coarse lattices need fewer than fine ones.  Half / all, one frame each: 1424x1070, width 32, K = 32 (2^3
+    // networks) 294 / 268 us, K = 128 (16^3) 176 / 168, 800x800, K = 512, 169 / 182; width 64, 1424x1070, K = 64 (2^3) 580 / 390, K = 256 (8^3)
+    // 340 / 310, K = 512 (16^3) 460 / 457, 1080p, K = 1024, 1,051 / 1,110.  At width 32 they have to be filled more than once.
+    static constexpr int LARGE_POOLS_BELOW = H == 32 ? 256 : 512;
+    static constexpr bool LARGE_POOLS_LATE = H == 32;
+    static constexpr int SHARE_LATER = 1;
+    static constexpr bool CHUNKS = H == 32; // how rays beyond the first pools are handed out (CHUNK_SHARE)
     // A round's march ends when fewer than half of the pool's rays have this little of their slots filled: at width 32 a second step
     // for the rest of a ray's slots is mostly thrown away; at width 64, where a visit of a network costs more, it pays.
     static constexpr int NEED_QUARTERS = H == 32 ? 2 : 4;
-};
 
-// Rays beyond the first pools.  Width 32: they are handed to a workgroup in chunks, its wavefronts take from those what they have places
-// for: an eighth of a workgroup's even share of what is left, so that the chunks become small towards the end.  (An atomic per
-// wavefront and round, all on one word, kept the wavefronts waiting: 11 ns each, 45 us for the 4,096 that ask after their first round.)
-// Width 64: half as many wavefronts, whose rounds take three times as long, take them for themselves (1080p 1,051 us, 1,084 in chunks:
-// rays that are under way at the same time lie closer together).
-constexpr int CHUNK_SHARE = 8, CHUNK_MIN = 16, CHUNK_MAX = 512;
-// Rays in a row that a workgroup which sets up its own rays takes together: some eight groups per workgroup, so that those rays that
-// meet content are spread evenly, of rays that meet the same networks.  Groups of 2 / 4 / 8 / 16 rays: 111x80 32 / 31 / 30 / 30 us, 87x90 25 /
-// 25 / 27 / -, 236x134 at width 64 169 / 149 / 136 / 131.
-constexpr int OWN_GROUP_MIN = 4, OWN_GROUP_MAX = 16;
-constexpr int OWN_RAYS_MAX = OWN_GROUP_MAX * (int)((KN_FUSED_OWN_RAYS + 256 * OWN_GROUP_MAX - 1) / (256 * OWN_GROUP_MAX));
-
-// a wavefront's part of the LDS
-template <int H> struct WaveLds {
-    f4 slot[Pool<H>::SLOTS];      // sample j of pool ray s at j * P + s: (x, y, z, density scale), then (r, g, b, alpha)
-    u4 dir[Pool<H>::RAYS * 4];    // gamma(d) of pool ray s in operand order
-    f4 ray[Pool<H>::RAYS * 2];    // (origin, jump scale), (direction, jump offset) of pool ray s
-    uint16_t idx[Pool<H>::SLOTS]; // the samples' networks, then the slots of the network at hand
-};
-
-// lattice points a lane tests per step of the march: enough look-ups in flight, and the work per step that does not
-// depend on the number of points (ranks, frontier, skip field) is shared by four
-constexpr int STEPS = 4;
-
-struct FusedArgs {
-    MarchParams p;
-    VoxelFast vox, net; // the grid that is marched through, the network grid
-    const uint16_t *packed;
-    const float *rays_o, *rays_d;
-    int32_t max_lg;    // log2 of the rays of a full pool
-    int32_t few_rays;  // a workgroup starts with fewer wavefronts where its wavefronts would get fewer rays than this
-    int32_t R, own_rays, own_group; // own_rays > 0: a workgroup sets up that many rays by itself, groups of own_group, and there is no list
-    const int4 *list;  // live rays: (ray, first lattice index, end of the clipped range, -)
-    int32_t *ctl;      // [0] = live rays, [1] = rays handed out beyond the wavefronts' first pools
-    float eps, bg[3];
-    float *rgb_out;
-    unsigned long long *counters; // nullable: [0] += samples evaluated, [1] += samples blended
-};
-
-// The arguments are read from the kernel's own argument segment where they are used: `opaque` hides where the pointer and
-// the lane number come from, so that neither arguments nor values derived from the lane number stay in registers across
-// the phases of a round (the evaluation has none to spare).
-typedef const __attribute__((address_space(4))) FusedArgs *ArgsPtr;
-__device__ __forceinline__ ArgsPtr opaque(ArgsPtr p)
-{
-    asm volatile("" : "+s"(p));
-    return p;
-}
-__device__ __forceinline__ int opaque(int lane)
-{
-    asm volatile("" : "+v"(lane));
-    return lane;
-}
-
-// The file is compiled for flushed fp32 denormals (the evaluation's encoding needs that, see build.py).  Where lattice points
-// are placed and tested, and in the blend, denormals count: a point at -1e-40 lies outside a box that starts at 0.  There the mode
-// register says so; the compiler's own divisions would set it back, so none is left to it in those parts, and neither is a
-// multiplication by two (the output modifier does nothing there).
-__device__ __forceinline__ void keep_denormals(bool keep)
-{
-    constexpr int FP32_DENORM = 1 | (4 << 6) | (1 << 11); // MODE, bits 4 and 5
-    if (keep) __builtin_amdgcn_s_setreg(FP32_DENORM, 3);
-    else __builtin_amdgcn_s_setreg(FP32_DENORM, 0);
-}
-// a / b rounded to nearest, with denormals kept: the instruction set's scaled division
-__device__ __forceinline__ float divide(float a, float b)
-{
-    bool scaled, unused;
-    const float d = __builtin_amdgcn_div_scalef(a, b, false, &unused), n = __builtin_amdgcn_div_scalef(a, b, true, &scaled);
-    float r = __builtin_amdgcn_rcpf(d);
-    r = fmaf(fmaf(-d, r, 1.0f), r, r);
-    float q = n * r;
-    q = fmaf(fmaf(-d, q, n), r, q);
-    return __builtin_amdgcn_div_fixupf(__builtin_amdgcn_div_fmasf(fmaf(-d, q, n), r, q, scaled), b, a);
-}
-
-// Eq. 6 itself
-__device__ __forceinline__ void voxel_coords_exact(const VoxelFast &g, float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz)
-{
-    ix = floor_int(divide(x - g.bmin[0], g.cell[0]));
-    iy = floor_int(divide(y - g.bmin[1], g.cell[1]));
-    iz = floor_int(divide(z - g.bmin[2], g.cell[2]));
-    __builtin_amdgcn_sched_barrier(0); // (the divisions of several points side by side would cost more registers than there are)
-}
-struct ExactDivide {
-    __device__ __forceinline__ float operator()(float a, float b) const { return divide(a, b); }
-};
-__device__ __forceinline__ bool is_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; } // (the file is compiled without NaNs)
-
-// the first n lanes, 1 <= n <= 64
-__device__ __forceinline__ unsigned long long lanes_below(int n) { return ~0ull >> (KN_WAVE - n); }
-
-// LDS writes of the wavefront's lanes before, reads after
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <int H, bool BF, bool WRAP, bool STRAT>
-__global__ void __launch_bounds__(Pool<H>::MAX_WAVES *KN_WAVE)
-    __attribute__((amdgpu_waves_per_eu(Pool<H>::WAVES_PER_SIMD, Pool<H>::WAVES_PER_SIMD))) k_render_fused(FusedArgs args_by_value)
-{
-    using L = Lay<H>;
-    using Pl = Pool<H>;
-    constexpr int HT = L::HT, HK = L::HK, NBLK = L::NBLK, NQ = Pl::NQ;
-    extern __shared__ f4 s_dynamic[];
-    WaveLds<H> *const s_wave = (WaveLds<H> *)s_dynamic; // one per wavefront of the workgroup
-    // sharing of the last rays inside the workgroup: what each wavefront is doing, the number of rays it
-    // was given, and how many wavefronts are out of work
-    __shared__ int32_t s_state[Pl::MAX_WAVES], s_given[Pl::MAX_WAVES], s_idle;
-    __shared__ int32_t s_lock, s_at, s_end; // what is left of the workgroup's chunk of the list
-    __shared__ int32_t s_own;               // live rays of a workgroup that sets up its own
-
-    const ArgsPtr args = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); // = &args_by_value
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
-    const int n_waves = blockDim.x / KN_WAVE;
-    f4 *slots = s_wave[wave].slot;
-    u4 *dirs = s_wave[wave].dir;
-    f4 *rays = s_wave[wave].ray;
-    uint16_t *idx = s_wave[wave].idx;
-
-    // this workgroup's place among all: those of one XCD (b mod 8) side by side
-    const int place_of_block = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
-    int4 *const own_list = (int4 *)(s_wave + n_waves);
-    const int own_rays = args->own_rays;
-    if (own_rays > 0) {
-        // ---- Small frames: the set-up is part of the kernel.  A workgroup takes groups of rays that lie as far apart as there are
-        // workgroups, eight lanes walk a ray, each through an eighth of its range.
-        if (threadIdx.x == 0) s_own = 0;
-        __syncthreads();
-        keep_denormals(true);
-        const ArgsPtr a = opaque(args);
-        const MarchParams &p = *(const MarchParams *)&a->p;
-        const VoxelFast vf = *(const VoxelFast *)&a->vox;
-        constexpr int LANES = 8, RAYS = KN_WAVE / LANES;
-        const int sub = lane & (LANES - 1);
-        for (int j0 = wave * RAYS; j0 < own_rays; j0 += n_waves * RAYS) {
-            const int j = j0 + lane / LANES;
-            const int group = a->own_group; // (a power of two)
-            const int r = (place_of_block + (int)gridDim.x * (j / group)) * group + (j & (group - 1));
-            int32_t k_lo = 0, k_hi = 0, first = 0x7fffffff;
-            if (r < a->R) {
-                const float o[3] = {a->rays_o[3 * (int64_t)r], a->rays_o[3 * (int64_t)r + 1], a->rays_o[3 * (int64_t)r + 2]};
-                const float d[3] = {a->rays_d[3 * (int64_t)r], a->rays_d[3 * (int64_t)r + 1], a->rays_d[3 * (int64_t)r + 2]};
-                clip_ray(*(const KnGrid *)&a->p.content, o, d, a->p.t_near, a->p.step, a->p.K, k_lo, k_hi, ExactDivide{});
-                // (a ray with a component that is no finite number has no lattice point inside the box)
-                if (!(is_finite(o[0]) & is_finite(o[1]) & is_finite(o[2]) & is_finite(d[0]) & is_finite(d[1]) & is_finite(d[2]))) k_hi = k_lo;
-                const int32_t part = (int32_t)(((uint32_t)(k_hi - k_lo) + (LANES - 1)) / LANES);
-                const int32_t from = k_lo + sub * part, to = min(from + part, k_hi);
-                const int32_t at = walk_to_content<STRAT>(p, vf, o, d, from, to, kn_mix32(a->p.seed_key + (uint32_t)r),
-                                                          [&](float x, float y, float z, int32_t &ix, int32_t &iy, int32_t &iz) { voxel_coords_exact(vf, x, y, z, ix, iy, iz); });
-                if (at < to) first = at;
-            }
+    static __device__ __forceinline__ void place_direction(const float (&d)[3], u4 *to) // gamma(d) in operand order
+    {
+        kn_enc::u4 q[4];
+        kn_enc::dir_slots<BF>(d[0], d[1], d[2], q);
 #pragma unroll
-            for (int w = 1; w < LANES; w <<= 1) first = min(first, __shfl_xor(first, w, KN_WAVE));
-            const bool lives = first < k_hi;
-            const unsigned long long m = __ballot(lives && sub == 0);
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&s_own, __popcll(m));
-            base = __builtin_amdgcn_readfirstlane(base);
-            if (sub == 0 && r < a->R) {
-                if (lives) {
-                    own_list[base + __popcll(m & ((1ull << lane) - 1ull))] = make_int4(r, first, k_hi, 0);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) a->rgb_out[3 * (int64_t)r + c] = a->bg[c];
-                }
-            }
-        }
-        keep_denormals(false);
-        __syncthreads();
+        for (int i = 0; i < 4; ++i) to[i] = q[i];
     }
-    const int n_live = own_rays > 0 ? s_own : args->ctl[0];
-    const int peers = own_rays > 0 ? 1 : (int)gridDim.x; // workgroups that share the list
-    const int few_rays = args->few_rays;
-    // as many wavefronts as get few_rays rays each; the others take what is shared out
-    const int users = min(n_waves, max(1, (n_live + peers * few_rays - 1) / (peers * few_rays)));
-    const int total_waves = peers * users;
-    // rays per pool: as many as give every wavefront one, up to the pool's size
-    int lgP = Pl::MIN_LG;
-    // (width 32: large pools only where they are filled a second time)
-    const int max_lg = H == 32 && n_live < 3 * (total_waves << (Pl::MAX_LG - 1)) ? Pl::MAX_LG - 1 : args->max_lg;
-    while (lgP < max_lg && ((int64_t)total_waves << lgP) < n_live) ++lgP;
 
-    // First pools: equal contiguous shares of the list's head.  A workgroup takes four that lie side by side (rays that meet the
-    // same networks) from each of up to four parts of the list (rays that cost differently); inside a part, shares that lie side by
-    // side go to the workgroups of one XCD (b mod 8), which find each other's networks in its L2.  A workgroup's shares
-    // scattered one by one: the same for large frames, 164x94 rays with a network per sample 79 -> 96 us instead of 72.
-    const int part = wave >> 2, width = min(4, users - 4 * part);
-    const int wid = own_rays > 0 ? wave : 4 * part * (int)gridDim.x + place_of_block * width + (wave & 3);
-    const int n_first = (int)min((int64_t)n_live, (int64_t)total_waves << lgP);
-    int at = __builtin_amdgcn_readfirstlane(wave < users ? (int)((int64_t)wid * n_first / total_waves) : 0);
-    int end = __builtin_amdgcn_readfirstlane(wave < users ? (int)((int64_t)(wid + 1) * n_first / total_waves) : 0);
-    bool more = n_live > n_first;
-    if (threadIdx.x < n_waves) s_state[threadIdx.x] = BUSY;
-    if (threadIdx.x == 0) s_idle = s_lock = s_at = s_end = 0;
-    __syncthreads();
-
-    int ray = -1, k = 0, k_hi = 0; // (the same in all lanes of a ray's group, like everything per ray below)
-    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-    long long evaluated = 0, blended = 0; // (uniform)
-
-    for (;;) {
-        bool moved = false;
-        if (at >= end && !more) {
-            // ---- The list is exhausted.  The rays that are left differ in cost (most end within two rounds, some take ten),
-            // and a wavefront with many long ones would run on alone: one that has run out of rays waits for a part of
-            // another wavefront's of its workgroup.  (LDS only; a waiting wavefront ends when all are out of work.)
-            unsigned long long live = __ballot(ray >= 0) & lanes_below(1 << lgP);
-            int n = __popcll(live);
-            const int ln = opaque(lane);
-            if (n == 0) {
-                if (ln == 0) {
-                    __hip_atomic_store(&s_state[wave], IDLE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    __hip_atomic_fetch_add(&s_idle, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
-                int st;
-                for (;;) {
-                    st = __hip_atomic_load(&s_state[wave], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (__builtin_amdgcn_readfirstlane(st) == GIVEN) break;
-                    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_idle, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == n_waves) break;
-                    __builtin_amdgcn_s_sleep(4);
-                }
-                if (__builtin_amdgcn_readfirstlane(st) != GIVEN) break; // everybody is out of work
-                n = __builtin_amdgcn_readfirstlane(s_given[wave]);
-                if (ln == 0) __hip_atomic_store(&s_state[wave], BUSY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                lgP = Pl::MAX_LG;
-                const int place = ln & ((1 << lgP) - 1);
-                if (place < n) {
-                    const f4 q0 = slots[2 * place], q1 = slots[2 * place + 1];
-                    ray = __float_as_int(q0[0]);
-                    k = __float_as_int(q0[1]);
-                    k_hi = __float_as_int(q0[2]);
-                    T = q0[3];
-                    c0 = q1[0];
-                    c1 = q1[1];
-                    c2 = q1[2];
-                }
-                live = (1ull << n) - 1ull; // (at most half a pool was given)
-                wave_sync();
-            } else if (n >= 2 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > 0) {
-                int to = -1;
-                if (ln == 0)
-                    for (int w = 1; w < n_waves && to < 0; ++w) {
-                        int expect = IDLE;
-                        const int other = wave + w < n_waves ? wave + w : wave + w - n_waves;
-                        if (__hip_atomic_compare_exchange_strong(&s_state[other], &expect, CLAIMED, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
-                                                                 __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                            to = other;
-                            __hip_atomic_fetch_sub(&s_idle, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        }
-                    }
-                to = __builtin_amdgcn_readfirstlane(to);
-                if (to >= 0) { // the upper half of the live rays moves to wavefront `to`'s part of the LDS
-                    const int P = 1 << lgP, place = ln & (P - 1), keep = n - n / 2;
-                    const int rank = __popcll(live & ((1ull << place) - 1ull)) - keep;
-                    const bool gives = ray >= 0 && rank >= 0;
-                    if (gives && ln < P) {
-                        s_wave[to].slot[2 * rank] = (f4){__int_as_float(ray), __int_as_float(k), __int_as_float(k_hi), T};
-                        s_wave[to].slot[2 * rank + 1] = (f4){c0, c1, c2, 0.0f};
-                    }
-                    if (gives) ray = -1;
-                    if (ln == 0) {
-                        s_given[to] = n / 2;
-                        // (the LDS is written in order: the rays are there before the state says so)
-                        __hip_atomic_store(&s_state[to], GIVEN, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                    n = keep;
-                    live = __ballot(ray >= 0) & lanes_below(P);
-                }
-            }
-            // ---- the rays that are left move together, so that each gets more lanes and more slots
-            int lg = lgP;
-            while (lg > Pl::MIN_LG && n <= (1 << (lg - 1))) --lg;
-            if (lg < lgP) {
-                if ((live >> ln) & 1ull) idx[__popcll(live & ((1ull << ln) - 1ull))] = (uint16_t)ln; // (a leading lane is its place's number)
-                wave_sync();
-                const int place = ln & ((1 << lg) - 1);
-                const int from = place < n ? (int)idx[place] : 0;
-                ray = __shfl(ray, from, KN_WAVE);
-                k = __shfl(k, from, KN_WAVE);
-                k_hi = __shfl(k_hi, from, KN_WAVE);
-                T = __shfl(T, from, KN_WAVE);
-                c0 = __shfl(c0, from, KN_WAVE);
-                c1 = __shfl(c1, from, KN_WAVE);
-                c2 = __shfl(c2, from, KN_WAVE);
-                if (place >= n) ray = -1;
-                moved = true;
-                lgP = lg;
-                wave_sync();
-            }
-        }
-        const int P = 1 << lgP, G = KN_WAVE >> lgP;
-        const int S_max = min(Pl::SLOTS >> lgP, Pl::MAX_S);
-        const unsigned long long firsts = lanes_below(P); // lanes that lead a ray's group
-        int cnt = 0;
+    struct Weights {
+        u4 areg[NBLK], a_out[HK];
+        f4 bias2[HT], bias_out;
+        __device__ __forceinline__ void load(const void *packed, int32_t net, int lane)
         {
-            const ArgsPtr a = opaque(args);
-            const int ln = opaque(lane), slot = ln & (P - 1), gl = ln >> lgP;
-            // ---- fill the free places of the pool
-            const unsigned long long free_places = __ballot(ray < 0) & firsts;
-            const int n_free = __popcll(free_places);
-            bool fresh = moved;
-            if (n_free > 0) {
-                if (at >= end && more) {
-                    int got = 0, last = 0;
-                    if (ln == 0) {
-                        if constexpr (Pl::CHUNKS) { // (the lock's holder is a resident wavefront and waits for nothing but memory)
-                            int expect = 0;
-                            while (!__hip_atomic_compare_exchange_strong(&s_lock, &expect, 1, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                                expect = 0;
-                                __builtin_amdgcn_s_sleep(1);
-                            }
-                            got = __hip_atomic_load(&s_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            last = __hip_atomic_load(&s_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            const int chunk = min(max((n_live - max(last, n_first)) / ((int)gridDim.x * CHUNK_SHARE), CHUNK_MIN), CHUNK_MAX);
-                            if (got >= last && last < n_live) {
-                                got = min(n_first + atomicAdd(&a->ctl[1], chunk), n_live);
-                                last = min(got + chunk, n_live);
-                                __hip_atomic_store(&s_end, last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            }
-                            __hip_atomic_store(&s_at, min(got + n_free, last), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            __hip_atomic_store(&s_lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        } else {
-                            got = min(n_first + atomicAdd(&a->ctl[1], n_free), n_live);
-                            last = min(got + n_free, n_live);
-                        }
-                    }
-                    at = __builtin_amdgcn_readfirstlane(got);
-                    last = __builtin_amdgcn_readfirstlane(last);
-                    end = min(at + n_free, last);
-                    more = end < n_live;
-                }
-                const int avail = end - at;
-                if (avail > 0) {
-                    const int rank = __popcll(free_places & ((1ull << slot) - 1ull));
-                    if (ray < 0 && rank < avail) {
-                        const int4 e = a->own_rays > 0 ? own_list[at + rank] : a->list[at + rank];
-                        ray = e.x;
-                        k = e.y;
-                        k_hi = e.z;
-                        T = 1.0f;
-                        c0 = c1 = c2 = 0.0f;
-                        fresh = true;
-                    }
-                    at += min(n_free, avail);
-                }
-            }
-            if (__ballot(ray >= 0) == 0ull) continue; // (only where the hand-out counter gave nothing any more)
-            if (ray >= 0 && fresh && gl == 0) { // a ray takes its place: what the rounds need of it goes to the LDS
-                float o[3], d[3];
+            const u4 *__restrict__ wp = (const u4 *)((const uint16_t *)packed + (int64_t)net * L::HALFS);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    o[c] = a->rays_o[3 * (int64_t)ray + c];
-                    d[c] = a->rays_d[3 * (int64_t)ray + c];
-                }
-                const SkipJump sj(*(const MarchParams *)&a->p, o, d, STRAT);
-                rays[2 * slot] = (f4){o[0], o[1], o[2], sj.use ? sj.a : 0.0f};
-                rays[2 * slot + 1] = (f4){d[0], d[1], d[2], sj.use ? sj.b : 1e30f}; // (no jumps)
-                kn_enc::u4 q[4];
-                kn_enc::dir_slots<BF>(d[0], d[1], d[2], q);
+            for (int b = 0; b < NBLK; ++b) areg[b] = wp[b * KN_WAVE + lane];
+            const float *__restrict__ tail = (const float *)(wp + NBLK * KN_WAVE);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) dirs[4 * slot + i] = q[i];
-            }
-            wave_sync();
-
-            keep_denormals(true);
-            // ---- march: up to S kept samples per ray.  A step tests G * STEPS consecutive lattice points, STEPS per lane,
-            // with all look-ups of the step in flight together; the skip field is asked at each lane's last point only.
-            // What the loop reads of the arguments is copied out in front of it (scalar registers): a scalar load inside costs
-            // its latency per step, and there were twenty of them (7,200 cycles per step, 1,300 without).
-            if (ray >= 0) {
-                const VoxelFast vf = *(const VoxelFast *)&a->vox;
-                const float t_near = a->p.t_near, step = a->p.step;
-                const uint4 *__restrict__ const bricks = a->p.bricks;
-                const int32_t *__restrict__ const cell_net = a->p.cell_net;
-                const uint32_t last_block = (uint32_t)(a->p.skip_res[0] * a->p.skip_res[1] * a->p.skip_res[2] - 1); // (points outside look up any block)
-                const int32_t skip1 = a->p.skip_res[1], skip2 = a->p.skip_res[2];
-                const int32_t has_occ = a->p.has_occ, brick_nets = a->p.brick_nets;
-                const int n_lanes = __popcll(__ballot(true));
-                const f4 ro = rays[2 * slot], rd = rays[2 * slot + 1];
-                const int S = S_max;
-                const uint32_t ray_key = kn_mix32(a->p.seed_key + (uint32_t)ray);
-                // The march of a round ends when fewer than half of the pool's rays still collect: the others would only wait.
-                while (2 * __popcll(__ballot(k < k_hi && 4 * cnt < Pl::NEED_QUARTERS * S)) >= n_lanes) {
-                  if (k < k_hi && cnt < S) {
-                    const int k0 = k + gl * STEPS;
-                    float x[STEPS], y[STEPS], z[STEPS];
-                    int32_t ix[STEPS], iy[STEPS], iz[STEPS], net[STEPS];
-                    bool in[STEPS], close = false;
-#pragma unroll
-                    for (int c = 0; c < STEPS; ++c) {
-                        kn_lattice_point<STRAT>(ro[0], ro[1], ro[2], rd[0], rd[1], rd[2], t_near, step, k0 + c, x[c], y[c], z[c], ray_key);
-                        close |= voxel_coords(vf, x[c], y[c], z[c], ix[c], iy[c], iz[c]);
-                    }
-                    if (close) { // some point within rounding of a voxel's face: the divisions themselves
-#pragma unroll
-                        for (int c = 0; c < STEPS; ++c) voxel_coords_exact(vf, x[c], y[c], z[c], ix[c], iy[c], iz[c]);
-                    }
-#pragma unroll
-                    for (int c = 0; c < STEPS; ++c) // (saturated integers: whatever the coordinates are, the look-ups stay inside)
-                        in[c] = inside(vf, ix[c], iy[c], iz[c]) & (k0 + c < k_hi);
-                    int32_t dist = 0;
-                    if (has_occ) { // (uniform)
-                        // occupancy bits, network and skip-field value of each point's block: one load per point, all in flight together
-                        uint4 brick[STEPS];
-#pragma unroll
-                        for (int c = 0; c < STEPS; ++c)
-                            brick[c] = bricks[min((uint32_t)mad24(mad24(ix[c] >> 2, skip1, iy[c] >> 2), skip2, iz[c] >> 2), last_block)];
-                        dist = in[STEPS - 1] ? (int32_t)brick[STEPS - 1].w : 0;
-#pragma unroll
-                        for (int c = 0; c < STEPS; ++c) {
-                            const uint64_t bits = (uint64_t)brick[c].y << 32 | brick[c].x;
-                            in[c] = in[c] & (((bits >> (((ix[c] & 3) << 4) | ((iy[c] & 3) << 2) | (iz[c] & 3))) & 1ull) != 0ull);
-                            net[c] = (int32_t)brick[c].z;
-                        }
-                    }
-                    if (!brick_nets) { // (uniform) a block may lie in several cells, or there is no occupancy grid
-                        const VoxelFast vn = *(const VoxelFast *)&a->net;
-                        bool close_net = false;
-#pragma unroll
-                        for (int c = 0; c < STEPS; ++c) {
-                            int32_t nx, ny, nz;
-                            close_net |= voxel_coords(vn, x[c], y[c], z[c], nx, ny, nz);
-                            in[c] = in[c] & inside(vn, nx, ny, nz);
-                            net[c] = mad24(mad24(nx, vn.res[1], ny), vn.res[2], nz);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                        if (close_net) {
-#pragma unroll
-                            for (int c = 0; c < STEPS; ++c) {
-                                int32_t nx, ny, nz;
-                                voxel_coords_exact(vn, x[c], y[c], z[c], nx, ny, nz);
-                                in[c] = in[c] & inside(vn, nx, ny, nz);
-                                net[c] = mad24(mad24(nx, vn.res[1], ny), vn.res[2], nz);
-                            }
-                        }
-                        if (cell_net) { // (uniform) a sparse grid: the cell's network, or none
-                            const uint32_t last_cell = (uint32_t)(vn.res[0] * vn.res[1] * vn.res[2] - 1);
-#pragma unroll
-                            for (int c = 0; c < STEPS; ++c) net[c] = cell_net[min((uint32_t)net[c], last_cell)];
-#pragma unroll
-                            for (int c = 0; c < STEPS; ++c) in[c] = in[c] & (net[c] >= 0);
-                        }
-                    }
-                    // ranks in order along the ray: kept points of the lanes in front of this one in the group, then this lane's
-                    int own = 0;
-#pragma unroll
-                    for (int c = 0; c < STEPS; ++c) own += in[c] ? 1 : 0;
-                    int incl = own;
-                    for (int w = P; w < KN_WAVE; w <<= 1) {
-                        const int v = __shfl_up(incl, w, KN_WAVE);
-                        if (ln >= w + slot) incl += v; // (lane ln - w belongs to the group as well)
-                    }
-                    const int total = __shfl(incl, slot + KN_WAVE - P, KN_WAVE);
-                    int rank = cnt + incl - own;
-                    int stop = 0x7fffffff; // first kept point that does not fit: where the next round resumes
-#pragma unroll
-                    for (int c = 0; c < STEPS; ++c) {
-                        if (in[c] & (rank < S)) {
-                            const int at_slot = (rank << lgP) + slot;
-                            float dscale = 1.0f;
-                            if constexpr (STRAT)
-                                dscale = divide(kn_lattice_t<true>(t_near, step, k0 + c + 1, ray_key) - kn_lattice_t<true>(t_near, step, k0 + c, ray_key), step);
-                            slots[at_slot] = (f4){x[c], y[c], z[c], dscale};
-                            idx[at_slot] = (uint16_t)net[c];
-                        }
-                        stop = (in[c] & (rank == S)) ? k0 + c : stop;
-                        rank += in[c] ? 1 : 0;
-                    }
-                    // the frontier: every index of this step was tested; the farthest jump extends the known-empty range
-                    const bool over = cnt + total > S; // (uniform in the group)
-                    int32_t v = over ? -stop : (dist >= 2 ? k0 + STEPS + (int32_t)fmaxf(floorf((float)(dist - 1) * ro[3] - rd[3]), 0.0f) : 0); // (SkipJump::jump)
-                    for (int w = P; w < KN_WAVE; w <<= 1) v = max(v, __shfl_xor(v, w, KN_WAVE));
-                    k = over ? -v : max(k + G * STEPS, v);
-                    cnt = min(cnt + total, S);
-                  }
-                }
-            }
+            for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * (lane >> 4));
+            bias_out = *(const f4 *)(tail + H);
         }
-        wave_sync();
-
-        // ---- evaluate: one network after the other
-        keep_denormals(false);
+        // density row and colour rows side by side (they are disjoint rows, repeated with period four: every lane group
+        // computes the four values of a sample, and group u keeps those of sample tile u)
+        __device__ __forceinline__ void arrived()
         {
-            const ArgsPtr a = opaque(args);
-            const int ln = opaque(lane), n = ln & 15, g = ln >> 4;
-            const unsigned m3 = (g == 3) ? 0xffffffffu : 0u;
-            const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-            // which word of a sample's slot each of a lane's three restart angles comes from, and its scale (see k_mlp_mfma)
-            const int wo0 = g < 3 ? g : 0, wo1 = g < 3 ? g : 1, wo2 = g < 3 ? g : 2;
-            const float f0 = g < 3 ? INV_2PI : 256.0f * INV_2PI, f1 = g < 3 ? 4.0f * INV_2PI : 256.0f * INV_2PI,
-                        f2_ = g < 3 ? 16.0f * INV_2PI : 256.0f * INV_2PI;
-            const float step = a->p.step;
-            // the networks of the slots a lane looks after, ln + 64 q (they are its own ray's)
-            uint32_t nq[NQ];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) nq[q] = (ln >> lgP) + q * G < cnt ? (uint32_t)idx[ln + KN_WAVE * q] : 0xffffffffu;
-            __builtin_amdgcn_wave_barrier();
-            for (;;) {
-                uint32_t mine = 0xffffffffu;
-#pragma unroll
-                for (int q = NQ - 1; q >= 0; --q) mine = nq[q] != 0xffffffffu ? nq[q] : mine;
-                const unsigned long long pending = __ballot(mine != 0xffffffffu);
-                if (pending == 0ull) break;
-                const int32_t sel = __builtin_amdgcn_readlane((int)mine, (int)__builtin_ctzll(pending));
-                // (weights are not kept across rounds: the march needs the registers)
-                u4 areg[NBLK], a_out[HK];
-                f4 bias2[HT], bias_out;
-                const u4 *__restrict__ wp = (const u4 *)(a->packed + (int64_t)sel * L::HALFS);
-#pragma unroll
-                for (int b = 0; b < NBLK; ++b) areg[b] = wp[b * KN_WAVE + ln];
-                const float *__restrict__ tail = (const float *)(wp + NBLK * KN_WAVE);
-#pragma unroll
-                for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
-                bias_out = *(const f4 *)(tail + H);
-                int c = 0;
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    const bool hit = nq[q] == (uint32_t)sel;
-                    const unsigned long long b = __ballot(hit);
-                    if (hit) {
-                        idx[c + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u))] = (uint16_t)(ln + KN_WAVE * q);
-                        nq[q] = 0xffffffffu;
-                    }
-                    c += __popcll(b);
-                }
-                wave_sync();
-                // density row and colour rows side by side (they are disjoint rows, repeated with period four: every lane group
-                // computes the four values of a sample, and group u keeps those of sample tile u)
-#pragma unroll
-                for (int kb = 0; kb < HK; ++kb) a_out[kb] = areg[L::LS + kb] | areg[L::L5 + kb];
-                for (int t0 = 0; t0 < c; t0 += KN_WAVE) {
-                    const int len = min(KN_WAVE, c - t0);
-                    f4 out = zero4; // pre-activations (r, g, b, sigma) of sample ln of the tile
-                    auto sample_tile = [&](int u) {
-                        f4 o_sig = bias_out, o_col = bias_out;
-                        const int i = idx[min(t0 + 16 * u + n, c - 1)];
-                        const float *sp = (const float *)(slots + i);
-                        const float v0 = sp[wo0], v1 = sp[wo1], v2 = sp[wo2];
-                        const f4 ang = {v0 * f0, v1 * f1, v2 * f2_, 0.0f};
-                        const u4 ident = {pk<BF>(v0, v1), pk<BF>(v2, 1.0f), 0u, 0u}; // (group 3: v0..v2 are x, y, z)
-                        u4 Bx[2];
-                        encode_position<BF, WRAP>(ang, ident, m3, Bx);
-                        const u4 Bd = dirs[4 * (i & (P - 1)) + g];
-                        f4 acc[HT];
-                        u4 Bh[HK];
-#pragma unroll
-                        for (int t = 0; t < HT; ++t) {
-                            acc[t] = mfma<BF>(areg[L::L1 + 2 * t], Bx[0], zero4);
-                            acc[t] = mfma<BF>(areg[L::L1 + 2 * t + 1], Bx[1], acc[t]);
-                        }
-                        pack_acts<H, BF, true>(acc, Bh);
-#pragma unroll
-                        for (int t = 0; t < HT; ++t) {
-                            acc[t] = bias2[t];
-#pragma unroll
-                            for (int kb = 0; kb < HK; ++kb) acc[t] = mfma<BF>(areg[L::L2 + t * HK + kb], Bh[kb], acc[t]);
-                        }
-                        pack_acts<H, BF, true>(acc, Bh);
-#pragma unroll
-                        for (int kb = 0; kb < HK; ++kb) o_sig = mfma<BF>(a_out[kb], Bh[kb], o_sig);
-#pragma unroll
-                        for (int t = 0; t < HT; ++t) {
-                            acc[t] = mfma<BF>(areg[L::L4 + t * (HK + 1) + HK], Bd, zero4);
-#pragma unroll
-                            for (int kb = 0; kb < HK; ++kb) acc[t] = mfma<BF>(areg[L::L4 + t * (HK + 1) + kb], Bh[kb], acc[t]);
-                        }
-                        pack_acts<H, BF, true>(acc, Bh);
-#pragma unroll
-                        for (int kb = 0; kb < HK; ++kb) o_col = mfma<BF>(a_out[kb], Bh[kb], o_col);
-                        out = g == u ? (f4){o_col[0], o_col[1], o_col[2], o_sig[3]} : out;
-                    };
-                    // (two sample tiles side by side wherever two are there; uniform branches)
-                    if (len > 16) { sample_tile(0); sample_tile(1); }
-                    else sample_tile(0);
-                    if (len > 48) { sample_tile(2); sample_tile(3); }
-                    else if (len > 32) sample_tile(2);
-                    if (ln < len) { // lane l holds sample l of the tile; its result takes the place of its position
-                        const int i = idx[t0 + ln];
-                        float sg = fmaxf(out[3], 0.0f);
-                        if constexpr (STRAT) sg *= slots[i][3];
-                        f4 res;
-#pragma unroll
-                        for (int q = 0; q < 3; ++q)
-                            res[q] = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * out[q]));
-                        res[3] = 1.0f - expf(-sg * step); // alpha (Eq. 4)
-                        slots[i] = res;
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
+            for (int kb = 0; kb < HK; ++kb) a_out[kb] = areg[L::LS + kb] | areg[L::L5 + kb];
         }
-        wave_sync();
+    };
 
-        // ---- blend (Eq. 2-4): the sequential recurrence, the same in all lanes of a ray's group
-        keep_denormals(true);
-        {
-            const ArgsPtr a = opaque(args);
-            const int ln = opaque(lane), slot = ln & (P - 1), gl = ln >> lgP;
-            const float eps = a->eps;
-            int used = 0;
-            if (ray >= 0) {
-                bool dead = false;
-                for (int j = 0; j < cnt && !dead; ++j) {
-                    const f4 q = slots[(j << lgP) + slot];
-                    const float wgt = T * q[3];
-                    c0 = fmaf(wgt, q[0], c0);
-                    c1 = fmaf(wgt, q[1], c1);
-                    c2 = fmaf(wgt, q[2], c2);
-                    T *= (1.0f - q[3]);
-                    ++used;
-                    dead = eps > 0.0f && T < eps;
-                }
-                if (dead || k >= k_hi) {
-                    if (gl == 0) {
-                        float *px = a->rgb_out + 3 * (int64_t)ray;
-                        px[0] = fmaf(T, a->bg[0], c0);
-                        px[1] = fmaf(T, a->bg[1], c1);
-                        px[2] = fmaf(T, a->bg[2], c2);
-                    }
-                    ray = -1;
-                }
-            }
-            if (a->counters) { // (uniform)
-                evaluated += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(gl == 0 ? cnt : 0), KN_WAVE - 1);
-                blended += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(gl == 0 ? used : 0), KN_WAVE - 1);
-            }
-        }
-        keep_denormals(false);
-        __builtin_amdgcn_wave_barrier(); // the slots are rewritten by the next round
+    // which word of a sample's slot each of a lane's three restart angles comes from, and its scale (see k_mlp_mfma)
+    int n, g, wo0, wo1, wo2;
+    unsigned m3;
+    float f0, f1, f2_;
+    __device__ __forceinline__ explicit Net16(int lane) : n(lane & 15), g(lane >> 4)
+    {
+        m3 = (g == 3) ? 0xffffffffu : 0u;
+        wo0 = g < 3 ? g : 0;
+        wo1 = g < 3 ? g : 1;
+        wo2 = g < 3 ? g : 2;
+        f0 = g < 3 ? INV_2PI : 256.0f * INV_2PI;
+        f1 = g < 3 ? 4.0f * INV_2PI : 256.0f * INV_2PI;
+        f2_ = g < 3 ? 16.0f * INV_2PI : 256.0f * INV_2PI;
     }
-    if (args->counters && lane == 0) {
-        atomicAdd(&args->counters[0], (unsigned long long)evaluated);
-        atomicAdd(&args->counters[1], (unsigned long long)blended);
+
+    // pre-activations (r, g, b, sigma) of sample `lane` of a tile of len samples; slot(j): the slot of the tile's sample j
+    template <typename Slot>
+    __device__ __forceinline__ f4 evaluate(const Weights &w, int, int len, Slot slot, const f4 *slots, const u4 *dirs, const f4 *, int P) const
+    {
+        const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+        f4 out = zero4;
+        auto sample_tile = [&](int u) {
+            f4 o_sig = w.bias_out, o_col = w.bias_out;
+            const int i = slot(16 * u + n);
+            const float *sp = (const float *)(slots + i);
+            const float v0 = sp[wo0], v1 = sp[wo1], v2 = sp[wo2];
+            const f4 ang = {v0 * f0, v1 * f1, v2 * f2_, 0.0f};
+            const u4 ident = {pk<BF>(v0, v1), pk<BF>(v2, 1.0f), 0u, 0u}; // (group 3: v0..v2 are x, y, z)
+            u4 Bx[2];
+            encode_position<BF, WRAP>(ang, ident, m3, Bx);
+            const u4 Bd = dirs[4 * (i & (P - 1)) + g];
+            f4 acc[HT];
+            u4 Bh[HK];
+#pragma unroll
+            for (int t = 0; t < HT; ++t) {
+                acc[t] = mfma<BF>(w.areg[L::L1 + 2 * t], Bx[0], zero4);
+                acc[t] = mfma<BF>(w.areg[L::L1 + 2 * t + 1], Bx[1], acc[t]);
+            }
+            pack_acts<H, BF, true>(acc, Bh);
+#pragma unroll
+            for (int t = 0; t < HT; ++t) {
+                acc[t] = w.bias2[t];
+#pragma unroll
+                for (int kb = 0; kb < HK; ++kb) acc[t] = mfma<BF>(w.areg[L::L2 + t * HK + kb], Bh[kb], acc[t]);
+            }
+            pack_acts<H, BF, true>(acc, Bh);
+#pragma unroll
+            for (int kb = 0; kb < HK; ++kb) o_sig = mfma<BF>(w.a_out[kb], Bh[kb], o_sig);
+#pragma unroll
+            for (int t = 0; t < HT; ++t) {
+                acc[t] = mfma<BF>(w.areg[L::L4 + t * (HK + 1) + HK], Bd, zero4);
+#pragma unroll
+                for (int kb = 0; kb < HK; ++kb) acc[t] = mfma<BF>(w.areg[L::L4 + t * (HK + 1) + kb], Bh[kb], acc[t]);
+            }
+            pack_acts<H, BF, true>(acc, Bh);
+#pragma unroll
+            for (int kb = 0; kb < HK; ++kb) o_col = mfma<BF>(w.a_out[kb], Bh[kb], o_col);
+            out = g == u ? (f4){o_col[0], o_col[1], o_col[2], o_sig[3]} : out;
+        };
+        // (two sample tiles side by side wherever two are there; uniform branches)
+        if (len > 16) { sample_tile(0); sample_tile(1); }
+        else sample_tile(0);
+        if (len > 48) { sample_tile(2); sample_tile(3); }
+        else if (len > 32) sample_tile(2);
+        return out;
     }
-}
+    static __device__ __forceinline__ float sigmoid(float v) { return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * v)); }
+};
 
 } // namespace
 
 // The kernel's voxel, block and cell numbers are formed with 24-bit multiplications, and it keeps a sample's network in
-// 16 bits.
+// 16 bits.  fp32 networks of width 64, and those whose layers are kept apart, are the wave loop's.
 bool kn_fused_supports(const kn_scene *sc)
 {
-    if (sc->desc.wdtype == KN_F32 || sc->N > 65536) return false;
+    if (sc->N > 65536 || (sc->desc.wdtype == KN_F32 && (sc->f32_apart || sc->desc.hidden != 32))) return false;
     auto fits = [](const int32_t r[3]) {
         constexpr int64_t lim = 1ll << 24;
         return (int64_t)r[0] * r[1] <= lim && r[0] < lim && r[1] < lim && r[2] < lim;
@@ -704,74 +141,29 @@ bool kn_fused_supports(const kn_scene *sc)
     return fits(sc->net_grid.res) && (!sc->has_occ || fits(sc->skip_res));
 }
 
-using FusedFn = decltype(&k_render_fused<32, false, false, false>);
-static const FusedFn fused_table[2][2][2][2] = {
-    {{{k_render_fused<32, false, false, false>, k_render_fused<32, false, false, true>},
-      {k_render_fused<32, false, true, false>, k_render_fused<32, false, true, true>}},
-     {{k_render_fused<32, true, false, false>, k_render_fused<32, true, false, true>},
-      {k_render_fused<32, true, true, false>, k_render_fused<32, true, true, true>}}},
-    {{{k_render_fused<64, false, false, false>, k_render_fused<64, false, false, true>},
-      {k_render_fused<64, false, true, false>, k_render_fused<64, false, true, true>}},
-     {{k_render_fused<64, true, false, false>, k_render_fused<64, true, false, true>},
-      {k_render_fused<64, true, true, false>, k_render_fused<64, true, true, true>}}}};
-
-// a workgroup's LDS is above the default limit of dynamic LDS (once per device, from kn_create)
 int kn_fused_configure()
 {
-    for (int i = 0; i < 16; ++i) {
-        const int bytes = ((i & 8) ? Pool<64>::MAX_WAVES * (int)sizeof(WaveLds<64>) : Pool<32>::MAX_WAVES * (int)sizeof(WaveLds<32>)) +
-                          OWN_RAYS_MAX * (int)sizeof(int4);
-        KN_HIP(hipFuncSetAttribute((const void *)fused_table[i >> 3][(i >> 2) & 1][(i >> 1) & 1][i & 1], hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-    }
-    return KN_OK;
+    KN_TRY((fused_configure<Net16<32, false, false>>()));
+    KN_TRY((fused_configure<Net16<32, false, true>>()));
+    KN_TRY((fused_configure<Net16<32, true, false>>()));
+    KN_TRY((fused_configure<Net16<32, true, true>>()));
+    KN_TRY((fused_configure<Net16<64, false, false>>()));
+    KN_TRY((fused_configure<Net16<64, false, true>>()));
+    KN_TRY((fused_configure<Net16<64, true, false>>()));
+    KN_TRY((fused_configure<Net16<64, true, true>>()));
+    return kn_fused_f32_configure();
 }
 
 int kn_fused_launch(const kn_scene *sc, hipStream_t st, const KnFusedJob &job, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
-    const int H = sc->desc.hidden;
-    const bool bf = sc->desc.wdtype == KN_BF16;
-    FusedArgs a;
-    a.p = *(const MarchParams *)job.march;
-    a.net = voxel_fast(a.p.net);
-    a.vox = voxel_fast(a.p.occ);
-    a.packed = (const uint16_t *)sc->packed_w;
-    a.rays_o = job.rays_o;
-    a.rays_d = job.rays_d;
-    a.list = job.list;
-    a.R = (int32_t)job.R;
-    a.ctl = job.ctl;
-    a.eps = job.eps;
-    for (int c = 0; c < 3; ++c) a.bg[c] = job.bg[c];
-    a.rgb_out = job.rgb_out;
-    a.counters = job.counters;
+    if (sc->desc.wdtype == KN_F32) return kn_fused_f32_launch(sc, st, job, ev_start, ev_stop);
     float reach = 0.0f; // (see the launch of k_mlp_mfma)
     for (int c = 0; c < 3; ++c) reach = fmaxf(reach, fmaxf(fabsf(sc->desc.aabb_min[c]), fabsf(sc->desc.aabb_max[c])));
     const bool wrap = !(reach * (256.0f * INV_2PI) < 250.0f);
-    // one workgroup per compute unit, of as many wavefronts as get four rays each, up to what a compute unit holds; a multiple of
-    // eight workgroups, for the shares of the XCDs
-    const int max_waves = H == 32 ? Pool<32>::MAX_WAVES : Pool<64>::MAX_WAVES;
-    const int64_t want = kn_div_up(job.R, 1 << Pool<32>::MIN_LG);
-    const int waves = (int)std::min<int64_t>(std::max<int64_t>(kn_div_up(want, 256), 4), max_waves);
-    const int64_t blocks = std::min<int64_t>(8 * kn_div_up(want, 8 * waves), 256);
-    // Full pools of many rays with few samples each where rays end after few samples, of half as many rays otherwise.  How many a ray
-    // takes depends on the scene; coarse lattices need fewer than fine ones.  Half / all, one frame each: 1424x1070, width 32, K = 32 (2^3
-    // networks) 294 / 268 us, K = 128 (16^3) 176 / 168, 800x800, K = 512, 169 / 182; width 64, 1424x1070, K = 64 (2^3) 580 / 390, K = 256 (8^3)
-    // 340 / 310, K = 512 (16^3) 460 / 457, 1080p, K = 1024, 1,051 / 1,110.
-    a.max_lg = H == 32 ? (a.p.K < 256 ? 5 : 4) : (a.p.K < 512 ? 6 : 5);
-    a.own_group = OWN_GROUP_MIN;
-    while (a.own_group < OWN_GROUP_MAX && job.R > 6 * 256 * (int64_t)a.own_group) a.own_group *= 2;
-    // With hardly two samples of a ray per network the weights' way to the wavefronts is what bounds a frame: there, and with enough
-    // rays for all compute units, four rays or more share what a wavefront loads (164x94, 1.2 samples per network, width 32 / 64: 93 -> 80 /
-    // 224 -> 172 us); elsewhere every wavefront gets a ray if there is one (100x100, 1.5 samples per network: 47 us, 62 with four).
-    const float points = fminf(a.p.net.cell[0], fminf(a.p.net.cell[1], a.p.net.cell[2])) / a.p.step;
-    a.few_rays = points < 2.0f && job.R > 12288 ? 4 : 1;
-    a.own_rays = job.list ? 0 : (int32_t)(a.own_group * kn_div_up(job.R, a.own_group * blocks));
-    const size_t lds = waves * (H == 32 ? sizeof(WaveLds<32>) : sizeof(WaveLds<64>)) + a.own_rays * sizeof(int4);
-    if (H != 32 && H != 64) return KN_E_UNSUPPORTED;
-    const FusedFn kernel = fused_table[H == 64][bf][wrap][job.strat ? 1 : 0];
-    const dim3 grid((unsigned)blocks), block(waves * KN_WAVE);
-    if (ev_start && ev_stop) hipExtLaunchKernelGGL(kernel, grid, block, lds, st, ev_start, ev_stop, 0, a);
-    else hipLaunchKernelGGL(kernel, grid, block, lds, st, a);
-    KN_CHECK_LAUNCH();
-    return KN_OK;
+    using Launch = decltype(&fused_launch<Net16<32, false, false>>);
+    static const Launch table[2][2][2] = {
+        {{fused_launch<Net16<32, false, false>>, fused_launch<Net16<32, false, true>>}, {fused_launch<Net16<32, true, false>>, fused_launch<Net16<32, true, true>>}},
+        {{fused_launch<Net16<64, false, false>>, fused_launch<Net16<64, false, true>>}, {fused_launch<Net16<64, true, false>>, fused_launch<Net16<64, true, true>>}}};
+    if (sc->desc.hidden != 32 && sc->desc.hidden != 64) return KN_E_UNSUPPORTED;
+    return table[sc->desc.hidden == 64][sc->desc.wdtype == KN_BF16][wrap](sc, st, job, ev_start, ev_stop);
 }

@@ -39,41 +39,15 @@
 // of the double-angle recurrence in between; all in fp32.
 #include "kn_common.h"
 #include "kn_direct.h"
+#include "kn_mlp_f32_core.h"
 #include "kn_mlp_shared.h"
 #include <hip/hip_ext.h>
 #include "kn_probe.h"
 
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-
 constexpr int F32_WAVES = 4;
 constexpr int F32_TILE_LEN = 64;
-
-__device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-
-__device__ __forceinline__ void double_angle(float s, float c, float &s2, float &c2)
-{
-    s2 = 2.0f * (s * c);
-    c2 = fmaf(-2.0f * s, s, 1.0f);
-}
-
-// Register file image of one network: register r of lane l sits at packed[(net * N + r) * 64 + l].
-template <int H> struct Regs {
-    static constexpr int HT = H / 16, HQ = H / 4;
-    static constexpr int W1 = 0;                     // (t, q)  -> W1 + 16 t + q
-    static constexpr int W2 = W1 + 16 * HT;          // (t, k)  -> W2 + HQ t + k
-    static constexpr int W4 = W2 + HQ * HT;          // (t, k)  -> W4 + (HQ + 8) t + k; k < HQ: folded with the feature layer; k >= HQ: gamma(d)
-    static constexpr int WO = W4 + (HQ + 8) * HT;    // (c, k)  -> WO + HQ c + k: colour c (c < 3) / density, hidden unit k of the lane group
-    static constexpr int B2 = WO + 4 * HQ;           // (t, j): accumulator initial values of this lane
-    static constexpr int BO = B2 + 4 * HT;
-    static constexpr int W3 = BO + 4;                // (t, k)  -> W3 + HQ t + k: feature rows, (t, j) -> B3 + 4 t + j: their biases;
-    static constexpr int B3 = W3 + HQ * HT;          // both only where the feature layer is kept apart
-    static constexpr int N = B3 + 4 * HT;
-    // canonical offsets (Sec. 3.2: five layers, weights before biases)
-    static constexpr int oW1 = 0, ob1 = 63 * H, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H, ob3 = oW3 + H * (H + 1),
-                         oW4 = ob3 + H + 1, ob4 = oW4 + (H + 27) * H, oW5 = ob4 + H, ob5 = oW5 + 3 * H;
-};
 
 // canonical index of the value in register r of lane `lane`; -1 = zero (or, with FOLD, an element of the product of feature
 // layer and layer 4 or of its bias, which the packing kernel forms)
@@ -256,158 +230,20 @@ __global__ void __launch_bounds__((PACK_WAVES<H> + FOLD) * KN_WAVE)
             }
     }
 }
-// one network's weights in registers
-template <int H, bool FOLD> struct NetF32 {
-    using R = Regs<H>;
-    static constexpr int HT = H / 16, HQ = H / 4; // output tiles per layer, MFMAs per hidden input vector
-    float w1[HT][16], w2[HT][HQ], w4[HT][HQ + 8], wo[4][HQ];
-    float w3[FOLD ? 1 : HT][HQ]; // (FOLD: not there)
-    f4 bias2[HT], bias3[FOLD ? 1 : HT], bias_out;
-    __device__ __forceinline__ void load(const float *__restrict__ packed, int32_t net, int lane)
+// what a wavefront has staged of a chunk: x, y, z, dx, dy, dz per sample
+struct Staged {
+    const float (*stage)[8];
+    __device__ __forceinline__ void operator()(int j, float (&p)[3], float (&d)[3]) const
     {
-        const float *__restrict__ wp = packed + (int64_t)net * (R::N * KN_WAVE) + lane;
-        auto reg = [&](int r) { return wp[r * KN_WAVE]; };
-#pragma unroll
-        for (int t = 0; t < HT; ++t) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) w1[t][q] = reg(R::W1 + 16 * t + q);
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) w2[t][k] = reg(R::W2 + HQ * t + k);
-#pragma unroll
-            for (int k = 0; k < HQ + 8; ++k) w4[t][k] = reg(R::W4 + (HQ + 8) * t + k);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bias2[t][j] = reg(R::B2 + 4 * t + j);
-            if constexpr (!FOLD) {
-#pragma unroll
-                for (int k = 0; k < HQ; ++k) w3[t][k] = reg(R::W3 + HQ * t + k);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) bias3[t][j] = reg(R::B3 + 4 * t + j);
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) wo[c][k] = reg(R::WO + HQ * c + k);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bias_out[j] = reg(R::BO + j);
+        const f4 s0 = *(const f4 *)&stage[j][0], s1 = *(const f4 *)&stage[j][4];
+        p[0] = s0[0];
+        p[1] = s0[1];
+        p[2] = s0[2];
+        d[0] = s0[3];
+        d[1] = s1[0];
+        d[2] = s1[1];
     }
 };
-
-// sum over the four lane groups, in all of them
-__device__ __forceinline__ float sum_groups(float v)
-{
-    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    const float h = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(h), __float_as_uint(h), false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
-// n_tiles sample tiles (16 u .. 16 u + 15, u < n_tiles <= 4) of a staged chunk; lane l returns the pre-activations
-// (r, g, b, sigma) of sample l
-template <int H, bool FOLD> __device__ __forceinline__ f4 eval_chunk(const NetF32<H, FOLD> &w, const float (*stage)[8], int lane, int n_tiles)
-{
-    constexpr int HT = H / 16, HQ = H / 4;
-    const int n = lane & 15, g = lane >> 4;
-    const bool g3 = g == 3;
-    const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    f4 out = zero4;
-#pragma unroll 1
-    for (int u = 0; u < n_tiles; ++u) {
-        __builtin_amdgcn_s_setprio(0);
-        const f4 s0 = *(const f4 *)&stage[16 * u + n][0];
-        const f4 s1 = *(const f4 *)&stage[16 * u + n][4];
-        const float p[3] = {s0[0], s0[1], s0[2]}, d[3] = {s0[3], s1[0], s1[1]};
-        const float pg = g == 0 ? p[0] : (g == 1 ? p[1] : p[2]);
-        const float dg = g == 0 ? d[0] : (g == 1 ? d[1] : d[2]);
-        // three accurate evaluations per lane; groups 0..2: axis g at frequencies 0 and 4 and the direction at 0,
-        // group 3: the three axes at frequency 8
-        const float ang[3] = {g3 ? 256.0f * p[0] : pg, g3 ? 256.0f * p[1] : 16.0f * pg, g3 ? 256.0f * p[2] : dg};
-        float cs[3][4], cc[3][4];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            sincosf(ang[c], &cs[c][0], &cc[c][0]);
-#pragma unroll
-            for (int k = 1; k < 4; ++k) double_angle(cs[c][k - 1], cc[c][k - 1], cs[c][k], cc[c][k]);
-        }
-        float enc[16], dirv[8];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int f = q >> 1;
-            const float axis_v = (q & 1) ? cc[f >> 2][f & 3] : cs[f >> 2][f & 3];
-            const float g3_v = q < 12 ? ((q & 1) ? cc[q >> 2][(q >> 1) & 1] : cs[q >> 2][(q >> 1) & 1])
-                                      : (q < 15 ? p[q >= 12 && q < 15 ? q - 12 : 0] : 1.0f);
-            enc[q] = g3 ? g3_v : axis_v;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const float axis_v = (q & 1) ? cc[2][q >> 1] : cs[2][q >> 1];
-            const float g3_v = q < 3 ? d[q < 3 ? q : 0] : (q == 3 ? 1.0f : 0.0f);
-            dirv[q] = g3 ? g3_v : axis_v;
-        }
-        __builtin_amdgcn_s_setprio(1); // the other wavefront of the SIMD encodes under these: 650 -> 630 us for 4 M points
-        f4 acc[HT], h[HT];
-        // layer 1: gamma(x) -> H, ReLU
-#pragma unroll
-        for (int t2 = 0; t2 < HT; ++t2) {
-            acc[t2] = zero4;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[t2] = mfma4(w.w1[t2][q], enc[q], acc[t2]);
-        }
-#pragma unroll
-        for (int t2 = 0; t2 < HT; ++t2)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-        // layer 2: H -> H, ReLU
-#pragma unroll
-        for (int t2 = 0; t2 < HT; ++t2) {
-            acc[t2] = w.bias2[t2];
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w.w2[t2][k], h[k >> 2][k & 3], acc[t2]);
-        }
-#pragma unroll
-        for (int t2 = 0; t2 < HT; ++t2)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-        // layer 3: the density; its feature vector is folded into layer 4, or takes the second hidden vector's place
-        f4 o = zero4;
-#pragma unroll
-        for (int k = 0; k < HQ; ++k) o[3] = fmaf(w.wo[3][k], h[k >> 2][k & 3], o[3]);
-        if constexpr (!FOLD) {
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2) {
-                acc[t2] = w.bias3[t2];
-#pragma unroll
-                for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w.w3[t2][k], h[k >> 2][k & 3], acc[t2]);
-            }
-#pragma unroll
-            for (int t2 = 0; t2 < HT; ++t2) h[t2] = acc[t2];
-        }
-        // layer 4: [second hidden vector through the folded feature layer (or the features), gamma(d)] -> H, ReLU
-#pragma unroll
-        for (int t2 = 0; t2 < HT; ++t2) {
-            acc[t2] = zero4;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc[t2] = mfma4(w.w4[t2][HQ + q], dirv[q], acc[t2]);
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w.w4[t2][k], h[k >> 2][k & 3], acc[t2]);
-        }
-#pragma unroll
-        for (int t2 = 0; t2 < HT; ++t2)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-        // layer 5: H -> colour
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) o[c] = fmaf(w.wo[c][k], h[k >> 2][k & 3], o[c]);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float v = sum_groups(o[c]) + w.bias_out[c];
-            out[c] = g == u ? v : out[c];
-        }
-    }
-    return out;
-}
 
 template <int H, bool FOLD>
 __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 2 : 1, H == 32 ? 2 : 1)))
@@ -457,7 +293,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-        const f4 out = eval_chunk<H, FOLD>(w, stage[wave], lane, (tl.len + 15) >> 4); // (a small group needs no empty sample tiles)
+        const f4 out = eval_chunk<H, FOLD>(w, lane, (tl.len + 15) >> 4, Staged{stage[wave]}); // (a small group needs no empty sample tiles)
         __builtin_amdgcn_wave_barrier(); // the staging buffer is rewritten by the next iteration
 
         if (lane < tl.len) {
@@ -509,7 +345,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const f4 out = eval_chunk<H, FOLD>(w, stage[wave], lane, (c + 15) / 16);
+        const f4 out = eval_chunk<H, FOLD>(w, lane, (c + 15) / 16, Staged{stage[wave]});
         if (lane < c) {
             const int64_t to = first + __float_as_int(stage[wave][lane][6]);
             job.sigma[to] = fmaxf(out[3], 0.0f);

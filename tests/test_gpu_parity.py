@@ -1665,6 +1665,38 @@ def test_render_in_one_kernel_equals_the_wave_loop(wdtype, H, rays, res, occ, or
     assert torch.equal(fused, waves) and (rays < 1000 or st["samples_blended"] > rays)
 
 
+@pytest.mark.parametrize("rays,res,occ,keep,eps", [
+    (1, (16, 16, 16), "nested", None, 0.01), (4097, (5, 8, 5), "odd", None, 0.01), (8191, (16, 16, 16), "nested", None, 0.0),
+    (12289, (16, 16, 16), "none", None, 0.01), (32767, (16, 16, 16), "nested", 0.6, 0.01), (32768, (8, 8, 8), "nested", None, 0.01),
+    (150001, (8, 8, 8), "nested", None, 0.01)])
+@pytest.mark.parametrize("seed", [None, 7])
+def test_fp32_render_in_one_kernel_equals_the_wave_loop(rays, res, occ, keep, eps, seed):
+    """Bit for bit, width 32: frames with their set-up inside and behind a list, more rays than the first pools hold, grids that nest,
+    do not nest, are sparse or absent.  (The timers say that the plain call marched in no kernel of its own.)"""
+    import torch
+    import paper_2103_13744_amd as kn
+    cfg = configs.config3(64, 64)
+    grid = {"nested": cfg["scene"]["occupancy"], "odd": ks.blob_occupancy((50, 45, 61), 12, 0.15, 5), "none": None}[occ]
+    sc = scene_dict(res, (-1, -1, -1), (1, 1, 1), 32, "f32", 13, occ=grid, sigma_scale=60.0)
+    if keep is not None:
+        sc = configs.sparsify(sc, np.random.default_rng(8).random(int(np.prod(res))) < keep, 9)
+    dev, _ = make_pair(sc)
+    pick = torch.arange(rays) % len(cfg["rays_o"])
+    o, d = torch.from_numpy(cfg["rays_o"])[pick].cuda(), torch.from_numpy(cfg["rays_d"])[pick].cuda()
+    args = (cfg["t_near"], cfg["step"], cfg["K"], eps, cfg["bg"])
+    waves, st = dev.render(o, d, *args, want_stats=True, seed=seed)
+    assert rays < 1000 or st["samples_blended"] > rays
+    for _ in range(2):
+        assert torch.equal(dev.render(o, d, *args, seed=seed), waves)
+    kn.profile_enable(1)
+    try:
+        kn.profile_read()
+        assert torch.equal(dev.render(o, d, *args, seed=seed), waves)
+        assert kn.profile_read()["ms_march"] == 0.0
+    finally:
+        kn.profile_enable(0)
+
+
 @pytest.mark.parametrize("wdtype,H,rays", [
     ("f16", 32, 33), ("bf16", 32, 4097), ("f16", 64, 5121), ("f16", 32, 7200), ("bf16", 32, 13313),  # workgroups of 4, 5, 8, 14 wavefronts
     ("f16", 32, 65536), ("bf16", 32, 65537), ("f16", 32, 65536 + 16), ("f16", 32, 180003),          # first pools just full; chunks of the list
