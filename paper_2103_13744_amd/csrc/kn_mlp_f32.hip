@@ -148,7 +148,7 @@ __device__ bool fold_leaves_range(const float *__restrict__ src, const float *w3
 // sets `apart` where the product may not be used.
 // Bound by the latency of its few trips to memory on small scenes, by memory traffic on large ones.
 // Against a thread per element that sums its own product over global memory (which made no bound), creating a scene of 16^3
-// networks: width 32 105 -> 71 us (this kernel 50, 232 MB), width 64 469 -> 210 (189, 628 MB); 32^3 931 -> 444 and 3,572 ->
+// networks: width 32 105 -> 66 us (this kernel 45, 232 MB), width 64 469 -> 195 (174, 628 MB); 32^3 931 -> 442 and 3,572 ->
 // 1,447; 2^3 24 -> 29 and 25 -> 36 (the bound's chain of layers, and the wait for it).
 template <int H> constexpr int PACK_WAVES = H == 32 ? 4 : 8;
 template <int H, bool FOLD>
@@ -182,26 +182,38 @@ __global__ void __launch_bounds__((PACK_WAVES<H> + FOLD) * KN_WAVE)
                 double acc = (double)src[R::ob4 + lane];
 #pragma unroll 16
                 for (int f = 0; f < H; ++f) acc = fma((double)src[R::ob3 + 1 + f], (double)s_w4[f * H + lane], acc);
-                image[(R::W4 + (HQ + 8) * (lane >> 4) + HQ + 3) * KN_WAVE + 48 + (lane & 15)] = (float)acc;
+                image[image_at<H>(R::W4 + (HQ + 8) * (lane >> 4) + HQ + 3, 48 + (lane & 15))] = (float)acc;
             }
             const bool out_of_range = fold_leaves_range<H>(src, s_w3, s_w4, reach, lane, s_h, s_moved);
             if (__ballot(out_of_range) != 0ull && lane == 0) __hip_atomic_store(apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             return;
         }
     }
-    constexpr int LAST = FOLD ? R::W3 : R::N, BATCH = 16; // registers whose loads are in flight together
-    for (int r0 = wave; r0 < LAST; r0 += WAVES * BATCH) {
-        int at[BATCH];
-        float v[BATCH];
+    constexpr int LAST = (FOLD ? R::W3 : R::N) / 4, BATCH = 3; // groups of four registers, and how many groups' loads are in flight together
+    for (int g0 = wave; g0 < LAST; g0 += WAVES * BATCH) {
+        int at[BATCH][4];
+        f4 v[BATCH];
 #pragma unroll
-        for (int q = 0; q < BATCH; ++q) at[q] = reg_source<H, FOLD>(min(r0 + WAVES * q, LAST - 1), lane);
+        for (int q = 0; q < BATCH; ++q)
 #pragma unroll
-        for (int q = 0; q < BATCH; ++q) v[q] = src[max(at[q], 0)];
+            for (int j = 0; j < 4; ++j) at[q][j] = reg_source<H, FOLD>(4 * min(g0 + WAVES * q, LAST - 1) + j, lane);
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[q][j] = src[max(at[q][j], 0)];
 #pragma unroll
         for (int q = 0; q < BATCH; ++q) {
-            const int r = r0 + WAVES * q, k = r >= R::W4 && r < R::WO ? (r - R::W4) % (HQ + 8) : -1;
-            // (FOLD: elements of the product and its bias are written elsewhere)
-            if (r < LAST && !(FOLD && ((k >= 0 && k < HQ) || (k == HQ + 3 && lane >= 48)))) image[r * KN_WAVE + lane] = at[q] < 0 ? 0.0f : v[q];
+            const int r = 4 * (g0 + WAVES * q), k = r >= R::W4 && r < R::WO ? (r - R::W4) % (HQ + 8) : -1;
+            if (r >= 4 * LAST || (FOLD && k >= 0 && k < HQ)) continue; // (FOLD: elements of the product and its bias are written elsewhere)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[q][j] = at[q][j] < 0 ? 0.0f : v[q][j];
+            if (H == 64 || (FOLD && k == HQ && lane >= 48)) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (!(FOLD && k == HQ && j == 3 && lane >= 48)) image[image_at<H>(r + j, lane)] = v[q][j];
+            } else {
+                *(f4 *)&image[image_at<H>(r, lane)] = v[q];
+            }
         }
     }
     if constexpr (FOLD) { // thread: rows 4 kt .. + 3 of the product, columns ct + COLS c
@@ -222,12 +234,16 @@ __global__ void __launch_bounds__((PACK_WAVES<H> + FOLD) * KN_WAVE)
             }
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int c = 0; c < CT; ++c) { // hidden unit 4 kt + q is MFMA 4 (kt / 4) + q of lane group kt % 4
+            const int col = ct + COLS * c;
+            const int r = R::W4 + (HQ + 8) * (col >> 4) + 4 * (kt >> 2), lane = 16 * (kt & 3) + (col & 15);
+            if constexpr (H == 32) {
+                *(f4 *)&image[image_at<H>(r, lane)] = (f4){(float)acc[0][c], (float)acc[1][c], (float)acc[2][c], (float)acc[3][c]};
+            } else {
 #pragma unroll
-            for (int c = 0; c < CT; ++c) { // hidden unit 4 kt + q is MFMA 4 (kt / 4) + q of lane group kt % 4
-                const int col = ct + COLS * c;
-                image[(R::W4 + (HQ + 8) * (col >> 4) + 4 * (kt >> 2) + q) * KN_WAVE + 16 * (kt & 3) + (col & 15)] = (float)acc[q][c];
+                for (int q = 0; q < 4; ++q) image[image_at<H>(r + q, lane)] = (float)acc[q][c];
             }
+        }
     }
 }
 // what a wavefront has staged of a chunk: x, y, z, dx, dy, dz per sample
@@ -382,20 +398,15 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
     float w1[HT][16], w2[HT][HQ], wo[HQ], bias_sig = 0.0f;
     f4 bias2[HT];
     auto load_network = [&](int32_t net) {
-        const float *__restrict__ wp = packed + (int64_t)net * (R::N * KN_WAVE) + lane;
-        auto reg = [&](int r) { return wp[r * KN_WAVE]; };
+        const float *__restrict__ image = packed + (int64_t)net * (R::N * KN_WAVE);
 #pragma unroll
         for (int t = 0; t < HT; ++t) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) w1[t][q] = reg(R::W1 + 16 * t + q);
-#pragma unroll
-            for (int k = 0; k < HQ; ++k) w2[t][k] = reg(R::W2 + HQ * t + k);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bias2[t][j] = reg(R::B2 + 4 * t + j);
+            fetch_registers<H>(image, lane, R::W1 + 16 * t, w1[t], 16);
+            fetch_registers<H>(image, lane, R::W2 + HQ * t, w2[t], HQ);
+            bias2[t] = fetch_registers<H>(image, lane, R::B2 + 4 * t);
         }
-#pragma unroll
-        for (int k = 0; k < HQ; ++k) wo[k] = reg(R::WO + 3 * HQ + k);
-        bias_sig = reg(R::BO + 3);
+        fetch_registers<H>(image, lane, R::WO + 3 * HQ, wo, HQ);
+        bias_sig = image[image_at<H>(R::BO + 3, lane)];
     };
     int32_t net_loaded = -1;
 
