@@ -232,8 +232,8 @@ int kn_composite_deltas(void *stream, const float *sigma /*dev*/, const float *r
 /* The whole path (Sec. 3.1 Eq. 1-4, Sec. 3.2, Sec. 3.4): render R rays.
  * 16-bit scenes (of up to 65536 networks), and fp32 scenes of width 32, are rendered by one kernel, in larger frames behind
  * a short set-up, and the call reads nothing back, unless `stats` is given, the context has a wave schedule or option of its
- * own, or the frame is of a kind that waves render faster: then samples are taken in
- * waves from near to far; rays whose transmittance fell below term_eps, or that ran out of
+ * own, or the frame is of a kind that waves render faster (and not captured into a graph, where counts cannot be read
+ * back): then samples are taken in waves from near to far; rays whose transmittance fell below term_eps, or that ran out of
  * lattice points, drop out between waves.  The result per ray equals the sequential definition
  * (march, evaluate, blend, stop at T < term_eps) regardless of how waves are cut.
  * R*2^ceil(log2 K) must be <= 2^32, R times the slot budget per ray (kn_set_render_params; 128 unless set)

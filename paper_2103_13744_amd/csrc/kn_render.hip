@@ -1237,23 +1237,42 @@ extern "C" int kn_composite_deltas(void *stream, const float *sigma, const float
 
 // Where the fused kernel is the faster one.  It evaluates a wavefront's samples network by network and loads the network's weights
 // for each, so it needs several samples of a ray per network: the lattice points in a cell's edge say how many there are.
-// Both ways on 120 frames of 2,000 to 3.2 million rays (its time over the wave loop's; profiles/frames_one_kernel_against_waves.csv):
-//   up to 32,768 rays, which do not fill the wave loop's launches: 0.42 to 0.89 in 39 frames, 1.82 in one (1.2 points, 32^3 networks
-//   without an occupancy grid); few networks, whose weights stay in the caches: 0.42 to 0.52;
-//   width 32, from 5 points on: 0.42 to 0.82 (1.02 in one of 29); 2.5 to 5: 0.70 to 0.87, so that the line at 5 gives
-//   some away; below: 0.70 and 1.37;
-//   sparse grids: 8 to 16 points 0.77 to 0.87, 2.5 to 8 0.70 to 0.89 (the same), below 1.01 to 1.53;
-//   width 64, whose weights are three times as many bytes: from 16 points on 0.64 to 0.91, 8 to 16 0.97 (sparse 1.58), below 0.78 to 3.89;
-//   without early termination, where every sample is evaluated anyway and the wave loop's tiles are full: up to 8,192 rays 0.47 to
-//   0.72; beyond 0.57 to 1.92, with no rule found yet that separates them.
+// Its time over the wave loop's on 450 frames of 1,600 to 3.3 million rays (profiles/frames_one_kernel_against_waves.csv), where it is taken /
+// where it is not:
+//   up to 64 networks, whose weights stay in the caches: 0.25 to 0.94;
+//   content everywhere (no occupancy grid), a new network every few points from the ray's first point on: 16-bit width 32 0.22 to 0.95 / 0.98 to
+//   2.41 (at 4.6 points 0.93, up to 2.3 1.1 to 2.4, but in frames of millions of rays 0.22 to 0.30; 200 networks: never above 0.95); width 64
+//   0.38 to 0.61 / 0.49 to 3.81; fp32 0.70 to 0.88 / 1.00 to 3.75;
+//   up to 8,192 rays: 0.29 to 0.89 (1.03 in one of 45 frames);
+//   16-bit width 32: dense 0.33 to 0.90; sparse grids, where a ray has fewer samples of a network: 0.48 to 0.94 / 0.92 to 1.27;
+//   width 64, whose weights are three times as many bytes: 0.40 to 1.00 / 0.74 to 1.30, sparse 0.68 / 0.98 to 1.63;
+//   fp32 (width 32): 0.61 to 0.90 (1.09 in one of 24) / 0.78 to 1.50, sparse 0.87 to 0.90 / 0.96 to 1.29;
+//   without early termination, where every sample is evaluated anyway and the wave loop's tiles are full: 16-bit width 32 0.46 to 1.06 (above
+//   1 in 2 of 54) / 1.01, sparse 0.80 to 1.31; width 64 0.57 to 1.83, sparse 1.51 to 2.85; fp32 0.86 to 1.79, sparse 1.46 to 2.58.
 static bool fused_pays(const kn_scene *sc, int64_t R, float step, float term_eps)
 {
-    if (term_eps == 0.0f) return R <= 8192;
-    if (R <= 32768 || sc->N <= 64) return true;
+    if (sc->N <= 64) return true;
     const KnGrid &g = sc->net_grid;
     const float points = fminf(g.cell[0], fminf(g.cell[1], g.cell[2])) / step;
-    if (sc->desc.hidden == 64) return points >= 16.0f;
-    return sc->cell_net ? points >= 8.0f : points >= 5.0f || R >= (1ll << 19);
+    const bool fp32 = sc->desc.wdtype == KN_F32, narrow = !fp32 && sc->desc.hidden == 32, sparse = sc->cell_net != nullptr;
+    if (!sc->has_occ && !sparse) {
+        if (term_eps == 0.0f && R > 8192) return narrow && (sc->N <= 256 || points >= 4.0f);
+        if (narrow) return sc->N <= 256 || points >= 4.0f || R >= (1ll << 19);
+        return points >= (fp32 ? 6.0f : 4.0f);
+    }
+    if (R <= 8192) return true;
+    if (term_eps == 0.0f) return narrow && (R <= 32768 || (!sparse && points >= 4.0f));
+    if (narrow) return R <= 32768 || (sparse ? points >= 4.0f || R >= (1ll << 18) : points >= 2.0f || R >= (1ll << 19));
+    if (fp32) return points >= (sparse && R > 32768 ? 8.0f : 5.0f);
+    return points >= (R <= 32768 ? 3.0f : sparse ? 16.0f : 6.0f);
+}
+
+// A capture is running on the stream.
+static bool captured(hipStream_t st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
+    return status == hipStreamCaptureStatusActive;
 }
 
 static int render_fused(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, const MarchParams &p, const float *rays_o, const float *rays_d,
@@ -1332,11 +1351,24 @@ static int render_impl(kn_ctx *ctx, const kn_scene *sc, void *stream, const floa
     KnCarver ws(workspace, workspace_bytes);
     const MarchParams p = make_params(sc, t_near, step, K, seed);
     const int opt = march_options(sc, seed);
-    // Counts per wave and a schedule or limits set by the caller are the wave loop's.
-    if (!stats && knobs.is_default() && kn_fused_supports(sc) && fused_pays(sc, R, step, term_eps))
+    const int64_t budget = R * knobs.slots_per_ray;
+    int first_samples = knobs.first_wave_samples > 0 ? knobs.first_wave_samples : (K / 16 > DEFAULT_FIRST_WAVE ? K / 16 : DEFAULT_FIRST_WAVE);
+    if (first_samples > knobs.slots_per_ray) first_samples = knobs.slots_per_ray;
+    // With K slots for each of `rays` rays a wave takes every ray to its end, and nobody has to read how many are left
+    // (unless the caller wants the counters of this frame): the first wave where it takes K samples per ray, else the second.
+    const bool first_wave_ends = (int64_t)first_samples >= (int64_t)K && R * (int64_t)K <= budget;
+    auto second_wave_ends = [&](int64_t rays) {
+        return (int64_t)first_samples < (int64_t)K && rays * (int64_t)K <= budget && (int64_t)first_samples * knobs.wave_growth >= (int64_t)K;
+    };
+    // Small frames that end like that don't read the number of live rays either: their grids are sized for all rays, at most
+    // some hundred workgroups too many, where the host's look at the count leaves the GPU idle for longer.  64x64 rays, K = 32,
+    // fp32, 2^3 networks: 79 -> 37 us (both waits gone); 180x180, K = 128, width 64, 372 -> 369 (the grids' extra workgroups are
+    // no loss there either); 400x400, K = 48 (not taken, the first wave ends it) 270 -> 245.
+    const bool no_look = R <= BLIND_RAYS && (first_wave_ends || second_wave_ends(R));
+    // Counts per wave and a schedule or limits set by the caller are the wave loop's.  (A capture cannot read counts back.)
+    if (!stats && knobs.is_default() && kn_fused_supports(sc) && (fused_pays(sc, R, step, term_eps) || (!no_look && captured(st))))
         return render_fused(ctx, sc, st, p, rays_o, rays_d, R, term_eps, bg, seed, rgb_out, ws);
     RenderWs w;
-    const int64_t budget = R * knobs.slots_per_ray;
     carve_render(ws, R, budget, w);
     if (!ws.ok()) return KN_E_WORKSPACE;
     KnGroupWs gw;
@@ -1352,20 +1384,8 @@ static int render_impl(kn_ctx *ctx, const kn_scene *sc, void *stream, const floa
     const int32_t march_hash = fused_hist ? 0 : knobs.group_hash_slots;
     KnStageTimer tm(ctx, st);
     tm.begin();
-    int first_samples = knobs.first_wave_samples > 0 ? knobs.first_wave_samples : (K / 16 > DEFAULT_FIRST_WAVE ? K / 16 : DEFAULT_FIRST_WAVE);
-    if (first_samples > knobs.slots_per_ray) first_samples = knobs.slots_per_ray;
     const bool want_counts = tm.counts || stats != nullptr;
-    // With K slots for each of `rays` rays a wave takes every ray to its end, and nobody has to read how many are left
-    // (unless the caller wants the counters of this frame): the first wave where it takes K samples per ray, else the second.
-    const bool first_wave_ends_it = !want_counts && (int64_t)first_samples >= (int64_t)K && R * (int64_t)K <= budget;
-    auto second_wave_ends = [&](int64_t rays) {
-        return (int64_t)first_samples < (int64_t)K && rays * (int64_t)K <= budget && (int64_t)first_samples * knobs.wave_growth >= (int64_t)K;
-    };
-    // Small frames that end like that don't read the number of live rays either: their grids are sized for all rays, at most
-    // some hundred workgroups too many, where the host's look at the count leaves the GPU idle for longer.  64x64 rays, K = 32,
-    // fp32, 2^3 networks: 79 -> 37 us (both waits gone); 180x180, K = 128, width 64, 372 -> 369 (the grids' extra workgroups are
-    // no loss there either); 400x400, K = 48 (not taken, the first wave ends it) 270 -> 245.
-    const bool blind = !want_counts && R <= BLIND_RAYS && (first_wave_ends_it || second_wave_ends(R));
+    const bool first_wave_ends_it = !want_counts && first_wave_ends, blind = !want_counts && no_look;
     KnMailbox *mb = blind ? nullptr : mailbox_for(ctx, st);
     unsigned long long *mb_dev = mb ? mb->dev : nullptr;
     unsigned long long seq_local = 0; // sequence numbers without a mailbox (nobody reads them)

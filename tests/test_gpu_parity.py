@@ -1854,3 +1854,57 @@ def test_sparse_and_stratified_edge_cases():
     assert dev.render(empty, empty, 1.0, 0.1, 8, 0.0, bg, seed=3).shape == (0, 3)
     k, c, nx = dev.march(cuda(o[:5]), cuda(d[:5]), cfg["t_near"], cfg["step"], 0, S=4, seed=4)
     assert (c.cpu().numpy() == 0).all() and (k.cpu().numpy() == -1).all()
+
+
+@pytest.mark.parametrize("wdtype,H,res,occ_res,keep,K,rays,eps,one_kernel", [
+    ("f16", 32, (16, 16, 16), None, None, 32, 4096, 0.01, False),         # content everywhere, few points in a cell
+    ("bf16", 32, (16, 16, 16), None, None, 128, 4096, 0.01, True),        # 4.6 points
+    ("f16", 64, (5, 8, 5), None, None, 32, 4096, 0.01, False),
+    ("f32", 32, (16, 16, 16), None, None, 256, 4096, 0.0, True),
+    ("f16", 32, (32, 32, 32), (64, 64, 64), 0.5, 160, 8192, 0.01, True),  # sparse: small, mid-sized and large frames
+    ("f16", 32, (32, 32, 32), (64, 64, 64), 0.5, 192, 32769, 0.01, False),
+    ("f16", 32, (32, 32, 32), (64, 64, 64), 0.5, 256, 32769, 0.01, True),
+    ("f16", 32, (32, 32, 32), (64, 64, 64), 0.5, 192, 1 << 18, 0.01, True),
+    ("bf16", 64, (16, 16, 16), (64, 64, 64), None, 160, 32769, 0.01, False),
+    ("bf16", 64, (16, 16, 16), (64, 64, 64), None, 192, 32769, 0.01, True),
+    ("bf16", 32, (16, 16, 16), (64, 64, 64), None, 128, 40000, 0.0, True),
+    ("bf16", 32, (16, 16, 16), (64, 64, 64), None, 96, 40000, 0.0, False)])
+def test_render_takes_the_faster_way_to_the_same_picture(wdtype, H, res, occ_res, keep, K, rays, eps, one_kernel):
+    """Both sides of the lines between one kernel and waves (the timers tell which it was): the counted call's bits.  Captured, a frame
+    is never one that has to read counts back: three replays, each on other rays, with eager frames between them."""
+    import torch
+    import paper_2103_13744_amd as kn
+    occ = None if occ_res is None else ks.blob_occupancy(occ_res, 12, 0.15, 5)
+    sc = scene_dict(res, (-1, -1, -1), (1, 1, 1), H, wdtype, 13, occ=occ, sigma_scale=60.0)
+    if keep is not None:
+        sc = configs.sparsify(sc, np.random.default_rng(8).random(int(np.prod(res))) < keep, 9)
+    dev, _ = make_pair(sc)
+    o, d = ks.camera_rays(96, 96, 40.0, 4.0, 45.0, 30.0)
+    pick = torch.arange(rays, device="cuda") % len(o)
+    o, d = cuda(o)[pick].contiguous(), cuda(d)[pick].contiguous()
+    args = (4.0 - math.sqrt(3.0), 2 * math.sqrt(3.0) / K, K, eps, (1.0, 1.0, 1.0))
+    waves, st = dev.render(o, d, *args, want_stats=True)
+    kn.profile_enable(1)
+    try:
+        kn.profile_read()
+        assert torch.equal(dev.render(o, d, *args), waves) and st["samples_blended"] > rays
+        assert (kn.profile_read()["ms_march"] == 0.0) == one_kernel
+    finally:
+        kn.profile_enable(0)
+    o_in, d_in, out = o.clone(), d.clone(), torch.empty_like(o)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            dev.render(o_in, d_in, *args, out=out)
+    torch.cuda.current_stream().wait_stream(side)
+    for shift in (0, 1000, 5):
+        want = dev.render(o.roll(shift, 0), d.roll(shift, 0), *args).clone()
+        torch.cuda.synchronize()
+        o_in.copy_(o.roll(shift, 0))
+        d_in.copy_(d.roll(shift, 0))
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
