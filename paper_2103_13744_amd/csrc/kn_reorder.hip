@@ -993,7 +993,8 @@ void carve_order(KnCarver &c, int64_t M, int32_t N, OrderWs &w)
 }
 // Every workgroup of k_place scans the counts of all networks, in steps of 1,024: up to eight of them.
 constexpr int32_t ORDER_MAX_N = 8191;
-constexpr int64_t ORDER_MAX_M = 9 << 14;
+constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_FEW = 1 << 17;
+constexpr int32_t ORDER_FEW = 512;
 } // namespace
 
 int64_t kn_order_ws_bytes(int64_t M, int32_t N)
@@ -1008,13 +1009,15 @@ int64_t kn_order_ws_bytes(int64_t M, int32_t N)
 // networks), and kernels of many small workgroups.  The evaluation then gathers its points and scatters its results, which
 // costs more than moving the samples does once a batch is far larger than the caches.  65,537 points, fp16, width 32, against the
 // radix passes: 16^3 networks 66 us -> 29, 10x16x10 61 -> 28, 5x8x5 39 -> 25; fp32 (10x16x10) 77 -> 35; in random order over two
-// cells of 16^3 60 -> 27.  The line was drawn at 147,456 points when atomics on few addresses slowed skewed batches beyond it
-// (150,000 points, 16^3 networks, nine in ten of them in a twentieth of the cells: 58 us against 56 for kn_count_run).  k_rank has lost that cost since, and the line stayed:
-// 150,000 points all over / skewed 36 / 38 us against 55 / 54, 196,608 41 / 42 against 54 / 52, on 10x16x10 networks 33 / 32
-// against 39 / 39, on 5x8x8 37 / 26 against 32 / 32.
+// cells of 16^3 60 -> 27. Against
+// kn_count_run (150,001 / 220,001 / 270,001 / 330,001 points, us): 16^3 networks, fp16, 36 / 44 / 52 / 60 against 55 / 54 / 55 / 56,
+// skewed (nine in ten points in a twentieth of the cells) 38 / 45 / 50 / 57 against 54 / 52 / 53 / 53, 10x16x10, bf16, skewed 29 / 35 / 40 / 45
+// against 39 / 39 / 41 / 41, width 64 36 / 46 / 50 / 56 against 45 / 48 / 50 / 50, fp32 49 / 62 / 67 / 71 against 60 / 70 / 74 / 75; 20^3 (radix
+// passes) 47 / 56 / 63 / 69 against 75 / 79 / 78 / 80.  Few networks, whose table is counted in fewer rows and whose atomics meet:
+// 5x8x5 32 / 38 / 41 / 47 against 30 / 32 / 35 / 37.
 bool kn_order_pays(const kn_scene *sc, int64_t M)
 {
-    return sc->N <= ORDER_MAX_N && M <= ORDER_MAX_M;
+    return sc->N <= ORDER_MAX_N && M <= (sc->N <= ORDER_FEW ? ORDER_MAX_M_FEW : ORDER_MAX_M);
 }
 
 int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_t M, int32_t tile_len, int32_t *user_ids,

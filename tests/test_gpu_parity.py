@@ -1908,3 +1908,12 @@ def test_render_takes_the_faster_way_to_the_same_picture(wdtype, H, res, occ_res
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("wdtype,H,res,M", [("f16", 32, (8, 8, 8), 1 << 17), ("bf16", 32, (8, 8, 8), (1 << 17) + 1), ("f16", 64, (19, 3, 9), (1 << 17) + 1),
+                                            ("bf16", 32, (16, 16, 16), 1 << 18), ("f32", 32, (16, 16, 16), (1 << 18) + 1),
+                                            ("f16", 32, (20, 20, 20), 1 << 18), ("f16", 32, (20, 20, 20), (1 << 18) + 1)])
+@pytest.mark.parametrize("spread", ["all over", "one network", "none"])
+def test_eval_grouped_around_the_largest_batches_of_ordered_indices(wdtype, H, res, M, spread):
+    """Up to 2^17 points for 512 networks, 2^18 for more; beyond, samples are moved by counting, or with 6,144 networks and more by passes."""
+    test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
