@@ -707,27 +707,24 @@ static int eval_grouped_impl(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, co
         // the samples themselves are brought into grouped order (Sec. 3.5); the kernel reads them contiguously
         tm.begin();
         KnBucketOut bo;
-        const uint32_t *records[2] = {nullptr, nullptr};
-        float *out4 = nullptr;
+        KnSampleSrc src{};
         KnCountBack back{};
         const bool counted = !perm && kn_count_pays(M, sc->N);
         if (counted) {
-            KN_TRY(kn_count_run(sc, st, points, dirs, M, kn_mlp_tile_len(sc), cell_id, counts, ws, &bo, records, &back, &tm));
-            out4 = back.out4;
+            KN_TRY(kn_count_run(sc, st, points, dirs, M, kn_mlp_tile_len(sc), cell_id, counts, ws, &bo, &src, &back, &tm));
         } else {
-            KN_TRY(kn_reorder_run(sc, st, points, dirs, M, kn_mlp_tile_len(sc), cell_id, counts, perm, ws, &bo, records, &out4, &tm));
+            const uint32_t *records[2] = {nullptr, nullptr};
+            KN_TRY(kn_reorder_run(sc, st, points, dirs, M, kn_mlp_tile_len(sc), cell_id, counts, perm, ws, &bo, records, &src.out4, &tm));
+            src.records = records[0];
+            src.records_dir = records[1];
         }
         tm.mark(KN_ST_BUCKET);
-        KnSampleSrc src{};
-        src.records = records[0];
-        src.records_dir = records[1];
-        src.out4 = out4;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         (void)tm.kernel_events(KN_ST_MLP, &e0, &e1);
         KN_TRY(kn_mlp_launch(sc, st, src, bo, M, sigma, rgb, e0, e1));
         tm.mark(KN_ST_MLP);
         if (counted) KN_TRY(kn_count_results(st, back, M, sigma, rgb));
-        else KN_TRY(kn_reorder_split_results(st, out4, M, sigma, rgb));
+        else KN_TRY(kn_reorder_split_results(st, src.out4, M, sigma, rgb));
         tm.mark(KN_ST_BUCKET); // the way back to the caller's order is charged to the re-ordering
         tm.add(1, M, M, 1);
         return KN_OK;

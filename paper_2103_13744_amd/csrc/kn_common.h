@@ -313,9 +313,10 @@ struct KnCountBack {
     const uint16_t *from;
     int32_t nblk;
 };
+struct KnSampleSrc;
 int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,
-                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, const uint32_t *records[2],
-                 KnCountBack *back, KnStageTimer *tm);
+                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, KnSampleSrc *src, KnCountBack *back,
+                 KnStageTimer *tm);
 int kn_count_results(hipStream_t st, const KnCountBack &back, int64_t M, float *sigma, float *rgb);
 // Unstable grouping of a render wave's samples (row layout: row i holds cnt[i] samples in slots i*S ..).
 // out->perm lists slot numbers group by group, in no particular order inside a group or between groups;
@@ -341,8 +342,10 @@ int kn_group_run(hipStream_t st, const KnKnobs &knobs, const int32_t *row_keys, 
 // Sample source of the grouped MLP kernels: either explicit points/dirs (eval_grouped) or the
 // packed (ray, k) records of a render wave.
 struct KnSampleSrc {
-    const float *points;   // M*3 or nullptr
-    const float *dirs;     // M*3 or nullptr
+    // M*3 or nullptr: the caller's arrays, through the sorted index list; or with out4 and no index list the samples in grouped order
+    // (kn_count_run), whose results go to their own places
+    const float *points;
+    const float *dirs;
     // eval_grouped after the physical re-ordering (kn_reorder_run): the samples in grouped order, 4 words each in two
     // arrays, (x, y, z, key) and (dx, dy, dz, caller index); then the sorted list is the samples themselves and
     // `perm` is not read
@@ -352,7 +355,7 @@ struct KnSampleSrc {
     const float *rays_d;   // R*3
     float t_near, step;
     int32_t kbits;
-    float *out4;           // render: (r, g, b, sigma) per sample, 16 bytes each; nullptr = separate sigma / rgb arrays
+    float *out4;           // (r, g, b, sigma) per sample, 16 bytes each; nullptr = separate sigma / rgb arrays
     // Stratified sampling (render only): lattice points sit at their drawn offsets, and the density that goes to
     // out4 is scaled by delta_k / step, delta_k = t_(k+1) - t_k, so that the blend's exp(-sigma * step) is Eq. 4
     // with the sample's own delta.

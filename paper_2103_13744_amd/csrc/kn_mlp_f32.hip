@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
     auto descriptor = [&](int t) -> KnTile { return tiles[min(t, t_hi - 1)]; };
     auto sample_index = [&](const KnTile &d) {
         const int32_t pos = d.start + min(lane, d.len - 1);
-        return src.records ? pos : perm[pos]; // re-ordered records: the sorted list holds the samples themselves
+        return perm ? perm[pos] : pos; // (without an index list the sorted list holds the samples themselves)
     };
     KnTile dsc_next = descriptor(t_lo);
     int32_t idx_next = sample_index(dsc_next);

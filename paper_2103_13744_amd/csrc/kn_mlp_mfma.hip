@@ -176,8 +176,9 @@ __global__ void k_clear_flag(int32_t *flag) { *flag = 0; }
 // paths it does not take).  SRC_RAYS (render): lattice points rebuilt from packed (ray, k) records; gamma(d) is the
 // same for every sample of a ray, so the render's set-up kernel encodes it once per ray, already in operand order
 // (KnSampleSrc::dir_table), and a lane fetches its 16 bytes instead of computing them.  SRC_POINTS: the caller's
-// arrays through the sorted index list `perm`.  SRC_RECORDS: the re-ordered samples themselves (`perm` is not read).
-enum { SRC_RAYS = 0, SRC_POINTS = 1, SRC_RECORDS = 2 };
+// arrays through the sorted index list `perm`.  SRC_RECORDS, SRC_SORTED: the re-ordered samples themselves (`perm` is not read), with the
+// place of the result in a sample's last word, or the sample's own place.
+enum { SRC_RAYS = 0, SRC_POINTS = 1, SRC_RECORDS = 2, SRC_SORTED = 3 };
 template <int H, bool BF, int WAVES, bool WRAP, bool STRAT, int SRC>
 __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 4 : 2, H == 32 ? 4 : 2)))
     k_mlp_mfma(const uint16_t *__restrict__ packed, KnSampleSrc src, const int32_t *__restrict__ perm,
@@ -251,7 +252,7 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
     auto descriptor = [&](int t) -> KnTile { return tiles[min(t, t_hi - 1)]; };
     auto sorted_pos = [&](const KnTile &d) { return d.start + min(lane, d.len - 1); };
     auto sample_at = [&](const KnTile &d) -> int32_t {
-        if constexpr (from_records) return sorted_pos(d);
+        if constexpr (from_records || SRC == SRC_SORTED) return sorted_pos(d);
         else return perm[sorted_pos(d)];
     };
     auto load_record = [&](int32_t i) -> uint32_t {
@@ -839,13 +840,14 @@ int launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &src, const KnB
     for (int a = 0; a < 3; ++a)
         reach = fmaxf(reach, fmaxf(fabsf(sc->desc.aabb_min[a]), fabsf(sc->desc.aabb_max[a])));
     const bool wrap = !(reach * (256.0f * INV_2PI) < 250.0f);
-    const bool rays = src.points == nullptr && src.records == nullptr;
+    const bool rays = src.points == nullptr && src.records == nullptr, sorted = src.points != nullptr && b.perm == nullptr;
     const bool strat = src.strat != 0 && rays;
     if (rays && !src.dir_table) return KN_E_INVALID_ARG;
-    if ((src.out4 != nullptr) != (rays || src.records != nullptr)) return KN_E_INVALID_ARG; // where the results go is part of the kernel variant
+    if ((src.out4 != nullptr) != (rays || sorted || src.records != nullptr)) return KN_E_INVALID_ARG; // where the results go is part of the kernel variant
     // render: the ray's encoded direction comes from the table, midpoint or stratified lattice; else explicit points,
     // through the index list or re-ordered
     auto kernel = src.records ? (wrap ? k_mlp_mfma<H, BF, WAVES, true, false, SRC_RECORDS> : k_mlp_mfma<H, BF, WAVES, false, false, SRC_RECORDS>)
+                  : sorted    ? (wrap ? k_mlp_mfma<H, BF, WAVES, true, false, SRC_SORTED> : k_mlp_mfma<H, BF, WAVES, false, false, SRC_SORTED>)
                   : !rays     ? (wrap ? k_mlp_mfma<H, BF, WAVES, true, false, SRC_POINTS> : k_mlp_mfma<H, BF, WAVES, false, false, SRC_POINTS>)
                   : wrap      ? (strat ? k_mlp_mfma<H, BF, WAVES, true, true, SRC_RAYS> : k_mlp_mfma<H, BF, WAVES, true, false, SRC_RAYS>)
                               : (strat ? k_mlp_mfma<H, BF, WAVES, false, true, SRC_RAYS> : k_mlp_mfma<H, BF, WAVES, false, false, SRC_RAYS>);

@@ -553,9 +553,10 @@ __global__ void __launch_bounds__(PLACE_THREADS)
 // A workgroup has about two samples per network with 4,096 networks, 32 bytes of each half side by side: the runs of one
 // network follow each other by workgroup, so an XCD takes one contiguous part of the batch, and its workgroups, which go
 // through the networks at the same pace, fill the lines in its L2 together.
-// Bound by memory traffic: 4 M points, 16^3 networks: count 20 us, scan 10, scatter 70 (118 MB read, 202 written where 159 are
-// needed: 4.6 TB/s, what a copy reaches), against 158 for the
-// two radix passes and 10 for the search for the tiles.  Whole calls, width 32, fp16: 4 M points 322 -> 245 us, 10x16x10
+// With 1,024 threads a result goes to its sample's own place (k_results_back), and the two halves are 12 bytes each; 16 with the key and the
+// result's place: 4 M points, 16^3 networks, scatter 72 us, MLP kernel 87 / 69, 80; 8 M skewed 127, 160 / 115, 148.
+// Bound by memory traffic: 4 M points, 16^3 networks: count 20 us, scan 10, scatter 69 (118 MB read, 126 to be written),
+// against 158 for the two radix passes and 10 for the search for the tiles.  Whole calls, width 32, fp16: 4 M points 322 -> 245 us, 10x16x10
 // networks 313 -> 215; 8 M 584 -> 470; 1 M 106 -> 76; 262,143 73 -> 57.
 constexpr int CO_ROWS = 8;
 // COUNT_MAX_N: the staging buffer of 1,024 threads (128 KB) and the networks' starts are the LDS of a compute unit.
@@ -663,10 +664,11 @@ constexpr int co_list(int threads)
     return (int)((COUNT_MAX_N + min_blocks) / min_blocks);
 }
 static_assert((COUNT_MAX_N + 1) * 4 <= 512 * CO_ROWS * 16, "the counts share the staging buffer's place");
+struct f3_t { float x, y, z; };
 template <int T>
 __global__ void __launch_bounds__(T)
-    k_count_scatter(const uint16_t *__restrict__ keys, const float *__restrict__ pts, const float *__restrict__ dirs, u4 *__restrict__ pout,
-                    u4 *__restrict__ dout, int64_t M, int32_t N, int32_t nblk, const int32_t *__restrict__ table,
+    k_count_scatter(const uint16_t *__restrict__ keys, const float *__restrict__ pts, const float *__restrict__ dirs, void *__restrict__ pout,
+                    void *__restrict__ dout, int64_t M, int32_t N, int32_t nblk, const int32_t *__restrict__ table,
                     const int32_t *__restrict__ totals, int32_t tile_len, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles,
                     int32_t *__restrict__ n_tiles, uint32_t *__restrict__ at, uint16_t *__restrict__ from, float *__restrict__ out4)
 {
@@ -745,6 +747,11 @@ __global__ void __launch_bounds__(T)
         for (int c = 0; c < 3; ++c) p[r][c] = dirs[3 * i + c];
     }
     __syncthreads();
+    // BACK: a sample's result goes to its own place, and its halves need no fourth word
+    auto put = [&](void *half, int32_t i, u4 v) {
+        if constexpr (BACK) ((f3_t *)half)[i] = (f3_t){__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2])};
+        else ((u4 *)half)[i] = v;
+    };
     int32_t dst[CO_ROWS];
 #pragma unroll
     for (int k = 0; k < CO_ROWS; ++k) {
@@ -752,7 +759,7 @@ __global__ void __launch_bounds__(T)
         if (sp < n_here) {
             const u4 v = stage[sp];
             dst[k] = sp + delta[v[3]];
-            pout[dst[k]] = v;
+            put(pout, dst[k], v);
             if constexpr (BACK) at[base + sp] = (uint32_t)dst[k];
             // no network: the result is zero
             if (BACK && v[3] == (uint32_t)N) *(float4 *)(out4 + 4 * (int64_t)dst[k]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -769,13 +776,9 @@ __global__ void __launch_bounds__(T)
         const int32_t sp = k * T + threadIdx.x;
         if (sp < n_here) {
             u4 v = stage[sp];
-            if constexpr (BACK) {
-                from[base + sp] = (uint16_t)v[3];
-                v[3] = (uint32_t)dst[k]; // the result goes to the sample's own place
-            } else {
-                v[3] += (uint32_t)base; // to the place in the caller's order
-            }
-            dout[dst[k]] = v;
+            if constexpr (BACK) from[base + sp] = (uint16_t)v[3];
+            else v[3] += (uint32_t)base; // the place in the caller's order
+            put(dout, dst[k], v);
         }
     }
     // tiles: a wavefront per network, the whole workgroup for networks of more than one tile per lane
@@ -1053,7 +1056,7 @@ struct CountWs {
     int32_t *n_tiles, *totals, *table;
     uint16_t *keys;
     KnTile *tiles;
-    u4 *pos, *dir;
+    void *pos, *dir; // the samples' halves: 12 bytes each with 1,024 threads, else 16
     uint32_t *at;
     uint16_t *from;
     float *out4;
@@ -1068,8 +1071,9 @@ void carve_count(KnCarver &c, int64_t M, int32_t N, CountWs &w)
     w.table = c.carve<int32_t>((int64_t)w.nblk * (N + 1));
     w.keys = c.carve<uint16_t>(M);
     w.tiles = c.carve<KnTile>(kn_max_tiles(M, N, 64));
-    w.pos = c.carve<u4>(M);
-    w.dir = c.carve<u4>(M);
+    const int64_t words = (w.threads == COUNT_BACK_THREADS ? 3 : 4) * M;
+    w.pos = c.carve<float>(words);
+    w.dir = c.carve<float>(words);
     w.at = w.threads == COUNT_BACK_THREADS ? c.carve<uint32_t>(M) : nullptr;
     w.from = w.threads == COUNT_BACK_THREADS ? c.carve<uint16_t>(M) : nullptr;
     w.out4 = c.carve<float>(4 * M);
@@ -1088,7 +1092,7 @@ int64_t kn_count_ws_bytes(int64_t M, int32_t N)
 }
 
 int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,
-                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, const uint32_t *records[2], KnCountBack *back,
+                 int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, KnSampleSrc *src, KnCountBack *back,
                  KnStageTimer *tm)
 {
     const int32_t N = sc->N;
@@ -1113,8 +1117,14 @@ int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const 
     out->offsets = nullptr;
     out->tiles = w.tiles;
     out->n_tiles = w.n_tiles;
-    records[0] = (const uint32_t *)w.pos;
-    records[1] = (const uint32_t *)w.dir;
+    if (w.at) {
+        src->points = (const float *)w.pos;
+        src->dirs = (const float *)w.dir;
+    } else {
+        src->records = (const uint32_t *)w.pos;
+        src->records_dir = (const uint32_t *)w.dir;
+    }
+    src->out4 = w.out4;
     *back = KnCountBack{w.out4, w.at, w.from, w.nblk};
     return KN_OK;
 }
