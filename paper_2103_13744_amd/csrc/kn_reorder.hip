@@ -555,7 +555,7 @@ __global__ void __launch_bounds__(PLACE_THREADS)
 // through the networks at the same pace, fill the lines in its L2 together.
 // With 1,024 threads a result goes to its sample's own place (k_results_back), and the two halves are 12 bytes each; 16 with the key and the
 // result's place: 4 M points, 16^3 networks, scatter 72 us, MLP kernel 87 / 69, 80; 8 M skewed 127, 160 / 115, 148.
-// Bound by memory traffic: 4 M points, 16^3 networks: count 20 us, scan 10, scatter 69 (118 MB read, 126 to be written),
+// Bound by memory traffic: 4 M points, 16^3 networks: count 20 us, scan 6 (11 with rows of N + 1 entries, whose lines two workgroups share; 8 M 17 -> 10), scatter 68 (118 MB read, 126 to be written),
 // against 158 for the two radix passes and 10 for the search for the tiles.  Whole calls, width 32, fp16: 4 M points 322 -> 245 us, 10x16x10
 // networks 313 -> 215; 8 M 584 -> 470; 1 M 106 -> 76; 262,143 73 -> 57.
 constexpr int CO_ROWS = 8;
@@ -570,6 +570,8 @@ constexpr int COUNT_BACK_THREADS = 1024;
 constexpr int32_t COUNT_MAX_N = 6143;
 constexpr int64_t COUNT_MIN_M = 1 << 17, COUNT_WIDE_M = 5 << 18;
 typedef uint16_t h4_t __attribute__((ext_vector_type(4)));
+// rows of the table start on lines
+__host__ __device__ inline int64_t table_stride(int32_t bins) { return (bins + 31) & ~31; }
 
 // (the same numbering in both kernels: row b of the table)
 __device__ __forceinline__ int32_t xcd_block(int32_t nblk)
@@ -620,38 +622,48 @@ __global__ void __launch_bounds__(T)
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i <= N; i += T) table[(int64_t)b * (N + 1) + i] = hist[i];
+    for (int i = threadIdx.x; i <= N; i += T) table[b * table_stride(N + 1) + i] = hist[i];
 }
 
-// 32 networks per workgroup, 32 shares of the table's rows
+// 32 networks per workgroup (their places in a row of the table are a line of their own: table_stride), 32 shares of the table's rows, two to
+// a wavefront
+constexpr int TS_NETS = 32, TS_SHARES = 1024 / TS_NETS;
 __global__ void __launch_bounds__(1024) k_table_scan(int32_t *__restrict__ table, int32_t bins, int32_t nblk, int32_t *__restrict__ totals)
 {
-    __shared__ int32_t part[32][33];
-    const int lane = threadIdx.x & 31, seg = threadIdx.x >> 5;
-    const int32_t d = blockIdx.x * 32 + lane;
-    const int32_t each = (nblk + 31) / 32, r0 = min(seg * each, nblk), r1 = min(r0 + each, nblk);
+    const int64_t stride = table_stride(bins);
+    __shared__ int32_t part[1024 / KN_WAVE][TS_NETS];
+    const int lane = threadIdx.x & (TS_NETS - 1), seg = threadIdx.x / TS_NETS, wv = threadIdx.x / KN_WAVE;
+    const int32_t d = blockIdx.x * TS_NETS + lane;
+    const int32_t each = (nblk + TS_SHARES - 1) / TS_SHARES, r0 = min(seg * each, nblk), r1 = min(r0 + each, nblk);
     const bool has = d < bins;
     int32_t *col = table + (has ? d : bins - 1);
     constexpr int KEPT = 32; // rows of a share that stay in registers between the two sweeps (all loads in flight together)
-    int32_t v[KEPT], sum = 0, run = 0;
+    int32_t v[KEPT], sum = 0;
 #pragma unroll
-    for (int k = 0; k < KEPT; ++k) v[k] = r0 + k < r1 ? col[(int64_t)(r0 + k) * bins] : 0;
+    for (int k = 0; k < KEPT; ++k) v[k] = r0 + k < r1 ? col[(r0 + k) * stride] : 0;
 #pragma unroll
     for (int k = 0; k < KEPT; ++k) sum += v[k];
-    for (int32_t r = r0 + KEPT; r < r1; ++r) sum += col[(int64_t)r * bins];
-    part[seg][lane] = sum;
+    for (int32_t r = r0 + KEPT; r < r1; ++r) sum += col[r * stride];
+    int32_t run = sum; // up to and with this share of the wavefront's
+#pragma unroll
+    for (int w = TS_NETS; w < KN_WAVE; w <<= 1) {
+        const int32_t o = __shfl_up(run, w, KN_WAVE);
+        if ((int)(threadIdx.x & (KN_WAVE - 1)) >= w) run += o;
+    }
+    if ((threadIdx.x & (KN_WAVE - 1)) >= KN_WAVE - TS_NETS) part[wv][lane] = run;
     __syncthreads();
-    for (int q = 0; q < seg; ++q) run += part[q][lane];
+    run -= sum;
+    for (int q = 0; q < wv; ++q) run += part[q][lane];
     if (!has) return;
-    if (seg == 31) totals[d] = run + sum;
+    if (seg == TS_SHARES - 1) totals[d] = run + sum;
 #pragma unroll
     for (int k = 0; k < KEPT; ++k) {
-        if (r0 + k < r1) col[(int64_t)(r0 + k) * bins] = run;
+        if (r0 + k < r1) col[(r0 + k) * stride] = run;
         run += v[k];
     }
     for (int32_t r = r0 + KEPT; r < r1; ++r) {
-        const int32_t c = col[(int64_t)r * bins];
-        col[(int64_t)r * bins] = run;
+        const int32_t c = col[r * stride];
+        col[r * stride] = run;
         run += c;
     }
 }
@@ -723,7 +735,7 @@ __global__ void __launch_bounds__(T)
     if (b == 0 && threadIdx.x == 0) *n_tiles = tiles_all;
     for (int32_t d = d0; d < d1; ++d) {
         const int32_t c = totals[d], n_t = d < N ? (c + tile_len - 1) / tile_len : 0, mine = cnt[d];
-        delta[d] = run[1] + table[(int64_t)b * bins + d] - run[0];
+        delta[d] = run[1] + table[b * table_stride(bins) + d] - run[0];
         cnt[d] = run[0];
         if (n_t > 0 && d % nblk == b) s_list[atomicAdd(&s_listed, 1)] = make_int4(d, c, run[1], run[2]);
         if (user_counts && b == 0) user_counts[d] = c;
@@ -1068,7 +1080,7 @@ void carve_count(KnCarver &c, int64_t M, int32_t N, CountWs &w)
     w.nblk = (int32_t)kn_div_up(M, w.threads * CO_ROWS);
     w.n_tiles = c.carve<int32_t>(1);
     w.totals = c.carve<int32_t>(N + 1);
-    w.table = c.carve<int32_t>((int64_t)w.nblk * (N + 1));
+    w.table = c.carve<int32_t>(w.nblk * table_stride(N + 1));
     w.keys = c.carve<uint16_t>(M);
     w.tiles = c.carve<KnTile>(kn_max_tiles(M, N, 64));
     const int64_t words = (w.threads == COUNT_BACK_THREADS ? 3 : 4) * M;
@@ -1107,7 +1119,7 @@ int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const 
     hipLaunchKernelGGL(count, grid, block, bins, st, points, M, sc->net_grid, sc->cell_net, user_ids, w.keys, N, w.nblk, w.table);
     KN_CHECK_LAUNCH();
     if (tm) tm->mark(KN_ST_CELL);
-    hipLaunchKernelGGL(k_table_scan, dim3((unsigned)kn_div_up(N + 1, 32)), dim3(1024), 0, st, w.table, N + 1, w.nblk, w.totals);
+    hipLaunchKernelGGL(k_table_scan, dim3((unsigned)kn_div_up(N + 1, TS_NETS)), dim3(1024), 0, st, w.table, N + 1, w.nblk, w.totals);
     KN_CHECK_LAUNCH();
     hipLaunchKernelGGL(scatter, grid, block, (size_t)w.threads * CO_ROWS * sizeof(u4) + bins, st, w.keys, points, dirs, w.pos, w.dir, M, N,
                        w.nblk, w.table, w.totals, tile_len, user_counts, w.tiles, w.n_tiles, w.at, w.from, w.out4);
