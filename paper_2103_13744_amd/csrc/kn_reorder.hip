@@ -553,7 +553,7 @@ __global__ void __launch_bounds__(PLACE_THREADS)
 // A workgroup has about two samples per network with 4,096 networks, 32 bytes of each half side by side: the runs of one
 // network follow each other by workgroup, so an XCD takes one contiguous part of the batch, and its workgroups, which go
 // through the networks at the same pace, fill the lines in its L2 together.
-// With 1,024 threads a result goes to its sample's own place (k_results_back), and the two halves are 12 bytes each; 16 with the key and the
+// From COUNT_BACK_M points on a result goes to its sample's own place (k_results_back), and the two halves are 12 bytes each; 16 with the key and the
 // result's place: 4 M points, 16^3 networks, scatter 72 us, MLP kernel 87 / 69, 80; 8 M skewed 127, 160 / 115, 148.
 // Bound by memory traffic: 4 M points, 16^3 networks: count 20 us, scan 6 (11 with rows of N + 1 entries, whose lines two workgroups share; 8 M 17 -> 10), scatter 68 (118 MB read, 126 to be written),
 // against 158 for the two radix passes and 10 for the search for the tiles.  Whole calls, width 32, fp16: 4 M points 322 -> 245 us, 10x16x10
@@ -563,10 +563,11 @@ constexpr int CO_ROWS = 8;
 // COUNT_WIDE_M: 1,024 threads from where their workgroups nearly fill the chip (1.3 M points 99 us with 512, 1.4 M 89 with 1,024).
 // COUNT_MIN_M: see kn_order_pays, which is asked first.  (Few networks, where the radix sort is one trip as well: 5x8x5, 270,000 points 50 -> 38 us, 1 M
 // 67 -> 51, 4 M 219 -> 169; 2^3 with nine in ten points in one network, the most LDS atomics on one address, 4 M 279 -> 180.)
-// COUNT_BACK_THREADS: results go through k_results_back.  Width 32, fp16 / width 64, bf16, 16^3 networks: 1.4 M points 88 -> 88 /
-// 123 -> 111 us, 4 M 245 -> 218 / 285 -> 276; with 512 threads (not taken) 1 M 76 -> 75 / 93 -> 91, 10x16x10 networks 60 -> 60 /
-// 73 -> 75, 262,143 43 -> 44 / 50 -> 53.
-constexpr int COUNT_BACK_THREADS = 1024;
+// COUNT_BACK_M: 16-bit scenes from here on, and all with 1,024 threads: results go through k_results_back.  Width 32, fp16 / width 64, bf16,
+// 16^3 networks: 1.4 M points 88 -> 88 / 123 -> 111 us, 4 M 245 -> 218 / 285 -> 276 (halves of 16 bytes still); with 512 threads
+// 1.3 M 94.6 -> 94.0 / 128 -> 114, skewed 87 -> 81, 1 M 72.7 -> 69.9 / 89.5 -> 86.3, skewed 67 -> 62, 800,001 67.9 -> 65.9 / 82.7 -> 81.5, 500,003
+// 58.8 -> 58.1 / 72.6 -> 74.6, 270,001 55.3 -> 57.2 / 69.8 -> 72.7; fp32, whose evaluation the scattered stores don't hold up, 1.3 M 186 -> 190.
+constexpr int64_t COUNT_BACK_M = 5 << 17;
 constexpr int32_t COUNT_MAX_N = 6143;
 constexpr int64_t COUNT_MIN_M = 1 << 17, COUNT_WIDE_M = 5 << 18;
 typedef uint16_t h4_t __attribute__((ext_vector_type(4)));
@@ -677,14 +678,13 @@ constexpr int co_list(int threads)
 }
 static_assert((COUNT_MAX_N + 1) * 4 <= 512 * CO_ROWS * 16, "the counts share the staging buffer's place");
 struct f3_t { float x, y, z; };
-template <int T>
+template <int T, bool BACK>
 __global__ void __launch_bounds__(T)
     k_count_scatter(const uint16_t *__restrict__ keys, const float *__restrict__ pts, const float *__restrict__ dirs, void *__restrict__ pout,
                     void *__restrict__ dout, int64_t M, int32_t N, int32_t nblk, const int32_t *__restrict__ table,
                     const int32_t *__restrict__ totals, int32_t tile_len, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles,
                     int32_t *__restrict__ n_tiles, uint32_t *__restrict__ at, uint16_t *__restrict__ from, float *__restrict__ out4)
 {
-    constexpr bool BACK = T == COUNT_BACK_THREADS;
     extern __shared__ u4 stage[];
     __shared__ int32_t s_sum[3][T / KN_WAVE];
     __shared__ int4 s_list[co_list(T)]; // (network, samples, first sample, first tile)
@@ -1068,13 +1068,14 @@ struct CountWs {
     int32_t *n_tiles, *totals, *table;
     uint16_t *keys;
     KnTile *tiles;
-    void *pos, *dir; // the samples' halves: 12 bytes each with 1,024 threads, else 16
+    void *pos, *dir; // the samples' halves: 12 bytes each where the results come back, else 16
     uint32_t *at;
     uint16_t *from;
     float *out4;
     int32_t threads, nblk;
 };
-void carve_count(KnCarver &c, int64_t M, int32_t N, CountWs &w)
+bool count_back(int64_t M, bool fp32) { return M > COUNT_WIDE_M || (!fp32 && M >= COUNT_BACK_M); }
+void carve_count(KnCarver &c, int64_t M, int32_t N, bool back, CountWs &w)
 {
     w.threads = M > COUNT_WIDE_M ? 1024 : 512;
     w.nblk = (int32_t)kn_div_up(M, w.threads * CO_ROWS);
@@ -1083,11 +1084,11 @@ void carve_count(KnCarver &c, int64_t M, int32_t N, CountWs &w)
     w.table = c.carve<int32_t>(w.nblk * table_stride(N + 1));
     w.keys = c.carve<uint16_t>(M);
     w.tiles = c.carve<KnTile>(kn_max_tiles(M, N, 64));
-    const int64_t words = (w.threads == COUNT_BACK_THREADS ? 3 : 4) * M;
+    const int64_t words = (back ? 3 : 4) * M;
     w.pos = c.carve<float>(words);
     w.dir = c.carve<float>(words);
-    w.at = w.threads == COUNT_BACK_THREADS ? c.carve<uint32_t>(M) : nullptr;
-    w.from = w.threads == COUNT_BACK_THREADS ? c.carve<uint16_t>(M) : nullptr;
+    w.at = back ? c.carve<uint32_t>(M) : nullptr;
+    w.from = back ? c.carve<uint16_t>(M) : nullptr;
     w.out4 = c.carve<float>(4 * M);
 }
 } // namespace
@@ -1099,7 +1100,7 @@ int64_t kn_count_ws_bytes(int64_t M, int32_t N)
     if (!kn_count_pays(M, N)) return 0;
     KnCarver c((void *)256, INT64_MAX / 2);
     CountWs w;
-    carve_count(c, M, N, w);
+    carve_count(c, M, N, count_back(M, true), w); // (the two ways differ in 2 bytes per point; the larger one)
     return c.used;
 }
 
@@ -1110,12 +1111,12 @@ int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const 
     const int32_t N = sc->N;
     if (!kn_count_pays(M, N) || M > (1ll << 30) || tile_len < 64) return KN_E_INVALID_ARG;
     CountWs w;
-    carve_count(ws, M, N, w);
+    carve_count(ws, M, N, count_back(M, sc->desc.wdtype == KN_F32), w);
     if (!ws.ok()) return KN_E_WORKSPACE;
     const dim3 grid((unsigned)w.nblk), block((unsigned)w.threads);
     const size_t bins = (size_t)(N + 1) * 4;
     auto count = w.threads == 1024 ? k_keys_count<1024> : k_keys_count<512>;
-    auto scatter = w.threads == 1024 ? k_count_scatter<1024> : k_count_scatter<512>;
+    auto scatter = w.threads == 1024 ? k_count_scatter<1024, true> : w.at ? k_count_scatter<512, true> : k_count_scatter<512, false>;
     hipLaunchKernelGGL(count, grid, block, bins, st, points, M, sc->net_grid, sc->cell_net, user_ids, w.keys, N, w.nblk, w.table);
     KN_CHECK_LAUNCH();
     if (tm) tm->mark(KN_ST_CELL);
@@ -1137,16 +1138,16 @@ int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const 
         src->records_dir = (const uint32_t *)w.dir;
     }
     src->out4 = w.out4;
-    *back = KnCountBack{w.out4, w.at, w.from, w.nblk};
+    *back = KnCountBack{w.out4, w.at, w.from, w.nblk, w.threads};
     return KN_OK;
 }
 
 int kn_count_results(hipStream_t st, const KnCountBack &back, int64_t M, float *sigma, float *rgb)
 {
     if (!back.at) return kn_reorder_split_results(st, back.out4, M, sigma, rgb);
-    constexpr int T = COUNT_BACK_THREADS;
-    hipLaunchKernelGGL(k_results_back<T>, dim3((unsigned)back.nblk), dim3(T), T * CO_ROWS * sizeof(u4), st, back.out4, back.at, back.from, M,
-                       back.nblk, sigma, rgb);
+    auto kernel = back.threads == 1024 ? k_results_back<1024> : k_results_back<512>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)back.nblk), dim3((unsigned)back.threads), back.threads * CO_ROWS * sizeof(u4), st, back.out4, back.at,
+                       back.from, M, back.nblk, sigma, rgb);
     KN_CHECK_LAUNCH();
     return KN_OK;
 }
@@ -1248,9 +1249,11 @@ int kn_reorder_configure()
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<true>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     const int counts = (COUNT_MAX_N + 1) * 4;
-    KN_HIP(hipFuncSetAttribute((const void *)k_results_back<COUNT_BACK_THREADS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               COUNT_BACK_THREADS * CO_ROWS * 16));
-    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<512>, hipFuncAttributeMaxDynamicSharedMemorySize, 512 * CO_ROWS * 16 + counts));
-    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, 1024 * CO_ROWS * 16 + counts));
+    constexpr int half = 512 * CO_ROWS * 16, full = 1024 * CO_ROWS * 16;
+    KN_HIP(hipFuncSetAttribute((const void *)k_results_back<512>, hipFuncAttributeMaxDynamicSharedMemorySize, half));
+    KN_HIP(hipFuncSetAttribute((const void *)k_results_back<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, full));
+    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<512, false>, hipFuncAttributeMaxDynamicSharedMemorySize, half + counts));
+    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<512, true>, hipFuncAttributeMaxDynamicSharedMemorySize, half + counts));
+    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<1024, true>, hipFuncAttributeMaxDynamicSharedMemorySize, full + counts));
     return KN_OK;
 }

@@ -1917,3 +1917,11 @@ def test_render_takes_the_faster_way_to_the_same_picture(wdtype, H, res, occ_res
 def test_eval_grouped_around_the_largest_batches_of_ordered_indices(wdtype, H, res, M, spread):
     """Up to 2^17 points for 512 networks, 2^18 for more; beyond, samples are moved by counting, or with 6,144 networks and more by passes."""
     test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
+
+
+@pytest.mark.parametrize("wdtype,H,res,M", [("bf16", 32, (16, 16, 16), (5 << 17) - 1), ("f16", 32, (16, 16, 16), 5 << 17), ("bf16", 64, (10, 16, 10), (5 << 17) + 1),
+                                            ("f32", 32, (10, 16, 10), 5 << 17), ("f16", 64, (18, 18, 18), 1300003)])
+@pytest.mark.parametrize("spread", ["all over", "one network", "none"])
+def test_eval_grouped_whose_results_come_back_through_lds(wdtype, H, res, M, spread):
+    """16-bit scenes from 655,360 points on, workgroups of 512 threads."""
+    test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
