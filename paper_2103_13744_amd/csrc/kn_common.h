@@ -294,7 +294,7 @@ struct KnStageTimer;
 int kn_reorder_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,
                    int32_t *user_ids, int32_t *user_counts, int32_t *user_perm, KnCarver &ws, KnBucketOut *out,
                    const uint32_t *records[2], float **out4, KnStageTimer *tm /* nullable: marks the end of the cell-id stage */);
-int kn_reorder_configure(); // once per device: lifts the dynamic-LDS limit of the scatter kernels
+int kn_reorder_configure(); // once per device: lifts the dynamic-LDS limit of the ordering kernels
 int kn_reorder_split_results(hipStream_t st, const float *out4, int64_t M, float *sigma, float *rgb);
 // Order of a batch by network alone (no order inside a network): out->perm, out->counts and the tiles; zero results of the
 // points without a network go straight to sigma / rgb.

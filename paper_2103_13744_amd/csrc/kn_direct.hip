@@ -112,9 +112,13 @@ __global__ void __launch_bounds__(DIRECT_WAVES *KN_WAVE) __attribute__((amdgpu_w
 
 // A batch goes unordered when its weight traffic takes less time than ordering does.  The traffic is at most one fetch per
 // point, or per wavefront and network where there are few networks; it was seen at 7 to 8 TB/s, and at 18 where the weights
-// of all networks fit the 4 MB of an XCD's L2.  Ordering costs
-// some 20 us with up to 255 networks, and 35 and more beyond.  At the border, random points, width 32, fp16: 16,384 points on 16^3 networks 29 us against 36, 32,768
-// (not taken) 55 against 36; 16,384 on 5x8x5 networks 15 against 23.
+// of all networks fit the 4 MB of an XCD's L2.
+// What ordering takes grows with the networks, whose counts every one of its workgroups looks at, and few points of a batch that is all over the grid
+// meet.  Near the lines, direct / ordered, points all over the grid (in brackets: nine in ten in a twentieth of the cells), us: 5x8x5
+// networks, fp32, 3,000 points 14 / 19, 6,000 (not taken) 24 / 20; 16^3, fp16, 12,000 22 / 25, 16,000 28 / 26 (12 / 20), 24,000 41 / 26 (16 / 19), 28,000
+// (not) 48 / 26 (20 / 20); 10x16x10, bf16, width 64, 6,000 28 / 23 (19 / 21), 9,000 (not) 47 / 23 (33 / 22), fp32 6,000 (not) 31 / 22; 24x20x28, fp16,
+// 24,000 43 / 49 (30 / 33), 34,000 (not) 69 / 53 (48 / 36), fp32 9,000 57 / 59; 32^3, fp16, 28,000 52 / 83 (46 / 57), 40,000 (not) 75 / 91 (67 / 59),
+// bf16, width 64, 16,000 77 / 122, fp32 16,000 77 / 119.
 int kn_direct_lg_points(const kn_scene *sc, int64_t M)
 {
     const int H = sc->desc.hidden;
@@ -126,7 +130,9 @@ int kn_direct_lg_points(const kn_scene *sc, int64_t M)
     const double shares = (double)kn_div_up(M, 1ll << lg), networks = (double)(sc->N < (1 << lg) ? sc->N : 1 << lg);
     const double fetches = fmin((double)M, shares * networks);
     const double us = fetches * (all / sc->N) / (all <= 3e6 ? 18e6 : 8e6);
-    return us <= (sc->N <= 255 ? 24.0 : 40.0) ? lg : -1;
+    const bool heavy = f32 || H == 64;
+    const double limit = sc->N <= 255 ? 24.0 : sc->N <= 8191 ? (heavy ? 26.0 : 40.0) : sc->N <= 16383 ? 45.0 : (heavy ? 80.0 : 50.0);
+    return us <= limit ? lg : -1;
 }
 
 int kn_direct_launch(const kn_scene *sc, hipStream_t st, const KnDirectJob &job, hipEvent_t ev_start, hipEvent_t ev_stop)

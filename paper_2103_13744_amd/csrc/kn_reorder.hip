@@ -1006,8 +1006,9 @@ void carve_order(KnCarver &c, int64_t M, int32_t N, OrderWs &w)
     w.perm = c.carve<int32_t>(M);
     w.tiles = c.carve<KnTile>(kn_max_tiles(M, N, 64));
 }
-// Every workgroup of k_place scans the counts of all networks, in steps of 1,024: up to eight of them.
-constexpr int32_t ORDER_MAX_N = 8191;
+// Every workgroup of k_place scans the counts of all networks, in steps of 1,024, and keeps their starts in LDS.
+constexpr int32_t ORDER_MAX_N = 32768;
+static_assert((ORDER_MAX_N + 1024) * 4 <= 150 * 1024, "the starts of the networks (k_place) fit the LDS of a compute unit");
 constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_FEW = 1 << 17;
 constexpr int32_t ORDER_FEW = 512;
 } // namespace
@@ -1029,7 +1030,9 @@ int64_t kn_order_ws_bytes(int64_t M, int32_t N)
 // skewed (nine in ten points in a twentieth of the cells) 38 / 45 / 50 / 57 against 54 / 52 / 53 / 53, 10x16x10, bf16, skewed 29 / 35 / 40 / 45
 // against 39 / 39 / 41 / 41, width 64 36 / 46 / 50 / 56 against 45 / 48 / 50 / 50, fp32 49 / 62 / 67 / 71 against 60 / 70 / 74 / 75; 20^3 (radix
 // passes) 47 / 56 / 63 / 69 against 75 / 79 / 78 / 80.  Few networks, whose table is counted in fewer rows and whose atomics meet:
-// 5x8x5 32 / 38 / 41 / 47 against 30 / 32 / 35 / 37.
+// 5x8x5 32 / 38 / 41 / 47 against 30 / 32 / 35 / 37.  Many networks, against the radix passes (28,000 / 65,000 / 260,000 points): 24x20x28, fp16, 50 / 56 /
+// 78 against 80 / 83 / 91, skewed 35 / 42 / 76 against 65 / 71 / 89, fp32 94 / 108 / 131 against 119 / 132 / 149; 32^3, fp16, 83 / 110 / 144 against
+// 99 / 123 / 152, skewed 57 / 64 / 110 against 72 / 79 / 110, bf16, width 64, 160 / 219 / 308 against 171 / 231 / 317.
 bool kn_order_pays(const kn_scene *sc, int64_t M)
 {
     return sc->N <= ORDER_MAX_N && M <= (sc->N <= ORDER_FEW ? ORDER_MAX_M_FEW : ORDER_MAX_M);
@@ -1249,6 +1252,9 @@ int kn_reorder_configure()
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<true>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     const int counts = (COUNT_MAX_N + 1) * 4;
+    KN_HIP(hipFuncSetAttribute((const void *)k_rank, hipFuncAttributeMaxDynamicSharedMemorySize, (ORDER_MAX_N + 1) * 4));
+    KN_HIP(hipFuncSetAttribute((const void *)k_place, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)kn_div_up(ORDER_MAX_N + 1, PLACE_THREADS) * PLACE_THREADS * 4));
     constexpr int half = 512 * CO_ROWS * 16, full = 1024 * CO_ROWS * 16;
     KN_HIP(hipFuncSetAttribute((const void *)k_results_back<512>, hipFuncAttributeMaxDynamicSharedMemorySize, half));
     KN_HIP(hipFuncSetAttribute((const void *)k_results_back<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, full));

@@ -1925,3 +1925,33 @@ def test_eval_grouped_around_the_largest_batches_of_ordered_indices(wdtype, H, r
 def test_eval_grouped_whose_results_come_back_through_lds(wdtype, H, res, M, spread):
     """16-bit scenes from 655,360 points on, workgroups of 512 threads."""
     test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
+
+
+@pytest.mark.parametrize("wdtype,H,res,M", [("f16", 32, (16, 32, 16), 40001), ("bf16", 32, (24, 20, 28), 131073), ("f32", 32, (24, 20, 28), 20001),
+                                            ("f16", 32, (32, 32, 32), 30000), ("bf16", 64, (32, 32, 32), 1 << 18), ("f16", 32, (32, 32, 33), 40001)])
+@pytest.mark.parametrize("spread", ["all over", "one network", "none"])
+def test_eval_grouped_of_points_ordered_among_many_networks(wdtype, H, res, M, spread):
+    """Networks around and between 8,192 and 32,768 (the most whose starts fit the ordering kernels), and one layer more."""
+    test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
+
+
+@pytest.mark.parametrize("wdtype,H,res,points", [("f32", 32, (5, 8, 5), (3000, 6000)), ("bf16", 64, (10, 16, 10), (6000, 7000)), ("f16", 32, (16, 16, 16), (25000, 26500)),
+                                                 ("f16", 32, (24, 20, 28), (28000, 30000)), ("bf16", 32, (32, 32, 32), (31000, 33000)),
+                                                 ("f32", 32, (32, 32, 32), (16000, 18000))])
+def test_eval_grouped_on_both_sides_of_the_unordered_lines(wdtype, H, res, points):
+    """Direct below, ordered beyond (the timers tell): what the call that reports the permutation computes."""
+    import torch
+    import paper_2103_13744_amd as kn
+    dev, _ = make_pair(scene_dict(res, (-1, -1, -1), (1, 1, 1), H, wdtype, 24))
+    for M, direct in zip(points, (True, False)):
+        pts, dirs = cuda(ks.uniform_points(M, 33, lo=(-1.02,) * 3, hi=(1.02,) * 3)), cuda(ks.sphere_dirs(M, 34))
+        want = dev.eval_grouped(pts, dirs, want_aux=True)
+        kn.profile_enable(1)
+        try:
+            kn.profile_read()
+            got = dev.eval_grouped(pts, dirs)
+            assert (kn.profile_read()["ms_cell"] == 0.0) == direct
+        finally:
+            kn.profile_enable(0)
+        for a, b in zip(got, want):
+            assert torch.allclose(a, b, rtol=1e-5, atol=1e-6) if wdtype == "f32" else torch.equal(a, b)
