@@ -688,10 +688,10 @@ static int eval_grouped_impl(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, co
         tm.add(1, M, M, 1);
         return KN_OK;
     }
-    if (reorder && M > 0 && !perm && kn_order_pays(sc, M)) {
+    if (reorder && M > 0 && (perm ? kn_order_stable_pays(sc, M) : kn_order_pays(sc, M))) {
         tm.begin();
         KnBucketOut bo;
-        KN_TRY(kn_order_run(sc, st, points, M, kn_mlp_tile_len(sc), cell_id, counts, sigma, rgb, ws, &bo, &tm));
+        KN_TRY(kn_order_run(sc, st, points, M, kn_mlp_tile_len(sc), cell_id, counts, perm, sigma, rgb, ws, &bo, &tm));
         tm.mark(KN_ST_BUCKET);
         KnSampleSrc src{};
         src.points = points;

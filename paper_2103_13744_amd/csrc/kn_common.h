@@ -300,8 +300,9 @@ int kn_reorder_split_results(hipStream_t st, const float *out4, int64_t M, float
 // points without a network go straight to sigma / rgb.
 int64_t kn_order_ws_bytes(int64_t M, int32_t N);
 bool kn_order_pays(const kn_scene *sc, int64_t M);
+bool kn_order_stable_pays(const kn_scene *sc, int64_t M); // with user_perm: the stable order, in memory of the caller
 int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_t M, int32_t tile_len, int32_t *user_ids,
-                 int32_t *user_counts, float *sigma, float *rgb, KnCarver &ws, KnBucketOut *out, KnStageTimer *tm);
+                 int32_t *user_counts, int32_t *user_perm, float *sigma, float *rgb, KnCarver &ws, KnBucketOut *out, KnStageTimer *tm);
 // kn_reorder_run without an order inside a network (no permutation is left), in fewer trips: where kn_count_pays.
 int64_t kn_count_ws_bytes(int64_t M, int32_t N); // 0 where it does not
 bool kn_count_pays(int64_t M, int32_t N);

@@ -437,10 +437,16 @@ __global__ void __launch_bounds__(OT_THREADS)
 //   go through the networks side by side, so that an atomic instruction meets few lines (one atomic per network by the first
 //   point that counted it: 65,537 points, 10x16x10, this kernel 12 us; 5 like this), which 1,024 threads with a point each do
 //   faster than 256 with four (131,072 points fp32, 16^3 networks 53 -> 51 us a call, 24x20x16 72 -> 70).
+//   STABLE (the permutation is asked for): ranks in the order of the points.  The lanes of a wavefront with the same network are found by ballots, a bit of
+//   the network at a time, and the wavefronts of a workgroup take their turns at the counts in LDS; the counts of the workgroups go to a (workgroup,
+//   network) table, k_table_scan sums them up (and is no launch more: there is nothing to be cleared), and k_place adds what is in front.
 constexpr int RANK_THREADS = 1024, RANK_BINS = 4; // networks per thread whose atomics are in flight together
+// rows of a (workgroup, network) table start on lines
+__host__ __device__ inline int64_t table_stride(int32_t bins) { return (bins + 31) & ~31; }
+template <bool STABLE>
 __global__ void __launch_bounds__(RANK_THREADS)
     k_rank(const float *__restrict__ pts, int64_t M, KnGrid g, const int32_t *__restrict__ cell_net, int32_t *__restrict__ ids, int32_t N,
-           int32_t *__restrict__ counts, uint2 *__restrict__ ranks, float *__restrict__ sigma, float *__restrict__ rgb)
+           int32_t *__restrict__ counts, int32_t *__restrict__ table, uint2 *__restrict__ ranks, float *__restrict__ sigma, float *__restrict__ rgb)
 {
     extern __shared__ int32_t hist[]; // N + 1
     const int64_t i = (int64_t)blockIdx.x * RANK_THREADS + threadIdx.x;
@@ -456,6 +462,29 @@ __global__ void __launch_bounds__(RANK_THREADS)
             sigma[i] = 0.0f;
             rgb[3 * i] = rgb[3 * i + 1] = rgb[3 * i + 2] = 0.0f;
         }
+    }
+    if constexpr (STABLE) {
+        const int lane = threadIdx.x & (KN_WAVE - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE);
+        unsigned long long same = __ballot(active); // (active lanes) with this lane's network
+        for (int b = 0; N >> b; ++b) {
+            const bool bit = (key >> b) & 1;
+            const unsigned long long with = __ballot(bit);
+            same &= bit ? with : ~with;
+        }
+        const int before = __popcll(same & ((1ull << lane) - 1ull));
+        int32_t base = 0;
+        for (int w = 0; w < RANK_THREADS / KN_WAVE; ++w) {
+            __syncthreads();
+            if (w == wv && active && before == 0) { // the first of each network (distinct addresses)
+                base = hist[key];
+                hist[key] = base + __popcll(same);
+            }
+        }
+        __syncthreads();
+        for (int n = threadIdx.x; n <= N; n += RANK_THREADS) table[blockIdx.x * table_stride(N + 1) + n] = hist[n];
+        base = __shfl(base, active ? (int)__builtin_ctzll(same) : 0, KN_WAVE);
+        if (active) ranks[i] = make_uint2((uint32_t)key, (uint32_t)(base + before));
+        return;
     }
     __syncthreads();
     const int32_t rank = active ? atomicAdd(&hist[key], 1) : 0;
@@ -480,7 +509,8 @@ constexpr int PLACE_OWN_TILES = 8;
 constexpr int PLACE_THREADS = 1024, PLACE_WAVES = PLACE_THREADS / KN_WAVE, PLACE_POINTS = 2; // points per thread
 __global__ void __launch_bounds__(PLACE_THREADS)
     k_place(const uint2 *__restrict__ ranks, int64_t M, int32_t N, int32_t per, int32_t tile_len, const int32_t *__restrict__ counts,
-            int32_t *__restrict__ perm, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles, int32_t *__restrict__ n_tiles)
+            const int32_t *__restrict__ table, int32_t *__restrict__ perm, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles,
+            int32_t *__restrict__ n_tiles)
 {
     extern __shared__ int32_t start[];
     __shared__ int32_t s_sum[2][PLACE_WAVES];
@@ -489,6 +519,11 @@ __global__ void __launch_bounds__(PLACE_THREADS)
     uint2 kr[PLACE_POINTS];
 #pragma unroll
     for (int r = 0; r < PLACE_POINTS; ++r) kr[r] = ranks[min(i0 + r * PLACE_THREADS, M - 1)];
+    if (table) { // (uniform) stable ranks: what the workgroups of k_rank in front counted
+#pragma unroll
+        for (int r = 0; r < PLACE_POINTS; ++r)
+            kr[r].y += (uint32_t)table[min(i0 + r * PLACE_THREADS, M - 1) / RANK_THREADS * table_stride(N + 1) + (int32_t)kr[r].x];
+    }
     // exclusive starts of the networks inside the wavefront's share, then across wavefronts (tiles: the same sums, kept for
     // the networks this workgroup writes the tiles of)
     int32_t sum = 0, tile_sum = 0;
@@ -571,8 +606,6 @@ constexpr int64_t COUNT_BACK_M = 5 << 17;
 constexpr int32_t COUNT_MAX_N = 6143;
 constexpr int64_t COUNT_MIN_M = 1 << 17, COUNT_WIDE_M = 5 << 18;
 typedef uint16_t h4_t __attribute__((ext_vector_type(4)));
-// rows of the table start on lines
-__host__ __device__ inline int64_t table_stride(int32_t bins) { return (bins + 31) & ~31; }
 
 // (the same numbering in both kernels: row b of the table)
 __device__ __forceinline__ int32_t xcd_block(int32_t nblk)
@@ -994,32 +1027,34 @@ int kn_reorder_run(const kn_scene *sc, hipStream_t st, const float *points, cons
 // order without passes
 namespace {
 struct OrderWs {
-    int32_t *counts, *n_tiles, *perm;
+    int32_t *counts, *n_tiles, *perm, *table;
     uint2 *ranks;
     KnTile *tiles;
 };
-void carve_order(KnCarver &c, int64_t M, int32_t N, OrderWs &w)
+void carve_order(KnCarver &c, int64_t M, int32_t N, bool stable, OrderWs &w)
 {
     w.n_tiles = c.carve<int32_t>(1);
     w.counts = c.carve<int32_t>(N + 1);
     w.ranks = c.carve<uint2>(M);
-    w.perm = c.carve<int32_t>(M);
+    w.perm = stable ? nullptr : c.carve<int32_t>(M); // (stable: the caller's)
+    w.table = stable ? c.carve<int32_t>(kn_div_up(M, RANK_THREADS) * table_stride(N + 1)) : nullptr;
     w.tiles = c.carve<KnTile>(kn_max_tiles(M, N, 64));
+}
+int64_t order_ws_bytes(int64_t M, int32_t N, bool stable)
+{
+    KnCarver c((void *)256, INT64_MAX / 2);
+    OrderWs w;
+    carve_order(c, M, N, stable, w);
+    return c.used;
 }
 // Every workgroup of k_place scans the counts of all networks, in steps of 1,024, and keeps their starts in LDS.
 constexpr int32_t ORDER_MAX_N = 32768;
 static_assert((ORDER_MAX_N + 1024) * 4 <= 150 * 1024, "the starts of the networks (k_place) fit the LDS of a compute unit");
 constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_FEW = 1 << 17;
-constexpr int32_t ORDER_FEW = 512;
+constexpr int32_t ORDER_FEW = 512, ORDER_STABLE_MAX_N = 16383;
 } // namespace
 
-int64_t kn_order_ws_bytes(int64_t M, int32_t N)
-{
-    KnCarver c((void *)256, INT64_MAX / 2);
-    OrderWs w;
-    carve_order(c, M, N, w);
-    return c.used;
-}
+int64_t kn_order_ws_bytes(int64_t M, int32_t N) { return order_ws_bytes(M, N, false); }
 
 // For batches that do not fill the chip with the radix passes' workgroups: four launches instead of nine (six with up to 255
 // networks), and kernels of many small workgroups.  The evaluation then gathers its points and scatters its results, which
@@ -1038,23 +1073,38 @@ bool kn_order_pays(const kn_scene *sc, int64_t M)
     return sc->N <= ORDER_MAX_N && M <= (sc->N <= ORDER_FEW ? ORDER_MAX_M_FEW : ORDER_MAX_M);
 }
 
+// The stable order, against the radix passes (3,000 / 40,000 / 260,000 / 550,000 points, us, with the ids, the counts and the permutation): 16^3 networks, fp16,
+// 25 / 31 / 47 / 83 against 57 / 66 / 75 / 87, skewed, bf16, 25 / 29 / 48 / 78 against 52 / 65 / 75 / 85; 10x16x10, fp32, 25 / 33 / 64 / 101 (1 M: 155) against
+// 59 / 70 / 104 / 137 (186); 2^3, fp16, 24 / 25 / 29 / 49 against 34 / 36 / 48 / 57; 24x20x28, fp16, 38 / 59 / 79 / 120 (400,000: 94) against 61 / 86 / 95 / 105
+// (100).  In no more workspace than the passes take; with 32^3 networks, whose table is larger, 300 points 60 against 45.
+bool kn_order_stable_pays(const kn_scene *sc, int64_t M)
+{
+    if (sc->N > ORDER_STABLE_MAX_N || order_ws_bytes(M, sc->N, true) > kn_reorder_ws_bytes(M, sc->N)) return false;
+    return M <= (sc->N > 8191 ? 3 << 17 : sc->desc.wdtype == KN_F32 ? 1 << 20 : 1 << 19);
+}
+
 int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_t M, int32_t tile_len, int32_t *user_ids,
-                 int32_t *user_counts, float *sigma, float *rgb, KnCarver &ws, KnBucketOut *out, KnStageTimer *tm)
+                 int32_t *user_counts, int32_t *user_perm, float *sigma, float *rgb, KnCarver &ws, KnBucketOut *out, KnStageTimer *tm)
 {
     const int32_t N = sc->N;
     if (M < 1 || M > (1ll << 30) || N < 1 || N > ORDER_MAX_N || tile_len < 64) return KN_E_INVALID_ARG;
     OrderWs w;
-    carve_order(ws, M, N, w);
+    carve_order(ws, M, N, user_perm != nullptr, w);
     if (!ws.ok()) return KN_E_WORKSPACE;
-    KN_TRY(kn_fill_i32(st, w.counts, N + 1, 0));
+    if (!user_perm) KN_TRY(kn_fill_i32(st, w.counts, N + 1, 0));
     const dim3 grid((unsigned)kn_div_up(M, RANK_THREADS)), block(RANK_THREADS);
-    hipLaunchKernelGGL(k_rank, grid, block, (size_t)(N + 1) * 4, st, points, M, sc->net_grid, sc->cell_net, user_ids, N, w.counts, w.ranks,
+    hipLaunchKernelGGL(user_perm ? k_rank<true> : k_rank<false>, grid, block, (size_t)(N + 1) * 4, st, points, M, sc->net_grid, sc->cell_net, user_ids, N, w.counts, w.table, w.ranks,
                        sigma, rgb);
     KN_CHECK_LAUNCH();
     if (tm) tm->mark(KN_ST_CELL);
+    if (user_perm) {
+        hipLaunchKernelGGL(k_table_scan, dim3((unsigned)kn_div_up(N + 1, TS_NETS)), dim3(1024), 0, st, w.table, N + 1, (int32_t)grid.x, w.counts);
+        KN_CHECK_LAUNCH();
+        w.perm = user_perm;
+    }
     const int32_t per = (int32_t)kn_div_up(N + 1, PLACE_THREADS);
     hipLaunchKernelGGL(k_place, dim3((unsigned)kn_div_up(M, PLACE_THREADS * PLACE_POINTS)), dim3(PLACE_THREADS), (size_t)per * PLACE_THREADS * 4, st,
-                       w.ranks, M, N, per, tile_len, w.counts, w.perm, user_counts, w.tiles, w.n_tiles);
+                       w.ranks, M, N, per, tile_len, w.counts, w.table, w.perm, user_counts, w.tiles, w.n_tiles);
     KN_CHECK_LAUNCH();
     out->perm = w.perm;
     out->counts = w.counts;
@@ -1252,7 +1302,8 @@ int kn_reorder_configure()
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     KN_HIP(hipFuncSetAttribute((const void *)k_reorder_scatter<true>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     const int counts = (COUNT_MAX_N + 1) * 4;
-    KN_HIP(hipFuncSetAttribute((const void *)k_rank, hipFuncAttributeMaxDynamicSharedMemorySize, (ORDER_MAX_N + 1) * 4));
+    KN_HIP(hipFuncSetAttribute((const void *)k_rank<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (ORDER_MAX_N + 1) * 4));
+    KN_HIP(hipFuncSetAttribute((const void *)k_rank<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (ORDER_MAX_N + 1) * 4));
     KN_HIP(hipFuncSetAttribute((const void *)k_place, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)kn_div_up(ORDER_MAX_N + 1, PLACE_THREADS) * PLACE_THREADS * 4));
     constexpr int half = 512 * CO_ROWS * 16, full = 1024 * CO_ROWS * 16;

@@ -1955,3 +1955,36 @@ def test_eval_grouped_on_both_sides_of_the_unordered_lines(wdtype, H, res, point
             kn.profile_enable(0)
         for a, b in zip(got, want):
             assert torch.allclose(a, b, rtol=1e-5, atol=1e-6) if wdtype == "f32" else torch.equal(a, b)
+
+
+@pytest.mark.parametrize("wdtype,H,res,M", [("f16", 32, (1, 1, 1), 1), ("bf16", 32, (2, 2, 2), 1025), ("f16", 32, (16, 16, 16), 1024), ("f32", 32, (5, 8, 5), 4097),
+                                            ("bf16", 64, (10, 16, 10), 65537), ("f16", 32, (24, 20, 28), 33000), ("f32", 64, (15, 17, 16), 20001),
+                                            ("f16", 32, (16, 16, 16), 1 << 19), ("f16", 32, (16, 16, 16), (1 << 19) + 1), ("bf16", 32, (32, 32, 32), 30000)])
+@pytest.mark.parametrize("spread", ["all over", "two networks", "none"])
+def test_eval_grouped_with_its_stable_permutation(wdtype, H, res, M, spread):
+    """ids, counts and the stable permutation as numpy makes them from the ids of kn_cell_ids; results as through the index sort of the static call."""
+    import torch
+    import paper_2103_13744_amd as kn
+    log("eval, stable order", wdtype, H, res, M, spread)
+    dev, _ = make_pair(scene_dict(res, (-1, -1, -1), (1, 1, 1), H, wdtype, 24))
+    pts, dirs = cuda(ks.uniform_points(M, 33, lo=(-1.02,) * 3, hi=(1.02,) * 3)), cuda(ks.sphere_dirs(M, 34))
+    if spread == "two networks":
+        pts = 0.01 + 0.1 / max(res) * pts.abs()
+        pts[::3] -= 0.5
+    if spread == "none":
+        pts += 3.0
+    pts[M // 3, 1] = float("nan")
+    N = int(np.prod(res))
+    ids = dev.cell_ids(pts)
+    key = torch.where(ids < 0, N, ids).cpu().numpy()
+    perm, counts = np.argsort(key, kind="stable"), np.bincount(key, minlength=N + 1)
+    for _ in range(2):
+        out = (torch.full((M,), -7.0, device="cuda"), torch.full((M, 3), -7.0, device="cuda"))
+        got = dev.eval_grouped(pts, dirs, want_aux=True, out=out)
+        assert torch.equal(got[2], ids)
+        np.testing.assert_array_equal(got[3].cpu().numpy(), counts)
+        np.testing.assert_array_equal(got[4].cpu().numpy(), perm)
+    want = (torch.empty(M, device="cuda"), torch.empty((M, 3), device="cuda"))
+    dev.eval_grouped_static(pts, dirs, want)
+    for a, b in zip(got[:2], want):
+        assert torch.allclose(a, b, rtol=1e-5, atol=1e-6) if wdtype == "f32" else torch.equal(a, b)
