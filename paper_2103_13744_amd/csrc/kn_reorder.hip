@@ -504,9 +504,12 @@ __global__ void __launch_bounds__(RANK_THREADS)
     if (active) ranks[i] = make_uint2((uint32_t)key, (uint32_t)(rank + hist[key]));
 }
 
-// Dynamic LDS: PLACE_WAVES * 64 * per ints, the networks' starts; per: steps of 64 networks per wavefront.
-constexpr int PLACE_OWN_TILES = 8;
+// Dynamic LDS: place_lds(per), the networks' starts and per step the tiles in front; per: steps of 64 networks per wavefront.
+// PLACE_AHEAD: steps whose counts are under way together (65,000 points, one after the other / so: 16^3 networks, fp16, 28 / 26 us a call, 24x20x28 55 / 49,
+// 32^3 111 / 96).
+constexpr int PLACE_OWN_TILES = 8, PLACE_AHEAD = 8;
 constexpr int PLACE_THREADS = 1024, PLACE_WAVES = PLACE_THREADS / KN_WAVE, PLACE_POINTS = 2; // points per thread
+constexpr int place_lds(int per) { return (PLACE_THREADS + PLACE_WAVES) * per * 4; }
 __global__ void __launch_bounds__(PLACE_THREADS)
     k_place(const uint2 *__restrict__ ranks, int64_t M, int32_t N, int32_t per, int32_t tile_len, const int32_t *__restrict__ counts,
             const int32_t *__restrict__ table, int32_t *__restrict__ perm, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles,
@@ -515,6 +518,7 @@ __global__ void __launch_bounds__(PLACE_THREADS)
     extern __shared__ int32_t start[];
     __shared__ int32_t s_sum[2][PLACE_WAVES];
     const int lane = threadIdx.x & (KN_WAVE - 1), wv = threadIdx.x / KN_WAVE, b0 = wv * KN_WAVE * per + lane;
+    int32_t *step_tiles = start + PLACE_THREADS * per; // tiles of the wavefront's networks in front of each step
     const int64_t i0 = (int64_t)blockIdx.x * (PLACE_THREADS * PLACE_POINTS) + threadIdx.x;
     uint2 kr[PLACE_POINTS];
 #pragma unroll
@@ -527,14 +531,23 @@ __global__ void __launch_bounds__(PLACE_THREADS)
     // exclusive starts of the networks inside the wavefront's share, then across wavefronts (tiles: the same sums, kept for
     // the networks this workgroup writes the tiles of)
     int32_t sum = 0, tile_sum = 0;
-    for (int s = 0; s < per; ++s) {
-        const int32_t n = b0 + s * KN_WAVE, c = n <= N ? counts[n] : 0;
-        const int32_t inc = kn_wave_inclusive_scan(c);
-        start[n] = sum + inc - c;
-        sum += __builtin_amdgcn_readlane(inc, KN_WAVE - 1);
-        const int32_t t = n < N ? (c + tile_len - 1) / tile_len : 0;
-        tile_sum += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(t), KN_WAVE - 1);
-        if (user_counts && n <= N && blockIdx.x == 0) user_counts[n] = c;
+    for (int s0 = 0; s0 < per; s0 += PLACE_AHEAD) {
+        int32_t c_ahead[PLACE_AHEAD];
+#pragma unroll
+        for (int q = 0; q < PLACE_AHEAD; ++q) c_ahead[q] = counts[min(b0 + (s0 + q) * KN_WAVE, N)];
+#pragma unroll
+        for (int q = 0; q < PLACE_AHEAD; ++q) {
+            const int s = s0 + q;
+            if (s >= per) break; // (uniform)
+            const int32_t n = b0 + s * KN_WAVE, c = n <= N ? c_ahead[q] : 0;
+            const int32_t inc = kn_wave_inclusive_scan(c);
+            start[n] = sum + inc - c;
+            sum += __builtin_amdgcn_readlane(inc, KN_WAVE - 1);
+            const int32_t t = n < N ? (c + tile_len - 1) / tile_len : 0;
+            if (lane == 0) step_tiles[wv * per + s] = tile_sum;
+            tile_sum += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(t), KN_WAVE - 1);
+            if (user_counts && n <= N && blockIdx.x == 0) user_counts[n] = c;
+        }
     }
     if (lane == 0) {
         s_sum[0][wv] = sum;
@@ -557,24 +570,22 @@ __global__ void __launch_bounds__(PLACE_THREADS)
         if (i < M) perm[start[kr[r].x] + (int32_t)kr[r].y] = (int32_t)i;
     }
     // tiles: those of step s of wavefront w are written by workgroup (w * per + s) % gridDim.x
-    for (int s = 0; s < per; ++s) {
+    const int grid = (int)gridDim.x, first_s = ((int)blockIdx.x - wv * per % grid + grid) % grid;
+    for (int s = first_s; s < per; s += grid) { // (uniform)
         const int32_t n = b0 + s * KN_WAVE, c = n <= N ? counts[n] : 0, t = n < N ? (c + tile_len - 1) / tile_len : 0;
-        const int32_t inc = kn_wave_inclusive_scan(t);
-        if ((wv * per + s) % (int)gridDim.x == (int)blockIdx.x) { // (uniform)
-            // a lane writes its own network's tiles, the wavefront together those of a network with many (one network after
-            // the other for all 64 took 5 of this kernel's 14 us at 65,537 points)
-            if (t <= PLACE_OWN_TILES) {
-                const int32_t first = n <= N ? start[n] : 0;
-                for (int32_t k = 0; k < t; ++k) tiles[tiles_before + inc - t + k] = KnTile{n, first + k * tile_len, min(tile_len, c - k * tile_len), 0};
-            }
-            for (unsigned long long many = __ballot(t > PLACE_OWN_TILES); many; many &= many - 1) { // (uniform)
-                const int q = (int)__builtin_ctzll(many);
-                const int32_t tq = __builtin_amdgcn_readlane(t, q), base = tiles_before + __builtin_amdgcn_readlane(inc, q) - tq;
-                const int32_t nq = n - lane + q, cq = __builtin_amdgcn_readlane(c, q), first = start[nq];
-                for (int32_t k = lane; k < tq; k += KN_WAVE) tiles[base + k] = KnTile{nq, first + k * tile_len, min(tile_len, cq - k * tile_len), 0};
-            }
+        const int32_t inc = kn_wave_inclusive_scan(t), in_front = tiles_before + step_tiles[wv * per + s];
+        // a lane writes its own network's tiles, the wavefront together those of a network with many (one network after
+        // the other for all 64 took 5 of this kernel's 14 us at 65,537 points)
+        if (t <= PLACE_OWN_TILES) {
+            const int32_t first = n <= N ? start[n] : 0;
+            for (int32_t k = 0; k < t; ++k) tiles[in_front + inc - t + k] = KnTile{n, first + k * tile_len, min(tile_len, c - k * tile_len), 0};
         }
-        tiles_before += __builtin_amdgcn_readlane(inc, KN_WAVE - 1);
+        for (unsigned long long many = __ballot(t > PLACE_OWN_TILES); many; many &= many - 1) { // (uniform)
+            const int q = (int)__builtin_ctzll(many);
+            const int32_t tq = __builtin_amdgcn_readlane(t, q), base = in_front + __builtin_amdgcn_readlane(inc, q) - tq;
+            const int32_t nq = n - lane + q, cq = __builtin_amdgcn_readlane(c, q), first = start[nq];
+            for (int32_t k = lane; k < tq; k += KN_WAVE) tiles[base + k] = KnTile{nq, first + k * tile_len, min(tile_len, cq - k * tile_len), 0};
+        }
     }
 }
 
@@ -1049,7 +1060,7 @@ int64_t order_ws_bytes(int64_t M, int32_t N, bool stable)
 }
 // Every workgroup of k_place scans the counts of all networks, in steps of 1,024, and keeps their starts in LDS.
 constexpr int32_t ORDER_MAX_N = 32768;
-static_assert((ORDER_MAX_N + 1024) * 4 <= 150 * 1024, "the starts of the networks (k_place) fit the LDS of a compute unit");
+static_assert(place_lds((ORDER_MAX_N + PLACE_THREADS) / PLACE_THREADS) <= 150 * 1024, "the starts of the networks (k_place) fit the LDS of a compute unit");
 constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_FEW = 1 << 17;
 constexpr int32_t ORDER_FEW = 512, ORDER_STABLE_MAX_N = 16383;
 } // namespace
@@ -1103,7 +1114,7 @@ int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_
         w.perm = user_perm;
     }
     const int32_t per = (int32_t)kn_div_up(N + 1, PLACE_THREADS);
-    hipLaunchKernelGGL(k_place, dim3((unsigned)kn_div_up(M, PLACE_THREADS * PLACE_POINTS)), dim3(PLACE_THREADS), (size_t)per * PLACE_THREADS * 4, st,
+    hipLaunchKernelGGL(k_place, dim3((unsigned)kn_div_up(M, PLACE_THREADS * PLACE_POINTS)), dim3(PLACE_THREADS), (size_t)place_lds(per), st,
                        w.ranks, M, N, per, tile_len, w.counts, w.table, w.perm, user_counts, w.tiles, w.n_tiles);
     KN_CHECK_LAUNCH();
     out->perm = w.perm;
@@ -1305,7 +1316,7 @@ int kn_reorder_configure()
     KN_HIP(hipFuncSetAttribute((const void *)k_rank<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (ORDER_MAX_N + 1) * 4));
     KN_HIP(hipFuncSetAttribute((const void *)k_rank<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (ORDER_MAX_N + 1) * 4));
     KN_HIP(hipFuncSetAttribute((const void *)k_place, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)kn_div_up(ORDER_MAX_N + 1, PLACE_THREADS) * PLACE_THREADS * 4));
+                               place_lds((int)kn_div_up(ORDER_MAX_N + 1, PLACE_THREADS))));
     constexpr int half = 512 * CO_ROWS * 16, full = 1024 * CO_ROWS * 16;
     KN_HIP(hipFuncSetAttribute((const void *)k_results_back<512>, hipFuncAttributeMaxDynamicSharedMemorySize, half));
     KN_HIP(hipFuncSetAttribute((const void *)k_results_back<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, full));
