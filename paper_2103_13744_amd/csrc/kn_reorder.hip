@@ -1062,7 +1062,7 @@ int64_t order_ws_bytes(int64_t M, int32_t N, bool stable)
 constexpr int32_t ORDER_MAX_N = 32768;
 static_assert(place_lds((ORDER_MAX_N + PLACE_THREADS) / PLACE_THREADS) <= 150 * 1024, "the starts of the networks (k_place) fit the LDS of a compute unit");
 constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_FEW = 1 << 17;
-constexpr int32_t ORDER_FEW = 512, ORDER_STABLE_MAX_N = 16383;
+constexpr int32_t ORDER_FEW = 512, ORDER_STABLE_MAX_N = 24575;
 } // namespace
 
 int64_t kn_order_ws_bytes(int64_t M, int32_t N) { return order_ws_bytes(M, N, false); }
@@ -1087,7 +1087,8 @@ bool kn_order_pays(const kn_scene *sc, int64_t M)
 // The stable order, against the radix passes (3,000 / 40,000 / 260,000 / 550,000 points, us, with the ids, the counts and the permutation): 16^3 networks, fp16,
 // 25 / 31 / 47 / 83 against 57 / 66 / 75 / 87, skewed, bf16, 25 / 29 / 48 / 78 against 52 / 65 / 75 / 85; 10x16x10, fp32, 25 / 33 / 64 / 101 (1 M: 155) against
 // 59 / 70 / 104 / 137 (186); 2^3, fp16, 24 / 25 / 29 / 49 against 34 / 36 / 48 / 57; 24x20x28, fp16, 38 / 59 / 79 / 120 (400,000: 94) against 61 / 86 / 95 / 105
-// (100).  In no more workspace than the passes take; with 32^3 networks, whose table is larger, 300 points 60 against 45.
+// (100).  In no more workspace than the passes take, which is the limit for more than some 17,000 networks; 28^3 networks, 1,000 / 4,000 points 42 / 44
+// against 51 / 67; 32^3, 200 points (not taken) 53 against 47.
 bool kn_order_stable_pays(const kn_scene *sc, int64_t M)
 {
     if (sc->N > ORDER_STABLE_MAX_N || order_ws_bytes(M, sc->N, true) > kn_reorder_ws_bytes(M, sc->N)) return false;

@@ -1959,7 +1959,7 @@ def test_eval_grouped_on_both_sides_of_the_unordered_lines(wdtype, H, res, point
 
 @pytest.mark.parametrize("wdtype,H,res,M", [("f16", 32, (1, 1, 1), 1), ("bf16", 32, (2, 2, 2), 1025), ("f16", 32, (16, 16, 16), 1024), ("f32", 32, (5, 8, 5), 4097),
                                             ("bf16", 64, (10, 16, 10), 65537), ("f16", 32, (24, 20, 28), 33000), ("f32", 64, (15, 17, 16), 20001),
-                                            ("f16", 32, (16, 16, 16), 1 << 19), ("f16", 32, (16, 16, 16), (1 << 19) + 1), ("bf16", 32, (32, 32, 32), 30000)])
+                                            ("f16", 32, (16, 16, 16), 1 << 19), ("f16", 32, (16, 16, 16), (1 << 19) + 1), ("bf16", 32, (28, 28, 28), 4000), ("bf16", 32, (32, 32, 32), 30000)])
 @pytest.mark.parametrize("spread", ["all over", "two networks", "none"])
 def test_eval_grouped_with_its_stable_permutation(wdtype, H, res, M, spread):
     """ids, counts and the stable permutation as numpy makes them from the ids of kn_cell_ids; results as through the index sort of the static call."""
