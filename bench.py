@@ -226,14 +226,14 @@ def isolated_mlp(kn, torch, wdtype, iters=10, skewed=False, layered=True):
         del ws_l
     # Re-ordering stage (everything between the cell ids and the MLP kernel, scan of the count table and the samples' one trip,
     # and after the MLP kernel the results' way back).  Algorithmic bytes per point = what a physical re-ordering of the batch has to
-    # move once: key 4 + position and direction 24 read, one 32-byte record written, results 16 read and 16 written = 92.
-    # What the kernels of batches of this size really move: k_count_scatter reads a 2-byte key and 24, writes 32 and the
+    # move once: key 4 + position and direction 24 read, 24 written, results 16 read and 16 written = 84.
+    # What the kernels of batches of this size really move: k_count_scatter reads a 2-byte key and 24, writes 24 and the
     # sample's two places (4 + 2); k_results_back reads those and 16, writes 16; the count table, a word per network and
     # workgroup of 8,192 points, is read and written by the scan and read again.  (k_keys_count is in ms_cell_ids.)  The figure a
     # sort of indices alone would be charged with, 16 per key (the definition this line used while the stage sorted
     # indices), is kept beside it.
-    moved = 26.0 + 38.0 + 38.0 + 3 * 4.0 * (scene.N + 1) / 8192
-    mlp_bytes = 48.0 * M + scene.N * NETWORK_BYTES_16BIT[sc["hidden"]]  # record read, result written; every network's weights once
+    moved = 26.0 + 30.0 + 38.0 + 3 * 4.0 * (scene.N + 1) / 8192
+    mlp_bytes = 40.0 * M + scene.N * NETWORK_BYTES_16BIT[sc["hidden"]]  # record read, result written; every network's weights once
     t_bucket = prof["ms_bucket"] / iters * 1e-3
     return {"workload": ("cfg4: 2^23 points, 90 %% in 5 %% of the cells, 16^3 networks, %s" if skewed else
                          "cfg2: 2^22 points, 16^3 networks, %s") % wdtype, "points": M, "points_per_sec": M / (dt_s / iters),
@@ -250,13 +250,13 @@ def isolated_mlp(kn, torch, wdtype, iters=10, skewed=False, layered=True):
                                           "mfma_bf16_tflops" if wdtype == "bf16" else "mfma_f16_tflops"),
             "roofline_bucket": with_measured({"kernel": "k_table_scan + k_count_scatter + k_results_back (samples ordered by counting, "
                                                         "results back in caller order)",
-                                              "bound": "hbm", "achieved": 92.0 * M / t_bucket / 1e9,
+                                              "bound": "hbm", "achieved": 84.0 * M / t_bucket / 1e9,
                                               "peak": PEAK_HBM / 1e9, "unit": "GB/s",
-                                              "frac": 92.0 * M / t_bucket / PEAK_HBM, "traffic": None,
-                                              "bytes_per_point_algorithmic": 92, "bytes_per_point_moved": moved,
+                                              "frac": 84.0 * M / t_bucket / PEAK_HBM, "traffic": None,
+                                              "bytes_per_point_algorithmic": 84, "bytes_per_point_moved": moved,
                                               "moved_gbps": moved * M / t_bucket / 1e9},
                                              "hbm_copy_gbps"),
-            "bucket_gbps_algorithmic": 92.0 * M / t_bucket / 1e9,
+            "bucket_gbps_algorithmic": 84.0 * M / t_bucket / 1e9,
             "bucket_gbps_at_16_bytes_per_key": 16.0 * M / t_bucket / 1e9,
             # kn_bucket alone (index sort): key read by the count and by the scatter of each of the two passes, key and
             # index written by each scatter, index read by the second: counted as 16 B per key
@@ -423,7 +423,7 @@ def measure_render(kn, torch, np, configs, cfg, wdtype, steps, warmup, poses, tr
         s_ = p["ms_mlp"] * 1e-3
         tf = FLOP_PER_SAMPLE[H] * n["evaluated"] / s_ / 1e12 if s_ > 0 else 0.0
         kernel = "k_render_fused (march, grouping, MLP and blend of a frame)" if one_kernel else "k_mlp_mfma (fused grouped MLP)"
-        r = {"kernel": "k_mlp_f32 (fused grouped MLP, fp32 MFMA)" if f32 else kernel, "bound": "mfma",
+        r = {"kernel": "k_mlp_f32 (fused grouped MLP, fp32 MFMA)" if f32 and not one_kernel else kernel, "bound": "mfma",
              "achieved": tf, "peak": mfma_peak / 1e12, "unit": "TFLOP/s", "frac": tf * 1e12 / mfma_peak,
              "traffic": traffic.get("k_render_fused" if one_kernel else "k_mlp_mfma"), "avg_launch_ms": p["ms_mlp"] / max(n["launches"], 1), "launches": n["launches"],
              "frames_with_events": n["frames"], "samples_per_launch": n["evaluated"] / max(n["launches"], 1),
