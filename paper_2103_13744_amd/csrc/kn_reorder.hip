@@ -618,6 +618,20 @@ constexpr int32_t COUNT_MAX_N = 6143;
 constexpr int64_t COUNT_MIN_M = 1 << 17, COUNT_WIDE_M = 5 << 18;
 typedef uint16_t h4_t __attribute__((ext_vector_type(4)));
 
+// Non-temporal: what a workgroup reads once stays out of the way of the lines that the workgroups of an XCD fill and read together in its L2.  4 M points,
+// 16^3 networks: k_count_scatter 68 -> 63 us, the MLP kernel 80 -> 77, k_results_back 40 -> 37; 8 M skewed 118 -> 108, 151 -> 147, 76 -> 73.  (With
+// 512 threads, whose batches fit the caches, 0.3 us slower; non-temporal stores of the results 38 -> 67.)
+template <bool STREAM, typename V> __device__ __forceinline__ V load_once(const V *p)
+{
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool STREAM, typename V> __device__ __forceinline__ void store_once(V *p, V v)
+{
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // (the same numbering in both kernels: row b of the table)
 __device__ __forceinline__ int32_t xcd_block(int32_t nblk)
 {
@@ -729,6 +743,7 @@ __global__ void __launch_bounds__(T)
                     const int32_t *__restrict__ totals, int32_t tile_len, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles,
                     int32_t *__restrict__ n_tiles, uint32_t *__restrict__ at, uint16_t *__restrict__ from, float *__restrict__ out4)
 {
+    constexpr bool STREAM = T == 1024;
     extern __shared__ u4 stage[];
     __shared__ int32_t s_sum[3][T / KN_WAVE];
     __shared__ int4 s_list[co_list(T)]; // (network, samples, first sample, first tile)
@@ -745,9 +760,9 @@ __global__ void __launch_bounds__(T)
 #pragma unroll
     for (int r = 0; r < CO_ROWS; ++r) {
         const int64_t i = base + min(r * T + (int)threadIdx.x, n_here - 1);
-        key[r] = keys[i];
+        key[r] = load_once<STREAM>(keys + i);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) p[r][c] = pts[3 * i + c];
+        for (int c = 0; c < 3; ++c) p[r][c] = load_once<STREAM>(pts + 3 * i + c);
     }
     __syncthreads();
     int32_t lpos[CO_ROWS];
@@ -800,7 +815,7 @@ __global__ void __launch_bounds__(T)
         const int64_t i = base + min(r * T + (int)threadIdx.x, n_here - 1);
         if (!BACK && key[r] == (uint32_t)N) *(float4 *)(out4 + 4 * i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) p[r][c] = dirs[3 * i + c];
+        for (int c = 0; c < 3; ++c) p[r][c] = load_once<STREAM>(dirs + 3 * i + c);
     }
     __syncthreads();
     // BACK: a sample's result goes to its own place, and its halves need no fourth word
@@ -816,7 +831,7 @@ __global__ void __launch_bounds__(T)
             const u4 v = stage[sp];
             dst[k] = sp + delta[v[3]];
             put(pout, dst[k], v);
-            if constexpr (BACK) at[base + sp] = (uint32_t)dst[k];
+            if constexpr (BACK) store_once<STREAM>(at + base + sp, (uint32_t)dst[k]);
             // no network: the result is zero
             if (BACK && v[3] == (uint32_t)N) *(float4 *)(out4 + 4 * (int64_t)dst[k]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
@@ -832,7 +847,7 @@ __global__ void __launch_bounds__(T)
         const int32_t sp = k * T + threadIdx.x;
         if (sp < n_here) {
             u4 v = stage[sp];
-            if constexpr (BACK) from[base + sp] = (uint16_t)v[3];
+            if constexpr (BACK) store_once<STREAM>(from + base + sp, (uint16_t)v[3]);
             else v[3] += (uint32_t)base; // the place in the caller's order
             put(dout, dst[k], v);
         }
@@ -865,6 +880,7 @@ __global__ void __launch_bounds__(T)
     k_results_back(const float *__restrict__ out4, const uint32_t *__restrict__ at, const uint16_t *__restrict__ from, int64_t M, int32_t nblk,
                    float *__restrict__ sigma, float *__restrict__ rgb)
 {
+    constexpr bool STREAM = T == 1024;
     extern __shared__ u4 stage[]; // T * CO_ROWS results
     const int64_t base = (int64_t)xcd_block(nblk) * (T * CO_ROWS);
     const int32_t n_here = (int32_t)min((int64_t)(T * CO_ROWS), M - base);
@@ -873,8 +889,8 @@ __global__ void __launch_bounds__(T)
 #pragma unroll
     for (int k = 0; k < CO_ROWS; ++k) {
         const int64_t i = base + min(k * T + (int)threadIdx.x, n_here - 1);
-        a[k] = at[i];
-        f[k] = from[i];
+        a[k] = load_once<STREAM>(at + i);
+        f[k] = load_once<STREAM>(from + i);
     }
 #pragma unroll
     for (int k = 0; k < CO_ROWS; ++k) v[k] = *(const u4 *)(out4 + 4 * (int64_t)a[k]);
