@@ -70,6 +70,7 @@ struct FusedArgs {
     const void *packed;
     const float *rays_o, *rays_d;
     int32_t max_lg;    // log2 of the rays of a full pool
+    int32_t late_lg, late_s; // when there is no ray left to be taken: log2 of the places that a pool keeps, samples per ray and round
     int32_t few_rays;  // a workgroup starts with fewer wavefronts where its wavefronts would get fewer rays than this
     int32_t R, own_rays, own_group; // own_rays > 0: a workgroup sets up that many rays by itself, groups of own_group, and there is no list
     const int4 *list;  // live rays: (ray, first lattice index, end of the clipped range, -)
@@ -314,7 +315,8 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
             }
             // ---- the rays that are left move together, so that each gets more lanes and more slots
             int lg = lgP;
-            while (lg > Net::MIN_LG && n <= (1 << (lg - 1))) --lg;
+            const int late_lg = Net::LONG_ROUNDS ? args->late_lg : Net::MIN_LG;
+            while (lg > late_lg && n <= (1 << (lg - 1))) --lg;
             if (lg < lgP) {
                 if ((live >> ln) & 1ull) idx[__popcll(live & ((1ull << ln) - 1ull))] = (uint16_t)ln; // (a leading lane is its place's number)
                 wave_sync();
@@ -334,7 +336,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
             }
         }
         const int P = 1 << lgP, G = KN_WAVE >> lgP;
-        const int S_max = min(Net::SLOTS >> lgP, Net::MAX_S);
+        const int S_max = min(Net::SLOTS >> lgP, Net::LONG_ROUNDS && at >= end && !more ? args->late_s : Net::MAX_S);
         const unsigned long long firsts = lanes_below(P); // lanes that lead a ray's group
         int cnt = 0;
         {
@@ -658,6 +660,20 @@ template <class Net> int fused_launch(const kn_scene *sc, hipStream_t st, const 
     const float points = fminf(a.p.net.cell[0], fminf(a.p.net.cell[1], a.p.net.cell[2])) / a.p.step;
     a.few_rays = points < 2.0f && job.R > 12288 ? 4 : 1;
     a.own_rays = job.list ? 0 : (int32_t)(a.own_group * kn_div_up(job.R, a.own_group * blocks));
+    // Small frames, where every wavefront has its few rays from the start and the chip is not full: longer rounds, where a round's samples are in few
+    // networks or none is evaluated in vain.  32 / 64 samples of a ray in pools of four / 128 of two, us: 16^3 networks, 18.5 points in a
+    // cell, 140x77 56 / 51 / 49, 27.7 points 70 / 61 / 54, 37 points 97 / 84 / 80, width 64, 37 points 98 / 92 / 85; 9.2 points 91 / 96 / 103, sparse 4.6
+    // points 57 / 61 / 64; fp32 (not taken), 18.5 points 82 / 81 / 92; without termination 89x87, 37 points 101 / 84 / 72, 6.2 points 51 / 48.5 / 48.
+    // (Frames behind a list: no change, sparse ones 3 % slower.)
+    a.late_lg = Net::MIN_LG;
+    a.late_s = Net::MAX_S;
+    if (a.own_rays > 0) {
+        if (a.eps == 0.0f || points >= 24.0f) {
+            a.late_lg = Net::MIN_LG - 1;
+            a.late_s = 4 * Net::MAX_S;
+        } else if (points >= 12.0f)
+            a.late_s = 2 * Net::MAX_S;
+    }
     const size_t lds = waves * sizeof(WaveLds<Net>) + a.own_rays * sizeof(int4);
     const FusedFn<Net> kernel = job.strat ? k_render_fused<Net, true> : k_render_fused<Net, false>;
     const dim3 grid((unsigned)blocks), block(waves * KN_WAVE);
