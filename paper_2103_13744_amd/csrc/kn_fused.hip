@@ -23,7 +23,7 @@ template <int H, bool BF, bool WRAP> struct Net16 {
     static constexpr int LARGE_POOLS_BELOW = H == 32 ? 256 : 512;
     static constexpr bool LARGE_POOLS_LATE = H == 32;
     static constexpr int SHARE_LATER = 1;
-    static constexpr bool LONG_ROUNDS = true; // small frames (fused_launch)
+    static constexpr int64_t LONG_ROUNDS_BELOW = H == 32 ? 400000 : KN_FUSED_OWN_RAYS + 1; // rays (fused_launch)
     static constexpr bool CHUNKS = H == 32; // how rays beyond the first pools are handed out (CHUNK_SHARE)
     // A round's march ends when fewer than half of the pool's rays have this little of their slots filled: at width 32 a second step
     // for the rest of a ray's slots is mostly thrown away; at width 64, where a visit of a network costs more, it pays.

@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
             }
             // ---- the rays that are left move together, so that each gets more lanes and more slots
             int lg = lgP;
-            const int late_lg = Net::LONG_ROUNDS ? args->late_lg : Net::MIN_LG;
+            const int late_lg = Net::LONG_ROUNDS_BELOW > 0 ? args->late_lg : Net::MIN_LG;
             while (lg > late_lg && n <= (1 << (lg - 1))) --lg;
             if (lg < lgP) {
                 if ((live >> ln) & 1ull) idx[__popcll(live & ((1ull << ln) - 1ull))] = (uint16_t)ln; // (a leading lane is its place's number)
@@ -336,7 +336,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
             }
         }
         const int P = 1 << lgP, G = KN_WAVE >> lgP;
-        const int S_max = min(Net::SLOTS >> lgP, Net::LONG_ROUNDS && at >= end && !more ? args->late_s : Net::MAX_S);
+        const int S_max = min(Net::SLOTS >> lgP, Net::LONG_ROUNDS_BELOW > 0 && at >= end && !more ? args->late_s : Net::MAX_S);
         const unsigned long long firsts = lanes_below(P); // lanes that lead a ray's group
         int cnt = 0;
         {
@@ -664,10 +664,11 @@ template <class Net> int fused_launch(const kn_scene *sc, hipStream_t st, const 
     // networks or none is evaluated in vain.  32 / 64 samples of a ray in pools of four / 128 of two, us: 16^3 networks, 18.5 points in a
     // cell, 140x77 56 / 51 / 49, 27.7 points 70 / 61 / 54, 37 points 97 / 84 / 80, width 64, 37 points 98 / 92 / 85; 9.2 points 91 / 96 / 103, sparse 4.6
     // points 57 / 61 / 64; fp32 (not taken), 18.5 points 82 / 81 / 92; without termination 89x87, 37 points 101 / 84 / 72, 6.2 points 51 / 48.5 / 48.
-    // (Frames behind a list: no change, sparse ones 3 % slower.)
+    // Behind a list (the last rays of each wavefront; 32 samples / so): width 32, 228x225, 37 points 108 / 95, 260x192 without termination 113 / 101,
+    // 425x316, 27.7 points 127 / 117, 800x800 no change; width 64, 288x290, 59 points 190 / 181, but 409x230, 24.6 points 190 / 200.
     a.late_lg = Net::MIN_LG;
     a.late_s = Net::MAX_S;
-    if (a.own_rays > 0) {
+    if (job.R < Net::LONG_ROUNDS_BELOW) {
         if (a.eps == 0.0f || points >= 24.0f) {
             a.late_lg = Net::MIN_LG - 1;
             a.late_s = 4 * Net::MAX_S;

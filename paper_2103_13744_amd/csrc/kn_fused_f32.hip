@@ -15,7 +15,8 @@ template <int H> struct Net32 {
     static constexpr int SLOTS = 256, MIN_LG = 2, MAX_LG = 4, MAX_S = 32;
     static constexpr int WAVES_PER_SIMD = 2, MAX_WAVES = 4 * WAVES_PER_SIMD;
     static constexpr int LARGE_POOLS_BELOW = 0x7fffffff, SHARE_LATER = 4;
-    static constexpr bool LARGE_POOLS_LATE = false, CHUNKS = false, LONG_ROUNDS = false;
+    static constexpr bool LARGE_POOLS_LATE = false, CHUNKS = false;
+    static constexpr int64_t LONG_ROUNDS_BELOW = 0;
     static constexpr int NEED_QUARTERS = 4;
 
     static __device__ __forceinline__ void place_direction(const float (&)[3], u4 *) {}
