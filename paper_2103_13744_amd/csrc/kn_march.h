@@ -260,6 +260,11 @@ inline VoxelFast voxel_fast(const KnGrid &g)
 // k_hi); no index in front of it can be a kept sample.  From a point whose block has distance D to the nearest occupied block the
 // ray jumps out of the empty cube of blocks around it ((2 D - 1)^3 of them, wherever in its block the point is), where skip_to_content
 // jumps by the radius of the ball that is empty around every point of the block: half as many dependent look-ups.
+// The place f in the block is counted from the block that was looked up.  Next to a block's face Eq. 6 and the approximate u may put
+// the point on different sides; the fraction of u would then be a whole block off, and the jump with it.  Counted like this (the
+// difference is exact, and the clamp moves it towards the face that Eq. 6 saw the point at) f is as wrong as u is, less than guard / 4 =
+// 5e-8 (A + res + 1) of a block (voxel_fast), and that, with the rounding of both points, is inside the margin: a thousandth of the
+// shortest block's edge plus 4e-6 of the box plus 1e-6 of the origin, of which the rounding takes 2^-23 (box + |o|) twice.
 // exact(x, y, z, ix, iy, iz): Eq. 6 with its divisions, for points within rounding of a voxel's face.
 template <bool STRAT, typename Exact>
 __device__ __forceinline__ int32_t walk_to_content(const MarchParams &p, const VoxelFast &g, const float o[3], const float d[3], int32_t k,
@@ -281,10 +286,11 @@ __device__ __forceinline__ int32_t walk_to_content(const MarchParams &p, const V
         }
         const int32_t dist = p.skip_dist[mad24(mad24(ix >> 2, p.skip_res[1], iy >> 2), p.skip_res[2], iz >> 2)];
         if (dist < 2) break;
+        const float block[3] = {(float)(ix >> 2), (float)(iy >> 2), (float)(iz >> 2)};
         float steps = INFINITY;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const float f = __builtin_amdgcn_fractf(u[a] * (1.0f / KN_SKIP_BLOCK));
+            const float f = __builtin_amdgcn_fmed3f(fmaf(u[a], 1.0f / KN_SKIP_BLOCK, -block[a]), 0.0f, 1.0f);
             steps = fminf(steps, ((float)dist - margin - (d[a] > 0.0f ? f : 1.0f - f)) * per_block[a]);
         }
         // (stratified: point k + j lies up to j + 1 steps from point k; saturated, the sum below would wrap)

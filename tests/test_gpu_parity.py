@@ -2004,3 +2004,36 @@ def test_small_frames_in_long_rounds_equal_the_wave_loop(wdtype, H, K, eps, rays
     args = (4.0 - math.sqrt(3.0), 2 * math.sqrt(3.0) / K, K, eps, (1.0, 1.0, 1.0))
     waves, st = dev.render(o, d, *args, want_stats=True, seed=seed)
     assert torch.equal(dev.render(o, d, *args, seed=seed), waves) and (rays < 100 or st["samples_blended"] > rays)
+
+
+@pytest.mark.parametrize("wdtype,H", [("f16", 32), ("bf16", 64), ("f32", 32)])
+@pytest.mark.parametrize("n", [96, 120, 144, 160, 192])
+@pytest.mark.parametrize("rays", [4096, 33000])
+@pytest.mark.parametrize("seed", [None, 7])
+def test_bundles_of_rays_with_lattice_points_on_the_faces_of_voxels(wdtype, H, n, rays, seed):
+    """Parallel rays along each axis whose first lattice points are on the faces of voxels and of blocks of 4^3: there Eq. 6 (with its
+    roundings) and the exact quotient may name different voxels.  Every seventh layer of blocks is occupied, as are two corners (so that
+    the range that is walked is long).  No content is jumped over: the counted call's bits, with the walk inside and in front."""
+    import torch
+    log("rays on faces", wdtype, H, n, rays, seed)
+    K, voxel = 384, 2.0 / n
+    step = 2 * math.sqrt(3.0) / K
+    at = 63 * H + H + H * H + H
+    m = torch.arange(rays, device="cuda") % (2 * n + 1)
+    across = torch.rand((rays, 3), generator=torch.Generator().manual_seed(n)).cuda() * 1.98 - 0.99
+    for axis in range(3):
+        occ = np.zeros((n, n, n), np.uint8)
+        np.moveaxis(occ, axis, 0)[(np.arange(n) + 4 * axis) % 28 < 3] = 1
+        occ[0, 0, 0] = occ[-1, -1, -1] = 1
+        sc = scene_dict((4, 4, 4), (-1, -1, -1), (1, 1, 1), H, wdtype, 14, occ=occ)
+        sc["weights"][:, at + H * (H + 1)] = 8.0          # the density's bias: every point inside is seen
+        dev, _ = make_pair(sc)
+        t_near = float(np.float32((4 + 16 * axis) * voxel - 0.5 * step))
+        for sign in (1.0, -1.0):
+            o, d = across.clone(), torch.zeros_like(across)
+            o[:, axis], d[:, axis] = ((m.double() / n - 1.0) * sign).float(), sign
+            args = (t_near, step, K, 0.0, (0.2, 0.4, 0.6))
+            waves, st = dev.render(o, d, *args, want_stats=True, seed=seed)
+            got = dev.render(o, d, *args, seed=seed)
+            assert st["samples_blended"] > rays
+            assert torch.equal(got, waves), "%d of %d pixels differ along axis %d, sign %g" % ((got != waves).any(dim=1).sum(), rays, axis, sign)
