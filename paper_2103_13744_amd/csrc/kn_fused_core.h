@@ -7,13 +7,13 @@
 // for the next round; free places are filled with the next rays of the live list.  Samples, results and encoded
 // directions never leave the LDS, a frame needs no slot buffers, no histogram and no host decision in the middle, and a
 // ray stops within S samples of its termination point.  Against the wave loop (march, group, evaluate and blend kernels
-// per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 57 us; 800x800 230 -> 164; 1080p,
+// per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 52 us; 800x800 230 -> 164; 1080p,
 // width 64, 1430 -> 1025.  Frames of up to 32,767 rays are this kernel alone: a workgroup also clips its rays and walks them to their
 // first lattice point near content (200x151: 67 us with two launches in front of it).
 //
 // What bounds it: vector-ALU issue while there is work (a march step of 256 points takes about 300 instructions, a tile of 16
 // samples about 65, a round about 350 besides), and the end of a frame, when the rays that are left are few.  The rays' costs differ
-// (most end within two rounds, some take ten) and neighbours cost alike, so a workgroup is all of a compute unit's wavefronts, whose
+// (most end within two rounds, some take ten) and neighbours cost alike, so behind a list a workgroup is all of a compute unit's wavefronts, whose
 // first pools lie in as many parts of the list, and who share their last rays through the LDS: workgroups of four
 // wavefronts, all places in a list filled by an atomic per wavefront and round, 203 us at 800x800 (call, with the set-up's 31), 181
 // at 767x577 stratified, 1,093 at 1080p, width 64; like this 164, 148 and 1,038.  Tried and slower: contiguous pieces of the list
@@ -46,8 +46,10 @@ enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last
 // rays that are under way at the same time lie closer together).
 constexpr int CHUNK_SHARE = 8, CHUNK_MIN = 16, CHUNK_MAX = 512;
 // Rays in a row that a workgroup which sets up its own rays takes together: some eight groups per workgroup, so that those rays that
-// meet content are spread evenly, of rays that meet the same networks.  Groups of 2 / 4 / 8 / 16 rays: 111x80 32 / 31 / 30 / 30 us, 87x90 25 /
-// 25 / 27 / -, 236x134 at width 64 169 / 149 / 136 / 131.
+// meet content are spread evenly, of rays that meet the same networks.  Six or four groups per workgroup and longer ones, the mean of twelve
+// views: 200x151 55.1 us, eight 51.7; at width 64 94 and 74; 128 drawn frames of 4,000 to 32,767 rays: the same in the mean at width 32, six
+// 0.98 of eight at width 64.  Shorter groups meet more networks: of two rays, 140x105 63 us instead of 52.
+constexpr int OWN_GROUPS = 8;
 constexpr int OWN_GROUP_MIN = 4, OWN_GROUP_MAX = 16;
 constexpr int OWN_RAYS_MAX = OWN_GROUP_MAX * (int)((KN_FUSED_OWN_RAYS + 256 * OWN_GROUP_MAX - 1) / (256 * OWN_GROUP_MAX));
 
@@ -646,14 +648,23 @@ template <class Net> int fused_launch(const kn_scene *sc, hipStream_t st, const 
     for (int c = 0; c < 3; ++c) a.bg[c] = job.bg[c];
     a.rgb_out = job.rgb_out;
     a.counters = job.counters;
-    // one workgroup per compute unit, of as many wavefronts as get four rays each, up to what a compute unit holds; a multiple of
-    // eight workgroups, for the shares of the XCDs
+    // As many wavefronts as get four rays each, up to what the compute units hold; a multiple of eight workgroups, for the shares of the
+    // XCDs.  Behind a list a workgroup is a compute unit's wavefronts.  A frame that sets up its own rays has workgroups of four to seven
+    // wavefronts, as many as load the compute units evenly: its rays are spread by then, none waits for the walks of fifteen others, and a
+    // compute unit is free for a frame on another stream as soon as the four are done.  One workgroup per compute unit / so, the mean of
+    // twelve views, one frame at a time and per frame with three in flight: 200x151 55.9, 39.1 / 51.7, 31.1 us; 170x170 60.3, 33.8 / 53.3, 27.4;
+    // 100x100 42.2, 26.7 / 43.0, 23.0; 140x105 49.0, 32.8 / 52.5, 32.0; 200x151 at width 64 80, 54 / 74, 48; 104 drawn frames of 4,000 to 32,767
+    // rays 1.03 to 1.05 and 1.03 to 1.11 times as fast in the mean, single ones 0.87 to 1.39 (whether a workgroup's groups of rays fall
+    // into one column of the image).  Behind a list eight wavefronts are 1.06 times as fast in flight, but 0.975 one at a time (24 frames
+    // of up to 400,000 rays; 577x433 115 -> 121 us): not taken.
     const int64_t want = kn_div_up(job.R, 1 << Net::MIN_LG);
-    const int waves = (int)std::min<int64_t>(std::max<int64_t>(kn_div_up(want, 256), 4), Net::MAX_WAVES);
-    const int64_t blocks = std::min<int64_t>(8 * kn_div_up(want, 8 * waves), 256);
+    const int per_cu = (int)std::min<int64_t>(std::max<int64_t>(kn_div_up(want, 256), 4), Net::MAX_WAVES);
+    const int groups = job.list ? 1 : per_cu / 4; // workgroups per compute unit
+    const int waves = (int)kn_div_up(per_cu, groups);
+    const int64_t blocks = std::min<int64_t>(8 * kn_div_up(want, 8 * waves), 256 * groups);
     a.max_lg = Net::MAX_LG - (a.p.K < Net::LARGE_POOLS_BELOW ? 0 : 1);
     a.own_group = OWN_GROUP_MIN;
-    while (a.own_group < OWN_GROUP_MAX && job.R > 6 * 256 * (int64_t)a.own_group) a.own_group *= 2;
+    while (a.own_group < OWN_GROUP_MAX && job.R > OWN_GROUPS * blocks * (int64_t)a.own_group) a.own_group *= 2;
     // With hardly two samples of a ray per network the weights' way to the wavefronts is what bounds a frame: there, and with enough
     // rays for all compute units, four rays or more share what a wavefront loads (164x94, 1.2 samples per network, width 32 / 64: 93 -> 80 /
     // 224 -> 172 us); elsewhere every wavefront gets a ray if there is one (100x100, 1.5 samples per network: 47 us, 62 with four).

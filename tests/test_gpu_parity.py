@@ -1698,7 +1698,8 @@ def test_fp32_render_in_one_kernel_equals_the_wave_loop(rays, res, occ, keep, ep
 
 
 @pytest.mark.parametrize("wdtype,H,rays", [
-    ("f16", 32, 33), ("bf16", 32, 4097), ("f16", 64, 5121), ("f16", 32, 7200), ("bf16", 32, 13313),  # workgroups of 4, 5, 8, 14 wavefronts
+    ("f16", 32, 33), ("bf16", 32, 4097), ("f16", 64, 5121), ("bf16", 64, 32767),                      # workgroups of 4, 5, 6, 4 wavefronts
+    ("f16", 32, 7200), ("bf16", 32, 10241), ("bf16", 32, 13313), ("f16", 32, 32767),                  # of 4, 6, 5, 4
     ("f16", 32, 65536), ("bf16", 32, 65537), ("f16", 32, 65536 + 16), ("f16", 32, 180003),          # first pools just full; chunks of the list
     ("bf16", 64, 65535), ("f16", 64, 65600), ("bf16", 64, 230001)])
 def test_render_in_one_kernel_hands_every_ray_out(wdtype, H, rays):
