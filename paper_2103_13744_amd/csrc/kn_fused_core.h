@@ -45,11 +45,11 @@ enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last
 // Width 64: half as many wavefronts, whose rounds take three times as long, take them for themselves (1080p 1,051 us, 1,084 in chunks:
 // rays that are under way at the same time lie closer together).
 constexpr int CHUNK_SHARE = 8, CHUNK_MIN = 16, CHUNK_MAX = 512;
-// Rays in a row that a workgroup which sets up its own rays takes together: some eight groups per workgroup, so that those rays that
-// meet content are spread evenly, of rays that meet the same networks.  Six or four groups per workgroup and longer ones, the mean of twelve
-// views: 200x151 55.1 us, eight 51.7; at width 64 94 and 74; 128 drawn frames of 4,000 to 32,767 rays: the same in the mean at width 32, six
-// 0.98 of eight at width 64.  Shorter groups meet more networks: of two rays, 140x105 63 us instead of 52.
-constexpr int OWN_GROUPS = 8;
+// Rays in a row that a workgroup which sets up its own rays takes together: some eight groups per workgroup (six in those of a whole
+// compute unit), so that those rays that meet content are spread evenly, of rays that meet the same networks.  Six or four groups per workgroup
+// and longer ones, the mean of twelve views: 200x151 55.1 us, eight 51.7; at width 64 94 and 74; 128 drawn frames of 4,000 to 32,767 rays: the
+// same in the mean at width 32, six 0.98 of eight at width 64.  Shorter groups meet more networks: of two rays, 140x105 63 us instead of 52.
+constexpr int OWN_GROUPS = 8, OWN_GROUPS_WHOLE = 6;
 constexpr int OWN_GROUP_MIN = 4, OWN_GROUP_MAX = 16;
 constexpr int OWN_RAYS_MAX = OWN_GROUP_MAX * (int)((KN_FUSED_OWN_RAYS + 256 * OWN_GROUP_MAX - 1) / (256 * OWN_GROUP_MAX));
 
@@ -654,17 +654,20 @@ template <class Net> int fused_launch(const kn_scene *sc, hipStream_t st, const 
     // compute unit is free for a frame on another stream as soon as the four are done.  One workgroup per compute unit / so, the mean of
     // twelve views, one frame at a time and per frame with three in flight: 200x151 55.9, 39.1 / 51.7, 31.1 us; 170x170 60.3, 33.8 / 53.3, 27.4;
     // 100x100 42.2, 26.7 / 43.0, 23.0; 140x105 49.0, 32.8 / 52.5, 32.0; 200x151 at width 64 80, 54 / 74, 48; 104 drawn frames of 4,000 to 32,767
-    // rays 1.03 to 1.05 and 1.03 to 1.11 times as fast in the mean, single ones 0.87 to 1.39 (whether a workgroup's groups of rays fall
-    // into one column of the image).  Behind a list eight wavefronts are 1.06 times as fast in flight, but 0.975 one at a time (24 frames
-    // of up to 400,000 rays; 577x433 115 -> 121 us): not taken.
+    // rays 1.03 to 1.05 and 1.03 to 1.11 times as fast in the mean, single ones 0.76 to 1.45: where a workgroup's groups of rays fall into one
+    // column of the image the rays' costs are spread worst (an offset from group to group moved that to other frames, the mean stayed).
+    // At width 32 without an occupancy grid, where nothing is walked, a workgroup stays a compute unit's wavefronts: with smaller ones 36
+    // drawn frames are 0.97 times as fast one at a time and 1.02 in flight.  Behind a list eight wavefronts are 1.06 times as fast in
+    // flight, but 0.98 one at a time (74 drawn frames of up to 400,000 rays; 577x433 115 -> 121 us): not taken.
     const int64_t want = kn_div_up(job.R, 1 << Net::MIN_LG);
     const int per_cu = (int)std::min<int64_t>(std::max<int64_t>(kn_div_up(want, 256), 4), Net::MAX_WAVES);
-    const int groups = job.list ? 1 : per_cu / 4; // workgroups per compute unit
+    const bool whole = job.list || (Net::MAX_WAVES == 16 && !a.p.has_occ);
+    const int groups = whole ? 1 : per_cu / 4; // workgroups per compute unit
     const int waves = (int)kn_div_up(per_cu, groups);
     const int64_t blocks = std::min<int64_t>(8 * kn_div_up(want, 8 * waves), 256 * groups);
     a.max_lg = Net::MAX_LG - (a.p.K < Net::LARGE_POOLS_BELOW ? 0 : 1);
     a.own_group = OWN_GROUP_MIN;
-    while (a.own_group < OWN_GROUP_MAX && job.R > OWN_GROUPS * blocks * (int64_t)a.own_group) a.own_group *= 2;
+    while (a.own_group < OWN_GROUP_MAX && job.R > (whole ? OWN_GROUPS_WHOLE : OWN_GROUPS) * blocks * (int64_t)a.own_group) a.own_group *= 2;
     // With hardly two samples of a ray per network the weights' way to the wavefronts is what bounds a frame: there, and with enough
     // rays for all compute units, four rays or more share what a wavefront loads (164x94, 1.2 samples per network, width 32 / 64: 93 -> 80 /
     // 224 -> 172 us); elsewhere every wavefront gets a ray if there is one (100x100, 1.5 samples per network: 47 us, 62 with four).
