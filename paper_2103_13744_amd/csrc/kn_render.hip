@@ -1237,18 +1237,20 @@ extern "C" int kn_composite_deltas(void *stream, const float *sigma, const float
 
 // Where the fused kernel is the faster one.  It evaluates a wavefront's samples network by network and loads the network's weights
 // for each, so it needs several samples of a ray per network: the lattice points in a cell's edge say how many there are.
-// Its time over the wave loop's on 450 frames of 1,600 to 3.3 million rays (profiles/frames_one_kernel_against_waves.csv), where it is taken /
+// Its time over the wave loop's on 580 frames of 1,600 to 3.3 million rays (profiles/frames_one_kernel_against_waves.csv), where it is taken /
 // where it is not:
-//   up to 64 networks, whose weights stay in the caches: 0.25 to 0.94;
-//   content everywhere (no occupancy grid), a new network every few points from the ray's first point on: 16-bit width 32 0.22 to 0.95 / 0.98 to
-//   2.41 (at 4.6 points 0.93, up to 2.3 1.1 to 2.4, but in frames of millions of rays 0.22 to 0.30; 200 networks: never above 0.95); width 64
-//   0.38 to 0.61 / 0.49 to 3.81; fp32 0.70 to 0.88 / 1.00 to 3.75;
-//   up to 8,192 rays: 0.29 to 0.89 (1.03 in one of 45 frames);
-//   16-bit width 32: dense 0.33 to 0.90; sparse grids, where a ray has fewer samples of a network: 0.48 to 0.94 / 0.92 to 1.27;
-//   width 64, whose weights are three times as many bytes: 0.40 to 1.00 / 0.74 to 1.30, sparse 0.68 / 0.98 to 1.63;
-//   fp32 (width 32): 0.61 to 0.90 (1.09 in one of 24) / 0.78 to 1.50, sparse 0.87 to 0.90 / 0.96 to 1.29;
-//   without early termination, where every sample is evaluated anyway and the wave loop's tiles are full: 16-bit width 32 0.46 to 1.06 (above
-//   1 in 2 of 54) / 1.01, sparse 0.80 to 1.31; width 64 0.57 to 1.83, sparse 1.51 to 2.85; fp32 0.86 to 1.79, sparse 1.46 to 2.58.
+//   up to 64 networks, whose weights stay in the caches: 0.25 to 0.97;
+//   content everywhere (no occupancy grid), a new network every few points from the ray's first point on: 16-bit width 32 0.21 to 1.00 / 0.99 to
+//   2.42; width 64 0.39 to 0.87 (1.02 in one of 22; 200 networks, fewer than four points: 0.97 to 1.31 up to 35,098 rays, 0.49 to 0.81 from 141,700 on) /
+//   0.97 to 3.80 (0.58 in one, without termination); fp32 0.64 to 0.87 / 0.98 to 4.17;
+//   up to 8,192 rays: 0.29 to 0.86 (1.01 in one of 55 frames);
+//   16-bit width 32: dense 0.32 to 0.89; sparse grids, where a ray has fewer samples of a network: 0.43 to 0.95 / 0.93 to 1.29;
+//   width 64, whose weights are three times as many bytes: 0.38 to 1.02 / 0.88 to 1.32, sparse 0.51 (one) / 0.88 to 1.66;
+//   fp32 (width 32): 0.55 to 1.22 (above 1 in 6 of 57, mean 0.81) / 0.81 to 1.83; of these with four to eight points in a cell: 0.57 to 1.06 up to
+//   32,768 rays, 0.81 to 1.35 beyond, 0.77 to 0.86 from 2^19 on; sparse 0.64 to 1.02 / 0.96 to 2.38;
+//   without early termination, where every sample is evaluated anyway and the wave loop's tiles are full: 16-bit width 32 0.34 to 1.06 (above
+//   1 in 3 of 48) / 1.01, sparse 0.48 to 0.90 / 0.76 to 1.31; width 64 up to 32,768 rays 0.41 to 1.18 (above 1 in 2 of 14, mean 0.66), beyond with
+//   512 networks 0.66 to 1.06 (mean of 8 frames 0.85), with more 0.82 to 1.83, sparse 1.52 to 2.85; fp32 0.77 (one of 13) to 1.87, sparse 1.47 to 2.60.
 static bool fused_pays(const kn_scene *sc, int64_t R, float step, float term_eps)
 {
     if (sc->N <= 64) return true;
@@ -1256,15 +1258,16 @@ static bool fused_pays(const kn_scene *sc, int64_t R, float step, float term_eps
     const float points = fminf(g.cell[0], fminf(g.cell[1], g.cell[2])) / step;
     const bool fp32 = sc->desc.wdtype == KN_F32, narrow = !fp32 && sc->desc.hidden == 32, sparse = sc->cell_net != nullptr;
     if (!sc->has_occ && !sparse) {
-        if (term_eps == 0.0f && R > 8192) return narrow && (sc->N <= 256 || points >= 4.0f);
-        if (narrow) return sc->N <= 256 || points >= 4.0f || R >= (1ll << 19);
-        return points >= (fp32 ? 6.0f : 4.0f);
+        const bool few = !fp32 && sc->N <= 256;
+        if (term_eps == 0.0f && R > 8192) return narrow ? few || points >= 4.0f : few && points >= 4.0f;
+        if (narrow) return few || points >= 4.0f || R >= (1ll << 19);
+        return points >= (fp32 && R <= 32768 ? 6.0f : 4.0f) || (few && R >= (1ll << 17));
     }
     if (R <= 8192) return true;
-    if (term_eps == 0.0f) return narrow && (R <= 32768 || (!sparse && points >= 4.0f));
+    if (term_eps == 0.0f) return !fp32 && (R <= 32768 || (!sparse && (narrow ? points >= 4.0f : sc->N <= 512)));
     if (narrow) return R <= 32768 || (sparse ? points >= 4.0f || R >= (1ll << 18) : points >= 2.0f || R >= (1ll << 19));
-    if (fp32) return points >= (sparse && R > 32768 ? 8.0f : 5.0f);
-    return points >= (R <= 32768 ? 3.0f : sparse ? 16.0f : 6.0f);
+    if (fp32) return points >= (R > 32768 && (sparse || R < (1ll << 19)) ? 8.0f : 4.0f);
+    return points >= (R <= 32768 ? 3.0f : sparse ? 16.0f : R < (1ll << 20) ? 6.0f : 2.0f);
 }
 
 // A capture is running on the stream.

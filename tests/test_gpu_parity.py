@@ -1869,7 +1869,21 @@ def test_sparse_and_stratified_edge_cases():
     ("bf16", 64, (16, 16, 16), (64, 64, 64), None, 160, 32769, 0.01, False),
     ("bf16", 64, (16, 16, 16), (64, 64, 64), None, 192, 32769, 0.01, True),
     ("bf16", 32, (16, 16, 16), (64, 64, 64), None, 128, 40000, 0.0, True),
-    ("bf16", 32, (16, 16, 16), (64, 64, 64), None, 96, 40000, 0.0, False)])
+    ("bf16", 32, (16, 16, 16), (64, 64, 64), None, 96, 40000, 0.0, False),
+    ("f32", 32, (16, 16, 16), (64, 64, 64), None, 128, 32768, 0.01, True),    # 4.6 points, fp32
+    ("f32", 32, (16, 16, 16), (64, 64, 64), None, 128, 32769, 0.01, False),
+    ("f32", 32, (16, 16, 16), (64, 64, 64), None, 224, 32769, 0.01, True),
+    ("f32", 32, (16, 16, 16), (64, 64, 64), None, 128, 1 << 19, 0.01, True),
+    ("f32", 32, (32, 32, 32), (64, 64, 64), 0.5, 256, 1 << 19, 0.01, False),  # (sparse)
+    ("f32", 32, (16, 16, 16), None, None, 128, 32768, 0.01, False),           # content everywhere
+    ("f32", 32, (16, 16, 16), None, None, 128, 32769, 0.01, True),
+    ("f16", 64, (5, 8, 5), None, None, 32, 1 << 17, 0.01, True),
+    ("f16", 64, (5, 8, 5), None, None, 64, 8193, 0.0, True),
+    ("bf16", 64, (7, 7, 7), None, None, 64, 8193, 0.0, False),
+    ("f16", 64, (16, 16, 16), (64, 64, 64), None, 128, 32768, 0.0, True),     # without termination, width 64
+    ("f16", 64, (16, 16, 16), (64, 64, 64), None, 128, 32769, 0.0, False),
+    ("bf16", 64, (8, 8, 8), (64, 64, 64), None, 128, 32769, 0.0, True),
+    ("bf16", 64, (16, 16, 16), (64, 64, 64), None, 64, 1 << 20, 0.01, True)])
 def test_render_takes_the_faster_way_to_the_same_picture(wdtype, H, res, occ_res, keep, K, rays, eps, one_kernel):
     """Both sides of the lines between one kernel and waves (the timers tell which it was): the counted call's bits.  Captured, a frame
     is never one that has to read counts back: three replays, each on other rays, with eager frames between them."""
