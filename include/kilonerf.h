@@ -230,8 +230,8 @@ int kn_composite_deltas(void *stream, const float *sigma /*dev*/, const float *r
                         int32_t *n_used /*dev R, nullable*/);
 
 /* The whole path (Sec. 3.1 Eq. 1-4, Sec. 3.2, Sec. 3.4): render R rays.
- * 16-bit scenes (of up to 65536 networks), and fp32 scenes of width 32, are rendered by one kernel, in larger frames behind
- * a short set-up, and the call reads nothing back, unless `stats` is given, the context has a wave schedule or option of its
+ * 16-bit scenes (of up to 65536 networks), and fp32 scenes of width 32 (but for those with a network whose feature layer times
+ * layer 4 could leave the range of fp32: their layers are kept apart), are rendered by one kernel, in larger frames behind a short set-up, and the call reads nothing back, unless `stats` is given, the context has a wave schedule or option of its
  * own, or the frame is of a kind that waves render faster (and not captured into a graph, where counts cannot be read
  * back): then samples are taken in waves from near to far; rays whose transmittance fell below term_eps, or that ran out of
  * lattice points, drop out between waves.  The result per ray equals the sequential definition
