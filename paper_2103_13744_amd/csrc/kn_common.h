@@ -8,6 +8,17 @@
 #include "kilonerf.h"
 
 #define KN_WAVE 64
+
+// A thread's number in its workgroup, and the workgroup's in the grid.  threadIdx, blockIdx, blockDim, gridDim and __umul24 are
+// functions of the device library, and the compiler does not inline those into units with other floating-point flags (the
+// 16-bit kernels, see build.py): each is a call there, and a called function first waits for every load in flight.
+__device__ __forceinline__ int kn_thread() { return (int)__builtin_amdgcn_workitem_id_x(); }
+__device__ __forceinline__ int kn_block() { return (int)__builtin_amdgcn_workgroup_id_x(); }
+// a * b + c of the factors' low 24 bits
+__device__ __forceinline__ int32_t kn_mad24(int32_t a, int32_t b, int32_t c)
+{
+    return (int32_t)(((uint32_t)a & 0xffffffu) * ((uint32_t)b & 0xffffffu) + (uint32_t)c);
+}
 #define KN_MAX_CELLS (1 << 24) // cells of a sparse network grid
 
 // Uniform grid over the scene AABB (Sec. 3.2).  `cell` is the fp32 quotient (b_max - b_min) / r

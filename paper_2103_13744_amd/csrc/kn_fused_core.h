@@ -71,6 +71,7 @@ struct FusedArgs {
     VoxelFast vox, net; // the grid that is marched through, the network grid
     const void *packed;
     const float *rays_o, *rays_d;
+    int32_t n_waves, n_blocks; // wavefronts of a workgroup, workgroups
     int32_t max_lg;    // log2 of the rays of a full pool
     int32_t late_lg, late_s; // when there is no ray left to be taken: log2 of the places that a pool keeps, samples per ray and round
     int32_t few_rays;  // a workgroup starts with fewer wavefronts where its wavefronts would get fewer rays than this
@@ -158,21 +159,21 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
     __shared__ int32_t s_own;               // live rays of a workgroup that sets up its own
 
     const ArgsPtr args = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); // = &args_by_value
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
-    const int n_waves = blockDim.x / KN_WAVE;
+    const int wave = __builtin_amdgcn_readfirstlane(kn_thread() / KN_WAVE), lane = kn_thread() & (KN_WAVE - 1);
+    const int n_waves = args->n_waves, n_blocks = args->n_blocks;
     f4 *slots = s_wave[wave].slot;
     u4 *dirs = s_wave[wave].dir;
     f4 *rays = s_wave[wave].ray;
     uint16_t *idx = s_wave[wave].idx;
 
     // this workgroup's place among all: those of one XCD (b mod 8) side by side
-    const int place_of_block = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+    const int place_of_block = (kn_block() & 7) * (n_blocks >> 3) + (kn_block() >> 3);
     int4 *const own_list = (int4 *)(s_wave + n_waves);
     const int own_rays = args->own_rays;
     if (own_rays > 0) {
         // ---- Small frames: the set-up is part of the kernel.  A workgroup takes groups of rays that lie as far apart as there are
         // workgroups, eight lanes walk a ray, each through an eighth of its range.
-        if (threadIdx.x == 0) s_own = 0;
+        if (kn_thread() == 0) s_own = 0;
         __syncthreads();
         keep_denormals<Net>(true);
         const ArgsPtr a = opaque(args);
@@ -183,7 +184,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
         for (int j0 = wave * RAYS; j0 < own_rays; j0 += n_waves * RAYS) {
             const int j = j0 + lane / LANES;
             const int group = a->own_group; // (a power of two)
-            const int r = (place_of_block + (int)gridDim.x * (j / group)) * group + (j & (group - 1));
+            const int r = (place_of_block + n_blocks * (j / group)) * group + (j & (group - 1));
             int32_t k_lo = 0, k_hi = 0, first = 0x7fffffff;
             if (r < a->R) {
                 const float o[3] = {a->rays_o[3 * (int64_t)r], a->rays_o[3 * (int64_t)r + 1], a->rays_o[3 * (int64_t)r + 2]};
@@ -217,7 +218,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
         __syncthreads();
     }
     const int n_live = own_rays > 0 ? s_own : args->ctl[0];
-    const int peers = own_rays > 0 ? 1 : (int)gridDim.x; // workgroups that share the list
+    const int peers = own_rays > 0 ? 1 : n_blocks; // workgroups that share the list
     const int few_rays = args->few_rays;
     // as many wavefronts as get few_rays rays each; the others take what is shared out
     const int users = min(n_waves, max(1, (n_live + peers * few_rays - 1) / (peers * few_rays)));
@@ -233,13 +234,13 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
     // side go to the workgroups of one XCD (b mod 8), which find each other's networks in its L2.  A workgroup's shares
     // scattered one by one: the same for large frames, 164x94 rays with a network per sample 79 -> 96 us instead of 72.
     const int part = wave >> 2, width = min(4, users - 4 * part);
-    const int wid = own_rays > 0 ? wave : 4 * part * (int)gridDim.x + place_of_block * width + (wave & 3);
+    const int wid = own_rays > 0 ? wave : 4 * part * n_blocks + place_of_block * width + (wave & 3);
     const int n_first = own_rays > 0 ? n_live : (int)min((int64_t)n_live, (int64_t)total_waves << lgP); // (its own rays are all there are)
     int at = __builtin_amdgcn_readfirstlane(wave < users ? (int)((int64_t)wid * n_first / total_waves) : 0);
     int end = __builtin_amdgcn_readfirstlane(wave < users ? (int)((int64_t)(wid + 1) * n_first / total_waves) : 0);
     bool more = n_live > n_first;
-    if (threadIdx.x < n_waves) s_state[threadIdx.x] = BUSY;
-    if (threadIdx.x == 0) s_idle = s_lock = s_at = s_end = 0;
+    if (kn_thread() < n_waves) s_state[kn_thread()] = BUSY;
+    if (kn_thread() == 0) s_idle = s_lock = s_at = s_end = 0;
     __syncthreads();
 
     int ray = -1, k = 0, k_hi = 0; // (the same in all lanes of a ray's group, like everything per ray below)
@@ -360,7 +361,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
                             }
                             got = __hip_atomic_load(&s_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                             last = __hip_atomic_load(&s_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            const int chunk = min(max((n_live - max(last, n_first)) / ((int)gridDim.x * CHUNK_SHARE), CHUNK_MIN), CHUNK_MAX);
+                            const int chunk = min(max((n_live - max(last, n_first)) / (n_blocks * CHUNK_SHARE), CHUNK_MIN), CHUNK_MAX);
                             if (got >= last && last < n_live) {
                                 got = min(n_first + atomicAdd(&a->ctl[1], chunk), n_live);
                                 last = min(got + chunk, n_live);
@@ -450,7 +451,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
                         uint4 brick[STEPS];
 #pragma unroll
                         for (int c = 0; c < STEPS; ++c)
-                            brick[c] = bricks[min((uint32_t)mad24(mad24(ix[c] >> 2, skip1, iy[c] >> 2), skip2, iz[c] >> 2), last_block)];
+                            brick[c] = bricks[min((uint32_t)kn_mad24(kn_mad24(ix[c] >> 2, skip1, iy[c] >> 2), skip2, iz[c] >> 2), last_block)];
                         dist = in[STEPS - 1] ? (int32_t)brick[STEPS - 1].w : 0;
 #pragma unroll
                         for (int c = 0; c < STEPS; ++c) {
@@ -467,7 +468,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
                             int32_t nx, ny, nz;
                             close_net |= voxel_coords(vn, x[c], y[c], z[c], nx, ny, nz);
                             in[c] = in[c] & inside(vn, nx, ny, nz);
-                            net[c] = mad24(mad24(nx, vn.res[1], ny), vn.res[2], nz);
+                            net[c] = kn_mad24(kn_mad24(nx, vn.res[1], ny), vn.res[2], nz);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                         if (close_net) {
@@ -476,7 +477,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
                                 int32_t nx, ny, nz;
                                 voxel_coords_exact(vn, x[c], y[c], z[c], nx, ny, nz);
                                 in[c] = in[c] & inside(vn, nx, ny, nz);
-                                net[c] = mad24(mad24(nx, vn.res[1], ny), vn.res[2], nz);
+                                net[c] = kn_mad24(kn_mad24(nx, vn.res[1], ny), vn.res[2], nz);
                             }
                         }
                         if (cell_net) { // (uniform) a sparse grid: the cell's network, or none
@@ -689,6 +690,8 @@ template <class Net> int fused_launch(const kn_scene *sc, hipStream_t st, const 
         } else if (points >= 12.0f)
             a.late_s = 2 * Net::MAX_S;
     }
+    a.n_waves = waves;
+    a.n_blocks = (int32_t)blocks;
     const size_t lds = waves * sizeof(WaveLds<Net>) + a.own_rays * sizeof(int4);
     const FusedFn<Net> kernel = job.strat ? k_render_fused<Net, true> : k_render_fused<Net, false>;
     const dim3 grid((unsigned)blocks), block(waves * KN_WAVE);

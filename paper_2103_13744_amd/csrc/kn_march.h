@@ -211,7 +211,6 @@ __device__ __forceinline__ int32_t floor_int(float f)
     asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(f));
     return i;
 }
-__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c) { return (int32_t)(__umul24((uint32_t)a, (uint32_t)b) + (uint32_t)c); }
 
 // Eq. 6 per axis on the grid that is marched through: integer cell coordinates (any value outside [0, res) for points
 // outside).  u = x / cell - bmin / cell in one multiply-add differs from the quotient of Eq. 6 by less than `guard` (host:
@@ -284,7 +283,7 @@ __device__ __forceinline__ int32_t walk_to_content(const MarchParams &p, const V
             ++k;
             continue;
         }
-        const int32_t dist = p.skip_dist[mad24(mad24(ix >> 2, p.skip_res[1], iy >> 2), p.skip_res[2], iz >> 2)];
+        const int32_t dist = p.skip_dist[kn_mad24(kn_mad24(ix >> 2, p.skip_res[1], iy >> 2), p.skip_res[2], iz >> 2)];
         if (dist < 2) break;
         const float block[3] = {(float)(ix >> 2), (float)(iy >> 2), (float)(iz >> 2)};
         float steps = INFINITY;

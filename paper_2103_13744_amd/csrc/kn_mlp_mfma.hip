@@ -129,12 +129,13 @@ __device__ __forceinline__ uint16_t float_to_half_bits(float v, bool bf)
 }
 
 // `overflow`: set when a folded element leaves the range of the 16-bit type although its factors are finite
+constexpr int PACK_THREADS = 256;
 template <int H>
 __global__ void k_pack_weights(const uint16_t *__restrict__ w, int64_t P, int32_t N, bool bf, uint16_t *__restrict__ packed,
                                int32_t *__restrict__ overflow)
 {
     using L = Lay<H>;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)kn_block() * PACK_THREADS + kn_thread();
     const int64_t per = L::NBLK * 512 + L::TAIL_FLOATS;
     if (i >= per * N) return;
     const int64_t net = i / per;
@@ -183,7 +184,7 @@ template <int H, bool BF, int WAVES, bool WRAP, bool STRAT, int SRC>
 __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 4 : 2, H == 32 ? 4 : 2)))
     k_mlp_mfma(const uint16_t *__restrict__ packed, KnSampleSrc src, const int32_t *__restrict__ perm,
                const KnTile *__restrict__ tiles, const int32_t *__restrict__ n_tiles, float *__restrict__ sigma,
-               float *__restrict__ rgb)
+               float *__restrict__ rgb, int32_t n_blocks)
 {
     using L = Lay<H>;
     constexpr int HT = L::HT, HK = L::HK, NBLK = L::NBLK;
@@ -193,7 +194,7 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
     //   [4..7] (group 3 only) the packed 16-bit pairs (x,y), (z,1), (dx,dy), (dz,1) that sit in its slots
     __shared__ f4 stage[WAVES][4][2][KN_WAVE]; // [lane group][half][sample]: conflict-free for writers and readers
 
-    const int wave = threadIdx.x / KN_WAVE, lane = threadIdx.x & (KN_WAVE - 1);
+    const int wave = kn_thread() / KN_WAVE, lane = kn_thread() & (KN_WAVE - 1);
     const int n = lane & 15, g = lane >> 4;
     const unsigned m3 = (g == 3) ? 0xffffffffu : 0u; // bit mask of lane group 3, for branch-free selects
     const int mrow = n >> 2; // the A-operand row of this lane is n; rows 4u..4u+3 belong to sample tile u
@@ -203,12 +204,12 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
     // the ranges differ by one chunk at most).  Neighbouring tiles mostly belong to the same network: weights
     // are fetched only when the network changes.
     const int total_tiles = *n_tiles;
-    const int total_waves = gridDim.x * WAVES;
+    const int total_waves = n_blocks * WAVES;
     // Workgroups are dealt to the eight XCDs round-robin (workgroup b runs on XCD b % 8, each with an L2 of its
     // own).  Renumbered so that an XCD works on one contiguous eighth of the tile list, i.e. on neighbouring
     // networks: a ray's data and a network's weights are then fetched into one L2 instead of several.
-    const int xcd_share = gridDim.x >> 3;
-    const int block_no = (gridDim.x & 7) == 0 ? (int)(blockIdx.x & 7) * xcd_share + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    const int xcd_share = n_blocks >> 3;
+    const int block_no = (n_blocks & 7) == 0 ? (kn_block() & 7) * xcd_share + (kn_block() >> 3) : kn_block();
     const int wid = __builtin_amdgcn_readfirstlane(block_no * WAVES + wave);
     // (kept in scalar registers: tile descriptors are then fetched through the scalar cache, whose counter is
     // separate from the one of the vector loads and stores in flight)
@@ -495,14 +496,14 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
     using L = Lay<H>;
     constexpr int HT = L::HT, HK = L::HK, ROW = 4 * HT + 1; // (padded: 16 rows are written side by side)
     __shared__ f4 s_row[WAVES][3 * 16][ROW]; // [sub-cell in x, row in y][output / 4]: the row's part of layer 1
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(kn_thread() / KN_WAVE), lane = kn_thread() & (KN_WAVE - 1);
     const int n = lane & 15, g = lane >> 4;
     const unsigned m3 = (g == 3) ? 0xffffffffu : 0u;
     const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const u4 zero_u4 = {0u, 0u, 0u, 0u};
     f4(*rows)[ROW] = s_row[wave];
 
-    const int32_t cell = blockIdx.x / job.parts, part = blockIdx.x - cell * job.parts;
+    const int32_t cell = kn_block() / job.parts, part = kn_block() - cell * job.parts;
     const int32_t net = __builtin_amdgcn_readfirstlane(kn_net_of_cell(job.cell_net, cell));
     if (net < 0) return; // no network: nothing to mark
     // the cell's probes per axis, counted from the first one of voxel v0: p0 .. p1-1 (uniform, like all numbers of units)
@@ -676,14 +677,14 @@ struct KnLayerBufs {
 template <bool BF, int WAVES, bool WRAP>
 __global__ void __launch_bounds__(WAVES *KN_WAVE)
     k_layer_encode(KnSampleSrc src, const int32_t *__restrict__ perm, const KnTile *__restrict__ tiles,
-                   const int32_t *__restrict__ n_tiles, KnLayerBufs buf)
+                   const int32_t *__restrict__ n_tiles, KnLayerBufs buf, int32_t n_blocks)
 {
     __shared__ f4 stage[WAVES][4][2][KN_WAVE];
-    const int wave = threadIdx.x / KN_WAVE, lane = threadIdx.x & (KN_WAVE - 1);
+    const int wave = kn_thread() / KN_WAVE, lane = kn_thread() & (KN_WAVE - 1);
     const int n = lane & 15, g = lane >> 4;
     const unsigned m3 = (g == 3) ? 0xffffffffu : 0u;
     const int total_tiles = *n_tiles;
-    for (int t = blockIdx.x * WAVES + wave; t < total_tiles; t += gridDim.x * WAVES) {
+    for (int t = kn_block() * WAVES + wave; t < total_tiles; t += n_blocks * WAVES) {
         const KnTile tl = tiles[t];
         const int32_t idx = perm[tl.start + min(lane, tl.len - 1)];
         float x, y, z, dx, dy, dz;
@@ -726,7 +727,7 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE)
 template <int H, bool BF, int WAVES, int LAYER>
 __global__ void __launch_bounds__(WAVES *KN_WAVE)
     k_layer(const uint16_t *__restrict__ packed, const int32_t *__restrict__ perm, const KnTile *__restrict__ tiles,
-            const int32_t *__restrict__ n_tiles, KnLayerBufs buf, float *__restrict__ sigma, float *__restrict__ rgb)
+            const int32_t *__restrict__ n_tiles, KnLayerBufs buf, float *__restrict__ sigma, float *__restrict__ rgb, int32_t n_blocks)
 {
     using L = Lay<H>;
     constexpr int HT = L::HT, HK = L::HK;
@@ -739,12 +740,12 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE)
     uint16_t *__restrict__ out = (LAYER == 1 || LAYER == 4) ? buf.ha : buf.hb;
     constexpr int IN_COLS = LAYER == 1 ? 64 : H;
 
-    const int wave = threadIdx.x / KN_WAVE, lane = threadIdx.x & (KN_WAVE - 1);
+    const int wave = kn_thread() / KN_WAVE, lane = kn_thread() & (KN_WAVE - 1);
     const int n = lane & 15, g = lane >> 4;
     const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const int total_tiles = *n_tiles;
-    const int total_waves = gridDim.x * WAVES;
-    const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * WAVES + wave);
+    const int total_waves = n_blocks * WAVES;
+    const int wid = __builtin_amdgcn_readfirstlane(kn_block() * WAVES + wave);
     const int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)wid * total_tiles / total_waves));
     const int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(wid + 1) * total_tiles / total_waves));
     if (t_lo >= t_hi) return;
@@ -855,10 +856,10 @@ int launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &src, const KnB
                               : (strat ? k_mlp_mfma<H, BF, WAVES, false, true, SRC_RAYS> : k_mlp_mfma<H, BF, WAVES, false, false, SRC_RAYS>);
     if (ev_start && ev_stop)
         hipExtLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(WAVES * KN_WAVE), 0, st, ev_start, ev_stop, 0,
-                              (const uint16_t *)sc->packed_w, src, b.perm, b.tiles, b.n_tiles, sigma, rgb);
+                              (const uint16_t *)sc->packed_w, src, b.perm, b.tiles, b.n_tiles, sigma, rgb, (int32_t)blocks);
     else
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(WAVES * KN_WAVE), 0, st, (const uint16_t *)sc->packed_w, src, b.perm,
-                           b.tiles, b.n_tiles, sigma, rgb);
+                           b.tiles, b.n_tiles, sigma, rgb, (int32_t)blocks);
     KN_CHECK_LAUNCH();
     return KN_OK;
 }
@@ -887,17 +888,17 @@ int kn_mlp_pack_weights(kn_scene *sc, hipStream_t st)
     const int64_t per = H == 32 ? Lay<32>::NBLK * 512 + Lay<32>::TAIL_FLOATS : Lay<64>::NBLK * 512 + Lay<64>::TAIL_FLOATS;
     sc->packed_halfs_per_net = halfs;
     const int64_t total = per * sc->N;
-    const int64_t blocks = kn_div_up(total, 256);
+    const int64_t blocks = kn_div_up(total, PACK_THREADS);
     if (blocks > 0x7fffffffLL) return KN_E_UNSUPPORTED;
     const uint16_t *w = (const uint16_t *)sc->desc.weights;
     int32_t *flag = (int32_t *)((char *)sc->packed_w + kn_align_up(halfs * 2 * sc->N, 256));
     hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, flag);
     KN_CHECK_LAUNCH();
     if (H == 32)
-        hipLaunchKernelGGL(k_pack_weights<32>, dim3((unsigned)blocks), dim3(256), 0, st, w, sc->P, sc->N, bf,
+        hipLaunchKernelGGL(k_pack_weights<32>, dim3((unsigned)blocks), dim3(PACK_THREADS), 0, st, w, sc->P, sc->N, bf,
                            (uint16_t *)sc->packed_w, flag);
     else
-        hipLaunchKernelGGL(k_pack_weights<64>, dim3((unsigned)blocks), dim3(256), 0, st, w, sc->P, sc->N, bf,
+        hipLaunchKernelGGL(k_pack_weights<64>, dim3((unsigned)blocks), dim3(PACK_THREADS), 0, st, w, sc->P, sc->N, bf,
                            (uint16_t *)sc->packed_w, flag);
     KN_CHECK_LAUNCH();
     int32_t overflow = 0;
@@ -949,19 +950,19 @@ static int layered_launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc 
     const dim3 grid((unsigned)blocks), block(W * KN_WAVE);
     const uint16_t *w = (const uint16_t *)sc->packed_w;
     if (wrap)
-        hipLaunchKernelGGL((k_layer_encode<BF, W, true>), grid, block, 0, st, src, b.perm, b.tiles, b.n_tiles, buf);
+        hipLaunchKernelGGL((k_layer_encode<BF, W, true>), grid, block, 0, st, src, b.perm, b.tiles, b.n_tiles, buf, (int32_t)blocks);
     else
-        hipLaunchKernelGGL((k_layer_encode<BF, W, false>), grid, block, 0, st, src, b.perm, b.tiles, b.n_tiles, buf);
+        hipLaunchKernelGGL((k_layer_encode<BF, W, false>), grid, block, 0, st, src, b.perm, b.tiles, b.n_tiles, buf, (int32_t)blocks);
     KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL((k_layer<H, BF, W, 1>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb);
+    hipLaunchKernelGGL((k_layer<H, BF, W, 1>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb, (int32_t)blocks);
     KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL((k_layer<H, BF, W, 2>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb);
+    hipLaunchKernelGGL((k_layer<H, BF, W, 2>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb, (int32_t)blocks);
     KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL((k_layer<H, BF, W, 3>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb);
+    hipLaunchKernelGGL((k_layer<H, BF, W, 3>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb, (int32_t)blocks);
     KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL((k_layer<H, BF, W, 4>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb);
+    hipLaunchKernelGGL((k_layer<H, BF, W, 4>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb, (int32_t)blocks);
     KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL((k_layer<H, BF, W, 5>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb);
+    hipLaunchKernelGGL((k_layer<H, BF, W, 5>), grid, block, 0, st, w, b.perm, b.tiles, b.n_tiles, buf, sigma, rgb, (int32_t)blocks);
     KN_CHECK_LAUNCH();
     return KN_OK;
 }
