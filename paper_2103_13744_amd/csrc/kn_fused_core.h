@@ -65,6 +65,7 @@ template <class Net> struct WaveLds {
 // lattice points a lane tests per step of the march: enough look-ups in flight, and the work per step that does not
 // depend on the number of points (ranks, frontier, skip field) is shared by four
 constexpr int STEPS = 4;
+constexpr int BLEND = 4; // samples that the blend requests together
 
 struct FusedArgs {
     MarchParams p;
@@ -584,21 +585,31 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
         {
             const ArgsPtr a = opaque(args);
             const int ln = opaque(lane), slot = ln & (P - 1), gl = ln >> lgP;
-            const float eps = a->eps;
+            const float stop_below = a->eps > 0.0f ? a->eps : -INFINITY;
             int used = 0;
             if (ray >= 0) {
-                bool dead = false;
-                for (int j = 0; j < cnt && !dead; ++j) {
-                    const f4 q = slots[(j << lgP) + slot];
-                    const float wgt = T * q[3];
-                    c0 = fmaf(wgt, q[0], c0);
-                    c1 = fmaf(wgt, q[1], c1);
-                    c2 = fmaf(wgt, q[2], c2);
-                    T *= (1.0f - q[3]);
-                    ++used;
-                    dead = eps > 0.0f && T < eps;
+                // Four samples per step, requested together: one at a time the recurrence waits for the LDS at each of them (82x49 rays
+                // 60.8 -> 54.9 us, 200x151 45.8 -> 44.6, 800x800 163.4 -> 162.0).
+                bool goes = cnt > 0;
+                for (int j = 0; goes; j += BLEND) {
+                    f4 q[BLEND];
+#pragma unroll
+                    for (int c = 0; c < BLEND; ++c) q[c] = slots[((j + c) << lgP) + slot]; // (S_max is a multiple of BLEND)
+                    asm volatile("" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3])); // (one wait for the four)
+#pragma unroll
+                    for (int c = 0; c < BLEND; ++c) {
+                        if (goes) {
+                            const float wgt = T * q[c][3];
+                            c0 = fmaf(wgt, q[c][0], c0);
+                            c1 = fmaf(wgt, q[c][1], c1);
+                            c2 = fmaf(wgt, q[c][2], c2);
+                            T *= (1.0f - q[c][3]);
+                            used = j + c + 1;
+                            goes = (used < cnt) & !(T < stop_below);
+                        }
+                    }
                 }
-                if (dead || k >= k_hi) {
+                if ((cnt > 0 && T < stop_below) || k >= k_hi) {
                     if (gl == 0) {
                         float *px = a->rgb_out + 3 * (int64_t)ray;
                         px[0] = fmaf(T, a->bg[0], c0);
