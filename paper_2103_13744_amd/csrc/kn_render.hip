@@ -296,7 +296,8 @@ __global__ void __launch_bounds__(RAY_BLOCK)
 
 // Set-up of the fused render: clips every ray and walks it to the first lattice point near content; rays without any
 // sample get the background right away.  recs[r] = (first lattice index, end of the clipped range, bucket, rank in the
-// bucket) of a live ray (a dead one: bucket -1), blk_sum[block] = its live rays + 2^16 * its runs of equal buckets.
+// bucket) of a live ray (a dead one: bucket -1; a short one: SHORT_RAY added), blk_sum[block] = its live rays, 2^10 * its
+// short ones and 2^20 * its runs of equal buckets.
 //
 // A bucket is a box of the scene, 32 per axis, that the ray's first point lies in.  Rays that follow each other in the
 // caller's arrays share a bucket for a while when they come from an image; rays in random order do not, and a wavefront
@@ -304,6 +305,7 @@ __global__ void __launch_bounds__(RAY_BLOCK)
 // counts the buckets, so that k_fused_list can order the rays.  Ordering an image anyway gained nothing (1080p, width 64:
 // 1.17 ms against 1.08), ordering two million shuffled rays of it took 12.3 ms to 2.5.
 constexpr int FUSED_BUCKETS_LG = 5, FUSED_BUCKETS = 1 << (3 * FUSED_BUCKETS_LG);
+constexpr int SHORT_RAY = 1 << (3 * FUSED_BUCKETS_LG);
 constexpr int64_t SORT_RAYS = 32768; // below, a frame has fewer rays than the first pools of the wavefronts hold
 struct BucketMap {
     float scale[3], shift[3];
@@ -317,13 +319,13 @@ __device__ __forceinline__ int32_t spread3(int32_t v) // bit i of a 5-bit number
 template <bool STRAT, bool SORT>
 __global__ void __launch_bounds__(RAY_BLOCK)
     k_fused_init(MarchParams p, VoxelFast vox, BucketMap map, const float *__restrict__ rays_o, const float *__restrict__ rays_d, int64_t R,
-                 int4 *__restrict__ recs, int32_t *__restrict__ blk_sum, int32_t *__restrict__ counts, float bg0, float bg1, float bg2,
-                 float *__restrict__ rgb_out)
+                 int4 *__restrict__ recs, int32_t *__restrict__ blk_sum, int32_t *__restrict__ counts, float short_below, float bg0, float bg1,
+                 float bg2, float *__restrict__ rgb_out)
 {
     __shared__ int32_t lds[RAY_BLOCK / KN_WAVE];
     const int64_t r = (int64_t)blockIdx.x * RAY_BLOCK + threadIdx.x;
     const int lane = threadIdx.x & (KN_WAVE - 1);
-    int32_t k_lo = 0, k_hi = 0, key = -1;
+    int32_t k_lo = 0, k_hi = 0, key = -1, is_short = 0;
     if (r < R) {
         const float o[3] = {rays_o[3 * r], rays_o[3 * r + 1], rays_o[3 * r + 2]};
         const float d[3] = {rays_d[3 * r], rays_d[3 * r + 1], rays_d[3 * r + 2]};
@@ -339,6 +341,7 @@ __global__ void __launch_bounds__(RAY_BLOCK)
         if (k_lo < k_hi) {
             key = 0;
             if constexpr (SORT) {
+                is_short = (float)(k_hi - k_lo) * sqrtf(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) <= short_below ? 1 : 0;
                 float x[3];
                 kn_lattice_point<STRAT>(o[0], o[1], o[2], d[0], d[1], d[2], p.t_near, p.step, k_lo, x[0], x[1], x[2], ray_key);
 #pragma unroll
@@ -351,7 +354,7 @@ __global__ void __launch_bounds__(RAY_BLOCK)
             rgb_out[3 * r + 2] = bg2;
         }
     }
-    int32_t rank = 0, mine = key >= 0 ? 1 : 0;
+    int32_t rank = 0, mine = key >= 0 ? 1 + (is_short << 10) : 0;
     if constexpr (SORT) { // one atomic per run of lanes with the same bucket
         const int32_t prev = __shfl_up(key, 1, KN_WAVE);
         const unsigned long long heads = __ballot(lane == 0 || prev != key); // bit l: lane l starts a run
@@ -361,17 +364,17 @@ __global__ void __launch_bounds__(RAY_BLOCK)
         int32_t base = 0;
         if (head == lane && key >= 0) {
             base = atomicAdd(&counts[key], len);
-            mine += 1 << 16;
+            mine += 1 << 20;
         }
         rank = __shfl(base, head, KN_WAVE) + lane - head;
     }
-    if (r < R) recs[r] = make_int4(k_lo, k_hi, key, rank);
+    if (r < R) recs[r] = make_int4(k_lo, k_hi, key + is_short * SHORT_RAY, rank);
     const int32_t total = kn_block_sum(mine, lds);
     if (threadIdx.x == 0) blk_sum[blockIdx.x] = total;
 }
 
-// The list of live rays, (ray, first lattice index, end of the clipped range, -): in the caller's order, or with SORT, where
-// that order's runs of equal buckets are shorter than SORT_RUN rays on average, in the order of the buckets.
+// The list of live rays, (ray, first lattice index, end of the clipped range, -): in the caller's order, the short ones behind all
+// others, or with SORT, where that order's runs of equal buckets are shorter than SORT_RUN rays on average, in the order of the buckets.
 // ctl[0] = number of live rays, everything behind it is cleared for the fused kernel.
 constexpr int LIST_BLOCK = 1024, LIST_RAYS = 8, LIST_WAVES = LIST_BLOCK / KN_WAVE; // threads, rays per thread
 constexpr int SORT_RUN = 4;
@@ -380,43 +383,52 @@ __global__ void __launch_bounds__(LIST_BLOCK)
     k_fused_list(const int4 *__restrict__ recs, int64_t R, const int32_t *__restrict__ blk_sum, const int32_t *__restrict__ counts,
                  int4 *__restrict__ list, int32_t *__restrict__ ctl)
 {
-    __shared__ int32_t s_start[SORT ? FUSED_BUCKETS : 1], s_live[LIST_WAVES], s_sum[3][LIST_WAVES];
+    __shared__ int32_t s_start[SORT ? FUSED_BUCKETS : 1], s_live[LIST_WAVES], s_sum[5][LIST_WAVES];
     const int lane = threadIdx.x & (KN_WAVE - 1), wv = threadIdx.x / KN_WAVE;
     // wavefront w of the workgroup looks after LIST_RAYS * 64 rays in a row
     const int64_t r0 = (int64_t)blockIdx.x * (LIST_BLOCK * LIST_RAYS) + wv * (KN_WAVE * LIST_RAYS) + lane;
     int4 rec[LIST_RAYS];
 #pragma unroll
     for (int i = 0; i < LIST_RAYS; ++i) rec[i] = recs[min(r0 + i * KN_WAVE, R - 1)];
-    // live rays in front of the workgroup; live rays and runs of the whole frame
+    // live and short rays in front of the workgroup; live rays, short ones and runs of the whole frame
     const int n_blk = (int)((R + RAY_BLOCK - 1) / RAY_BLOCK), b_first = blockIdx.x * (LIST_BLOCK * LIST_RAYS / RAY_BLOCK);
-    int32_t front = 0, all = 0, runs = 0;
+    int32_t front = 0, all = 0, runs = 0, front_short = 0, all_short = 0;
     for (int b = threadIdx.x; b < n_blk; b += LIST_BLOCK) {
         const int32_t v = blk_sum[b];
-        front += b < b_first ? v & 0xffff : 0;
-        all += v & 0xffff;
-        runs += v >> 16;
+        front += b < b_first ? v & 0x3ff : 0;
+        front_short += b < b_first ? (v >> 10) & 0x3ff : 0;
+        all += v & 0x3ff;
+        all_short += (v >> 10) & 0x3ff;
+        runs += v >> 20;
     }
-    unsigned long long live[LIST_RAYS];
-    int32_t n_live = 0;
+    unsigned long long live[LIST_RAYS], shorts[LIST_RAYS];
+    int32_t n_live = 0; // and 2^16 * the short ones
 #pragma unroll
     for (int i = 0; i < LIST_RAYS; ++i) {
         live[i] = __ballot(r0 + i * KN_WAVE < R && rec[i].z >= 0);
-        n_live += __popcll(live[i]);
+        shorts[i] = live[i] & __ballot(rec[i].z >= SHORT_RAY);
+        n_live += __popcll(live[i]) + (__popcll(shorts[i]) << 16);
     }
     front = kn_wave_inclusive_scan(front);
     all = kn_wave_inclusive_scan(all);
     runs = kn_wave_inclusive_scan(runs);
+    front_short = kn_wave_inclusive_scan(front_short);
+    all_short = kn_wave_inclusive_scan(all_short);
     if (lane == KN_WAVE - 1) {
         s_live[wv] = n_live;
         s_sum[0][wv] = front;
         s_sum[1][wv] = all;
         s_sum[2][wv] = runs;
+        s_sum[3][wv] = front_short;
+        s_sum[4][wv] = all_short;
     }
     __syncthreads();
-    front = all = runs = 0;
+    front = all = runs = front_short = all_short = 0;
     for (int w = 0; w < LIST_WAVES; ++w) {
-        front += s_sum[0][w] + (w < wv ? s_live[w] : 0);
+        front += s_sum[0][w] + (w < wv ? s_live[w] & 0xffff : 0);
+        front_short += s_sum[3][w] + (w < wv ? s_live[w] >> 16 : 0);
         all += s_sum[1][w];
+        all_short += s_sum[4][w];
         runs += s_sum[2][w];
     }
     if (blockIdx.x == 0 && threadIdx.x < KN_FUSED_CTL) ctl[threadIdx.x] = threadIdx.x == 0 ? all : 0;
@@ -444,15 +456,20 @@ __global__ void __launch_bounds__(LIST_BLOCK)
 #pragma unroll
             for (int i = 0; i < LIST_RAYS; ++i)
                 if ((live[i] >> lane) & 1ull)
-                    list[s_start[rec[i].z] + rec[i].w] = make_int4((int32_t)(r0 + i * KN_WAVE), rec[i].x, rec[i].y, 0);
+                    list[s_start[rec[i].z & (FUSED_BUCKETS - 1)] + rec[i].w] = make_int4((int32_t)(r0 + i * KN_WAVE), rec[i].x, rec[i].y, 0);
             return;
         }
     }
+    int32_t at = front - front_short, at_short = all - all_short + front_short;
 #pragma unroll
     for (int i = 0; i < LIST_RAYS; ++i) {
-        if ((live[i] >> lane) & 1ull)
-            list[front + __popcll(live[i] & ((1ull << lane) - 1ull))] = make_int4((int32_t)(r0 + i * KN_WAVE), rec[i].x, rec[i].y, 0);
-        front += __popcll(live[i]);
+        const unsigned long long before = (1ull << lane) - 1ull, others = live[i] ^ shorts[i];
+        if ((live[i] >> lane) & 1ull) {
+            const int32_t to = (shorts[i] >> lane) & 1ull ? at_short + __popcll(shorts[i] & before) : at + __popcll(others & before);
+            list[to] = make_int4((int32_t)(r0 + i * KN_WAVE), rec[i].x, rec[i].y, 0);
+        }
+        at += __popcll(others);
+        at_short += __popcll(shorts[i]);
     }
 }
 
@@ -1295,11 +1312,23 @@ static int render_fused(kn_ctx *ctx, const kn_scene *sc, hipStream_t st, const M
     const bool own = R <= KN_FUSED_OWN_RAYS && !tm.counts;
     if (!own) {
         const bool sort = R >= SORT_RAYS;
+        // Rays whose way through the content's box is short come last in the list: most of them end in one round, and when no ray is left to
+        // be handed out a workgroup should not have begun one that takes ten.  In the caller's order / short ones (up to a quarter of the
+        // box's diagonal) last, us per frame, two views each: 767x577 stratified 160 / 156, 800x800 164 / 161, sparse 198 / 189, 726x545 sparse
+        // 238 / 223, 436x433 106 / 100; 1769x995 no change.  A tenth, a fifth, 0.4 and 0.55 of the diagonal: 0.1, 0, 1.2 and 3 % behind.  Not taken
+        // at width 64 (1080p 1,052 to 1,070: neighbours in the list share their networks, which counts more there), in fp32 (no
+        // change) and without an occupancy grid, where all rays begin at the box (1671x1674 297 / 305).
+        float short_below = -1.0f;
+        if (sc->desc.wdtype != KN_F32 && sc->desc.hidden == 32 && p.has_occ) {
+            float diagonal = 0.0f;
+            for (int a = 0; a < 3; ++a) diagonal += p.content.cell[a] * (float)p.content.res[a] * (p.content.cell[a] * (float)p.content.res[a]);
+            short_below = 0.25f * sqrtf(diagonal) / p.step;
+        }
         if (sort) KN_TRY(kn_fill_i32(st, w.counts, FUSED_BUCKETS, 0));
         const auto init = sort ? (seed ? k_fused_init<true, true> : k_fused_init<false, true>)
                                : (seed ? k_fused_init<true, false> : k_fused_init<false, false>);
         hipLaunchKernelGGL(init, dim3((unsigned)kn_div_up(R, RAY_BLOCK)), dim3(RAY_BLOCK), 0, st, p, voxel_fast(p.occ), map, rays_o, rays_d, R, w.recs, w.blk_sum,
-                           w.counts, bg[0], bg[1], bg[2], rgb_out);
+                           w.counts, short_below, bg[0], bg[1], bg[2], rgb_out);
         KN_CHECK_LAUNCH();
         hipLaunchKernelGGL(sort ? k_fused_list<true> : k_fused_list<false>, dim3((unsigned)kn_div_up(R, LIST_BLOCK * LIST_RAYS)), dim3(LIST_BLOCK), 0,
                            st, w.recs, R, w.blk_sum, w.counts, w.list, w.ctl);

@@ -1721,6 +1721,30 @@ def test_render_in_one_kernel_hands_every_ray_out(wdtype, H, rays):
     assert st["samples_blended"] >= rays
 
 
+@pytest.mark.parametrize("rays", [32768, 32769, 40961])
+@pytest.mark.parametrize("kind", ["long", "short", "both"])
+def test_render_in_one_kernel_of_short_and_long_rays(kind, rays):
+    """Rays along the content's diagonal, across one of its edges, and both in turn, some of them dead: the short ones are listed last,
+    whatever their number, around whole workgroups of the listing kernel (8,192 rays)."""
+    import torch
+    log("fused render, short and long rays", kind, rays)
+    occ = np.zeros((64, 64, 64), np.uint8)
+    occ[8:56, 8:56, 8:56] = 1
+    dev, _ = make_pair(scene_dict((8, 8, 8), (-1, -1, -1), (1, 1, 1), 32, "f16", 13, occ=occ, sigma_scale=20.0))
+    g = torch.Generator().manual_seed(rays)
+    to_long = torch.rand((rays, 3), generator=g) * 0.2 - 0.1
+    edge = torch.tensor([0.7, -0.7, 0.0]) * (1.0 - 0.05 * torch.rand((rays, 1), generator=g)) + torch.tensor([0.0, 0.0, 0.4]) * torch.rand((rays, 1), generator=g)
+    is_long = {"long": torch.ones(rays, dtype=torch.bool), "short": torch.zeros(rays, dtype=torch.bool), "both": torch.arange(rays) % 5 < 2}[kind]
+    d = torch.where(is_long[:, None], torch.tensor([[1.0, 1.0, 1.0]]), torch.tensor([[1.0, 1.0, 0.0]])) / 3.0 ** 0.5
+    o = torch.where(is_long[:, None], to_long, edge) - 3.0 * d
+    d[torch.arange(rays) % 7 == 3] *= -1.0 # away from the scene
+    args = (o.cuda(), d.cuda(), 1.0, 4.0 / 128, 128, 0.01, (0.2, 0.4, 0.9))
+    waves, st = dev.render(*args, want_stats=True)
+    assert st["samples_blended"] > rays
+    for _ in range(2):
+        assert torch.equal(dev.render(*args), waves)
+
+
 @pytest.mark.parametrize("wdtype,H,res,occ_res,keep,box,eps", [
     ("f16", 32, (24, 24, 24), (96, 96, 96), 0.6, 1.0, 0.01),      # sparse, a block of voxels lies in one cell
     ("bf16", 64, (12, 12, 24), (96, 48, 96), 0.5, 1.0, 0.01),
