@@ -48,10 +48,12 @@ enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last
 
 // Rays beyond the first pools.  Width 32: they are handed to a workgroup in chunks, its wavefronts take from those what they have places
 // for: an eighth of a workgroup's even share of what is left, so that the chunks become small towards the end.  (An atomic per
-// wavefront and round, all on one word, kept the wavefronts waiting: 11 ns each, 45 us for the 4,096 that ask after their first round.)
+// wavefront and round, all on one word, kept the wavefronts waiting: 11 ns each, 45 us for the 4,096 that ask after their first round.  At
+// least 8 rays and a sixteenth / 16 and an eighth / 32 and an eighth / 32 and a half, us: 899x900 163 / 124.5 / 115.5 / 116, 800x800 175 / 151.6 / 150.8 /
+// 152.6, sparse 197 / 186.9 / 186.3 / 192, 1071x1070 sparse - / 327 / 326 / 343.)
 // Width 64: half as many wavefronts, whose rounds take three times as long, take them for themselves (1080p 1,051 us, 1,084 in chunks:
 // rays that are under way at the same time lie closer together).
-constexpr int CHUNK_SHARE = 8, CHUNK_MIN = 16, CHUNK_MAX = 512;
+constexpr int CHUNK_SHARE = 8, CHUNK_MIN = 32, CHUNK_MAX = 512;
 // Rays in a row that a workgroup which sets up its own rays takes together: some eight groups per workgroup (six in those of a whole
 // compute unit), so that those rays that meet content are spread evenly, of rays that meet the same networks.  Six or four groups per workgroup
 // and longer ones, the mean of twelve views: 200x151 55.1 us, eight 51.7; at width 64 94 and 74; 128 drawn frames of 4,000 to 32,767 rays: the
