@@ -20,8 +20,8 @@ int kn_mlp_mfma_launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &sr
 int kn_mlp_mfma_tile_len(const kn_scene *sc);
 int kn_mlp_f32_tile_len(const kn_scene *sc);
 int kn_mlp_f32_pack_weights(kn_scene *sc, hipStream_t st, const KnHostWord &word);
-int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, const KnProbeRowsJob &job);
-int kn_probe_f32_launch(const kn_scene *sc, hipStream_t st, const KnProbeJob &job);
+int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, KnProbeJob job);
+int kn_probe_f32_launch(const kn_scene *sc, hipStream_t st, KnProbeJob job);
 int64_t kn_layered_act_bytes(const kn_scene *sc, int64_t M);
 int kn_mlp_layered_launch(const kn_scene *sc, hipStream_t st, const KnSampleSrc &src, const KnBucketOut &b, int64_t M,
                           int64_t max_tiles, void *acts, float *sigma, float *rgb);
@@ -838,29 +838,9 @@ __global__ void k_fill_bytes(uint8_t *p, int64_t n, uint8_t v)
     }
 }
 
-// first[c] = first voxel along axis blockIdx.x whose centre lies in network cell c or beyond (res + 1 entries):
-// the voxels whose centre lies in cell c are first[c] .. first[c+1]-1.
-__global__ void k_probe_ranges(KnGrid occ, KnGrid net, int32_t *first0, int32_t *first1, int32_t *first2)
-{
-    const int a = blockIdx.x;
-    int32_t *first = a == 0 ? first0 : (a == 1 ? first1 : first2);
-    const int nc = net.res[a], nv = occ.res[a];
-    for (int c = threadIdx.x; c <= nc; c += blockDim.x) first[c] = nv;
-    __syncthreads();
-    auto home = [&](int v) {
-        const float x = fmaf((float)v + 0.5f, occ.cell[a], occ.bmin[a]);
-        const float f = floorf((x - net.bmin[a]) / net.cell[a]);
-        return (int)fminf(fmaxf(f, 0.0f), (float)(nc - 1));
-    };
-    for (int v = threadIdx.x; v < nv; v += blockDim.x) {
-        const int h = home(v), before = v == 0 ? -1 : home(v - 1); // non-decreasing in v
-        for (int c = before + 1; c <= h; ++c) first[c] = v;
-    }
-}
-
-// Set-up of the 16-bit kernels in one launch: workgroups 0..2 find the first probe of every network cell along their axis
-// (KnProbeRowsJob; a search: positions and Eq. 6 are non-decreasing in the probe's number), the others clear the grid.
-__global__ void __launch_bounds__(256) k_probe_rows_setup(KnGrid occ, KnGrid net, int64_t *first0, int64_t *first1, int64_t *first2,
+// Set-up of the probe kernels in one launch: workgroups 0..2 find the first probe of every network cell along their axis
+// (KnProbeJob; a search: positions and Eq. 6 are non-decreasing in the probe's number), the others clear the grid.
+__global__ void __launch_bounds__(256) k_probe_setup(KnGrid occ, KnGrid net, int32_t *first0, int32_t *first1, int32_t *first2,
                                                           uint8_t *bytes, int64_t n)
 {
     if (blockIdx.x >= 3) {
@@ -873,7 +853,7 @@ __global__ void __launch_bounds__(256) k_probe_rows_setup(KnGrid occ, KnGrid net
         return;
     }
     const int a = blockIdx.x;
-    int64_t *first = a == 0 ? first0 : (a == 1 ? first1 : first2);
+    int32_t *first = a == 0 ? first0 : (a == 1 ? first1 : first2);
     for (int c = threadIdx.x; c <= net.res[a]; c += 256) {
         int64_t lo = 0, hi = 3 * (int64_t)occ.res[a]; // the first probe in cell c or beyond lies in [lo, hi]
         while (lo < hi) {
@@ -883,15 +863,14 @@ __global__ void __launch_bounds__(256) k_probe_rows_setup(KnGrid occ, KnGrid net
             if (cell >= (float)c) hi = mid;
             else lo = mid + 1;
         }
-        first[c] = lo;
+        first[c] = (int32_t)(lo - kn_probe_base(occ.res[a], net.res[a], c));
     }
 }
 
 int64_t extract_ws_bytes(const kn_scene *sc)
 {
-    const int64_t entry = sc->desc.wdtype == KN_F32 ? 4 : 8;
     int64_t b = 0;
-    for (int a = 0; a < 3; ++a) b += kn_align_up(((int64_t)sc->desc.res[a] + 1) * entry, 256);
+    for (int a = 0; a < 3; ++a) b += kn_align_up(((int64_t)sc->desc.res[a] + 1) * 4, 256);
     return b;
 }
 
@@ -929,65 +908,21 @@ extern "C" int kn_extract_occupancy(kn_ctx *ctx, const kn_scene *sc, void *strea
         tm.add(0, 0, 0, 1);
         return KN_OK;
     }
-    if (sc->desc.wdtype != KN_F32) {
-        KnProbeRowsJob rows{};
-        int64_t *first_probe[3], units = 1;
-        for (int a = 0; a < 3; ++a) {
-            rows.first[a] = first_probe[a] = ws.carve<int64_t>(sc->desc.res[a] + 1);
-            rows.net_res[a] = sc->desc.res[a];
-            const int64_t per_cell = kn_div_up(occ_res[a], sc->desc.res[a]); // voxels
-            units *= a == 0 ? per_cell : (a == 1 ? kn_div_up(per_cell, 5) : kn_div_up(per_cell, 16));
-        }
-        if (!ws.ok()) return KN_E_WORKSPACE;
-        rows.occ = job.occ;
-        rows.cell_net = sc->cell_net;
-        rows.tau = tau;
-        rows.occupancy = occupancy;
-        // several times the workgroups that are resident (1,024 at width 32), each wavefront with two units of work or more
-        int64_t parts = kn_div_up(4096, sc->cells);
-        if (parts > units / 8) parts = units / 8;
-        if (parts < 1) parts = 1;
-        rows.parts = (int32_t)parts;
-        tm.begin();
-        hipLaunchKernelGGL(k_probe_rows_setup, dim3((unsigned)(3 + kn_div_up(kn_div_up(voxels, 16), 256))), dim3(256), 0, st, rows.occ,
-                           sc->net_grid, first_probe[0], first_probe[1], first_probe[2], occupancy, voxels);
-        KN_CHECK_LAUNCH();
-        tm.mark(KN_ST_SETUP);
-        KN_TRY(kn_probe_mfma_launch(sc, st, rows));
-        tm.mark(KN_ST_MLP);
-        tm.add(1, KN_PROBES * voxels, 0, 1);
-        return KN_OK;
-    }
     int32_t *first[3];
-    for (int a = 0; a < 3; ++a) first[a] = ws.carve<int32_t>(sc->desc.res[a] + 1);
+    for (int a = 0; a < 3; ++a) {
+        job.first[a] = first[a] = ws.carve<int32_t>(sc->desc.res[a] + 1);
+        job.net_res[a] = sc->desc.res[a];
+    }
     if (!ws.ok()) return KN_E_WORKSPACE;
-    job.net = sc->net_grid;
     job.cell_net = sc->cell_net;
-    for (int a = 0; a < 3; ++a) job.first[a] = first[a];
     job.tau = tau;
     job.occupancy = occupancy;
-    // Where the grid being filled refines the network grid, a probe lies at least a sixth of a voxel from the faces of
-    // its voxel's home cell; if that is far more than the rounding of its position and of Eq. 6 can amount to (a few
-    // units in the last place of the largest coordinate), Eq. 6 gives the home cell for every probe and is skipped.
-    job.nested = 1;
-    for (int a = 0; a < 3; ++a) {
-        const float reach = fabsf(sc->desc.aabb_min[a]) + fabsf(sc->desc.aabb_max[a]) + (sc->desc.aabb_max[a] - sc->desc.aabb_min[a]);
-        if (occ_res[a] % sc->desc.res[a] != 0 || !(job.occ.cell[a] > 48.0f * 2.4e-7f * reach)) job.nested = 0;
-    }
-    // enough workgroups to fill the chip several times over, but at least some tens of tiles per wavefront
-    const int64_t tiles_per_cell = kn_div_up(KN_PROBES * kn_div_up(voxels, sc->cells), KN_WAVE);
-    int64_t parts = kn_div_up(2048, sc->cells);
-    if (parts > tiles_per_cell / 32) parts = tiles_per_cell / 32;
-    if (parts < 1) parts = 1;
-    job.parts = (int32_t)parts;
-
     tm.begin();
-    hipLaunchKernelGGL(k_fill_bytes, fill_grid, dim3(256), 0, st, occupancy, voxels, (uint8_t)0);
-    KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_probe_ranges, dim3(3), dim3(256), 0, st, job.occ, job.net, first[0], first[1], first[2]);
+    hipLaunchKernelGGL(k_probe_setup, dim3((unsigned)(3 + kn_div_up(kn_div_up(voxels, 16), 256))), dim3(256), 0, st, job.occ, sc->net_grid,
+                       first[0], first[1], first[2], occupancy, voxels);
     KN_CHECK_LAUNCH();
     tm.mark(KN_ST_SETUP);
-    KN_TRY(kn_probe_f32_launch(sc, st, job));
+    KN_TRY(sc->desc.wdtype == KN_F32 ? kn_probe_f32_launch(sc, st, job) : kn_probe_mfma_launch(sc, st, job));
     tm.mark(KN_ST_MLP);
     tm.add(1, KN_PROBES * voxels, 0, 1);
     return KN_OK;

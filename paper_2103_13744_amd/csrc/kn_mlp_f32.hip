@@ -373,127 +373,164 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
 }
 
 
-// Density only, for occupancy extraction (Sec. 3.4): layers 1 and 2 and the density row of layer 3 at the probe
-// points of one network cell's voxels, which are generated in the kernel.  Same formulation as k_mlp_f32.
+// Density only, for occupancy extraction (Sec. 3.4): layers 1 and 2 and the density row of layer 3 at the probes of one
+// network cell (KnProbeBox).
+//
+// The probes are a lattice and gamma(x) is a concatenation of what belongs to x, to y and to z, so layer 1 is a sum of three
+// vectors that depend on one coordinate each.  A workgroup takes a part of the cell's box of up to job.sub probes per axis,
+// forms the vectors of its rows of x (with the bias), y and z once and keeps them in LDS; layer 1 of a probe is then two
+// additions per output instead of an encoding and 16 matrix products per 16 outputs, and the probes of the part, numbered z fastest
+// and dealt out in chunks of 64, need no order of their own (a lane looks up the rows of its probe wherever they are, so short ranges in z
+// leave no lanes empty).  Layer 2 runs on the matrix cores as in k_mlp_f32; the density's partial sums of four tiles are summed over
+// the lane groups together, so that lane l ends with probe l of the chunk, and marks its voxel.
+//
+// Bound: the matrix cores (16 products of 32 cycles per tile at width 32, 64 at width 64; 530 us for 120x100x80 voxels at width 32, where
+// they take 400 at the 2.0 GHz of such a load, 1,750 to 1,810 of 1,620 at width 64).  Against an encoding and all of layer 1 per probe, with a
+// voxel's probes together (a second pass over every tile with the neighbour's weights where grids do not nest):
+// 64^3 voxels on 8^3 networks 519 -> 156 us, on 20^3 1,938 -> 192, 120x100x80 on 16^3 2,986 -> 529; width 64 1,089 -> 500,
+// 4,149 -> 631, 6,260 -> 1,748.  The marks: no voxel of twelve 64^3 grids differs from 64 bits, before or after.  Three and
+// two wavefronts per SIMD: 1 % faster and 3 % slower.
 template <int H>
-__global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 4 : 3, H == 32 ? 4 : 3)))
     k_probe_f32(const float *__restrict__ packed, KnProbeJob job)
 {
     using R = Regs<H>;
-    constexpr int HT = H / 16, HQ = H / 4;
-    __shared__ float stage[F32_WAVES][KN_WAVE][4];
-    const int wave = threadIdx.x / KN_WAVE, lane = threadIdx.x & (KN_WAVE - 1);
+    constexpr int HT = H / 16, HQ = H / 4, ENC = 24, THREADS = F32_WAVES * KN_WAVE;
+    extern __shared__ f4 s_probe[];
+    const int pitch = (job.sub[0] + job.sub[1] + job.sub[2]) | 1; // (odd: the rows' stores below fall on different banks)
+    f4 *const tab = s_probe;                                      // [output / 4][row]: the row's part of layer 1; rows of z, y, x
+    float *const enc = (float *)(s_probe + HQ * pitch);           // [row][ENC]: sines and cosines of the ten frequencies, coordinate
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / KN_WAVE), lane = tid & (KN_WAVE - 1);
     const int n = lane & 15, g = lane >> 4;
-    const bool g3 = g == 3;
-    const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
 
     const int32_t cell = blockIdx.x / job.parts, part = blockIdx.x - cell * job.parts;
-    const KnProbeBox box = kn_probe_box(job, cell);
-    if (box.points == 0) return;
-    const int shares = job.parts * F32_WAVES, share = part * F32_WAVES + wave;
-    const int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)share * box.tiles / shares));
-    const int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(share + 1) * box.tiles / shares));
-    if (t_lo >= t_hi) return;
+    const int32_t net = __builtin_amdgcn_readfirstlane(kn_net_of_cell(job.cell_net, cell));
+    if (net < 0) return; // no network: nothing to mark
+    KnProbeBox box;
+    if (!kn_probe_box(job, cell, box)) return;
+    int32_t len[3], cuts[3]; // probes of the cell, parts they are cut into (of equal size or one more)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        len[a] = box.p1[a] - box.p0[a];
+        cuts[a] = (len[a] + job.sub[a] - 1) / job.sub[a];
+    }
+    const int32_t all = cuts[0] * cuts[1] * cuts[2];
+    if (part >= all) return;
 
-    float w1[HT][16], w2[HT][HQ], wo[HQ], bias_sig = 0.0f;
-    f4 bias2[HT];
-    auto load_network = [&](int32_t net) {
-        const float *__restrict__ image = packed + (int64_t)net * (R::N * KN_WAVE);
+    const float *__restrict__ image = packed + (int64_t)net * (R::N * KN_WAVE);
+    for (int32_t s = part; s < all; s += job.parts) {
+        const int32_t sq = s / cuts[2], at[3] = {sq / cuts[1], sq % cuts[1], s % cuts[2]};
+        int32_t lo[3], num[3]; // first probe (counted like box.p0) and probes of the part
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int32_t each = len[a] / cuts[a], more = len[a] % cuts[a];
+            lo[a] = box.p0[a] + at[a] * each + min(at[a], more);
+            num[a] = each + (at[a] < more ? 1 : 0);
+        }
+        const int32_t row_y = num[2], row_x = num[2] + num[1], rows = row_x + num[0];
+
+        // ---- encodings of the rows: three accurate evaluations each, at frequencies 0, 4 and 8
+        for (int i = tid; i < 3 * rows; i += THREADS) {
+            const int restart = i < rows ? 0 : (i < 2 * rows ? 1 : 2), row = i - restart * rows;
+            const bool is_z = row < row_y, is_y = !is_z && row < row_x;
+            auto axis = [&](auto x, auto y, auto z) { return is_z ? z : (is_y ? y : x); };
+            const float p = kn_probe_coord(axis(job.occ.cell[0], job.occ.cell[1], job.occ.cell[2]), axis(job.occ.bmin[0], job.occ.bmin[1], job.occ.bmin[2]),
+                                           axis(box.v0[0], box.v0[1], box.v0[2]), axis(lo[0], lo[1], lo[2]) + row - axis(row_x, row_y, 0));
+            float sn[4], cs[4];
+            sincosf(p * (restart == 0 ? 1.0f : (restart == 1 ? 16.0f : 256.0f)), &sn[0], &cs[0]);
+#pragma unroll
+            for (int k = 1; k < 4; ++k) double_angle(sn[k - 1], cs[k - 1], sn[k], cs[k]);
+            float *const to = enc + row * ENC + 8 * restart;
+            *(f4 *)to = (f4){sn[0], cs[0], sn[1], cs[1]};
+            *(f4 *)(to + 4) = restart == 2 ? (f4){p, 0.0f, 0.0f, 0.0f} : (f4){sn[2], cs[2], sn[3], cs[3]};
+        }
+        __syncthreads();
+        // ---- the rows' parts of layer 1: thread = (output, every THREADS / H-th row)
+        {
+            const int col = tid & (H - 1);
+            const float *const w1 = image;
+            float *const out = (float *)(tab + (col >> 2) * pitch) + (col & 3);
+            auto weight = [&](int q, int from) { return w1[image_at<H>(R::W1 + 16 * (col >> 4) + q, from + (col & 15))]; };
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                float w[21];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) w[q] = weight(q, 16 * a);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) w[16 + q] = weight(4 * a + q, 48);
+                w[20] = weight(12 + a, 48);
+                const float b1 = a == 0 ? weight(15, 48) : 0.0f;
+                const int first = a == 0 ? row_x : (a == 1 ? row_y : 0);
+                for (int row = first + tid / H; row < first + num[a]; row += THREADS / H) {
+                    const f4 *const e = (const f4 *)(enc + row * ENC);
+                    float acc = b1;
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) {
+                        const f4 v = e[q];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (4 * q + j < 21) acc = fmaf(w[4 * q + j < 21 ? 4 * q + j : 0], v[j], acc);
+                    }
+                    out[4 * row] = acc;
+                }
+            }
+        }
+        __syncthreads();
+
+        // ---- the probes, 64 at a time
+        float w2[HT][HQ], wo[HQ];
+        f4 bias2[HT];
 #pragma unroll
         for (int t = 0; t < HT; ++t) {
-            fetch_registers<H>(image, lane, R::W1 + 16 * t, w1[t], 16);
             fetch_registers<H>(image, lane, R::W2 + HQ * t, w2[t], HQ);
             bias2[t] = fetch_registers<H>(image, lane, R::B2 + 4 * t);
         }
         fetch_registers<H>(image, lane, R::WO + 3 * HQ, wo, HQ);
-        bias_sig = image[image_at<H>(R::BO + 3, lane)];
-    };
-    int32_t net_loaded = -1;
-
-    // every probe of a voxel in its home cell: one network for the whole box (none: nothing to mark)
-    const int32_t home_net = kn_net_of_cell(job.cell_net, cell);
-    if (job.nested && home_net < 0) return;
-    KnProbeCursor cur = kn_probe_cursor(box, t_lo * KN_WAVE + lane);
-    for (int t = t_lo; t < t_hi; ++t, kn_probe_cursor_step(box, cur)) {
-        const int32_t p = t * KN_WAVE + lane;
-        const bool active = p < box.points; // (beyond the box's last probe the cursor points past the box: unused)
-        float x, y, z;
-        int64_t voxel;
-        const int32_t probe = cur.probe;
-        kn_probe_point(job, box, cur, x, y, z, voxel);
-        const int32_t net = job.nested ? home_net : kn_net_of_cell(job.cell_net, kn_grid_index(job.net, x, y, z));
-        bool todo = active && net >= 0;
-        float sg = 0.0f;
-        *(f4 *)&stage[wave][lane][0] = (f4){x, y, z, 0.0f};
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-        // one pass per network met in the tile (a single one when the grids nest)
-        for (;;) {
-            const unsigned long long pending = __ballot(todo);
-            if (pending == 0ull) break;
-            const int32_t nsel = __builtin_amdgcn_readlane(net, (int)__builtin_ctzll(pending));
-            if (nsel != net_loaded) {
-                load_network(nsel);
-                net_loaded = nsel;
-            }
-            f4 out = {0.0f, 0.0f, 0.0f, bias_sig};
-#pragma unroll 1
+        const float bias_sig = image[image_at<H>(R::BO + 3, 0)];
+        const int32_t points = num[0] * num[1] * num[2]; // (at most 48^3: quotients by multiplication are exact)
+        const uint32_t by_z = (0x80000000u + (uint32_t)num[2] - 1u) / (uint32_t)num[2], by_y = (0x80000000u + (uint32_t)num[1] - 1u) / (uint32_t)num[1];
+        for (int32_t first = wave * KN_WAVE; first < points; first += THREADS) {
+            const int32_t p = min(first + lane, points - 1);
+            const int32_t pq = (int32_t)__umulhi(2u * (uint32_t)p, by_z), iz = p - pq * num[2];
+            const int32_t ix = (int32_t)__umulhi(2u * (uint32_t)pq, by_y), iy = pq - ix * num[1];
+            const int32_t where = iz | (row_y + iy) << 8 | (row_x + ix) << 16;
+            float d[4];
+#pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const f4 s0 = *(const f4 *)&stage[wave][16 * u + n][0];
-                const float pt[3] = {s0[0], s0[1], s0[2]};
-                const float pg = g == 0 ? pt[0] : (g == 1 ? pt[1] : pt[2]);
-                // groups 0..2: axis g at frequencies 0 and 4; group 3: the three axes at frequency 8
-                const float ang[3] = {g3 ? 256.0f * pt[0] : pg, g3 ? 256.0f * pt[1] : 16.0f * pg, 256.0f * pt[2]};
-                float cs[3][4], cc[3][4];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    sincosf(ang[c], &cs[c][0], &cc[c][0]);
-#pragma unroll
-                    for (int k = 1; k < 4; ++k) double_angle(cs[c][k - 1], cc[c][k - 1], cs[c][k], cc[c][k]);
-                }
-                float enc[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const int f = q >> 1;
-                    const float axis_v = (q & 1) ? cc[f >> 2][f & 3] : cs[f >> 2][f & 3];
-                    const float g3_v = q < 12 ? ((q & 1) ? cc[q >> 2][(q >> 1) & 1] : cs[q >> 2][(q >> 1) & 1])
-                                              : (q < 15 ? pt[q >= 12 && q < 15 ? q - 12 : 0] : 1.0f);
-                    enc[q] = g3 ? g3_v : axis_v;
-                }
-                const bool sig_row = (n >> 2) == u && (n & 3) == 3;
+                const int32_t r = __builtin_amdgcn_ds_bpermute(4 * (16 * u + n), where);
+                const f4 *const pz = tab + g * pitch + (r & 255), *const py = tab + g * pitch + ((r >> 8) & 255), *const px = tab + g * pitch + (r >> 16);
                 f4 acc[HT], h[HT];
 #pragma unroll
-                for (int t2 = 0; t2 < HT; ++t2) {
-                    acc[t2] = zero4;
+                for (int t = 0; t < HT; ++t) {
+                    const f4 a = px[4 * t * pitch], b = py[4 * t * pitch], c = pz[4 * t * pitch];
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) acc[t2] = mfma4(w1[t2][q], enc[q], acc[t2]);
+                    for (int j = 0; j < 4; ++j) h[t][j] = fmaxf((a[j] + b[j]) + c[j], 0.0f);
                 }
 #pragma unroll
-                for (int t2 = 0; t2 < HT; ++t2)
+                for (int t = 0; t < HT; ++t) {
+                    acc[t] = bias2[t];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-#pragma unroll
-                for (int t2 = 0; t2 < HT; ++t2) {
-                    acc[t2] = bias2[t2];
-#pragma unroll
-                    for (int k = 0; k < HQ; ++k) acc[t2] = mfma4(w2[t2][k], h[k >> 2][k & 3], acc[t2]);
+                    for (int k = 0; k < HQ; ++k) acc[t] = mfma4(w2[t][k], h[k >> 2][k & 3], acc[t]);
                 }
+                d[u] = 0.0f;
 #pragma unroll
-                for (int t2 = 0; t2 < HT; ++t2)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) h[t2][j] = fmaxf(acc[t2][j], 0.0f);
-#pragma unroll
-                for (int k = 0; k < HQ; ++k) out = mfma4(sig_row ? wo[k] : 0.0f, h[k >> 2][k & 3], out);
+                for (int k = 0; k < HQ; ++k) d[u] = fmaf(wo[k], fmaxf(acc[k >> 2][k & 3], 0.0f), d[u]);
             }
-            if (todo && net == nsel) {
-                sg = fmaxf(out[3], 0.0f);
-                todo = false;
+            // sums over the lane groups, tile u's in lane group u
+            float half[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[q]), __float_as_uint(d[2 + q]), false, false);
+                half[q] = __uint_as_float(v[0]) + __uint_as_float(v[1]);
+            }
+            const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(half[0]), __float_as_uint(half[1]), false, false);
+            const float sg = fmaxf((__uint_as_float(v[0]) + __uint_as_float(v[1])) + bias_sig, 0.0f);
+            if (sg > job.tau && first + lane < points) {
+                const int64_t vx = box.v0[0] + (lo[0] + ix) / 3, vy = box.v0[1] + (lo[1] + iy) / 3, vz = box.v0[2] + (lo[2] + iz) / 3;
+                job.occupancy[(vx * job.occ.res[1] + vy) * job.occ.res[2] + vz] = 1;
             }
         }
-        __builtin_amdgcn_wave_barrier(); // the staging buffer is rewritten by the next iteration
-        kn_probe_mark(job, active, sg > job.tau, voxel, probe, lane);
+        __syncthreads(); // the tables are rewritten by the next part
     }
 }
 
@@ -574,16 +611,33 @@ int kn_direct_f32_launch(const kn_scene *sc, hipStream_t st, const KnDirectJob &
     return KN_OK;
 }
 
-int kn_probe_f32_launch(const kn_scene *sc, hipStream_t st, const KnProbeJob &job)
+int kn_probe_f32_launch(const kn_scene *sc, hipStream_t st, KnProbeJob job)
 {
     const int H = sc->desc.hidden;
     if (H != 32 && H != 64) return KN_E_UNSUPPORTED;
-    const dim3 grid((unsigned)(sc->cells * job.parts)), block(F32_WAVES * KN_WAVE);
+    // up to 48 probes per axis together; fewer in x where that leaves too few workgroups to fill the chip twice
+    int64_t parts = 1, probes[3];
+    for (int a = 0; a < 3; ++a) {
+        probes[a] = 3 * kn_div_up(job.occ.res[a], job.net_res[a]);
+        const int64_t cuts = kn_div_up(probes[a], 48);
+        job.sub[a] = (int32_t)kn_div_up(probes[a], cuts);
+        parts *= cuts;
+    }
+    while (sc->cells * parts < 2048 && job.sub[0] > 6) {
+        parts *= 2;
+        job.sub[0] = (job.sub[0] + 1) / 2;
+    }
+    if (parts > 65536) parts = 65536; // (a workgroup goes on to the cell's next part)
+    while (sc->cells * parts > 0x7fffffffLL) parts = kn_div_up(parts, 2);
+    job.parts = (int32_t)parts;
+    const int pitch = (job.sub[0] + job.sub[1] + job.sub[2]) | 1;
+    const size_t lds = (size_t)pitch * (H * 4 + 24 * 4);
+    const dim3 grid((unsigned)(sc->cells * parts)), block(F32_WAVES * KN_WAVE);
     const float *w = (const float *)sc->packed_w;
     if (H == 32)
-        hipLaunchKernelGGL(k_probe_f32<32>, grid, block, 0, st, w, job);
+        hipLaunchKernelGGL(k_probe_f32<32>, grid, block, lds, st, w, job);
     else
-        hipLaunchKernelGGL(k_probe_f32<64>, grid, block, 0, st, w, job);
+        hipLaunchKernelGGL(k_probe_f32<64>, grid, block, lds, st, w, job);
     KN_CHECK_LAUNCH();
     return KN_OK;
 }

@@ -471,7 +471,7 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
 
 
 // Density only, for occupancy extraction (Sec. 3.4): layers 1 and 2 and the density row of layer 3 at the probes of one
-// network cell (KnProbeRowsJob).
+// network cell (KnProbeBox).
 //
 // The probes of a cell are a lattice, and gamma(x) is a concatenation of what belongs to x, to y and to z, so layer 1 is a
 // sum of three vectors that depend on one coordinate each.  A wavefront takes the probes of one voxel in x, up to five in
@@ -491,7 +491,7 @@ constexpr int PROBE_Y = 5, PROBE_ZT = 3; // voxels in y, tiles of 16 probes in z
 __device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 template <int H, bool BF, int WAVES, bool WRAP>
 __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_per_eu(H == 32 ? 4 : 3, H == 32 ? 4 : 3)))
-    k_probe_mfma(const uint16_t *__restrict__ packed, KnProbeRowsJob job)
+    k_probe_mfma(const uint16_t *__restrict__ packed, KnProbeJob job)
 {
     using L = Lay<H>;
     constexpr int HT = L::HT, HK = L::HK, ROW = 4 * HT + 1; // (padded: 16 rows are written side by side)
@@ -506,19 +506,9 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
     const int32_t cell = kn_block() / job.parts, part = kn_block() - cell * job.parts;
     const int32_t net = __builtin_amdgcn_readfirstlane(kn_net_of_cell(job.cell_net, cell));
     if (net < 0) return; // no network: nothing to mark
-    // the cell's probes per axis, counted from the first one of voxel v0: p0 .. p1-1 (uniform, like all numbers of units)
-    int32_t v0[3], p0[3], p1[3];
-    {
-        const int32_t q = cell / job.net_res[2], c[3] = {q / job.net_res[1], q % job.net_res[1], cell % job.net_res[2]};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int64_t lo = job.first[a][c[a]], hi = job.first[a][c[a] + 1];
-            if (lo >= hi) return;
-            v0[a] = uniform((int32_t)((uint64_t)lo / 3u));
-            p0[a] = uniform((int32_t)(lo - 3 * (int64_t)v0[a]));
-            p1[a] = uniform((int32_t)(hi - 3 * (int64_t)v0[a]));
-        }
-    }
+    KnProbeBox box; // (all numbers of units are uniform)
+    if (!kn_probe_box(job, cell, box)) return;
+    const auto &v0 = box.v0, &p0 = box.p0, &p1 = box.p1;
     const int32_t nvx = (p1[0] + 2) / 3, nvy = (p1[1] + 2) / 3, z_tiles = (p1[2] - p0[2] + 15) / 16;
     const int32_t y_parts = (nvy + PROBE_Y - 1) / PROBE_Y, z_parts = (z_tiles + PROBE_ZT - 1) / PROBE_ZT;
     const int64_t units = (int64_t)nvx * y_parts * z_parts;
@@ -907,8 +897,18 @@ int kn_mlp_pack_weights(kn_scene *sc, hipStream_t st)
     return overflow ? KN_E_UNSUPPORTED : KN_OK;
 }
 
-int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, const KnProbeRowsJob &job)
+int kn_probe_mfma_launch(const kn_scene *sc, hipStream_t st, KnProbeJob job)
 {
+    int64_t units = 1;
+    for (int a = 0; a < 3; ++a) {
+        const int64_t per_cell = kn_div_up(job.occ.res[a], job.net_res[a]); // voxels
+        units *= a == 0 ? per_cell : kn_div_up(per_cell, a == 1 ? PROBE_Y : 16);
+    }
+    // several times the workgroups that are resident (1,024 at width 32), each wavefront with two units of work or more
+    int64_t parts = kn_div_up(4096, sc->cells);
+    if (parts > units / 8) parts = units / 8;
+    if (parts < 1) parts = 1;
+    job.parts = (int32_t)parts;
     const bool bf = sc->desc.wdtype == KN_BF16;
     const int H = sc->desc.hidden;
     float reach = 0.0f;

@@ -1302,6 +1302,23 @@ def test_extract_occupancy_edges_of_the_row_kernel(wdtype, H, res):
     extraction_check(sc, res, median_density(sc, res), sigma_unit=20.0)
 
 
+@pytest.mark.parametrize("H", [32, 64])
+@pytest.mark.parametrize("nres,res", [((3, 2, 2), (33, 3, 35)), ((1, 1, 1), (17, 18, 3)), ((2, 1, 3), (1, 33, 7)), ((7, 5, 6), (7, 11, 4)), ((2, 2, 2), (5, 5, 70))])
+def test_extract_occupancy_edges_of_the_fp32_kernel(H, nres, res):
+    # per cell and axis: 1 to 105 probes (up to 48 together: 16 voxels; 51, 52.5, 54, 99, 105 are cut into parts of unequal size), parts
+    # of fewer than 64 probes and of several chunks with a remainder, one to seven networks per axis, cut voxels
+    # A voxel whose oracle density lies within the fp32 bar of tau (a share of about 0.002 of them, see extraction_check) may come out
+    # either way; of 210 to 3,465 voxels 2 + 1 % is four standard deviations and more above what is expected.
+    sc = scene_dict(nres, (-1, 0, 0.5), (1, 2, 4.5), H, "f32", 36, sigma_scale=20.0)
+    dev, orc = make_pair(sc, threads=True)
+    tau = median_density(sc, res)
+    got = dev.extract_occupancy(res, tau).cpu().numpy()
+    want, _, mg = orc.extract_occupancy(res, tau)
+    close = mg <= 1e-4 * 20.0
+    assert 0.02 < want.mean() < 0.98 and close.sum() <= 2 + 0.01 * close.size
+    np.testing.assert_array_equal(got[~close], want[~close])
+
+
 def test_extract_occupancy_threshold_cases_and_single_network():
     import torch
     sc = scene_dict((1, 1, 1), (0, 0, 0), (1, 1, 1), 32, "f16", 33, sigma_scale=20.0)
