@@ -323,7 +323,7 @@ struct KnCountBack {
     float *out4;
     const uint32_t *at;   // nullptr: out4 is in the caller's order; else in the samples'
     const uint16_t *from;
-    int32_t nblk, threads;
+    int32_t nblk, rows, share;
 };
 struct KnSampleSrc;
 int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,

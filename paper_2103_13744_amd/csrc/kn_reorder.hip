@@ -441,6 +441,8 @@ __global__ void __launch_bounds__(OT_THREADS)
 //   the network at a time, and the wavefronts of a workgroup take their turns at the counts in LDS; the counts of the workgroups go to a (workgroup,
 //   network) table, k_table_scan sums them up (and is no launch more: there is nothing to be cleared), and k_place adds what is in front.
 constexpr int RANK_THREADS = 1024, RANK_BINS = 4; // networks per thread whose atomics are in flight together
+// tiles of c samples (tile_len: a power of two)
+__device__ __forceinline__ int32_t tiles_of(int32_t c, int32_t tile_len) { return (c + tile_len - 1) >> __builtin_ctz((uint32_t)tile_len); }
 // rows of a (workgroup, network) table start on lines
 __host__ __device__ inline int64_t table_stride(int32_t bins) { return (bins + 31) & ~31; }
 template <bool STABLE>
@@ -543,7 +545,7 @@ __global__ void __launch_bounds__(PLACE_THREADS)
             const int32_t inc = kn_wave_inclusive_scan(c);
             start[n] = sum + inc - c;
             sum += __builtin_amdgcn_readlane(inc, KN_WAVE - 1);
-            const int32_t t = n < N ? (c + tile_len - 1) / tile_len : 0;
+            const int32_t t = n < N ? tiles_of(c, tile_len) : 0;
             if (lane == 0) step_tiles[wv * per + s] = tile_sum;
             tile_sum += __builtin_amdgcn_readlane(kn_wave_inclusive_scan(t), KN_WAVE - 1);
             if (user_counts && n <= N && blockIdx.x == 0) user_counts[n] = c;
@@ -572,7 +574,7 @@ __global__ void __launch_bounds__(PLACE_THREADS)
     // tiles: those of step s of wavefront w are written by workgroup (w * per + s) % gridDim.x
     const int grid = (int)gridDim.x, first_s = ((int)blockIdx.x - wv * per % grid + grid) % grid;
     for (int s = first_s; s < per; s += grid) { // (uniform)
-        const int32_t n = b0 + s * KN_WAVE, c = n <= N ? counts[n] : 0, t = n < N ? (c + tile_len - 1) / tile_len : 0;
+        const int32_t n = b0 + s * KN_WAVE, c = n <= N ? counts[n] : 0, t = n < N ? tiles_of(c, tile_len) : 0;
         const int32_t inc = kn_wave_inclusive_scan(t), in_front = tiles_before + step_tiles[wv * per + s];
         // a lane writes its own network's tiles, the wavefront together those of a network with many (one network after
         // the other for all 64 took 5 of this kernel's 14 us at 65,537 points)
@@ -590,7 +592,7 @@ __global__ void __launch_bounds__(PLACE_THREADS)
 }
 
 // Order by counting with the samples themselves (kn_eval_grouped, large batches whose permutation nobody asks for): one
-// trip of the samples instead of one per digit.  A workgroup of T threads takes T * CO_ROWS consecutive points.
+// trip of the samples instead of one per digit.  A workgroup takes `share` consecutive points, up to ROWS per thread.
 //   k_keys_count    network of each point, the workgroup's count per network (LDS) -> row of the (workgroup, network) table
 //   k_table_scan    per network exclusive prefix over the workgroups, totals
 //   k_count_scatter the workgroup's samples into sorted order in LDS (a sample's rank comes from an LDS atomic), then to
@@ -601,26 +603,30 @@ __global__ void __launch_bounds__(PLACE_THREADS)
 // through the networks at the same pace, fill the lines in its L2 together.
 // From COUNT_BACK_M points on a result goes to its sample's own place (k_results_back), and the two halves are 12 bytes each; 16 with the key and the
 // result's place: 4 M points, 16^3 networks, scatter 72 us, MLP kernel 87 / 69, 80; 8 M skewed 127, 160 / 115, 148.
-// Bound by memory traffic: 4 M points, 16^3 networks: count 20 us, scan 6 (11 with rows of N + 1 entries, whose lines two workgroups share; 8 M 17 -> 10), scatter 68 (118 MB read, 126 to be written),
-// against 158 for the two radix passes and 10 for the search for the tiles.  Whole calls, width 32, fp16: 4 M points 322 -> 245 us, 10x16x10
-// networks 313 -> 215; 8 M 584 -> 470; 1 M 106 -> 76; 262,143 73 -> 57.
-constexpr int CO_ROWS = 8;
-// COUNT_MAX_N: the staging buffer of 1,024 threads (128 KB) and the networks' starts are the LDS of a compute unit.
-// COUNT_WIDE_M: 1,024 threads from where their workgroups nearly fill the chip (1.3 M points 99 us with 512, 1.4 M 89 with 1,024).
-// COUNT_MIN_M: see kn_order_pays, which is asked first.  (Few networks, where the radix sort is one trip as well: 5x8x5, 270,000 points 50 -> 38 us, 1 M
-// 67 -> 51, 4 M 219 -> 169; 2^3 with nine in ten points in one network, the most LDS atomics on one address, 4 M 279 -> 180.)
-// COUNT_BACK_M: 16-bit scenes from here on, and all with 1,024 threads: results go through k_results_back.  Width 32, fp16 / width 64, bf16,
-// 16^3 networks: 1.4 M points 88 -> 88 / 123 -> 111 us, 4 M 245 -> 218 / 285 -> 276 (halves of 16 bytes still); with 512 threads
-// 1.3 M 94.6 -> 94.0 / 128 -> 114, skewed 87 -> 81, 1 M 72.7 -> 69.9 / 89.5 -> 86.3, skewed 67 -> 62, 800,001 67.9 -> 65.9 / 82.7 -> 81.5, 500,003
-// 58.8 -> 58.1 / 72.6 -> 74.6, 270,001 55.3 -> 57.2 / 69.8 -> 72.7; fp32, whose evaluation the scattered stores don't hold up, 1.3 M 186 -> 190.
-constexpr int64_t COUNT_BACK_M = 5 << 17;
+// Bound by memory traffic: 4 M points, 16^3 networks: count 20 us, scan 6 (11 with rows of N + 1 entries, whose lines two workgroups share; 8 M 17 -> 10), scatter 59 (118 MB read, 126 to be written),
+// against 158 for the two radix passes and 10 for the search for the tiles.  Batches of less than a round of workgroups: by the chain of a workgroup's
+// phases (300,000 points: some 10 us in the kernel, of which reading the points 1, ranks 1.4, starts 2.3, either half 1 to 2).
+// Whole calls, width 32, fp16, against the radix passes: 4 M points 322 -> 180 us, 1 M 106 -> 63, 270,001 73 -> 36.
+constexpr int CO_T = 1024;
+// COUNT_MAX_N: the staging buffer of eight rows (128 KB) and the networks' starts are the LDS of a compute unit.
+// COUNT_WIDE_M: four rows where they hold a 256th of the batch.  Against 512 threads of eight rows (twice the networks per thread): 300,007 points
+// 48.8 -> 46.8 us, 1 M, width 64, bf16 82.5 -> 80.6.
+// COUNT_FULL_M: shares are a 256th or a 512th of the batch (all compute units, one or two workgroups one after the other, all of one size) up to here, beyond
+// as large as they can be, since short shares have short runs.  Shares of 4,096 / a 256th, 16^3 networks, fp16: 270,001 points 40.9 / 38.8 us, 560,001 51.7 / 49.6, 1.3 M
+// 83 / 74.6; of 8,192 / a 512th: 2.1 M 127 / 114, 2.5 M 131 / 125, 3.2 M 151 / 151; of 8,192 / a 768th: 5 M 230 / 239.
+// COUNT_MIN_M: see kn_order_pays, which is asked first.  (Few networks, where the radix sort is one trip as well: 5x8x5, 270,000 points 50 -> 30 us, 1 M
+// 67 -> 47, 4 M 219 -> 150; 2^3 with nine in ten points in one network, the most LDS atomics on one address, 4 M 279 -> 180.)
+// COUNT_BACK_M: 16-bit scenes from here on, and all with eight rows: results go through k_results_back.  Width 32, fp16 / width 64, bf16,
+// 16^3 networks, before / with it: 270,001 points 40.9 / 43.2, 55.9 / 58.7 us, 400,001 47.5 / 46.8, 59.6 / 61.0, 560,001 51.6 / 51.6, 67.2 / 67.3 (skewed, width 32, 46.6 / 44.1;
+// 5x8x5 38.8 / 37.6), 1 M 72.7 / 69.9, 89.5 / 86.3; fp32, whose evaluation the scattered stores don't hold up, 1.3 M 186 / 190.
+constexpr int64_t COUNT_BACK_M = 1 << 19;
 constexpr int32_t COUNT_MAX_N = 6143;
-constexpr int64_t COUNT_MIN_M = 1 << 17, COUNT_WIDE_M = 5 << 18;
+constexpr int64_t COUNT_MIN_M = 3 << 15, COUNT_WIDE_M = 1 << 20, COUNT_FULL_M = 1 << 22;
 typedef uint16_t h4_t __attribute__((ext_vector_type(4)));
 
 // Non-temporal: what a workgroup reads once stays out of the way of the lines that the workgroups of an XCD fill and read together in its L2.  4 M points,
 // 16^3 networks: k_count_scatter 68 -> 63 us, the MLP kernel 80 -> 77, k_results_back 40 -> 37; 8 M skewed 118 -> 108, 151 -> 147, 76 -> 73.  (With
-// 512 threads, whose batches fit the caches, 0.3 us slower; non-temporal stores of the results 38 -> 67.)
+// four rows, whose batches fit the caches, 0.3 us slower; non-temporal stores of the results 38 -> 67.)
 template <bool STREAM, typename V> __device__ __forceinline__ V load_once(const V *p)
 {
     if constexpr (STREAM) return __builtin_nontemporal_load(p);
@@ -639,11 +645,12 @@ __device__ __forceinline__ int32_t xcd_block(int32_t nblk)
     return x * each + min(x, more) + ((int32_t)blockIdx.x >> 3);
 }
 
-template <int T>
-__global__ void __launch_bounds__(T)
+template <int ROWS>
+__global__ void __launch_bounds__(CO_T)
     k_keys_count(const float *__restrict__ pts, int64_t M, KnGrid g, const int32_t *__restrict__ cell_net, int32_t *__restrict__ ids,
-                 uint16_t *__restrict__ keys, int32_t N, int32_t nblk, int32_t *__restrict__ table)
+                 uint16_t *__restrict__ keys, int32_t N, int32_t nblk, int32_t share, int32_t *__restrict__ table)
 {
+    constexpr int T = CO_T;
     extern __shared__ int32_t hist[]; // N + 1
     for (int i = threadIdx.x; i <= N; i += T) hist[i] = 0;
     __syncthreads();
@@ -655,15 +662,17 @@ __global__ void __launch_bounds__(T)
         atomicAdd(&hist[key], 1);
         return (uint16_t)key;
     };
-    const int64_t base = (int64_t)b * (T * CO_ROWS);
-    if (base + T * CO_ROWS <= M && ((uintptr_t)pts & 15) == 0) { // (uniform) four points per thread and step, 16-byte loads
-        float4 v[CO_ROWS / 4][3];
+    const int64_t base = (int64_t)b * share;
+    const int32_t n_here = (int32_t)min((int64_t)share, M - base);
+    if ((n_here & 3) == 0 && ((uintptr_t)pts & 15) == 0) { // (uniform) four points per thread and step, 16-byte loads
+        float4 v[ROWS / 4][3];
 #pragma unroll
-        for (int r = 0; r < CO_ROWS / 4; ++r)
+        for (int r = 0; r < ROWS / 4; ++r)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) v[r][c] = *(const float4 *)(pts + 3 * (base + 4 * (r * T + (int)threadIdx.x)) + 4 * c);
+            for (int c = 0; c < 3; ++c) v[r][c] = *(const float4 *)(pts + 3 * (base + min(4 * (r * T + (int)threadIdx.x), n_here - 4)) + 4 * c);
 #pragma unroll
-        for (int r = 0; r < CO_ROWS / 4; ++r) {
+        for (int r = 0; r < ROWS / 4; ++r) {
+            if (4 * (r * T + (int)threadIdx.x) >= n_here) break;
             const int64_t i = base + 4 * (r * T + (int)threadIdx.x);
             const float4 p = v[r][0], q = v[r][1], s = v[r][2];
             h4_t k;
@@ -675,9 +684,9 @@ __global__ void __launch_bounds__(T)
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < CO_ROWS; ++r) {
+        for (int r = 0; r < ROWS; ++r) {
             const int64_t i = base + r * T + threadIdx.x;
-            if (i < M) keys[i] = point(i, pts[3 * i], pts[3 * i + 1], pts[3 * i + 2]);
+            if (i < base + n_here) keys[i] = point(i, pts[3 * i], pts[3 * i + 1], pts[3 * i + 2]);
         }
     }
     __syncthreads();
@@ -727,56 +736,79 @@ __global__ void __launch_bounds__(1024) k_table_scan(int32_t *__restrict__ table
     }
 }
 
-// Dynamic LDS: T * CO_ROWS halves of 16 bytes (first the counts), then N + 1 ints.
-// networks whose tiles one workgroup writes, at most: network d is workgroup d % nblk's
-constexpr int co_list(int threads)
-{
-    const int64_t min_m = threads == 512 ? COUNT_MIN_M : COUNT_WIDE_M, min_blocks = min_m / (threads * CO_ROWS);
-    return (int)((COUNT_MAX_N + min_blocks) / min_blocks);
-}
-static_assert((COUNT_MAX_N + 1) * 4 <= 512 * CO_ROWS * 16, "the counts share the staging buffer's place");
+// Dynamic LDS: CO_T * ROWS halves of 16 bytes (first the counts), then N + 1 ints.
+// CO_LIST: networks whose tiles one workgroup writes, at most: network d is workgroup d % nblk's, and there are 250 workgroups or more (a share is
+// less than 4 points more than a 256th of COUNT_MIN_M points or more, and at most a 512th of more than COUNT_FULL_M).
+constexpr int CO_LIST = (COUNT_MAX_N + 249) / 250;
+static_assert((COUNT_MAX_N + 1) * 4 <= CO_T * 4 * 16, "the counts share the staging buffer's place");
+constexpr int LIST_LANES = 16, LIST_LONG = 512; // lanes that write one network's tiles; those of networks with more than LIST_LONG the whole workgroup writes
 struct f3_t { float x, y, z; };
-template <int T, bool BACK>
-__global__ void __launch_bounds__(T)
+__device__ __forceinline__ int opaque(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+// What a thread needs of its networks is requested with the points, all of it together, and a thread's place is made anew for each phase (left to
+// itself the compiler keeps the addresses of all phases from the start on, which took the registers for that): one network after the other 24.6 us at
+// 300,007 points, 23.8 at 1 M, 63 at 4 M; so, with the tiles by sixteen lanes per network, 13 / 19 / 59.
+template <int ROWS, bool BACK>
+__global__ void __launch_bounds__(CO_T)
     k_count_scatter(const uint16_t *__restrict__ keys, const float *__restrict__ pts, const float *__restrict__ dirs, void *__restrict__ pout,
-                    void *__restrict__ dout, int64_t M, int32_t N, int32_t nblk, const int32_t *__restrict__ table,
+                    void *__restrict__ dout, int64_t M, int32_t N, int32_t nblk, int32_t share, const int32_t *__restrict__ table,
                     const int32_t *__restrict__ totals, int32_t tile_len, int32_t *__restrict__ user_counts, KnTile *__restrict__ tiles,
                     int32_t *__restrict__ n_tiles, uint32_t *__restrict__ at, uint16_t *__restrict__ from, float *__restrict__ out4)
 {
-    constexpr bool STREAM = T == 1024;
+    constexpr int T = CO_T;
+    constexpr bool STREAM = ROWS == 8;
     extern __shared__ u4 stage[];
     __shared__ int32_t s_sum[3][T / KN_WAVE];
-    __shared__ int4 s_list[co_list(T)]; // (network, samples, first sample, first tile)
-    __shared__ int32_t s_listed;
-    int32_t *cnt = (int32_t *)stage, *delta = (int32_t *)(stage + T * CO_ROWS);
-    const int lane = threadIdx.x & (KN_WAVE - 1), wv = threadIdx.x / KN_WAVE;
+    __shared__ int4 s_list[CO_LIST]; // (network, samples, first sample, first tile)
+    __shared__ int32_t s_listed, s_long; // how many; whether one has more than LIST_LONG tiles
+    int32_t *cnt = (int32_t *)stage, *delta = (int32_t *)(stage + T * ROWS);
+    int tid = threadIdx.x;
+    const int lane = tid & (KN_WAVE - 1), wv = tid / KN_WAVE;
     const int32_t b = xcd_block(nblk), bins = N + 1;
-    const int64_t base = (int64_t)b * (T * CO_ROWS);
-    const int32_t n_here = (int32_t)min((int64_t)(T * CO_ROWS), M - base);
-    if (threadIdx.x == 0) s_listed = 0;
-    for (int i = threadIdx.x; i < bins; i += T) cnt[i] = 0;
-    uint32_t key[CO_ROWS];
-    float p[CO_ROWS][3];
+    const int64_t base = (int64_t)b * share;
+    const int32_t n_here = (int32_t)min((int64_t)share, M - base);
+    if (tid == 0) s_listed = s_long = 0;
+    for (int i = tid; i < bins; i += T) cnt[i] = 0;
+    uint32_t key[ROWS];
+    float p[ROWS][3];
 #pragma unroll
-    for (int r = 0; r < CO_ROWS; ++r) {
-        const int64_t i = base + min(r * T + (int)threadIdx.x, n_here - 1);
+    for (int r = 0; r < ROWS; ++r) {
+        const int64_t i = base + min(r * T + tid, n_here - 1);
         key[r] = load_once<STREAM>(keys + i);
 #pragma unroll
         for (int c = 0; c < 3; ++c) p[r][c] = load_once<STREAM>(pts + 3 * i + c);
     }
-    __syncthreads();
-    int32_t lpos[CO_ROWS];
+    // thread t: networks t * per ..
+    const int32_t per = (bins + T - 1) / T, d0 = min(tid * per, bins), d1 = min(d0 + per, bins);
+    constexpr int KEPT = (COUNT_MAX_N + T) / T;
+    int32_t total[KEPT], in_front[KEPT], here[KEPT]; // all requested together
+    const int32_t *const row = table + b * table_stride(bins);
 #pragma unroll
-    for (int r = 0; r < CO_ROWS; ++r) lpos[r] = r * T + (int)threadIdx.x < n_here ? atomicAdd(&cnt[key[r]], 1) : 0;
+    for (int j = 0; j < KEPT; ++j)
+        if (j < per) total[j] = totals[min(d0 + j, N)];
+#pragma unroll
+    for (int j = 0; j < KEPT; ++j)
+        if (j < per) in_front[j] = row[min(d0 + j, N)];
     __syncthreads();
-    // thread t: networks t * per ..; sums in front of them of the workgroup's samples, of all samples and of tiles
-    const int32_t per = (bins + T - 1) / T, d0 = min((int32_t)threadIdx.x * per, bins), d1 = min(d0 + per, bins);
+    int32_t lpos[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) lpos[r] = r * T + tid < n_here ? atomicAdd(&cnt[key[r]], 1) : 0;
+    __syncthreads();
+    // sums in front of a thread's networks of the workgroup's samples, of all samples and of tiles
     int32_t own[3] = {0, 0, 0}, run[3];
-    for (int32_t d = d0; d < d1; ++d) {
-        const int32_t c = totals[d];
-        own[0] += cnt[d];
-        own[1] += c;
-        own[2] += d < N ? (c + tile_len - 1) / tile_len : 0;
+#pragma unroll
+    for (int j = 0; j < KEPT; ++j)
+        if (j < per) here[j] = cnt[min(d0 + j, N)];
+#pragma unroll
+    for (int j = 0; j < KEPT; ++j) {
+        if (j >= per) break; // (uniform)
+        if (d0 + j >= d1) here[j] = total[j] = 0; // (another thread's, or none)
+        own[0] += here[j];
+        own[1] += total[j];
+        own[2] += d0 + j < N ? tiles_of(total[j], tile_len) : 0;
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -791,28 +823,38 @@ __global__ void __launch_bounds__(T)
         for (int q = 0; q < 3; ++q) run[q] += w < wv ? s_sum[q][w] : 0;
         tiles_all += s_sum[2][w];
     }
-    if (b == 0 && threadIdx.x == 0) *n_tiles = tiles_all;
-    for (int32_t d = d0; d < d1; ++d) {
-        const int32_t c = totals[d], n_t = d < N ? (c + tile_len - 1) / tile_len : 0, mine = cnt[d];
-        delta[d] = run[1] + table[b * table_stride(bins) + d] - run[0];
-        cnt[d] = run[0];
-        if (n_t > 0 && d % nblk == b) s_list[atomicAdd(&s_listed, 1)] = make_int4(d, c, run[1], run[2]);
-        if (user_counts && b == 0) user_counts[d] = c;
-        run[0] += mine;
-        run[1] += c;
+    if (b == 0 && tid == 0) *n_tiles = tiles_all;
+    int32_t turn = d0 % nblk; // (network d's tiles are written by workgroup d % nblk)
+#pragma unroll
+    for (int j = 0; j < KEPT; ++j) {
+        if (j >= per) break;
+        const int32_t d = d0 + j, n_t = d < N ? tiles_of(total[j], tile_len) : 0;
+        if (d < d1) {
+            delta[d] = run[1] + in_front[j] - run[0];
+            cnt[d] = run[0];
+            if (user_counts && b == 0) user_counts[d] = total[j];
+        }
+        if (n_t > 0 && turn == b) {
+            s_list[atomicAdd(&s_listed, 1)] = make_int4(d, total[j], run[1], run[2]);
+            if (n_t > LIST_LONG) s_long = 1;
+        }
+        if (++turn == nblk) turn = 0;
+        run[0] += here[j];
+        run[1] += total[j];
         run[2] += n_t;
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < CO_ROWS; ++r) lpos[r] += cnt[key[r]];
+    for (int r = 0; r < ROWS; ++r) lpos[r] += cnt[key[r]];
     __syncthreads(); // the counts' place is the staging buffer's from here on
 #pragma unroll
-    for (int r = 0; r < CO_ROWS; ++r)
-        if (r * T + (int)threadIdx.x < n_here)
+    for (int r = 0; r < ROWS; ++r)
+        if (r * T + tid < n_here)
             stage[lpos[r]] = (u4){__float_as_uint(p[r][0]), __float_as_uint(p[r][1]), __float_as_uint(p[r][2]), key[r]};
+    tid = opaque(tid);
 #pragma unroll
-    for (int r = 0; r < CO_ROWS; ++r) { // (the second halves are under way while the first ones are written)
-        const int64_t i = base + min(r * T + (int)threadIdx.x, n_here - 1);
+    for (int r = 0; r < ROWS; ++r) { // (the second halves are under way while the first ones are written)
+        const int64_t i = base + min(r * T + tid, n_here - 1);
         if (!BACK && key[r] == (uint32_t)N) *(float4 *)(out4 + 4 * i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int c = 0; c < 3; ++c) p[r][c] = load_once<STREAM>(dirs + 3 * i + c);
@@ -823,10 +865,11 @@ __global__ void __launch_bounds__(T)
         if constexpr (BACK) ((f3_t *)half)[i] = (f3_t){__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2])};
         else ((u4 *)half)[i] = v;
     };
-    int32_t dst[CO_ROWS];
+    tid = opaque(tid);
+    int32_t dst[ROWS];
 #pragma unroll
-    for (int k = 0; k < CO_ROWS; ++k) {
-        const int32_t sp = k * T + threadIdx.x;
+    for (int k = 0; k < ROWS; ++k) {
+        const int32_t sp = k * T + tid;
         if (sp < n_here) {
             const u4 v = stage[sp];
             dst[k] = sp + delta[v[3]];
@@ -838,13 +881,13 @@ __global__ void __launch_bounds__(T)
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < CO_ROWS; ++r)
-        if (r * T + (int)threadIdx.x < n_here)
-            stage[lpos[r]] = (u4){__float_as_uint(p[r][0]), __float_as_uint(p[r][1]), __float_as_uint(p[r][2]), (uint32_t)(r * T + threadIdx.x)};
+    for (int r = 0; r < ROWS; ++r)
+        if (r * T + tid < n_here)
+            stage[lpos[r]] = (u4){__float_as_uint(p[r][0]), __float_as_uint(p[r][1]), __float_as_uint(p[r][2]), (uint32_t)(r * T + tid)};
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < CO_ROWS; ++k) {
-        const int32_t sp = k * T + threadIdx.x;
+    for (int k = 0; k < ROWS; ++k) {
+        const int32_t sp = k * T + tid;
         if (sp < n_here) {
             u4 v = stage[sp];
             if constexpr (BACK) store_once<STREAM>(from + base + sp, (uint16_t)v[3]);
@@ -852,22 +895,18 @@ __global__ void __launch_bounds__(T)
             put(dout, dst[k], v);
         }
     }
-    // tiles: a wavefront per network, the whole workgroup for networks of more than one tile per lane
+    // tiles: sixteen lanes per network, the whole workgroup for networks of many (a wavefront per network, and a look at the whole list for
+    // those of more tiles than lanes: 3 of this kernel's 18 us at 300,000 points)
     const int32_t listed = s_listed;
-    for (int pass = 0; pass < 2; ++pass)
-        for (int e = pass == 0 ? wv : 0; e < listed; e += pass == 0 ? T / KN_WAVE : 1) {
-            const int4 l = s_list[e];
-            const int32_t n_t = (l.y + tile_len - 1) / tile_len;
-            if ((n_t > KN_WAVE) != (pass == 1)) continue;
-            for (int32_t k = pass == 0 ? lane : (int)threadIdx.x; k < n_t; k += pass == 0 ? KN_WAVE : T) {
-                KnTile tl;
-                tl.net = l.x;
-                tl.start = l.z + k * tile_len;
-                tl.len = min(tile_len, l.y - k * tile_len);
-                tl.pad = 0;
-                tiles[l.w + k] = tl;
-            }
-        }
+    auto write_tiles = [&](const int4 &l, int32_t first, int32_t stride) {
+        const int32_t n_t = tiles_of(l.y, tile_len);
+        for (int32_t k = first; k < n_t; k += stride) tiles[l.w + k] = KnTile{l.x, l.z + k * tile_len, min(tile_len, l.y - k * tile_len), 0};
+    };
+    for (int e = tid / LIST_LANES; e < listed; e += T / LIST_LANES)
+        if (const int4 l = s_list[e]; tiles_of(l.y, tile_len) <= LIST_LONG) write_tiles(l, tid & (LIST_LANES - 1), LIST_LANES);
+    if (s_long) // (uniform)
+        for (int e = 0; e < listed; ++e)
+            if (const int4 l = s_list[e]; tiles_of(l.y, tile_len) > LIST_LONG) write_tiles(l, tid, T);
 }
 
 // Results in the order of the samples -> the caller's sigma and rgb arrays, by the workgroups of k_count_scatter: sample `sp` of
@@ -875,32 +914,33 @@ __global__ void __launch_bounds__(T)
 // results, which its neighbours on the XCD read the rest of the lines of, and writes its points one after the other.
 // Instead of one random 16-byte store per sample by the MLP kernel (one transaction each, 57 G/s): 4 M points, 16^3 networks,
 // MLP kernel 120 -> 83 us, this kernel 40 (169 MB, 4.2 TB/s) against 25 for k_split_results.
-template <int T>
-__global__ void __launch_bounds__(T)
-    k_results_back(const float *__restrict__ out4, const uint32_t *__restrict__ at, const uint16_t *__restrict__ from, int64_t M, int32_t nblk,
+template <int ROWS>
+__global__ void __launch_bounds__(CO_T)
+    k_results_back(const float *__restrict__ out4, const uint32_t *__restrict__ at, const uint16_t *__restrict__ from, int64_t M, int32_t nblk, int32_t share,
                    float *__restrict__ sigma, float *__restrict__ rgb)
 {
-    constexpr bool STREAM = T == 1024;
-    extern __shared__ u4 stage[]; // T * CO_ROWS results
-    const int64_t base = (int64_t)xcd_block(nblk) * (T * CO_ROWS);
-    const int32_t n_here = (int32_t)min((int64_t)(T * CO_ROWS), M - base);
-    uint32_t a[CO_ROWS], f[CO_ROWS];
-    u4 v[CO_ROWS];
+    constexpr int T = CO_T;
+    constexpr bool STREAM = ROWS == 8;
+    extern __shared__ u4 stage[]; // T * ROWS results
+    const int64_t base = (int64_t)xcd_block(nblk) * share;
+    const int32_t n_here = (int32_t)min((int64_t)share, M - base);
+    uint32_t a[ROWS], f[ROWS];
+    u4 v[ROWS];
 #pragma unroll
-    for (int k = 0; k < CO_ROWS; ++k) {
+    for (int k = 0; k < ROWS; ++k) {
         const int64_t i = base + min(k * T + (int)threadIdx.x, n_here - 1);
         a[k] = load_once<STREAM>(at + i);
         f[k] = load_once<STREAM>(from + i);
     }
 #pragma unroll
-    for (int k = 0; k < CO_ROWS; ++k) v[k] = *(const u4 *)(out4 + 4 * (int64_t)a[k]);
+    for (int k = 0; k < ROWS; ++k) v[k] = *(const u4 *)(out4 + 4 * (int64_t)a[k]);
 #pragma unroll
-    for (int k = 0; k < CO_ROWS; ++k) stage[f[k]] = v[k]; // (beyond the end: the last sample once more)
+    for (int k = 0; k < ROWS; ++k) stage[f[k]] = v[k]; // (beyond the end: the last sample once more)
     __syncthreads();
     const float *res = (const float *)stage;
-    const bool aligned = (((uintptr_t)sigma | (uintptr_t)rgb) & 15) == 0; // (base is a multiple of 4,096)
+    const bool aligned = (((uintptr_t)sigma | (uintptr_t)rgb) & 15) == 0; // (base is a multiple of 4)
 #pragma unroll
-    for (int r = 0; r < CO_ROWS / 4; ++r) {
+    for (int r = 0; r < ROWS / 4; ++r) {
         const int32_t q = 4 * (r * T + (int)threadIdx.x);
         if (q + 3 < n_here && aligned) {
             float4 o[4];
@@ -1077,7 +1117,7 @@ int64_t order_ws_bytes(int64_t M, int32_t N, bool stable)
 // Every workgroup of k_place scans the counts of all networks, in steps of 1,024, and keeps their starts in LDS.
 constexpr int32_t ORDER_MAX_N = 32768;
 static_assert(place_lds((ORDER_MAX_N + PLACE_THREADS) / PLACE_THREADS) <= 150 * 1024, "the starts of the networks (k_place) fit the LDS of a compute unit");
-constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_FEW = 1 << 17;
+constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_COUNTED = 5 << 15, ORDER_MAX_M_FEW = 3 << 15;
 constexpr int32_t ORDER_FEW = 512, ORDER_STABLE_MAX_N = 24575;
 } // namespace
 
@@ -1088,16 +1128,17 @@ int64_t kn_order_ws_bytes(int64_t M, int32_t N) { return order_ws_bytes(M, N, fa
 // costs more than moving the samples does once a batch is far larger than the caches.  65,537 points, fp16, width 32, against the
 // radix passes: 16^3 networks 66 us -> 29, 10x16x10 61 -> 28, 5x8x5 39 -> 25; fp32 (10x16x10) 77 -> 35; in random order over two
 // cells of 16^3 60 -> 27. Against
-// kn_count_run (150,001 / 220,001 / 270,001 / 330,001 points, us): 16^3 networks, fp16, 36 / 44 / 52 / 60 against 55 / 54 / 55 / 56,
-// skewed (nine in ten points in a twentieth of the cells) 38 / 45 / 50 / 57 against 54 / 52 / 53 / 53, 10x16x10, bf16, skewed 29 / 35 / 40 / 45
-// against 39 / 39 / 41 / 41, width 64 36 / 46 / 50 / 56 against 45 / 48 / 50 / 50, fp32 49 / 62 / 67 / 71 against 60 / 70 / 74 / 75; 20^3 (radix
-// passes) 47 / 56 / 63 / 69 against 75 / 79 / 78 / 80.  Few networks, whose table is counted in fewer rows and whose atomics meet:
-// 5x8x5 32 / 38 / 41 / 47 against 30 / 32 / 35 / 37.  Many networks, against the radix passes (28,000 / 65,000 / 260,000 points): 24x20x28, fp16, 50 / 56 /
+// kn_count_run (100,001 / 140,001 / 160,001 / 180,001 / 196,001 points, us): 16^3 networks, fp16, 29 / 31 / 33 / 35 / 38 against 32 / 33 / 34 / 35 / 36,
+// bf16, skewed (nine in ten points in a twentieth of the cells) 29 / 33 / 34 / 37 / 38 against 32 / 33 / 33 / 34 / 34, width 64 40 / 45 / 48 / 49 / 52 against
+// 44 / 45 / 45 / 48 / 49, 10x16x10 22 / 26 / 27 / 29 / 31 against 26 / 28 / 28 / 29 / 29; fp32, whose tiles and not whose order decide, 160,001 / 220,001 / 260,001
+// 51 / 67 / 72 against 53 / 68 / 70; 20^3 (radix passes, 150,001 / 220,001 / 270,001) 47 / 56 / 63 against 75 / 79 / 78.  Few networks, whose table is counted in fewer
+// rows and whose atomics meet (5x8x5, 70,001 / 100,001 / 120,001): 19 / 24 / 28 against 22 / 22 / 24, fp32 29 / 33 / 38 against 33 / 34 / 35.  Many networks, against the radix passes (28,000 / 65,000 / 260,000 points): 24x20x28, fp16, 50 / 56 /
 // 78 against 80 / 83 / 91, skewed 35 / 42 / 76 against 65 / 71 / 89, fp32 94 / 108 / 131 against 119 / 132 / 149; 32^3, fp16, 83 / 110 / 144 against
 // 99 / 123 / 152, skewed 57 / 64 / 110 against 72 / 79 / 110, bf16, width 64, 160 / 219 / 308 against 171 / 231 / 317.
 bool kn_order_pays(const kn_scene *sc, int64_t M)
 {
-    return sc->N <= ORDER_MAX_N && M <= (sc->N <= ORDER_FEW ? ORDER_MAX_M_FEW : ORDER_MAX_M);
+    const int64_t line = sc->N <= ORDER_FEW ? ORDER_MAX_M_FEW : sc->desc.wdtype == KN_F32 ? ORDER_MAX_M : ORDER_MAX_M_COUNTED;
+    return sc->N <= ORDER_MAX_N && (M <= line || (M <= ORDER_MAX_M && !kn_count_pays(M, sc->N)));
 }
 
 // The stable order, against the radix passes (3,000 / 40,000 / 260,000 / 550,000 points, us, with the ids, the counts and the permutation): 16^3 networks, fp16,
@@ -1115,7 +1156,7 @@ int kn_order_run(const kn_scene *sc, hipStream_t st, const float *points, int64_
                  int32_t *user_counts, int32_t *user_perm, float *sigma, float *rgb, KnCarver &ws, KnBucketOut *out, KnStageTimer *tm)
 {
     const int32_t N = sc->N;
-    if (M < 1 || M > (1ll << 30) || N < 1 || N > ORDER_MAX_N || tile_len < 64) return KN_E_INVALID_ARG;
+    if (M < 1 || M > (1ll << 30) || N < 1 || N > ORDER_MAX_N || tile_len < 64 || (tile_len & (tile_len - 1)) != 0) return KN_E_INVALID_ARG;
     OrderWs w;
     carve_order(ws, M, N, user_perm != nullptr, w);
     if (!ws.ok()) return KN_E_WORKSPACE;
@@ -1153,13 +1194,14 @@ struct CountWs {
     uint32_t *at;
     uint16_t *from;
     float *out4;
-    int32_t threads, nblk;
+    int32_t rows, share, nblk;
 };
 bool count_back(int64_t M, bool fp32) { return M > COUNT_WIDE_M || (!fp32 && M >= COUNT_BACK_M); }
 void carve_count(KnCarver &c, int64_t M, int32_t N, bool back, CountWs &w)
 {
-    w.threads = M > COUNT_WIDE_M ? 1024 : 512;
-    w.nblk = (int32_t)kn_div_up(M, w.threads * CO_ROWS);
+    w.rows = M > COUNT_WIDE_M ? 8 : 4;
+    w.share = (int32_t)(M <= COUNT_FULL_M ? kn_align_up(kn_div_up(M, M <= COUNT_FULL_M / 2 ? 256 : 512), 4) : CO_T * w.rows);
+    w.nblk = (int32_t)kn_div_up(M, w.share);
     w.n_tiles = c.carve<int32_t>(1);
     w.totals = c.carve<int32_t>(N + 1);
     w.table = c.carve<int32_t>(w.nblk * table_stride(N + 1));
@@ -1172,39 +1214,40 @@ void carve_count(KnCarver &c, int64_t M, int32_t N, bool back, CountWs &w)
     w.from = back ? c.carve<uint16_t>(M) : nullptr;
     w.out4 = c.carve<float>(4 * M);
 }
-} // namespace
-
-bool kn_count_pays(int64_t M, int32_t N) { return N <= COUNT_MAX_N && M >= COUNT_MIN_M; }
-
-int64_t kn_count_ws_bytes(int64_t M, int32_t N)
+int64_t count_bytes(int64_t M, int32_t N)
 {
-    if (!kn_count_pays(M, N)) return 0;
     KnCarver c((void *)256, INT64_MAX / 2);
     CountWs w;
     carve_count(c, M, N, count_back(M, true), w); // (the two ways differ in 2 bytes per point; the larger one)
     return c.used;
 }
+} // namespace
+
+// (in no more workspace than the passes take: the table is the larger part of it for many networks and few points)
+bool kn_count_pays(int64_t M, int32_t N) { return N <= COUNT_MAX_N && M >= COUNT_MIN_M && count_bytes(M, N) <= kn_reorder_ws_bytes(M, N); }
+
+int64_t kn_count_ws_bytes(int64_t M, int32_t N) { return kn_count_pays(M, N) ? count_bytes(M, N) : 0; }
 
 int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const float *dirs, int64_t M, int32_t tile_len,
                  int32_t *user_ids, int32_t *user_counts, KnCarver &ws, KnBucketOut *out, KnSampleSrc *src, KnCountBack *back,
                  KnStageTimer *tm)
 {
     const int32_t N = sc->N;
-    if (!kn_count_pays(M, N) || M > (1ll << 30) || tile_len < 64) return KN_E_INVALID_ARG;
+    if (!kn_count_pays(M, N) || M > (1ll << 30) || tile_len < 64 || (tile_len & (tile_len - 1)) != 0) return KN_E_INVALID_ARG;
     CountWs w;
     carve_count(ws, M, N, count_back(M, sc->desc.wdtype == KN_F32), w);
     if (!ws.ok()) return KN_E_WORKSPACE;
-    const dim3 grid((unsigned)w.nblk), block((unsigned)w.threads);
+    const dim3 grid((unsigned)w.nblk), block(CO_T);
     const size_t bins = (size_t)(N + 1) * 4;
-    auto count = w.threads == 1024 ? k_keys_count<1024> : k_keys_count<512>;
-    auto scatter = w.threads == 1024 ? k_count_scatter<1024, true> : w.at ? k_count_scatter<512, true> : k_count_scatter<512, false>;
-    hipLaunchKernelGGL(count, grid, block, bins, st, points, M, sc->net_grid, sc->cell_net, user_ids, w.keys, N, w.nblk, w.table);
+    auto count = w.rows == 8 ? k_keys_count<8> : k_keys_count<4>;
+    auto scatter = w.rows == 8 ? k_count_scatter<8, true> : w.at ? k_count_scatter<4, true> : k_count_scatter<4, false>;
+    hipLaunchKernelGGL(count, grid, block, bins, st, points, M, sc->net_grid, sc->cell_net, user_ids, w.keys, N, w.nblk, w.share, w.table);
     KN_CHECK_LAUNCH();
     if (tm) tm->mark(KN_ST_CELL);
     hipLaunchKernelGGL(k_table_scan, dim3((unsigned)kn_div_up(N + 1, TS_NETS)), dim3(1024), 0, st, w.table, N + 1, w.nblk, w.totals);
     KN_CHECK_LAUNCH();
-    hipLaunchKernelGGL(scatter, grid, block, (size_t)w.threads * CO_ROWS * sizeof(u4) + bins, st, w.keys, points, dirs, w.pos, w.dir, M, N,
-                       w.nblk, w.table, w.totals, tile_len, user_counts, w.tiles, w.n_tiles, w.at, w.from, w.out4);
+    hipLaunchKernelGGL(scatter, grid, block, (size_t)CO_T * w.rows * sizeof(u4) + bins, st, w.keys, points, dirs, w.pos, w.dir, M, N,
+                       w.nblk, w.share, w.table, w.totals, tile_len, user_counts, w.tiles, w.n_tiles, w.at, w.from, w.out4);
     KN_CHECK_LAUNCH();
     out->perm = nullptr; // the records are the sorted list
     out->counts = w.totals;
@@ -1219,16 +1262,16 @@ int kn_count_run(const kn_scene *sc, hipStream_t st, const float *points, const 
         src->records_dir = (const uint32_t *)w.dir;
     }
     src->out4 = w.out4;
-    *back = KnCountBack{w.out4, w.at, w.from, w.nblk, w.threads};
+    *back = KnCountBack{w.out4, w.at, w.from, w.nblk, w.rows, w.share};
     return KN_OK;
 }
 
 int kn_count_results(hipStream_t st, const KnCountBack &back, int64_t M, float *sigma, float *rgb)
 {
     if (!back.at) return kn_reorder_split_results(st, back.out4, M, sigma, rgb);
-    auto kernel = back.threads == 1024 ? k_results_back<1024> : k_results_back<512>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)back.nblk), dim3((unsigned)back.threads), back.threads * CO_ROWS * sizeof(u4), st, back.out4, back.at,
-                       back.from, M, back.nblk, sigma, rgb);
+    auto kernel = back.rows == 8 ? k_results_back<8> : k_results_back<4>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)back.nblk), dim3(CO_T), (size_t)CO_T * back.rows * sizeof(u4), st, back.out4, back.at,
+                       back.from, M, back.nblk, back.share, sigma, rgb);
     KN_CHECK_LAUNCH();
     return KN_OK;
 }
@@ -1334,11 +1377,11 @@ int kn_reorder_configure()
     KN_HIP(hipFuncSetAttribute((const void *)k_rank<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (ORDER_MAX_N + 1) * 4));
     KN_HIP(hipFuncSetAttribute((const void *)k_place, hipFuncAttributeMaxDynamicSharedMemorySize,
                                place_lds((int)kn_div_up(ORDER_MAX_N + 1, PLACE_THREADS))));
-    constexpr int half = 512 * CO_ROWS * 16, full = 1024 * CO_ROWS * 16;
-    KN_HIP(hipFuncSetAttribute((const void *)k_results_back<512>, hipFuncAttributeMaxDynamicSharedMemorySize, half));
-    KN_HIP(hipFuncSetAttribute((const void *)k_results_back<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, full));
-    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<512, false>, hipFuncAttributeMaxDynamicSharedMemorySize, half + counts));
-    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<512, true>, hipFuncAttributeMaxDynamicSharedMemorySize, half + counts));
-    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<1024, true>, hipFuncAttributeMaxDynamicSharedMemorySize, full + counts));
+    constexpr int half = CO_T * 4 * 16, full = CO_T * 8 * 16;
+    KN_HIP(hipFuncSetAttribute((const void *)k_results_back<4>, hipFuncAttributeMaxDynamicSharedMemorySize, half));
+    KN_HIP(hipFuncSetAttribute((const void *)k_results_back<8>, hipFuncAttributeMaxDynamicSharedMemorySize, full));
+    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<4, false>, hipFuncAttributeMaxDynamicSharedMemorySize, half + counts));
+    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, half + counts));
+    KN_HIP(hipFuncSetAttribute((const void *)k_count_scatter<8, true>, hipFuncAttributeMaxDynamicSharedMemorySize, full + counts));
     return KN_OK;
 }

@@ -1983,6 +1983,18 @@ def test_eval_grouped_whose_results_come_back_through_lds(wdtype, H, res, M, spr
     test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
 
 
+@pytest.mark.parametrize("wdtype,H,res,M", [("f16", 32, (8, 8, 8), 3 << 15), ("bf16", 32, (8, 8, 8), (3 << 15) + 1), ("f32", 32, (5, 8, 5), (3 << 15) + 4),
+                                            ("f16", 32, (16, 16, 16), 5 << 15), ("bf16", 64, (16, 16, 16), (5 << 15) + 1), ("f16", 32, (10, 16, 10), (5 << 15) + 2),
+                                            ("f16", 32, (23, 23, 11), (5 << 15) + 4), ("f16", 32, (17, 19, 19), 170003), ("bf16", 32, (2, 2, 2), 1 << 19),
+                                            ("f16", 32, (17, 19, 19), 1 << 20), ("f16", 32, (17, 19, 19), (1 << 20) + 1), ("bf16", 32, (10, 16, 10), (1 << 21) + 1),
+                                            ("f16", 32, (16, 16, 16), 1 << 22), ("bf16", 32, (5, 8, 5), (1 << 22) + 3)])
+@pytest.mark.parametrize("spread", ["all over", "one network", "none"])
+def test_eval_grouped_on_both_sides_of_the_lines_of_counting(wdtype, H, res, M, spread):
+    """Where samples are moved instead of indices (98,304 points for up to 512 networks, 163,840 for more), where a workgroup's share of the batch
+    changes its form (2^20, 2^21, 2^22), shares that end with one to three points, 5,819 to 6,137 networks, one network with all points."""
+    test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
+
+
 @pytest.mark.parametrize("wdtype,H,res,M", [("f16", 32, (16, 32, 16), 40001), ("bf16", 32, (24, 20, 28), 131073), ("f32", 32, (24, 20, 28), 20001),
                                             ("f16", 32, (32, 32, 32), 30000), ("bf16", 64, (32, 32, 32), 1 << 18), ("f16", 32, (32, 32, 33), 40001)])
 @pytest.mark.parametrize("spread", ["all over", "one network", "none"])
