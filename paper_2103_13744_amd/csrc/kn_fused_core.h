@@ -570,7 +570,6 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
                     c += __popcll(b);
                 }
                 wave_sync();
-                w.arrived();
                 for (int t0 = 0; t0 < c; t0 += KN_WAVE) {
                     const int len = min(KN_WAVE, c - t0);
                     // pre-activations (r, g, b, sigma) of sample ln of the tile

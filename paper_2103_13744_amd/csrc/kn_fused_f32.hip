@@ -23,7 +23,6 @@ template <int H> struct Net32 {
 
     struct Weights : NetF32<H, true> {
         __device__ __forceinline__ void load(const void *packed, int32_t net, int lane) { NetF32<H, true>::load((const float *)packed, net, lane); }
-        __device__ __forceinline__ void arrived() {}
     };
 
     __device__ __forceinline__ explicit Net32(int) {}

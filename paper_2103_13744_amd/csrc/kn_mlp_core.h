@@ -26,11 +26,10 @@ template <int H> struct Lay {
     static constexpr int HT = H / 16, HK = H / 32;
     static constexpr int L1 = 0;                          // (t, kb) -> L1 + 2t + kb
     static constexpr int L2 = L1 + 2 * HT;                // (t, kb) -> L2 + t*HK + kb
-    static constexpr int LS = L2 + HT * HK;               // density row of layer 3, (kb)
-    static constexpr int L4 = LS + HK;                    // (t, kb) -> L4 + t*(HK+1) + kb; kb < HK: h2 through the folded
+    static constexpr int LO = L2 + HT * HK;               // density row of layer 3 and colour rows of layer 5, (kb): one block for both heads
+    static constexpr int L4 = LO + HK;                    // (t, kb) -> L4 + t*(HK+1) + kb; kb < HK: h2 through the folded
                                                           // feature layer, kb = HK: gamma(d)
-    static constexpr int L5 = L4 + HT * (HK + 1);         // colour rows, (kb)
-    static constexpr int NBLK = L5 + HK;
+    static constexpr int NBLK = L4 + HT * (HK + 1);
     static constexpr int TAIL_FLOATS = H + 4;             // b2[H], b5[3], b3 density
     static constexpr int HALFS = NBLK * 512 + TAIL_FLOATS * 2;
     // canonical offsets

@@ -86,23 +86,19 @@ template <int H> __device__ int pack_source(int e)
         const int t = (blk - L::L1) >> 1, kb = (blk - L::L1) & 1, col = 16 * t + m, r = l1_row(kb, g, j);
         return r < 63 ? L::oW1 + r * H + col : L::ob1 + col;
     }
-    if (blk < L::LS) {
+    if (blk < L::LO) {
         const int t = (blk - L::L2) / L::HK, kb = (blk - L::L2) % L::HK;
         return L::oW2 + hid_feat(kb, g, j) * H + 16 * t + m;
     }
     if (blk < L::L4) {
-        const int kb = blk - L::LS;
-        return (m & 3) == 3 ? L::oW3 + hid_feat(kb, g, j) * (H + 1) : -1;
+        const int kb = blk - L::LO; // rows of period four: the colours' and the density's (an accumulator fed with h4 gives the first three, with h2 the last)
+        return (m & 3) == 3 ? L::oW3 + hid_feat(kb, g, j) * (H + 1) : L::oW5 + hid_feat(kb, g, j) * 3 + (m & 3);
     }
-    if (blk < L::L5) {
-        const int t = (blk - L::L4) / (L::HK + 1), kb = (blk - L::L4) % (L::HK + 1), col = 16 * t + m;
-        if (kb < L::HK) return FOLD_ROW - (hid_feat(kb, g, j) * H + col); // column `col` of row hid_feat of W3f W4f
-        const int r = dir_row(g, j);
-        if (r == -2) return -1;
-        return r == -1 ? FOLD_BIAS - col : L::oW4 + (H + r) * H + col;     // b4 + W4f^T b3f
-    }
-    const int kb = blk - L::L5;
-    return (m & 3) < 3 ? L::oW5 + hid_feat(kb, g, j) * 3 + (m & 3) : -1;
+    const int t = (blk - L::L4) / (L::HK + 1), kb = (blk - L::L4) % (L::HK + 1), col = 16 * t + m;
+    if (kb < L::HK) return FOLD_ROW - (hid_feat(kb, g, j) * H + col); // column `col` of row hid_feat of W3f W4f
+    const int r = dir_row(g, j);
+    if (r == -2) return -1;
+    return r == -1 ? FOLD_BIAS - col : L::oW4 + (H + r) * H + col;     // b4 + W4f^T b3f
 }
 
 template <int H> __device__ int tail_source(int q)
@@ -169,7 +165,7 @@ __global__ void k_pack_weights(const uint16_t *__restrict__ w, int64_t P, int32_
 __global__ void k_clear_flag(int32_t *flag) { *flag = 0; }
 
 // ---------------------------------------------------------------------------------------------
-// Weights stay in registers: 12 blocks (48 VGPRs) for H = 32, four wavefronts per SIMD; 32 blocks (128 VGPRs) for
+// Weights stay in registers: 11 blocks (44 VGPRs) for H = 32, four wavefronts per SIMD; 30 blocks (120 VGPRs) for
 // H = 64, two wavefronts per SIMD (the matrix-core operands are read straight from the register file either way).
 // STRAT (render with stratified sampling): the lattice points sit at their drawn offsets and the density is
 // scaled by delta_k / step on the way out (see KnSampleSrc).
@@ -237,7 +233,7 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int kb = 0; kb < HK; ++kb) a_out[u][kb] = mrow == u ? (areg[L::LS + kb] | areg[L::L5 + kb]) : zero_u4;
+            for (int kb = 0; kb < HK; ++kb) a_out[u][kb] = mrow == u ? areg[L::LO + kb] : zero_u4;
         const float *__restrict__ tail = (const float *)(wp + NBLK * KN_WAVE);
 #pragma unroll
         for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
@@ -529,7 +525,7 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
 #pragma unroll
     for (int b = 0; b < HT * HK; ++b) a2[b] = wp[(L::L2 + b) * KN_WAVE + lane];
 #pragma unroll
-    for (int kb = 0; kb < HK; ++kb) a_sig[kb] = wp[(L::LS + kb) * KN_WAVE + lane]; // (row 3 of every four: all lane groups get the density)
+    for (int kb = 0; kb < HK; ++kb) a_sig[kb] = wp[(L::LO + kb) * KN_WAVE + lane]; // (row 3 of every four: all lane groups get the density)
     const float *__restrict__ tail = (const float *)(wp + L::NBLK * KN_WAVE);
 #pragma unroll
     for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
@@ -725,7 +721,6 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE)
     constexpr int NT = (LAYER == 3 || LAYER == 5) ? 0 : HT;          // output tiles of the layer proper
     constexpr int W0 = LAYER == 1 ? L::L1 : (LAYER == 2 ? L::L2 : L::L4);
     constexpr bool HEAD = LAYER == 3 || LAYER == 5;                  // a density / colour head
-    constexpr int WH = LAYER == 3 ? L::LS : L::L5;
     const uint16_t *__restrict__ in = LAYER == 1 ? buf.x0 : ((LAYER == 2 || LAYER == 5) ? buf.ha : buf.hb);
     uint16_t *__restrict__ out = (LAYER == 1 || LAYER == 4) ? buf.ha : buf.hb;
     constexpr int IN_COLS = LAYER == 1 ? 64 : H;
@@ -748,7 +743,7 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE)
         for (int b = 0; b < NT * NB; ++b) aw[b] = wp[(W0 + b) * KN_WAVE + lane];
         if constexpr (HEAD) {
 #pragma unroll
-            for (int kb = 0; kb < HK; ++kb) ah[kb] = wp[(WH + kb) * KN_WAVE + lane];
+            for (int kb = 0; kb < HK; ++kb) ah[kb] = wp[(L::LO + kb) * KN_WAVE + lane];
         }
         const float *__restrict__ tail = (const float *)(wp + L::NBLK * KN_WAVE);
 #pragma unroll
