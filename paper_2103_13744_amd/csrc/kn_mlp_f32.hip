@@ -160,7 +160,7 @@ __global__ void __launch_bounds__((PACK_WAVES<H> + FOLD) * KN_WAVE)
     __shared__ float s_w3[FOLD ? H * (H + 1) : 1], s_w4[FOLD ? H * H : 1], s_h[H], s_moved[H];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / KN_WAVE), lane = threadIdx.x & (KN_WAVE - 1);
     const float *__restrict__ src = w + blockIdx.x * P;
-    float *__restrict__ image = packed + (int64_t)blockIdx.x * (R::N * KN_WAVE);
+    float *__restrict__ image = packed + (int64_t)blockIdx.x * R::IMAGE;
     if constexpr (FOLD) {
         constexpr int T = (WAVES + 1) * KN_WAVE, STEPS = (H * (H + 1) + T - 1) / T;
         float v[2][STEPS]; // (all loads in flight together)
@@ -417,7 +417,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
     const int32_t all = cuts[0] * cuts[1] * cuts[2];
     if (part >= all) return;
 
-    const float *__restrict__ image = packed + (int64_t)net * (R::N * KN_WAVE);
+    const float *__restrict__ image = packed + (int64_t)net * R::IMAGE;
     for (int32_t s = part; s < all; s += job.parts) {
         const int32_t sq = s / cuts[2], at[3] = {sq / cuts[1], sq % cuts[1], s % cuts[2]};
         int32_t lo[3], num[3]; // first probe (counted like box.p0) and probes of the part
@@ -538,13 +538,11 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
 
 int kn_mlp_f32_tile_len(const kn_scene *) { return F32_TILE_LEN; }
 
-static int64_t image_bytes(int32_t H, int64_t N) { return (int64_t)(H == 32 ? Regs<32>::N : Regs<64>::N) * KN_WAVE * 4 * N; }
-
 // bytes of the packed weights of N networks of width H (0: no kernel for that width)
 int64_t kn_mlp_f32_packed_bytes(int32_t H, int64_t N)
 {
     if (H != 32 && H != 64) return 0;
-    return (int64_t)(H == 32 ? Regs<32>::N : Regs<64>::N) * KN_WAVE * 4 * N;
+    return (int64_t)(H == 32 ? Regs<32>::IMAGE : Regs<64>::IMAGE) * 4 * N;
 }
 
 // fills sc->packed_w (kn_mlp_f32_packed_bytes bytes, assigned by the caller) and sets sc->f32_apart; waits for the stream

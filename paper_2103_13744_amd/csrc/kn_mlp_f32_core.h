@@ -17,13 +17,38 @@ __device__ __forceinline__ void double_angle(float s, float c, float &s2, float 
     c2 = fmaf(-2.0f * s, s, 1.0f);
 }
 
-// Register file image of one network: register r of lane l sits at packed[net * N * 64 + image_at(r, l)].  Width 32: four registers of a
+template <int H> struct Regs {
+    static constexpr int HT = H / 16, HQ = H / 4;
+    static constexpr int W1 = 0;                     // (t, q)  -> W1 + 16 t + q
+    static constexpr int W2 = W1 + 16 * HT;          // (t, k)  -> W2 + HQ t + k
+    static constexpr int W4 = W2 + HQ * HT;          // (t, k)  -> W4 + (HQ + 8) t + k; k < HQ: folded with the feature layer; k >= HQ: gamma(d)
+    static constexpr int WO = W4 + (HQ + 8) * HT;    // (c, k)  -> WO + HQ c + k: colour c (c < 3) / density, hidden unit k of the lane group
+    static constexpr int B2 = WO + 4 * HQ;           // (t, j): accumulator initial values of this lane
+    static constexpr int BO = B2 + 4 * HT;
+    static constexpr int W3 = BO + 4;                // (t, k)  -> W3 + HQ t + k: feature rows, (t, j) -> B3 + 4 t + j: their biases;
+    static constexpr int B3 = W3 + HQ * HT;          // both only where the feature layer is kept apart
+    static constexpr int N = B3 + 4 * HT;
+    // Registers WO .. W3 - 1 are the same in the sixteen lanes of a lane group: the image holds them once per group, behind the others.
+    static constexpr int GROUPED = W3 - WO, LANED = N - GROUPED, GROUPED_AT = LANED * KN_WAVE;
+    static constexpr int IMAGE = GROUPED_AT + ((4 * GROUPED + 31) & ~31); // floats (lines of 128 bytes)
+    static_assert(((W2 | W4 | WO | B2 | BO | W3 | B3 | N | HQ) & 3) == 0, "registers are fetched in fours");
+    // canonical offsets (Sec. 3.2: five layers, weights before biases)
+    static constexpr int oW1 = 0, ob1 = 63 * H, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H, ob3 = oW3 + H * (H + 1),
+                         oW4 = ob3 + H + 1, ob4 = oW4 + (H + 27) * H, oW5 = ob4 + H, ob5 = oW5 + 3 * H;
+};
+
+// Register file image of one network: register r of lane l sits at packed[net * IMAGE + image_at(r, l)].  Width 32: four registers of a
 // lane side by side, so that a wavefront fetches them with one 16-byte load per lane (31 loads instead of 124, more than the 63 that can
 // be in flight): 300 points 18.2 -> 16 us, 5,000 33 -> 30, 65,537 34 -> 32.5, 4 M 530 -> 520.  Width 64, where weights live in both halves of the
 // register file and a load fills either, one by one: in fours 5,000 points 56 -> 59 us, 4 M the same.
+// GROUPED registers by lane, half as much again to be fetched / so: 5,003 points on 16^3 networks 29.5 -> 23.1 us, 65,537 32.8 -> 30.6, 100,003 41.5 -> 37.9; width 64 (a
+// third) 52.1 -> 47.9, 100,003 89.8 -> 79.9, 1 M 342 -> 337; 64x64 rays 28.4 -> 27.8, 400x300 sparse, width 64, 325 -> 316.
 template <int H> __host__ __device__ __forceinline__ constexpr int image_at(int r, int lane)
 {
-    return H == 32 ? ((r >> 2) * KN_WAVE + lane) * 4 + (r & 3) : r * KN_WAVE + lane;
+    using R = Regs<H>;
+    const bool grouped = r >= R::WO && r < R::W3;
+    const int at = grouped ? r - R::WO : (r < R::WO ? r : r - R::GROUPED), stride = grouped ? 4 : KN_WAVE, l = grouped ? lane >> 4 : lane;
+    return (grouped ? R::GROUPED_AT : 0) + (H == 32 ? ((at >> 2) * stride + l) * 4 + (at & 3) : at * stride + l);
 }
 // registers first .. first + n - 1 (multiples of four) of an image
 template <int H> __device__ __forceinline__ void fetch_registers(const float *__restrict__ image, int lane, int first, float *to, int n)
@@ -46,23 +71,6 @@ template <int H> __device__ __forceinline__ f4 fetch_registers(const float *__re
     fetch_registers<H>(image, lane, first, v, 4);
     return (f4){v[0], v[1], v[2], v[3]};
 }
-template <int H> struct Regs {
-    static constexpr int HT = H / 16, HQ = H / 4;
-    static constexpr int W1 = 0;                     // (t, q)  -> W1 + 16 t + q
-    static constexpr int W2 = W1 + 16 * HT;          // (t, k)  -> W2 + HQ t + k
-    static constexpr int W4 = W2 + HQ * HT;          // (t, k)  -> W4 + (HQ + 8) t + k; k < HQ: folded with the feature layer; k >= HQ: gamma(d)
-    static constexpr int WO = W4 + (HQ + 8) * HT;    // (c, k)  -> WO + HQ c + k: colour c (c < 3) / density, hidden unit k of the lane group
-    static constexpr int B2 = WO + 4 * HQ;           // (t, j): accumulator initial values of this lane
-    static constexpr int BO = B2 + 4 * HT;
-    static constexpr int W3 = BO + 4;                // (t, k)  -> W3 + HQ t + k: feature rows, (t, j) -> B3 + 4 t + j: their biases;
-    static constexpr int B3 = W3 + HQ * HT;          // both only where the feature layer is kept apart
-    static constexpr int N = B3 + 4 * HT;
-    static_assert(((W2 | W4 | WO | B2 | BO | W3 | B3 | N | HQ) & 3) == 0, "registers are fetched in fours");
-    // canonical offsets (Sec. 3.2: five layers, weights before biases)
-    static constexpr int oW1 = 0, ob1 = 63 * H, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H, ob3 = oW3 + H * (H + 1),
-                         oW4 = ob3 + H + 1, ob4 = oW4 + (H + 27) * H, oW5 = ob4 + H, ob5 = oW5 + 3 * H;
-};
-
 // one network's weights in registers
 template <int H, bool FOLD> struct NetF32 {
     using R = Regs<H>;
@@ -72,7 +80,7 @@ template <int H, bool FOLD> struct NetF32 {
     f4 bias2[HT], bias3[FOLD ? 1 : HT], bias_out;
     __device__ __forceinline__ void load(const float *__restrict__ packed, int32_t net, int lane)
     {
-        const float *__restrict__ image = packed + (int64_t)net * (R::N * KN_WAVE);
+        const float *__restrict__ image = packed + (int64_t)net * R::IMAGE;
 #pragma unroll
         for (int t = 0; t < HT; ++t) {
             fetch_registers<H>(image, lane, R::W1 + 16 * t, w1[t], 16);
