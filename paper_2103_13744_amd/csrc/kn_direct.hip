@@ -6,7 +6,7 @@
 // up is that the points of one network meet in full tiles and share one fetch of the weights, so it is for batches whose
 // weights, fetched once per wavefront and network, are still little traffic (see kn_direct_lg_points).
 //
-// What bounds it: the latency of a pass over one network (weights 11.4 / 31 KB per wavefront from the caches, then five
+// What bounds it: the latency of a pass over one network (weights 11.4 / 29 KB per wavefront from the caches, then five
 // dependent layers), P times in a row at worst; so P is as small as leaves every resident wavefront one share.
 // Measured, 1,000 points on 16^3 networks, width 32, fp16: 45 us -> 15 (the host's share of a call); fp32: 56 -> 15.
 #include "kn_direct.h"
@@ -32,15 +32,17 @@ __global__ void __launch_bounds__(DIRECT_WAVES *KN_WAVE) __attribute__((amdgpu_w
     unsigned long long pending = kn_direct_point(job, first, lane, pt);
     while (pending != 0ull) {
         const int32_t sel = __builtin_amdgcn_readlane(pt.net, (int)__builtin_ctzll(pending));
-        u4 areg[NBLK];
+        u4 areg[NBLK], heads[HK];
         f4 bias2[HT], bias_out;
         const u4 *__restrict__ wp = (const u4 *)(packed + (int64_t)sel * L::HALFS);
-        const float *__restrict__ tail = (const float *)(wp + NBLK * KN_WAVE);
+        const float *__restrict__ tail = (const float *)(wp + L::TAIL);
 #pragma unroll
         for (int b = 0; b < L::L2; ++b) areg[b] = wp[b * KN_WAVE + lane]; // (in the order of their use)
 #pragma unroll
         for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
         bias_out = *(const f4 *)(tail + H);
+#pragma unroll
+        for (int kb = 0; kb < HK; ++kb) heads[kb] = wp[L::heads_at(kb, lane)];
 #pragma unroll
         for (int b = L::L2; b < NBLK; ++b) areg[b] = wp[b * KN_WAVE + lane];
         const bool hit = pt.net == sel;
@@ -55,7 +57,7 @@ __global__ void __launch_bounds__(DIRECT_WAVES *KN_WAVE) __attribute__((amdgpu_w
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // (density row and colour rows, LO, are repeated with period four: every lane group computes the four values of a sample, and
+        // (density row and colour rows are repeated with period four: every lane group computes the four values of a sample, and
         // group u keeps those of sample tile u)
         f4 out = zero4;
         for (int u = 0; 16 * u < c; ++u) {
@@ -85,7 +87,7 @@ __global__ void __launch_bounds__(DIRECT_WAVES *KN_WAVE) __attribute__((amdgpu_w
             }
             pack_acts<H, BF, true>(acc, Bh);
 #pragma unroll
-            for (int kb = 0; kb < HK; ++kb) o_sig = mfma<BF>(areg[L::LO + kb], Bh[kb], o_sig);
+            for (int kb = 0; kb < HK; ++kb) o_sig = mfma<BF>(heads[kb], Bh[kb], o_sig);
 #pragma unroll
             for (int t = 0; t < HT; ++t) {
                 acc[t] = mfma<BF>(areg[L::L4 + t * (HK + 1) + HK], Bd, zero4);
@@ -94,7 +96,7 @@ __global__ void __launch_bounds__(DIRECT_WAVES *KN_WAVE) __attribute__((amdgpu_w
             }
             pack_acts<H, BF, true>(acc, Bh);
 #pragma unroll
-            for (int kb = 0; kb < HK; ++kb) o_col = mfma<BF>(areg[L::LO + kb], Bh[kb], o_col);
+            for (int kb = 0; kb < HK; ++kb) o_col = mfma<BF>(heads[kb], Bh[kb], o_col);
             out = g == u ? (f4){o_col[0], o_col[1], o_col[2], o_sig[3]} : out;
         }
         if (lane < c) {
@@ -119,7 +121,7 @@ __global__ void __launch_bounds__(DIRECT_WAVES *KN_WAVE) __attribute__((amdgpu_w
 // (not) 48 / 26 (20 / 20); 10x16x10, bf16, width 64, 6,000 28 / 23 (19 / 21), 9,000 (not) 47 / 23 (33 / 22), fp32 6,000 (not) 31 / 22; 24x20x28, fp16,
 // 24,000 43 / 49 (30 / 33), 34,000 (not) 69 / 53 (48 / 36), fp32 9,000 57 / 59; 32^3, fp16, 28,000 52 / 83 (46 / 57), 40,000 (not) 75 / 91 (67 / 59),
 // bf16, width 64, 16,000 77 / 122, fp32 16,000 77 / 119.  (16-bit images were a twelfth and a sixteenth larger then; smaller, with the heads in one block: 5,003 points
-// direct 10.8 -> 9.6, width 64 25.9 -> 24.3, 20,011 34.6 -> 31.2.)
+// direct 10.8 -> 9.6, width 64 25.9 -> 23.3, 20,011 34.6 -> 31.2; fp32 29.5 -> 23.1.)
 int kn_direct_lg_points(const kn_scene *sc, int64_t M)
 {
     const int H = sc->desc.hidden;
@@ -130,7 +132,7 @@ int kn_direct_lg_points(const kn_scene *sc, int64_t M)
     const double all = (double)(f32 ? kn_mlp_f32_packed_bytes(H, sc->N) : kn_mlp_packed_bytes(H, sc->N));
     const double shares = (double)kn_div_up(M, 1ll << lg), networks = (double)(sc->N < (1 << lg) ? sc->N : 1 << lg);
     const double fetches = fmin((double)M, shares * networks);
-    const double us = fetches * (all / sc->N) / ((all <= 3e6 ? 18e6 : 8e6) * (f32 ? (H == 32 ? 0.723 : 0.798) : 0.925)); // (what fetches wait for is not their bytes alone: images that got smaller)
+    const double us = fetches * (all / sc->N) / ((all <= 3e6 ? 18e6 : 8e6) * (f32 ? (H == 32 ? 0.723 : 0.798) : (H == 32 ? 0.918 : 0.895))); // (what fetches wait for is not their bytes alone: images that got smaller)
     const bool heavy = f32 || H == 64;
     const double limit = sc->N <= 255 ? 24.0 : sc->N <= 8191 ? (heavy ? 26.0 : 40.0) : sc->N <= 16383 ? 45.0 : (heavy ? 80.0 : 50.0);
     return us <= limit ? lg : -1;

@@ -38,12 +38,12 @@ template <int H, bool BF, bool WRAP> struct Net16 {
     }
 
     struct Weights {
-        u4 areg[NBLK];
+        u4 areg[NBLK], heads[HK];
         f4 bias2[HT], bias_out;
         __device__ __forceinline__ void load(const void *packed, int32_t net, int lane)
         {
             const u4 *__restrict__ wp = (const u4 *)((const uint16_t *)packed + (int64_t)net * L::HALFS);
-            const float *__restrict__ tail = (const float *)(wp + NBLK * KN_WAVE);
+            const float *__restrict__ tail = (const float *)(wp + L::TAIL);
             // in the order of their use, nothing to be done to them in front of the first layer: that runs while the others' are under way (with the heads
             // in blocks of their own, joined here, 800x800 144.9 -> 143.5 us, sparse 145.5 -> 137.1, 1080p, width 64, 990 -> 970)
 #pragma unroll
@@ -51,6 +51,8 @@ template <int H, bool BF, bool WRAP> struct Net16 {
 #pragma unroll
             for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * (lane >> 4));
             bias_out = *(const f4 *)(tail + H);
+#pragma unroll
+            for (int kb = 0; kb < HK; ++kb) heads[kb] = wp[L::heads_at(kb, lane)];
 #pragma unroll
             for (int b = L::L2; b < NBLK; ++b) areg[b] = wp[b * KN_WAVE + lane];
         }
@@ -103,7 +105,7 @@ template <int H, bool BF, bool WRAP> struct Net16 {
             }
             pack_acts<H, BF, true>(acc, Bh);
 #pragma unroll
-            for (int kb = 0; kb < HK; ++kb) o_sig = mfma<BF>(w.areg[L::LO + kb], Bh[kb], o_sig);
+            for (int kb = 0; kb < HK; ++kb) o_sig = mfma<BF>(w.heads[kb], Bh[kb], o_sig);
 #pragma unroll
             for (int t = 0; t < HT; ++t) {
                 acc[t] = mfma<BF>(w.areg[L::L4 + t * (HK + 1) + HK], Bd, zero4);
@@ -112,7 +114,7 @@ template <int H, bool BF, bool WRAP> struct Net16 {
             }
             pack_acts<H, BF, true>(acc, Bh);
 #pragma unroll
-            for (int kb = 0; kb < HK; ++kb) o_col = mfma<BF>(w.areg[L::LO + kb], Bh[kb], o_col);
+            for (int kb = 0; kb < HK; ++kb) o_col = mfma<BF>(w.heads[kb], Bh[kb], o_col);
             out = g == u ? (f4){o_col[0], o_col[1], o_col[2], o_sig[3]} : out;
         };
         // (two sample tiles side by side wherever two are there; uniform branches)

@@ -26,12 +26,19 @@ template <int H> struct Lay {
     static constexpr int HT = H / 16, HK = H / 32;
     static constexpr int L1 = 0;                          // (t, kb) -> L1 + 2t + kb
     static constexpr int L2 = L1 + 2 * HT;                // (t, kb) -> L2 + t*HK + kb
-    static constexpr int LO = L2 + HT * HK;               // density row of layer 3 and colour rows of layer 5, (kb): one block for both heads
-    static constexpr int L4 = LO + HK;                    // (t, kb) -> L4 + t*(HK+1) + kb; kb < HK: h2 through the folded
+    static constexpr int L4 = L2 + HT * HK;                   // (t, kb) -> L4 + t*(HK+1) + kb; kb < HK: h2 through the folded
                                                           // feature layer, kb = HK: gamma(d)
     static constexpr int NBLK = L4 + HT * (HK + 1);
+    // Behind the blocks, density row of layer 3 and colour rows of layer 5: one block (kb) for both heads, whose rows have period four.  Width 64: stored
+    // for four rows, 256 bytes instead of 1,024, and images start on lines (a block is eight of them then, not parts of nine): 160x120 sparse 69.8 -> 66.6 us,
+    // 1080p 978 -> 966, 5,003 points 24.3 -> 23.3.  Width 32, by row: 20,011 points 31.2 -> 29.5, but 800x800 143.5 -> 145.5, 400x300 76.5 -> 79 (three
+    // more spilled registers in the fused render); on lines 31.2 -> 32.0.
+    static constexpr int HEADS = H == 32 ? 64 : 16;       // in 16 bytes
+    static constexpr int LO = NBLK * 64;
+    static constexpr int TAIL = LO + HEADS * HK;
     static constexpr int TAIL_FLOATS = H + 4;             // b2[H], b5[3], b3 density
-    static constexpr int HALFS = NBLK * 512 + TAIL_FLOATS * 2;
+    static constexpr int HALFS = H == 32 ? TAIL * 8 + TAIL_FLOATS * 2 : (TAIL * 8 + TAIL_FLOATS * 2 + 63) & ~63;
+    __device__ static constexpr int heads_at(int kb, int lane) { return LO + HEADS * kb + (H == 32 ? lane : 4 * (lane >> 4) + (lane & 3)); }
     // canonical offsets
     static constexpr int oW1 = 0, ob1 = 63 * H, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H,
                          ob3 = oW3 + H * (H + 1), oW4 = ob3 + H + 1, ob4 = oW4 + (H + 27) * H, oW5 = ob4 + H,

@@ -86,13 +86,13 @@ template <int H> __device__ int pack_source(int e)
         const int t = (blk - L::L1) >> 1, kb = (blk - L::L1) & 1, col = 16 * t + m, r = l1_row(kb, g, j);
         return r < 63 ? L::oW1 + r * H + col : L::ob1 + col;
     }
-    if (blk < L::LO) {
-        const int t = (blk - L::L2) / L::HK, kb = (blk - L::L2) % L::HK;
-        return L::oW2 + hid_feat(kb, g, j) * H + 16 * t + m;
+    if (e >= L::LO * 8) { // rows of period four: the colours' and the density's (an accumulator fed with h4 gives the first three, with h2 the last)
+        const int q = (e >> 3) - L::LO, kb = q / L::HEADS, hg = H == 32 ? g : (q >> 2) & 3, hm = q & 3;
+        return hm == 3 ? L::oW3 + hid_feat(kb, hg, j) * (H + 1) : L::oW5 + hid_feat(kb, hg, j) * 3 + hm;
     }
     if (blk < L::L4) {
-        const int kb = blk - L::LO; // rows of period four: the colours' and the density's (an accumulator fed with h4 gives the first three, with h2 the last)
-        return (m & 3) == 3 ? L::oW3 + hid_feat(kb, g, j) * (H + 1) : L::oW5 + hid_feat(kb, g, j) * 3 + (m & 3);
+        const int t = (blk - L::L2) / L::HK, kb = (blk - L::L2) % L::HK;
+        return L::oW2 + hid_feat(kb, g, j) * H + 16 * t + m;
     }
     const int t = (blk - L::L4) / (L::HK + 1), kb = (blk - L::L4) % (L::HK + 1), col = 16 * t + m;
     if (kb < L::HK) return FOLD_ROW - (hid_feat(kb, g, j) * H + col); // column `col` of row hid_feat of W3f W4f
@@ -126,19 +126,20 @@ __device__ __forceinline__ uint16_t float_to_half_bits(float v, bool bf)
 
 // `overflow`: set when a folded element leaves the range of the 16-bit type although its factors are finite
 constexpr int PACK_THREADS = 256;
+template <int H> __host__ __device__ constexpr int64_t pack_elements() { return Lay<H>::TAIL * 8 + Lay<H>::TAIL_FLOATS; } // a thread each
 template <int H>
 __global__ void k_pack_weights(const uint16_t *__restrict__ w, int64_t P, int32_t N, bool bf, uint16_t *__restrict__ packed,
                                int32_t *__restrict__ overflow)
 {
     using L = Lay<H>;
     const int64_t i = (int64_t)kn_block() * PACK_THREADS + kn_thread();
-    const int64_t per = L::NBLK * 512 + L::TAIL_FLOATS;
+    const int64_t per = pack_elements<H>();
     if (i >= per * N) return;
     const int64_t net = i / per;
     const int e = (int)(i - net * per);
     const uint16_t *src = w + net * P;
     uint16_t *dst = packed + net * (int64_t)L::HALFS;
-    if (e < L::NBLK * 512) {
+    if (e < L::TAIL * 8) {
         const int s = pack_source<H>(e);
         if (s >= -1) {
             dst[e] = s < 0 ? (uint16_t)0 : src[s];
@@ -157,15 +158,15 @@ __global__ void k_pack_weights(const uint16_t *__restrict__ w, int64_t P, int32_
             dst[e] = r;
         }
     } else {
-        const int q = e - L::NBLK * 512;
+        const int q = e - L::TAIL * 8;
         const float v = half_bits_to_float(src[tail_source<H>(q)], bf);
-        ((float *)(dst + L::NBLK * 512))[q] = v;
+        ((float *)(dst + L::TAIL * 8))[q] = v;
     }
 }
 __global__ void k_clear_flag(int32_t *flag) { *flag = 0; }
 
 // ---------------------------------------------------------------------------------------------
-// Weights stay in registers: 11 blocks (44 VGPRs) for H = 32, four wavefronts per SIMD; 30 blocks (120 VGPRs) for
+// Weights stay in registers: 10 blocks (40 VGPRs) and the heads' for H = 32, four wavefronts per SIMD; 28 blocks (112 VGPRs) and the heads' two for
 // H = 64, two wavefronts per SIMD (the matrix-core operands are read straight from the register file either way).
 // STRAT (render with stratified sampling): the lattice points sit at their drawn offsets and the density is
 // scaled by delta_k / step on the way out (see KnSampleSrc).
@@ -230,11 +231,14 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
         const u4 *__restrict__ wp = (const u4 *)(packed + (int64_t)net * L::HALFS);
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) areg[b] = wp[b * KN_WAVE + lane];
+        u4 heads[HK];
+#pragma unroll
+        for (int kb = 0; kb < HK; ++kb) heads[kb] = wp[L::heads_at(kb, lane)];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int kb = 0; kb < HK; ++kb) a_out[u][kb] = mrow == u ? areg[L::LO + kb] : zero_u4;
-        const float *__restrict__ tail = (const float *)(wp + NBLK * KN_WAVE);
+            for (int kb = 0; kb < HK; ++kb) a_out[u][kb] = mrow == u ? heads[kb] : zero_u4;
+        const float *__restrict__ tail = (const float *)(wp + L::TAIL);
 #pragma unroll
         for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
         bias_out = *(const f4 *)(tail + H);
@@ -525,8 +529,8 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
 #pragma unroll
     for (int b = 0; b < HT * HK; ++b) a2[b] = wp[(L::L2 + b) * KN_WAVE + lane];
 #pragma unroll
-    for (int kb = 0; kb < HK; ++kb) a_sig[kb] = wp[(L::LO + kb) * KN_WAVE + lane]; // (row 3 of every four: all lane groups get the density)
-    const float *__restrict__ tail = (const float *)(wp + L::NBLK * KN_WAVE);
+    for (int kb = 0; kb < HK; ++kb) a_sig[kb] = wp[L::heads_at(kb, lane)]; // (row 3 of every four: all lane groups get the density)
+    const float *__restrict__ tail = (const float *)(wp + L::TAIL);
 #pragma unroll
     for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);
     f4 bias_sig = {0.0f, 0.0f, 0.0f, tail[H + 3]};
@@ -743,9 +747,9 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE)
         for (int b = 0; b < NT * NB; ++b) aw[b] = wp[(W0 + b) * KN_WAVE + lane];
         if constexpr (HEAD) {
 #pragma unroll
-            for (int kb = 0; kb < HK; ++kb) ah[kb] = wp[(L::LO + kb) * KN_WAVE + lane];
+            for (int kb = 0; kb < HK; ++kb) ah[kb] = wp[L::heads_at(kb, lane)];
         }
-        const float *__restrict__ tail = (const float *)(wp + L::NBLK * KN_WAVE);
+        const float *__restrict__ tail = (const float *)(wp + L::TAIL);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             if constexpr (LAYER == 2) bias[t] = *(const f4 *)(tail + 16 * t + 4 * g);
@@ -870,7 +874,7 @@ int kn_mlp_pack_weights(kn_scene *sc, hipStream_t st)
     const bool bf = sc->desc.wdtype == KN_BF16;
     if (!sc->packed_w || (H != 32 && H != 64)) return KN_E_INVALID_ARG;
     const int64_t halfs = H == 32 ? Lay<32>::HALFS : Lay<64>::HALFS;
-    const int64_t per = H == 32 ? Lay<32>::NBLK * 512 + Lay<32>::TAIL_FLOATS : Lay<64>::NBLK * 512 + Lay<64>::TAIL_FLOATS;
+    const int64_t per = H == 32 ? pack_elements<32>() : pack_elements<64>();
     sc->packed_halfs_per_net = halfs;
     const int64_t total = per * sc->N;
     const int64_t blocks = kn_div_up(total, PACK_THREADS);
