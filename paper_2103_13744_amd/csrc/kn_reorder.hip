@@ -786,12 +786,15 @@ __global__ void __launch_bounds__(CO_T)
     constexpr int KEPT = (COUNT_MAX_N + T) / T;
     int32_t total[KEPT], in_front[KEPT], here[KEPT]; // all requested together
     const int32_t *const row = table + b * table_stride(bins);
+    // (wavefronts without a network of their own do not wait for any, and so not for the points in front of them: 5 M points on 2^3 networks, the call, 208.3 -> 205.5 us)
+    if (d0 < d1) {
 #pragma unroll
-    for (int j = 0; j < KEPT; ++j)
-        if (j < per) total[j] = totals[min(d0 + j, N)];
+        for (int j = 0; j < KEPT; ++j)
+            if (j < per) total[j] = totals[min(d0 + j, N)];
 #pragma unroll
-    for (int j = 0; j < KEPT; ++j)
-        if (j < per) in_front[j] = row[min(d0 + j, N)];
+        for (int j = 0; j < KEPT; ++j)
+            if (j < per) in_front[j] = row[min(d0 + j, N)];
+    }
     __syncthreads();
     int32_t lpos[ROWS];
 #pragma unroll
@@ -799,16 +802,18 @@ __global__ void __launch_bounds__(CO_T)
     __syncthreads();
     // sums in front of a thread's networks of the workgroup's samples, of all samples and of tiles
     int32_t own[3] = {0, 0, 0}, run[3];
+    if (d0 < d1) {
 #pragma unroll
-    for (int j = 0; j < KEPT; ++j)
-        if (j < per) here[j] = cnt[min(d0 + j, N)];
+        for (int j = 0; j < KEPT; ++j)
+            if (j < per) here[j] = cnt[min(d0 + j, N)];
 #pragma unroll
-    for (int j = 0; j < KEPT; ++j) {
-        if (j >= per) break; // (uniform)
-        if (d0 + j >= d1) here[j] = total[j] = 0; // (another thread's, or none)
-        own[0] += here[j];
-        own[1] += total[j];
-        own[2] += d0 + j < N ? tiles_of(total[j], tile_len) : 0;
+        for (int j = 0; j < KEPT; ++j) {
+            if (j >= per) break; // (uniform)
+            if (d0 + j >= d1) here[j] = total[j] = 0; // (another thread's, or none)
+            own[0] += here[j];
+            own[1] += total[j];
+            own[2] += d0 + j < N ? tiles_of(total[j], tile_len) : 0;
+        }
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -825,23 +830,25 @@ __global__ void __launch_bounds__(CO_T)
     }
     if (b == 0 && tid == 0) *n_tiles = tiles_all;
     int32_t turn = d0 % nblk; // (network d's tiles are written by workgroup d % nblk)
+    if (d0 < d1) {
 #pragma unroll
-    for (int j = 0; j < KEPT; ++j) {
-        if (j >= per) break;
-        const int32_t d = d0 + j, n_t = d < N ? tiles_of(total[j], tile_len) : 0;
-        if (d < d1) {
-            delta[d] = run[1] + in_front[j] - run[0];
-            cnt[d] = run[0];
-            if (user_counts && b == 0) user_counts[d] = total[j];
+        for (int j = 0; j < KEPT; ++j) {
+            if (j >= per) break;
+            const int32_t d = d0 + j, n_t = d < N ? tiles_of(total[j], tile_len) : 0;
+            if (d < d1) {
+                delta[d] = run[1] + in_front[j] - run[0];
+                cnt[d] = run[0];
+                if (user_counts && b == 0) user_counts[d] = total[j];
+            }
+            if (n_t > 0 && turn == b) {
+                s_list[atomicAdd(&s_listed, 1)] = make_int4(d, total[j], run[1], run[2]);
+                if (n_t > LIST_LONG) s_long = 1;
+            }
+            if (++turn == nblk) turn = 0;
+            run[0] += here[j];
+            run[1] += total[j];
+            run[2] += n_t;
         }
-        if (n_t > 0 && turn == b) {
-            s_list[atomicAdd(&s_listed, 1)] = make_int4(d, total[j], run[1], run[2]);
-            if (n_t > LIST_LONG) s_long = 1;
-        }
-        if (++turn == nblk) turn = 0;
-        run[0] += here[j];
-        run[1] += total[j];
-        run[2] += n_t;
     }
     __syncthreads();
 #pragma unroll
