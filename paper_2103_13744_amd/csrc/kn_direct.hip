@@ -132,7 +132,7 @@ int kn_direct_lg_points(const kn_scene *sc, int64_t M)
     const double all = (double)(f32 ? kn_mlp_f32_packed_bytes(H, sc->N) : kn_mlp_packed_bytes(H, sc->N));
     const double shares = (double)kn_div_up(M, 1ll << lg), networks = (double)(sc->N < (1 << lg) ? sc->N : 1 << lg);
     const double fetches = fmin((double)M, shares * networks);
-    const double us = fetches * (all / sc->N) / ((all <= 3e6 ? 18e6 : 8e6) * (f32 ? (H == 32 ? 0.723 : 0.798) : (H == 32 ? 0.918 : 0.895))); // (what fetches wait for is not their bytes alone: images that got smaller)
+    const double us = fetches * (all / sc->N) / ((all <= 3e6 ? 18e6 : 8e6) * (f32 ? (H == 32 ? 0.723 : 0.798) : (H == 32 ? 1.0 : 0.895))); // (what fetches wait for is not their bytes alone: images that got smaller)
     const bool heavy = f32 || H == 64;
     const double limit = sc->N <= 255 ? 24.0 : sc->N <= 8191 ? (heavy ? 26.0 : 40.0) : sc->N <= 16383 ? 45.0 : (heavy ? 80.0 : 50.0);
     return us <= limit ? lg : -1;
