@@ -863,7 +863,7 @@ __global__ void __launch_bounds__(256) k_probe_setup(KnGrid occ, KnGrid net, int
             if (cell >= (float)c) hi = mid;
             else lo = mid + 1;
         }
-        first[c] = (int32_t)(lo - kn_probe_base(occ.res[a], net.res[a], c));
+        first[c] = (int32_t)(lo - kn_probe_base(occ.res[a] / net.res[a], c));
     }
 }
 
@@ -912,6 +912,7 @@ extern "C" int kn_extract_occupancy(kn_ctx *ctx, const kn_scene *sc, void *strea
     for (int a = 0; a < 3; ++a) {
         job.first[a] = first[a] = ws.carve<int32_t>(sc->desc.res[a] + 1);
         job.net_res[a] = sc->desc.res[a];
+        job.per[a] = occ_res[a] / sc->desc.res[a];
     }
     if (!ws.ok()) return KN_E_WORKSPACE;
     job.cell_net = sc->cell_net;

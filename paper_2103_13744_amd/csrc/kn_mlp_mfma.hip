@@ -529,8 +529,13 @@ __global__ void __launch_bounds__(WAVES *KN_WAVE) __attribute__((amdgpu_waves_pe
 #pragma unroll
     for (int b = 0; b < HT * HK; ++b) a2[b] = wp[(L::L2 + b) * KN_WAVE + lane];
 #pragma unroll
-    for (int kb = 0; kb < HK; ++kb) // row 3 of every four: all lane groups get the density (the colours' rows zero: less power, 256^3 voxels 1,709 -> 1,687 us)
-        a_sig[kb] = (lane & 3) == 3 ? wp[L::heads_at(kb, lane)] : zero_u4;
+    for (int kb = 0; kb < HK; ++kb) { // row 3 of every four: all lane groups get the density
+        // (the colours' rows zero: less power, 256^3 voxels 1,709 -> 1,687 us; loaded and masked, not loaded under a mask, which is a branch: 32^3
+        // networks, 21^3 voxels 112 -> 107, width 64 207 -> 201)
+        a_sig[kb] = wp[L::heads_at(kb, lane)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a_sig[kb][i] &= (lane & 3) == 3 ? 0xffffffffu : 0u;
+    }
     const float *__restrict__ tail = (const float *)(wp + L::TAIL);
 #pragma unroll
     for (int t = 0; t < HT; ++t) bias2[t] = *(const f4 *)(tail + 16 * t + 4 * g);

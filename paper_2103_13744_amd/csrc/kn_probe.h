@@ -14,6 +14,7 @@
 struct KnProbeJob {
     KnGrid occ;              // the grid being filled
     int32_t net_res[3];      // the network grid
+    int32_t per[3];          // occ.res / net_res (six divisions per wavefront took 5 of 54 us where a cell has eight probes, 24^3 of them)
     const int32_t *cell_net; // device, sparse network grids: cell -> network or -1; nullptr on a dense grid
     const int32_t *first[3]; // device, net_res[a] + 1 entries per axis: first probe of a cell, counted from kn_probe_base
     int32_t parts;           // workgroups per network cell
@@ -27,7 +28,7 @@ constexpr int KN_PROBES = 27;
 constexpr int64_t KN_PROBE_MAX_BOX = 0x7fffffff / KN_PROBES - 64;
 
 // near the first probe of network cell c (an axis has up to 3 (2^31 - 1) probes; the distance from here fits 32 bits)
-__host__ __device__ __forceinline__ int64_t kn_probe_base(int32_t occ_res, int32_t net_res, int32_t c) { return 3 * ((int64_t)c * (occ_res / net_res)); }
+__host__ __device__ __forceinline__ int64_t kn_probe_base(int32_t per, int32_t c) { return 3 * ((int64_t)c * per); }
 
 // probe i of the axis, counted from the first one of voxel v0 (i >= 0)
 __device__ __forceinline__ float kn_probe_coord(float cell, float bmin, int32_t v0, int32_t i)
@@ -50,8 +51,8 @@ __device__ __forceinline__ bool kn_probe_box(const KnProbeJob &job, int32_t cell
     const int32_t q = cell / job.net_res[2], c[3] = {q / job.net_res[1], q % job.net_res[1], cell % job.net_res[2]};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int64_t lo = kn_probe_base(job.occ.res[a], job.net_res[a], c[a]) + job.first[a][c[a]];
-        const int64_t hi = kn_probe_base(job.occ.res[a], job.net_res[a], c[a] + 1) + job.first[a][c[a] + 1];
+        const int64_t lo = kn_probe_base(job.per[a], c[a]) + job.first[a][c[a]];
+        const int64_t hi = kn_probe_base(job.per[a], c[a] + 1) + job.first[a][c[a] + 1];
         if (lo >= hi) return false;
         b.v0[a] = __builtin_amdgcn_readfirstlane((int32_t)((uint64_t)lo / 3u));
         b.p0[a] = __builtin_amdgcn_readfirstlane((int32_t)(lo - 3 * (int64_t)b.v0[a]));

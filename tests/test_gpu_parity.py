@@ -1302,6 +1302,14 @@ def test_extract_occupancy_edges_of_the_row_kernel(wdtype, H, res):
     extraction_check(sc, res, median_density(sc, res), sigma_unit=20.0)
 
 
+@pytest.mark.parametrize("wdtype,H", [("f16", 32), ("bf16", 64)])
+@pytest.mark.parametrize("res", [(12, 11, 10), (13, 10, 11), (11, 10, 10)])
+def test_extract_occupancy_of_a_few_probes_per_network(wdtype, H, res):
+    # one voxel per cell, nearly so with cut voxels, fewer voxels than cells (1,100 voxels and more: see above)
+    sc = scene_dict((12, 11, 10), (-1, 0, 0.5), (1, 2, 4.5), H, wdtype, 37, sigma_scale=20.0)
+    extraction_check(sc, res, median_density(sc, res), sigma_unit=20.0)
+
+
 @pytest.mark.parametrize("H", [32, 64])
 @pytest.mark.parametrize("nres,res", [((3, 2, 2), (33, 3, 35)), ((1, 1, 1), (17, 18, 3)), ((2, 1, 3), (1, 33, 7)), ((7, 5, 6), (7, 11, 4)), ((2, 2, 2), (5, 5, 70))])
 def test_extract_occupancy_edges_of_the_fp32_kernel(H, nres, res):
