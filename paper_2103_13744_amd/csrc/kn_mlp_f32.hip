@@ -395,8 +395,9 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
     k_probe_f32(const float *__restrict__ packed, KnProbeJob job)
 {
     using R = Regs<H>;
-    constexpr int HT = H / 16, HQ = H / 4, ENC = 24, THREADS = F32_WAVES * KN_WAVE;
+    constexpr int HT = H / 16, HQ = H / 4, ENC = 24;
     extern __shared__ f4 s_probe[];
+    const int threads = job.waves * KN_WAVE;
     const int pitch = (job.sub[0] + job.sub[1] + job.sub[2]) | 1; // (odd: the rows' stores below fall on different banks)
     f4 *const tab = s_probe;                                      // [output / 4][row]: the row's part of layer 1; rows of z, y, x
     float *const enc = (float *)(s_probe + HQ * pitch);           // [row][ENC]: sines and cosines of the ten frequencies, coordinate
@@ -430,7 +431,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         const int32_t row_y = num[2], row_x = num[2] + num[1], rows = row_x + num[0];
 
         // ---- encodings of the rows: three accurate evaluations each, at frequencies 0, 4 and 8
-        for (int i = tid; i < 3 * rows; i += THREADS) {
+        for (int i = tid; i < 3 * rows; i += threads) {
             const int restart = i < rows ? 0 : (i < 2 * rows ? 1 : 2), row = i - restart * rows;
             const bool is_z = row < row_y, is_y = !is_z && row < row_x;
             auto axis = [&](auto x, auto y, auto z) { return is_z ? z : (is_y ? y : x); };
@@ -445,7 +446,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
             *(f4 *)(to + 4) = restart == 2 ? (f4){p, 0.0f, 0.0f, 0.0f} : (f4){sn[2], cs[2], sn[3], cs[3]};
         }
         __syncthreads();
-        // ---- the rows' parts of layer 1: thread = (output, every THREADS / H-th row)
+        // ---- the rows' parts of layer 1: thread = (output, every threads / H-th row)
         {
             const int col = tid & (H - 1);
             const float *const w1 = image;
@@ -461,7 +462,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
                 w[20] = weight(12 + a, 48);
                 const float b1 = a == 0 ? weight(15, 48) : 0.0f;
                 const int first = a == 0 ? row_x : (a == 1 ? row_y : 0);
-                for (int row = first + tid / H; row < first + num[a]; row += THREADS / H) {
+                for (int row = first + tid / H; row < first + num[a]; row += threads / H) {
                     const f4 *const e = (const f4 *)(enc + row * ENC);
                     float acc = b1;
 #pragma unroll
@@ -489,7 +490,7 @@ __global__ void __launch_bounds__(F32_WAVES *KN_WAVE) __attribute__((amdgpu_wave
         const float bias_sig = image[image_at<H>(R::BO + 3, 0)];
         const int32_t points = num[0] * num[1] * num[2]; // (at most 48^3: quotients by multiplication are exact)
         const uint32_t by_z = (0x80000000u + (uint32_t)num[2] - 1u) / (uint32_t)num[2], by_y = (0x80000000u + (uint32_t)num[1] - 1u) / (uint32_t)num[1];
-        for (int32_t first = wave * KN_WAVE; first < points; first += THREADS) {
+        for (int32_t first = wave * KN_WAVE; first < points; first += threads) {
             const int32_t p = min(first + lane, points - 1);
             const int32_t pq = (int32_t)__umulhi(2u * (uint32_t)p, by_z), iz = p - pq * num[2];
             const int32_t ix = (int32_t)__umulhi(2u * (uint32_t)pq, by_y), iy = pq - ix * num[1];
@@ -628,9 +629,14 @@ int kn_probe_f32_launch(const kn_scene *sc, hipStream_t st, KnProbeJob job)
     if (parts > 65536) parts = 65536; // (a workgroup goes on to the cell's next part)
     while (sc->cells * parts > 0x7fffffffLL) parts = kn_div_up(parts, 2);
     job.parts = (int32_t)parts;
+    // A wavefront for 64 probes of a part, in the mean.  Four / so, where a cell has one voxel, 27 probes: 32^3 networks 400 -> 143 us, width 64
+    // 1,147 -> 451 (three of four wavefronts held places on the compute units, and the one that worked was on the same SIMD in all workgroups);
+    // 48^3 voxels on 32^3 networks, 91 probes, 416 -> 247, width 64 1,227 -> 735.
+    const int64_t points = KN_PROBES * (int64_t)job.occ.res[0] * job.occ.res[1] * job.occ.res[2] / (sc->cells * parts);
+    job.waves = (int32_t)(points >= F32_WAVES * KN_WAVE ? F32_WAVES : points < KN_WAVE ? 1 : kn_div_up(points, KN_WAVE));
     const int pitch = (job.sub[0] + job.sub[1] + job.sub[2]) | 1;
     const size_t lds = (size_t)pitch * (H * 4 + 24 * 4);
-    const dim3 grid((unsigned)(sc->cells * parts)), block(F32_WAVES * KN_WAVE);
+    const dim3 grid((unsigned)(sc->cells * parts)), block(job.waves * KN_WAVE);
     const float *w = (const float *)sc->packed_w;
     if (H == 32)
         hipLaunchKernelGGL(k_probe_f32<32>, grid, block, lds, st, w, job);

@@ -18,7 +18,7 @@ struct KnProbeJob {
     const int32_t *cell_net; // device, sparse network grids: cell -> network or -1; nullptr on a dense grid
     const int32_t *first[3]; // device, net_res[a] + 1 entries per axis: first probe of a cell, counted from kn_probe_base
     int32_t parts;           // workgroups per network cell
-    int32_t sub[3];          // fp32 kernel: probes per axis that a workgroup takes together, at most
+    int32_t sub[3], waves;   // fp32 kernel: probes per axis that a workgroup takes together, at most; its wavefronts
     float tau;
     uint8_t *occupancy;      // device, occ.res[0]*[1]*[2] bytes, zero before the launch
 };

@@ -1311,6 +1311,21 @@ def test_extract_occupancy_of_a_few_probes_per_network(wdtype, H, res):
 
 
 @pytest.mark.parametrize("H", [32, 64])
+@pytest.mark.parametrize("res", [(12, 11, 10), (13, 10, 11), (11, 10, 10), (15, 15, 14), (17, 15, 13), (18, 17, 15), (19, 18, 19)])
+def test_extract_occupancy_of_a_few_probes_per_network_fp32(H, res):
+    # 22 to 132 probes per network in the mean, workgroups of one to three wavefronts (64 and 67, 93 and 132 probes: around the lines), boxes with more
+    # chunks than wavefronts (voxels that differ: see below)
+    sc = scene_dict((12, 11, 10), (-1, 0, 0.5), (1, 2, 4.5), H, "f32", 37, sigma_scale=20.0)
+    dev, orc = make_pair(sc, threads=True)
+    tau = median_density(sc, res)
+    got = dev.extract_occupancy(res, tau).cpu().numpy()
+    want, _, mg = orc.extract_occupancy(res, tau)
+    close = mg <= 1e-4 * 20.0
+    assert 0.02 < want.mean() < 0.98 and close.sum() <= 2 + 0.01 * close.size
+    np.testing.assert_array_equal(got[~close], want[~close])
+
+
+@pytest.mark.parametrize("H", [32, 64])
 @pytest.mark.parametrize("nres,res", [((3, 2, 2), (33, 3, 35)), ((1, 1, 1), (17, 18, 3)), ((2, 1, 3), (1, 33, 7)), ((7, 5, 6), (7, 11, 4)), ((2, 2, 2), (5, 5, 70))])
 def test_extract_occupancy_edges_of_the_fp32_kernel(H, nres, res):
     # per cell and axis: 1 to 105 probes (up to 48 together: 16 voxels; 51, 52.5, 54, 99, 105 are cut into parts of unequal size), parts
