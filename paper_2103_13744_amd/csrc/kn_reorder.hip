@@ -509,7 +509,9 @@ __global__ void __launch_bounds__(RANK_THREADS)
 // Dynamic LDS: place_lds(per), the networks' starts and per step the tiles in front; per: steps of 64 networks per wavefront.
 // PLACE_AHEAD: steps whose counts are under way together (65,000 points, one after the other / so: 16^3 networks, fp16, 28 / 26 us a call, 24x20x28 55 / 49,
 // 32^3 111 / 96).
-constexpr int PLACE_OWN_TILES = 8, PLACE_AHEAD = 8;
+// PLACE_PART: networks whose tiles a wavefront writes where all of them are one step.  Sixty-four / so, the call: 4^3 networks, 98,305 points 25.6 / 18.8 us, 5x8x5, 112,001
+// 26.8 / 19.7, width 64 29.0 / 22.2 (more than PLACE_OWN_TILES tiles each, written one network after the other, 6 us of k_place's 11).
+constexpr int PLACE_OWN_TILES = 8, PLACE_AHEAD = 8, PLACE_PART = 8;
 constexpr int PLACE_THREADS = 1024, PLACE_WAVES = PLACE_THREADS / KN_WAVE, PLACE_POINTS = 2; // points per thread
 constexpr int place_lds(int per) { return (PLACE_THREADS + PLACE_WAVES) * per * 4; }
 __global__ void __launch_bounds__(PLACE_THREADS)
@@ -571,18 +573,22 @@ __global__ void __launch_bounds__(PLACE_THREADS)
         const int64_t i = i0 + r * PLACE_THREADS;
         if (i < M) perm[start[kr[r].x] + (int32_t)kr[r].y] = (int32_t)i;
     }
-    // tiles: those of step s of wavefront w are written by workgroup (w * per + s) % gridDim.x
-    const int grid = (int)gridDim.x, first_s = ((int)blockIdx.x - wv * per % grid + grid) % grid;
-    for (int s = first_s; s < per; s += grid) { // (uniform)
+    // tiles: those of part u of wavefront w's networks are written by workgroup (w * parts + u) % gridDim.x.  A part is a step of 64 networks, or, with
+    // one step only, PLACE_PART of them
+    const int grid = (int)gridDim.x, lg_part = per == 1 && grid >= KN_WAVE / PLACE_PART ? __builtin_ctz(PLACE_PART) : __builtin_ctz(KN_WAVE);
+    const int parts = per << (__builtin_ctz(KN_WAVE) - lg_part), first_u = ((int)blockIdx.x - wv * parts % grid + grid) % grid;
+    for (int u = first_u; u < parts; u += grid) { // (uniform)
+        const int s = u >> (__builtin_ctz(KN_WAVE) - lg_part);
+        const bool mine = (u << lg_part) - (s << __builtin_ctz(KN_WAVE)) == (lane & -(1 << lg_part));
         const int32_t n = b0 + s * KN_WAVE, c = n <= N ? counts[n] : 0, t = n < N ? tiles_of(c, tile_len) : 0;
         const int32_t inc = kn_wave_inclusive_scan(t), in_front = tiles_before + step_tiles[wv * per + s];
         // a lane writes its own network's tiles, the wavefront together those of a network with many (one network after
         // the other for all 64 took 5 of this kernel's 14 us at 65,537 points)
-        if (t <= PLACE_OWN_TILES) {
+        if (mine && t <= PLACE_OWN_TILES) {
             const int32_t first = n <= N ? start[n] : 0;
             for (int32_t k = 0; k < t; ++k) tiles[in_front + inc - t + k] = KnTile{n, first + k * tile_len, min(tile_len, c - k * tile_len), 0};
         }
-        for (unsigned long long many = __ballot(t > PLACE_OWN_TILES); many; many &= many - 1) { // (uniform)
+        for (unsigned long long many = __ballot(mine && t > PLACE_OWN_TILES); many; many &= many - 1) { // (uniform)
             const int q = (int)__builtin_ctzll(many);
             const int32_t tq = __builtin_amdgcn_readlane(t, q), base = in_front + __builtin_amdgcn_readlane(inc, q) - tq;
             const int32_t nq = n - lane + q, cq = __builtin_amdgcn_readlane(c, q), first = start[nq];
@@ -614,14 +620,14 @@ constexpr int CO_T = 1024;
 // COUNT_FULL_M: shares are a 256th or a 512th of the batch (all compute units, one or two workgroups one after the other, all of one size) up to here, beyond
 // as large as they can be, since short shares have short runs.  Shares of 4,096 / a 256th, 16^3 networks, fp16: 270,001 points 40.9 / 38.8 us, 560,001 51.7 / 49.6, 1.3 M
 // 83 / 74.6; of 8,192 / a 512th: 2.1 M 127 / 114, 2.5 M 131 / 125, 3.2 M 151 / 151; of 8,192 / a 768th: 5 M 230 / 239.
-// COUNT_MIN_M: see kn_order_pays, which is asked first.  (Few networks, where the radix sort is one trip as well: 5x8x5, 270,000 points 50 -> 30 us, 1 M
+// COUNT_MIN_M: ORDER_MAX_M_COUNTED, see kn_order_pays, which is asked first.  (Few networks, where the radix sort is one trip as well: 5x8x5, 270,000 points 50 -> 30 us, 1 M
 // 67 -> 47, 4 M 219 -> 150; 2^3 with nine in ten points in one network, the most LDS atomics on one address, 4 M 279 -> 180.)
 // COUNT_BACK_M: 16-bit scenes from here on, and all with eight rows: results go through k_results_back.  Width 32, fp16 / width 64, bf16,
 // 16^3 networks, before / with it: 270,001 points 40.9 / 43.2, 55.9 / 58.7 us, 400,001 47.5 / 46.8, 59.6 / 61.0, 560,001 51.6 / 51.6, 67.2 / 67.3 (skewed, width 32, 46.6 / 44.1;
 // 5x8x5 38.8 / 37.6), 1 M 72.7 / 69.9, 89.5 / 86.3; fp32, whose evaluation the scattered stores don't hold up, 1.3 M 186 / 190.
 constexpr int64_t COUNT_BACK_M = 1 << 19;
 constexpr int32_t COUNT_MAX_N = 6143;
-constexpr int64_t COUNT_MIN_M = 3 << 15, COUNT_WIDE_M = 1 << 20, COUNT_FULL_M = 1 << 22;
+constexpr int64_t COUNT_MIN_M = 5 << 15, COUNT_WIDE_M = 1 << 20, COUNT_FULL_M = 1 << 22;
 typedef uint16_t h4_t __attribute__((ext_vector_type(4)));
 
 // Non-temporal: what a workgroup reads once stays out of the way of the lines that the workgroups of an XCD fill and read together in its L2.  4 M points,
@@ -1124,8 +1130,8 @@ int64_t order_ws_bytes(int64_t M, int32_t N, bool stable)
 // Every workgroup of k_place scans the counts of all networks, in steps of 1,024, and keeps their starts in LDS.
 constexpr int32_t ORDER_MAX_N = 32768;
 static_assert(place_lds((ORDER_MAX_N + PLACE_THREADS) / PLACE_THREADS) <= 150 * 1024, "the starts of the networks (k_place) fit the LDS of a compute unit");
-constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_COUNTED = 5 << 15, ORDER_MAX_M_FEW = 3 << 15;
-constexpr int32_t ORDER_FEW = 512, ORDER_STABLE_MAX_N = 24575;
+constexpr int64_t ORDER_MAX_M = 1 << 18, ORDER_MAX_M_COUNTED = 5 << 15, ORDER_MAX_M_FEW = 3 << 16;
+constexpr int32_t ORDER_FEW = PLACE_THREADS - 1, ORDER_STABLE_MAX_N = 24575;
 } // namespace
 
 int64_t kn_order_ws_bytes(int64_t M, int32_t N) { return order_ws_bytes(M, N, false); }
@@ -1138,13 +1144,16 @@ int64_t kn_order_ws_bytes(int64_t M, int32_t N) { return order_ws_bytes(M, N, fa
 // kn_count_run (100,001 / 140,001 / 160,001 / 180,001 / 196,001 points, us): 16^3 networks, fp16, 29 / 31 / 33 / 35 / 38 against 32 / 33 / 34 / 35 / 36,
 // bf16, skewed (nine in ten points in a twentieth of the cells) 29 / 33 / 34 / 37 / 38 against 32 / 33 / 33 / 34 / 34, width 64 40 / 45 / 48 / 49 / 52 against
 // 44 / 45 / 45 / 48 / 49, 10x16x10 22 / 26 / 27 / 29 / 31 against 26 / 28 / 28 / 29 / 29; fp32, whose tiles and not whose order decide, 160,001 / 220,001 / 260,001
-// 51 / 67 / 72 against 53 / 68 / 70; 20^3 (radix passes, 150,001 / 220,001 / 270,001) 47 / 56 / 63 against 75 / 79 / 78.  Few networks, whose table is counted in fewer
-// rows and whose atomics meet (5x8x5, 70,001 / 100,001 / 120,001): 19 / 24 / 28 against 22 / 22 / 24, fp32 29 / 33 / 38 against 33 / 34 / 35.  Many networks, against the radix passes (28,000 / 65,000 / 260,000 points): 24x20x28, fp16, 50 / 56 /
+// 51 / 67 / 72 against 53 / 68 / 70; 20^3 (radix passes, 150,001 / 220,001 / 270,001) 47 / 56 / 63 against 75 / 79 / 78.  Networks of one
+// step of k_place (112,001 / 140,001 / 163,841 / 180,001 / 196,608): 5x8x5, fp16, 20 / 23 / 24 / 26 / 28 against 22 / 24 / 25 / 25 / 26, skewed 19 / 20 / 21 / 22 / 24
+// against 22 / 24 / 25 / 25 / 27; 8^3, bf16, width 64, 22 / 26 / 26 / 27 / 29 against 25 / 29 / 29 / 30 / 31, skewed 23 / 24 / 25 / 27 / 28 against 27 / 28 / 29 / 30 / 30; 10^3, fp16, at
+// 163,841 and beyond 27 / 28 / 30 against 27 / 28 / 29, skewed 25 / 26 / 27 against 27 / 28 / 28; fp32, 8^3, 98,305 / 131,072 / 200,001 / 262,144, 30 / 40 / 47 / 62 against
+// 34 / 44 / 50 / 64.  Many networks, against the radix passes (28,000 / 65,000 / 260,000 points): 24x20x28, fp16, 50 / 56 /
 // 78 against 80 / 83 / 91, skewed 35 / 42 / 76 against 65 / 71 / 89, fp32 94 / 108 / 131 against 119 / 132 / 149; 32^3, fp16, 83 / 110 / 144 against
 // 99 / 123 / 152, skewed 57 / 64 / 110 against 72 / 79 / 110, bf16, width 64, 160 / 219 / 308 against 171 / 231 / 317.
 bool kn_order_pays(const kn_scene *sc, int64_t M)
 {
-    const int64_t line = sc->N <= ORDER_FEW ? ORDER_MAX_M_FEW : sc->desc.wdtype == KN_F32 ? ORDER_MAX_M : ORDER_MAX_M_COUNTED;
+    const int64_t line = sc->desc.wdtype == KN_F32 ? ORDER_MAX_M : sc->N <= ORDER_FEW ? ORDER_MAX_M_FEW : ORDER_MAX_M_COUNTED;
     return sc->N <= ORDER_MAX_N && (M <= line || (M <= ORDER_MAX_M && !kn_count_pays(M, sc->N)));
 }
 

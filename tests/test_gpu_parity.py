@@ -2013,8 +2013,19 @@ def test_eval_grouped_whose_results_come_back_through_lds(wdtype, H, res, M, spr
                                             ("f16", 32, (16, 16, 16), 1 << 22), ("bf16", 32, (5, 8, 5), (1 << 22) + 3)])
 @pytest.mark.parametrize("spread", ["all over", "one network", "none"])
 def test_eval_grouped_on_both_sides_of_the_lines_of_counting(wdtype, H, res, M, spread):
-    """Where samples are moved instead of indices (98,304 points for up to 512 networks, 163,840 for more), where a workgroup's share of the batch
+    """Where samples are moved instead of indices (see the next test; and 98,304 points), where a workgroup's share of the batch
     changes its form (2^20, 2^21, 2^22), shares that end with one to three points, 5,819 to 6,137 networks, one network with all points."""
+    test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
+
+
+@pytest.mark.parametrize("wdtype,H,res,M", [("f16", 32, (8, 8, 8), 14336), ("f16", 32, (8, 8, 8), 14337), ("bf16", 64, (4, 4, 4), 98305), ("f16", 32, (7, 9, 1), 65537),
+                                            ("f32", 32, (13, 5, 1), 98305), ("f16", 32, (11, 31, 3), 3 << 16), ("bf16", 32, (11, 31, 3), (3 << 16) + 1),
+                                            ("bf16", 64, (16, 16, 4), 5 << 15), ("f16", 32, (16, 16, 4), (5 << 15) + 1), ("f32", 32, (11, 31, 3), 1 << 18),
+                                            ("f32", 64, (5, 8, 5), (1 << 18) + 1)])
+@pytest.mark.parametrize("spread", ["all over", "one network", "none"])
+def test_eval_grouped_of_points_ordered_among_few_networks(wdtype, H, res, M, spread):
+    """Seven and eight workgroups, among which the writing of tiles is split in two ways; 63 to 65 networks of more tiles than a lane writes for itself; up to
+    1,023 networks and 1,024 on both sides of where samples are moved instead of indices (196,608 and 163,840 points, in fp32 262,144)."""
     test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
 
 
