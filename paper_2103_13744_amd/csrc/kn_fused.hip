@@ -28,6 +28,12 @@ template <int H, bool BF, bool WRAP> struct Net16 {
     // A round's march ends when fewer than half of the pool's rays have this little of their slots filled: at width 32 a second step
     // for the rest of a ray's slots is mostly thrown away; at width 64, where a visit of a network costs more, it pays.
     static constexpr int NEED_QUARTERS = H == 32 ? 2 : 4;
+    // Issue priorities of a wavefront's phases.  At equal ones the four wavefronts of a SIMD drift into the same phase, and all wait for
+    // their look-ups or all want the vector ALU; like this one that evaluates gets through, and the others' look-ups are under way meanwhile.
+    // Equal / 2, 1, 0 for evaluation, blend and hand-out, march, us per frame: 800x800 161.7 / 153.0, 767x577 stratified 154.9 / 147.9, 695x518
+    // 164.7 / 154.9, sparse 800x800 189.2 / 186.4, 146x106 42.8 / 40.6; width 64 (two wavefronts) no change.  1, 0, 0 and 3, 0, 0
+    // are within 0.3 % of it, a higher priority outside the evaluation (0, 1, 1) changes nothing.
+    static constexpr int PRIO_EVALUATE = 2, PRIO_BETWEEN = 1, PRIO_MARCH = 0;
 
     static __device__ __forceinline__ void place_direction(const float (&d)[3], u4 *to) // gamma(d) in operand order
     {

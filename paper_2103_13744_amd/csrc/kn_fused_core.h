@@ -37,13 +37,6 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 
-// Issue priorities of a wavefront's phases.  At equal ones the four wavefronts of a SIMD drift into the same phase, and all wait for
-// their look-ups or all want the vector ALU; like this one that evaluates gets through, and the others' look-ups are under way meanwhile.
-// Equal / 2, 1, 0 for evaluation, blend and hand-out, march, us per frame: 800x800 161.7 / 153.0, 767x577 stratified 154.9 / 147.9, 695x518
-// 164.7 / 154.9, sparse 800x800 189.2 / 186.4, 146x106 42.8 / 40.6; width 64 (two wavefronts) and fp32 no change.  1, 0, 0 and 3, 0, 0
-// are within 0.3 % of it, a higher priority outside the evaluation (0, 1, 1) changes nothing.
-constexpr int PRIO_EVALUATE = 2, PRIO_BETWEEN = 1, PRIO_MARCH = 0;
-
 enum { BUSY = 0, IDLE, CLAIMED, GIVEN }; // states of a wavefront while the last rays of a workgroup are shared out
 
 // Rays beyond the first pools.  Width 32: they are handed to a workgroup in chunks, its wavefronts take from those what they have places
@@ -420,7 +413,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
             wave_sync();
 
             keep_denormals<Net>(true);
-            __builtin_amdgcn_s_setprio(PRIO_MARCH);
+            __builtin_amdgcn_s_setprio(Net::PRIO_MARCH);
             // ---- march: up to S kept samples per ray.  A step tests G * STEPS consecutive lattice points, STEPS per lane,
             // with all look-ups of the step in flight together; the skip field is asked at each lane's last point only.
             // What the loop reads of the arguments is copied out in front of it (scalar registers): a scalar load inside costs
@@ -536,7 +529,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
         }
         wave_sync();
 
-        __builtin_amdgcn_s_setprio(PRIO_EVALUATE);
+        __builtin_amdgcn_s_setprio(Net::PRIO_EVALUATE);
         // ---- evaluate: one network after the other
         keep_denormals<Net>(false);
         {
@@ -590,7 +583,7 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
         }
         wave_sync();
 
-        __builtin_amdgcn_s_setprio(PRIO_BETWEEN);
+        __builtin_amdgcn_s_setprio(Net::PRIO_BETWEEN);
         // ---- blend (Eq. 2-4): the sequential recurrence, the same in all lanes of a ray's group
         keep_denormals<Net>(true);
         {

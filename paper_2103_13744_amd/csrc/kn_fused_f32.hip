@@ -18,6 +18,10 @@ template <int H> struct Net32 {
     static constexpr bool LARGE_POOLS_LATE = false, CHUNKS = false;
     static constexpr int64_t LONG_ROUNDS_BELOW = 0;
     static constexpr int NEED_QUARTERS = 4;
+    // Issue priorities (eval_chunk itself sets 0 and 1 for encoding and matrix products): what is not matrix products first, so that they are always in
+    // flight.  42 frames of 280x280 to 1842x1378, geometric mean against no priorities outside the evaluation: so 0.997, the 16-bit networks' order
+    // (2 and 3 for the evaluation, 1, 0) 1.004, with the evaluation's 0 and 1 in it 1.001; 885x661 on 2^3 networks 504 / 502 / 511 / 506 us.
+    static constexpr int PRIO_EVALUATE = 0, PRIO_BETWEEN = 2, PRIO_MARCH = 2;
 
     static __device__ __forceinline__ void place_direction(const float (&)[3], u4 *) {}
 
