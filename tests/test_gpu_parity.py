@@ -1342,6 +1342,24 @@ def test_extract_occupancy_edges_of_the_fp32_kernel(H, nres, res):
     np.testing.assert_array_equal(got[~close], want[~close])
 
 
+@pytest.mark.parametrize("H", [32, 64])
+def test_extract_occupancy_in_fp32_of_more_parts_than_workgroups(H):
+    # 3,300,009 probes in a row, up to 48 to a part: 68,751 parts for 65,536 workgroups, the first 3,215 of which go on to a second part.  Looked at: voxels all over and more
+    # of the second parts', those on both sides of part 65,536 and the last ones.  (2 + 1 % of the voxels may come out either way: see above)
+    n = 1100003
+    sc = scene_dict((1, 1, 1), (-1, -1, -1), (1, 1, 1), H, "f32", 36, sigma_scale=20.0)
+    dev, orc = make_pair(sc, threads=True)
+    tau = median_density(sc, (1, 1, n))
+    got = dev.extract_occupancy((1, 1, n), tau).cpu().numpy().reshape(-1)
+    around = 65536 * 48 // 3
+    pick = np.unique(np.concatenate([np.arange(0, n, 997), np.arange(around, n, 97), np.arange(around - 200, around + 200), np.arange(n - 200, n)])).astype(np.int64)
+    want, _, mg = orc.extract_occupancy((1, 1, n), tau, voxels=pick)
+    close = mg <= 1e-4 * 20.0
+    assert 0.02 < want.mean() < 0.98 and close.sum() <= 2 + 0.01 * close.size
+    np.testing.assert_array_equal(got[pick][~close], want[~close])
+    assert 0.02 < want[pick >= around].mean() < 0.98
+
+
 def test_extract_occupancy_threshold_cases_and_single_network():
     import torch
     sc = scene_dict((1, 1, 1), (0, 0, 0), (1, 1, 1), 32, "f16", 33, sigma_scale=20.0)
