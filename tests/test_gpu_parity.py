@@ -1780,27 +1780,57 @@ def test_render_in_one_kernel_hands_every_ray_out(wdtype, H, rays):
 
 
 @pytest.mark.parametrize("rays", [32768, 32769, 40961])
-@pytest.mark.parametrize("kind", ["long", "short", "both"])
-def test_render_in_one_kernel_of_short_and_long_rays(kind, rays):
+@pytest.mark.parametrize("kind,alike", [("long", 16), ("short", 16), ("both", 16), ("both", 32), ("both", 1)])
+def test_render_in_one_kernel_of_short_and_long_rays(kind, alike, rays):
     """Rays along the content's diagonal, across one of its edges, and both in turn, some of them dead: the short ones are listed last,
-    whatever their number, around whole workgroups of the listing kernel (8,192 rays)."""
+    whatever their number, around whole workgroups of the listing kernel (8,192 rays).  Groups of equal rays, whose runs of equal buckets are
+    four rays and more on average, keep the caller's order otherwise; rays that are all different (alike = 1) are ordered by their buckets, the short ones among them."""
     import torch
-    log("fused render, short and long rays", kind, rays)
+    log("fused render, short and long rays", kind, alike, rays)
     occ = np.zeros((64, 64, 64), np.uint8)
     occ[8:56, 8:56, 8:56] = 1
     dev, _ = make_pair(scene_dict((8, 8, 8), (-1, -1, -1), (1, 1, 1), 32, "f16", 13, occ=occ, sigma_scale=20.0))
     g = torch.Generator().manual_seed(rays)
-    to_long = torch.rand((rays, 3), generator=g) * 0.2 - 0.1
+    group = torch.arange(rays) // alike
+    to_long = (torch.rand((rays, 3), generator=g) * 0.2 - 0.1)[group]
     edge = torch.tensor([0.7, -0.7, 0.0]) * (1.0 - 0.05 * torch.rand((rays, 1), generator=g)) + torch.tensor([0.0, 0.0, 0.4]) * torch.rand((rays, 1), generator=g)
-    is_long = {"long": torch.ones(rays, dtype=torch.bool), "short": torch.zeros(rays, dtype=torch.bool), "both": torch.arange(rays) % 5 < 2}[kind]
+    edge = edge[group]
+    is_long = {"long": torch.ones(rays, dtype=torch.bool), "short": torch.zeros(rays, dtype=torch.bool), "both": group % 5 < 2}[kind]
     d = torch.where(is_long[:, None], torch.tensor([[1.0, 1.0, 1.0]]), torch.tensor([[1.0, 1.0, 0.0]])) / 3.0 ** 0.5
     o = torch.where(is_long[:, None], to_long, edge) - 3.0 * d
-    d[torch.arange(rays) % 7 == 3] *= -1.0 # away from the scene
+    dead = group % 7 == 3
+    d[dead] *= -1.0 # away from the scene
+    if alike > 1: # (groups divide a wavefront's 64 rays: none is cut into two runs)
+        assert (~dead).sum() >= 4 * len(group[~dead].unique())
     args = (o.cuda(), d.cuda(), 1.0, 4.0 / 128, 128, 0.01, (0.2, 0.4, 0.9))
     waves, st = dev.render(*args, want_stats=True)
     assert st["samples_blended"] > rays
+    for _ in range(2): # (into a buffer that holds no picture: a ray that is left out shows)
+        assert torch.equal(dev.render(*args, out=torch.full_like(waves, -7.0)), waves)
+
+
+@pytest.mark.parametrize("wdtype,width,height,eps,seed", [("f16", 400, 300, 0.01, None), ("bf16", 403, 301, 0.0, 5), ("f16", 800, 801, 0.01, 7),
+                                                          ("bf16", 767, 577, 0.01, None)])
+def test_render_in_one_kernel_of_an_image(wdtype, width, height, eps, seed):
+    """Pixels row by row, whose rays stay in a bucket for many pixels (a 32nd of the box is ten of them and more): listed in the caller's order with the short rays
+    last.  All pixels: the wave loop's bits."""
+    import torch
+    import paper_2103_13744_amd as kn
+    log("fused render, image", wdtype, width, height, eps, seed)
+    cfg = configs.config3(width, height, wdtype=wdtype)
+    dev, _ = make_pair(cfg["scene"])
+    args = (cuda(cfg["rays_o"]), cuda(cfg["rays_d"]), cfg["t_near"], cfg["step"], cfg["K"], eps, (0.2, 0.4, 0.9))
+    waves, st = dev.render(*args, want_stats=True, seed=seed)
+    assert st["samples_blended"] > width * height
     for _ in range(2):
-        assert torch.equal(dev.render(*args), waves)
+        assert torch.equal(dev.render(*args, out=torch.full_like(waves, -7.0), seed=seed), waves)
+    kn.profile_enable(1)
+    try:
+        kn.profile_read()
+        assert torch.equal(dev.render(*args, out=torch.full_like(waves, -7.0), seed=seed), waves)
+        assert kn.profile_read()["ms_march"] == 0.0
+    finally:
+        kn.profile_enable(0)
 
 
 @pytest.mark.parametrize("wdtype,H,res,occ_res,keep,box,eps", [
