@@ -594,11 +594,13 @@ __global__ void __launch_bounds__(Net::MAX_WAVES *KN_WAVE)
             if (ray >= 0) {
                 // Four samples per step, requested together: one at a time the recurrence waits for the LDS at each of them (82x49 rays
                 // 60.8 -> 54.9 us, 200x151 45.8 -> 44.6, 800x800 163.4 -> 162.0).
+                // What is requested beyond a ray's samples lies among its slots: a round has S_max of them, a multiple of BLEND.
+                static_assert((Net::SLOTS >> Net::MAX_LG) % BLEND == 0 && Net::MAX_S % BLEND == 0, "S_max is a multiple of BLEND");
                 bool goes = cnt > 0;
                 for (int j = 0; goes; j += BLEND) {
                     f4 q[BLEND];
 #pragma unroll
-                    for (int c = 0; c < BLEND; ++c) q[c] = slots[((j + c) << lgP) + slot]; // (S_max is a multiple of BLEND)
+                    for (int c = 0; c < BLEND; ++c) q[c] = slots[((j + c) << lgP) + slot];
                     asm volatile("" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3])); // (one wait for the four)
 #pragma unroll
                     for (int c = 0; c < BLEND; ++c) {
