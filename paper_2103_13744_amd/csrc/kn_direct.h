@@ -16,9 +16,6 @@ struct KnDirectJob {
     float *sigma, *rgb;
 };
 
-int64_t kn_mlp_packed_bytes(int32_t H, int64_t N);
-int64_t kn_mlp_f32_packed_bytes(int32_t H, int64_t N);
-
 // -1: the batch is better ordered by network first; else KnDirectJob::lg_points
 int kn_direct_lg_points(const kn_scene *sc, int64_t M);
 int kn_direct_launch(const kn_scene *sc, hipStream_t st, const KnDirectJob &job, hipEvent_t ev_start, hipEvent_t ev_stop);

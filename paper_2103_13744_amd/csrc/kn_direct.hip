@@ -113,15 +113,14 @@ __global__ void __launch_bounds__(DIRECT_WAVES *KN_WAVE) __attribute__((amdgpu_w
 } // namespace
 
 // A batch goes unordered when its weight traffic takes less time than ordering does.  The traffic is at most one fetch per
-// point, or per wavefront and network where there are few networks; it was seen at 7 to 8 TB/s, and at 18 where the weights
-// of all networks fit the 4 MB of an XCD's L2.
+// point, or per wavefront and network where there are few networks; what a fetch takes when all wavefronts fetch is in `ns` (40,000 points all over 16^3
+// networks: 1.53 in 16 bits, 4.3 at width 64, fp32 3.8 and 11.9), and less than half of it where the weights of all networks fit the 4 MB of an XCD's L2.
 // What ordering takes grows with the networks, whose counts every one of its workgroups looks at, and few points of a batch that is all over the grid
 // meet.  Near the lines, direct / ordered, points all over the grid (in brackets: nine in ten in a twentieth of the cells), us: 5x8x5
-// networks, fp32, 3,000 points 14 / 19, 6,000 (not taken) 24 / 20; 16^3, fp16, 12,000 22 / 25, 16,000 28 / 26 (12 / 20), 24,000 41 / 26 (16 / 19), 28,000
-// (not) 48 / 26 (20 / 20); 10x16x10, bf16, width 64, 6,000 28 / 23 (19 / 21), 9,000 (not) 47 / 23 (33 / 22), fp32 6,000 (not) 31 / 22; 24x20x28, fp16,
-// 24,000 43 / 49 (30 / 33), 34,000 (not) 69 / 53 (48 / 36), fp32 9,000 57 / 59; 32^3, fp16, 28,000 52 / 83 (46 / 57), 40,000 (not) 75 / 91 (67 / 59),
-// bf16, width 64, 16,000 77 / 122, fp32 16,000 77 / 119.  (16-bit images were a twelfth and a sixteenth larger then; smaller, with the heads in one block: 5,003 points
-// direct 10.8 -> 9.6, width 64 25.9 -> 23.3, 20,011 34.6 -> 31.2; fp32 29.5 -> 23.1.)
+// networks, fp32, 3,000 points 11 / 19, 6,000 (not taken) 20 / 19; 16^3, fp16, 12,000 20 / 22, 16,000 25 / 22 (12 / 19), 24,000 37 / 22 (16 / 19), 28,000
+// (not) 43 / 22 (19 / 19); 10x16x10, bf16, width 64, 6,000 24 / 21 (13 / 19), 8,000 (not) 32 / 21 (13 / 19), fp32 6,000 (not) 23 / 19 (20 / 25); 24x20x28, fp16,
+// 24,000 40 / 40 (26 / 24), 34,000 (not) 61 / 42 (40 / 27), fp32 8,000 30 / 40 (25 / 26); 32^3, fp16, 28,000 48 / 60 (42 / 38), 40,000 (not) 67 / 70 (56 / 39),
+// bf16, width 64, 16,000 68 / 94 (62 / 43), fp32 16,000 54 / 70 (50 / 41).
 int kn_direct_lg_points(const kn_scene *sc, int64_t M)
 {
     const int H = sc->desc.hidden;
@@ -129,10 +128,10 @@ int kn_direct_lg_points(const kn_scene *sc, int64_t M)
     const int64_t resident = 1024 * (f32 ? (H == 32 ? 2 : 1) : (H == 32 ? 4 : 2)); // wavefronts
     int lg = 0;
     while (lg < 6 && (resident << lg) < M) ++lg;
-    const double all = (double)(f32 ? kn_mlp_f32_packed_bytes(H, sc->N) : kn_mlp_packed_bytes(H, sc->N));
     const double shares = (double)kn_div_up(M, 1ll << lg), networks = (double)(sc->N < (1 << lg) ? sc->N : 1 << lg);
     const double fetches = fmin((double)M, shares * networks);
-    const double us = fetches * (all / sc->N) / ((all <= 3e6 ? 18e6 : 8e6) * (f32 ? (H == 32 ? 0.723 : 0.798) : (H == 32 ? 1.0 : 0.895))); // (what fetches wait for is not their bytes alone: images that got smaller)
+    const int near = f32 ? (H == 32 ? 109 : 37) : (H == 32 ? 241 : 101); // networks whose images, 2.7 to 3.0 MB, stay in the L2
+    const double ns = f32 ? (H == 32 ? 4.74 : 12.4) : (H == 32 ? 1.55 : 4.13), us = 1e-3 * fetches * (sc->N <= near ? ns / 2.25 : ns);
     const bool heavy = f32 || H == 64;
     const double limit = sc->N <= 255 ? 24.0 : sc->N <= 8191 ? (heavy ? 26.0 : 40.0) : sc->N <= 16383 ? 45.0 : (heavy ? 80.0 : 50.0);
     return us <= limit ? lg : -1;
