@@ -37,10 +37,8 @@ template <int H> struct Lay {
     static constexpr int LO = NBLK * 64;
     static constexpr int TAIL = LO + HEADS * HK;
     static constexpr int TAIL_FLOATS = H + 4;             // b2[H], b5[3], b3 density
-    // (Width 32: 1 KB behind the tail is not used.  Images lie as far apart as those of twelve blocks did, so that kn_scene_bytes gives no less than
-    // callers have been told a scene takes; it is never fetched.)
-    static constexpr int HALFS = H == 32 ? 12 * 512 + TAIL_FLOATS * 2 : (TAIL * 8 + TAIL_FLOATS * 2 + 63) & ~63;
-    static_assert(HALFS >= TAIL * 8 + TAIL_FLOATS * 2, "an image holds its blocks, heads and tail");
+    static constexpr int HALFS = H == 32 ? TAIL * 8 + TAIL_FLOATS * 2 : (TAIL * 8 + TAIL_FLOATS * 2 + 63) & ~63;
+    static_assert(HALFS % 8 == 0, "blocks are fetched 16 bytes at a time");
     __device__ static constexpr int heads_at(int kb, int lane) { return LO + HEADS * kb + (H == 32 ? lane : 4 * (lane >> 4) + (lane & 3)); }
     // canonical offsets
     static constexpr int oW1 = 0, ob1 = 63 * H, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H,

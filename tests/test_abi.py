@@ -90,10 +90,19 @@ def test_host_side_argument_validation(lib):
     d.occupancy = 256
     d.occ_res[:] = [64, 64, 64]
     assert lib.kn_scene_bytes(C.byref(d), C.byref(n)) == 0
-    f32_small = n.value
-    assert f32_small >= 8 * 124 * 64 * 4 + 64 ** 3 // 8 + 2 * 16 ** 3      # weight image, occupancy bits, skip field twice
+    grid = 64 ** 3 // 8 + 16 ** 3 * 16 + 2 * 16 ** 3                       # occupancy bits; blocks of 4^3 voxels, their skip field twice
+    rounding = 6 * 256                                                  # five buffers on multiples of 256 bytes, the 16-bit networks' status word
+
+    def takes(images):
+        return lib.kn_scene_bytes(C.byref(d), C.byref(n)) == 0 and images + grid <= n.value < images + grid + rounding
+
+    assert takes(8 * 4 * (104 * 64 + 44 * 4 + 16))      # fp32, width 32: 104 registers of 64 lanes, 44 of four lane groups, to a line
+    d.hidden = 64
+    assert takes(8 * 4 * (304 * 64 + 84 * 4 + 16))
     d.wdtype, d.res[:] = 1, [16, 16, 16]
-    assert lib.kn_scene_bytes(C.byref(d), C.byref(n)) == 0 and n.value >= 4096 * (12 * 1024 + 36 * 4)
+    assert takes(4096 * (28 * 1024 + 2 * 256 + 68 * 4 + 112))           # 16 bit, width 64: blocks, heads, tail, to a line
+    d.hidden = 32
+    assert takes(4096 * (10 * 1024 + 1024 + 36 * 4))                    # width 32: blocks, heads, tail
     out = C.c_int64()
     assert lib.kn_create(None, 0) == -1
     assert lib.kn_destroy(None) == 0
