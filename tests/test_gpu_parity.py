@@ -349,8 +349,8 @@ def test_eval_grouped_without_aux_equals_the_ordered_batch(wdtype, H, res, M):
 @pytest.mark.parametrize("wdtype,H,res,M", [
     ("f16", 32, (10, 16, 10), 65537), ("f32", 32, (16, 16, 16), 131071),                    # indices ordered by counting
     ("f16", 32, (16, 16, 16), 131073), ("f32", 32, (16, 16, 16), 160000), ("bf16", 64, (4, 8, 8), 300001),
-    ("f16", 32, (1, 1, 1), 147457), ("f16", 32, (16, 16, 16), 147456), ("f16", 32, (16, 16, 16), 147457), ("f32", 64, (5, 8, 5), 131073), ("bf16", 32, (2, 2, 2), 1400001),  # samples moved, 512 threads
-    ("f16", 32, (16, 16, 16), 5 << 18), ("bf16", 32, (17, 19, 19), (5 << 18) + 1), ("f16", 64, (16, 16, 16), 2100003)])  # 1,024
+    ("f16", 32, (1, 1, 1), 147457), ("f16", 32, (16, 16, 16), 147456), ("f16", 32, (16, 16, 16), 147457), ("f32", 64, (5, 8, 5), 131073), ("bf16", 32, (2, 2, 2), 1400001),  # one network: unordered; samples moved from 196,609 points on, in fp32 262,145
+    ("f16", 32, (16, 16, 16), 5 << 18), ("bf16", 32, (17, 19, 19), (5 << 18) + 1), ("f16", 64, (16, 16, 16), 2100003)])  # eight points per thread
 @pytest.mark.parametrize("spread", ["all over", "one network", "none"])
 def test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread):
     """Batches ordered by counting: results, ids and counts are those of the call that reports the permutation."""
@@ -2042,15 +2042,17 @@ def test_render_takes_the_faster_way_to_the_same_picture(wdtype, H, res, occ_res
                                             ("f16", 32, (20, 20, 20), 1 << 18), ("f16", 32, (20, 20, 20), (1 << 18) + 1)])
 @pytest.mark.parametrize("spread", ["all over", "one network", "none"])
 def test_eval_grouped_around_the_largest_batches_of_ordered_indices(wdtype, H, res, M, spread):
-    """Up to 2^17 points for 512 networks, 2^18 for more; beyond, samples are moved by counting, or with 6,144 networks and more by passes."""
+    """2^18 points, the largest such batch in fp32 and, in 16 bit, with 6,144 networks and more, which the radix passes take beyond; 2^17 points."""
     test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
 
 
 @pytest.mark.parametrize("wdtype,H,res,M", [("bf16", 32, (16, 16, 16), (5 << 17) - 1), ("f16", 32, (16, 16, 16), 5 << 17), ("bf16", 64, (10, 16, 10), (5 << 17) + 1),
-                                            ("f32", 32, (10, 16, 10), 5 << 17), ("f16", 64, (18, 18, 18), 1300003)])
+                                            ("f32", 32, (10, 16, 10), 5 << 17), ("f16", 64, (18, 18, 18), 1300003),
+                                            ("f16", 32, (16, 16, 16), (1 << 19) - 1), ("f16", 32, (16, 16, 16), 1 << 19), ("bf16", 64, (16, 16, 16), (1 << 19) - 1),
+                                            ("bf16", 64, (16, 16, 16), 1 << 19)])
 @pytest.mark.parametrize("spread", ["all over", "one network", "none"])
 def test_eval_grouped_whose_results_come_back_through_lds(wdtype, H, res, M, spread):
-    """16-bit scenes from 655,360 points on, workgroups of 512 threads."""
+    """16-bit scenes from 2^19 points on (2^19 - 1: the last whose results the evaluation scatters), fp32 from 2^20 on."""
     test_eval_grouped_of_large_batches_without_permutation(wdtype, H, res, M, spread)
 
 
