@@ -7,8 +7,8 @@
 // for the next round; free places are filled with the next rays of the live list.  Samples, results and encoded
 // directions never leave the LDS, a frame needs no slot buffers, no histogram and no host decision in the middle, and a
 // ray stops within S samples of its termination point.  Against the wave loop (march, group, evaluate and blend kernels
-// per wave, the host waiting for a count): 30,000 rays, width 32 (200x151) 141 -> 52 us; 800x800 230 -> 164; 1080p,
-// width 64, 1430 -> 1025.  Frames of up to 32,767 rays are this kernel alone: a workgroup also clips its rays and walks them to their
+// per wave, the host waiting for a count), two views each: 30,000 rays, width 32 (200x151) 115, 133 -> 41, 46 us; 800x800 215, 225 -> 135, 158; 1080p,
+// width 64, 1623, 1583 -> 1040, 920.  Frames of up to 32,767 rays are this kernel alone: a workgroup also clips its rays and walks them to their
 // first lattice point near content (200x151: 67 us with two launches in front of it).
 //
 // What bounds it: vector-ALU issue while there is work (a march step of 256 points takes about 300 instructions, a tile of 16
@@ -16,7 +16,8 @@
 // (most end within two rounds, some take ten) and neighbours cost alike, so behind a list a workgroup is all of a compute unit's wavefronts, whose
 // first pools lie in as many parts of the list, and who share their last rays through the LDS: workgroups of four
 // wavefronts, all places in a list filled by an atomic per wavefront and round, 203 us at 800x800 (call, with the set-up's 31), 181
-// at 767x577 stratified, 1,093 at 1080p, width 64; like this 164, 148 and 1,038.  Tried and slower: contiguous pieces of the list
+// at 767x577 stratified, 1,093 at 1080p, width 64; like this 164, 148 and 1,038 (145, 136 and 920 since the march's look-ups are under way together).
+// Tried and slower, before that: contiguous pieces of the list
 // larger than what a wavefront has places for (800x800 +3, 1080p +60: the last pieces decide), hand-out counters per XCD (+3, +20),
 // half of the list handed out beforehand (+6, +190), 12 wavefronts per compute unit (+3).
 //

@@ -1254,20 +1254,19 @@ extern "C" int kn_composite_deltas(void *stream, const float *sigma, const float
 
 // Where the fused kernel is the faster one.  It evaluates a wavefront's samples network by network and loads the network's weights
 // for each, so it needs several samples of a ray per network: the lattice points in a cell's edge say how many there are.
-// Its time over the wave loop's on 580 frames of 1,600 to 3.3 million rays (profiles/frames_one_kernel_against_waves.csv), where it is taken /
-// where it is not:
-//   up to 64 networks, whose weights stay in the caches: 0.25 to 0.97;
-//   content everywhere (no occupancy grid), a new network every few points from the ray's first point on: 16-bit width 32 0.21 to 1.00 / 0.99 to
-//   2.42; width 64 0.39 to 0.87 (1.02 in one of 22; 200 networks, fewer than four points: 0.97 to 1.31 up to 35,098 rays, 0.49 to 0.81 from 141,700 on) /
-//   0.97 to 3.80 (0.58 in one, without termination); fp32 0.64 to 0.87 / 0.98 to 4.17;
-//   up to 8,192 rays: 0.29 to 0.86 (1.01 in one of 55 frames);
-//   16-bit width 32: dense 0.32 to 0.89; sparse grids, where a ray has fewer samples of a network: 0.43 to 0.95 / 0.93 to 1.29;
-//   width 64, whose weights are three times as many bytes: 0.38 to 1.02 / 0.88 to 1.32, sparse 0.51 (one) / 0.88 to 1.66;
-//   fp32 (width 32): 0.55 to 1.22 (above 1 in 6 of 57, mean 0.81) / 0.81 to 1.83; of these with four to eight points in a cell: 0.57 to 1.06 up to
-//   32,768 rays, 0.81 to 1.35 beyond, 0.77 to 0.86 from 2^19 on; sparse 0.64 to 1.02 / 0.96 to 2.38;
-//   without early termination, where every sample is evaluated anyway and the wave loop's tiles are full: 16-bit width 32 0.34 to 1.06 (above
-//   1 in 3 of 48) / 1.01, sparse 0.48 to 0.90 / 0.76 to 1.31; width 64 up to 32,768 rays 0.41 to 1.18 (above 1 in 2 of 14, mean 0.66), beyond with
-//   512 networks 0.66 to 1.06 (mean of 8 frames 0.85), with more 0.82 to 1.83, sparse 1.52 to 2.85; fp32 0.77 (one of 13) to 1.87, sparse 1.47 to 2.60.
+// The lines were drawn on 580 frames when the march's look-ups still went out one by one, and the one kernel has become 10 to 20 % faster since.  Its time over the
+// wave loop's now, on 580 others of 1,600 to 3.6 million rays (profiles/frames_one_kernel_against_waves.csv), where it is taken / where it is not:
+//   up to 64 networks, whose weights stay in the caches: 0.33 to 0.82 (fp32 without termination 1.18 in one of 29);
+//   content everywhere (no occupancy grid), a new network every few points from the ray's first point on: 16-bit width 32 0.39 to 0.75 / 0.56 to
+//   1.96; width 64 0.31 to 0.51 / 0.45 to 3.62; fp32 0.64 to 1.04 / 0.92 to 2.05;
+//   up to 8,192 rays: 0.22 to 1.00 (1.07 in one of 107 frames);
+//   16-bit width 32: dense 0.24 to 0.67; sparse grids, where a ray has fewer samples of a network: 0.25 to 0.75;
+//   width 64, whose weights are nearly three times as many bytes: 0.31 to 0.95 / 0.83 to 1.00, sparse 0.45 (one) / 0.68 to 2.22;
+//   fp32 (width 32): 0.47 to 0.99 / 0.78 to 1.29, sparse 0.67 to 1.01 / 0.77 to 1.41;
+//   without early termination, where every sample is evaluated anyway and the wave loop's tiles are full: 16-bit width 32 0.36 to 0.87 / 0.59 to
+//   0.71 (four), sparse 0.40 to 0.84 / 0.81 and 0.94; width 64 0.42 to 1.34 (above 1 in 3 of 18) / 0.71 to 1.27 (mean of 22 0.98), sparse 0.50 (one) / 1.06 to 1.64;
+//   fp32 0.74 to 1.28 (mean of 21 1.10), sparse 1.36 to 1.61.
+// The kernel taken is more than 5 % behind in 4 of 446, the waves in 44 of 134: of all types, most without termination or with few points in a cell.
 static bool fused_pays(const kn_scene *sc, int64_t R, float step, float term_eps)
 {
     if (sc->N <= 64) return true;
