@@ -891,7 +891,7 @@ extern "C" int kn_extract_occupancy(kn_ctx *ctx, const kn_scene *sc, void *strea
     if (!make_grid(sc->desc.aabb_min, sc->desc.aabb_max, occ_res, job.occ)) return KN_E_INVALID_ARG;
     const int64_t voxels = (int64_t)occ_res[0] * occ_res[1] * occ_res[2];
     if (voxels > 0x7fffffffLL) return KN_E_UNSUPPORTED;
-    // upper bound of the voxels one network cell can own, and the nominal number of tiles per cell
+    // upper bound of the voxels one network cell can own
     int64_t box = 1;
     for (int a = 0; a < 3; ++a) box *= kn_div_up(occ_res[a], sc->desc.res[a]) + 1;
     if (box > KN_PROBE_MAX_BOX) return KN_E_UNSUPPORTED;
