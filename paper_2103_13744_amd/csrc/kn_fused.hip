@@ -10,6 +10,7 @@ template <int H, bool BF, bool WRAP> struct Net16 {
     static constexpr bool FLUSHED = true;
     static constexpr int DIR = 4;
 
+    // (Shapes, pools and rounds were chosen, and the figures of this block measured, when the march's look-ups went out one by one.)
     // Rays and slots per wavefront.  Large pools keep few lanes per ray and cut a ray into many rounds, small ones evaluate more samples
     // behind the termination point; many slots mean many samples per visit of a network, few fit a step of the march (256 points).
     // Rays x slots, 800x800 and 767x577 / 1080p at width 64, us: 32 x 384 183, 167 / 64 x 768 1,211; 16 x 384 173, 163 / 32 x 768 1,100;
